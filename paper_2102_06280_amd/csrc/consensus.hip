@@ -46,28 +46,14 @@ __global__ void phi_step_kernel(int Npad, const int32_t *__restrict__ rowptr, co
     next[(size_t)i * Npad + c] = acc;
 }
 
-// Row-major Phi -> the A-fragment order of the 32x32x2 matrix instruction that the dense mixing
-// kernel reads: [row block of 32][k-step][lane], lane = 32 (column & 1) + (row & 31).  Padding
-// rows [N, Npad) become zero whatever the buffer holds there.  grid = Npad, block = Npad.
+// Row-major Phi -> the order in which the dense mixing kernel reads it: [row block of 32][k pair][lane],
+// lane = 32 (column & 1) + (row & 31).  Padding rows [N, Npad) become zero whatever the buffer holds there.
+// grid = Npad, block = Npad.
 __global__ void phi_fragment_kernel(int N, int Npad, const float *__restrict__ phi, float *__restrict__ frag)
 {
     const int i = blockIdx.x, c = threadIdx.x;
     const int KB = Npad / 2;
     frag[((size_t)(i >> 5) * KB + (c >> 1)) * 64 + (c & 1) * 32 + (i & 31)] = i < N ? phi[(size_t)i * Npad + c] : 0.0f;
-}
-
-// out[i][c] = sum_j Phi[i][j] x[j][c] for the columns [c_begin, d) that the matrix-core kernel
-// leaves out (a ragged tail, or rows that are not 16-byte aligned).  grid = (ceil(cols / 256), N).
-__global__ __launch_bounds__(256) void phi_apply_scalar_kernel(int N, int Npad, int64_t c_begin, int64_t d, int64_t ld,
-                                                               const float *__restrict__ phi,
-                                                               const float *__restrict__ x, float *__restrict__ out)
-{
-    const int i = blockIdx.y;
-    const int64_t c = c_begin + (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (c >= d) return;
-    float acc = 0.f;
-    for (int j = 0; j < N; ++j) acc = fmaf(phi[(size_t)i * Npad + j], x[(int64_t)j * ld + c], acc);
-    out[(int64_t)i * ld + c] = acc;
 }
 
 }  // namespace
@@ -98,14 +84,5 @@ int dbw_launch_consensus_rounds(dbw_ctx *c, const float *x, float *out, const fl
         hipLaunchKernelGGL(phi_fragment_kernel, dim3(Npad), dim3(Npad), 0, s, c->N, Npad, cur, c->phi_frag);
         DBW_HIP(hipGetLastError());
     }
-    const int rc = dbw_launch_mix_dense(c, x, nullptr, out, 0.f, nullptr, s, c->phi_frag);
-    if (rc != DBW_OK) return rc;
-    const int64_t done = dbw_dense_columns(c, x, nullptr, out);
-    if (done < c->d) {
-        dbw_timer tm(c, "phi_apply_scalar_kernel", s);
-        hipLaunchKernelGGL(phi_apply_scalar_kernel, dim3((unsigned)((c->d - done + 255) / 256), c->N), dim3(256), 0, s,
-                           c->N, Npad, done, c->d, c->ld, cur, x, out);
-        DBW_HIP(hipGetLastError());
-    }
-    return DBW_OK;
+    return dbw_launch_mix_dense(c, x, nullptr, out, 0.f, nullptr, s, c->phi_frag);
 }

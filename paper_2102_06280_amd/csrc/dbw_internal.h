@@ -17,7 +17,7 @@
     } while (0)
 
 constexpr int DBW_DENSE_MAX_N = 256;   // the dense mixing kernel keeps all of P(k) in registers
-// the dense mixing kernel adds 32-bit per-lane byte offsets of up to 40 rows to 64-bit uniform bases
+// the dense mixing kernel adds 32-bit per-lane byte offsets of a few rows to 64-bit uniform bases
 constexpr int64_t DBW_DENSE_MAX_LD = (int64_t)UINT32_MAX / (40 * 4);
 constexpr int DBW_SELECT_LDS_KEYS = 2048;
 constexpr int DBW_FUSED_SELECT_MAX_N = 256;   // threshold rule + selection in one workgroup up to this many workers
@@ -108,10 +108,7 @@ struct dbw_lr_vector {
 int dbw_launch_mix_csr(dbw_ctx *c, const float *x, const float *g, float *out, float lr, const float *lr_vec,
                        hipStream_t s);
 // mix_dense.hip
-// Columns [0, dbw_dense_columns) are the ones the matrix-core kernel covers (0 when rows are not
-// 16-byte aligned).  W (A-fragment order, Npad x Npad) defaults to the matrix of the last
-// selection; with a W of the caller's the remaining columns are left to the caller.
-int64_t dbw_dense_columns(const dbw_ctx *c, const float *x, const float *g, const float *out);
+// W (A-fragment order, Npad x Npad) defaults to the matrix of the last selection.
 int dbw_launch_mix_dense(dbw_ctx *c, const float *x, const float *g, float *out, float lr, const float *lr_vec,
                          hipStream_t s, const float *W = nullptr);
 // mix_tiles.hip (tile-major layout)

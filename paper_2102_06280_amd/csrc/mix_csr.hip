@@ -362,17 +362,3 @@ int dbw_launch_mix_csr(dbw_ctx *c, const float *x, const float *g, float *out, f
     if (c->order == DBW_ORDER_ATC) return launch<DBW_ORDER_ATC, true>(c, x, g, out, dbw_lr_scalar{lr}, s);
     return launch<DBW_ORDER_CTA, true>(c, x, g, out, dbw_lr_scalar{lr}, s);
 }
-
-// Scalar evaluation of columns [c_begin, d) only (the ragged tail left by a vector path).
-int dbw_launch_mix_csr_range(dbw_ctx *c, const float *x, const float *g, float *out, float lr, const float *lr_vec,
-                             int64_t c_begin, hipStream_t s)
-{
-    if (g == nullptr) return launch_scalar<DBW_ORDER_CTA, false>(c, x, g, out, dbw_lr_scalar{0.f}, c_begin, s);
-    if (lr_vec) {
-        if (c->order == DBW_ORDER_ATC)
-            return launch_scalar<DBW_ORDER_ATC, true>(c, x, g, out, dbw_lr_vector{lr_vec}, c_begin, s);
-        return launch_scalar<DBW_ORDER_CTA, true>(c, x, g, out, dbw_lr_vector{lr_vec}, c_begin, s);
-    }
-    if (c->order == DBW_ORDER_ATC) return launch_scalar<DBW_ORDER_ATC, true>(c, x, g, out, dbw_lr_scalar{lr}, c_begin, s);
-    return launch_scalar<DBW_ORDER_CTA, true>(c, x, g, out, dbw_lr_scalar{lr}, c_begin, s);
-}

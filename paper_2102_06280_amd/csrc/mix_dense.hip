@@ -4,6 +4,8 @@
 //
 //   CTA: out = P X - lr G            ATC: out = P (X - lr G)
 //
+// More than 32 workers, and rows off 16-byte boundaries, take the kernel of mix_split.h; the one below does the rest.
+//
 // P (N x N, zero-padded to NPAD = 32 * MB) is tiny and lives in registers: each of the 8
 // wavefronts of a workgroup keeps the A-operand fragments of one 32-row block of P for the
 // whole kernel.  The workgroup walks over column tiles of X; a tile (NPAD rows x TC
@@ -24,6 +26,7 @@
 #include <algorithm>
 
 #include "dbw_internal.h"
+#include "mix_split.h"
 
 namespace {
 
@@ -32,20 +35,7 @@ typedef __attribute__((address_space(1))) const void *global_cptr;
 typedef __attribute__((address_space(3))) void *lds_ptr;
 
 constexpr int DENSE_THREADS = 512;
-
-// A wave-uniform address, pinned to scalar registers.  Global loads and stores take a scalar
-// base plus a 32-bit lane offset; without the pin the compiler folds the lane offset into one
-// loop-invariant 64-bit vector address per row, and those dozens of register pairs push the
-// P block out to scratch memory.
-__device__ __forceinline__ const char *uniform_base(const void *p)
-{
-    const uint64_t a = (uint64_t)p;
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a);
-    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
-    uint64_t v = ((uint64_t)hi << 32) | lo;
-    asm volatile("" : "+s"(v));
-    return (const char *)v;
-}
+using mixsplit::uniform_base;
 
 template <int MB>
 struct dense_cfg {
@@ -280,85 +270,88 @@ __global__ __launch_bounds__(DENSE_THREADS) void mix_dense_kernel(
     }
 }
 
-template <int MB, int ORDER, bool HAS_G, class LR>
-int launch_mb(dbw_ctx *c, const float *W, const float *x, const float *g, float *out, LR lr, int64_t n_vec,
-              hipStream_t s)
+template <int ORDER, bool HAS_G, class LR>
+int launch_fp32(dbw_ctx *c, const float *W, const float *x, const float *g, float *out, LR lr, hipStream_t s)
 {
-    using C = dense_cfg<MB>;
-    const int64_t n_tiles = (n_vec * 4 + C::TC - 1) / C::TC;
+    using C = dense_cfg<1>;
+    // rows are padded to a multiple of four floats: the float4 that straddles column d is read whole and stored up to d
+    const int64_t n_vec = (c->d + 3) / 4, n_tiles = (n_vec * 4 + C::TC - 1) / C::TC;
     if (n_tiles > INT32_MAX) return DBW_ERR_UNSUPPORTED;
-    if (c->ld > DBW_DENSE_MAX_LD) return DBW_ERR_UNSUPPORTED;
-    int cus = 256;
-    int dev = 0;
-    hipDeviceProp_t prop;
-    if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess)
-        cus = prop.multiProcessorCount;
-    const int blocks_per_cu = (int)((160 * 1024) / (sizeof(float) * 2 * C::TILE));
-    const int64_t grid = std::min<int64_t>(n_tiles, (int64_t)cus * std::max(1, std::min(blocks_per_cu, 4)));
+    const int64_t grid = std::min<int64_t>(n_tiles, 256 * 2);     // two workgroups' tiles fill a compute unit's LDS
     const bool full = c->N == C::NPAD && c->d % C::TC == 0;
     dbw_timer tm(c, "mix_dense_kernel", s);
     if (full)
-        hipLaunchKernelGGL((mix_dense_kernel<MB, ORDER, HAS_G, true, LR>), dim3((unsigned)grid), dim3(DENSE_THREADS), 0, s,
+        hipLaunchKernelGGL((mix_dense_kernel<1, ORDER, HAS_G, true, LR>), dim3((unsigned)grid), dim3(DENSE_THREADS), 0, s,
                            c->N, n_vec, c->d, c->ld / 4, W, (const float4 *)x, (const float4 *)g, out, g, lr,
                            (int)n_tiles);
     else
-        hipLaunchKernelGGL((mix_dense_kernel<MB, ORDER, HAS_G, false, LR>), dim3((unsigned)grid), dim3(DENSE_THREADS), 0,
+        hipLaunchKernelGGL((mix_dense_kernel<1, ORDER, HAS_G, false, LR>), dim3((unsigned)grid), dim3(DENSE_THREADS), 0,
                            s, c->N, n_vec, c->d, c->ld / 4, W, (const float4 *)x, (const float4 *)g, out, g, lr,
                            (int)n_tiles);
     DBW_HIP(hipGetLastError());
     return DBW_OK;
 }
 
-template <int ORDER, bool HAS_G, class LR>
-int launch(dbw_ctx *c, const float *W, const float *x, const float *g, float *out, LR lr, int64_t n_vec,
-           hipStream_t s)
+template <int MB, int WAVES, int ORDER, bool HAS_G, bool WIDE, class LR>
+int launch_split(dbw_ctx *c, const float *W, const float *x, const float *g, float *out, LR lr, hipStream_t s)
 {
+    using C = mixsplit::Cfg<MB, WAVES>;
+    const int64_t n_tiles = (c->d + C::TC - 1) / C::TC;
+    if (n_tiles > INT32_MAX) return DBW_ERR_UNSUPPORTED;
+    dbw_timer tm(c, "mix_dense_kernel", s);
+    // persistent: as many workgroups as the compute units' LDS holds
+    hipLaunchKernelGGL((mixsplit::kernel<MB, WAVES, ORDER, HAS_G, WIDE, LR>), dim3((unsigned)std::min<int64_t>(n_tiles, 256 * 8 / WAVES)),
+                       dim3(64 * WAVES), 0, s, c->N, c->d, c->ld, W, x, g, out, lr, (int)n_tiles);
+    DBW_HIP(hipGetLastError());
+    return DBW_OK;
+}
+
+template <int MB, int ORDER, bool HAS_G, bool WIDE, class LR>
+int launch_mb(dbw_ctx *c, const float *W, const float *x, const float *g, float *out, LR lr, hipStream_t s)
+{
+    // Up to 64 workers two workgroups of four wavefronts per compute unit, with tiles of half the width, give shorter
+    // vectors more even rounds of tiles; longer vectors want the longer pieces of a row (N = 60, four / eight waves:
+    // 134 154 columns 23.0 / 25.7 us, 600 000 93 / 96, 1.2 M 180 / 176, 4 M 600 / 555).
+    if constexpr (MB <= 2)
+        if (c->d <= 24 * 256 * (int64_t)mixsplit::Cfg<MB, 8>::TC) return launch_split<MB, 4, ORDER, HAS_G, WIDE, LR>(c, W, x, g, out, lr, s);
+    return launch_split<MB, 8, ORDER, HAS_G, WIDE, LR>(c, W, x, g, out, lr, s);
+}
+
+template <int ORDER, bool HAS_G, class LR>
+int launch(dbw_ctx *c, const float *W, const float *x, const float *g, float *out, LR lr, hipStream_t s)
+{
+    if (c->ld > DBW_DENSE_MAX_LD) return DBW_ERR_UNSUPPORTED;
+    const bool wide = c->ld % 4 == 0 && (uintptr_t)x % 16 == 0 && (!HAS_G || (uintptr_t)g % 16 == 0);
+    if (!wide) {
+        switch (c->Npad) {
+        case 32: return launch_mb<1, ORDER, HAS_G, false, LR>(c, W, x, g, out, lr, s);
+        case 64: return launch_mb<2, ORDER, HAS_G, false, LR>(c, W, x, g, out, lr, s);
+        case 128: return launch_mb<4, ORDER, HAS_G, false, LR>(c, W, x, g, out, lr, s);
+        case 256: return launch_mb<8, ORDER, HAS_G, false, LR>(c, W, x, g, out, lr, s);
+        default: return DBW_ERR_UNSUPPORTED;
+        }
+    }
     switch (c->Npad) {
-    case 32: return launch_mb<1, ORDER, HAS_G, LR>(c, W, x, g, out, lr, n_vec, s);
-    case 64: return launch_mb<2, ORDER, HAS_G, LR>(c, W, x, g, out, lr, n_vec, s);
-    case 128: return launch_mb<4, ORDER, HAS_G, LR>(c, W, x, g, out, lr, n_vec, s);
-    case 256: return launch_mb<8, ORDER, HAS_G, LR>(c, W, x, g, out, lr, n_vec, s);
+    // Up to 32 workers the fp32 matrix instructions are far from being the bound and the rows of padding would only be
+    // fetched and split: N = 10 x 134 154 columns 10.4 us against 13.3, x 4 M 116 against 184; N = 30 x 4 M 286 against 279.
+    case 32: return launch_fp32<ORDER, HAS_G, LR>(c, W, x, g, out, lr, s);
+    case 64: return launch_mb<2, ORDER, HAS_G, true, LR>(c, W, x, g, out, lr, s);
+    case 128: return launch_mb<4, ORDER, HAS_G, true, LR>(c, W, x, g, out, lr, s);
+    case 256: return launch_mb<8, ORDER, HAS_G, true, LR>(c, W, x, g, out, lr, s);
     default: return DBW_ERR_UNSUPPORTED;
     }
 }
 
 }  // namespace
 
-int dbw_launch_mix_csr_range(dbw_ctx *c, const float *x, const float *g, float *out, float lr, const float *lr_vec,
-                             int64_t c_begin, hipStream_t s);
-
-int64_t dbw_dense_columns(const dbw_ctx *c, const float *x, const float *g, const float *out)
-{
-    const bool aligned = (c->ld % 4 == 0) && ((uintptr_t)x % 16 == 0) && ((uintptr_t)out % 16 == 0) &&
-                         (!g || (uintptr_t)g % 16 == 0);
-    return aligned ? c->d : 0;
-}
-
 int dbw_launch_mix_dense(dbw_ctx *c, const float *x, const float *g, float *out, float lr, const float *lr_vec,
                          hipStream_t s, const float *W)
 {
-    const bool own_matrix = W != nullptr;
     if (!W) W = c->Wdense;
     if (!W) return DBW_ERR_STATE;
-    // rows are aligned and padded to a multiple of four floats: the float4 that straddles column d is
-    // read whole and stored up to d
-    const int64_t covered = dbw_dense_columns(c, x, g, out), n_vec = (covered + 3) / 4;
-    int rc = DBW_OK;
-    if (n_vec > 0) {
-        if (!g)
-            rc = launch<DBW_ORDER_CTA, false>(c, W, x, g, out, dbw_lr_scalar{0.f}, n_vec, s);
-        else if (lr_vec && c->order == DBW_ORDER_ATC)
-            rc = launch<DBW_ORDER_ATC, true>(c, W, x, g, out, dbw_lr_vector{lr_vec}, n_vec, s);
-        else if (lr_vec)
-            rc = launch<DBW_ORDER_CTA, true>(c, W, x, g, out, dbw_lr_vector{lr_vec}, n_vec, s);
-        else if (c->order == DBW_ORDER_ATC)
-            rc = launch<DBW_ORDER_ATC, true>(c, W, x, g, out, dbw_lr_scalar{lr}, n_vec, s);
-        else
-            rc = launch<DBW_ORDER_CTA, true>(c, W, x, g, out, dbw_lr_scalar{lr}, n_vec, s);
-        if (rc != DBW_OK) return rc;
-    }
-    // everything when rows are not 16-byte aligned; a caller that brought its own matrix covers
-    // those columns itself
-    if (covered < c->d && !own_matrix) rc = dbw_launch_mix_csr_range(c, x, g, out, lr, lr_vec, covered, s);
-    return rc;
+    if (!g) return launch<DBW_ORDER_CTA, false>(c, W, x, g, out, dbw_lr_scalar{0.f}, s);
+    if (lr_vec && c->order == DBW_ORDER_ATC) return launch<DBW_ORDER_ATC, true>(c, W, x, g, out, dbw_lr_vector{lr_vec}, s);
+    if (lr_vec) return launch<DBW_ORDER_CTA, true>(c, W, x, g, out, dbw_lr_vector{lr_vec}, s);
+    if (c->order == DBW_ORDER_ATC) return launch<DBW_ORDER_ATC, true>(c, W, x, g, out, dbw_lr_scalar{lr}, s);
+    return launch<DBW_ORDER_CTA, true>(c, W, x, g, out, dbw_lr_scalar{lr}, s);
 }

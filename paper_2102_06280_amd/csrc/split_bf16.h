@@ -1,0 +1,97 @@
+// fp32 products on the bf16 matrix instructions, without giving up any of the 24 significant bits.
+//
+// A finite fp32 value is the exact sum of three bf16 values: its upper 16 bits (high), the remainder rounded to
+// bf16 (middle), and what is left (low; at most 8 significant bits, so it is exact as well).  The product of two
+// split values has nine partial products; the six kept here,
+//   low * high + high * low + middle * middle + middle * high + high * middle + high * high,
+// leave out terms below 2^-24 of the product that have no preferred sign.  Every partial product of two bf16 values is exact in
+// fp32 and the matrix instruction accumulates in fp32.  v_mfma_f32_32x32x16_bf16 multiplies 16 times as
+// many values per cycle as v_mfma_f32_32x32x2_f32 does, so six of them per 16-wide step have 2.7 times the rate: a
+// register-resident loop reaches 312 TFLOP/s of fp32 products against 155 (212 to 246 when both operands are split
+// in the loop as well).  The result is closer to the exact sum than the fp32 instruction's, because an accumulator is
+// rounded 6 times per 16 terms instead of 8 times, and 5 of the 6 additions are small ones: relative error against
+// 64 bits 1.1e-7 / 2.4e-7 / 4.3e-7 / 7.0e-7 at 64 / 256 / 800 / 2048 terms, against 1.4e-7 / 2.9e-7 / 5.1e-7 /
+// 8.1e-7 (normally distributed operands; positive weights give the same figures).
+//
+// An operand that is not finite makes the middle term NaN, and with it every sum it enters: an infinity does not
+// survive as one.  Kernels therefore look at their sums and compute the ones that are not finite again with plain
+// fp32 multiply-adds, so that infinities and NaN come out as they do elsewhere.
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+namespace split_bf16 {
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+
+// Eight values as three planes of eight bf16.
+struct planes {
+    u32x4 h, m, l;
+};
+
+__device__ __forceinline__ uint32_t bits(float v) { return __builtin_bit_cast(uint32_t, v); }
+__device__ __forceinline__ float value(uint32_t v) { return __builtin_bit_cast(float, v); }
+// the upper halves of a (low 16 bits of the result) and b
+__device__ __forceinline__ uint32_t upper(float a, float b) { return __builtin_amdgcn_perm(bits(b), bits(a), 0x07060302u); }
+
+// Two values at a time: 11 vector instructions.
+__device__ __forceinline__ void split2(float a, float b, uint32_t &h, uint32_t &m, uint32_t &l)
+{
+    h = upper(a, b);
+    a -= value(bits(a) & 0xffff0000u);
+    b -= value(bits(b) & 0xffff0000u);
+    const bf16x2 r = {(__bf16)a, (__bf16)b};          // to nearest
+    m = __builtin_bit_cast(uint32_t, r);
+    a -= value(m << 16);
+    b -= value(m & 0xffff0000u);
+    l = upper(a, b);
+}
+
+__device__ __forceinline__ planes split8(const float (&x)[8])
+{
+    planes p;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        uint32_t h, m, l;
+        split2(x[2 * q], x[2 * q + 1], h, m, l);
+        p.h[q] = h;
+        p.m[q] = m;
+        p.l[q] = l;
+    }
+    return p;
+}
+
+__device__ __forceinline__ bf16x8 frag(const u32x4 &v) { return __builtin_bit_cast(bf16x8, v); }
+
+// acc += a b over 16 terms (32 x 32 outputs), smallest partial products first.  Lane l holds row (or column) l % 32
+// of the operand and the terms 8 (l / 32) .. + 7 of the step: any assignment of terms to lanes that is the same for both
+// operands gives the same sums.
+__device__ __forceinline__ f32x16 mma32(const planes &a, const planes &b, f32x16 acc)
+{
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(a.l), frag(b.h), acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(a.h), frag(b.l), acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(a.m), frag(b.m), acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(a.m), frag(b.h), acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(a.h), frag(b.m), acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(a.h), frag(b.h), acc, 0, 0, 0);
+    return acc;
+}
+
+// NaN or infinity
+__device__ __forceinline__ bool not_finite(float v) { return (bits(v) & 0x7f800000u) == 0x7f800000u; }
+
+// whether any value of an accumulator is NaN or infinite (0 * v is NaN then)
+__device__ __forceinline__ bool any_not_finite(const f32x16 &acc)
+{
+    float t = 0.f;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) t = fmaf(acc[v], 0.f, t);
+    return t != t;
+}
+
+}  // namespace split_bf16

@@ -73,3 +73,57 @@ def test_auto_path_choice(B):
     with pytest.raises(B.DbwError) as e:
         B.dbw_create(rowptr, colidx, 300, 64, mix_path=B.MIX_DENSE)
     assert e.value.code == B.ERR_UNSUPPORTED
+
+
+# Worker counts at the edges of the four sizes of the kernel (32, 64, 128, 256 rows), columns at the edges of their
+# tiles (256, 128, 64 and 32 columns) and of a float4, fewer and more tiles than compute units, rows with and without
+# padding (the 4-byte loads).
+EDGES = [(32, 255, 4), (33, 129, 1), (64, 128, 4), (65, 61, 4), (128, 64 * 257 + 3, 1), (129, 33, 1), (256, 32 * 256 + 31, 4),
+         (256, 95, 1), (20, 517, 1), (200, 1, 4)]
+
+
+@pytest.mark.parametrize("n,d,pad", EDGES, ids=[f"n{n}-d{d}-pad{p}" for n, d, p in EDGES])
+def test_tile_edges_and_values_that_are_not_finite(B, orc, n, d, pad):
+    """Both orders with a rate per worker against the oracle; then the same with an infinity and a NaN among the
+    parameters: a row that waits for the infinite worker gets the infinity, every other row 0 * inf = NaN, and no
+    other column changes.  Tolerance: the repository's 1e-5 per row, or where a row has so few columns that its sums
+    can cancel, the first-order bound of an fp32 sum of n + 2 terms, (n + 2) 2^-24 times the sum of their magnitudes."""
+    rowptr, colidx = inputs.graph_complete(n)
+    deg = np.diff(rowptr)
+    ld = (d + pad - 1) // pad * pad
+    g = np.random.default_rng(1000 * n + d)
+    x = g.standard_normal((n, ld)).astype(np.float32)
+    gr = (g.standard_normal((n, ld)) * 0.01).astype(np.float32)
+    eta = g.uniform(0.01, 0.1, n).astype(np.float32)
+    t = g.standard_exponential(n).astype(np.float32)
+    b = g.integers(0, deg // 2 + 1).astype(np.int32)
+    mask, _, _ = orc.select(rowptr, colidx, t, b)
+    bad = x.copy()
+    j, c = n // 2, d // 2
+    bad[j, c] = np.inf
+    if d > 1:
+        bad[n - 1, d - 1] = np.nan
+    for order in (0, 1):
+        h = B.dbw_create(rowptr, colidx, n, d, ld=ld, order=order, mix_path=B.MIX_DENSE)
+        try:
+            outs = []
+            for v in (x, bad):
+                out = torch.full((n, ld), 7.0, dtype=torch.float32, device="cuda")
+                B.dbw_select(h, dev(t), dev(b))
+                B.dbw_round_eta(h, dev(v), out, dev(eta), ext_grads=dev(gr))
+                outs.append(out.cpu().numpy())
+        finally:
+            B.dbw_destroy(h)
+        want = orc.round_eta(rowptr, colidx, mask, (deg - b).astype(np.int32), x, gr, eta, order, d=d)
+        size = orc.round_(rowptr, colidx, mask, (deg - b).astype(np.int32), np.abs(x), None, 0.0, 0, d=d)
+        bound = (n + 2) * 2.0 ** -24 * np.linalg.norm(size[:, :d], axis=1) / np.linalg.norm(want[:, :d], axis=1)
+        assert_params_close(outs[0], want, d=d, tol=np.maximum(1e-5, bound), what=f"n {n} d {d} order {order}")
+        assert np.all(outs[0][:, d:] == 7.0) and np.all(outs[1][:, d:] == 7.0)
+        waits = np.array([i == j or bool(mask[rowptr[i] + (j if j < i else j - 1)]) for i in range(n)])
+        assert np.all(outs[1][waits, c] == np.inf) and np.all(np.isnan(outs[1][~waits, c]))
+        same = np.ones(ld, bool)
+        same[c] = False
+        if d > 1:
+            same[d - 1] = False
+            assert np.all(np.isnan(outs[1][:, d - 1]))
+        assert np.array_equal(outs[0][:, same], outs[1][:, same])
