@@ -47,28 +47,60 @@ __device__ __forceinline__ float4 fma4(float w, float4 a, float4 acc)
     return acc;
 }
 
-__device__ __forceinline__ float4 load_stream(const float4 *p)
+// Four consecutive floats of a row.  WIDE: the rows start on 16-byte boundaries and are padded to a multiple of four
+// floats.  Otherwise the same 16 bytes are fetched on a 4-byte boundary, which the memory instructions allow (the type says
+// so to the compiler), and the last, partial group of a row is taken apart, because what follows it need not be
+// this row's memory.  A wave's accesses stay one run; the lines at its ends are touched twice, which is why the
+// accesses are then not marked as streaming (the caches join the halves).
+typedef float vf4_any __attribute__((ext_vector_type(4), aligned(4)));
+
+template <bool WIDE>
+__device__ __forceinline__ float4 load_row(const float *p, int64_t left /* floats up to column d */)
 {
+    if (WIDE) {
+        const vf4 v = *(const vf4 *)p;
+        return make_float4(v.x, v.y, v.z, v.w);
+    }
+    if (left >= 4) {
+        const vf4_any v = *(const vf4_any *)p;
+        return make_float4(v.x, v.y, v.z, v.w);
+    }
+    return make_float4(p[0], left > 1 ? p[1] : 0.f, left > 2 ? p[2] : 0.f, 0.f);
+}
+
+template <bool WIDE>
+__device__ __forceinline__ float4 load_stream(const float *p, int64_t left)
+{
+    if (!WIDE) return load_row<WIDE>(p, left);
     const vf4 v = __builtin_nontemporal_load((const vf4 *)p);
     return make_float4(v.x, v.y, v.z, v.w);
 }
 
-__device__ __forceinline__ void store_stream(float4 *p, float4 v)
+// Stores up to column d: padding stays untouched.
+template <bool WIDE>
+__device__ __forceinline__ void store_stream(float *p, float4 v, int64_t left)
 {
-    vf4 t;
-    t.x = v.x; t.y = v.y; t.z = v.z; t.w = v.w;
-    __builtin_nontemporal_store(t, (vf4 *)p);
+    if (left >= 4) {
+        vf4 t;
+        t.x = v.x; t.y = v.y; t.z = v.z; t.w = v.w;
+        if (WIDE) __builtin_nontemporal_store(t, (vf4 *)p);
+        else *(vf4_any *)p = t;
+        return;
+    }
+    p[0] = v.x;
+    if (left > 1) p[1] = v.y;
+    if (left > 2) p[2] = v.z;
 }
 
 // Persistent workgroup, tiles of N rows x TC4 float4 columns (N * TC4 <= LDS_TILE).
 // Element f of a tile is (row f / TC4, column f % TC4); thread `tid` owns elements
 // tid + u * LDS_THREADS, the same (row, column offset) in every tile.
-template <int ORDER, bool HAS_G, int TC4, class LR>
+template <int ORDER, bool HAS_G, int TC4, bool WIDE, class LR>
 __global__ __launch_bounds__(LDS_THREADS) void mix_lds_tiles(
-    int N, int nnz, int64_t n_vec, int64_t ld4, int64_t n_tiles, const int32_t *__restrict__ rowptr,
+    int N, int nnz, int64_t n_vec, int64_t ld, int64_t n_tiles, const int32_t *__restrict__ rowptr,
     const int32_t *__restrict__ p, const int32_t *__restrict__ sel_idx, const float *__restrict__ sel_w,
-    const float *__restrict__ self_w, const float4 *__restrict__ x, const float4 *__restrict__ g,
-    float4 *__restrict__ out, LR lr, int64_t d)
+    const float *__restrict__ self_w, const float *__restrict__ x, const float *__restrict__ g,
+    float *__restrict__ out, LR lr, int64_t d)
 {
     extern __shared__ float4 sm[];
     float4 *tiles = sm;                                  // 2 * LDS_TILE
@@ -93,7 +125,7 @@ __global__ __launch_bounds__(LDS_THREADS) void mix_lds_tiles(
         cnt[u] = p[r];
         ws[u] = self_w[r];
         eta[u] = lr.at(r);
-        rowoff[u] = (int64_t)r * ld4;
+        rowoff[u] = (int64_t)r * ld;
     }
 
     float4 xs[LDS_PER], gs[LDS_PER];
@@ -104,8 +136,8 @@ __global__ __launch_bounds__(LDS_THREADS) void mix_lds_tiles(
             xs[u] = make_float4(0.f, 0.f, 0.f, 0.f);
             gs[u] = xs[u];
             if (col[u] < TC4 && c < n_vec) {
-                xs[u] = load_stream(&x[rowoff[u] + c]);
-                if (HAS_G) gs[u] = load_stream(&g[rowoff[u] + c]);
+                xs[u] = load_stream<WIDE>(&x[rowoff[u] + 4 * c], d - 4 * c);
+                if (HAS_G) gs[u] = load_stream<WIDE>(&g[rowoff[u] + 4 * c], d - 4 * c);
                 if (ORDER == DBW_ORDER_ATC && HAS_G) xs[u] = fma4(-eta[u], gs[u], xs[u]);
             }
         }
@@ -136,14 +168,7 @@ __global__ __launch_bounds__(LDS_THREADS) void mix_lds_tiles(
                 for (int k = 0; k < cnt[u]; ++k)
                     acc = fma4(s_w[beg[u] + k], tl[s_idx[beg[u] + k] * TC4 + col[u]], acc);
                 if (ORDER == DBW_ORDER_CTA && HAS_G) acc = fma4(-eta[u], gc[u], acc);
-                if (4 * c + 4 <= d) {
-                    store_stream(&out[rowoff[u] + c], acc);
-                } else {                           // the float4 that straddles column d: padding stays untouched
-                    float *o = (float *)&out[rowoff[u] + c];
-                    o[0] = acc.x;
-                    if (4 * c + 1 < d) o[1] = acc.y;
-                    if (4 * c + 2 < d) o[2] = acc.z;
-                }
+                store_stream<WIDE>(&out[rowoff[u] + 4 * c], acc, d - 4 * c);
             }
         }
         if (nx < n_tiles) {
@@ -156,13 +181,13 @@ __global__ __launch_bounds__(LDS_THREADS) void mix_lds_tiles(
 }
 
 // One workgroup = one worker x one chunk of MIX_THREADS*UNROLL float4 columns.
-template <int ORDER, bool HAS_G, int UNROLL, class LR>
+template <int ORDER, bool HAS_G, int UNROLL, bool WIDE, class LR>
 __global__ __launch_bounds__(MIX_THREADS) void mix_csr_vec4(
-    int N, int64_t n_vec /* float4 columns per row */, int64_t ld4 /* row stride in float4 */,
+    int N, int64_t n_vec /* groups of four columns per row */, int64_t ld,
     int n_chunks, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ p,
     const int32_t *__restrict__ sel_idx, const float *__restrict__ sel_w,
-    const float *__restrict__ self_w, const float4 *__restrict__ x, const float4 *__restrict__ g,
-    float4 *__restrict__ out, LR lr, int64_t d)
+    const float *__restrict__ self_w, const float *__restrict__ x, const float *__restrict__ g,
+    float *__restrict__ out, LR lr, int64_t d)
 {
     const int64_t L = blockIdx.x;
     const int xcd = (int)(L % MIX_XCDS);
@@ -174,7 +199,7 @@ __global__ __launch_bounds__(MIX_THREADS) void mix_csr_vec4(
     const int beg = rowptr[i], cnt = p[i];
     const float ws = self_w[i], eta_i = lr.at(i);
     const int64_t c0 = chunk * (int64_t)(MIX_THREADS * UNROLL) + threadIdx.x;
-    const float4 *xi = x + (int64_t)i * ld4;
+    const float *xi = x + (int64_t)i * ld;
 
     float4 acc[UNROLL], gv[UNROLL];
 #pragma unroll
@@ -183,8 +208,8 @@ __global__ __launch_bounds__(MIX_THREADS) void mix_csr_vec4(
         acc[u] = make_float4(0.f, 0.f, 0.f, 0.f);
         gv[u] = acc[u];
         if (c < n_vec) {
-            float4 v = xi[c];
-            if (HAS_G) gv[u] = load_stream(&g[(int64_t)i * ld4 + c]);
+            float4 v = load_row<WIDE>(xi + 4 * c, d - 4 * c);
+            if (HAS_G) gv[u] = load_stream<WIDE>(&g[(int64_t)i * ld + 4 * c], d - 4 * c);
             if (ORDER == DBW_ORDER_ATC && HAS_G) v = fma4(-eta_i, gv[u], v);
             acc[u] = make_float4(ws * v.x, ws * v.y, ws * v.z, ws * v.w);
         }
@@ -192,13 +217,13 @@ __global__ __launch_bounds__(MIX_THREADS) void mix_csr_vec4(
     for (int k = 0; k < cnt; ++k) {
         const int j = sel_idx[beg + k];
         const float w = sel_w[beg + k], eta_j = lr.at(j);
-        const float4 *xj = x + (int64_t)j * ld4;
+        const float *xj = x + (int64_t)j * ld;
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u) {
             const int64_t c = c0 + (int64_t)u * MIX_THREADS;
             if (c < n_vec) {
-                float4 v = xj[c];
-                if (ORDER == DBW_ORDER_ATC && HAS_G) v = fma4(-eta_j, g[(int64_t)j * ld4 + c], v);
+                float4 v = load_row<WIDE>(xj + 4 * c, d - 4 * c);
+                if (ORDER == DBW_ORDER_ATC && HAS_G) v = fma4(-eta_j, load_row<WIDE>(&g[(int64_t)j * ld + 4 * c], d - 4 * c), v);
                 acc[u] = fma4(w, v, acc[u]);
             }
         }
@@ -209,42 +234,9 @@ __global__ __launch_bounds__(MIX_THREADS) void mix_csr_vec4(
         if (c < n_vec) {
             float4 r = acc[u];
             if (ORDER == DBW_ORDER_CTA && HAS_G) r = fma4(-eta_i, gv[u], r);
-            if (4 * c + 4 <= d) {
-                store_stream(&out[(int64_t)i * ld4 + c], r);
-            } else {                               // the float4 that straddles column d: padding stays untouched
-                float *o = (float *)&out[(int64_t)i * ld4 + c];
-                o[0] = r.x;
-                if (4 * c + 1 < d) o[1] = r.y;
-                if (4 * c + 2 < d) o[2] = r.z;
-            }
+            store_stream<WIDE>(&out[(int64_t)i * ld + 4 * c], r, d - 4 * c);
         }
     }
-}
-
-// Scalar columns [c_begin, d): the ragged tail of a row, or everything when rows are
-// not 16-byte aligned.  grid = (ceil(cols / 256), N).
-template <int ORDER, bool HAS_G, class LR>
-__global__ __launch_bounds__(256) void mix_csr_scalar(
-    int N, int64_t c_begin, int64_t d, int64_t ld, const int32_t *__restrict__ rowptr,
-    const int32_t *__restrict__ p, const int32_t *__restrict__ sel_idx,
-    const float *__restrict__ sel_w, const float *__restrict__ self_w, const float *__restrict__ x,
-    const float *__restrict__ g, float *__restrict__ out, LR lr)
-{
-    const int i = blockIdx.y;
-    const int64_t c = c_begin + (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (c >= d) return;
-    const int beg = rowptr[i], cnt = p[i];
-    float v = x[(int64_t)i * ld + c];
-    if (ORDER == DBW_ORDER_ATC && HAS_G) v = fmaf(-lr.at(i), g[(int64_t)i * ld + c], v);
-    float acc = self_w[i] * v;
-    for (int k = 0; k < cnt; ++k) {
-        const int j = sel_idx[beg + k];
-        float vj = x[(int64_t)j * ld + c];
-        if (ORDER == DBW_ORDER_ATC && HAS_G) vj = fmaf(-lr.at(j), g[(int64_t)j * ld + c], vj);
-        acc = fmaf(sel_w[beg + k], vj, acc);
-    }
-    if (ORDER == DBW_ORDER_CTA && HAS_G) acc = fmaf(-lr.at(i), g[(int64_t)i * ld + c], acc);
-    out[(int64_t)i * ld + c] = acc;
 }
 
 int device_cus()
@@ -259,23 +251,12 @@ int device_cus()
     return cus;
 }
 
-template <int ORDER, bool HAS_G, class LR>
-int launch_scalar(dbw_ctx *c, const float *x, const float *g, float *out, LR lr, int64_t c_begin, hipStream_t s)
-{
-    const int64_t cols = c->d - c_begin;
-    dbw_timer tm(c, "mix_csr_scalar", s);
-    hipLaunchKernelGGL((mix_csr_scalar<ORDER, HAS_G, LR>), dim3((unsigned)((cols + 255) / 256), c->N), dim3(256), 0, s,
-                       c->N, c_begin, c->d, c->ld, c->rowptr, c->p, c->sel_idx, c->sel_w, c->self_w, x, g, out, lr);
-    DBW_HIP(hipGetLastError());
-    return DBW_OK;
-}
-
-template <int ORDER, bool HAS_G, int TC4, class LR>
+template <int ORDER, bool HAS_G, int TC4, bool WIDE, class LR>
 int launch_lds(dbw_ctx *c, const float *x, const float *g, float *out, LR lr, int64_t n_vec, hipStream_t s)
 {
     const int64_t n_tiles = (n_vec + TC4 - 1) / TC4;
     const size_t lds = sizeof(float4) * 2 * LDS_TILE + (size_t)c->nnz * 8;
-    auto kern = mix_lds_tiles<ORDER, HAS_G, TC4, LR>;
+    auto kern = mix_lds_tiles<ORDER, HAS_G, TC4, WIDE, LR>;
     static bool attr_set = false;                      // per instantiation
     if (!attr_set) {
         DBW_HIP(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
@@ -283,9 +264,54 @@ int launch_lds(dbw_ctx *c, const float *x, const float *g, float *out, LR lr, in
     }
     const int64_t grid = std::min<int64_t>(n_tiles, device_cus());
     dbw_timer tm(c, "mix_lds_tiles", s);
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(LDS_THREADS), lds, s, c->N, c->nnz, n_vec, c->ld / 4, n_tiles,
-                       c->rowptr, c->p, c->sel_idx, c->sel_w, c->self_w, (const float4 *)x, (const float4 *)g,
-                       (float4 *)out, lr, c->d);
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(LDS_THREADS), lds, s, c->N, c->nnz, n_vec, c->ld, n_tiles,
+                       c->rowptr, c->p, c->sel_idx, c->sel_w, c->self_w, x, g, out, lr, c->d);
+    DBW_HIP(hipGetLastError());
+    return DBW_OK;
+}
+
+template <int ORDER, bool HAS_G, bool WIDE, class LR>
+int launch_aligned(dbw_ctx *c, const float *x, const float *g, float *out, LR lr, hipStream_t s)
+{
+    constexpr int UNROLL = 2;
+    // groups of four columns; the last may straddle column d
+    const int64_t n_vec = (c->d + 3) / 4;
+    // Tile width: a power of two of groups of four columns, 8..256, that holds all N rows in 64 KB.  The widest one
+    // moves the longest pieces of a row (2 KB pieces run at about 70 % of the HBM peak, 1 KB 68 %, 512 B 62 %,
+    // 256 B 54 %), but a short parameter vector then gives the CUs unequal numbers of tiles (d = 159 010 on 32
+    // workers: 311 tiles of 128 columns on 256 CUs, two rounds for 55 of them), so the width that minimises
+    // rounds x width / efficiency is taken.
+    int tc4 = 0;
+    double best = 0.0;
+    for (int cand = 256; cand >= 8; cand /= 2) {
+        if ((int64_t)c->N * cand > LDS_TILE) continue;
+        const int64_t tiles = (n_vec + cand - 1) / cand, rounds = (tiles + device_cus() - 1) / device_cus();
+        const double eff = cand >= 128 ? 0.70 : (cand == 64 ? 0.68 : (cand == 32 ? 0.62 : (cand == 16 ? 0.54 : 0.40)));
+        const double cost = (double)rounds * cand / eff;
+        if (tc4 == 0 || cost < best) {
+            best = cost;
+            tc4 = cand;
+        }
+    }
+    const bool use_lds = tc4 >= 8 && c->nnz <= LDS_MAX_EDGES && (n_vec + tc4 - 1) / tc4 >= device_cus() / 2;
+    if (use_lds) {
+        switch (tc4) {
+        case 256: return launch_lds<ORDER, HAS_G, 256, WIDE, LR>(c, x, g, out, lr, n_vec, s);
+        case 128: return launch_lds<ORDER, HAS_G, 128, WIDE, LR>(c, x, g, out, lr, n_vec, s);
+        case 64: return launch_lds<ORDER, HAS_G, 64, WIDE, LR>(c, x, g, out, lr, n_vec, s);
+        case 32: return launch_lds<ORDER, HAS_G, 32, WIDE, LR>(c, x, g, out, lr, n_vec, s);
+        case 16: return launch_lds<ORDER, HAS_G, 16, WIDE, LR>(c, x, g, out, lr, n_vec, s);
+        default: return launch_lds<ORDER, HAS_G, 8, WIDE, LR>(c, x, g, out, lr, n_vec, s);
+        }
+    }
+    const int64_t per = (int64_t)MIX_THREADS * UNROLL;
+    const int64_t n_chunks = (n_vec + per - 1) / per;
+    const int64_t per_xcd = (n_chunks + MIX_XCDS - 1) / MIX_XCDS;
+    const int64_t blocks = per_xcd * MIX_XCDS * c->N;
+    if (n_chunks > INT32_MAX || blocks > INT32_MAX) return DBW_ERR_UNSUPPORTED;
+    dbw_timer tm(c, "mix_csr_vec4", s);
+    hipLaunchKernelGGL((mix_csr_vec4<ORDER, HAS_G, UNROLL, WIDE, LR>), dim3((unsigned)blocks), dim3(MIX_THREADS), 0, s,
+                       c->N, n_vec, c->ld, (int)n_chunks, c->rowptr, c->p, c->sel_idx, c->sel_w, c->self_w, x, g, out, lr, c->d);
     DBW_HIP(hipGetLastError());
     return DBW_OK;
 }
@@ -293,60 +319,13 @@ int launch_lds(dbw_ctx *c, const float *x, const float *g, float *out, LR lr, in
 template <int ORDER, bool HAS_G, class LR>
 int launch(dbw_ctx *c, const float *x, const float *g, float *out, LR lr, hipStream_t s)
 {
-    constexpr int UNROLL = 2;
-    const bool aligned = (c->ld % 4 == 0) && ((uintptr_t)x % 16 == 0) && ((uintptr_t)out % 16 == 0) &&
-                         (!HAS_G || (uintptr_t)g % 16 == 0);
-    int64_t n_vec = aligned ? c->d / 4 : 0;
-    if (n_vec > 0) {
-        // Tile width: a power of two of float4 columns, 8..256, that holds all N rows in 64 KB.  The widest one
-        // moves the longest pieces of a row (2 KB pieces run at about 70 % of the HBM peak, 1 KB 68 %, 512 B 62 %,
-        // 256 B 54 %), but a short parameter vector then gives the CUs unequal numbers of tiles (d = 159 010 on 32
-        // workers: 311 tiles of 128 columns on 256 CUs, two rounds for 55 of them), so the width that minimises
-        // rounds x width / efficiency is taken.
-        const int64_t vec_cols = (c->d + 3) / 4;
-        int tc4 = 0;
-        double best = 0.0;
-        for (int cand = 256; cand >= 8; cand /= 2) {
-            if ((int64_t)c->N * cand > LDS_TILE) continue;
-            const int64_t tiles = (vec_cols + cand - 1) / cand, rounds = (tiles + device_cus() - 1) / device_cus();
-            const double eff = cand >= 128 ? 0.70 : (cand == 64 ? 0.68 : (cand == 32 ? 0.62 : (cand == 16 ? 0.54 : 0.40)));
-            const double cost = (double)rounds * cand / eff;
-            if (tc4 == 0 || cost < best) {
-                best = cost;
-                tc4 = cand;
-            }
-        }
-        const bool use_lds = tc4 >= 8 && c->nnz <= LDS_MAX_EDGES && (vec_cols + tc4 - 1) / tc4 >= device_cus() / 2;
-        int rc = DBW_OK;
-        if (use_lds) {
-            // the LDS kernel also takes the float4 that straddles column d (rows are aligned and
-            // ld is a multiple of 4, so that float4 lies inside the row): no separate tail launch
-            n_vec = (c->d + 3) / 4;
-            switch (tc4) {
-            case 256: rc = launch_lds<ORDER, HAS_G, 256, LR>(c, x, g, out, lr, n_vec, s); break;
-            case 128: rc = launch_lds<ORDER, HAS_G, 128, LR>(c, x, g, out, lr, n_vec, s); break;
-            case 64: rc = launch_lds<ORDER, HAS_G, 64, LR>(c, x, g, out, lr, n_vec, s); break;
-            case 32: rc = launch_lds<ORDER, HAS_G, 32, LR>(c, x, g, out, lr, n_vec, s); break;
-            case 16: rc = launch_lds<ORDER, HAS_G, 16, LR>(c, x, g, out, lr, n_vec, s); break;
-            default: rc = launch_lds<ORDER, HAS_G, 8, LR>(c, x, g, out, lr, n_vec, s); break;
-            }
-            if (rc != DBW_OK) return rc;
-        } else {
-            n_vec = (c->d + 3) / 4;                 // as above: the straddling float4 lies inside the aligned row
-            const int64_t per = (int64_t)MIX_THREADS * UNROLL;
-            const int64_t n_chunks = (n_vec + per - 1) / per;
-            const int64_t per_xcd = (n_chunks + MIX_XCDS - 1) / MIX_XCDS;
-            const int64_t blocks = per_xcd * MIX_XCDS * c->N;
-            if (n_chunks > INT32_MAX || blocks > INT32_MAX) return DBW_ERR_UNSUPPORTED;
-            dbw_timer tm(c, "mix_csr_vec4", s);
-            hipLaunchKernelGGL((mix_csr_vec4<ORDER, HAS_G, UNROLL, LR>), dim3((unsigned)blocks), dim3(MIX_THREADS), 0, s,
-                               c->N, n_vec, c->ld / 4, (int)n_chunks, c->rowptr, c->p, c->sel_idx, c->sel_w,
-                               c->self_w, (const float4 *)x, (const float4 *)g, (float4 *)out, lr, c->d);
-            DBW_HIP(hipGetLastError());
-        }
-    }
-    if (n_vec * 4 < c->d) return launch_scalar<ORDER, HAS_G, LR>(c, x, g, out, lr, n_vec * 4, s);
-    return DBW_OK;
+    // Rows without padding or on odd addresses (N = 48 x 1 000 003 columns, row stride 1 000 003: 129 us against 106 on
+    // padded rows; N = 128 x 2.8 M: 1.08 ms against 0.82).  They are never sent to a thread per column, which
+    // gathers its neighbours from the caches: 359 us and 3.97 ms at these sizes.
+    const bool wide = (c->ld % 4 == 0) && ((uintptr_t)x % 16 == 0) && ((uintptr_t)out % 16 == 0) &&
+                      (!HAS_G || (uintptr_t)g % 16 == 0);
+    return wide ? launch_aligned<ORDER, HAS_G, true, LR>(c, x, g, out, lr, s)
+                : launch_aligned<ORDER, HAS_G, false, LR>(c, x, g, out, lr, s);
 }
 
 }  // namespace
