@@ -11,8 +11,8 @@
 // from a small LDS table, the weights stream through LDS in 64-wide k chunks (double
 // buffered).  Accumulators stay in registers across channel groups.
 //
-// The data gradient of a convolution is the same operation applied to the output deltas
-// with the filters transposed and rotated by 180 degrees (see flip_filters_kernel).
+// Taken for the first layer of the 3 -> 32 channel network on 32 x 32 inputs (5 x 5 filters); other layers and shapes
+// take conv_split.h.
 //
 // Fragment layout of v_mfma_f32_16x16x4_f32, lane l: A[m = l % 16][slot l / 16],
 // B[slot l / 16][n = l % 16], D: d[v] = D[m = 4 (l / 16) + v][n = l % 16]; instruction j of a
@@ -78,7 +78,8 @@ __device__ __forceinline__ void load_bias(float (&bv)[MT][4], const float *bias,
 }
 
 // ReLU + 2 x 2 max pooling of one sample's accumulators, written as the pooled map ob [COUT][H/2][W/2]
-// and the window codes cb of the same shape (see conv_forward_kernel).  A wave's fragments cover
+// and the window codes cb of the same shape (one byte: which element of the window, in the
+// order (0,0) (0,1) (1,0) (1,1), was the first to attain the maximum, or 4 when the maximum is not positive).  A wave's fragments cover
 // whole pairs of image rows, so a window is two accumulators of one lane and of its neighbour.
 template <int MT, int NT, int H, int W>
 __device__ __forceinline__ void relu_pool_store(const f32x4 (&acc)[MT][NT], const float (&bv)[MT][4], float *ob, uint8_t *cb,
@@ -114,144 +115,7 @@ __device__ __forceinline__ void relu_pool_store(const f32x4 (&acc)[MT][NT], cons
         }
 }
 
-// in  [worker][B][Cin][H][W]   (worker stride in_stride)
-// wgt [worker][COUT][ldw]      (row co holds its Cin * KK filter taps, worker stride w_stride)
-// out [worker][B][COUT][H][W]  (worker stride out_stride);  grid = (B, workers)
-// POOL: the epilogue applies ReLU and 2 x 2 max pooling and writes out [worker][B][COUT][H/2][W/2]
-// together with code [worker][B][COUT][H/2][W/2] (one byte: which element of the window, in the
-// order (0,0) (0,1) (1,0) (1,1), was the first to attain the maximum, or 4 when the maximum is
-// not positive); the pre-activation map is not written at all.  A wave's fragments cover whole
-// pairs of image rows, so a window is two accumulators of one lane and of its neighbour.
-// EXPAND: the input is given as in [worker][B][Cin][H/2][W/2] (pooled gradients) with in_code of the same
-// shape and is expanded to [Cin][H][W] while it is copied into LDS (see expand_pooled): the data-gradient
-// convolution then needs no un-pooled delta map in memory.
-template <int CG, int MT, int NT, int H, int W, int KS, int WAVES, bool POOL = false, bool EXPAND = false>
-__global__ __launch_bounds__(64 * WAVES) void conv_forward_kernel(
-    const float *__restrict__ in, int64_t in_stride, const float *__restrict__ wgt, int64_t w_stride, int ldw,
-    const float *__restrict__ bias, int64_t bias_stride, float *__restrict__ out, int64_t out_stride, int Cin,
-    uint8_t *__restrict__ code = nullptr, int64_t code_stride = 0, const uint8_t *__restrict__ in_code = nullptr,
-    int64_t in_code_stride = 0)
-{
-    using C = Cfg<CG, MT, NT, H, W, KS, WAVES>;
-    __shared__ __attribute__((aligned(16))) float img[C::IMG];
-    __shared__ __attribute__((aligned(16))) float As[2][C::COUT * C::LDA];
-    __shared__ __attribute__((aligned(16))) int taptab[C::KGS * 16];
-
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int b = blockIdx.x, w = blockIdx.y;
-
-    for (int k = tid; k < C::KGS * 16; k += C::THREADS) {
-        const int c = k / C::KK, rr = k % C::KK, kh = rr / KS, kw = rr % KS;
-        taptab[k] = k < C::TAPS ? c * C::HP * C::WP + kh * C::WP + kw : 0;
-    }
-    for (int e = tid; e < C::IMG; e += C::THREADS) img[e] = 0.f;     // the halo stays zero
-
-    int pixoff[NT];
-#pragma unroll
-    for (int nf = 0; nf < NT; ++nf) {
-        const int p = (wave * NT + nf) * 16 + (lane & 15);
-        pixoff[nf] = (p / W) * C::WP + (p % W);
-    }
-    f32x4 acc[MT][NT];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int nf = 0; nf < NT; ++nf) acc[mt][nf] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    float bv[MT][4];
-    load_bias<MT>(bv, bias ? bias + w * bias_stride : nullptr, lane);
-    const float *inb = in + w * in_stride + (int64_t)b * Cin * (EXPAND ? C::PIX / 4 : C::PIX);
-    const uint8_t *icb = EXPAND ? in_code + w * in_code_stride + (int64_t)b * Cin * (C::PIX / 4) : nullptr;
-    const float *ww = wgt + w * w_stride;
-    const int groups = (Cin + CG - 1) / CG;
-
-    float areg[C::AROWS];
-    auto fetch_a = [&](int g, int chunk) {
-        const int kloc = chunk * 64 + lane;
-        const bool ok = kloc < C::TAPS && g * CG + kloc / C::KK < Cin;
-        const int kglob = ok ? g * C::TAPS + kloc : 0;
-#pragma unroll
-        for (int j = 0; j < C::AROWS; ++j) {
-            const float v = ww[(wave + WAVES * j) * ldw + kglob];
-            areg[j] = ok ? v : 0.f;
-        }
-    };
-    auto commit_a = [&](int buf) {
-#pragma unroll
-        for (int j = 0; j < C::AROWS; ++j) As[buf][(wave + WAVES * j) * C::LDA + lane] = areg[j];
-    };
-
-    int buf = 0;
-    for (int g = 0; g < groups; ++g) {
-        __syncthreads();                       // image and weight buffers of the previous group are free
-        for (int e = tid; e < CG * H * (W / 4); e += C::THREADS) {
-            const int c = e / (H * (W / 4)), rem = e % (H * (W / 4)), y = rem / (W / 4), x4 = rem % (W / 4);
-            const int ch = g * CG + c;
-            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (ch < Cin) {
-                if (EXPAND)
-                    v = expand_pooled(inb + ch * (C::PIX / 4), icb + ch * (C::PIX / 4), y, x4, W);
-                else
-                    v = *(const float4 *)&inb[(ch * H + y) * W + 4 * x4];
-            }
-            float *dst = &img[c * C::HP * C::WP + (y + C::PAD) * C::WP + C::PAD + 4 * x4];
-            dst[0] = v.x; dst[1] = v.y; dst[2] = v.z; dst[3] = v.w;
-        }
-        fetch_a(g, 0);
-        commit_a(buf);
-        __syncthreads();
-        for (int chunk = 0; chunk < C::CHUNKS; ++chunk) {
-            if (chunk + 1 < C::CHUNKS) fetch_a(g, chunk + 1);
-#pragma unroll
-            for (int kgl = 0; kgl < 4; ++kgl) {
-                const int kg = chunk * 4 + kgl;
-                if (kg < C::KGS) {
-                    const i32x4 tap = *(const i32x4 *)&taptab[kg * 16 + 4 * (lane >> 4)];
-                    f32x4 fa[MT], fb[NT];
-#pragma unroll
-                    for (int mt = 0; mt < MT; ++mt)
-                        fa[mt] = *(const f32x4 *)&As[buf][(16 * mt + (lane & 15)) * C::LDA + kgl * 16 + 4 * (lane >> 4)];
-#pragma unroll
-                    for (int nf = 0; nf < NT; ++nf)
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) fb[nf][j] = img[pixoff[nf] + tap[j]];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-#pragma unroll
-                        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                            for (int nf = 0; nf < NT; ++nf)
-                                acc[mt][nf] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[mt][j], fb[nf][j], acc[mt][nf], 0, 0, 0);
-                }
-            }
-            if (chunk + 1 < C::CHUNKS) commit_a(buf ^ 1);
-            __syncthreads();
-            buf ^= 1;
-        }
-    }
-
-    if (POOL) {
-        constexpr int PP = (H / 2) * (W / 2);
-        relu_pool_store<MT, NT, H, W>(acc, bv, out + w * out_stride + (int64_t)b * C::COUT * PP,
-                                      code + w * code_stride + (int64_t)b * C::COUT * PP, wave, lane);
-        return;
-    }
-    float *ob = out + w * out_stride + (int64_t)b * C::COUT * C::PIX;
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int co = 16 * mt + 4 * (lane >> 4) + v;
-#pragma unroll
-            for (int nf = 0; nf < NT; ++nf) {
-                const int p = (wave * NT + nf) * 16 + (lane & 15);
-                ob[co * C::PIX + p] = acc[mt][nf][v] + bv[mt][v];
-            }
-        }
-}
-
-// conv_forward_kernel with POOL for a layer whose input channels all fit one LDS fill (Cin <= CG)
+// Convolution, ReLU and pooling of a layer whose input channels all fit one LDS fill (Cin <= CG)
 // and whose filters fit the two weight buffers: a workgroup keeps the filters in LDS and runs
 // through SB consecutive samples.  The next sample's image is requested before the multiplies
 // of the current one and put into LDS after them, so that neither the filter fetch nor the
@@ -363,18 +227,6 @@ __global__ __launch_bounds__(64 * WAVES) void conv_forward_pool_multi_kernel(
         put_image();
         __syncthreads();
     }
-}
-
-// dst[ci][(co, kh, kw)] = src[co][ci][KS - 1 - kh][KS - 1 - kw] per worker: the filters of the
-// data-gradient convolution.  grid = (ceil(Cin * Cout * KK / 256), workers).
-__global__ __launch_bounds__(256) void flip_filters_kernel(const float *__restrict__ src, int64_t src_stride,
-                                                           float *__restrict__ dst, int64_t dst_stride, int Cin,
-                                                           int Cout, int KK)
-{
-    const int w = blockIdx.y, idx = blockIdx.x * 256 + threadIdx.x;
-    if (idx >= Cin * Cout * KK) return;
-    const int ci = idx / (Cout * KK), rem = idx - ci * Cout * KK, co = rem / KK, rr = rem - co * KK;
-    dst[w * dst_stride + idx] = src[w * src_stride + (co * Cin + ci) * KK + (KK - 1 - rr)];
 }
 
 // Weight gradient of the same convolution: dW[co][t] = sum over samples b and pixels p of

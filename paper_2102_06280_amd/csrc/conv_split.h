@@ -1,0 +1,629 @@
+// Stride-1 'same' convolutions and their weight gradients on the bf16 matrix instructions, every fp32 value split into three
+// bf16 values (split_bf16.h), for any number of channels and image size that fits LDS (forward_lds, wgrad_lds below).
+//
+// Forward (and, with flipped filters, the data gradient): one workgroup takes 64 pooling windows = 256 output pixels,
+// of one sample or of several small ones, and all output channels (up to 64; more in further workgroups).
+//   out[co][p] = sum over taps t and channels c of  Wt[co][t][c] * in[p + t][c]
+// The reduction runs over channels inside a tap, 16 at a time, so that the eight values of a lane's fragment are
+// eight channels of ONE pixel: the image lies in LDS as [plane][8 channels][position][8 values], split once when
+// it is copied there, and the fragment of any pixel shifted by any tap is one aligned 128-bit read, with no bounds
+// check (zero halo) and no patch matrix.  The filters are brought into the same order, split, once per round
+// (prepare_kernel) and stream through LDS, two taps (or four) at a time, by loads that bypass the registers.
+//
+// The 32 columns of a fragment are eight 2 x 2 pooling windows, four lanes each: ReLU, pooling and the window
+// codes need three moves inside a quad of lanes.
+//
+// What bounds it, at 64 workers x 32 samples, 32 -> 64 channels, 16 x 16 pixels (53.7 GFLOP, six times that in bf16):
+// forward 252 us = 1.28 PFLOP/s of bf16, about what this card sustains on this instruction with operands from LDS (a
+// register-resident loop reaches 1.87); the data gradient, with 32 output rows per wave, reads 9 KB of LDS per 12
+// matrix instructions and comes to 264.  The fp32 kernels they replace took 433 and 447 us (122 TFLOP/s).
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "split_bf16.h"
+
+namespace convsplit {
+
+using split_bf16::f32x16;
+using split_bf16::planes;
+using split_bf16::u32x4;
+
+constexpr int THREADS = 256, WINDOWS = 64;            // of the forward kernel: 4 waves x 2 blocks x 8 windows
+
+struct Shape {
+    int Cin, Cout, H, W, KS, B;
+};
+
+// Row pitch of the image in LDS (positions): an odd multiple of 4, so that the two rows of eight lanes' windows fall
+// into different banks.
+__host__ __device__ inline int pitch(const Shape &s)
+{
+    int p = s.W + s.KS - 1;
+    while (p % 8 != 4) ++p;
+    return p;
+}
+__host__ __device__ inline int samples_per_group(const Shape &s)
+{
+    const int t = s.H * s.W / 4;
+    return t >= WINDOWS ? 1 : WINDOWS / t;
+}
+__host__ __device__ inline int positions(const Shape &s) { return (s.H + s.KS - 1) * pitch(s); }
+constexpr int chunk_taps(int MB) { return MB == 1 ? 4 : 2; }
+inline size_t forward_lds(const Shape &s, int MB)
+{
+    return 16 * ((size_t)6 * samples_per_group(s) * positions(s) + (size_t)2 * chunk_taps(MB) * MB * 192);
+}
+
+// Filters in fragment order: [worker][16-channel group][tap][32-row block][plane][lane][8 values].
+__host__ __device__ inline int row_blocks(int Cout) { return Cout <= 32 ? 1 : (Cout + 63) / 64 * 2; }
+inline int64_t filter_floats(int Cin, int Cout, int KS) { return (int64_t)((Cin + 15) / 16) * KS * KS * row_blocks(Cout) * 768; }
+
+// src: filters [C2][C1][KK] of a convolution C1 -> C2, in its forward order (rows = C2, reduction over C1), or in that
+// of its data gradient (rows = C1, reduction over C2, taps reversed).  A workgroup brings the filters of 32 rows x 16
+// reduction channels into LDS as they lie in memory (runs of 16 KK or 32 KK floats) and writes all their taps.  64
+// workers x 32 -> 64 channels, 5 x 5: 15 us; a thread per group of eight that gathers them from memory itself 38.
+// grid = (16-channel groups x row blocks of both directions, workers).
+__host__ __device__ inline int prepare_blocks(int Cin, int Cout) { return (Cin + 15) / 16 * row_blocks(Cout); }
+
+constexpr int PREPARE_THREADS = 1024;
+
+template <int KK, bool FLIP>
+__device__ __forceinline__ void prepare(float *tile /* LDS [16 channels][32 rows][KK] */, const float *__restrict__ s, u32x4 *__restrict__ d,
+                                        int C1, int C2, int blk)
+{
+    static_assert(KK % 2 == 1, "the row length keeps lanes' rows in different banks");
+    constexpr int INNER = (FLIP ? 32 : 16) * KK, OUTER = FLIP ? 16 : 32;     // the outer index in memory is C2
+    const int mbt = row_blocks(FLIP ? C1 : C2), mb = blk % mbt, g = blk / mbt, tid = threadIdx.x;
+    const int i0 = (FLIP ? 32 * mb : 16 * g) * KK, o0 = FLIP ? 16 * g : 32 * mb;
+    constexpr int PER = (512 * KK + PREPARE_THREADS - 1) / PREPARE_THREADS;
+    static_assert(INNER * OUTER == 512 * KK, "the loops cover the block");
+    float f[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {                  // all of a thread's loads in flight
+        const int e = tid + PREPARE_THREADS * u, o = e / INNER, i = e % INNER;
+        const bool ok = e < 512 * KK && o0 + o < C2 && i0 + i < C1 * KK;
+        const float v = s[ok ? (int64_t)(o0 + o) * C1 * KK + i0 + i : 0];
+        f[u] = ok ? v : 0.f;
+    }
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int e = tid + PREPARE_THREADS * u, o = e / INNER, i = e % INNER, ch = FLIP ? o : i / KK, row = FLIP ? i / KK : o;
+        if (e < 512 * KK) tile[(ch * 32 + row) * KK + i % KK] = f[u];
+    }
+    __syncthreads();
+    for (int e = tid; e < KK * 64; e += PREPARE_THREADS) {
+        const int lane = e % 64, tap = e / 64;
+        float v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = tile[((8 * (lane / 32) + j) * 32 + lane % 32) * KK + (FLIP ? KK - 1 - tap : tap)];
+        const planes p = split_bf16::split8(v);
+        u32x4 *at = d + ((int64_t)(g * KK + tap) * mbt + mb) * 192 + lane;
+        at[0] = p.h;
+        at[64] = p.m;
+        at[128] = p.l;
+    }
+}
+
+template <int KK>
+__global__ __launch_bounds__(PREPARE_THREADS) void prepare_kernel(const float *__restrict__ src, int64_t src_stride, u32x4 *__restrict__ fwd,
+                                                      u32x4 *__restrict__ bwd, int64_t dst_stride, int C1, int C2)
+{
+    __shared__ float tile[512 * KK];
+    const int nf = prepare_blocks(C1, C2), blk = blockIdx.x;
+    const float *s = src + blockIdx.y * src_stride;
+    if (blk < nf) prepare<KK, false>(tile, s, fwd + blockIdx.y * dst_stride, C1, C2, blk);
+    else prepare<KK, true>(tile, s, bwd + blockIdx.y * dst_stride, C1, C2, blk - nf);
+}
+
+struct FwdArgs {
+    Shape s;
+    const float *in;            // [worker][B][Cin][H][W]; EXPAND: the pooled gradients [B][Cin][H/2][W/2] with in_code
+    int64_t in_stride;
+    const uint8_t *in_code;
+    int64_t in_code_stride;
+    const u32x4 *filters;       // prepare_kernel
+    int64_t filters_stride;
+    const float *wgt;           // the filters themselves, [C2][C1][KK]: only for sums that are not finite
+    int64_t wgt_stride;
+    const float *bias;          // or null
+    int64_t bias_stride;
+    float *out;                 // [worker][B][Cout][H][W]; POOL: [B][Cout][H/2][W/2] after ReLU and pooling, with code
+    int64_t out_stride;
+    uint8_t *code;
+    int64_t code_stride;
+};
+
+// A value of the expanded input (see conv_lds.h, expand_pooled): the pooled gradient where the pixel was its
+// window's first maximum, else zero.
+__device__ __forceinline__ float expanded(const float *pooled, const uint8_t *code, int y, int x, int W)
+{
+    const int o = (y >> 1) * (W >> 1) + (x >> 1);
+    return code[o] == (uint8_t)(2 * (y & 1) + (x & 1)) ? pooled[o] : 0.f;
+}
+
+// One output value with plain multiply-adds (no bias).
+template <bool EXPAND>
+__device__ float plain_value(const FwdArgs &a, int w, int b, int co, int y, int x)
+{
+    const int KS = a.s.KS, KK = KS * KS, pad = KS / 2, HW = a.s.H * a.s.W;
+    const float *wg = a.wgt + w * a.wgt_stride;
+    float r = 0.f;
+    for (int c = 0; c < a.s.Cin; ++c)
+        for (int t = 0; t < KK; ++t) {
+            const int yy = y + t / KS - pad, xx = x + t % KS - pad;
+            if ((unsigned)yy >= (unsigned)a.s.H || (unsigned)xx >= (unsigned)a.s.W) continue;
+            const int64_t plane = (int64_t)b * a.s.Cin + c;
+            const float v = EXPAND ? expanded(a.in + w * a.in_stride + plane * (HW / 4), a.in_code + w * a.in_code_stride + plane * (HW / 4), yy, xx, a.s.W)
+                                   : a.in[w * a.in_stride + plane * HW + yy * a.s.W + xx];
+            r = fmaf(EXPAND ? wg[(c * a.s.Cout + co) * KK + KK - 1 - t] : wg[(co * a.s.Cin + c) * KK + t], v, r);
+        }
+    return r;
+}
+
+template <int CTRL>
+__device__ __forceinline__ float quad(float v)        // the value of lane CTRL / 0x55 of the quad
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
+}
+
+// 64 x 16 bytes from global memory to LDS; the caller waits for them (see mix_split.h).
+__device__ __forceinline__ void load_to_lds(const u32x4 *src, const u32x4 *dst)
+{
+    const uint32_t m0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) const u32x4 *)dst);
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(m0) : "memory");
+}
+
+// grid = (ceil(B / samples_per_group) x ceil(windows of a sample / 64 if there is one sample), workers, row blocks / MB);
+// dynamic LDS = forward_lds.
+template <int MB, bool POOL, bool EXPAND>
+__global__ __launch_bounds__(THREADS, 2) void forward_kernel(FwdArgs a)
+{
+    extern __shared__ __attribute__((aligned(16))) u32x4 sm[];
+    constexpr int TCH = chunk_taps(MB);
+    const int H = a.s.H, W = a.s.W, KS = a.s.KS, KK = KS * KS, HW = H * W, T = HW / 4, WP = pitch(a.s), POS = positions(a.s);
+    const int spg = samples_per_group(a.s), xt = spg > 1 ? 1 : (T + WINDOWS - 1) / WINDOWS;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int w = blockIdx.y, b0 = blockIdx.x / xt * spg, q0 = blockIdx.x % xt * WINDOWS, nb_s = min(spg, a.s.B - b0);
+    const int half = spg * POS, plane = 2 * half;     // 16-byte groups of eight channels / of a plane
+    u32x4 *img = sm, *wb = sm + 3 * plane;
+
+    const int groups = (a.s.Cin + 15) / 16, mbt = row_blocks(a.s.Cout), cpg = (KK + TCH - 1) / TCH, chunks = groups * cpg;
+    const u32x4 *fl = a.filters + w * a.filters_stride + blockIdx.z * MB * 192 + lane;
+    auto fetch = [&](int c) {                          // chunk c of the filters, a quarter of it by each wave
+        const int t0 = c % cpg * TCH, n = min(TCH, KK - t0) * MB * 3;
+        const int64_t first = (int64_t)(c / cpg * KK + t0) * mbt * 192;
+#pragma unroll
+        for (int u = 0; u < TCH * MB * 3 / 4; ++u) {
+            const int i = wave + 4 * u;
+            if (i < n) load_to_lds(fl + first + (int64_t)(i / (MB * 3)) * mbt * 192 + i % (MB * 3) * 64, wb + (c & 1) * TCH * MB * 192 + i * 64);
+        }
+    };
+    fetch(0);
+    for (int e = tid; e < 3 * plane; e += THREADS) img[e] = u32x4{0u, 0u, 0u, 0u};       // the halo stays zero
+
+    // this lane's pixel in each of the two blocks: four lanes per window
+    int pos[2], smp[2], win[2];
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb) {
+        const int q = q0 + 8 * (2 * wave + nb) + (lane % 32) / 4;
+        smp[nb] = spg > 1 ? q / T : 0;
+        win[nb] = spg > 1 ? q % T : q;
+        if (smp[nb] >= nb_s || win[nb] >= T) smp[nb] = -1;                                // beyond the samples: never stored
+        const int wy = win[nb] / (W / 2), wx = win[nb] % (W / 2);
+        pos[nb] = (smp[nb] < 0 ? 0 : smp[nb] * POS + (2 * wy + (lane >> 1 & 1)) * WP + 2 * wx + (lane & 1)) + (lane >> 5) * half;
+    }
+    f32x16 acc[MB][2];
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[mb][nb][v] = 0.f;
+
+    for (int c = 0; c < chunks; ++c) {
+        if (c % cpg == 0) {                            // the next 16 channels of the image
+            __syncthreads();
+            const int pad = KS / 2, g = c / cpg;
+            if (EXPAND) {
+                // a window of eight channels: split once, then masked by the codes into its four positions
+                for (int e = tid; e < 2 * spg * T; e += THREADS) {
+                    const int hh = e / (spg * T), r = e % (spg * T), s = r / T, q = r % T, wy = q / (W / 2), wx = q % (W / 2);
+                    float v[8];
+                    int cd[8];
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        const int ch = 16 * g + 8 * hh + j;
+                        const bool ok = s < nb_s && ch < a.s.Cin;
+                        const int64_t at = ok ? ((int64_t)(b0 + s) * a.s.Cin + ch) * T + q : 0;
+                        const float f = a.in[w * a.in_stride + at];
+                        const int code = a.in_code[w * a.in_code_stride + at];
+                        v[j] = ok ? f : 0.f;
+                        cd[j] = ok ? code : 4;
+                    }
+                    const planes p = split_bf16::split8(v);
+                    u32x4 *d = img + hh * half + s * POS + (2 * wy + pad) * WP + 2 * wx + pad;
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        u32x4 mask;
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) mask[j] = (cd[2 * j] == k ? 0xffffu : 0u) | (cd[2 * j + 1] == k ? 0xffff0000u : 0u);
+                        u32x4 *dk = d + (k >> 1) * WP + (k & 1);
+                        dk[0] = p.h & mask;
+                        dk[plane] = p.m & mask;
+                        dk[2 * plane] = p.l & mask;
+                    }
+                }
+            } else {
+                for (int e = tid; e < 2 * spg * HW; e += THREADS) {
+                    const int hh = e / (spg * HW), r = e % (spg * HW), s = r / HW, px = r % HW, y = px / W, x = px % W;
+                    float v[8];
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        const int ch = 16 * g + 8 * hh + j;
+                        const bool ok = s < nb_s && ch < a.s.Cin;
+                        const float f = a.in[w * a.in_stride + (ok ? ((int64_t)(b0 + s) * a.s.Cin + ch) * HW + px : 0)];
+                        v[j] = ok ? f : 0.f;
+                    }
+                    const planes p = split_bf16::split8(v);
+                    u32x4 *d = img + hh * half + s * POS + (y + pad) * WP + x + pad;
+                    d[0] = p.h;
+                    d[plane] = p.m;
+                    d[2 * plane] = p.l;
+                }
+            }
+        }
+        // chunk c has landed and everybody is done with chunk c - 1, whose place chunk c + 1 takes
+        __builtin_amdgcn_s_waitcnt(0);
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        if (c + 1 < chunks) fetch(c + 1);
+        const int t0 = c % cpg * TCH, nt = min(TCH, KK - t0);
+        const u32x4 *wc = wb + (c & 1) * TCH * MB * 192 + lane;
+#pragma unroll
+        for (int t = 0; t < TCH; ++t) {
+            if (t < nt) {
+                const int off = (t0 + t) / KS * WP + (t0 + t) % KS;
+                planes fa[MB], fb[2];
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb) {
+                    const u32x4 *p = wc + (t * MB + mb) * 192;
+                    fa[mb] = planes{p[0], p[64], p[128]};
+                }
+#pragma unroll
+                for (int nb = 0; nb < 2; ++nb) {
+                    const u32x4 *p = img + pos[nb] + off;
+                    fb[nb] = planes{p[0], p[plane], p[2 * plane]};
+                }
+                split_bf16::mma32_block<MB, 2>(fa, fb, acc);
+            }
+        }
+    }
+
+    // ---- epilogue.  Register v of a lane: output channel 32 mb + 8 (v / 4) + 4 (lane / 32) + v % 4, the lane's pixel.
+    const int m0 = 32 * MB * blockIdx.z, PP = T;
+    float *ob = a.out + w * a.out_stride;
+    bool bad = false;
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) bad |= smp[nb] >= 0 && split_bf16::any_not_finite(acc[mb][nb]);
+    if (!__any(bad)) {
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int c0 = m0 + 32 * mb + 8 * k + 4 * (lane >> 5);
+                float bv[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) bv[i] = a.bias && c0 + i < a.s.Cout ? a.bias[w * a.bias_stride + c0 + i] : 0.f;
+#pragma unroll
+                for (int nb = 0; nb < 2; ++nb) {
+                    const int64_t sample = (int64_t)(b0 + smp[nb]) * a.s.Cout;
+                    if (POOL) {
+                        // every lane of the quad holds the window's result for the four channels; it stores one of them
+                        float m = 0.f;
+                        int arg = 4;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const float v = acc[mb][nb][4 * k + i] + bv[i];
+                            const float v0 = quad<0x00>(v), v1 = quad<0x55>(v), v2 = quad<0xAA>(v), v3 = quad<0xFF>(v);
+                            const float mx = fmaxf(fmaxf(v0, v1), fmaxf(v2, v3));
+                            int ai = v2 == mx ? 2 : 3;
+                            ai = v1 == mx ? 1 : ai;
+                            ai = v0 == mx ? 0 : ai;
+                            ai = mx > 0.f ? ai : 4;
+                            m = (lane & 3) == i ? fmaxf(mx, 0.f) : m;
+                            arg = (lane & 3) == i ? ai : arg;
+                        }
+                        const int co = c0 + (lane & 3);
+                        if (smp[nb] >= 0 && co < a.s.Cout) {
+                            ob[(sample + co) * PP + win[nb]] = m;
+                            a.code[w * a.code_stride + (sample + co) * PP + win[nb]] = (uint8_t)arg;
+                        }
+                    } else if (smp[nb] >= 0) {
+                        const int y = 2 * (win[nb] / (W / 2)) + (lane >> 1 & 1), x = 2 * (win[nb] % (W / 2)) + (lane & 1);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            if (c0 + i < a.s.Cout) ob[(sample + c0 + i) * HW + y * W + x] = acc[mb][nb][4 * k + i] + bv[i];
+                    }
+                }
+            }
+        return;
+    }
+    // ---- some sum of the wave is not finite: all of its outputs again with plain multiply-adds (see split_bf16.h)
+#pragma unroll 1
+    for (int e = 0; e < 2 * 16 * MB; ++e) {
+        const int nb = e & 1, v = e >> 1 & 15, co = m0 + 32 * (e >> 5) + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+        const int s = nb ? smp[1] : smp[0], q = nb ? win[1] : win[0];
+        const int y = 2 * (q / (W / 2)) + (lane >> 1 & 1), x = 2 * (q % (W / 2)) + (lane & 1);
+        const bool ok = s >= 0 && co < a.s.Cout;
+        float r = 0.f;
+        if (ok) r = plain_value<EXPAND>(a, w, b0 + s, co, y, x) + (a.bias ? a.bias[w * a.bias_stride + co] : 0.f);
+        const int64_t at = ok ? (int64_t)(b0 + s) * a.s.Cout + co : 0;
+        if (POOL) {
+            const float v0 = quad<0x00>(r), v1 = quad<0x55>(r), v2 = quad<0xAA>(r), v3 = quad<0xFF>(r);
+            const float mx = fmaxf(fmaxf(v0, v1), fmaxf(v2, v3));
+            const int arg = !(mx > 0.f) ? 4 : (v0 == mx ? 0 : (v1 == mx ? 1 : (v2 == mx ? 2 : 3)));
+            if (ok && (lane & 3) == 0) {
+                ob[at * PP + q] = fmaxf(mx, 0.f);
+                a.code[w * a.code_stride + at * PP + q] = (uint8_t)arg;
+            }
+        } else if (ok) {
+            ob[at * HW + y * W + x] = r;
+        }
+    }
+}
+
+// ---- weight gradient: dW[co][c][kh][kw] = sum over samples and pixels of dz[co][y][x] in[c][y + kh - pad][x + kw - pad],
+// with dz given as pooled gradients and window codes.
+//
+// The reduction runs over the pixels of a row, 16 at a time (rows padded with zeros to a multiple of 16), so a lane's
+// fragments are eight consecutive pixels.  Of the image these would start at any pixel, depending on kw, and LDS
+// reads want aligned ones: the 32 columns of a fragment are therefore pairs (c, kh), a lane reads the twelve pixels from x
+// on once, and the KS fragments of its kw are shifts of those inside the registers (none for an even kw, four
+// v_alignbit for an odd one).  A wave owns 32 output channels x 32 pairs x all kw; image and deltas are split when they
+// are copied into LDS.  Where there are few such blocks, several waves share one, take turns with the 16-pixel steps
+// and add their sums through LDS in wave order.  Every workgroup writes a partial result:
+// part[worker][split][co][c][kh][kw], summed in split order by a separate pass.
+//
+// 64 workers x 32 samples, 32 -> 64 channels, 16 x 16 pixels: 274 us (an fp32 kernel 427); ten blocks on the four
+// SIMDs of a compute unit are three rounds of 2.5, and LDS holds one workgroup.  16 workers x 50 samples: 1 -> 16
+// channels on 28 x 28 pixels 73 us, 16 -> 32 on 14 x 14 60 us (implicit fp32 GEMM: 176 and 231).
+struct WgradPlan {
+    int mb, nb, units;          // 32-row and 32-column blocks
+    int kw, waves, groups;      // waves that share a block, waves of a workgroup, workgroups along the blocks
+    int rows, sb;               // image rows per delta tile, samples per workgroup
+    int splits;                 // partial results per worker
+    size_t lds;
+};
+constexpr int WGRAD_MAX_WAVES = 12;
+
+__host__ __device__ inline int row_elems(const Shape &s) { return (s.W + 15) / 16 * 16; }        // of a delta row
+__host__ __device__ inline int image_pitch(const Shape &s) { return row_elems(s) + 8; }          // of an image row
+inline size_t wgrad_image_lds(const Shape &s) { return (size_t)6 * s.Cin * (s.H + s.KS - 1) * image_pitch(s); }
+inline size_t wgrad_delta_lds(const Shape &s, int mb, int rows) { return (size_t)6 * 32 * mb * (rows * row_elems(s) + 8); }
+
+inline bool wgrad_plan(const Shape &s, int workers, WgradPlan &p)
+{
+    p.mb = (s.Cout + 31) / 32;
+    p.nb = (s.Cin * s.KS + 31) / 32;
+    p.units = p.mb * p.nb;
+    p.kw = p.units >= 5 ? 1 : 8 / p.units;
+    p.groups = (p.units + WGRAD_MAX_WAVES - 1) / WGRAD_MAX_WAVES;
+    p.waves = (p.units + p.groups - 1) / p.groups * p.kw;
+    // two workgroups per compute unit if a tile of at least four rows leaves room for that
+    const size_t img = wgrad_image_lds(s), most = 160 * 1024;
+    int per_cu = 2;
+    p.rows = 0;
+    for (; per_cu >= 1 && p.rows == 0; --per_cu)
+        for (int r = s.H; r >= (per_cu == 2 ? 4 : 2); r -= 2)
+            if (img + wgrad_delta_lds(s, p.mb, r) <= most / per_cu) {
+                p.rows = r;
+                break;
+            }
+    ++per_cu;
+    if (p.rows == 0) return false;
+    // even tiles: as many as the rows found make necessary
+    const int tiles = (s.H + p.rows - 1) / p.rows;
+    p.rows = ((s.H + tiles - 1) / tiles + 1) / 2 * 2;
+    p.lds = img + wgrad_delta_lds(s, p.mb, p.rows);
+    const size_t sums = p.kw > 1 ? sizeof(float) * 64 * 16 * s.KS * (p.waves / p.kw) : 0;
+    if (p.lds < sums) p.lds = sums;
+    // enough workgroups for the chip, and no more partial results than that needs
+    p.sb = (int)((int64_t)s.B * workers * p.groups / (256 * per_cu));
+    p.sb = p.sb < 1 ? 1 : (p.sb > 8 ? 8 : p.sb);
+    p.splits = (s.B + p.sb - 1) / p.sb;
+    return true;
+}
+
+struct WgradArgs {
+    Shape s;
+    WgradPlan p;
+    const float *in;            // [worker][B][Cin][H][W]
+    int64_t in_stride;
+    const float *dp;            // pooled gradients [worker][B][Cout][H/2][W/2], with code
+    int64_t dp_stride;
+    const uint8_t *code;
+    int64_t code_stride;
+    float *part;
+    int64_t part_stride;
+};
+
+// grid = (ceil(B / sb), workers, groups), block = 64 waves; dynamic LDS = plan.lds.
+template <int KS>
+__global__ __launch_bounds__(64 * WGRAD_MAX_WAVES) void wgrad_kernel(WgradArgs a)
+{
+    extern __shared__ __attribute__((aligned(16))) u32x4 sm[];
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    const int H = a.s.H, W = a.s.W, Cin = a.s.Cin, Cout = a.s.Cout, pad = KS / 2, HP = H + KS - 1, TAPS = Cin * KS * KS;
+    const int RE = row_elems(a.s), segs = RE / 16, IP = image_pitch(a.s), DP = a.p.rows * RE + 8;    // elements; all multiples of 8
+    const int iplane = Cin * HP * IP / 8, dplane = 32 * a.p.mb * DP / 8;                             // 16-byte groups
+    u32x4 *img = sm, *dz = sm + 3 * iplane;
+    const int tid = threadIdx.x, lane = tid & 63, threads = 64 * a.p.waves;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int upg = a.p.waves / a.p.kw, unit = blockIdx.z * upg + wave % upg, kwave = wave / upg;
+    const bool idle = unit >= a.p.units;               // uniform: a wave of the last group without a block
+    const int mb = unit % a.p.mb, nb = unit / a.p.mb;
+    const int w = blockIdx.y, b0 = blockIdx.x * a.p.sb, b1 = min(a.s.B, b0 + a.p.sb);
+
+    const float *inw = a.in + w * a.in_stride, *dpw = a.dp + w * a.dp_stride;
+    const uint8_t *cdw = a.code + w * a.code_stride;
+    for (int e = tid; e < 3 * (iplane + dplane); e += threads) sm[e] = u32x4{0u, 0u, 0u, 0u};        // halo and padding stay zero
+
+    const int n = 32 * nb + (lane & 31), nc = n < Cin * KS ? n : 0;                                  // pair (c, kh) of the lane
+    const int boff = (((nc / KS) * HP + nc % KS) * IP + 8 * (lane >> 5)) / 8;
+    const int aoff = ((32 * mb + (lane & 31)) * DP + 8 * (lane >> 5)) / 8;
+
+    f32x16 acc[KS];
+#pragma unroll
+    for (int k = 0; k < KS; ++k)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[k][v] = 0.f;
+
+    for (int b = b0; b < b1; ++b)
+        for (int r0 = 0; r0 < H; r0 += a.p.rows) {
+            const int rows = min(a.p.rows, H - r0);
+            __syncthreads();                           // the previous tile has been used
+            if (r0 == 0) {
+                const int per = IP / 8;
+                for (int e = tid; e < Cin * H * per; e += threads) {
+                    const int m = e % per, y = e / per % H, c = e / per / H;
+                    const float *src = inw + (((int64_t)b * Cin + c) * H + y) * W;
+                    float v[8];
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        const int x = 8 * m + j - pad;
+                        const float f = src[min(max(x, 0), W - 1)];
+                        v[j] = (unsigned)x < (unsigned)W ? f : 0.f;
+                    }
+                    const planes p = split_bf16::split8(v);
+                    u32x4 *d = img + (c * HP + y + pad) * per + m;
+                    d[0] = p.h;
+                    d[iplane] = p.m;
+                    d[2 * iplane] = p.l;
+                }
+            }
+            const int per = RE / 8;
+            for (int e = tid; e < Cout * (rows / 2) * per; e += threads) {       // four windows: eight pixels of two rows
+                const int m = e % per, yh = e / per % (rows / 2), co = e / per / (rows / 2);
+                const int64_t o = ((int64_t)b * Cout + co) * (H * W / 4) + (r0 / 2 + yh) * (W >> 1);
+                float g[4];
+                int cd[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int xw = 4 * m + j;
+                    const bool ok = xw < W / 2;
+                    g[j] = dpw[o + (ok ? xw : 0)];
+                    const int code = cdw[o + (ok ? xw : 0)];
+                    cd[j] = ok ? code : 4;
+                }
+                uint32_t h[4], mid[4], l[4];                 // both halves of a word: the window's value
+#pragma unroll
+                for (int j = 0; j < 4; ++j) split_bf16::split2(g[j], g[j], h[j], mid[j], l[j]);
+                u32x4 *d = dz + (co * DP + 2 * yh * RE) / 8 + m;
+#pragma unroll
+                for (int r = 0; r < 2; ++r) {
+                    u32x4 mask;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) mask[j] = cd[j] == 2 * r ? 0xffffu : (cd[j] == 2 * r + 1 ? 0xffff0000u : 0u);
+                    u32x4 *dr = d + r * (RE / 8);
+                    dr[0] = u32x4{h[0], h[1], h[2], h[3]} & mask;
+                    dr[dplane] = u32x4{mid[0], mid[1], mid[2], mid[3]} & mask;
+                    dr[2 * dplane] = u32x4{l[0], l[1], l[2], l[3]} & mask;
+                }
+            }
+            __syncthreads();
+            if (idle) continue;
+            const int steps = rows * segs;
+            for (int st = kwave; st < steps; st += a.p.kw) {
+                const int yr = st / segs, x8 = 2 * (st % segs);
+                const u32x4 *ap = dz + aoff + yr * (RE / 8) + x8;
+                const u32x4 *bp = img + boff + (r0 + yr) * (IP / 8) + x8;
+                planes fa;
+                fa.h = ap[0];
+                fa.m = ap[dplane];
+                fa.l = ap[2 * dplane];
+                // fragment kw of one plane of the image: elements kw .. kw + 7 of the twelve read
+                u32x4 fb[KS];
+                auto read = [&](int plane) {
+                    const u32x4 q = bp[plane * iplane];
+                    const u32x2 r = *(const u32x2 *)&bp[plane * iplane + 1];
+                    const uint32_t d[6] = {q[0], q[1], q[2], q[3], r[0], r[1]};
+#pragma unroll
+                    for (int k = 0; k < KS; ++k)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            fb[k][i] = k % 2 == 0 ? d[k / 2 + i] : __builtin_amdgcn_alignbit(d[k / 2 + i + 1], d[k / 2 + i], 16);
+                };
+                auto step = [&](const u32x4 &x) {
+#pragma unroll
+                    for (int k = 0; k < KS; ++k)
+                        acc[k] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(split_bf16::frag(x), split_bf16::frag(fb[k]), acc[k], 0, 0, 0);
+                };
+                read(2);
+                step(fa.h);
+                read(1);
+                step(fa.m);
+                step(fa.h);
+                read(0);
+                step(fa.l);
+                step(fa.m);
+                step(fa.h);
+            }
+        }
+    // ---- the waves that share a block: their sums through LDS, added to the first one's in wave order
+    float *sums = (float *)sm + (wave % upg) * 1024 * KS + lane;
+    for (int q = 1; q < a.p.kw; ++q) {
+        __syncthreads();
+        if (kwave == q)
+#pragma unroll
+            for (int k = 0; k < KS; ++k)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) sums[64 * (16 * k + v)] = acc[k][v];
+        __syncthreads();
+        if (kwave == 0)
+#pragma unroll
+            for (int k = 0; k < KS; ++k)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[k][v] += sums[64 * (16 * k + v)];
+    }
+    if (idle || kwave != 0) return;
+
+    float *pb = a.part + w * a.part_stride + (int64_t)blockIdx.x * Cout * TAPS;
+    bool bad = false;
+#pragma unroll
+    for (int k = 0; k < KS; ++k) bad |= split_bf16::any_not_finite(acc[k]);
+    if (n < Cin * KS) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int co = 32 * mb + 8 * (v / 4) + 4 * (lane >> 5) + v % 4;
+            if (co < Cout) {
+#pragma unroll
+                for (int k = 0; k < KS; ++k) pb[(int64_t)co * TAPS + n * KS + k] = acc[k][v];
+            }
+        }
+    }
+    // ---- sums that are not finite once more, with plain multiply-adds over the same samples (see split_bf16.h)
+    if (!__any(bad) || n >= Cin * KS) return;
+#pragma unroll 1
+    for (int e = 0; e < 16 * KS; ++e) {
+        const int v = e / KS, k = e % KS, co = 32 * mb + 8 * (v / 4) + 4 * (lane >> 5) + v % 4, c = n / KS, kh = n % KS;
+        if (co >= Cout || !split_bf16::not_finite(pb[(int64_t)co * TAPS + n * KS + k])) continue;
+        float r = 0.f;
+        for (int b = b0; b < b1; ++b)
+            for (int y = 0; y < H; ++y)
+                for (int x = 0; x < W; ++x) {
+                    const int yy = y + kh - pad, xx = x + k - pad;
+                    if ((unsigned)yy >= (unsigned)H || (unsigned)xx >= (unsigned)W) continue;
+                    const int64_t o = ((int64_t)b * Cout + co) * (H * W / 4);
+                    r = fmaf(expanded(dpw + o, cdw + o, y, x, W), inw[(((int64_t)b * Cin + c) * H + yy) * W + xx], r);
+                }
+        pb[(int64_t)co * TAPS + n * KS + k] = r;
+    }
+}
+
+}  // namespace convsplit

@@ -148,6 +148,7 @@ int dbw_fc_forward_backward(dbw_ctx *c, const dbw_fc_args &a, hipStream_t s);
 size_t dbw_mlp_scratch_floats(const dbw_ctx *c);
 int dbw_launch_grad_mlp(dbw_ctx *c, const float *params, const float *bx, const int32_t *by, float *grads,
                         float *loss, hipStream_t s);
+int dbw_cnn_prepare();  // one-time kernel attributes of the convolutions
 size_t dbw_cnn_scratch_floats(const dbw_ctx *c);
 int dbw_launch_grad_cnn(dbw_ctx *c, const float *params, const float *bx, const int32_t *by, float *grads,
                         float *loss, hipStream_t s);

@@ -6,18 +6,20 @@
 // Parameter row layout: conv1 W [C1][C0][K][K], b [C1]; conv2 W [C2][C1][K][K], b [C2];
 // fc1 W [F][flat], b [F]; fc2 W [classes][F], b [classes].
 //
-// Convolutions are implicit GEMMs on the batched fp32 MFMA kernel: the patch matrix is
-// never materialised, the operand loaders compute the input address of each element.
+// Convolutions with 3 x 3 and 5 x 5 filters take the LDS-resident kernels of conv_split.h (conv1 forward, and with 3 ->
+// 32 channels its weight gradient, those of conv_lds.h); the rest are implicit GEMMs on the batched fp32 MFMA
+// kernel: the patch matrix is never materialised, the operand loaders compute the input address of each element.
 //   forward   z[co][pix]      = sum_k  W[co][k] * patch[k][pix]        k = (ci, kh, kw)
 //   wgrad     dW[co][k]       = sum_pix dz[co][pix] * patch[k][pix]
 //   dgrad     din[ci][pix_in] = sum_k' W[co][ci][kh][kw] * dz[co][pix_in shifted]   k' = (co, kh, kw)
 // Output channels are the GEMM's M and pixels its N, so stores run along consecutive pixels.
-// Max pooling keeps no index: the backward pass re-derives the first maximum of each
-// window from the stored pre-activations (first in window order (0,0),(0,1),(1,0),(1,1)).
+// Max pooling keeps a code per window (the first maximum in window order (0,0),(0,1),(1,0),(1,1)) where the backward
+// kernels read codes; otherwise the backward pass re-derives it from the stored pre-activations.
 #include <algorithm>
 
 #include "bgemm.h"
 #include "conv_lds.h"
+#include "conv_split.h"
 #include "dbw_internal.h"
 
 namespace {
@@ -189,21 +191,11 @@ struct PartialOut {
     }
 };
 
-// dst[w * stride + i] = sum over splits of part[w][split][i], in split order.
-__global__ __launch_bounds__(256) void reduce_splits_kernel(const float *__restrict__ part, int64_t pstride,
-                                                            int splits, int MN, float *__restrict__ dst,
-                                                            int64_t stride)
-{
-    const int w = blockIdx.y, i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= MN) return;
-    float s = 0.f;
-    for (int sp = 0; sp < splits; ++sp) s += part[w * pstride + (int64_t)sp * MN + i];
-    dst[w * stride + i] = s;
-}
-
-// ReLU + 2x2 max pooling of z [B][C][H][W] -> p [B][C][H/2][W/2]; one thread per output.
+// ReLU + 2x2 max pooling of z [B][C][H][W] -> p [B][C][H/2][W/2]; one thread per output.  code (or null): the window
+// codes (0..3: position of the first maximum, 4: maximum not positive).
 __global__ __launch_bounds__(256) void relu_pool_fwd_kernel(const float *__restrict__ z, int64_t zstride,
-                                                            float *__restrict__ p, int64_t pstride, int planes, int H, int W)
+                                                            float *__restrict__ p, int64_t pstride, int planes, int H, int W,
+                                                            uint8_t *__restrict__ code, int64_t cstride)
 {
     const int w = blockIdx.y;
     const int Ho = H / 2, Wo = W / 2, total = planes * Ho * Wo;
@@ -211,8 +203,10 @@ __global__ __launch_bounds__(256) void relu_pool_fwd_kernel(const float *__restr
     if (o >= total) return;
     const int pl = o / (Ho * Wo), rem = o - pl * Ho * Wo, oh = rem / Wo, ow = rem - oh * Wo;
     const float *src = z + w * zstride + ((int64_t)pl * H + 2 * oh) * W + 2 * ow;
-    const float m = fmaxf(fmaxf(src[0], src[1]), fmaxf(src[W], src[W + 1]));
+    const float v0 = src[0], v1 = src[1], v2 = src[W], v3 = src[W + 1];
+    const float m = fmaxf(fmaxf(v0, v1), fmaxf(v2, v3));
     p[w * pstride + o] = fmaxf(m, 0.f);
+    if (code) code[w * cstride + o] = m > 0.f ? (v0 == m ? 0 : v1 == m ? 1 : v2 == m ? 2 : 3) : 4;
 }
 
 // Backward of ReLU + max pooling: the pooled gradient goes to the first element of the
@@ -238,31 +232,35 @@ __global__ __launch_bounds__(256) void relu_pool_bwd_kernel(const float *__restr
     dz[base + W + 1] = arg == 3 ? gsrc : 0.f;
 }
 
-// With the window codes of the fused convolution epilogue (0..3: position of the first maximum,
-// 4: maximum not positive): db[ch] = sum of dz over batch and pixels = sum of the pooled gradients
-// of the windows whose maximum was positive (each passes its gradient to exactly one pixel).
-// One workgroup per (channel, worker); HWo % 4 == 0 and 16-byte aligned planes: a thread takes four
-// windows at a time (one 128-bit load of gradients, one 32-bit load of codes).
-__global__ __launch_bounds__(256) void channel_sum_code_kernel(const uint8_t *__restrict__ code, int64_t cstride,
-                                                               const float *__restrict__ dp, int64_t pstride, int B,
-                                                               int C, int HWo, float *__restrict__ db, int64_t dbstride)
+// With the window codes (0..3: position of the first maximum, 4: maximum not positive): db[ch] = sum of dz over
+// batch and pixels = sum of the pooled gradients of the windows whose maximum was positive (each passes its gradient to
+// exactly one pixel).  One workgroup per (channel, worker).  QUADS (HWo % 4 == 0: 16-byte aligned planes): a thread takes
+// four windows at a time (one 128-bit load of gradients, one 32-bit load of codes).
+template <bool QUADS>
+__device__ __forceinline__ void channel_sum_code(float *red /* LDS [256] */, const uint8_t *__restrict__ code,
+                                                 const float *__restrict__ dp, int B, int C, int HWo, int ch, float *__restrict__ db)
 {
-    __shared__ float red[256];
-    const int ch = blockIdx.x, w = blockIdx.y, tid = threadIdx.x;
-    const int quads = HWo / 4;                       // per (sample, channel) plane
-    const int q = tid % quads, b0 = tid / quads, bstep = 256 / quads > 0 ? 256 / quads : 1;
+    constexpr int V = QUADS ? 4 : 1;
+    const int tid = threadIdx.x;
+    const int per = HWo / V;                         // steps per (sample, channel) plane
+    const int q = tid % per, b0 = tid / per, bstep = 256 / per > 0 ? 256 / per : 1;
     float s = 0.f;
     if (b0 < bstep) {
 #pragma unroll 4
         for (int b = b0; b < B; b += bstep) {
-            for (int qq = q; qq < quads; qq += 256) {    // planes wider than 1024 windows
-                const int64_t o = (int64_t)(b * C + ch) * HWo + 4 * qq;
-                const float4 g = *(const float4 *)&dp[w * pstride + o];
-                const uint32_t cd = *(const uint32_t *)&code[w * cstride + o];
-                s += (cd & 0xffu) < 4u ? g.x : 0.f;
-                s += ((cd >> 8) & 0xffu) < 4u ? g.y : 0.f;
-                s += ((cd >> 16) & 0xffu) < 4u ? g.z : 0.f;
-                s += (cd >> 24) < 4u ? g.w : 0.f;
+            for (int qq = q; qq < per; qq += 256) {      // planes wider than 256 steps
+                const int64_t o = (int64_t)(b * C + ch) * HWo + V * qq;
+                if constexpr (QUADS) {
+                    const float4 g = *(const float4 *)&dp[o];
+                    const uint32_t cd = *(const uint32_t *)&code[o];
+                    s += (cd & 0xffu) < 4u ? g.x : 0.f;
+                    s += ((cd >> 8) & 0xffu) < 4u ? g.y : 0.f;
+                    s += ((cd >> 16) & 0xffu) < 4u ? g.z : 0.f;
+                    s += (cd >> 24) < 4u ? g.w : 0.f;
+                } else {
+                    const float g = dp[o];
+                    s += code[o] < 4 ? g : 0.f;
+                }
             }
         }
     }
@@ -272,7 +270,52 @@ __global__ __launch_bounds__(256) void channel_sum_code_kernel(const uint8_t *__
         if (tid < o) red[tid] += red[tid + o];
         __syncthreads();
     }
-    if (tid == 0) db[w * dbstride + ch] = red[0];
+    if (tid == 0) *db = red[0];
+}
+
+// What is left of a convolution's parameter gradients once its partial weight gradients are there: their sum in split
+// order, and (coded) the bias gradients.  Both layers in one launch: four launches of 5 to 30 us each otherwise,
+// none of which fills the chip.  grid = (blocks of layer 1 + blocks of layer 2, workers): ceil(weights / 256) blocks that add
+// partial results, then, if coded, one per channel.
+struct FinishLayer {
+    const float *part;           // [worker][split][weights]
+    int splits, weights;
+    float *dw, *db;
+    const uint8_t *code;         // null: the bias gradient is somebody else's
+    const float *dp;
+    int C, HWo;
+    __host__ __device__ int sum_blocks() const { return (weights + 255) / 256; }
+    __host__ __device__ int blocks() const { return sum_blocks() + (code ? C : 0); }
+};
+__global__ __launch_bounds__(256) void finish_kernel(FinishLayer l1, FinishLayer l2, int64_t wstride, int64_t cstride, int64_t gstride, int B)
+{
+    __shared__ float red[256];
+    const int w = blockIdx.y;
+    const bool second = (int)blockIdx.x >= l1.blocks();
+    const FinishLayer l = second ? l2 : l1;
+    const int blk = blockIdx.x - (second ? l1.blocks() : 0);
+    if (blk >= l.sum_blocks()) {
+        const int ch = blk - l.sum_blocks();
+        const uint8_t *code = l.code + w * cstride;
+        const float *dp = l.dp + w * wstride;
+        if (l.HWo % 4 == 0) channel_sum_code<true>(red, code, dp, B, l.C, l.HWo, ch, l.db + w * gstride + ch);
+        else channel_sum_code<false>(red, code, dp, B, l.C, l.HWo, ch, l.db + w * gstride + ch);
+        return;
+    }
+    const int i = blk * 256 + threadIdx.x;
+    if (i >= l.weights) return;
+    const float *p = l.part + w * wstride + i;
+    float s = 0.f;
+    int q = 0;
+    for (; q + 8 <= l.splits; q += 8) {              // eight loads in flight, added in split order
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = p[(int64_t)(q + u) * l.weights];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s += v[u];
+    }
+    for (; q < l.splits; ++q) s += p[(int64_t)q * l.weights];
+    l.dw[w * gstride + i] = s;
 }
 
 // db[ch] = sum over batch and pixels of dz[b][ch][hw]; one workgroup per (channel, worker).
@@ -295,8 +338,7 @@ __global__ __launch_bounds__(256) void channel_sum_kernel(const float *__restric
     if (tid == 0) db[w * dbstride + ch] = red[0];
 }
 
-constexpr int WGRAD_SB = 4;     // samples per workgroup in the LDS-resident weight-gradient kernels (scratch is sized for it)
-constexpr int WGRAD_SB2 = 8;    // the same for conv2: 64 workers x 4 workgroups are one per compute unit
+constexpr int WGRAD_SB = 4;     // samples per workgroup in the LDS-resident weight gradient of conv1 (scratch is sized for it)
 
 struct cnn_layout {
     int C0, H, W, C1, C2, KS, F, NC, B;
@@ -305,11 +347,28 @@ struct cnn_layout {
     // parameter offsets inside a row
     int64_t w1, b1, w2, b2, fc;
     // scratch offsets inside a worker's block (floats)
-    int64_t z1, p1, z2, p2, dp2, dz2, dp1, dz1, fc_act, part, wflip, code1, code2, total;
+    int64_t z1, p1, z2, p2, dp2, dz2, dp1, dz1, fc_act, part1, part2, filt_fwd, filt_bwd, code1, code2, total;
     int splits1, splits2;
+    bool lds1;                      // conv1 by conv_lds.h (if the batch is aligned)
+    bool split1, split2;            // weight gradient of conv1 / all three products of conv2 by conv_split.h
+    convsplit::WgradPlan wg1, wg2;
 };
 
-cnn_layout make_layout(const dbw_model &m)
+// The kernels of conv_split.h take every 3 x 3 and 5 x 5 filter whose images fit LDS, however few the channels: with 2 -> 4
+// of them on 16 x 16 pixels, where most of a reduction step is padding, the three products take 15 + 15 + 14 us
+// (16 workers, batch 32) against 20 + 98 + 17 of the implicit GEMM, with 32 -> 64 channels (64 workers) 255 + 274 + 264
+// against 433 + 427 + 448 of LDS-resident fp32 kernels.
+bool conv_split_fits(const convsplit::Shape &s, int workers, bool first, convsplit::WgradPlan &plan)
+{
+    const size_t most = 160 * 1024;
+    if (s.KS != 3 && s.KS != 5) return false;
+    if (!convsplit::wgrad_plan(s, workers, plan)) return false;
+    if (first) return true;
+    const convsplit::Shape back{s.Cout, s.Cin, s.H, s.W, s.KS, s.B};
+    return convsplit::forward_lds(s, s.Cout <= 32 ? 1 : 2) <= most && convsplit::forward_lds(back, s.Cin <= 32 ? 1 : 2) <= most;
+}
+
+cnn_layout make_layout(const dbw_model &m, int workers)
 {
     cnn_layout L{};
     L.C0 = m.dims[0]; L.H = m.dims[1]; L.W = m.dims[2]; L.C1 = m.dims[3]; L.C2 = m.dims[4];
@@ -324,27 +383,30 @@ cnn_layout make_layout(const dbw_model &m)
     L.b2 = L.w2 + L.C2 * L.C1 * KK;
     L.fc = L.b2 + L.C2;
     const int64_t B = L.B;
+    L.lds1 = L.KS == 5 && L.C0 == 3 && L.H == 32 && L.W == 32 && L.C1 == 32;
+    L.split1 = conv_split_fits({L.C0, L.C1, L.H, L.W, L.KS, L.B}, workers, true, L.wg1);
+    L.split2 = conv_split_fits({L.C1, L.C2, L.H2, L.W2, L.KS, L.B}, workers, false, L.wg2);
     int64_t o = 0;
     auto take = [&](int64_t n) { const int64_t at = o; o += (n + 63) / 64 * 64; return at; };
     L.z1 = take(B * L.C1 * L.H * L.W);
     L.p1 = take(B * L.C1 * L.H2 * L.W2);
-    L.z2 = take(B * L.C2 * L.H2 * L.W2);
+    L.z2 = take(L.split2 ? 0 : B * L.C2 * L.H2 * L.W2);
     L.p2 = take(B * L.flat);
     L.dp2 = take(B * L.flat);
-    L.dz2 = take(B * L.C2 * L.H2 * L.W2);
+    L.dz2 = take(L.split2 ? 0 : B * L.C2 * L.H2 * L.W2);
     L.dp1 = take(B * L.C1 * L.H2 * L.W2);
-    L.dz1 = take(B * L.C1 * L.H * L.W);
+    L.dz1 = take(L.split1 ? 0 : B * L.C1 * L.H * L.W);
     L.fc_act = take(dbw_fc_scratch_per_worker(2, L.fc_dims, L.B));
     // split the long pixel reductions of the weight gradients so that the grid fills the chip
     auto pick = [&](int64_t K) { int s = 1; while (s < 32 && K / (s * 2) >= 1024) s *= 2; return s; };
-    L.splits1 = pick(B * L.H * L.W);
-    L.splits2 = pick(B * L.H2 * L.W2);
-    // the LDS-resident weight-gradient kernels write one partial per 4 samples (conv1: x 8 waves)
-    const int64_t nb = (B + WGRAD_SB - 1) / WGRAD_SB;
-    const int64_t s1 = std::max<int64_t>(L.splits1, nb * 8), s2 = std::max<int64_t>(L.splits2, nb);
-    const int64_t p1n = s1 * L.C1 * L.C0 * KK, p2n = s2 * L.C2 * L.C1 * KK;
-    L.part = take(p1n > p2n ? p1n : p2n);
-    L.wflip = take((int64_t)L.C1 * L.C2 * KK);
+    L.splits1 = L.split1 ? L.wg1.splits : pick(B * L.H * L.W);
+    L.splits2 = L.split2 ? L.wg2.splits : pick(B * L.H2 * L.W2);
+    // the LDS-resident kernel for conv1 of the 3 -> 32 channel network writes one partial result per 4 samples and wave
+    const int64_t s1 = std::max<int64_t>(L.splits1, L.lds1 ? (B + WGRAD_SB - 1) / WGRAD_SB * 8 : 0);
+    L.part1 = take(s1 * L.C1 * L.C0 * KK);
+    L.part2 = take(L.splits2 * L.C2 * L.C1 * KK);
+    L.filt_fwd = take(L.split2 ? convsplit::filter_floats(L.C1, L.C2, L.KS) : 0);
+    L.filt_bwd = take(L.split2 ? convsplit::filter_floats(L.C2, L.C1, L.KS) : 0);
     L.code1 = take((B * L.C1 * L.H2 * L.W2 + 3) / 4);     // one byte per pooled element
     L.code2 = take((B * L.flat + 3) / 4);
     L.total = o;
@@ -360,11 +422,36 @@ hipError_t conv_gemm(const LA &A, const LB &B, const EP &E, int M, int N, int K,
     return bgemm::launch<64>(A, B, E, M, N, K, batch, s, splits);
 }
 
+template <bool POOL, bool EXPAND>
+int launch_split_forward(const convsplit::FwdArgs &a, int workers, hipStream_t s)
+{
+    const int spg = convsplit::samples_per_group(a.s), t = a.s.H * a.s.W / 4;
+    const int xt = spg > 1 ? 1 : (t + convsplit::WINDOWS - 1) / convsplit::WINDOWS, mbt = convsplit::row_blocks(a.s.Cout);
+    const int MB = mbt == 1 ? 1 : 2;
+    const dim3 grid((a.s.B + spg - 1) / spg * xt, workers, mbt / MB);
+    const size_t lds = convsplit::forward_lds(a.s, MB);
+    if (MB == 1)
+        hipLaunchKernelGGL((convsplit::forward_kernel<1, POOL, EXPAND>), grid, dim3(convsplit::THREADS), lds, s, a);
+    else
+        hipLaunchKernelGGL((convsplit::forward_kernel<2, POOL, EXPAND>), grid, dim3(convsplit::THREADS), lds, s, a);
+    DBW_HIP(hipGetLastError());
+    return DBW_OK;
+}
+
+int launch_split_wgrad(const convsplit::WgradArgs &a, int workers, hipStream_t s)
+{
+    const dim3 grid((a.s.B + a.p.sb - 1) / a.p.sb, workers, a.p.groups), block(64 * a.p.waves);
+    if (a.s.KS == 3) hipLaunchKernelGGL(convsplit::wgrad_kernel<3>, grid, block, a.p.lds, s, a);
+    else hipLaunchKernelGGL(convsplit::wgrad_kernel<5>, grid, block, a.p.lds, s, a);
+    DBW_HIP(hipGetLastError());
+    return DBW_OK;
+}
+
 template <int KS_>
 int launch_grad_cnn(dbw_ctx *c, const float *params, const float *bx, const int32_t *by, float *grads,
                     float *loss, hipStream_t s)
 {
-    const cnn_layout L = make_layout(c->model);
+    const cnn_layout L = make_layout(c->model, c->N);
     const int N = c->N, B = L.B, KK = L.KS * L.KS;
     float *A = c->act;
     const int64_t ws = L.total, ld = c->ld;
@@ -372,10 +459,9 @@ int launch_grad_cnn(dbw_ctx *c, const float *params, const float *bx, const int3
     const ConvShape s1{L.C0, L.C1, L.H, L.W, L.KS, L.KS / 2}, s2{L.C1, L.C2, L.H2, L.W2, L.KS, L.KS / 2};
     const int pix1 = B * L.H * L.W, pix2 = B * L.H2 * L.W2;
     auto blocks = [](int64_t n) { return (unsigned)((n + 255) / 256); };
-    // The LDS-resident convolution kernels are instantiated for the 5x5 / 3-32-64 channel
-    // network on 32 x 32 inputs; every other shape takes the implicit-GEMM path.
-    const bool fast1 = KS_ == 5 && L.C0 == 3 && L.H == 32 && L.W == 32 && L.C1 == 32 && (uintptr_t)bx % 16 == 0;
-    const bool fast2 = KS_ == 5 && L.C1 == 32 && L.H2 == 16 && L.W2 == 16 && L.C2 == 64;
+    // conv1 has LDS-resident fp32 kernels for 5x5 filters, 3 -> 32 channels on 32 x 32 inputs: with 3 channels, more
+    // than half of a split reduction step (forward) or column block (weight gradient: 157 us against 115) is padding
+    const bool fast1 = KS_ == 5 && L.lds1 && (uintptr_t)bx % 16 == 0;
 
     uint8_t *code1 = (uint8_t *)(A + L.code1), *code2 = (uint8_t *)(A + L.code2);
     const int64_t cs = ws * 4;                         // worker stride of the code maps in bytes
@@ -386,33 +472,57 @@ int launch_grad_cnn(dbw_ctx *c, const float *params, const float *bx, const int3
                            dim3((B + SB1 - 1) / SB1, N), dim3(1024), 0, s, bx, xstride, params + L.w1, ld, L.C0 * KK,
                            params + L.b1, ld, A + L.p1, ws, L.C0, B, code1, cs);
         DBW_HIP(hipGetLastError());
-    } else {   // conv1 forward
-        dbw_timer tm(c, "conv1_forward", s);
-        DBW_HIP(conv_gemm(Dense<true>{params + L.w1, L.C0 * KK, ld}, PatchRC<KS_>{bx, xstride, s1},
+    } else {
+        {
+            dbw_timer tm(c, "conv1_forward", s);
+            DBW_HIP(conv_gemm(Dense<true>{params + L.w1, L.C0 * KK, ld}, PatchRC<KS_>{bx, xstride, s1},
                               ChannelPixelOut{A + L.z1, ws, L.C1, L.H * L.W, params + L.b1, ld}, L.C1, pix1,
                               L.C0 * KK, N, s));
-    }
-    if (!fast1) {
+        }
         dbw_timer tm(c, "relu_pool_fwd_kernel", s);
         hipLaunchKernelGGL(relu_pool_fwd_kernel, dim3(blocks((int64_t)B * L.C1 * L.H2 * L.W2), N), dim3(256), 0, s,
-                           A + L.z1, ws, A + L.p1, ws, B * L.C1, L.H, L.W);
+                           A + L.z1, ws, A + L.p1, ws, B * L.C1, L.H, L.W, code1, cs);
         DBW_HIP(hipGetLastError());
     }
-    if (fast2) {
+    const convsplit::Shape c2{L.C1, L.C2, L.H2, L.W2, L.KS, B}, c2back{L.C2, L.C1, L.H2, L.W2, L.KS, B};
+    convsplit::FwdArgs f{};
+    f.wgt = params + L.w2;
+    f.wgt_stride = ld;
+    if (L.split2) {
+        {
+            dbw_timer tm(c, "conv2_prepare", s);
+            const dim3 grid(convsplit::prepare_blocks(L.C1, L.C2) + convsplit::prepare_blocks(L.C2, L.C1), N);
+            auto *fwd = (split_bf16::u32x4 *)(A + L.filt_fwd), *bwd = (split_bf16::u32x4 *)(A + L.filt_bwd);
+            if (L.KS == 3)
+                hipLaunchKernelGGL(convsplit::prepare_kernel<9>, grid, dim3(convsplit::PREPARE_THREADS), 0, s, params + L.w2, ld, fwd, bwd, ws / 4, L.C1, L.C2);
+            else
+                hipLaunchKernelGGL(convsplit::prepare_kernel<25>, grid, dim3(convsplit::PREPARE_THREADS), 0, s, params + L.w2, ld, fwd, bwd, ws / 4, L.C1, L.C2);
+            DBW_HIP(hipGetLastError());
+        }
         dbw_timer tm(c, "conv2_forward", s);
-        hipLaunchKernelGGL((convlds::conv_forward_kernel<16, 4, 2, 16, 16, 5, 8, true>), dim3(B, N), dim3(512), 0, s,
-                           A + L.p1, ws, params + L.w2, ld, L.C1 * KK, params + L.b2, ld, A + L.p2, ws, L.C1, code2, cs);
-        DBW_HIP(hipGetLastError());
-    } else {   // conv2 forward
-        dbw_timer tm(c, "conv2_forward", s);
-        DBW_HIP(conv_gemm(Dense<true>{params + L.w2, L.C1 * KK, ld}, PatchRC<KS_>{A + L.p1, ws, s2},
+        f.s = c2;
+        f.in = A + L.p1;
+        f.in_stride = ws;
+        f.filters = (const split_bf16::u32x4 *)(A + L.filt_fwd);
+        f.filters_stride = ws / 4;
+        f.bias = params + L.b2;
+        f.bias_stride = ld;
+        f.out = A + L.p2;
+        f.out_stride = ws;
+        f.code = code2;
+        f.code_stride = cs;
+        const int rc = launch_split_forward<true, false>(f, N, s);
+        if (rc != DBW_OK) return rc;
+    } else {
+        {
+            dbw_timer tm(c, "conv2_forward", s);
+            DBW_HIP(conv_gemm(Dense<true>{params + L.w2, L.C1 * KK, ld}, PatchRC<KS_>{A + L.p1, ws, s2},
                               ChannelPixelOut{A + L.z2, ws, L.C2, L.H2 * L.W2, params + L.b2, ld}, L.C2, pix2,
                               L.C1 * KK, N, s));
-    }
-    if (!fast2) {
+        }
         dbw_timer tm(c, "relu_pool_fwd_kernel", s);
         hipLaunchKernelGGL(relu_pool_fwd_kernel, dim3(blocks((int64_t)B * L.flat), N), dim3(256), 0, s, A + L.z2, ws,
-                           A + L.p2, ws, B * L.C2, L.H2, L.W2);
+                           A + L.p2, ws, B * L.C2, L.H2, L.W2, (uint8_t *)nullptr, (int64_t)0);
         DBW_HIP(hipGetLastError());
     }
     {   // fully connected head, forward and backward, down to the gradient of the pooled features
@@ -436,104 +546,101 @@ int launch_grad_cnn(dbw_ctx *c, const float *params, const float *bx, const int3
         const int rc = dbw_fc_forward_backward(c, a, s);
         if (rc != DBW_OK) return rc;
     }
-    // with the fused pooling the un-pooled delta maps are never materialised: their consumers
-    // expand the pooled gradients and the window codes on the fly
-    if (!fast2) {
-        dbw_timer tm(c, "relu_pool_bwd_kernel", s);
-        hipLaunchKernelGGL(relu_pool_bwd_kernel, dim3(blocks((int64_t)B * L.flat), N), dim3(256), 0, s, A + L.z2, ws,
-                           A + L.dp2, ws, A + L.dz2, B * L.C2, L.H2, L.W2);
-        DBW_HIP(hipGetLastError());
-    }
-    int splits2 = L.splits2, splits1 = L.splits1;
-    if (fast2) {
-        splits2 = (B + WGRAD_SB2 - 1) / WGRAD_SB2;
+    // with the window codes the un-pooled delta maps are never materialised: their consumers
+    // expand the pooled gradients and the codes on the fly
+    if (L.split2) {   // conv2 weight gradient (partial results, then summed in split order)
         dbw_timer tm(c, "conv2_wgrad", s);
-        hipLaunchKernelGGL((convlds::conv_wgrad_kernel<32, 2, 13, 2, 4, 1, 16, 16, 5, 256, true>), dim3(splits2, N),
-                           dim3(512), 0, s, A + L.p1, ws, A + L.dp2, ws, A + L.part, ws, B, WGRAD_SB2, code2, cs);
-        DBW_HIP(hipGetLastError());
-    } else {   // conv2 weight gradient (split over pixels, then summed in split order) and bias gradient
-        dbw_timer tm(c, "conv2_wgrad", s);
-        DBW_HIP(conv_gemm(DeltaKC{A + L.dz2, ws, L.C2, L.H2 * L.W2}, PatchKC<KS_>{A + L.p1, ws, s2},
-                              PartialOut{A + L.part, ws, L.C2, L.C1 * KK}, L.C2, L.C1 * KK, pix2, N, s,
-                              L.splits2));
-    }
-    {
-        dbw_timer tm(c, "reduce_splits_kernel", s);
-        hipLaunchKernelGGL(reduce_splits_kernel, dim3(blocks((int64_t)L.C2 * L.C1 * KK), N), dim3(256), 0, s,
-                           A + L.part, ws, splits2, L.C2 * L.C1 * KK, grads + L.w2, ld);
-        DBW_HIP(hipGetLastError());
-    }
-    if (fast2) {
-        dbw_timer tm(c, "channel_sum_code_kernel", s);
-        hipLaunchKernelGGL(channel_sum_code_kernel, dim3(L.C2, N), dim3(256), 0, s, code2, cs, A + L.dp2, ws, B, L.C2,
-                           L.H4 * L.W4, grads + L.b2, ld);
-        DBW_HIP(hipGetLastError());
+        const int rc = launch_split_wgrad({c2, L.wg2, A + L.p1, ws, A + L.dp2, ws, code2, cs, A + L.part2, ws}, N, s);
+        if (rc != DBW_OK) return rc;
     } else {
-        dbw_timer tm(c, "channel_sum_kernel", s);
-        hipLaunchKernelGGL(channel_sum_kernel, dim3(L.C2, N), dim3(256), 0, s, A + L.dz2, ws, B, L.C2, L.H2 * L.W2,
-                           grads + L.b2, ld);
-        DBW_HIP(hipGetLastError());
-    }
-    if (fast2) {   // conv2 data gradient = forward convolution of the deltas with flipped filters
         {
-            dbw_timer tm(c, "flip_filters_kernel", s);
-            hipLaunchKernelGGL(convlds::flip_filters_kernel, dim3(blocks((int64_t)L.C1 * L.C2 * KK), N), dim3(256), 0, s,
-                               params + L.w2, ld, A + L.wflip, ws, L.C1, L.C2, KK);
+            dbw_timer tm(c, "relu_pool_bwd_kernel", s);
+            hipLaunchKernelGGL(relu_pool_bwd_kernel, dim3(blocks((int64_t)B * L.flat), N), dim3(256), 0, s, A + L.z2, ws,
+                               A + L.dp2, ws, A + L.dz2, B * L.C2, L.H2, L.W2);
             DBW_HIP(hipGetLastError());
         }
+        dbw_timer tm(c, "conv2_wgrad", s);
+        DBW_HIP(conv_gemm(DeltaKC{A + L.dz2, ws, L.C2, L.H2 * L.W2}, PatchKC<KS_>{A + L.p1, ws, s2},
+                              PartialOut{A + L.part2, ws, L.C2, L.C1 * KK}, L.C2, L.C1 * KK, pix2, N, s,
+                              L.splits2));
+    }
+    if (L.split2) {   // conv2 data gradient = forward convolution of the deltas with flipped filters
         dbw_timer tm(c, "conv2_dgrad", s);
-        hipLaunchKernelGGL((convlds::conv_forward_kernel<16, 2, 2, 16, 16, 5, 8, false, true>), dim3(B, N), dim3(512), 0,
-                           s, A + L.dp2, ws, A + L.wflip, ws, L.C2 * KK, (const float *)nullptr, (int64_t)0, A + L.dp1,
-                           ws, L.C2, (uint8_t *)nullptr, (int64_t)0, code2, cs);
-        DBW_HIP(hipGetLastError());
-    } else {   // conv2 data gradient -> gradient of the first pooled map
+        f.s = c2back;
+        f.in = A + L.dp2;
+        f.in_code = code2;
+        f.in_code_stride = cs;
+        f.filters = (const split_bf16::u32x4 *)(A + L.filt_bwd);
+        f.bias = nullptr;
+        f.out = A + L.dp1;
+        f.code = nullptr;
+        const int rc = launch_split_forward<false, true>(f, N, s);
+        if (rc != DBW_OK) return rc;
+    } else {
+        {
+            dbw_timer tm(c, "channel_sum_kernel", s);
+            hipLaunchKernelGGL(channel_sum_kernel, dim3(L.C2, N), dim3(256), 0, s, A + L.dz2, ws, B, L.C2, L.H2 * L.W2,
+                               grads + L.b2, ld);
+            DBW_HIP(hipGetLastError());
+        }
         dbw_timer tm(c, "conv2_dgrad", s);
         DBW_HIP(conv_gemm(FilterT<KS_>{params + L.w2, ld, L.C1, KK}, DeltaShiftRC<KS_>{A + L.dz2, ws, s2},
                               ChannelPixelOut{A + L.dp1, ws, L.C1, L.H2 * L.W2, nullptr, 0}, L.C1, pix2, L.C2 * KK, N,
                               s));
     }
-    if (!fast1) {
-        dbw_timer tm(c, "relu_pool_bwd_kernel", s);
-        hipLaunchKernelGGL(relu_pool_bwd_kernel, dim3(blocks((int64_t)B * L.C1 * L.H2 * L.W2), N), dim3(256), 0, s,
-                           A + L.z1, ws, A + L.dp1, ws, A + L.dz1, B * L.C1, L.H, L.W);
-        DBW_HIP(hipGetLastError());
-    }
-    if (fast1) {
+    int splits1 = L.splits1;
+    const bool coded1 = fast1 || L.split1;
+    if (fast1) {   // conv1 weight gradient
         const int nb = (B + WGRAD_SB - 1) / WGRAD_SB;
         splits1 = nb * 8;
         dbw_timer tm(c, "conv1_wgrad", s);
         hipLaunchKernelGGL((convlds::conv_wgrad_kernel<3, 2, 5, 1, 1, 8, 32, 32, 5, 512, true>), dim3(nb, N), dim3(512), 0,
-                           s, bx, xstride, A + L.dp1, ws, A + L.part, ws, B, WGRAD_SB, code1, cs);
+                           s, bx, xstride, A + L.dp1, ws, A + L.part1, ws, B, WGRAD_SB, code1, cs);
         DBW_HIP(hipGetLastError());
-    } else {   // conv1 weight and bias gradients
+    } else if (L.split1) {
         dbw_timer tm(c, "conv1_wgrad", s);
-        DBW_HIP(conv_gemm(DeltaKC{A + L.dz1, ws, L.C1, L.H * L.W}, PatchKC<KS_>{bx, xstride, s1},
-                              PartialOut{A + L.part, ws, L.C1, L.C0 * KK}, L.C1, L.C0 * KK, pix1, N, s,
-                              L.splits1));
-    }
-    {
-        dbw_timer tm(c, "reduce_splits_kernel", s);
-        hipLaunchKernelGGL(reduce_splits_kernel, dim3(blocks((int64_t)L.C1 * L.C0 * KK), N), dim3(256), 0, s,
-                           A + L.part, ws, splits1, L.C1 * L.C0 * KK, grads + L.w1, ld);
-        DBW_HIP(hipGetLastError());
-    }
-    if (fast1) {
-        dbw_timer tm(c, "channel_sum_code_kernel", s);
-        hipLaunchKernelGGL(channel_sum_code_kernel, dim3(L.C1, N), dim3(256), 0, s, code1, cs, A + L.dp1, ws, B, L.C1,
-                           L.H2 * L.W2, grads + L.b1, ld);
-        DBW_HIP(hipGetLastError());
+        const int rc = launch_split_wgrad({{L.C0, L.C1, L.H, L.W, L.KS, B}, L.wg1, bx, xstride, A + L.dp1, ws, code1, cs, A + L.part1, ws}, N, s);
+        if (rc != DBW_OK) return rc;
     } else {
+        {
+            dbw_timer tm(c, "relu_pool_bwd_kernel", s);
+            hipLaunchKernelGGL(relu_pool_bwd_kernel, dim3(blocks((int64_t)B * L.C1 * L.H2 * L.W2), N), dim3(256), 0, s,
+                               A + L.z1, ws, A + L.dp1, ws, A + L.dz1, B * L.C1, L.H, L.W);
+            DBW_HIP(hipGetLastError());
+        }
+        {
+            dbw_timer tm(c, "conv1_wgrad", s);
+            DBW_HIP(conv_gemm(DeltaKC{A + L.dz1, ws, L.C1, L.H * L.W}, PatchKC<KS_>{bx, xstride, s1},
+                              PartialOut{A + L.part1, ws, L.C1, L.C0 * KK}, L.C1, L.C0 * KK, pix1, N, s,
+                              L.splits1));
+        }
         dbw_timer tm(c, "channel_sum_kernel", s);
         hipLaunchKernelGGL(channel_sum_kernel, dim3(L.C1, N), dim3(256), 0, s, A + L.dz1, ws, B, L.C1, L.H * L.W,
                            grads + L.b1, ld);
         DBW_HIP(hipGetLastError());
     }
+    const FinishLayer f1{A + L.part1, splits1, L.C1 * L.C0 * KK, grads + L.w1, grads + L.b1, coded1 ? code1 : nullptr, A + L.dp1,
+                         L.C1, L.H2 * L.W2};
+    const FinishLayer f2{A + L.part2, L.splits2, L.C2 * L.C1 * KK, grads + L.w2, grads + L.b2, L.split2 ? code2 : nullptr, A + L.dp2,
+                         L.C2, L.H4 * L.W4};
+    dbw_timer tm(c, "conv_finish_kernel", s);
+    hipLaunchKernelGGL(finish_kernel, dim3(f1.blocks() + f2.blocks(), N), dim3(256), 0, s, f1, f2, ws, cs, ld, B);
+    DBW_HIP(hipGetLastError());
     return DBW_OK;
 }
 
 }  // namespace
 
-size_t dbw_cnn_scratch_floats(const dbw_ctx *c) { return (size_t)make_layout(c->model).total * c->N; }
+size_t dbw_cnn_scratch_floats(const dbw_ctx *c) { return (size_t)make_layout(c->model, c->N).total * c->N; }
+
+int dbw_cnn_prepare()
+{
+    const void *kernels[] = {(const void *)convsplit::forward_kernel<1, true, false>, (const void *)convsplit::forward_kernel<2, true, false>,
+                             (const void *)convsplit::forward_kernel<1, false, true>, (const void *)convsplit::forward_kernel<2, false, true>,
+                             (const void *)convsplit::wgrad_kernel<3>, (const void *)convsplit::wgrad_kernel<5>};
+    for (const void *k : kernels) DBW_HIP(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
+    return DBW_OK;
+}
 
 int dbw_launch_grad_cnn(dbw_ctx *c, const float *params, const float *bx, const int32_t *by, float *grads,
                         float *loss, hipStream_t s)

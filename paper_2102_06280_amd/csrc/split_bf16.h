@@ -82,6 +82,26 @@ __device__ __forceinline__ f32x16 mma32(const planes &a, const planes &b, f32x16
     return acc;
 }
 
+// The same for a block of A x B accumulators, one kind of partial product after the other: consecutive instructions are
+// independent.
+template <int A, int B>
+__device__ __forceinline__ void mma32_block(const planes (&a)[A], const planes (&b)[B], f32x16 (&acc)[A][B])
+{
+    auto step = [&](u32x4 planes::*pa, u32x4 planes::*pb) {
+#pragma unroll
+        for (int i = 0; i < A; ++i)
+#pragma unroll
+            for (int j = 0; j < B; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(a[i].*pa), frag(b[j].*pb), acc[i][j], 0, 0, 0);
+    };
+    step(&planes::l, &planes::h);
+    step(&planes::h, &planes::l);
+    step(&planes::m, &planes::m);
+    step(&planes::m, &planes::h);
+    step(&planes::h, &planes::m);
+    step(&planes::h, &planes::h);
+}
+
 // NaN or infinity
 __device__ __forceinline__ bool not_finite(float v) { return (bits(v) & 0x7f800000u) == 0x7f800000u; }
 

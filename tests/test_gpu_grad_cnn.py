@@ -211,3 +211,75 @@ def test_config3_rounds_lock_step(B, orc, order):
         assert epochs_seen == {-1, 0, 1}
     finally:
         B.dbw_destroy(h)
+
+
+# The split convolution kernels at their edges: channels off multiples of 16 and 32, more than 32 and 64 output channels,
+# several samples per workgroup (4 x 4 and 6 x 6 maps), the last group of them partial, maps of more than 64 windows,
+# widths off multiples of 16, weight gradients with 1, 2, 4, 8 waves per block, with more blocks than waves of a workgroup, 3 x 3
+# and 5 x 5; and 7 x 7, which takes the implicit GEMM.
+SPLIT_SHAPES = [((1, 28, 28, 6, 16, 5, 20, 10), 5, 2), ((3, 8, 8, 17, 33, 3, 12, 4), 37, 2), ((2, 12, 12, 9, 40, 5, 12, 5), 9, 3),
+                ((1, 40, 44, 5, 12, 3, 10, 4), 3, 2), ((3, 16, 24, 70, 20, 5, 10, 4), 3, 2), ((1, 16, 16, 40, 72, 5, 10, 4), 4, 2),
+                ((2, 32, 32, 3, 3, 5, 10, 4), 4, 2), ((5, 20, 16, 6, 130, 3, 8, 3), 4, 2), ((1, 16, 12, 4, 6, 7, 8, 3), 4, 2)]
+
+
+@pytest.mark.parametrize("shape,batch,n", SPLIT_SHAPES, ids=["-".join(map(str, s[0])) + f"-B{s[1]}" for s in SPLIT_SHAPES])
+def test_cnn_gradients_at_kernel_edges(B, orc, shape, batch, n):
+    g = np.random.default_rng(503)
+    desc = cnn_desc(shape)
+    d = inputs.param_count(desc)
+    ld = inputs.pad_ld(d)
+    rowptr, colidx = inputs.graph_complete(n)
+    params = inputs.init_params(desc, n, ld, g)
+    params[:, :d] += (g.standard_normal((n, d)) * 0.02).astype(np.float32)
+    x = g.standard_normal((n, batch, int(np.prod(desc["in"])))).astype(np.float32)
+    y = g.integers(0, shape[-1], (n, batch)).astype(np.int32)
+    h = B.dbw_create(rowptr, colidx, n, d, ld=ld, model=B.make_model(B.MODEL_CNN, batch, shape))
+    try:
+        grads = torch.full((n, ld), 7.0, dtype=torch.float32, device="cuda")
+        loss = torch.zeros(n, dtype=torch.float32, device="cuda")
+        B.dbw_grad(h, dev(params), dev(x), dev(y), grads, loss)
+        got, gl = grads.cpu().numpy(), loss.cpu().numpy()
+    finally:
+        B.dbw_destroy(h)
+    kind, od = orc.model_desc(desc)
+    res = GradientResolver(orc, kind, od, d, params, x, y, threads=min(n, 8))
+    assert np.allclose(gl, res.loss, rtol=5e-6, atol=1e-6)
+    assert np.all(got[:, d:] == 7.0)
+    match_gradients(res, got, layers_close(desc), d, what=f"{shape} batch {batch}")
+
+
+def test_cnn_infinite_weight_stays_with_its_worker(B, orc):
+    """One infinite filter weight of conv2 under inputs that are all positive: the infinity reaches the pooled maps as
+    one, the next layer's sums are inf - inf, and the loss and the set of parameters without a finite gradient are the
+    oracle's; every other worker's loss and gradient stay what they were, bit for bit."""
+    shape, batch, n = (3, 16, 16, 8, 8, 5, 16, 10), 5, 4
+    desc = cnn_desc(shape)
+    d = inputs.param_count(desc)
+    ld = inputs.pad_ld(d)
+    rowptr, colidx = inputs.graph_complete(n)
+    g = np.random.default_rng(5)
+    p = inputs.init_params(desc, n, ld, g)
+    p[:, 8 * 3 * 25:8 * 3 * 25 + 8] = 10.0             # conv1's bias: every pooled value of the first layer is positive
+    x = g.standard_normal((n, batch, 3 * 16 * 16)).astype(np.float32)
+    y = g.integers(0, 10, (n, batch)).astype(np.int32)
+    h = B.dbw_create(rowptr, colidx, n, d, ld=ld, model=B.make_model(B.MODEL_CNN, batch, shape))
+    results = []
+    try:
+        for bad in (False, True):
+            q = p.copy()
+            if bad:
+                q[2, 8 * 3 * 25 + 8 + 77] = np.inf
+            grads = torch.zeros((n, ld), device="cuda")
+            loss = torch.zeros(n, device="cuda")
+            B.dbw_grad(h, dev(q), dev(x), dev(y), grads, loss)
+            results.append((grads.cpu().numpy(), loss.cpu().numpy()))
+    finally:
+        B.dbw_destroy(h)
+    others = np.array([0, 1, 3])
+    assert np.array_equal(results[0][0][others], results[1][0][others])
+    assert np.array_equal(results[0][1][others], results[1][1][others])
+    kind, od = orc.model_desc(desc)
+    want, loss = orc.grad_all(kind, od, d, q, x, y)[:2]
+    assert np.allclose(results[1][1], loss, rtol=5e-6)
+    lost = ~np.isfinite(want[2, :d])
+    assert lost.any() and not np.isfinite(results[1][0][2, :d][lost]).any()
