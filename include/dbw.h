@@ -260,7 +260,7 @@ int dbw_consensus_rounds(dbw_ctx *ctx, const float *params_in, float *params_out
  * the graph is passed with every call, as device CSR arrays (same form as dbw_create's host
  * arrays: rowptr [dev, N+1], colidx [dev, nnz], nnz = rowptr[N] given by the host as well), and
  * all working memory (a checked copy of the graph, the selection state of each round, the product
- * of the consensus matrices) is a fixed array of about 1.7 MB inside the library's device image,
+ * of the consensus matrices) is a fixed array of about 2.2 MB inside the library's device image,
  * which every GPU the library runs on holds until the process ends.  The call allocates and frees
  * nothing, records no memset, and does not synchronise.
  *   Limits: N <= 256, nnz <= 256 * 255, ld <= 26 843 545 (DBW_ERR_UNSUPPORTED beyond them); ld = 0

@@ -90,7 +90,7 @@ void free_ctx(dbw_ctx *c)
 {
     if (!c) return;
     void *ptrs[] = {c->rowptr, c->colidx, c->p, c->mask, c->wait, c->listed, c->sel_idx, c->sel_w, c->self_w, c->Wdense,
-                    c->phi[0], c->phi[1], c->phi_frag,
+                    c->phi[0], c->phi[1], c->phi_frag, c->tail_p, c->tail_self, c->tail_idx, c->tail_w,
                     c->err, c->links, c->visited, c->n_visited, c->grads, c->act, c->loss_part, c->loss_ticket};
     for (void *q : ptrs)
         if (q) (void)hipFree(q);
@@ -179,6 +179,12 @@ int fill_ctx(dbw_ctx *c, int32_t N, int64_t d, int64_t nnz64, const int32_t *row
         A(dev_alloc(&c->phi[0], (size_t)c->Npad * c->Npad));
         A(dev_alloc(&c->phi[1], (size_t)c->Npad * c->Npad));
         A(dev_alloc(&c->phi_frag, (size_t)c->Npad * c->Npad));
+        if (c->nnz <= DBW_TAIL_LINKS) {
+            A(dev_alloc(&c->tail_p, (size_t)DBW_TAIL_ROUNDS * N));
+            A(dev_alloc(&c->tail_self, (size_t)DBW_TAIL_ROUNDS * N));
+            A(dev_alloc(&c->tail_idx, (size_t)DBW_TAIL_ROUNDS * c->nnz));
+            A(dev_alloc(&c->tail_w, (size_t)DBW_TAIL_ROUNDS * c->nnz));
+        }
     }
     if (c->model.kind != DBW_MODEL_NONE) {
         A(dbw_fc_prepare());

@@ -24,6 +24,11 @@ constexpr int DBW_FUSED_SELECT_MAX_N = 256;   // threshold rule + selection in o
 constexpr int DBW_LOSS_CHUNKS = 16;     // workgroups per worker in the loss kernel, at most
 constexpr int DBW_TILES_MAX_N = 256;   // the tile-major mixing kernel holds one 256-byte piece per worker in LDS
 
+// Gradient-free rounds of graphs with at most this many links (directed) are selected and multiplied together, up to
+// DBW_TAIL_ROUNDS of them per pair of launches.
+constexpr int DBW_TAIL_LINKS = 4096;
+constexpr int DBW_TAIL_ROUNDS = 16;
+
 struct dbw_timing_slot {
     const char *name;
     hipEvent_t start, stop;
@@ -56,6 +61,11 @@ struct dbw_ctx {
     float *Wdense = nullptr;          // [Npad*Npad] in MFMA A-fragment order (dense path only)
     float *phi[2] = {nullptr, nullptr};   // [Npad*Npad] running product of consensus matrices (N <= 256)
     float *phi_frag = nullptr;        // the product in MFMA A-fragment order
+    // selections of several gradient-free rounds at once (N <= 256, nnz <= DBW_TAIL_LINKS), else null
+    int32_t *tail_p = nullptr;        // [DBW_TAIL_ROUNDS][N]
+    float *tail_self = nullptr;       // [DBW_TAIL_ROUNDS][N]
+    int32_t *tail_idx = nullptr;      // [DBW_TAIL_ROUNDS][nnz]
+    float *tail_w = nullptr;          // [DBW_TAIL_ROUNDS][nnz]
     int32_t *err = nullptr;           // [1] deferred status
     // device: threshold rule
     int32_t *links = nullptr;         // [2*(N-1)]
@@ -86,6 +96,9 @@ struct dbw_timer {
 int dbw_validate_graph(int32_t N, const int32_t *rowptr, const int32_t *colidx);
 // select.hip
 int dbw_launch_select(dbw_ctx *c, const float *t, const int32_t *b, hipStream_t s);
+// Selections of rounds 0 .. rounds - 1 (t, b [rounds][N]) into the context's tail arrays; if last, those of the
+// last round go to the context's selection state instead, as dbw_launch_select leaves it.
+int dbw_launch_select_tail(dbw_ctx *c, const float *t, const int32_t *b, int rounds, bool last, hipStream_t s);
 int dbw_launch_round_time(dbw_ctx *c, float *out, hipStream_t s);
 int dbw_launch_dtur(dbw_ctx *c, const float *t, int32_t *b_out, float *theta_out, hipStream_t s);
 bool dbw_fused_dtur_select_fits(const dbw_ctx *c);

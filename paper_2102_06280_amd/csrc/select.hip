@@ -70,7 +70,7 @@ struct SelectLds {
 
 // Selection, weights and wait time of worker i by a row group of WAVES wavefronts (tid = thread index inside
 // the group).  Each wave ranks one 64-wide slice of the row at a time; slices are compacted in ascending order
-// through per-wave counts.  b may point to global memory or to LDS.
+// through per-wave counts.  b may point to global memory or to LDS; mask, wait and Wdense may be null.
 template <int WAVES, int KEYS>
 __device__ __forceinline__ void select_row(
     int i, int tid, SelectLds<WAVES, KEYS> &L, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
@@ -118,7 +118,7 @@ __device__ __forceinline__ void select_row(
                 }
             }
             sel = rank < pi;
-            mask[beg + k] = sel ? 1 : 0;
+            if (mask) mask[beg + k] = sel ? 1 : 0;
             if (sel) {
                 const int degj = rowptr[j + 1] - rowptr[j];
                 const int pj = degj - clamp_b(b[j], degj);
@@ -167,7 +167,7 @@ __device__ __forceinline__ void select_row(
     const float ws = 1.0f - wsum;
     if (tid == 0) {
         p_out[i] = pi;
-        wait[i] = tmax;
+        if (wait) wait[i] = tmax;
         self_w[i] = ws;
     }
     if (Wdense) {
@@ -194,6 +194,25 @@ __global__ __launch_bounds__(64 * WAVES) void select_kernel(
     __shared__ SelectLds<WAVES, DBW_SELECT_LDS_KEYS> L;
     select_row<WAVES, DBW_SELECT_LDS_KEYS>(blockIdx.x, threadIdx.x, L, rowptr, colidx, t, b, p_out, mask, wait, sel_idx,
                                            sel_w, self_w, Wdense, Npad, err);
+}
+
+// The same for several rounds at once: grid = (N, rounds).  Rounds before `last_round` go to the tail arrays (round q
+// at q N and q nnz), round last_round to the context's selection state.
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void select_tail_kernel(
+    int N, int nnz, int last_round, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
+    const float *__restrict__ t, const int32_t *__restrict__ b, int32_t *__restrict__ tail_p, int32_t *__restrict__ tail_idx,
+    float *__restrict__ tail_w, float *__restrict__ tail_self, int32_t *__restrict__ p_out, uint8_t *__restrict__ mask,
+    float *__restrict__ wait, int32_t *__restrict__ sel_idx, float *__restrict__ sel_w, float *__restrict__ self_w,
+    float *__restrict__ Wdense, int Npad, int32_t *__restrict__ err)
+{
+    __shared__ SelectLds<WAVES, DBW_DENSE_MAX_N> L;
+    const int q = blockIdx.y;
+    const bool state = q == last_round;
+    select_row<WAVES, DBW_DENSE_MAX_N>(
+        blockIdx.x, threadIdx.x, L, rowptr, colidx, t + (size_t)q * N, b + (size_t)q * N, state ? p_out : tail_p + (size_t)q * N,
+        state ? mask : nullptr, state ? wait : nullptr, state ? sel_idx : tail_idx + (size_t)q * nnz,
+        state ? sel_w : tail_w + (size_t)q * nnz, state ? self_w : tail_self + (size_t)q * N, state ? Wdense : nullptr, Npad, err);
 }
 
 // Rows [N, Npad) of the padded dense matrix stay zero: cleared once at create.
@@ -375,6 +394,21 @@ int dbw_launch_select(dbw_ctx *c, const float *t, const int32_t *b, hipStream_t 
     else
         hipLaunchKernelGGL(select_kernel<1>, dim3(c->N), dim3(64), 0, s, c->N, c->rowptr, c->colidx, t, b, c->p,
                            c->mask, c->wait, c->sel_idx, c->sel_w, c->self_w, c->Wdense, c->Npad, c->err);
+    DBW_HIP(hipGetLastError());
+    return DBW_OK;
+}
+
+int dbw_launch_select_tail(dbw_ctx *c, const float *t, const int32_t *b, int rounds, bool last, hipStream_t s)
+{
+    dbw_timer tm(c, "select_kernel", s);
+    const int last_round = last ? rounds - 1 : rounds;
+    auto go = [&](auto kern, int threads) {
+        hipLaunchKernelGGL(kern, dim3(c->N, rounds), dim3(threads), 0, s, c->N, c->nnz, last_round, c->rowptr, c->colidx, t, b,
+                           c->tail_p, c->tail_idx, c->tail_w, c->tail_self, c->p, c->mask, c->wait, c->sel_idx, c->sel_w, c->self_w,
+                           c->Wdense, c->Npad, c->err);
+    };
+    if (c->max_deg > 64) go(select_tail_kernel<4>, 256);
+    else go(select_tail_kernel<1>, 64);
     DBW_HIP(hipGetLastError());
     return DBW_OK;
 }

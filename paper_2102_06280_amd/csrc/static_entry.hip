@@ -31,7 +31,11 @@ constexpr size_t OFF_PHI0 = OFF_ERR + 256;
 constexpr size_t PHI_BYTES = sizeof(float) * STATIC_MAX_N * STATIC_MAX_N;
 constexpr size_t OFF_PHI1 = OFF_PHI0 + PHI_BYTES;
 constexpr size_t OFF_PHI_FRAG = OFF_PHI1 + PHI_BYTES;
-constexpr size_t SCRATCH_BYTES = OFF_PHI_FRAG + PHI_BYTES;          // about 1.7 MB
+constexpr size_t OFF_TAIL_P = OFF_PHI_FRAG + PHI_BYTES;
+constexpr size_t OFF_TAIL_SELF = OFF_TAIL_P + sizeof(int32_t) * DBW_TAIL_ROUNDS * STATIC_MAX_N;
+constexpr size_t OFF_TAIL_IDX = OFF_TAIL_SELF + sizeof(float) * DBW_TAIL_ROUNDS * STATIC_MAX_N;
+constexpr size_t OFF_TAIL_W = OFF_TAIL_IDX + sizeof(int32_t) * DBW_TAIL_ROUNDS * DBW_TAIL_LINKS;
+constexpr size_t SCRATCH_BYTES = OFF_TAIL_W + sizeof(float) * DBW_TAIL_ROUNDS * DBW_TAIL_LINKS;   // about 2.2 MB
 
 static __device__ __align__(256) unsigned char scratch[SCRATCH_BYTES];
 
@@ -159,12 +163,15 @@ extern "C" int dbw_consensus_rounds_static(int32_t N, int64_t d, int64_t ld, int
     view.phi[0] = (float *)(base + OFF_PHI0);
     view.phi[1] = (float *)(base + OFF_PHI1);
     view.phi_frag = (float *)(base + OFF_PHI_FRAG);
+    view.tail_p = (int32_t *)(base + OFF_TAIL_P);
+    view.tail_self = (float *)(base + OFF_TAIL_SELF);
+    view.tail_idx = (int32_t *)(base + OFF_TAIL_IDX);
+    view.tail_w = (float *)(base + OFF_TAIL_W);
 
     // The array keeps what the previous call left.  The status words must start at zero (the
     // staging kernel writes them; no memset, so that a caller may record this call into a graph);
     // every other piece is written by this call's kernels before it is read: the product starts
-    // from the identity over the whole padded square, and the fragment form writes its padding
-    // rows as zero.
+    // from the identity, and the fragment form writes its padding rows as zero.
     hipLaunchKernelGGL(stage_graph_kernel, dim3(1), dim3(1024), 0, s, N, nnz, rowptr, colidx, view.rowptr, view.colidx,
                        view.err);
     DBW_HIP(hipGetLastError());

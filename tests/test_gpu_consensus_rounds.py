@@ -124,3 +124,45 @@ def test_collapsed_rounds_argument_checks(B):
         assert e.value.code == B.ERR_UNSUPPORTED
     finally:
         B.dbw_destroy(h)
+
+
+# Rounds selected and multiplied together: more rounds than one batch of 16 holds (17, 33, 48), lists that fit LDS for
+# eight, a few and one round at a time (nnz 16, 624 to 1024, 4032), and just too long (4160: a launch per round).
+TAIL_BATCHES = [("ring8", 17), ("ring8", 48), ("reg8x128", 33), ("complete64", 5), ("complete64", 18), ("complete65", 3), ("two", 4)]
+
+
+@pytest.mark.parametrize("gname,r", TAIL_BATCHES, ids=[f"{c[0]}-r{c[1]}" for c in TAIL_BATCHES])
+def test_batches_of_rounds_match_oracle(B, orc, gname, r):
+    """The product of all rounds against the oracle's rounds one by one, at the repository's 1e-5 (roundings of the r products
+    average out like the values themselves: sqrt(r) 2^-24 per value), and the selection state left behind
+    against the last round's."""
+    graph = {"ring8": lambda: inputs.graph_ring(8), "complete64": lambda: inputs.graph_complete(64),
+             "complete65": lambda: inputs.graph_complete(65), "two": lambda: inputs.graph_complete(2),
+             "reg8x128": lambda: inputs.graph_regular(128, 8, np.random.default_rng(3))}[gname]
+    rowptr, colidx = graph()
+    n = rowptr.size - 1
+    deg = np.diff(rowptr)
+    d, ld = 517, 520
+    g = np.random.default_rng(77 + r)
+    x = 1.0 + g.standard_normal((n, ld)).astype(np.float32)              # a mean that the averaging keeps
+    t = g.standard_exponential((r, n)).astype(np.float32)
+    b = np.stack([g.integers(0, deg // 2 + 1) for _ in range(r)]).astype(np.int32)
+    h = B.dbw_create(rowptr, colidx, n, d, ld=ld)
+    try:
+        out = torch.full((n, ld), 7.0, dtype=torch.float32, device="cuda")
+        B.dbw_consensus_rounds(h, dev(x), out, dev(t), dev(b), r)
+        p = torch.zeros(n, dtype=torch.int32, device="cuda")
+        mask = torch.zeros(colidx.size, dtype=torch.uint8, device="cuda")
+        wait = torch.zeros(n, dtype=torch.float32, device="cuda")
+        B.dbw_get_selection(h, p, mask, wait)
+        got = out.cpu().numpy()
+    finally:
+        B.dbw_destroy(h)
+    want = x.copy()
+    for q in range(r):
+        want_mask, want_p, want_wait = orc.select(rowptr, colidx, t[q], b[q])
+        want = orc.round_(rowptr, colidx, want_mask, want_p, want, None, 0.0, 0, d=d)
+    assert_params_close(got, want, d=d, what=f"{gname} r {r}")
+    assert np.all(got[:, d:] == 7.0)
+    assert np.array_equal(p.cpu().numpy(), want_p) and np.array_equal(mask.cpu().numpy(), want_mask)
+    assert np.array_equal(wait.cpu().numpy(), want_wait)
