@@ -15,8 +15,19 @@
 // per-lane context once per k-step (KC) or once per kernel (otherwise).
 // The tile keeps the operand's natural layout in LDS.
 //
-// Workgroup: 256 threads = 4 wavefronts, tile BM x BN (64 x 64 or 32 x 128), k-step 64.
-// Each wavefront owns a 32 x 32 part as 2 x 2 fragments of v_mfma_f32_16x16x4_f32 (true fp32):
+// Workgroup: 256 threads = 4 wavefronts, tile BM x BN (64 x 64 or 32 x 128), k-step 64.  Each wavefront owns a 32 x 32
+// part.  Two kernels:
+//
+// split_kernel (dense operands of any alignment): every value is split into
+// three bf16 values (split_bf16.h) when the tile is written to LDS, as [plane][8 k][row][8 values], where a lane's
+// fragment of v_mfma_f32_32x32x16_bf16 is one 128-bit read.  A thread therefore fetches eight consecutive k of a row
+// at a time: two 16-byte loads on whatever 4-byte boundary the row starts, or, of a row-contiguous operand, eight loads
+// whose lanes run along the rows.  20 workers, batch 101, 617-301-75-26 on rows without padding: three forward products 43
+// us (fp32 matrix instructions and 4-byte loads 111), three weight gradients 42 (46), two data gradients 26 (26); 11 workers,
+// batch 1 024, 161-185-185-24: 53 (123), 52 (61), 38 (44); aligned, 29 workers, batch 697, 256-192-240-48-10: 84 (94) and
+// 66 (63).  The small partial products have an accumulator of their own, which makes the sums three times as exact.
+//
+// kernel (convolution operands): 2 x 2 fragments of v_mfma_f32_16x16x4_f32 per wavefront (true fp32):
 //   A fragment: lane l holds A[m = l % 16][slot l / 16], B fragment: B[slot l / 16][n = l % 16]
 //   D: 4 floats, d[v] = D[m = 4 * (l / 16) + v][n = l % 16]
 // The four k-slots of instruction j (0..3) of a 16-wide k group are k = 4 * slot + j for
@@ -26,6 +37,8 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include "split_bf16.h"
 
 namespace bgemm {
 
@@ -38,15 +51,11 @@ constexpr int lds_floats(bool kc, int rows) { return kc ? rows * LDS_KC : BK * l
 
 // Dense operand.  KC: element (r, k) at p[w * stride + r * ld + k]; otherwise at
 // p[w * stride + k * ld + r].  Offsets inside one worker's block fit 32 bits.
-// `vec` (set by launch() when every row of the operand starts on a 16-byte boundary and the
-// extents divide by 4) lets the tile be fetched with 128-bit loads.
 template <bool KC_>
 struct Dense {
     static constexpr bool KC = KC_;
-    static constexpr bool CAN_VEC = true;
     const float *p;
     int64_t ld, stride;
-    bool vec;
     struct RowCtx { int off; bool ok; };
     struct KCtx { int off; bool ok; };
     __device__ __forceinline__ RowCtx row_ctx(int r, bool ok) const { return {KC ? r * (int)ld : r, ok}; }
@@ -121,67 +130,6 @@ __device__ __forceinline__ void fetch_tile(const L &op, int w, int r0, int R, in
     }
 }
 
-// 128-bit variants for dense operands (ROWS / 16 float4 per thread, float4 index f = tid + 256 j):
-//   KC: (row = f / 16, k = 4 (f % 16)): a wave instruction reads 256 contiguous bytes of four rows
-//   RC: (k = f / (ROWS / 4), row = 4 (f % (ROWS / 4))): ROWS contiguous floats of one k
-// A float4 outside the operand is read from offset 0 instead and its bit in `okbits` stays clear;
-// the value is only replaced by zero when the tile is written to LDS (commit_tile_vec).  Masking
-// right after the load would make the wave wait for the load before its matrix instructions, and
-// the point of fetching one k-step ahead is that the loads are in flight during them.
-template <class L, int ROWS>
-__device__ __forceinline__ void fetch_tile_vec(const L &op, int w, int r0, int R, int k0, int K, int tid,
-                                               float (&v)[ROWS / 4], uint32_t &okbits)
-{
-    okbits = 0;
-    const float *base = op.p + w * op.stride;
-#pragma unroll
-    for (int j = 0; j < ROWS / 16; ++j) {
-        const int f = tid + 256 * j;
-        int r, k;
-        if (L::KC) {
-            r = r0 + (f >> 4);
-            k = k0 + 4 * (f & 15);
-        } else {
-            r = r0 + 4 * (f % (ROWS / 4));
-            k = k0 + f / (ROWS / 4);
-        }
-        const bool ok = r < R && k < K;
-        const int off = ok ? (L::KC ? r * (int)op.ld + k : k * (int)op.ld + r) : 0;
-        const f32x4 q = *(const f32x4 *)(base + off);
-        okbits |= (ok ? 1u : 0u) << j;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[4 * j + e] = q[e];
-    }
-}
-
-template <class L, int ROWS>
-__device__ __forceinline__ void commit_tile_vec(float *lds, int tid, const float (&v)[ROWS / 4], uint32_t okbits)
-{
-#pragma unroll
-    for (int j = 0; j < ROWS / 16; ++j) {
-        const int f = tid + 256 * j;
-        const bool ok = (okbits >> j) & 1u;
-        const f32x4 q = {ok ? v[4 * j] : 0.f, ok ? v[4 * j + 1] : 0.f, ok ? v[4 * j + 2] : 0.f, ok ? v[4 * j + 3] : 0.f};
-        if (L::KC)
-            *(f32x4 *)&lds[(f >> 4) * LDS_KC + 4 * (f & 15)] = q;
-        else
-            *(f32x4 *)&lds[(f / (ROWS / 4)) * lds_rc(ROWS) + 4 * (f % (ROWS / 4))] = q;
-    }
-}
-
-template <class L>
-struct can_vec {
-    template <class T> static constexpr auto test(int) -> decltype(T::CAN_VEC, true) { return T::CAN_VEC; }
-    template <class T> static constexpr bool test(...) { return false; }
-    static constexpr bool value = test<L>(0);
-};
-template <class L>
-__host__ __device__ __forceinline__ bool use_vec(const L &op)
-{
-    if constexpr (can_vec<L>::value) return op.vec;
-    else return false;
-}
-
 template <class L, int ROWS>
 __device__ __forceinline__ void commit_tile(float *lds, int wave, int lane, const float (&v)[ROWS / 4])
 {
@@ -211,8 +159,7 @@ __device__ __forceinline__ f32x4 frag(const float *lds, int rbase, int kg, int l
 // blockIdx.z = worker * splits + split; a split covers k in [split * kper, (split + 1) * kper)
 // (kper a multiple of BK) and hands its partial sum to the epilogue, which decides where it
 // goes; with splits == 1 the result is final.
-// VA / VB: fetch the A / B tile with 128-bit loads (see mark_vec).
-template <class LA, class LB, class EP, int BM, int BN, bool VA, bool VB>
+template <class LA, class LB, class EP, int BM, int BN>
 __global__ __launch_bounds__(THREADS) void kernel(LA A, LB B, EP E, int M, int N, int K, int splits, int kper)
 {
     static_assert((BM == 64 && BN == 64) || (BM == 32 && BN == 128), "supported tiles: 64 x 64, 32 x 128");
@@ -238,21 +185,17 @@ __global__ __launch_bounds__(THREADS) void kernel(LA A, LB B, EP E, int M, int N
     make_rows<LA, BM>(A, m0, M, lane, arows);
     make_rows<LB, BN>(B, n0, N, lane, brows);
     float ra[BM / 4], rb[BN / 4];
-    uint32_t oka = 0, okb = 0;
     auto fetch = [&](int k0) {
-        if constexpr (VA) fetch_tile_vec<LA, BM>(A, w, m0, M, k0, kend, tid, ra, oka);
-        else fetch_tile<LA, BM>(A, w, m0, M, k0, kend, wave, lane, arows, ra);
-        if constexpr (VB) fetch_tile_vec<LB, BN>(B, w, n0, N, k0, kend, tid, rb, okb);
-        else fetch_tile<LB, BN>(B, w, n0, N, k0, kend, wave, lane, brows, rb);
+        fetch_tile<LA, BM>(A, w, m0, M, k0, kend, wave, lane, arows, ra);
+        fetch_tile<LB, BN>(B, w, n0, N, k0, kend, wave, lane, brows, rb);
     };
     fetch(kbeg);
     for (int k0 = kbeg; k0 < kend; k0 += BK) {
         __syncthreads();                       // previous tile fully consumed
-        if constexpr (VA) commit_tile_vec<LA, BM>(As, tid, ra, oka); else commit_tile<LA, BM>(As, wave, lane, ra);
-        if constexpr (VB) commit_tile_vec<LB, BN>(Bs, tid, rb, okb); else commit_tile<LB, BN>(Bs, wave, lane, rb);
+        commit_tile<LA, BM>(As, wave, lane, ra);
+        commit_tile<LB, BN>(Bs, wave, lane, rb);
         __syncthreads();
         if (k0 + BK < kend) fetch(k0 + BK);    // next tile's loads fly during the MFMAs
-        if constexpr (VA || VB) __builtin_amdgcn_sched_barrier(0);   // nothing that consumes them moves up here
 #pragma unroll
         for (int kg = 0; kg < BK / 16; ++kg) {
             f32x4 fa[2], fb[2];
@@ -282,15 +225,125 @@ __global__ __launch_bounds__(THREADS) void kernel(LA A, LB B, EP E, int M, int N
         }
 }
 
-// 128-bit tile fetches need every row of the operand on a 16-byte boundary and the contiguous
-// extent (k for a k-contiguous operand, rows otherwise) divisible by 4.  The choice is a template
-// parameter of the kernel: as a run-time branch inside it, it cost the 32-bit path 15-20 %.
-template <class L>
-inline void mark_vec(L &op, int rows, int K)
+// ---- the split kernel
+
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+
+// A 64 x 64 operand tile as units of (eight consecutive k, row), two of them per thread.
+//   KC: unit u is (row tid / 8 + 32 u, k 8 (tid % 8)): eight lanes read 256 contiguous bytes of a row
+//   otherwise unit u of wave `wave` is k group wave + 4 u of the rows, one per lane
+template <bool KC>
+struct SplitTile {
+    static constexpr int ROWS = 64, UNITS = 2;
+    static constexpr int PITCH = ROWS + 1;               // 16-byte groups between k groups: the lanes of a unit column differ in bank
+    static constexpr int GROUPS = 8 * PITCH;
+
+    float v[UNITS][8];
+
+    __device__ __forceinline__ void fetch(const Dense<KC> &op, int w, int r0, int R, int k0, int K, int tid)
+    {
+        const float *base = op.p + w * op.stride;
+#pragma unroll
+        for (int u = 0; u < UNITS; ++u) {
+            if constexpr (KC) {
+                const int r = r0 + tid / 8 + 32 * u, k = k0 + 8 * (tid % 8), left = r < R ? K - k : 0;
+                const float *src = base + (left > 0 ? r * (int)op.ld + k : 0);
+                if (left >= 8) {
+                    const f32x4_any a = *(const f32x4_any *)src, b = *(const f32x4_any *)(src + 4);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        v[u][j] = a[j];
+                        v[u][4 + j] = b[j];
+                    }
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) v[u][j] = j < left ? src[j] : 0.f;
+                }
+            } else {
+                // rows and k beyond the operand: any valid element; commit replaces those of k, those of a row reach
+                // only results that are not stored
+                const int kg = __builtin_amdgcn_readfirstlane(tid >> 6) + 4 * u;
+                const uint32_t lane_off = (uint32_t)min(r0 + (tid & 63), R - 1);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) v[u][j] = (base + (int64_t)min(k0 + 8 * kg + j, K - 1) * op.ld)[lane_off];
+            }
+        }
+    }
+    // k_left: k of the tile that exist (64 or more: all)
+    __device__ __forceinline__ void commit(split_bf16::u32x4 *lds, int tid, int k_left)
+    {
+#pragma unroll
+        for (int u = 0; u < UNITS; ++u) {
+            const int kg = KC ? tid % 8 : (tid >> 6) + 4 * u, r = KC ? tid / 8 + 32 * u : tid & 63;
+            if (!KC && k_left < 64) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) v[u][j] = 8 * kg + j < k_left ? v[u][j] : 0.f;
+            }
+            const split_bf16::planes p = split_bf16::split8(v[u]);
+            split_bf16::u32x4 *d = lds + kg * PITCH + r;
+            d[0] = p.h;
+            d[GROUPS] = p.m;
+            d[2 * GROUPS] = p.l;
+        }
+    }
+    // fragment of the 32 rows from rbase on, step s (k 16 s .. + 15) of the tile
+    static __device__ __forceinline__ split_bf16::planes frag(const split_bf16::u32x4 *lds, int rbase, int s, int lane)
+    {
+        const split_bf16::u32x4 *d = lds + (2 * s + (lane >> 5)) * PITCH + rbase + (lane & 31);
+        return {d[0], d[GROUPS], d[2 * GROUPS]};
+    }
+};
+
+template <bool KCA, bool KCB, class EP>
+__global__ __launch_bounds__(THREADS, 3) void split_kernel(Dense<KCA> A, Dense<KCB> B, EP E, int M, int N, int K, int splits, int kper)
 {
-    if constexpr (can_vec<L>::value) {
-        const int contiguous = L::KC ? K : rows;
-        op.vec = ((uintptr_t)op.p % 16 == 0) && op.ld % 4 == 0 && op.stride % 4 == 0 && contiguous % 4 == 0;
+    typedef SplitTile<KCA> TA;
+    typedef SplitTile<KCB> TB;
+    __shared__ __attribute__((aligned(16))) split_bf16::u32x4 As[3 * TA::GROUPS];
+    __shared__ __attribute__((aligned(16))) split_bf16::u32x4 Bs[3 * TB::GROUPS];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int w = blockIdx.z / splits, split = blockIdx.z % splits;
+    const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
+    const int kbeg = split * kper, kend = min(K, kbeg + kper);
+    const int wm = (wave % 2) * 32, wn = (wave / 2) * 32;
+
+    split_bf16::f32x16 acc, small;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = small[v] = 0.f;
+    TA ta;
+    TB tb;
+    if (kbeg < kend) {
+        ta.fetch(A, w, m0, M, kbeg, kend, tid);
+        tb.fetch(B, w, n0, N, kbeg, kend, tid);
+    }
+    for (int k0 = kbeg; k0 < kend; k0 += BK) {
+        __syncthreads();                       // previous tile fully consumed
+        ta.commit(As, tid, kend - k0);
+        tb.commit(Bs, tid, kend - k0);
+        __syncthreads();
+        if (k0 + BK < kend) {                  // next tile's loads fly during the MFMAs
+            ta.fetch(A, w, m0, M, k0 + BK, kend, tid);
+            tb.fetch(B, w, n0, N, k0 + BK, kend, tid);
+        }
+        __builtin_amdgcn_sched_barrier(0);     // nothing that consumes them moves up here
+#pragma unroll
+        for (int s = 0; s < BK / 16; ++s) split_bf16::mma32(TA::frag(As, wm, s, lane), TB::frag(Bs, wn, s, lane), acc, small);
+    }
+    acc += small;
+    const int n = n0 + wn + (lane & 31);
+    const bool bad = __any(split_bf16::any_not_finite(acc));
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const int m = m0 + wm + 8 * (v / 4) + 4 * (lane >> 5) + v % 4;
+        if (m >= M || n >= N) continue;
+        float r = acc[v];
+        if (bad && split_bf16::not_finite(r)) {          // once more, with plain multiply-adds (split_bf16.h)
+            r = 0.f;
+            for (int k = kbeg; k < kend; ++k)
+                r = fmaf(A.load(w, A.row_ctx(m, true), A.k_ctx(k, true)), B.load(w, B.row_ctx(n, true), B.k_ctx(k, true)), r);
+        }
+        E.store(w, split, m, n, r);
     }
 }
 
@@ -302,28 +355,20 @@ inline hipError_t launch(const LA &A, const LB &B, const EP &E, int M, int N, in
     constexpr int BN = BM == 32 ? 128 : 64;
     int kper = (K + splits - 1) / splits;
     kper = (kper + BK - 1) / BK * BK;
-    dim3 grid((N + BN - 1) / BN, (M + BM - 1) / BM, batch * splits);
-    LA a = A;
-    LB b = B;
-    mark_vec(a, M, K);
-    mark_vec(b, N, K);
-    const bool va = use_vec(a), vb = use_vec(b);
-    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, dim3(THREADS), 0, s, a, b, E, M, N, K, splits, kper); };
-    constexpr bool CA = can_vec<LA>::value, CB = can_vec<LB>::value;
-    if constexpr (CA && CB) {
-        if (va && vb) go(kernel<LA, LB, EP, BM, BN, true, true>);
-        else if (va) go(kernel<LA, LB, EP, BM, BN, true, false>);
-        else if (vb) go(kernel<LA, LB, EP, BM, BN, false, true>);
-        else go(kernel<LA, LB, EP, BM, BN, false, false>);
-    } else if constexpr (CA) {
-        if (va) go(kernel<LA, LB, EP, BM, BN, true, false>);
-        else go(kernel<LA, LB, EP, BM, BN, false, false>);
-    } else if constexpr (CB) {
-        if (vb) go(kernel<LA, LB, EP, BM, BN, false, true>);
-        else go(kernel<LA, LB, EP, BM, BN, false, false>);
-    } else {
-        go(kernel<LA, LB, EP, BM, BN, false, false>);
-    }
+    const dim3 grid((N + BN - 1) / BN, (M + BM - 1) / BM, batch * splits);
+    hipLaunchKernelGGL((kernel<LA, LB, EP, BM, BN>), grid, dim3(THREADS), 0, s, A, B, E, M, N, K, splits, kper);
+    return hipGetLastError();
+}
+
+// The same of two dense operands, 64 x 64 tiles.
+template <bool KCA, bool KCB, class EP>
+inline hipError_t launch_dense(const Dense<KCA> &A, const Dense<KCB> &B, const EP &E, int M, int N, int K, int batch, hipStream_t s,
+                               int splits = 1)
+{
+    int kper = (K + splits - 1) / splits;
+    kper = (kper + BK - 1) / BK * BK;
+    const dim3 grid((N + 63) / 64, (M + 63) / 64, batch * splits);
+    hipLaunchKernelGGL((split_kernel<KCA, KCB, EP>), grid, dim3(THREADS), 0, s, A, B, E, M, N, K, splits, kper);
     return hipGetLastError();
 }
 

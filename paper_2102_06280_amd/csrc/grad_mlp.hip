@@ -455,7 +455,7 @@ int dbw_fc_forward_backward(dbw_ctx *c, const dbw_fc_args &a, hipStream_t s)
             float *part = act + 2 * per;
             {
                 dbw_timer tm(c, "mlp_forward_gemm", s);
-                DBW_HIP(bgemm::launch<64>(A, Bm, SplitOut{part, wstride, B, dims[l]}, B, dims[l], dims[l - 1], N, s,
+                DBW_HIP(bgemm::launch_dense(A, Bm, SplitOut{part, wstride, B, dims[l]}, B, dims[l], dims[l - 1], N, s,
                                           splits));
             }
             if (head_can_sum && l == L - 1) {
@@ -471,7 +471,7 @@ int dbw_fc_forward_backward(dbw_ctx *c, const dbw_fc_args &a, hipStream_t s)
         }
         Epilogue E{act + a_off[l], dims[l], wstride, params + b_off[l], c->ld, nullptr, 0, 0, l < L ? 1 : 0};
         dbw_timer tm(c, "mlp_forward_gemm", s);
-        DBW_HIP(bgemm::launch<64>(A, Bm, E, B, dims[l], dims[l - 1], N, s));
+        DBW_HIP(bgemm::launch_dense(A, Bm, E, B, dims[l], dims[l - 1], N, s));
     }
     // Weight gradients of the layers the GEMM kernels would take: all of them in one launch when the library may
     // choose and every operand allows 128-bit accesses.  Batches of 256 and more: mlp_wgrad.h, four wavefronts per
@@ -623,7 +623,7 @@ int dbw_fc_forward_backward(dbw_ctx *c, const dbw_fc_args &a, hipStream_t s)
                     float *part = act + 2 * per;
                     {
                         dbw_timer tm(c, "mlp_wgrad_gemm", s);
-                        DBW_HIP(bgemm::launch<64>(A, Bm, SplitOut{part, wstride, dims[l], dims[l - 1]}, dims[l], dims[l - 1],
+                        DBW_HIP(bgemm::launch_dense(A, Bm, SplitOut{part, wstride, dims[l], dims[l - 1]}, dims[l], dims[l - 1],
                                                   B, N, s, splits));
                     }
                     dbw_timer tm(c, "fc_reduce_kernel", s);
@@ -634,7 +634,7 @@ int dbw_fc_forward_backward(dbw_ctx *c, const dbw_fc_args &a, hipStream_t s)
                 } else {
                     Epilogue E{grads + w_off[l], dims[l - 1], c->ld, nullptr, 0, nullptr, 0, 0, 0};
                     dbw_timer tm(c, "mlp_wgrad_gemm", s);
-                    DBW_HIP(bgemm::launch<64>(A, Bm, E, dims[l], dims[l - 1], B, N, s));
+                    DBW_HIP(bgemm::launch_dense(A, Bm, E, dims[l], dims[l - 1], B, N, s));
                 }
             }
         }
@@ -667,13 +667,13 @@ int dbw_fc_forward_backward(dbw_ctx *c, const dbw_fc_args &a, hipStream_t s)
             Epilogue E{act + dz_off[l - 1], dims[l - 1], wstride, nullptr, 0, act + a_off[l - 1], dims[l - 1],
                        wstride, 0};
             dbw_timer tm(c, "mlp_dgrad_gemm", s);
-            DBW_HIP(bgemm::launch<64>(A, Bm, E, B, dims[l - 1], dims[l], N, s));
+            DBW_HIP(bgemm::launch_dense(A, Bm, E, B, dims[l - 1], dims[l], N, s));
         } else if (a.din) {   // gradient with respect to the stack's input, unmasked
             Dense<true> A{act + dz_off[1], dims[1], wstride};
             Dense<false> Bm{params + w_off[1], dims[0], c->ld};
             Epilogue E{a.din, a.din_ld, a.din_stride, nullptr, 0, nullptr, 0, 0, 0};
             dbw_timer tm(c, "mlp_dgrad_gemm", s);
-            DBW_HIP(bgemm::launch<64>(A, Bm, E, B, dims[0], dims[1], N, s));
+            DBW_HIP(bgemm::launch_dense(A, Bm, E, B, dims[0], dims[1], N, s));
         }
     }
     if (grouped) {

@@ -421,3 +421,51 @@ def test_graph_replay_matches_eager(B, cid):
     finally:
         eager.close()
         graphed.close()
+
+
+# The dense product kernel at its edges, on rows without padding (4-byte boundaries, the last row ends the allocation):
+# widths below one group of eight, one off 64 on either side, batches of one tile and one row more, a reduction split with a
+# partial last tile, more than 16 classes (every layer goes through it), few tiles (split) and many.
+DENSE_SHAPES = [([65, 63, 70, 20], 66, 3), ([7, 9, 21], 130, 2), ([129, 64, 33, 18], 65, 4), ([617, 31, 26], 101, 3), ([3, 17], 257, 2)]
+
+
+@pytest.mark.parametrize("dims,batch,n", DENSE_SHAPES, ids=[f"{'-'.join(map(str, s[0]))}-B{s[1]}-N{s[2]}" for s in DENSE_SHAPES])
+def test_dense_products_on_unpadded_rows(B, orc, dims, batch, n):
+    desc = {"kind": "mlp", "dims": dims, "loss": "xent"}
+    d = inputs.param_count(desc)
+    rowptr, colidx = inputs.graph_complete(n)
+    g = np.random.default_rng(417)
+    params = inputs.init_params(desc, n, d, g)
+    params += (g.standard_normal((n, d)) * 0.05).astype(np.float32)
+    x = g.standard_normal((n, batch, dims[0])).astype(np.float32)
+    y = g.integers(0, dims[-1], (n, batch)).astype(np.int32)
+    h = B.dbw_create(rowptr, colidx, n, d, ld=d, model=B.make_model(B.MODEL_MLP, batch, dims))
+    try:
+        grads, loss = torch.zeros((n, d), device="cuda"), torch.zeros(n, device="cuda")
+        B.dbw_grad(h, dev(params), dev(x), dev(y), grads, loss)
+        got, gl = grads.cpu().numpy(), loss.cpu().numpy()
+        # an infinite weight of the first layer of worker 1: its own affair, and not hidden from it
+        bad = params.copy()
+        bad[1, 0] = np.inf
+        grads_bad, loss_bad = torch.zeros((n, d), device="cuda"), torch.zeros(n, device="cuda")
+        B.dbw_grad(h, dev(bad), dev(x), dev(y), grads_bad, loss_bad)
+    finally:
+        B.dbw_destroy(h)
+    kind, od = orc.model_desc(desc)
+    res = GradientResolver(orc, kind, od, d, params, x, y, threads=min(n, 8))
+    assert np.allclose(gl, res.loss, rtol=5e-6, atol=1e-6)
+
+    def layers_close(got_row, want_row):
+        off = 0
+        for _, nw, nb in inputs.layer_shapes(desc):
+            for lo, hi in ((off, off + nw), (off + nw, off + nw + nb)):
+                w = want_row[lo:hi].astype(np.float64)
+                diff = got_row[lo:hi] - w
+                if np.linalg.norm(diff) > 2e-5 * np.linalg.norm(w) or np.abs(diff).max() > 2e-5 * np.abs(w).max():
+                    return False
+            off += nw + nb
+        return True
+    match_gradients(res, got, layers_close, d, what=f"dims {dims} batch {batch}")
+    others = np.array([i for i in range(n) if i != 1])
+    assert np.array_equal(grads_bad.cpu().numpy()[others], got[others]) and np.array_equal(loss_bad.cpu().numpy()[others], gl[others])
+    assert not np.isfinite(grads_bad.cpu().numpy()[1]).all()
