@@ -8,8 +8,9 @@
 // only (`k_ctx`) and a cheap combination (`load`), all in 32-bit arithmetic relative to
 // the worker's base pointer, and states whether its elements are contiguous along k (KC)
 // or along the row index.
-// The global -> LDS copy assigns work so that one of the two indices is the same for a
-// whole wavefront and the other runs with the lane: for a KC operand a wavefront reads 64
+// A dense operand that is contiguous along k (WIDE) is fetched eight k of a row per thread, two 16-byte loads on whatever
+// 4-byte boundary the row starts.  For the others the global -> LDS copy assigns work so that one of the two indices is
+// the same for a whole wavefront and the other runs with the lane: for a KC operand a wavefront reads 64
 // consecutive k of one row, otherwise 64 consecutive rows of one k.  Loads are therefore
 // coalesced; the context of the wave-uniform index is computed on the scalar unit, the
 // per-lane context once per k-step (KC) or once per kernel (otherwise).
@@ -18,16 +19,19 @@
 // Workgroup: 256 threads = 4 wavefronts, tile BM x BN (64 x 64 or 32 x 128), k-step 64.  Each wavefront owns a 32 x 32
 // part.  Two kernels:
 //
-// split_kernel (dense operands of any alignment): every value is split into
+// split_kernel (weight and data gradients of dense layers): every value is split into
 // three bf16 values (split_bf16.h) when the tile is written to LDS, as [plane][8 k][row][8 values], where a lane's
 // fragment of v_mfma_f32_32x32x16_bf16 is one 128-bit read.  A thread therefore fetches eight consecutive k of a row
-// at a time: two 16-byte loads on whatever 4-byte boundary the row starts, or, of a row-contiguous operand, eight loads
-// whose lanes run along the rows.  20 workers, batch 101, 617-301-75-26 on rows without padding: three forward products 43
-// us (fp32 matrix instructions and 4-byte loads 111), three weight gradients 42 (46), two data gradients 26 (26); 11 workers,
-// batch 1 024, 161-185-185-24: 53 (123), 52 (61), 38 (44); aligned, 29 workers, batch 697, 256-192-240-48-10: 84 (94) and
-// 66 (63).  The small partial products have an accumulator of their own, which makes the sums three times as exact.
+// at a time, of a row-contiguous operand with eight loads whose lanes run along the rows.  20 workers, batch 101,
+// 617-301-75-26 on rows without padding: three weight gradients 42 us (fp32 matrix instructions and 4-byte loads 46), two
+// data gradients 26 (26); 11 workers, batch 1 024, 161-185-185-24: 52 (61), 38 (44).  The small partial products have an
+// accumulator of their own, which makes the sums three times as exact.
 //
-// kernel (convolution operands): 2 x 2 fragments of v_mfma_f32_16x16x4_f32 per wavefront (true fp32):
+// kernel (forward products of dense layers, convolution operands): 2 x 2 fragments of v_mfma_f32_16x16x4_f32 per
+// wavefront (true fp32).  The sign of a forward product decides whole samples' gradients where it is next to zero, so its
+// rounding is that of the chain and head kernels that compute the same layer; the split form gained nothing, since
+// the fetches bound both.  The three forward products of the first example: 46 us (with 4-byte loads 113), of the second
+// 59 (123).
 //   A fragment: lane l holds A[m = l % 16][slot l / 16], B fragment: B[slot l / 16][n = l % 16]
 //   D: 4 floats, d[v] = D[m = 4 * (l / 16) + v][n = l % 16]
 // The four k-slots of instruction j (0..3) of a 16-wide k group are k = 4 * slot + j for
@@ -53,7 +57,7 @@ constexpr int lds_floats(bool kc, int rows) { return kc ? rows * LDS_KC : BK * l
 // p[w * stride + k * ld + r].  Offsets inside one worker's block fit 32 bits.
 template <bool KC_>
 struct Dense {
-    static constexpr bool KC = KC_;
+    static constexpr bool KC = KC_, WIDE = KC_;
     const float *p;
     int64_t ld, stride;
     struct RowCtx { int off; bool ok; };
@@ -86,7 +90,34 @@ struct Epilogue {
     }
 };
 
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+
+// Eight consecutive floats, on any 4-byte boundary, of which the first `left` exist; the rest are zero.
+__device__ __forceinline__ void load8(const float *src, int left, float *v)
+{
+    if (left >= 8) {
+        const f32x4_any a = *(const f32x4_any *)src, b = *(const f32x4_any *)(src + 4);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            v[j] = a[j];
+            v[4 + j] = b[j];
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = j < left ? src[j] : 0.f;
+    }
+}
+
+// Operands with a member WIDE that is true (dense ones, contiguous along k) are fetched eight k at a time.
+template <class L>
+struct wide {
+    template <class T> static constexpr bool test(decltype(T::WIDE) *) { return T::WIDE; }
+    template <class T> static constexpr bool test(...) { return false; }
+    static constexpr bool value = test<L>(nullptr);
+};
+
 // Global -> registers for a ROWS x 64 operand tile (ROWS / 4 elements per thread).
+//   WIDE: elements 8 u .. 8 u + 7 are (row = tid / 8 + 32 u, k = 8 (tid % 8) ..): eight lanes read 256 contiguous bytes
 //   KC: element j of the thread is (row = wave + 4 j, k = lane)
 //   RC: ROWS >= 64; element j is (row = lane + 64 (j % (ROWS / 64)), k = wave + 4 (j / (ROWS / 64)))
 // `rows` holds the per-lane row contexts of an RC operand (computed once per kernel).
@@ -112,7 +143,15 @@ __device__ __forceinline__ void fetch_tile(const L &op, int w, int r0, int R, in
                                            const RowCache<L, ROWS> &rows, float (&v)[ROWS / 4])
 {
     static_assert(L::KC || ROWS >= 64, "a row-contiguous operand needs at least 64 tile rows");
-    if (L::KC) {
+    if constexpr (wide<L>::value) {
+        const float *base = op.p + w * op.stride;
+        const int tid = 64 * wave + lane;
+#pragma unroll
+        for (int u = 0; u < ROWS / 32; ++u) {
+            const int r = r0 + tid / 8 + 32 * u, k = k0 + 8 * (tid % 8), left = r < R ? K - k : 0;
+            load8(base + (left > 0 ? r * (int)op.ld + k : 0), left, v + 8 * u);
+        }
+    } else if (L::KC) {
         const int k = k0 + lane;
         const typename L::KCtx kc = op.k_ctx(k < K ? k : 0, k < K);      // per lane, shared by all rows
 #pragma unroll
@@ -133,6 +172,14 @@ __device__ __forceinline__ void fetch_tile(const L &op, int w, int r0, int R, in
 template <class L, int ROWS>
 __device__ __forceinline__ void commit_tile(float *lds, int wave, int lane, const float (&v)[ROWS / 4])
 {
+    if constexpr (wide<L>::value) {
+        const int tid = 64 * wave + lane;
+#pragma unroll
+        for (int q = 0; q < ROWS / 16; ++q)
+            *(f32x4 *)&lds[(tid / 8 + 32 * (q / 2)) * LDS_KC + 8 * (tid % 8) + 4 * (q % 2)] =
+                f32x4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
+        return;
+    }
 #pragma unroll
     for (int j = 0; j < ROWS / 4; ++j) {
         if (L::KC)
@@ -196,6 +243,7 @@ __global__ __launch_bounds__(THREADS) void kernel(LA A, LB B, EP E, int M, int N
         commit_tile<LB, BN>(Bs, wave, lane, rb);
         __syncthreads();
         if (k0 + BK < kend) fetch(k0 + BK);    // next tile's loads fly during the MFMAs
+        if constexpr (wide<LA>::value || wide<LB>::value) __builtin_amdgcn_sched_barrier(0);   // nothing that consumes them moves up here
 #pragma unroll
         for (int kg = 0; kg < BK / 16; ++kg) {
             f32x4 fa[2], fb[2];
@@ -227,8 +275,6 @@ __global__ __launch_bounds__(THREADS) void kernel(LA A, LB B, EP E, int M, int N
 
 // ---- the split kernel
 
-typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
-
 // A 64 x 64 operand tile as units of (eight consecutive k, row), two of them per thread.
 //   KC: unit u is (row tid / 8 + 32 u, k 8 (tid % 8)): eight lanes read 256 contiguous bytes of a row
 //   otherwise unit u of wave `wave` is k group wave + 4 u of the rows, one per lane
@@ -247,18 +293,7 @@ struct SplitTile {
         for (int u = 0; u < UNITS; ++u) {
             if constexpr (KC) {
                 const int r = r0 + tid / 8 + 32 * u, k = k0 + 8 * (tid % 8), left = r < R ? K - k : 0;
-                const float *src = base + (left > 0 ? r * (int)op.ld + k : 0);
-                if (left >= 8) {
-                    const f32x4_any a = *(const f32x4_any *)src, b = *(const f32x4_any *)(src + 4);
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        v[u][j] = a[j];
-                        v[u][4 + j] = b[j];
-                    }
-                } else {
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) v[u][j] = j < left ? src[j] : 0.f;
-                }
+                load8(base + (left > 0 ? r * (int)op.ld + k : 0), left, v[u]);
             } else {
                 // rows and k beyond the operand: any valid element; commit replaces those of k, those of a row reach
                 // only results that are not stored

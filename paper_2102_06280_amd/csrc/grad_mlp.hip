@@ -455,7 +455,7 @@ int dbw_fc_forward_backward(dbw_ctx *c, const dbw_fc_args &a, hipStream_t s)
             float *part = act + 2 * per;
             {
                 dbw_timer tm(c, "mlp_forward_gemm", s);
-                DBW_HIP(bgemm::launch_dense(A, Bm, SplitOut{part, wstride, B, dims[l]}, B, dims[l], dims[l - 1], N, s,
+                DBW_HIP(bgemm::launch<64>(A, Bm, SplitOut{part, wstride, B, dims[l]}, B, dims[l], dims[l - 1], N, s,
                                           splits));
             }
             if (head_can_sum && l == L - 1) {
@@ -471,7 +471,7 @@ int dbw_fc_forward_backward(dbw_ctx *c, const dbw_fc_args &a, hipStream_t s)
         }
         Epilogue E{act + a_off[l], dims[l], wstride, params + b_off[l], c->ld, nullptr, 0, 0, l < L ? 1 : 0};
         dbw_timer tm(c, "mlp_forward_gemm", s);
-        DBW_HIP(bgemm::launch_dense(A, Bm, E, B, dims[l], dims[l - 1], N, s));
+        DBW_HIP(bgemm::launch<64>(A, Bm, E, B, dims[l], dims[l - 1], N, s));
     }
     // Weight gradients of the layers the GEMM kernels would take: all of them in one launch when the library may
     // choose and every operand allows 128-bit accesses.  Batches of 256 and more: mlp_wgrad.h, four wavefronts per

@@ -12,8 +12,7 @@
 // and writes a_1 .. a_{L-2} and dz_1 .. dz_{L-1} to the worker's scratch block, from where the weight
 // gradients dW_l = dz_l^T a_{l-1} (sums over the whole batch) are taken by the GEMM kernels.
 //
-// Products run on v_mfma_f32_16x16x4_f32 (true fp32), or where that is faster on the bf16 instruction with every value
-// split in three (chunk_split).  A wavefront owns 16 CB output columns of all
+// Products run on v_mfma_f32_16x16x4_f32 (true fp32).  A wavefront owns 16 CB output columns of all
 // S rows, worked off 32 columns at a time: RB x min(CB, 2) accumulator tiles.  Its A fragments come from the LDS image of the layer's input
 // (one 128-bit read per 16 rows and 16 k), its B fragments straight from the weights in global
 // memory (L2), since no other wavefront of the workgroup wants the same ones; they are fetched one
@@ -27,7 +26,6 @@
 #pragma once
 
 #include "fc_head.h"
-#include "split_bf16.h"
 
 namespace mlpchain {
 
@@ -155,68 +153,10 @@ __device__ __forceinline__ void chunk_mfma(f32x4 (&acc)[RB][CB], const float *ap
     }
 }
 
-// The split form of the same (split_bf16.h), taken where it is the faster one: three row blocks by two column blocks.
-// Both operands are split in registers, 44 vector instructions per fragment of eight values and wave, against 6 matrix
-// instructions per pair of fragments, so it takes some blocking to pay; four row blocks leave too few registers.  Whole
-// launches, split / fp32: 256-256-256-10 on 10 workers x 1 024 samples (3 x 2 blocks) 65 / 70 us; 4 workers (2 x 2) 45 / 39,
-// 20 workers (4 x 2) 195 / 169; 784-128-128-10 on 30 x 256 (2 x 1) 62 / 60; 64-512-512-10 on 10 x 1 500 (4 x 2) 338 / 298.
-// acc + small += A(rows of `in`, k0 .. k0 + 63) x (the chunk in b); FWD tells which of the two layouts b has.  Two units
-// of 16 k are one step of v_mfma_f32_16x16x32_bf16: the eight values of a lane (four of each unit, the same k for both
-// operands) are split into three bf16 values (split_bf16.h) in registers.  next(u) is called before the multiplies of the
-// step of unit u and issues the loads of unit u of the chunk after: a wavefront that issues all
-// loads of a chunk in one burst waits at the memory pipeline's queue with its matrix instructions behind them, and so
-// does its partner on the SIMD, which runs the same code.
-template <int RB, int CB, bool FWD, class Next>
-__device__ __forceinline__ void chunk_split(f32x4 (&acc)[RB][CB], f32x4 (&small)[RB][CB], const float *ap, int pitch, int k0,
-                                           const BRegs<CB> &b, Next next)
-{
-    f32x4 av[2][RB];
-    auto read = [&](int k) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int rb = 0; rb < RB; ++rb) av[h][rb] = *(const f32x4 *)(ap + 16 * rb * pitch + k + 16 * h);
-    };
-    read(k0);
-#pragma unroll
-    for (int st = 0; st < 2; ++st) {
-        next(2 * st);
-        next(2 * st + 1);
-        __builtin_amdgcn_sched_barrier(0);
-        split_bf16::planes pa[RB];
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb) {
-            float x[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) x[e] = av[e / 4][rb][e % 4];
-            pa[rb] = split_bf16::split8(x);
-        }
-        if (st == 0) read(k0 + 32);                  // arrives during the multiplies
-        // one column block at a time, or the planes of all of them would not fit the register file
-#pragma unroll
-        for (int cb = 0; cb < CB; ++cb) {
-            float x[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) x[e] = FWD ? b.v[2 * st + e / 4][4 * cb + e % 4] : b.v[2 * st + e / 4][CB * (e % 4) + cb];
-            split_bf16::mma16_column<RB, CB>(pa, split_bf16::split8(x), acc, small, cb);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-    }
-}
-
-template <int RB, int CB>
-__device__ __forceinline__ void zero(f32x4 (&acc)[RB][CB])
-{
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-        for (int cb = 0; cb < CB; ++cb) acc[rb][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
-}
-
 // The k loop of one product.  b0 holds chunk 0 on entry (when K >= 64); the chunks alternate between b0 and a
 // second set, each fetched while the other is multiplied, so that a fetch has a whole chunk of matrix
 // instructions (of both wavefronts of the SIMD) to arrive.  K is a multiple of 16; the 16-wide groups behind the
-// last whole chunk are fetched and multiplied one by one (fp32 matrix instructions).
+// last whole chunk are fetched and multiplied one by one.
 template <int RB, int CB, bool FWD>
 __device__ __forceinline__ void product(f32x4 (&acc)[RB][CB], const float *in, int pitch, int K, const float *__restrict__ Wg,
                                         int ldw, int n0, int lane, BRegs<CB> &b0)
@@ -229,41 +169,17 @@ __device__ __forceinline__ void product(f32x4 (&acc)[RB][CB], const float *in, i
         if (FWD) load_fwd_unit<CB>(b, Wg, ldw, 64 * kc, n0, lane, u);
         else load_bwd_unit<CB>(b, Wg, ldw, 64 * kc, n0, lane, u);
     };
-    constexpr bool SPLIT = RB == 3 && CB == 2;
-    f32x4 small[SPLIT ? RB : 1][SPLIT ? CB : 1];
-    if constexpr (SPLIT) zero<RB, CB>(small);
-    auto multiply = [&](int k0, const BRegs<CB> &b, auto next) {
-        if constexpr (SPLIT) chunk_split<RB, CB, FWD>(acc, small, ap, pitch, k0, b, next);
-        else chunk_mfma<RB, CB, FWD>(acc, ap, pitch, k0, b, next);
-    };
     for (int kc = 0; kc < nch; kc += 2) {
         const bool two = kc + 1 < nch, three = kc + 2 < nch;
-        multiply(64 * kc, b0, [&](int u) {
+        chunk_mfma<RB, CB, FWD>(acc, ap, pitch, 64 * kc, b0, [&](int u) {
             if (two) load_unit(b1, kc + 1, u);
         });
         if (two)
-            multiply(64 * (kc + 1), b1, [&](int u) {
+            chunk_mfma<RB, CB, FWD>(acc, ap, pitch, 64 * (kc + 1), b1, [&](int u) {
                 if (three) load_unit(b0, kc + 2, u);
             });
     }
-    int k = 64 * nch;
-    if constexpr (SPLIT) {
-        // the two parts of the sums; if one is not finite, all of the wave's with the fp32 matrix instructions
-        float t = 0.f;
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-            for (int cb = 0; cb < CB; ++cb) {
-                acc[rb][cb] += small[rb][cb];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) t = fmaf(acc[rb][cb][r], 0.f, t);
-            }
-        if (__any(t != t)) {
-            k = 0;
-            zero<RB, CB>(acc);
-        }
-    }
-    for (; k < K; k += 16) {
+    for (int k = 64 * nch; k < K; k += 16) {
         f32x4 av[RB];
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) av[rb] = *(const f32x4 *)(ap + 16 * rb * pitch + k);
@@ -293,6 +209,15 @@ __device__ __forceinline__ void product(f32x4 (&acc)[RB][CB], const float *in, i
                         acc[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[rb][j], bv[j].v[cb], acc[rb][cb], 0, 0, 0);
         }
     }
+}
+
+template <int RB, int CB>
+__device__ __forceinline__ void zero(f32x4 (&acc)[RB][CB])
+{
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) acc[rb][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
 }
 
 // Forward epilogue: out[s][n] = relu(acc + bias[n]) for this wavefront's columns n = n0 + 16 cb + l16.

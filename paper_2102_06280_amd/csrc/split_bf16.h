@@ -115,24 +115,6 @@ __device__ __forceinline__ void mma32_block(const planes (&a)[A], const planes (
     step(&planes::h, &planes::h);
 }
 
-// Column block j of A x B blocks of 16 x 16 outputs over 32 terms: lane l holds row (column) l % 16 and eight terms, the
-// same ones for both operands in lanes of the same l / 16.
-template <int A, int B>
-__device__ __forceinline__ void mma16_column(const planes (&a)[A], const planes &b, f32x4 (&large)[A][B], f32x4 (&small)[A][B], int j)
-{
-    auto step = [&](u32x4 planes::*pa, u32x4 planes::*pb, f32x4 (&acc)[A][B]) {
-#pragma unroll
-        for (int i = 0; i < A; ++i)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag(a[i].*pa), frag(b.*pb), acc[i][j], 0, 0, 0);
-    };
-    step(&planes::l, &planes::h, small);
-    step(&planes::h, &planes::h, large);
-    step(&planes::h, &planes::l, small);
-    step(&planes::m, &planes::m, small);
-    step(&planes::m, &planes::h, small);
-    step(&planes::h, &planes::m, small);
-}
-
 // NaN or infinity
 __device__ __forceinline__ bool not_finite(float v) { return (bits(v) & 0x7f800000u) == 0x7f800000u; }
 
