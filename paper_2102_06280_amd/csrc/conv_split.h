@@ -378,6 +378,217 @@ __global__ __launch_bounds__(THREADS, 2) void forward_kernel(FwdArgs a)
     }
 }
 
+// ---- forward pass, ReLU and pooling of a layer with few input channels (the network's first).
+//
+// With one or three channels the reduction of forward_kernel would be mostly padding.  Here it runs over pairs (c, kh),
+// two of them per step, with the KS taps of a row in a lane's eight values (the rest zero weights).  A lane's eight values of
+// the image are then eight consecutive pixels of a row, starting at any pixel: as in wgrad_kernel a lane reads aligned
+// ones, sixteen here, and the eight fragments for the output pixels 8 m .. 8 m + 7 are shifts of them in registers.  A wave
+// takes 32 positions (y, m) = 256 output pixels at a time, even and odd y in neighbouring lanes for the pooling; the
+// filters stay in LDS, split, over all samples of the workgroup.
+//
+// The matrix instructions bound it (5 of 8 values of a 5 x 5 filter's reduction are used).  16 workers x 50 samples, 1 -> 16
+// channels on 28 x 28 pixels, 5 x 5: 30 us (implicit fp32 GEMM 68, pooling pass 12); 32 x 32 samples, 3 -> 16 on 32 x 32,
+// 3 x 3: 41 (108 + 17); 64 x 32 samples, 3 -> 32 on 32 x 32, 5 x 5: 107 (an LDS-resident fp32 kernel 113).
+struct FirstPlan {
+    int spg, iters;             // samples in LDS at a time, and how often
+    size_t lds;
+};
+__host__ __device__ inline int first_groups(const Shape &s) { return (s.W + 7) / 8; }            // m
+__host__ __device__ inline int first_steps(const Shape &s) { return (s.Cin * s.KS + 1) / 2; }
+// 16-byte groups of one plane of one sample's image: rows of 8 m + 8 values
+__host__ __device__ inline int first_image(const Shape &s) { return s.Cin * (s.H + s.KS - 1) * (first_groups(s) + 1); }
+inline bool first_plan(const Shape &s, int workers, FirstPlan &p)
+{
+    const int per = s.H * first_groups(s);              // positions of a sample; four waves x 32 of them
+    p.spg = per >= 128 ? 1 : 128 / per;
+    if (p.spg > s.B) p.spg = s.B;
+    p.lds = 48 * ((size_t)p.spg * first_image(s) + (size_t)first_steps(s) * 64);
+    if (p.lds > 160 * 1024) {
+        p.spg = 1;
+        p.lds = 48 * ((size_t)first_image(s) + (size_t)first_steps(s) * 64);
+    }
+    const int64_t groups = (int64_t)((s.B + p.spg - 1) / p.spg) * workers;
+    p.iters = groups >= 4096 ? 4 : (groups >= 2048 ? 2 : 1);
+    return p.lds <= 160 * 1024;
+}
+
+// grid = (ceil(B / (spg iters)), workers, 32-row blocks of the output channels); dynamic LDS = plan.lds.  Of FwdArgs: s, in, wgt
+// (not split), bias, out, code.
+template <int KS>
+__global__ __launch_bounds__(THREADS, 2) void first_kernel(FwdArgs a, FirstPlan plan)
+{
+    extern __shared__ __attribute__((aligned(16))) u32x4 sm[];
+    const int H = a.s.H, W = a.s.W, Cin = a.s.Cin, Cout = a.s.Cout, pad = KS / 2, HP = H + KS - 1, M = first_groups(a.s), IPG = M + 1;
+    const int spg = plan.spg, image = first_image(a.s), iplane = spg * image, steps = first_steps(a.s), wplane = steps * 64;
+    const int pairs = Cin * KS, PP = H * W / 4, m0 = 32 * blockIdx.z;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int w = blockIdx.y;
+    u32x4 *img = sm, *wl = sm + 3 * iplane;
+    const float *inw = a.in + w * a.in_stride, *wg = a.wgt + w * a.wgt_stride;
+
+    for (int e = tid; e < wplane; e += THREADS) {        // filters: lane (row, half) of step e / 64 holds pair 2 step + half
+        const int ln = e % 64, pair = e / 64 * 2 + ln / 32, co = m0 + ln % 32;
+        float v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const bool ok = j < KS && pair < pairs && co < Cout;
+            const float f = wg[ok ? (co * pairs + pair) * KS + j : 0];
+            v[j] = ok ? f : 0.f;
+        }
+        const planes p = split_bf16::split8(v);
+        wl[e] = p.h;
+        wl[e + wplane] = p.m;
+        wl[e + 2 * wplane] = p.l;
+    }
+    for (int e = tid; e < 3 * iplane; e += THREADS) img[e] = u32x4{0u, 0u, 0u, 0u};      // the halo stays zero
+
+    for (int it = 0; it < plan.iters; ++it) {
+        const int b0 = (blockIdx.x * plan.iters + it) * spg, ns = min(spg, a.s.B - b0);
+        if (ns <= 0) break;                              // uniform
+        __syncthreads();                                 // the images before have been used
+        for (int e = tid; e < ns * Cin * H * IPG; e += THREADS) {
+            const int g = e % IPG, y = e / IPG % H, sc = e / IPG / H;                     // sc = sample Cin + channel
+            const float *src = inw + (((int64_t)b0 * Cin + sc) * H + y) * W;
+            float v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int x = 8 * g + j - pad;
+                const float f = src[min(max(x, 0), W - 1)];
+                v[j] = (unsigned)x < (unsigned)W ? f : 0.f;
+            }
+            const planes p = split_bf16::split8(v);
+            u32x4 *d = img + (sc * HP + y + pad) * IPG + g;
+            d[0] = p.h;
+            d[iplane] = p.m;
+            d[2 * iplane] = p.l;
+        }
+        __syncthreads();
+        const int total = ns * H * M;
+        for (int blk = wave; blk * 32 < total; blk += 4) {
+            // position n of the block: y parity innermost, then m, then pairs of rows, then samples
+            const int n = 32 * blk + (lane & 31), nn = n < total ? n : 0, q = nn >> 1;
+            const int m = q % M, yh = q / M % (H / 2), smp = q / M / (H / 2), dy = nn & 1;
+            const u32x4 *base = img + smp * image + (2 * yh + dy) * IPG + m;
+            f32x16 acc[8];
+#pragma unroll
+            for (int x = 0; x < 8; ++x)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[x][v] = 0.f;
+#pragma unroll 1
+            for (int st = 0; st < steps; ++st) {
+                const int p0 = 2 * st, p1 = min(2 * st + 1, pairs - 1);                   // (beyond the last pair: zero weights)
+                const u32x4 *src = base + ((lane < 32 ? (p0 / KS) * HP + p0 % KS : (p1 / KS) * HP + p1 % KS)) * IPG;
+                const u32x4 *ws = wl + st * 64 + lane;
+                const u32x4 fh = ws[0], fm = ws[wplane], fl = ws[2 * wplane];
+                uint32_t d[8];
+                auto read = [&](int plane) {
+                    const u32x4 lo = src[plane * iplane], hi = src[plane * iplane + 1];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        d[i] = lo[i];
+                        d[4 + i] = hi[i];
+                    }
+                };
+                auto shifted = [&](int x) {              // values x .. x + 7 of the sixteen
+                    u32x4 f;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        f[i] = x % 2 == 0 ? d[x / 2 + i] : __builtin_amdgcn_alignbit(d[x / 2 + i + 1], d[x / 2 + i], 16);
+                    return split_bf16::frag(f);
+                };
+                auto mma = [&](const u32x4 &f, split_bf16::bf16x8 b, int x) {
+                    acc[x] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(split_bf16::frag(f), b, acc[x], 0, 0, 0);
+                };
+                read(2);
+#pragma unroll
+                for (int x = 0; x < 8; ++x) mma(fh, shifted(x), x);
+                read(1);
+#pragma unroll
+                for (int x = 0; x < 8; ++x) {
+                    const auto b = shifted(x);
+                    mma(fm, b, x);
+                    mma(fh, b, x);
+                }
+                read(0);
+#pragma unroll
+                for (int x = 0; x < 8; ++x) {
+                    const auto b = shifted(x);
+                    mma(fl, b, x);
+                    mma(fm, b, x);
+                    mma(fh, b, x);
+                }
+            }
+            bool bad = false;
+#pragma unroll
+            for (int x = 0; x < 8; ++x) bad |= n < total && split_bf16::any_not_finite(acc[x]);
+            const bool plain = __any(bad);
+            // ---- the two lanes of a position pair hold the same four windows; each stores every other output channel
+            const int64_t wbase = yh * (W / 2) + 4 * m;
+            const int left = W / 2 - 4 * m;              // windows that exist
+#pragma unroll
+            for (int v2 = 0; v2 < 16; v2 += 2) {
+                const int co = m0 + 8 * (v2 / 4) + 4 * (lane >> 5) + v2 % 4 + dy;
+                float mx[4];
+                uint32_t code = 0;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    float r[2];
+                    uint32_t cd[2];
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        const int cv = co - dy + i;      // the bias of the register's channel
+                        const float bias = a.bias[w * a.bias_stride + min(cv, Cout - 1)];
+                        const float x0 = acc[2 * j][v2 + i] + bias, x1 = acc[2 * j + 1][v2 + i] + bias;
+                        const float y0 = quad<0xB1>(x0), y1 = quad<0xB1>(x1);             // the other row
+                        const float t0 = dy ? y0 : x0, t1 = dy ? y1 : x1, u0 = dy ? x0 : y0, u1 = dy ? x1 : y1;
+                        const float top = fmaxf(fmaxf(t0, t1), fmaxf(u0, u1));
+                        uint32_t k = u0 == top ? 2 : 3;
+                        k = t1 == top ? 1 : k;
+                        k = t0 == top ? 0 : k;
+                        cd[i] = top > 0.f ? k : 4;
+                        r[i] = fmaxf(top, 0.f);
+                    }
+                    mx[j] = dy ? r[1] : r[0];
+                    code |= (dy ? cd[1] : cd[0]) << (8 * j);
+                }
+                if (n < total && co < Cout && !plain) {
+                    const int64_t at = ((int64_t)(b0 + smp) * Cout + co) * PP + wbase;
+                    float *o = a.out + w * a.out_stride + at;
+                    uint8_t *c = a.code + w * a.code_stride + at;
+                    if (left >= 4) {
+                        typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+                        *(f32x4_any *)o = f32x4_any{mx[0], mx[1], mx[2], mx[3]};
+                    }
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        if (j < left) {
+                            if (left < 4) o[j] = mx[j];
+                            c[j] = (uint8_t)(code >> (8 * j));
+                        }
+                }
+            }
+            if (!plain) continue;
+            // ---- some sum is not finite: all of the wave's windows with plain multiply-adds (see split_bf16.h)
+#pragma unroll 1
+            for (int e = 0; e < 32; ++e) {
+                const int v = 2 * (e / 4) + dy, j = e % 4, co = m0 + 8 * (v / 4) + 4 * (lane >> 5) + v % 4;
+                if (n >= total || co >= Cout || j >= left) continue;
+                float r[4], top = 0.f;
+#pragma unroll 1
+                for (int k = 0; k < 4; ++k) {
+                    r[k] = plain_value<false>(a, w, b0 + smp, co, 2 * yh + k / 2, 8 * m + 2 * j + k % 2) + a.bias[w * a.bias_stride + co];
+                    top = k ? fmaxf(top, r[k]) : r[k];
+                }
+                const int64_t at = ((int64_t)(b0 + smp) * Cout + co) * PP + wbase + j;
+                a.out[w * a.out_stride + at] = fmaxf(top, 0.f);
+                a.code[w * a.code_stride + at] = (uint8_t)(!(top > 0.f) ? 4 : (r[0] == top ? 0 : (r[1] == top ? 1 : (r[2] == top ? 2 : 3))));
+            }
+        }
+    }
+}
+
 // ---- weight gradient: dW[co][c][kh][kw] = sum over samples and pixels of dz[co][y][x] in[c][y + kh - pad][x + kw - pad],
 // with dz given as pooled gradients and window codes.
 //

@@ -6,8 +6,8 @@
 // Parameter row layout: conv1 W [C1][C0][K][K], b [C1]; conv2 W [C2][C1][K][K], b [C2];
 // fc1 W [F][flat], b [F]; fc2 W [classes][F], b [classes].
 //
-// Convolutions with 3 x 3 and 5 x 5 filters take the LDS-resident kernels of conv_split.h (conv1 forward, and with 3 ->
-// 32 channels its weight gradient, those of conv_lds.h); the rest are implicit GEMMs on the batched fp32 MFMA
+// Convolutions with 3 x 3 and 5 x 5 filters take the LDS-resident kernels of conv_split.h (conv1's weight gradient with 3 ->
+// 32 channels that of conv_lds.h); the rest are implicit GEMMs on the batched fp32 MFMA
 // kernel: the patch matrix is never materialised, the operand loaders compute the input address of each element.
 //   forward   z[co][pix]      = sum_k  W[co][k] * patch[k][pix]        k = (ci, kh, kw)
 //   wgrad     dW[co][k]       = sum_pix dz[co][pix] * patch[k][pix]
@@ -350,8 +350,10 @@ struct cnn_layout {
     int64_t z1, p1, z2, p2, dp2, dz2, dp1, dz1, fc_act, part1, part2, filt_fwd, filt_bwd, code1, code2, total;
     int splits1, splits2;
     bool lds1;                      // conv1 by conv_lds.h (if the batch is aligned)
+    bool first;                     // conv1's forward pass by convsplit::first_kernel
     bool split1, split2;            // weight gradient of conv1 / all three products of conv2 by conv_split.h
     convsplit::WgradPlan wg1, wg2;
+    convsplit::FirstPlan fp;
 };
 
 // The kernels of conv_split.h take every 3 x 3 and 5 x 5 filter whose images fit LDS, however few the channels: with 2 -> 4
@@ -386,9 +388,10 @@ cnn_layout make_layout(const dbw_model &m, int workers)
     L.lds1 = L.KS == 5 && L.C0 == 3 && L.H == 32 && L.W == 32 && L.C1 == 32;
     L.split1 = conv_split_fits({L.C0, L.C1, L.H, L.W, L.KS, L.B}, workers, true, L.wg1);
     L.split2 = conv_split_fits({L.C1, L.C2, L.H2, L.W2, L.KS, L.B}, workers, false, L.wg2);
+    L.first = (L.KS == 3 || L.KS == 5) && convsplit::first_plan({L.C0, L.C1, L.H, L.W, L.KS, L.B}, workers, L.fp);
     int64_t o = 0;
     auto take = [&](int64_t n) { const int64_t at = o; o += (n + 63) / 64 * 64; return at; };
-    L.z1 = take(B * L.C1 * L.H * L.W);
+    L.z1 = take(L.first && L.split1 ? 0 : B * L.C1 * L.H * L.W);
     L.p1 = take(B * L.C1 * L.H2 * L.W2);
     L.z2 = take(L.split2 ? 0 : B * L.C2 * L.H2 * L.W2);
     L.p2 = take(B * L.flat);
@@ -459,18 +462,21 @@ int launch_grad_cnn(dbw_ctx *c, const float *params, const float *bx, const int3
     const ConvShape s1{L.C0, L.C1, L.H, L.W, L.KS, L.KS / 2}, s2{L.C1, L.C2, L.H2, L.W2, L.KS, L.KS / 2};
     const int pix1 = B * L.H * L.W, pix2 = B * L.H2 * L.W2;
     auto blocks = [](int64_t n) { return (unsigned)((n + 255) / 256); };
-    // conv1 has LDS-resident fp32 kernels for 5x5 filters, 3 -> 32 channels on 32 x 32 inputs: with 3 channels, more
-    // than half of a split reduction step (forward) or column block (weight gradient: 157 us against 115) is padding
-    const bool fast1 = KS_ == 5 && L.lds1 && (uintptr_t)bx % 16 == 0;
-
     uint8_t *code1 = (uint8_t *)(A + L.code1), *code2 = (uint8_t *)(A + L.code2);
     const int64_t cs = ws * 4;                         // worker stride of the code maps in bytes
-    if (fast1) {   // convolution + ReLU + pooling in one kernel
+    if (L.first && L.split1) {   // convolution + ReLU + pooling in one kernel
         dbw_timer tm(c, "conv1_forward", s);
-        constexpr int SB1 = 4;                         // samples per workgroup
-        hipLaunchKernelGGL((convlds::conv_forward_pool_multi_kernel<3, 2, 4, 32, 32, 5, 16, SB1>),
-                           dim3((B + SB1 - 1) / SB1, N), dim3(1024), 0, s, bx, xstride, params + L.w1, ld, L.C0 * KK,
-                           params + L.b1, ld, A + L.p1, ws, L.C0, B, code1, cs);
+        convsplit::FwdArgs g{};
+        g.s = {L.C0, L.C1, L.H, L.W, L.KS, B};
+        g.in = bx; g.in_stride = xstride;
+        g.wgt = params + L.w1; g.wgt_stride = ld;
+        g.bias = params + L.b1; g.bias_stride = ld;
+        g.out = A + L.p1; g.out_stride = ws;
+        g.code = code1; g.code_stride = cs;
+        const int per = L.fp.spg * L.fp.iters;
+        const dim3 grid((B + per - 1) / per, N, (L.C1 + 31) / 32);
+        if (L.KS == 3) hipLaunchKernelGGL(convsplit::first_kernel<3>, grid, dim3(convsplit::THREADS), L.fp.lds, s, g, L.fp);
+        else hipLaunchKernelGGL(convsplit::first_kernel<5>, grid, dim3(convsplit::THREADS), L.fp.lds, s, g, L.fp);
         DBW_HIP(hipGetLastError());
     } else {
         {
@@ -589,8 +595,7 @@ int launch_grad_cnn(dbw_ctx *c, const float *params, const float *bx, const int3
                               s));
     }
     int splits1 = L.splits1;
-    const bool coded1 = fast1 || L.split1;
-    if (fast1) {   // conv1 weight gradient
+    if (KS_ == 5 && L.lds1 && L.split1 && (uintptr_t)bx % 16 == 0) {   // conv1 weight gradient (conv_lds.h; it reads code1)
         const int nb = (B + WGRAD_SB - 1) / WGRAD_SB;
         splits1 = nb * 8;
         dbw_timer tm(c, "conv1_wgrad", s);
@@ -619,7 +624,7 @@ int launch_grad_cnn(dbw_ctx *c, const float *params, const float *bx, const int3
                            grads + L.b1, ld);
         DBW_HIP(hipGetLastError());
     }
-    const FinishLayer f1{A + L.part1, splits1, L.C1 * L.C0 * KK, grads + L.w1, grads + L.b1, coded1 ? code1 : nullptr, A + L.dp1,
+    const FinishLayer f1{A + L.part1, splits1, L.C1 * L.C0 * KK, grads + L.w1, grads + L.b1, L.split1 ? code1 : nullptr, A + L.dp1,
                          L.C1, L.H2 * L.W2};
     const FinishLayer f2{A + L.part2, L.splits2, L.C2 * L.C1 * KK, grads + L.w2, grads + L.b2, L.split2 ? code2 : nullptr, A + L.dp2,
                          L.C2, L.H4 * L.W4};
@@ -637,6 +642,7 @@ int dbw_cnn_prepare()
 {
     const void *kernels[] = {(const void *)convsplit::forward_kernel<1, true, false>, (const void *)convsplit::forward_kernel<2, true, false>,
                              (const void *)convsplit::forward_kernel<1, false, true>, (const void *)convsplit::forward_kernel<2, false, true>,
+                             (const void *)convsplit::first_kernel<3>, (const void *)convsplit::first_kernel<5>,
                              (const void *)convsplit::wgrad_kernel<3>, (const void *)convsplit::wgrad_kernel<5>};
     for (const void *k : kernels) DBW_HIP(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
     return DBW_OK;

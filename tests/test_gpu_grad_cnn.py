@@ -216,10 +216,12 @@ def test_config3_rounds_lock_step(B, orc, order):
 # The split convolution kernels at their edges: channels off multiples of 16 and 32, more than 32 and 64 output channels,
 # several samples per workgroup (4 x 4 and 6 x 6 maps), the last group of them partial, maps of more than 64 windows,
 # widths off multiples of 16, weight gradients with 1, 2, 4, 8 waves per block, with more blocks than waves of a workgroup, 3 x 3
-# and 5 x 5; and 7 x 7, which takes the implicit GEMM.
+# and 5 x 5; and 7 x 7, which takes the implicit GEMM.  Of the first layer: widths off multiples of 8 and of four windows, more
+# than 32 channels, several samples at a time, several turns per workgroup, images too large for LDS.
 SPLIT_SHAPES = [((1, 28, 28, 6, 16, 5, 20, 10), 5, 2), ((3, 8, 8, 17, 33, 3, 12, 4), 37, 2), ((2, 12, 12, 9, 40, 5, 12, 5), 9, 3),
                 ((1, 40, 44, 5, 12, 3, 10, 4), 3, 2), ((3, 16, 24, 70, 20, 5, 10, 4), 3, 2), ((1, 16, 16, 40, 72, 5, 10, 4), 4, 2),
-                ((2, 32, 32, 3, 3, 5, 10, 4), 4, 2), ((5, 20, 16, 6, 130, 3, 8, 3), 4, 2), ((1, 16, 12, 4, 6, 7, 8, 3), 4, 2)]
+                ((2, 32, 32, 3, 3, 5, 10, 4), 4, 2), ((5, 20, 16, 6, 130, 3, 8, 3), 4, 2), ((1, 16, 12, 4, 6, 7, 8, 3), 4, 2),
+                ((1, 8, 36, 33, 4, 5, 8, 3), 3, 2), ((3, 4, 4, 2, 2, 3, 5, 3), 70, 2), ((40, 24, 24, 4, 4, 5, 8, 3), 2, 2)]
 
 
 @pytest.mark.parametrize("shape,batch,n", SPLIT_SHAPES, ids=["-".join(map(str, s[0])) + f"-B{s[1]}" for s in SPLIT_SHAPES])
