@@ -19,7 +19,7 @@
 // Workgroup: 256 threads = 4 wavefronts, tile BM x BN (64 x 64 or 32 x 128), k-step 64.  Each wavefront owns a 32 x 32
 // part.  Two kernels:
 //
-// split_kernel (weight and data gradients of dense layers): every value is split into
+// backward_kernel, split_kernel (weight and data gradients of dense layers): every value is split into
 // three bf16 values (split_bf16.h) when the tile is written to LDS, as [plane][8 k][row][8 values], where a lane's
 // fragment of v_mfma_f32_32x32x16_bf16 is one 128-bit read.  A thread therefore fetches eight consecutive k of a row
 // at a time, of a row-contiguous operand with eight loads whose lanes run along the rows.  20 workers, batch 101,
@@ -329,17 +329,18 @@ struct SplitTile {
     }
 };
 
+constexpr int SPLIT_GROUPS = 3 * SplitTile<true>::GROUPS;     // LDS of one operand, in 16-byte groups
+
 template <bool KCA, bool KCB, class EP>
-__global__ __launch_bounds__(THREADS, 3) void split_kernel(Dense<KCA> A, Dense<KCB> B, EP E, int M, int N, int K, int splits, int kper)
+__device__ __forceinline__ void split_tile(const Dense<KCA> &A, const Dense<KCB> &B, const EP &E, int M, int N, int K, int splits,
+                                           int kper, int tile_n, int tile_m, int z, split_bf16::u32x4 *As, split_bf16::u32x4 *Bs)
 {
     typedef SplitTile<KCA> TA;
     typedef SplitTile<KCB> TB;
-    __shared__ __attribute__((aligned(16))) split_bf16::u32x4 As[3 * TA::GROUPS];
-    __shared__ __attribute__((aligned(16))) split_bf16::u32x4 Bs[3 * TB::GROUPS];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int w = blockIdx.z / splits, split = blockIdx.z % splits;
-    const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
+    const int w = z / splits, split = z % splits;
+    const int m0 = tile_m * 64, n0 = tile_n * 64;
     const int kbeg = split * kper, kend = min(K, kbeg + kper);
     const int wm = (wave % 2) * 32, wn = (wave / 2) * 32;
 
@@ -382,6 +383,96 @@ __global__ __launch_bounds__(THREADS, 3) void split_kernel(Dense<KCA> A, Dense<K
     }
 }
 
+// One problem set of split_tile: grid of tiles x workers x splits, flat.
+template <bool KCA, bool KCB, class EP>
+struct SplitProblem {
+    Dense<KCA> A;
+    Dense<KCB> B;
+    EP E;
+    int M, N, K, splits, kper;
+    __host__ __device__ int tiles() const { return ((M + 63) / 64) * ((N + 63) / 64); }
+    __device__ __forceinline__ void run(int id, split_bf16::u32x4 *As, split_bf16::u32x4 *Bs) const
+    {
+        const int tn = (N + 63) / 64, t = id % tiles();
+        split_tile(A, B, E, M, N, K, splits, kper, t % tn, t / tn, id / tiles(), As, Bs);
+    }
+};
+template <bool KCA, bool KCB, class EP>
+inline SplitProblem<KCA, KCB, EP> split_problem(const Dense<KCA> &A, const Dense<KCB> &B, const EP &E, int M, int N, int K, int splits = 1)
+{
+    const int kper = (K + splits - 1) / splits;
+    return {A, B, E, M, N, K, splits, (kper + BK - 1) / BK * BK};
+}
+
+// Column sums of the deltas dz [B][C] (the bias gradient): RG groups of rows, each with four independent partial sums,
+// combined in a fixed order; a workgroup of RG * COLS threads takes COLS columns.
+template <int RG, int COLS>
+__device__ __forceinline__ void column_sums(int B, int C, const float *__restrict__ d, float *__restrict__ db, int c0, float *part)
+{
+    const int cl = threadIdx.x % COLS, rg = threadIdx.x / COLS, o = c0 + cl;
+    float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
+    if (o < C) {
+        int b = rg;
+        for (; b + 3 * RG < B; b += 4 * RG) {
+            s0 += d[(int64_t)b * C + o];
+            s1 += d[(int64_t)(b + RG) * C + o];
+            s2 += d[(int64_t)(b + 2 * RG) * C + o];
+            s3 += d[(int64_t)(b + 3 * RG) * C + o];
+        }
+        for (; b < B; b += RG) s0 += d[(int64_t)b * C + o];
+    }
+    part[rg * COLS + cl] = (s0 + s1) + (s2 + s3);
+    __syncthreads();
+    if (rg == 0 && o < C) {
+        float s = part[cl];
+        for (int r = 1; r < RG; ++r) s += part[r * COLS + cl];
+        db[o] = s;
+    }
+}
+
+// The backward pass of one dense layer, whose three parts all wait for the same deltas and for nothing else: data gradient
+// (workgroups 0 .. nd - 1; none: nd = 0), weight gradient (the next nw) and bias gradient (the rest, `chunks` per worker; none:
+// db = nullptr).  As launches of their own the parts of the narrow layers leave most of the chip idle one after the
+// other: for 617-301-75-26 on 20 workers x 101 samples eight launches took 87 us, three take 50 (round 145 -> 122 us); for
+// 161-185-185-24 on 11 x 1 024 111 -> 75, for 784-256-256-10 on 40 x 100 79 -> 60.
+struct BiasSums {
+    const float *dz;
+    int64_t stride;
+    float *db;
+    int64_t stride_db;
+    int B, C, chunks;           // chunks of 8 columns (batches of 512 and more: 32 groups of rows) or of 32 (8 groups)
+};
+constexpr int LONG_BATCH = 512;
+template <class EP, class EPD>
+__global__ __launch_bounds__(THREADS, 3) void backward_kernel(SplitProblem<false, false, EP> wg, SplitProblem<true, false, EPD> dg, BiasSums bs,
+                                                              int nd, int nw)
+{
+    __shared__ __attribute__((aligned(16))) split_bf16::u32x4 As[SPLIT_GROUPS];
+    __shared__ __attribute__((aligned(16))) split_bf16::u32x4 Bs[SPLIT_GROUPS];
+    const int id = blockIdx.x;
+    if (id < nd) {
+        dg.run(id, As, Bs);
+    } else if (id < nd + nw) {
+        wg.run(id - nd, As, Bs);
+    } else {
+        const int c = (id - nd - nw) % bs.chunks, w = (id - nd - nw) / bs.chunks;
+        const float *d = bs.dz + w * bs.stride;
+        float *db = bs.db + w * bs.stride_db;
+        if (bs.B >= LONG_BATCH) column_sums<32, 8>(bs.B, bs.C, d, db, 8 * c, (float *)As);
+        else column_sums<8, 32>(bs.B, bs.C, d, db, 32 * c, (float *)As);
+    }
+}
+
+template <class EP, class EPD>
+inline hipError_t launch_backward(const SplitProblem<false, false, EP> &wg, const SplitProblem<true, false, EPD> *dg, const BiasSums &bs,
+                                  int workers, hipStream_t s)
+{
+    const int nd = dg ? dg->tiles() * workers * dg->splits : 0, nw = wg.tiles() * workers * wg.splits, nb = bs.db ? bs.chunks * workers : 0;
+    hipLaunchKernelGGL((backward_kernel<EP, EPD>), dim3(nd + nw + nb), dim3(THREADS), 0, s, wg, dg ? *dg : SplitProblem<true, false, EPD>{},
+                       bs, nd, nw);
+    return hipGetLastError();
+}
+
 // BM = 32 uses 32 x 128 tiles (for problems with at most 32 rows), otherwise 64 x 64.
 template <int BM, class LA, class LB, class EP>
 inline hipError_t launch(const LA &A, const LB &B, const EP &E, int M, int N, int K, int batch, hipStream_t s,
@@ -395,15 +486,18 @@ inline hipError_t launch(const LA &A, const LB &B, const EP &E, int M, int N, in
     return hipGetLastError();
 }
 
-// The same of two dense operands, 64 x 64 tiles.
-template <bool KCA, bool KCB, class EP>
-inline hipError_t launch_dense(const Dense<KCA> &A, const Dense<KCB> &B, const EP &E, int M, int N, int K, int batch, hipStream_t s,
-                               int splits = 1)
+// The data gradient alone (its layer's weight gradient has another kernel).
+template <class EP>
+__global__ __launch_bounds__(THREADS, 3) void split_kernel(SplitProblem<true, false, EP> p)
 {
-    int kper = (K + splits - 1) / splits;
-    kper = (kper + BK - 1) / BK * BK;
-    const dim3 grid((N + 63) / 64, (M + 63) / 64, batch * splits);
-    hipLaunchKernelGGL((split_kernel<KCA, KCB, EP>), grid, dim3(THREADS), 0, s, A, B, E, M, N, K, splits, kper);
+    __shared__ __attribute__((aligned(16))) split_bf16::u32x4 As[SPLIT_GROUPS];
+    __shared__ __attribute__((aligned(16))) split_bf16::u32x4 Bs[SPLIT_GROUPS];
+    p.run(blockIdx.x, As, Bs);
+}
+template <class EP>
+inline hipError_t launch_split(const SplitProblem<true, false, EP> &p, int workers, hipStream_t s)
+{
+    hipLaunchKernelGGL(split_kernel<EP>, dim3(p.tiles() * workers * p.splits), dim3(THREADS), 0, s, p);
     return hipGetLastError();
 }
 

@@ -95,35 +95,13 @@ __global__ __launch_bounds__(256) void softmax_loss_kernel(
     }
 }
 
-// Bias gradient: db[o] = sum over the batch of dz[s][o].  grid = (ceil(C / 32), workers); a
-// workgroup covers 32 columns with RG groups of 32 threads that stride over the batch, four
-// independent partial sums each, combined in a fixed order.
-template <int RG>
-__global__ __launch_bounds__(32 * RG) void colsum_kernel(int B, int C, const float *__restrict__ dz, int64_t stride_dz,
-                                                         float *__restrict__ db, int64_t stride_db)
+// Bias gradient: db[o] = sum over the batch of dz[s][o], for the layers whose weight gradient has a kernel of its own.
+// grid = (ceil(C / 32), workers).
+__global__ __launch_bounds__(256) void colsum_kernel(int B, int C, const float *__restrict__ dz, int64_t stride_dz,
+                                                     float *__restrict__ db, int64_t stride_db)
 {
-    __shared__ float part[RG][32];
-    const int w = blockIdx.y, cl = threadIdx.x & 31, rg = threadIdx.x >> 5;
-    const int o = blockIdx.x * 32 + cl;
-    const float *d = dz + w * stride_dz;
-    float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-    if (o < C) {
-        int b = rg;
-        for (; b + 3 * RG < B; b += 4 * RG) {
-            s0 += d[(int64_t)b * C + o];
-            s1 += d[(int64_t)(b + RG) * C + o];
-            s2 += d[(int64_t)(b + 2 * RG) * C + o];
-            s3 += d[(int64_t)(b + 3 * RG) * C + o];
-        }
-        for (; b < B; b += RG) s0 += d[(int64_t)b * C + o];
-    }
-    part[rg][cl] = (s0 + s1) + (s2 + s3);
-    __syncthreads();
-    if (rg == 0 && o < C) {
-        float s = part[0][cl];
-        for (int r = 1; r < RG; ++r) s += part[r][cl];
-        db[w * stride_db + o] = s;
-    }
+    __shared__ float part[256];
+    bgemm::column_sums<8, 32>(B, C, dz + blockIdx.y * stride_dz, db + blockIdx.y * stride_db, 32 * blockIdx.x, part);
 }
 
 // Partial sums of a split-k forward GEMM: part[worker][split][m][n].
@@ -601,6 +579,16 @@ int dbw_fc_forward_backward(dbw_ctx *c, const dbw_fc_args &a, hipStream_t s)
     for (int l = Lw; l >= 1; --l) {
         const bool fast = batch32_layer(B, dims[l - 1], dims[l], c->ld, w_off[l], params, grads) && wstride % 4 == 0 &&
                           dz_off[l] % 4 == 0 && fc32::aligned16(act);
+        // the data gradient: dz_{l-1} = (dz_l W_l) masked by a_{l-1} > 0, or that of the stack's input, unmasked
+        const bool dgrad32 = l > 1 ? fast && a_off[l - 1] % 4 == 0 && dz_off[l - 1] % 4 == 0
+                                   : a.din && fast && a.din_ld % 4 == 0 && a.din_stride % 4 == 0 && fc32::aligned16(a.din);
+        bool dgrad_gemm = !dgrad32 && (l > 1 || a.din);
+        const auto dg = bgemm::split_problem(
+            Dense<true>{act + dz_off[l], dims[l], wstride}, Dense<false>{params + w_off[l], dims[l - 1], c->ld},
+            l > 1 ? Epilogue{act + dz_off[l - 1], dims[l - 1], wstride, nullptr, 0, act + a_off[l - 1], dims[l - 1], wstride, 0}
+                  : Epilogue{a.din, a.din_ld, a.din_stride, nullptr, 0, nullptr, 0, 0, 0},
+            B, dims[l - 1], dims[l]);
+        bool bias = !grouped && !(head.use && l == L - 1);   // (the head has written the bias gradient of the layer below it)
         if (!grouped) {   // dW_l = dz_l^T a_{l-1}
             Dense<false> A{act + dz_off[l], dims[l], wstride}, Bm;
             if (l == 1)
@@ -614,7 +602,11 @@ int dbw_fc_forward_backward(dbw_ctx *c, const dbw_fc_args &a, hipStream_t s)
                                    grads + w_off[l], c->ld);
                 DBW_HIP(hipGetLastError());
             } else {
-                // few output tiles and a long batch: split the reduction like the forward pass does
+                // with the data and the bias gradient of the layer in one launch; few output tiles and a long batch: split
+                // the reduction like the forward pass does
+                const int cols = B >= bgemm::LONG_BATCH ? 8 : 32;
+                const bgemm::BiasSums bs{act + dz_off[l], wstride, bias ? grads + b_off[l] : nullptr, c->ld, B, dims[l],
+                                         (dims[l] + cols - 1) / cols};
                 int splits = forward_splits(dims[l], dims[l - 1], B, N);
                 int64_t part_cap = 0;
                 for (int q = 1; q <= L; ++q) part_cap = std::max<int64_t>(part_cap, (int64_t)MAX_SPLITS * B * dims[q]);
@@ -623,8 +615,9 @@ int dbw_fc_forward_backward(dbw_ctx *c, const dbw_fc_args &a, hipStream_t s)
                     float *part = act + 2 * per;
                     {
                         dbw_timer tm(c, "mlp_wgrad_gemm", s);
-                        DBW_HIP(bgemm::launch_dense(A, Bm, SplitOut{part, wstride, dims[l], dims[l - 1]}, dims[l], dims[l - 1],
-                                                  B, N, s, splits));
+                        DBW_HIP(bgemm::launch_backward(bgemm::split_problem(A, Bm, SplitOut{part, wstride, dims[l], dims[l - 1]}, dims[l],
+                                                                            dims[l - 1], B, splits),
+                                                       dgrad_gemm ? &dg : nullptr, bs, N, s));
                     }
                     dbw_timer tm(c, "fc_reduce_kernel", s);
                     hipLaunchKernelGGL(fc_reduce_kernel, dim3((dims[l] * dims[l - 1] + 255) / 256, N), dim3(256), 0, s, part,
@@ -634,46 +627,34 @@ int dbw_fc_forward_backward(dbw_ctx *c, const dbw_fc_args &a, hipStream_t s)
                 } else {
                     Epilogue E{grads + w_off[l], dims[l - 1], c->ld, nullptr, 0, nullptr, 0, 0, 0};
                     dbw_timer tm(c, "mlp_wgrad_gemm", s);
-                    DBW_HIP(bgemm::launch_dense(A, Bm, E, dims[l], dims[l - 1], B, N, s));
+                    DBW_HIP(bgemm::launch_backward(bgemm::split_problem(A, Bm, E, dims[l], dims[l - 1], B), dgrad_gemm ? &dg : nullptr,
+                                                   bs, N, s));
                 }
+                dgrad_gemm = bias = false;
             }
         }
-        if (!grouped && !(head.use && l == L - 1)) {       // the head has written the bias gradient of the layer below it
+        if (bias) {
             dbw_timer tm(c, "colsum_kernel", s);
-            if (B >= 512)    // long batches: 32 row groups per workgroup
-                hipLaunchKernelGGL(colsum_kernel<32>, dim3((dims[l] + 31) / 32, N), dim3(1024), 0, s, B, dims[l],
-                                   act + dz_off[l], wstride, grads + b_off[l], c->ld);
-            else
-                hipLaunchKernelGGL(colsum_kernel<8>, dim3((dims[l] + 31) / 32, N), dim3(256), 0, s, B, dims[l],
-                                   act + dz_off[l], wstride, grads + b_off[l], c->ld);
+            hipLaunchKernelGGL(colsum_kernel, dim3((dims[l] + 31) / 32, N), dim3(256), 0, s, B, dims[l], act + dz_off[l], wstride,
+                               grads + b_off[l], c->ld);
             DBW_HIP(hipGetLastError());
         }
-        if (l > 1 && fast && a_off[l - 1] % 4 == 0 && dz_off[l - 1] % 4 == 0) {
+        if (l > 1 && dgrad32) {
             dbw_timer tm(c, "fc32_dgrad", s);
             hipLaunchKernelGGL(fc32::dgrad_kernel<4>, dim3(dims[l - 1] / 128, N), dim3(fc32::THREADS), 0, s, dims[l],
                                dims[l - 1], act + dz_off[l], (int64_t)dims[l], wstride, params + w_off[l], c->ld,
                                act + a_off[l - 1], (int64_t)dims[l - 1], wstride, act + dz_off[l - 1],
                                (int64_t)dims[l - 1], wstride);
             DBW_HIP(hipGetLastError());
-        } else if (l == 1 && a.din && fast && a.din_ld % 4 == 0 && a.din_stride % 4 == 0 && fc32::aligned16(a.din)) {
+        } else if (dgrad32) {
             dbw_timer tm(c, "fc32_dgrad", s);
             hipLaunchKernelGGL(fc32::dgrad_kernel<1>, dim3(dims[0] / 512, N), dim3(fc32::THREADS), 0, s, dims[1], dims[0],
                                act + dz_off[1], (int64_t)dims[1], wstride, params + w_off[1], c->ld,
                                (const float *)nullptr, (int64_t)0, (int64_t)0, a.din, a.din_ld, a.din_stride);
             DBW_HIP(hipGetLastError());
-        } else if (l > 1) {   // dz_{l-1} = (dz_l W_l) masked by a_{l-1} > 0
-            Dense<true> A{act + dz_off[l], dims[l], wstride};
-            Dense<false> Bm{params + w_off[l], dims[l - 1], c->ld};
-            Epilogue E{act + dz_off[l - 1], dims[l - 1], wstride, nullptr, 0, act + a_off[l - 1], dims[l - 1],
-                       wstride, 0};
+        } else if (dgrad_gemm) {
             dbw_timer tm(c, "mlp_dgrad_gemm", s);
-            DBW_HIP(bgemm::launch_dense(A, Bm, E, B, dims[l - 1], dims[l], N, s));
-        } else if (a.din) {   // gradient with respect to the stack's input, unmasked
-            Dense<true> A{act + dz_off[1], dims[1], wstride};
-            Dense<false> Bm{params + w_off[1], dims[0], c->ld};
-            Epilogue E{a.din, a.din_ld, a.din_stride, nullptr, 0, nullptr, 0, 0, 0};
-            dbw_timer tm(c, "mlp_dgrad_gemm", s);
-            DBW_HIP(bgemm::launch_dense(A, Bm, E, B, dims[0], dims[1], N, s));
+            DBW_HIP(bgemm::launch_split(dg, N, s));
         }
     }
     if (grouped) {

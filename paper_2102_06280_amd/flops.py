@@ -20,7 +20,8 @@ def _mlp(cfg, dims):
     dgrad = [2 * B * dims[l] * dims[l + 1] for l in range(1, last)]
     table = {"fc_head_kernel": _head(B, n, dims[-2], dims[-1], L > 1)}
     if fwd:
-        table.update({"mlp_forward_gemm": n * sum(fwd) / len(fwd), "mlp_wgrad_gemm": n * sum(fwd) / len(fwd),
+        table.update({"mlp_forward_gemm": n * sum(fwd) / len(fwd),
+                      "mlp_wgrad_gemm": n * (sum(fwd) + sum(dgrad)) / len(fwd),      # a layer's weight and data gradient
                       "mlp_thin_forward": n * sum(fwd) / len(fwd)})
     if dgrad:
         table["mlp_dgrad_gemm"] = n * sum(dgrad) / len(dgrad)
@@ -44,7 +45,8 @@ def _cnn(cfg, desc):
     if B == 32 and flat % 512 == 0 and f % 32 == 0:      # the first FC layer runs on the batch-32 kernels
         table.update({"fc32_forward": n * fc[0], "fc32_wgrad": n * fc[0], "fc32_dgrad": n * fc[0]})
     else:
-        table.update({"mlp_forward_gemm": n * fc[0], "mlp_wgrad_gemm": n * fc[0], "mlp_dgrad_gemm": n * fc[0]})
+        table.update({"mlp_forward_gemm": n * fc[0], "mlp_wgrad_gemm": 2 * n * fc[0],
+                      "mlp_dgrad_gemm": n * fc[0]})
     return table
 
 

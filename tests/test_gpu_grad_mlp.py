@@ -425,8 +425,9 @@ def test_graph_replay_matches_eager(B, cid):
 
 # The dense product kernel at its edges, on rows without padding (4-byte boundaries, the last row ends the allocation):
 # widths below one group of eight, one off 64 on either side, batches of one tile and one row more, a reduction split with a
-# partial last tile, more than 16 classes (every layer goes through it), few tiles (split) and many.
-DENSE_SHAPES = [([65, 63, 70, 20], 66, 3), ([7, 9, 21], 130, 2), ([129, 64, 33, 18], 65, 4), ([617, 31, 26], 101, 3), ([3, 17], 257, 2)]
+# partial last tile, more than 16 classes (every layer goes through it), few tiles (split) and many; bias sums of long and
+# short batches, columns off their chunks.
+DENSE_SHAPES = [([65, 63, 70, 20], 66, 3), ([7, 9, 21], 130, 2), ([129, 64, 33, 18], 65, 4), ([617, 31, 26], 101, 3), ([3, 17], 257, 2), ([65, 70, 33, 20], 515, 2)]
 
 
 @pytest.mark.parametrize("dims,batch,n", DENSE_SHAPES, ids=[f"{'-'.join(map(str, s[0]))}-B{s[1]}-N{s[2]}" for s in DENSE_SHAPES])
