@@ -203,13 +203,25 @@ __global__ __launch_bounds__(64 * WAVES, 2) void kernel(
         split_bf16::f32x16 acc;
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+        // all small partial products first: the accumulator is then rounded in units of the result's size once per 16 terms only
+        // (256 workers: error of a round against 64 bits 2.5e-7, in one pass 3.7e-7, fp32 instruction 3.2 to 3.6e-7; same time)
 #pragma unroll
         for (int s = 0; s < C::KS; ++s) {
             split_bf16::planes b;
             b.h = b0[2 * s * C::TC];
             b.m = b0[2 * s * C::TC + C::GROUPS];
             b.l = b0[2 * s * C::TC + 2 * C::GROUPS];
-            acc = split_bf16::mma32(P[s], b, acc);
+            acc = split_bf16::mma32_small(P[s], b, acc);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int s4 = 0; s4 < C::KS; s4 += STEP) {
+            u32x4 h[STEP];
+#pragma unroll
+            for (int s = 0; s < STEP; ++s) h[s] = b0[2 * (s4 + s) * C::TC];
+#pragma unroll
+            for (int s = 0; s < STEP; ++s)
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(split_bf16::frag(P[s4 + s].h), split_bf16::frag(h[s]), acc, 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
         }
         bad |= __any(split_bf16::any_not_finite(acc));

@@ -11,7 +11,8 @@
 // in the loop as well).  The result is closer to the exact sum than the fp32 instruction's, because an accumulator is
 // rounded 6 times per 16 terms instead of 8 times, and 5 of the 6 additions are small ones: relative error against
 // 64 bits 1.1e-7 / 2.4e-7 / 4.3e-7 / 7.0e-7 at 64 / 256 / 800 / 2048 terms, against 1.4e-7 / 2.9e-7 / 5.1e-7 /
-// 8.1e-7 (normally distributed operands; positive weights give the same figures).
+// 8.1e-7 (normally distributed operands; positive weights give the same figures).  With all small partial products of a sum
+// first, or in an accumulator of their own, the large ones are rounded once per 16 terms: a third of that error again.
 //
 // An operand that is not finite makes the middle term NaN, and with it every sum it enters: an infinity does not
 // survive as one.  Kernels therefore look at their sums and compute the ones that are not finite again with plain
@@ -68,21 +69,20 @@ __device__ __forceinline__ planes split8(const float (&x)[8])
 
 __device__ __forceinline__ bf16x8 frag(const u32x4 &v) { return __builtin_bit_cast(bf16x8, v); }
 
-// acc += a b over 16 terms (32 x 32 outputs), smallest partial products first.  Lane l holds row (or column) l % 32
-// of the operand and the terms 8 (l / 32) .. + 7 of the step: any assignment of terms to lanes that is the same for both
-// operands gives the same sums.
-__device__ __forceinline__ f32x16 mma32(const planes &a, const planes &b, f32x16 acc)
+// acc += a b over 16 terms (32 x 32 outputs) without the large partial products h h, smallest ones first.  Lane l holds row
+// (or column) l % 32 of the operand and the terms 8 (l / 32) .. + 7 of the step: any assignment of terms to lanes that is
+// the same for both operands gives the same sums.
+__device__ __forceinline__ f32x16 mma32_small(const planes &a, const planes &b, f32x16 acc)
 {
     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(a.l), frag(b.h), acc, 0, 0, 0);
     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(a.h), frag(b.l), acc, 0, 0, 0);
     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(a.m), frag(b.m), acc, 0, 0, 0);
     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(a.m), frag(b.h), acc, 0, 0, 0);
     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(a.h), frag(b.m), acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(a.h), frag(b.h), acc, 0, 0, 0);
     return acc;
 }
 
-// The same with an accumulator of its own for the five small partial products: the large one is then rounded once per
+// All of them, with an accumulator of its own for the five small partial products: the large one is then rounded once per
 // 16 terms, and the sum of the two (the caller's) is three times closer to the exact one (9e-8 at 256 terms, 1.6e-7 at
 // 800); also two shorter chains of dependent instructions.
 __device__ __forceinline__ void mma32(const planes &a, const planes &b, f32x16 &large, f32x16 &small)
