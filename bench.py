@@ -24,6 +24,8 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E
 MFMA_FP32_PEAK_TFLOPS = 157.3  # MI355X dense fp32 matrix
+MFMA_SPLIT_PEAK_TFLOPS = 2516.6 / 6   # fp32 values as three bf16 values: six dense bf16 matrix instructions for each product
+SPLIT_KERNELS = ("mix_dense", "conv1_forward", "conv2_")   # (the timing names of the kernels that do so)
 
 def measured_traffic(kernel: str, cid: int):
     """HBM bytes per launch from hardware counters, as tabulated in profiles/hbm_traffic.md, or None
@@ -253,6 +255,9 @@ def main():
         work = kernel_flops(cfg, dominant)
         roofline = {"bound": "mfma", "achieved": work / (dom_ms * 1e-3) / 1e12, "peak": MFMA_FP32_PEAK_TFLOPS,
                     "unit": "TFLOP/s", "traffic": None}
+    split = dominant.startswith(SPLIT_KERNELS) and not (dominant.startswith("mix_dense") and cfg.n <= 32)
+    if split:
+        roofline["peak"] = MFMA_SPLIT_PEAK_TFLOPS
     roofline["traffic"] = measured_traffic(dominant, cfg.cid)
     roofline["frac"] = roofline["achieved"] / roofline["peak"]
     roofline["kernel"] = dominant
@@ -305,12 +310,12 @@ def main():
         del wl2
         torch.cuda.empty_cache()
     # what plain kernels reach on this device, next to the nominal peak: a streaming triad
-    # over three 1 GiB arrays, or register-resident fp32 matrix instructions
+    # over three 1 GiB arrays, or register-resident fp32 matrix instructions (no such loop for the split form)
     if roofline["bound"] == "hbm":
         roofline["achievable"] = B.dbw_calibrate(B.CAL_HBM_TRIAD, 1 << 30, 10)
     else:
-        roofline["achievable"] = B.dbw_calibrate(B.CAL_MFMA_FP32, 4096, 5)
-    roofline["frac_of_achievable"] = roofline["achieved"] / roofline["achievable"]
+        roofline["achievable"] = None if split else B.dbw_calibrate(B.CAL_MFMA_FP32, 4096, 5)
+    roofline["frac_of_achievable"] = roofline["achieved"] / roofline["achievable"] if roofline["achievable"] else None
     if not args.no_cpu_baseline:
         out["cpu_baseline"] = cpu_baseline(args.config, rowptr, colidx)
     print(json.dumps(out))
