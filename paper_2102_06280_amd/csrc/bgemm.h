@@ -366,20 +366,12 @@ __device__ __forceinline__ void split_tile(const Dense<KCA> &A, const Dense<KCB>
 #pragma unroll
         for (int s = 0; s < BK / 16; ++s) split_bf16::mma32(TA::frag(As, wm, s, lane), TB::frag(Bs, wn, s, lane), acc, small);
     }
-    acc += small;
+    split_bf16::add_small(acc, small);
     const int n = n0 + wn + (lane & 31);
-    const bool bad = __any(split_bf16::any_not_finite(acc));
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
         const int m = m0 + wm + 8 * (v / 4) + 4 * (lane >> 5) + v % 4;
-        if (m >= M || n >= N) continue;
-        float r = acc[v];
-        if (bad && split_bf16::not_finite(r)) {          // once more, with plain multiply-adds (split_bf16.h)
-            r = 0.f;
-            for (int k = kbeg; k < kend; ++k)
-                r = fmaf(A.load(w, A.row_ctx(m, true), A.k_ctx(k, true)), B.load(w, B.row_ctx(n, true), B.k_ctx(k, true)), r);
-        }
-        E.store(w, split, m, n, r);
+        if (m < M && n < N) E.store(w, split, m, n, acc[v]);
     }
 }
 

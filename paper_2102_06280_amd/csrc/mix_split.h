@@ -193,38 +193,25 @@ __global__ __launch_bounds__(64 * WAVES, 2) void kernel(
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
 
-    int bad = 0;                                       // uniform: some sum of this wave was not finite
     int buf = 0;
     for (; tile < n_tiles; tile += gridDim.x) {
         const int64_t next = tile + gridDim.x;
         const int64_t col0 = tile * C::TC + 32 * cg;                              // uniform
         const bool full = 32 * rb + 32 <= N && col0 + 32 <= dcols;                // uniform: no element needs a guard
         const u32x4 *b0 = &pl[buf][0][(lane >> 5) * C::TC + 32 * cg + (lane & 31)];
-        split_bf16::f32x16 acc;
+        split_bf16::f32x16 acc, small;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-        // all small partial products first: the accumulator is then rounded in units of the result's size once per 16 terms only
-        // (256 workers: error of a round against 64 bits 2.5e-7, in one pass 3.7e-7, fp32 instruction 3.2 to 3.6e-7; same time)
+        for (int v = 0; v < 16; ++v) acc[v] = small[v] = 0.f;
 #pragma unroll
         for (int s = 0; s < C::KS; ++s) {
             split_bf16::planes b;
             b.h = b0[2 * s * C::TC];
             b.m = b0[2 * s * C::TC + C::GROUPS];
             b.l = b0[2 * s * C::TC + 2 * C::GROUPS];
-            acc = split_bf16::mma32_small(P[s], b, acc);
+            split_bf16::mma32(P[s], b, acc, small);
             __builtin_amdgcn_sched_barrier(0);
         }
-#pragma unroll
-        for (int s4 = 0; s4 < C::KS; s4 += STEP) {
-            u32x4 h[STEP];
-#pragma unroll
-            for (int s = 0; s < STEP; ++s) h[s] = b0[2 * (s4 + s) * C::TC];
-#pragma unroll
-            for (int s = 0; s < STEP; ++s)
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(split_bf16::frag(P[s4 + s].h), split_bf16::frag(h[s]), acc, 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        bad |= __any(split_bf16::any_not_finite(acc));
+        split_bf16::add_small(acc, small);
 
         // ---- local SGD correction and store, 32 consecutive columns per row
         if (EPI) {
@@ -274,26 +261,6 @@ __global__ __launch_bounds__(64 * WAVES, 2) void kernel(
         asm volatile("" ::: "memory");
         buf ^= 1;
     }
-
-    // ---- results that are not finite once more, with plain multiply-adds (see split_bf16.h): the wave looks through
-    // everything it stored, each lane its own elements; only a run that has such values pays for it
-    if (!bad) return;
-    for (tile = blockIdx.x; tile < n_tiles; tile += gridDim.x)
-#pragma unroll 1
-        for (int e = 0; e < 16; ++e) {
-            const int row = 32 * rb + 8 * (e / 4) + e % 4 + 4 * (lane >> 5);
-            const int64_t col = tile * C::TC + 32 * cg + (lane & 31);
-            if (row >= N || col >= dcols || !split_bf16::not_finite(out[(int64_t)row * ld + col])) continue;
-            float r = 0.f;
-            for (int j = 0; j < N; ++j) {
-                const float p = Wsw[((size_t)rb * (C::NPAD / 2) + (j >> 1)) * 64 + 32 * (j & 1) + row % 32];
-                float xv = x[(int64_t)j * ld + col];
-                if (PRO) xv = fmaf(-lr.at(j), g[(int64_t)j * ld + col], xv);
-                r = fmaf(p, xv, r);
-            }
-            if (EPI) r = fmaf(-lr.at(row), g[(int64_t)row * ld + col], r);
-            out[(int64_t)row * ld + col] = r;
-        }
 }
 
 }  // namespace mixsplit

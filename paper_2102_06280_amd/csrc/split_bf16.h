@@ -14,9 +14,8 @@
 // 8.1e-7 (normally distributed operands; positive weights give the same figures).  With all small partial products of a sum
 // first, or in an accumulator of their own, the large ones are rounded once per 16 terms: a third of that error again.
 //
-// An operand that is not finite makes the middle term NaN, and with it every sum it enters: an infinity does not
-// survive as one.  Kernels therefore look at their sums and compute the ones that are not finite again with plain
-// fp32 multiply-adds, so that infinities and NaN come out as they do elsewhere.
+// An operand that is not finite makes the middle value NaN, and with it every small partial product it enters: an infinity
+// does not survive as one.  It does among the large ones, which is why their sum decides (add_small).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -69,22 +68,11 @@ __device__ __forceinline__ planes split8(const float (&x)[8])
 
 __device__ __forceinline__ bf16x8 frag(const u32x4 &v) { return __builtin_bit_cast(bf16x8, v); }
 
-// acc += a b over 16 terms (32 x 32 outputs) without the large partial products h h, smallest ones first.  Lane l holds row
-// (or column) l % 32 of the operand and the terms 8 (l / 32) .. + 7 of the step: any assignment of terms to lanes that is
-// the same for both operands gives the same sums.
-__device__ __forceinline__ f32x16 mma32_small(const planes &a, const planes &b, f32x16 acc)
-{
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(a.l), frag(b.h), acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(a.h), frag(b.l), acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(a.m), frag(b.m), acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(a.m), frag(b.h), acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(a.h), frag(b.m), acc, 0, 0, 0);
-    return acc;
-}
-
-// All of them, with an accumulator of its own for the five small partial products: the large one is then rounded once per
-// 16 terms, and the sum of the two (the caller's) is three times closer to the exact one (9e-8 at 256 terms, 1.6e-7 at
-// 800); also two shorter chains of dependent instructions.
+// large + small += a b over 16 terms (32 x 32 outputs).  Lane l holds row (or column) l % 32 of the operand and the terms 8 (l / 32) ..
+// + 7 of the step: any assignment of terms to lanes that is the same for both operands gives the same sums.  The large partial
+// products, of 16 bits each, have an accumulator of their own, which is rounded once per 16 terms and for a few terms hardly at all;
+// the sum of the two (the caller's) is two to three times closer to the exact one than a single accumulator (9e-8 at
+// 256 terms, 1.6e-7 at 800); also two shorter chains of dependent instructions.
 __device__ __forceinline__ void mma32(const planes &a, const planes &b, f32x16 &large, f32x16 &small)
 {
     small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(a.l), frag(b.h), small, 0, 0, 0);
@@ -95,8 +83,8 @@ __device__ __forceinline__ void mma32(const planes &a, const planes &b, f32x16 &
     small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(a.h), frag(b.m), small, 0, 0, 0);
 }
 
-// The same for a block of A x B accumulators, one kind of partial product after the other: consecutive instructions are
-// independent.
+// Six partial products for a block of A x B accumulators, one kind after the other, the large one last: consecutive
+// instructions are independent.
 template <int A, int B>
 __device__ __forceinline__ void mma32_block(const planes (&a)[A], const planes (&b)[B], f32x16 (&acc)[A][B])
 {
@@ -125,6 +113,19 @@ __device__ __forceinline__ bool any_not_finite(const f32x16 &acc)
 #pragma unroll
     for (int v = 0; v < 16; ++v) t = fmaf(acc[v], 0.f, t);
     return t != t;
+}
+
+// large += small, where large is finite.  The high plane holds an infinity or NaN as what it is and zero as zero, so a large sum
+// that is not finite is what fp32 multiply-adds give; the small one is then NaN for reasons of its own (a middle value next to an infinity
+// has either sign or is zero).
+__device__ __forceinline__ void add_small(f32x16 &large, const f32x16 &small)
+{
+    if (__any(any_not_finite(large))) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) large[v] = not_finite(large[v]) ? large[v] : large[v] + small[v];
+    } else {
+        large += small;
+    }
 }
 
 }  // namespace split_bf16

@@ -1,0 +1,128 @@
+"""Infinities and NaN in the kernels that split fp32 values into three bf16 values: element by element
+what plain sums give (the oracle), and in about the time that other values take."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2102_06280_amd import inputs
+from gpu_util import dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2102_06280_amd import binding
+    return binding
+
+
+def same_elements(got, want, slices, tol):
+    """NaN and infinities where the oracle has them, and nowhere else; the finite rest of every layer within tol of its
+    largest element and norm (or 1e-7: the deltas, up to 1 / batch and rounded to 2^-24 of that, can cancel in a bias gradient)."""
+    for lo, hi in slices:
+        g, w = got[lo:hi].astype(np.float64), want[lo:hi].astype(np.float64)
+        for what, f in (("NaN", np.isnan), ("+inf", np.isposinf), ("-inf", np.isneginf)):
+            assert np.array_equal(f(g), f(w)), f"[{lo}:{hi}] {what}: {f(g).sum()} here, {f(w).sum()} in the oracle"
+        ok = np.isfinite(w)
+        if ok.any():
+            diff, size = g[ok] - w[ok], np.abs(w[ok]).max()
+            assert np.abs(diff).max() <= max(tol * size, 1e-7), f"[{lo}:{hi}]"
+            assert np.linalg.norm(diff) <= max(tol * np.linalg.norm(w[ok]), 1e-7), f"[{lo}:{hi}]"
+
+
+def slices_of(desc):
+    off, out = 0, []
+    for _, nw, nb in inputs.layer_shapes(desc):
+        out += [(off, off + nw), (off + nw, off + nw + nb)]
+        off += nw + nb
+    return out
+
+
+def gradients(B, desc, dims, params, x, y):
+    n, batch = x.shape[:2]
+    d = inputs.param_count(desc)
+    rowptr, colidx = inputs.graph_complete(n)
+    h = B.dbw_create(rowptr, colidx, n, d, ld=params.shape[1], model=B.make_model(B.MODEL_MLP, batch, dims))
+    try:
+        grads, loss = torch.zeros(params.shape, device="cuda"), torch.zeros(n, device="cuda")
+        B.dbw_grad(h, dev(params), dev(x), dev(y), grads, loss)
+        return grads.cpu().numpy()[:, :d], loss.cpu().numpy()
+    finally:
+        B.dbw_destroy(h)
+
+
+@pytest.mark.parametrize("sign", [-1, 1])
+@pytest.mark.parametrize("dims,batch", [([65, 63, 70, 20], 66), ([129, 64, 33, 18], 65), ([7, 9, 21], 130)], ids=["65", "129", "7"])
+def test_mlp_element_by_element(B, orc, dims, batch, sign):
+    """An infinite input value of worker 1 under first-layer weights of one sign.  Negative: the layer is -inf, after ReLU zero,
+    and of the gradients only that input's column is lost (0 * inf).  Positive: the activations are infinite and the layer above gets
+    inf - inf, so with a third layer its weight gradient is lost as well (0 * inf), with two layers everything is."""
+    desc = {"kind": "mlp", "dims": dims, "loss": "xent"}
+    d = inputs.param_count(desc)
+    g = np.random.default_rng(21)
+    params = inputs.init_params(desc, 3, d, g)
+    x = g.standard_normal((3, batch, dims[0])).astype(np.float32)
+    y = g.integers(0, dims[-1], (3, batch)).astype(np.int32)
+    x[1, 4, 3] = np.inf
+    w = params[1, :dims[0] * dims[1]].reshape(dims[1], dims[0])
+    w[:, 3] = sign * (np.abs(w[:, 3]) + 0.01)
+    got, loss = gradients(B, desc, dims, params, x, y)
+    kind, od = orc.model_desc(desc)
+    want, wloss = orc.grad_all(kind, od, d, params, x, y)[:2]
+    np.testing.assert_allclose(loss, wloss, rtol=5e-6, atol=1e-6)
+    if sign < 0:
+        assert np.isnan(want[1, :d]).sum() == dims[1]
+    for i in range(3):
+        same_elements(got[i], want[i, :d], slices_of(desc), 2e-5)
+
+
+def _time(fn):
+    best = float("inf")
+    for _ in range(4):
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        fn()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b))
+    return best
+
+
+@pytest.mark.parametrize("model", ["dense average", "perceptron"])
+def test_time_with_values_that_are_not_finite(B, model):
+    """A worker that has diverged must not hold up the others: with NaN or infinities throughout one worker's parameters, or a
+    single one of either, a call takes at most three times as long as with finite values (lane-by-lane sums took up to 75
+    times as long)."""
+    n = 64 if model == "dense average" else 8
+    rowptr, colidx = inputs.graph_complete(n)
+    if model == "dense average":
+        d, desc, kw = 400_000, None, {"mix_path": B.MIX_DENSE}
+    else:
+        dims, batch = [256, 395, 295, 64, 28], 1024
+        desc = {"kind": "mlp", "dims": dims, "loss": "xent"}
+        d, kw = inputs.param_count(desc), {"model": B.make_model(B.MODEL_MLP, batch, dims)}
+    ld = inputs.pad_ld(d)
+    g = np.random.default_rng(31)
+    x = dev(inputs.init_params(desc, n, ld, g) if desc else g.standard_normal((n, ld)).astype(np.float32))
+    out = torch.zeros_like(x)
+    h = B.dbw_create(rowptr, colidx, n, d, ld=ld, **kw)
+    try:
+        if desc is None:
+            B.dbw_select(h, dev(g.standard_exponential(n).astype(np.float32)), dev(np.full(n, 5, np.int32)))
+            def call(): B.dbw_round(h, x, out, 0.0)
+        else:
+            bx = dev(g.standard_normal((n, batch, 256)).astype(np.float32))
+            by, loss = dev(g.integers(0, 10, (n, batch)).astype(np.int32)), torch.zeros(n, device="cuda")
+            def call(): B.dbw_grad(h, x, bx, by, out, loss)
+        finite, values = _time(call), x.clone()
+        for v in (float("nan"), float("inf")):
+            for whole in (True, False):
+                x.copy_(values)
+                if whole:
+                    x[1] = v
+                else:
+                    x[1, 100] = v
+                t = _time(call)
+                assert t <= 3 * finite, f"{v} {'throughout' if whole else 'once'}: {t:.3f} ms, finite {finite:.3f}"
+    finally:
+        B.dbw_destroy(h)
