@@ -22,6 +22,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "split_bf16.h"
 
 namespace convsplit {
@@ -125,42 +127,15 @@ struct FwdArgs {
     int64_t in_code_stride;
     const u32x4 *filters;       // prepare_kernel
     int64_t filters_stride;
-    const float *wgt;           // the filters themselves, [C2][C1][KK]: only for sums that are not finite
-    int64_t wgt_stride;
     const float *bias;          // or null
     int64_t bias_stride;
     float *out;                 // [worker][B][Cout][H][W]; POOL: [B][Cout][H/2][W/2] after ReLU and pooling, with code
     int64_t out_stride;
     uint8_t *code;
     int64_t code_stride;
+    const float *wgt;           // first_kernel: the filters themselves
+    int64_t wgt_stride;
 };
-
-// A value of the expanded input (see conv_lds.h, expand_pooled): the pooled gradient where the pixel was its
-// window's first maximum, else zero.
-__device__ __forceinline__ float expanded(const float *pooled, const uint8_t *code, int y, int x, int W)
-{
-    const int o = (y >> 1) * (W >> 1) + (x >> 1);
-    return code[o] == (uint8_t)(2 * (y & 1) + (x & 1)) ? pooled[o] : 0.f;
-}
-
-// One output value with plain multiply-adds (no bias).
-template <bool EXPAND>
-__device__ float plain_value(const FwdArgs &a, int w, int b, int co, int y, int x)
-{
-    const int KS = a.s.KS, KK = KS * KS, pad = KS / 2, HW = a.s.H * a.s.W;
-    const float *wg = a.wgt + w * a.wgt_stride;
-    float r = 0.f;
-    for (int c = 0; c < a.s.Cin; ++c)
-        for (int t = 0; t < KK; ++t) {
-            const int yy = y + t / KS - pad, xx = x + t % KS - pad;
-            if ((unsigned)yy >= (unsigned)a.s.H || (unsigned)xx >= (unsigned)a.s.W) continue;
-            const int64_t plane = (int64_t)b * a.s.Cin + c;
-            const float v = EXPAND ? expanded(a.in + w * a.in_stride + plane * (HW / 4), a.in_code + w * a.in_code_stride + plane * (HW / 4), yy, xx, a.s.W)
-                                   : a.in[w * a.in_stride + plane * HW + yy * a.s.W + xx];
-            r = fmaf(EXPAND ? wg[(c * a.s.Cout + co) * KK + KK - 1 - t] : wg[(co * a.s.Cin + c) * KK + t], v, r);
-        }
-    return r;
-}
 
 template <int CTRL>
 __device__ __forceinline__ float quad(float v)        // the value of lane CTRL / 0x55 of the quad
@@ -216,166 +191,166 @@ __global__ __launch_bounds__(THREADS, 2) void forward_kernel(FwdArgs a)
         pos[nb] = (smp[nb] < 0 ? 0 : smp[nb] * POS + (2 * wy + (lane >> 1 & 1)) * WP + 2 * wx + (lane & 1)) + (lane >> 5) * half;
     }
     f32x16 acc[MB][2];
+    auto zero = [&] {
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
+        for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-        for (int nb = 0; nb < 2; ++nb)
+            for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[mb][nb][v] = 0.f;
+                for (int v = 0; v < 16; ++v) acc[mb][nb][v] = 0.f;
+    };
+    zero();
 
-    for (int c = 0; c < chunks; ++c) {
-        if (c % cpg == 0) {                            // the next 16 channels of the image
-            __syncthreads();
-            const int pad = KS / 2, g = c / cpg;
-            if (EXPAND) {
-                // a window of eight channels: split once, then masked by the codes into its four positions
-                for (int e = tid; e < 2 * spg * T; e += THREADS) {
-                    const int hh = e / (spg * T), r = e % (spg * T), s = r / T, q = r % T, wy = q / (W / 2), wx = q % (W / 2);
-                    float v[8];
-                    int cd[8];
+    // the partial products of the whole reduction, all of them or those of one kind; chunk 0 is on its way
+    auto products = [&](auto small, auto large) {
+        for (int c = 0; c < chunks; ++c) {
+            if (c % cpg == 0) {                            // the next 16 channels of the image
+                __syncthreads();
+                const int pad = KS / 2, g = c / cpg;
+                if (EXPAND) {
+                    // a window of eight channels: split once, then masked by the codes into its four positions
+                    for (int e = tid; e < 2 * spg * T; e += THREADS) {
+                        const int hh = e / (spg * T), r = e % (spg * T), s = r / T, q = r % T, wy = q / (W / 2), wx = q % (W / 2);
+                        float v[8];
+                        int cd[8];
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) {
-                        const int ch = 16 * g + 8 * hh + j;
-                        const bool ok = s < nb_s && ch < a.s.Cin;
-                        const int64_t at = ok ? ((int64_t)(b0 + s) * a.s.Cin + ch) * T + q : 0;
-                        const float f = a.in[w * a.in_stride + at];
-                        const int code = a.in_code[w * a.in_code_stride + at];
-                        v[j] = ok ? f : 0.f;
-                        cd[j] = ok ? code : 4;
+                        for (int j = 0; j < 8; ++j) {
+                            const int ch = 16 * g + 8 * hh + j;
+                            const bool ok = s < nb_s && ch < a.s.Cin;
+                            const int64_t at = ok ? ((int64_t)(b0 + s) * a.s.Cin + ch) * T + q : 0;
+                            const float f = a.in[w * a.in_stride + at];
+                            const int code = a.in_code[w * a.in_code_stride + at];
+                            v[j] = ok ? f : 0.f;
+                            cd[j] = ok ? code : 4;
+                        }
+                        const planes p = split_bf16::split8(v);
+                        u32x4 *d = img + hh * half + s * POS + (2 * wy + pad) * WP + 2 * wx + pad;
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            u32x4 mask;
+#pragma unroll
+                            for (int j = 0; j < 4; ++j) mask[j] = (cd[2 * j] == k ? 0xffffu : 0u) | (cd[2 * j + 1] == k ? 0xffff0000u : 0u);
+                            u32x4 *dk = d + (k >> 1) * WP + (k & 1);
+                            dk[0] = p.h & mask;
+                            dk[plane] = p.m & mask;
+                            dk[2 * plane] = p.l & mask;
+                        }
                     }
-                    const planes p = split_bf16::split8(v);
-                    u32x4 *d = img + hh * half + s * POS + (2 * wy + pad) * WP + 2 * wx + pad;
+                } else {
+                    for (int e = tid; e < 2 * spg * HW; e += THREADS) {
+                        const int hh = e / (spg * HW), r = e % (spg * HW), s = r / HW, px = r % HW, y = px / W, x = px % W;
+                        float v[8];
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        u32x4 mask;
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) mask[j] = (cd[2 * j] == k ? 0xffffu : 0u) | (cd[2 * j + 1] == k ? 0xffff0000u : 0u);
-                        u32x4 *dk = d + (k >> 1) * WP + (k & 1);
-                        dk[0] = p.h & mask;
-                        dk[plane] = p.m & mask;
-                        dk[2 * plane] = p.l & mask;
+                        for (int j = 0; j < 8; ++j) {
+                            const int ch = 16 * g + 8 * hh + j;
+                            const bool ok = s < nb_s && ch < a.s.Cin;
+                            const float f = a.in[w * a.in_stride + (ok ? ((int64_t)(b0 + s) * a.s.Cin + ch) * HW + px : 0)];
+                            v[j] = ok ? f : 0.f;
+                        }
+                        const planes p = split_bf16::split8(v);
+                        u32x4 *d = img + hh * half + s * POS + (y + pad) * WP + x + pad;
+                        d[0] = p.h;
+                        d[plane] = p.m;
+                        d[2 * plane] = p.l;
                     }
                 }
-            } else {
-                for (int e = tid; e < 2 * spg * HW; e += THREADS) {
-                    const int hh = e / (spg * HW), r = e % (spg * HW), s = r / HW, px = r % HW, y = px / W, x = px % W;
-                    float v[8];
+            }
+            // chunk c has landed and everybody is done with chunk c - 1, whose place chunk c + 1 takes
+            __builtin_amdgcn_s_waitcnt(0);
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            if (c + 1 < chunks) fetch(c + 1);
+            const int t0 = c % cpg * TCH, nt = min(TCH, KK - t0);
+            const u32x4 *wc = wb + (c & 1) * TCH * MB * 192 + lane;
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) {
-                        const int ch = 16 * g + 8 * hh + j;
-                        const bool ok = s < nb_s && ch < a.s.Cin;
-                        const float f = a.in[w * a.in_stride + (ok ? ((int64_t)(b0 + s) * a.s.Cin + ch) * HW + px : 0)];
-                        v[j] = ok ? f : 0.f;
+            for (int t = 0; t < TCH; ++t) {
+                if (t < nt) {
+                    const int off = (t0 + t) / KS * WP + (t0 + t) % KS;
+                    planes fa[MB], fb[2];
+#pragma unroll
+                    for (int mb = 0; mb < MB; ++mb) {
+                        const u32x4 *p = wc + (t * MB + mb) * 192;
+                        fa[mb] = planes{p[0], p[64], p[128]};
                     }
-                    const planes p = split_bf16::split8(v);
-                    u32x4 *d = img + hh * half + s * POS + (y + pad) * WP + x + pad;
-                    d[0] = p.h;
-                    d[plane] = p.m;
-                    d[2 * plane] = p.l;
+#pragma unroll
+                    for (int nb = 0; nb < 2; ++nb) {
+                        const u32x4 *p = img + pos[nb] + off;
+                        fb[nb] = planes{p[0], p[plane], p[2 * plane]};
+                    }
+                    split_bf16::mma32_block<decltype(small)::value, decltype(large)::value>(fa, fb, acc);
                 }
             }
         }
-        // chunk c has landed and everybody is done with chunk c - 1, whose place chunk c + 1 takes
-        __builtin_amdgcn_s_waitcnt(0);
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        if (c + 1 < chunks) fetch(c + 1);
-        const int t0 = c % cpg * TCH, nt = min(TCH, KK - t0);
-        const u32x4 *wc = wb + (c & 1) * TCH * MB * 192 + lane;
-#pragma unroll
-        for (int t = 0; t < TCH; ++t) {
-            if (t < nt) {
-                const int off = (t0 + t) / KS * WP + (t0 + t) % KS;
-                planes fa[MB], fb[2];
-#pragma unroll
-                for (int mb = 0; mb < MB; ++mb) {
-                    const u32x4 *p = wc + (t * MB + mb) * 192;
-                    fa[mb] = planes{p[0], p[64], p[128]};
-                }
-#pragma unroll
-                for (int nb = 0; nb < 2; ++nb) {
-                    const u32x4 *p = img + pos[nb] + off;
-                    fb[nb] = planes{p[0], p[plane], p[2 * plane]};
-                }
-                split_bf16::mma32_block<MB, 2>(fa, fb, acc);
-            }
-        }
-    }
-
-    // ---- epilogue.  Register v of a lane: output channel 32 mb + 8 (v / 4) + 4 (lane / 32) + v % 4, the lane's pixel.
-    const int m0 = 32 * MB * blockIdx.z, PP = T;
-    float *ob = a.out + w * a.out_stride;
+    };
+    products(std::true_type{}, std::true_type{});
+    // ---- some sum of the workgroup is not finite: again, in the order that tells infinities from NaN (see split_bf16.h)
     bool bad = false;
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
         for (int nb = 0; nb < 2; ++nb) bad |= smp[nb] >= 0 && split_bf16::any_not_finite(acc[mb][nb]);
-    if (!__any(bad)) {
+    int *votes = (int *)(wb + (chunks & 1) * TCH * MB * 192);     // in the half of the filters that nobody reads any more
+    const int vote = __any(bad);
+    if (lane == 0) votes[wave] = vote;
+    __syncthreads();
+    if (votes[0] | votes[1] | votes[2] | votes[3]) {
+        __syncthreads();                               // the votes have been read
+        fetch(0);
+        zero();
+        products(std::true_type{}, std::false_type{});
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int c0 = m0 + 32 * mb + 8 * k + 4 * (lane >> 5);
-                float bv[4];
+            for (int nb = 0; nb < 2; ++nb) split_bf16::drop_not_finite(acc[mb][nb]);
+        __syncthreads();                               // the filters have been used
+        fetch(0);
+        products(std::false_type{}, std::true_type{});
+    }
+
+    // ---- epilogue.  Register v of a lane: output channel 32 mb + 8 (v / 4) + 4 (lane / 32) + v % 4, the lane's pixel.
+    const int m0 = 32 * MB * blockIdx.z, PP = T;
+    float *ob = a.out + w * a.out_stride;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) bv[i] = a.bias && c0 + i < a.s.Cout ? a.bias[w * a.bias_stride + c0 + i] : 0.f;
+    for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-                for (int nb = 0; nb < 2; ++nb) {
-                    const int64_t sample = (int64_t)(b0 + smp[nb]) * a.s.Cout;
-                    if (POOL) {
-                        // every lane of the quad holds the window's result for the four channels; it stores one of them
-                        float m = 0.f;
-                        int arg = 4;
+        for (int k = 0; k < 4; ++k) {
+            const int c0 = m0 + 32 * mb + 8 * k + 4 * (lane >> 5);
+            float bv[4];
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            const float v = acc[mb][nb][4 * k + i] + bv[i];
-                            const float v0 = quad<0x00>(v), v1 = quad<0x55>(v), v2 = quad<0xAA>(v), v3 = quad<0xFF>(v);
-                            const float mx = fmaxf(fmaxf(v0, v1), fmaxf(v2, v3));
-                            int ai = v2 == mx ? 2 : 3;
-                            ai = v1 == mx ? 1 : ai;
-                            ai = v0 == mx ? 0 : ai;
-                            ai = mx > 0.f ? ai : 4;
-                            m = (lane & 3) == i ? fmaxf(mx, 0.f) : m;
-                            arg = (lane & 3) == i ? ai : arg;
-                        }
-                        const int co = c0 + (lane & 3);
-                        if (smp[nb] >= 0 && co < a.s.Cout) {
-                            ob[(sample + co) * PP + win[nb]] = m;
-                            a.code[w * a.code_stride + (sample + co) * PP + win[nb]] = (uint8_t)arg;
-                        }
-                    } else if (smp[nb] >= 0) {
-                        const int y = 2 * (win[nb] / (W / 2)) + (lane >> 1 & 1), x = 2 * (win[nb] % (W / 2)) + (lane & 1);
+            for (int i = 0; i < 4; ++i) bv[i] = a.bias && c0 + i < a.s.Cout ? a.bias[w * a.bias_stride + c0 + i] : 0.f;
 #pragma unroll
-                        for (int i = 0; i < 4; ++i)
-                            if (c0 + i < a.s.Cout) ob[(sample + c0 + i) * HW + y * W + x] = acc[mb][nb][4 * k + i] + bv[i];
+            for (int nb = 0; nb < 2; ++nb) {
+                const int64_t sample = (int64_t)(b0 + smp[nb]) * a.s.Cout;
+                if (POOL) {
+                    // every lane of the quad holds the window's result for the four channels; it stores one of them
+                    float m = 0.f;
+                    int arg = 4;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const float v = acc[mb][nb][4 * k + i] + bv[i];
+                        const float v0 = quad<0x00>(v), v1 = quad<0x55>(v), v2 = quad<0xAA>(v), v3 = quad<0xFF>(v);
+                        const float mx = fmaxf(fmaxf(v0, v1), fmaxf(v2, v3));
+                        int ai = v2 == mx ? 2 : 3;
+                        ai = v1 == mx ? 1 : ai;
+                        ai = v0 == mx ? 0 : ai;
+                        ai = mx > 0.f ? ai : 4;
+                        m = (lane & 3) == i ? fmaxf(mx, 0.f) : m;
+                        arg = (lane & 3) == i ? ai : arg;
                     }
+                    const int co = c0 + (lane & 3);
+                    if (smp[nb] >= 0 && co < a.s.Cout) {
+                        ob[(sample + co) * PP + win[nb]] = m;
+                        a.code[w * a.code_stride + (sample + co) * PP + win[nb]] = (uint8_t)arg;
+                    }
+                } else if (smp[nb] >= 0) {
+                    const int y = 2 * (win[nb] / (W / 2)) + (lane >> 1 & 1), x = 2 * (win[nb] % (W / 2)) + (lane & 1);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (c0 + i < a.s.Cout) ob[(sample + c0 + i) * HW + y * W + x] = acc[mb][nb][4 * k + i] + bv[i];
                 }
             }
-        return;
-    }
-    // ---- some sum of the wave is not finite: all of its outputs again with plain multiply-adds (see split_bf16.h)
-#pragma unroll 1
-    for (int e = 0; e < 2 * 16 * MB; ++e) {
-        const int nb = e & 1, v = e >> 1 & 15, co = m0 + 32 * (e >> 5) + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-        const int s = nb ? smp[1] : smp[0], q = nb ? win[1] : win[0];
-        const int y = 2 * (q / (W / 2)) + (lane >> 1 & 1), x = 2 * (q % (W / 2)) + (lane & 1);
-        const bool ok = s >= 0 && co < a.s.Cout;
-        float r = 0.f;
-        if (ok) r = plain_value<EXPAND>(a, w, b0 + s, co, y, x) + (a.bias ? a.bias[w * a.bias_stride + co] : 0.f);
-        const int64_t at = ok ? (int64_t)(b0 + s) * a.s.Cout + co : 0;
-        if (POOL) {
-            const float v0 = quad<0x00>(r), v1 = quad<0x55>(r), v2 = quad<0xAA>(r), v3 = quad<0xFF>(r);
-            const float mx = fmaxf(fmaxf(v0, v1), fmaxf(v2, v3));
-            const int arg = !(mx > 0.f) ? 4 : (v0 == mx ? 0 : (v1 == mx ? 1 : (v2 == mx ? 2 : 3)));
-            if (ok && (lane & 3) == 0) {
-                ob[at * PP + q] = fmaxf(mx, 0.f);
-                a.code[w * a.code_stride + at * PP + q] = (uint8_t)arg;
-            }
-        } else if (ok) {
-            ob[at * HW + y * W + x] = r;
         }
-    }
 }
 
 // ---- forward pass, ReLU and pooling of a layer with few input channels (the network's first).
@@ -472,58 +447,80 @@ __global__ __launch_bounds__(THREADS, 2) void first_kernel(FwdArgs a, FirstPlan 
             const int m = q % M, yh = q / M % (H / 2), smp = q / M / (H / 2), dy = nn & 1;
             const u32x4 *base = img + smp * image + (2 * yh + dy) * IPG + m;
             f32x16 acc[8];
+            auto zero = [&] {
 #pragma unroll
-            for (int x = 0; x < 8; ++x)
+                for (int x = 0; x < 8; ++x)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) acc[x][v] = 0.f;
+                    for (int v = 0; v < 16; ++v) acc[x][v] = 0.f;
+            };
+            zero();
+            // the partial products of the whole reduction, all of them or those of one kind.  MASK: nothing but the filter's taps
+            // is multiplied (otherwise zero weights take up the rest of a step, which is the same for finite values)
+            auto products = [&](auto small, auto large, auto mask) {
+                constexpr bool SMALL = decltype(small)::value, LARGE = decltype(large)::value, MASK = decltype(mask)::value;
 #pragma unroll 1
-            for (int st = 0; st < steps; ++st) {
-                const int p0 = 2 * st, p1 = min(2 * st + 1, pairs - 1);                   // (beyond the last pair: zero weights)
-                const u32x4 *src = base + ((lane < 32 ? (p0 / KS) * HP + p0 % KS : (p1 / KS) * HP + p1 % KS)) * IPG;
-                const u32x4 *ws = wl + st * 64 + lane;
-                const u32x4 fh = ws[0], fm = ws[wplane], fl = ws[2 * wplane];
-                uint32_t d[8];
-                auto read = [&](int plane) {
-                    const u32x4 lo = src[plane * iplane], hi = src[plane * iplane + 1];
+                for (int st = 0; st < steps; ++st) {
+                    const int p0 = 2 * st, p1 = min(2 * st + 1, pairs - 1);               // (beyond the last pair: zero weights)
+                    const u32x4 *src = base + ((lane < 32 ? (p0 / KS) * HP + p0 % KS : (p1 / KS) * HP + p1 % KS)) * IPG;
+                    const bool exists = lane < 32 || 2 * st + 1 < pairs;
+                    const u32x4 *ws = wl + st * 64 + lane;
+                    const u32x4 fh = ws[0], fm = ws[wplane], fl = ws[2 * wplane];
+                    uint32_t d[8];
+                    auto read = [&](int plane) {
+                        const u32x4 lo = src[plane * iplane], hi = src[plane * iplane + 1];
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        d[i] = lo[i];
-                        d[4 + i] = hi[i];
+                        for (int i = 0; i < 4; ++i) {
+                            d[i] = lo[i];
+                            d[4 + i] = hi[i];
+                        }
+                    };
+                    auto shifted = [&](int x) {          // values x .. x + 7 of the sixteen
+                        u32x4 f;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            f[i] = x % 2 == 0 ? d[x / 2 + i] : __builtin_amdgcn_alignbit(d[x / 2 + i + 1], d[x / 2 + i], 16);
+                            if (MASK) f[i] = 2 * i < KS && exists ? (2 * i + 1 < KS ? f[i] : f[i] & 0xffffu) : 0u;
+                        }
+                        return split_bf16::frag(f);
+                    };
+                    auto mma = [&](const u32x4 &f, split_bf16::bf16x8 b, int x) {
+                        acc[x] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(split_bf16::frag(f), b, acc[x], 0, 0, 0);
+                    };
+                    if (SMALL) {
+                        read(2);
+#pragma unroll
+                        for (int x = 0; x < 8; ++x) mma(fh, shifted(x), x);
+                        read(1);
+#pragma unroll
+                        for (int x = 0; x < 8; ++x) {
+                            const auto b = shifted(x);
+                            mma(fm, b, x);
+                            mma(fh, b, x);
+                        }
                     }
-                };
-                auto shifted = [&](int x) {              // values x .. x + 7 of the sixteen
-                    u32x4 f;
+                    read(0);
 #pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        f[i] = x % 2 == 0 ? d[x / 2 + i] : __builtin_amdgcn_alignbit(d[x / 2 + i + 1], d[x / 2 + i], 16);
-                    return split_bf16::frag(f);
-                };
-                auto mma = [&](const u32x4 &f, split_bf16::bf16x8 b, int x) {
-                    acc[x] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(split_bf16::frag(f), b, acc[x], 0, 0, 0);
-                };
-                read(2);
-#pragma unroll
-                for (int x = 0; x < 8; ++x) mma(fh, shifted(x), x);
-                read(1);
-#pragma unroll
-                for (int x = 0; x < 8; ++x) {
-                    const auto b = shifted(x);
-                    mma(fm, b, x);
-                    mma(fh, b, x);
+                    for (int x = 0; x < 8; ++x) {
+                        const auto b = shifted(x);
+                        if (SMALL) {
+                            mma(fl, b, x);
+                            mma(fm, b, x);
+                        }
+                        if (LARGE) mma(fh, b, x);
+                    }
                 }
-                read(0);
-#pragma unroll
-                for (int x = 0; x < 8; ++x) {
-                    const auto b = shifted(x);
-                    mma(fl, b, x);
-                    mma(fm, b, x);
-                    mma(fh, b, x);
-                }
-            }
+            };
+            products(std::true_type{}, std::true_type{}, std::false_type{});
             bool bad = false;
 #pragma unroll
             for (int x = 0; x < 8; ++x) bad |= n < total && split_bf16::any_not_finite(acc[x]);
-            const bool plain = __any(bad);
+            if (__any(bad)) {      // again, in the order that tells infinities from NaN (see split_bf16.h)
+                zero();
+                products(std::true_type{}, std::false_type{}, std::true_type{});
+#pragma unroll
+                for (int x = 0; x < 8; ++x) split_bf16::drop_not_finite(acc[x]);
+                products(std::false_type{}, std::true_type{}, std::true_type{});
+            }
             // ---- the two lanes of a position pair hold the same four windows; each stores every other output channel
             const int64_t wbase = yh * (W / 2) + 4 * m;
             const int left = W / 2 - 4 * m;              // windows that exist
@@ -553,7 +550,7 @@ __global__ __launch_bounds__(THREADS, 2) void first_kernel(FwdArgs a, FirstPlan 
                     mx[j] = dy ? r[1] : r[0];
                     code |= (dy ? cd[1] : cd[0]) << (8 * j);
                 }
-                if (n < total && co < Cout && !plain) {
+                if (n < total && co < Cout) {
                     const int64_t at = ((int64_t)(b0 + smp) * Cout + co) * PP + wbase;
                     float *o = a.out + w * a.out_stride + at;
                     uint8_t *c = a.code + w * a.code_stride + at;
@@ -568,22 +565,6 @@ __global__ __launch_bounds__(THREADS, 2) void first_kernel(FwdArgs a, FirstPlan 
                             c[j] = (uint8_t)(code >> (8 * j));
                         }
                 }
-            }
-            if (!plain) continue;
-            // ---- some sum is not finite: all of the wave's windows with plain multiply-adds (see split_bf16.h)
-#pragma unroll 1
-            for (int e = 0; e < 32; ++e) {
-                const int v = 2 * (e / 4) + dy, j = e % 4, co = m0 + 8 * (v / 4) + 4 * (lane >> 5) + v % 4;
-                if (n >= total || co >= Cout || j >= left) continue;
-                float r[4], top = 0.f;
-#pragma unroll 1
-                for (int k = 0; k < 4; ++k) {
-                    r[k] = plain_value<false>(a, w, b0 + smp, co, 2 * yh + k / 2, 8 * m + 2 * j + k % 2) + a.bias[w * a.bias_stride + co];
-                    top = k ? fmaxf(top, r[k]) : r[k];
-                }
-                const int64_t at = ((int64_t)(b0 + smp) * Cout + co) * PP + wbase + j;
-                a.out[w * a.out_stride + at] = fmaxf(top, 0.f);
-                a.code[w * a.code_stride + at] = (uint8_t)(!(top > 0.f) ? 4 : (r[0] == top ? 0 : (r[1] == top ? 1 : (r[2] == top ? 2 : 3))));
             }
         }
     }
@@ -690,102 +671,135 @@ __global__ __launch_bounds__(64 * WGRAD_MAX_WAVES) void wgrad_kernel(WgradArgs a
     const int aoff = ((32 * mb + (lane & 31)) * DP + 8 * (lane >> 5)) / 8;
 
     f32x16 acc[KS];
+    auto zero = [&] {
 #pragma unroll
-    for (int k = 0; k < KS; ++k)
+        for (int k = 0; k < KS; ++k)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[k][v] = 0.f;
+            for (int v = 0; v < 16; ++v) acc[k][v] = 0.f;
+    };
+    zero();
 
-    for (int b = b0; b < b1; ++b)
-        for (int r0 = 0; r0 < H; r0 += a.p.rows) {
-            const int rows = min(a.p.rows, H - r0);
-            __syncthreads();                           // the previous tile has been used
-            if (r0 == 0) {
-                const int per = IP / 8;
-                for (int e = tid; e < Cin * H * per; e += threads) {
-                    const int m = e % per, y = e / per % H, c = e / per / H;
-                    const float *src = inw + (((int64_t)b * Cin + c) * H + y) * W;
-                    float v[8];
+    // the partial products of the whole reduction, all of them or those of one kind.  MASK: pixels that meet only the padding of the delta
+    // rows are left out (otherwise they meet zeros there, which is the same for finite values)
+    auto products = [&](auto small, auto large, auto mask) {
+        constexpr bool SMALL = decltype(small)::value, LARGE = decltype(large)::value, MASK = decltype(mask)::value;
+        for (int b = b0; b < b1; ++b)
+            for (int r0 = 0; r0 < H; r0 += a.p.rows) {
+                const int rows = min(a.p.rows, H - r0);
+                __syncthreads();                           // the previous tile has been used
+                if (r0 == 0) {
+                    const int per = IP / 8;
+                    for (int e = tid; e < Cin * H * per; e += threads) {
+                        const int m = e % per, y = e / per % H, c = e / per / H;
+                        const float *src = inw + (((int64_t)b * Cin + c) * H + y) * W;
+                        float v[8];
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) {
-                        const int x = 8 * m + j - pad;
-                        const float f = src[min(max(x, 0), W - 1)];
-                        v[j] = (unsigned)x < (unsigned)W ? f : 0.f;
+                        for (int j = 0; j < 8; ++j) {
+                            const int x = 8 * m + j - pad;
+                            const float f = src[min(max(x, 0), W - 1)];
+                            v[j] = (unsigned)x < (unsigned)W ? f : 0.f;
+                        }
+                        const planes p = split_bf16::split8(v);
+                        u32x4 *d = img + (c * HP + y + pad) * per + m;
+                        d[0] = p.h;
+                        d[iplane] = p.m;
+                        d[2 * iplane] = p.l;
                     }
-                    const planes p = split_bf16::split8(v);
-                    u32x4 *d = img + (c * HP + y + pad) * per + m;
-                    d[0] = p.h;
-                    d[iplane] = p.m;
-                    d[2 * iplane] = p.l;
+                }
+                const int per = RE / 8;
+                for (int e = tid; e < Cout * (rows / 2) * per; e += threads) {       // four windows: eight pixels of two rows
+                    const int m = e % per, yh = e / per % (rows / 2), co = e / per / (rows / 2);
+                    const int64_t o = ((int64_t)b * Cout + co) * (H * W / 4) + (r0 / 2 + yh) * (W >> 1);
+                    float g[8];                                  // (each window's value twice)
+                    int cd[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const int xw = 4 * m + j;
+                        const bool ok = xw < W / 2;
+                        g[2 * j] = g[2 * j + 1] = dpw[o + (ok ? xw : 0)];
+                        const int code = cdw[o + (ok ? xw : 0)];
+                        cd[j] = ok ? code : 4;
+                    }
+                    const planes p = split_bf16::split8(g);      // both halves of a word: the window's value
+                    u32x4 *d = dz + (co * DP + 2 * yh * RE) / 8 + m;
+#pragma unroll
+                    for (int r = 0; r < 2; ++r) {
+                        u32x4 mask;
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) mask[j] = cd[j] == 2 * r ? 0xffffu : (cd[j] == 2 * r + 1 ? 0xffff0000u : 0u);
+                        u32x4 *dr = d + r * (RE / 8);
+                        dr[0] = p.h & mask;
+                        dr[dplane] = p.m & mask;
+                        dr[2 * dplane] = p.l & mask;
+                    }
+                }
+                __syncthreads();
+                if (idle) continue;
+                const int steps = rows * segs;
+                for (int st = kwave; st < steps; st += a.p.kw) {
+                    const int yr = st / segs, x8 = 2 * (st % segs);
+                    const u32x4 *ap = dz + aoff + yr * (RE / 8) + x8;
+                    const u32x4 *bp = img + boff + (r0 + yr) * (IP / 8) + x8;
+                    planes fa;
+                    fa.h = ap[0];
+                    fa.m = ap[dplane];
+                    fa.l = ap[2 * dplane];
+                    // fragment kw of one plane of the image: elements kw .. kw + 7 of the twelve read
+                    u32x4 fb[KS];
+                    auto read = [&](int plane) {
+                        const u32x4 q = bp[plane * iplane];
+                        const u32x2 r = *(const u32x2 *)&bp[plane * iplane + 1];
+                        const uint32_t d[6] = {q[0], q[1], q[2], q[3], r[0], r[1]};
+#pragma unroll
+                        for (int k = 0; k < KS; ++k)
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) {
+                                fb[k][i] = k % 2 == 0 ? d[k / 2 + i] : __builtin_amdgcn_alignbit(d[k / 2 + i + 1], d[k / 2 + i], 16);
+                                if (MASK) fb[k][i] = 8 * x8 + 8 * (lane >> 5) + 2 * i < W ? fb[k][i] : 0u;
+                            }
+                    };
+                    auto step = [&](const u32x4 &x) {
+#pragma unroll
+                        for (int k = 0; k < KS; ++k)
+                            acc[k] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(split_bf16::frag(x), split_bf16::frag(fb[k]), acc[k], 0, 0, 0);
+                    };
+                    if (SMALL) {
+                        read(2);
+                        step(fa.h);
+                        read(1);
+                        step(fa.m);
+                        step(fa.h);
+                    }
+                    read(0);
+                    if (SMALL) {
+                        step(fa.l);
+                        step(fa.m);
+                    }
+                    if (LARGE) step(fa.h);
                 }
             }
-            const int per = RE / 8;
-            for (int e = tid; e < Cout * (rows / 2) * per; e += threads) {       // four windows: eight pixels of two rows
-                const int m = e % per, yh = e / per % (rows / 2), co = e / per / (rows / 2);
-                const int64_t o = ((int64_t)b * Cout + co) * (H * W / 4) + (r0 / 2 + yh) * (W >> 1);
-                float g[4];
-                int cd[4];
+    };
+    products(std::true_type{}, std::true_type{}, std::false_type{});
+    // ---- some sum of the workgroup is not finite: again, in the order that tells infinities from NaN (see split_bf16.h)
+    bool bad = false;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int xw = 4 * m + j;
-                    const bool ok = xw < W / 2;
-                    g[j] = dpw[o + (ok ? xw : 0)];
-                    const int code = cdw[o + (ok ? xw : 0)];
-                    cd[j] = ok ? code : 4;
-                }
-                uint32_t h[4], mid[4], l[4];                 // both halves of a word: the window's value
+    for (int k = 0; k < KS; ++k) bad |= n < Cin * KS && split_bf16::any_not_finite(acc[k]);
+    int *votes = (int *)sm;                            // in the upper halo of the first channel, which holds more than 12 zeros
+    const int vote = __any(bad);
+    __syncthreads();                                   // the tiles have been used
+    if (lane == 0) votes[wave] = vote;
+    __syncthreads();
+    int again = 0;
+    for (int q = 0; q < a.p.waves; ++q) again |= votes[q];
+    if (again) {
+        __syncthreads();                               // the votes have been read
+        if (tid < a.p.waves) votes[tid] = 0;
+        zero();
+        products(std::true_type{}, std::false_type{}, std::true_type{});
 #pragma unroll
-                for (int j = 0; j < 4; ++j) split_bf16::split2(g[j], g[j], h[j], mid[j], l[j]);
-                u32x4 *d = dz + (co * DP + 2 * yh * RE) / 8 + m;
-#pragma unroll
-                for (int r = 0; r < 2; ++r) {
-                    u32x4 mask;
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) mask[j] = cd[j] == 2 * r ? 0xffffu : (cd[j] == 2 * r + 1 ? 0xffff0000u : 0u);
-                    u32x4 *dr = d + r * (RE / 8);
-                    dr[0] = u32x4{h[0], h[1], h[2], h[3]} & mask;
-                    dr[dplane] = u32x4{mid[0], mid[1], mid[2], mid[3]} & mask;
-                    dr[2 * dplane] = u32x4{l[0], l[1], l[2], l[3]} & mask;
-                }
-            }
-            __syncthreads();
-            if (idle) continue;
-            const int steps = rows * segs;
-            for (int st = kwave; st < steps; st += a.p.kw) {
-                const int yr = st / segs, x8 = 2 * (st % segs);
-                const u32x4 *ap = dz + aoff + yr * (RE / 8) + x8;
-                const u32x4 *bp = img + boff + (r0 + yr) * (IP / 8) + x8;
-                planes fa;
-                fa.h = ap[0];
-                fa.m = ap[dplane];
-                fa.l = ap[2 * dplane];
-                // fragment kw of one plane of the image: elements kw .. kw + 7 of the twelve read
-                u32x4 fb[KS];
-                auto read = [&](int plane) {
-                    const u32x4 q = bp[plane * iplane];
-                    const u32x2 r = *(const u32x2 *)&bp[plane * iplane + 1];
-                    const uint32_t d[6] = {q[0], q[1], q[2], q[3], r[0], r[1]};
-#pragma unroll
-                    for (int k = 0; k < KS; ++k)
-#pragma unroll
-                        for (int i = 0; i < 4; ++i)
-                            fb[k][i] = k % 2 == 0 ? d[k / 2 + i] : __builtin_amdgcn_alignbit(d[k / 2 + i + 1], d[k / 2 + i], 16);
-                };
-                auto step = [&](const u32x4 &x) {
-#pragma unroll
-                    for (int k = 0; k < KS; ++k)
-                        acc[k] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(split_bf16::frag(x), split_bf16::frag(fb[k]), acc[k], 0, 0, 0);
-                };
-                read(2);
-                step(fa.h);
-                read(1);
-                step(fa.m);
-                step(fa.h);
-                read(0);
-                step(fa.l);
-                step(fa.m);
-                step(fa.h);
-            }
-        }
+        for (int k = 0; k < KS; ++k) split_bf16::drop_not_finite(acc[k]);
+        products(std::false_type{}, std::true_type{}, std::true_type{});
+    }
     // ---- the waves that share a block: their sums through LDS, added to the first one's in wave order
     float *sums = (float *)sm + (wave % upg) * 1024 * KS + lane;
     for (int q = 1; q < a.p.kw; ++q) {
@@ -805,9 +819,6 @@ __global__ __launch_bounds__(64 * WGRAD_MAX_WAVES) void wgrad_kernel(WgradArgs a
     if (idle || kwave != 0) return;
 
     float *pb = a.part + w * a.part_stride + (int64_t)blockIdx.x * Cout * TAPS;
-    bool bad = false;
-#pragma unroll
-    for (int k = 0; k < KS; ++k) bad |= split_bf16::any_not_finite(acc[k]);
     if (n < Cin * KS) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
@@ -817,23 +828,6 @@ __global__ __launch_bounds__(64 * WGRAD_MAX_WAVES) void wgrad_kernel(WgradArgs a
                 for (int k = 0; k < KS; ++k) pb[(int64_t)co * TAPS + n * KS + k] = acc[k][v];
             }
         }
-    }
-    // ---- sums that are not finite once more, with plain multiply-adds over the same samples (see split_bf16.h)
-    if (!__any(bad) || n >= Cin * KS) return;
-#pragma unroll 1
-    for (int e = 0; e < 16 * KS; ++e) {
-        const int v = e / KS, k = e % KS, co = 32 * mb + 8 * (v / 4) + 4 * (lane >> 5) + v % 4, c = n / KS, kh = n % KS;
-        if (co >= Cout || !split_bf16::not_finite(pb[(int64_t)co * TAPS + n * KS + k])) continue;
-        float r = 0.f;
-        for (int b = b0; b < b1; ++b)
-            for (int y = 0; y < H; ++y)
-                for (int x = 0; x < W; ++x) {
-                    const int yy = y + kh - pad, xx = x + k - pad;
-                    if ((unsigned)yy >= (unsigned)H || (unsigned)xx >= (unsigned)W) continue;
-                    const int64_t o = ((int64_t)b * Cout + co) * (H * W / 4);
-                    r = fmaf(expanded(dpw + o, cdw + o, y, x, W), inw[(((int64_t)b * Cin + c) * H + yy) * W + xx], r);
-                }
-        pb[(int64_t)co * TAPS + n * KS + k] = r;
     }
 }
 

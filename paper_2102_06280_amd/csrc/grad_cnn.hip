@@ -492,8 +492,6 @@ int launch_grad_cnn(dbw_ctx *c, const float *params, const float *bx, const int3
     }
     const convsplit::Shape c2{L.C1, L.C2, L.H2, L.W2, L.KS, B}, c2back{L.C2, L.C1, L.H2, L.W2, L.KS, B};
     convsplit::FwdArgs f{};
-    f.wgt = params + L.w2;
-    f.wgt_stride = ld;
     if (L.split2) {
         {
             dbw_timer tm(c, "conv2_prepare", s);

@@ -83,9 +83,9 @@ __device__ __forceinline__ void mma32(const planes &a, const planes &b, f32x16 &
     small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(a.h), frag(b.m), small, 0, 0, 0);
 }
 
-// Six partial products for a block of A x B accumulators, one kind after the other, the large one last: consecutive
-// instructions are independent.
-template <int A, int B>
+// Six partial products (or the five small ones, or the large one) for a block of A x B accumulators, one kind after the other,
+// the large one last: consecutive instructions are independent.
+template <bool SMALL, bool LARGE, int A, int B>
 __device__ __forceinline__ void mma32_block(const planes (&a)[A], const planes (&b)[B], f32x16 (&acc)[A][B])
 {
     auto step = [&](u32x4 planes::*pa, u32x4 planes::*pb) {
@@ -95,12 +95,14 @@ __device__ __forceinline__ void mma32_block(const planes (&a)[A], const planes (
             for (int j = 0; j < B; ++j)
                 acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(a[i].*pa), frag(b[j].*pb), acc[i][j], 0, 0, 0);
     };
-    step(&planes::l, &planes::h);
-    step(&planes::h, &planes::l);
-    step(&planes::m, &planes::m);
-    step(&planes::m, &planes::h);
-    step(&planes::h, &planes::m);
-    step(&planes::h, &planes::h);
+    if (SMALL) {
+        step(&planes::l, &planes::h);
+        step(&planes::h, &planes::l);
+        step(&planes::m, &planes::m);
+        step(&planes::m, &planes::h);
+        step(&planes::h, &planes::m);
+    }
+    if (LARGE) step(&planes::h, &planes::h);
 }
 
 // NaN or infinity
@@ -128,4 +130,13 @@ __device__ __forceinline__ void add_small(f32x16 &large, const f32x16 &small)
     }
 }
 
+// The same where one accumulator is all there is room for: the small partial products of the whole reduction first, then this, then the
+// large ones on top.
+__device__ __forceinline__ void drop_not_finite(f32x16 &small)
+{
+#pragma unroll
+    for (int v = 0; v < 16; ++v) small[v] = not_finite(small[v]) ? 0.f : small[v];
+}
+
 }  // namespace split_bf16
+

@@ -42,13 +42,85 @@ def gradients(B, desc, dims, params, x, y):
     n, batch = x.shape[:2]
     d = inputs.param_count(desc)
     rowptr, colidx = inputs.graph_complete(n)
-    h = B.dbw_create(rowptr, colidx, n, d, ld=params.shape[1], model=B.make_model(B.MODEL_MLP, batch, dims))
+    kind = B.MODEL_CNN if desc["kind"] == "cnn" else B.MODEL_MLP
+    h = B.dbw_create(rowptr, colidx, n, d, ld=params.shape[1], model=B.make_model(kind, batch, dims))
     try:
         grads, loss = torch.zeros(params.shape, device="cuda"), torch.zeros(n, device="cuda")
         B.dbw_grad(h, dev(params), dev(x), dev(y), grads, loss)
         return grads.cpu().numpy()[:, :d], loss.cpu().numpy()
     finally:
         B.dbw_destroy(h)
+
+
+# One filter row and two with a partial last step, widths on and off 16 and 8, 3 x 3 and 5 x 5, one and several blocks of
+# output channels, one and several samples per workgroup, shared blocks of the weight gradient and not.
+CNN = [(1, 28, 28, 6, 16, 5, 20, 10), (3, 12, 20, 9, 40, 5, 12, 5), (2, 16, 16, 17, 33, 3, 12, 4), (1, 8, 8, 4, 70, 3, 8, 3)]
+CNN_WHERE = ["pixels", "conv1 +inf", "conv2 +inf", "conv2 -inf", "conv2 nan"]
+
+
+@pytest.mark.parametrize("where", CNN_WHERE)
+@pytest.mark.parametrize("shape", CNN, ids=["-".join(map(str, s)) for s in CNN])
+def test_cnn_element_by_element(B, orc, shape, where):
+    """Worker 1 of two, batch 3.  pixels: an infinite pixel inside one sample and one in the corner of another, under negative
+    filters, so that the pooled maps and the loss stay finite and only those weight gradients of conv1 are lost that the
+    pixels enter (0 * inf), not those of filter positions that would need an output outside the image.  conv1 / conv2: one infinite or NaN weight at a filter's centre, which no output reaches
+    over the border with; conv1's under positive pixels, so that the channel is infinite throughout, and below filters
+    of both signs, so that all of conv2 is inf - inf.  Tolerance as for finite gradients (3e-5 per layer)."""
+    C0, H, W, C1, C2, K, F, NC = shape
+    desc = {"kind": "cnn", "in": (C0, H, W), "c1": C1, "c2": C2, "k": K, "fc": F, "classes": NC}
+    d, KK = inputs.param_count(desc), K * K
+    g = np.random.default_rng(11)
+    params = inputs.init_params(desc, 2, d + 3, g)
+    x = g.standard_normal((2, 3, C0, H, W)).astype(np.float32)
+    y = g.integers(0, NC, (2, 3)).astype(np.int32)
+    c, centre = C0 - 1, KK // 2
+    w1 = params[1, :C1 * C0 * KK].reshape(C1, C0, KK)
+    b1 = params[:, C1 * C0 * KK:C1 * C0 * KK + C1]
+    w2 = params[1, C1 * C0 * KK + C1:][:C2 * C1 * KK].reshape(C2, C1, KK)
+    if where == "pixels":
+        w1[:, c] = -np.abs(w1[:, c]) - 0.01
+        x[1, 0, c, H // 2, W // 2] = np.inf
+        x[1, 2, c, 0, W - 1] = np.inf
+    elif where == "conv1 +inf":
+        x[1, :, c] = np.abs(x[1, :, c]) + 0.1
+        w1[C1 - 1, c, centre] = np.inf
+        w2[:, C1 - 1] = np.abs(w2[:, C1 - 1]) * (-1.0) ** np.arange(KK)
+    else:
+        b1[:] = 10.0                                    # every pooled value of the first layer is positive
+        w2[C2 - 1, C1 - 1, centre] = float(where.split()[1])
+    x = x.reshape(2, 3, -1)
+    got, loss = gradients(B, desc, shape, params, x, y)
+    kind, od = orc.model_desc(desc)
+    want, wloss = orc.grad_all(kind, od, d, params, x, y)[:2]
+    if where == "pixels":
+        lost = np.isnan(want[1, :C1 * C0 * KK].reshape(C1, C0, KK))
+        assert lost[:, c].all() and not lost[:, :c].any() and np.isfinite(want[1, C1 * C0 * KK:d]).all()
+    np.testing.assert_allclose(loss, wloss, rtol=5e-6, atol=1e-6)
+    for i in range(2):
+        same_elements(got[i], want[i, :d], slices_of(desc), 3e-5)
+
+
+def test_corner_pixel_reaches_its_own_taps_only(B, orc):
+    """An infinite pixel in the upper right corner, alone: the weight gradients of the filter positions that no output inside the
+    image pairs with it stay finite and right, on a width that is padded to a multiple of 16 in the kernel."""
+    shape = (1, 12, 20, 9, 8, 5, 12, 5)
+    desc = {"kind": "cnn", "in": shape[:3], "c1": 9, "c2": 8, "k": 5, "fc": 12, "classes": 5}
+    d = inputs.param_count(desc)
+    g = np.random.default_rng(12)
+    params = inputs.init_params(desc, 2, d, g)
+    params[:, :9 * 25] = -np.abs(params[:, :9 * 25]) - 0.01
+    params[:, 9 * 25:9 * 25 + 9] = 0.5
+    x = g.standard_normal((2, 3, 12, 20)).astype(np.float32)
+    x[1, 1, 0, 19] = np.inf
+    x = x.reshape(2, 3, -1)
+    y = g.integers(0, 5, (2, 3)).astype(np.int32)
+    got, _ = gradients(B, desc, shape, params, x, y)
+    kind, od = orc.model_desc(desc)
+    want = orc.grad_all(kind, od, d, params, x, y)[0]
+    lost = np.isnan(want[1, :9 * 25].reshape(9, 5, 5))
+    assert lost[:, :3, 2:].all() and lost.sum() == 9 * 9
+    for i in range(2):
+        same_elements(got[i], want[i, :d], slices_of(desc), 3e-5)
 
 
 @pytest.mark.parametrize("sign", [-1, 1])
@@ -88,19 +160,23 @@ def _time(fn):
     return best
 
 
-@pytest.mark.parametrize("model", ["dense average", "perceptron"])
+@pytest.mark.parametrize("model", ["dense average", "perceptron", "convolutions"])
 def test_time_with_values_that_are_not_finite(B, model):
     """A worker that has diverged must not hold up the others: with NaN or infinities throughout one worker's parameters, or a
-    single one of either, a call takes at most three times as long as with finite values (lane-by-lane sums took up to 75
-    times as long)."""
+    single one of either, a call takes at most three times as long as with finite values (a kernel that goes through its
+    products a second and a third time; lane-by-lane sums took 13 to 75 times as long)."""
     n = 64 if model == "dense average" else 8
     rowptr, colidx = inputs.graph_complete(n)
     if model == "dense average":
         d, desc, kw = 400_000, None, {"mix_path": B.MIX_DENSE}
     else:
-        dims, batch = [256, 395, 295, 64, 28], 1024
-        desc = {"kind": "mlp", "dims": dims, "loss": "xent"}
-        d, kw = inputs.param_count(desc), {"model": B.make_model(B.MODEL_MLP, batch, dims)}
+        if model == "perceptron":
+            dims, batch = [256, 395, 295, 64, 28], 1024
+            desc, kind = {"kind": "mlp", "dims": dims, "loss": "xent"}, B.MODEL_MLP
+        else:
+            dims, batch = [3, 32, 32, 32, 64, 5, 64, 10], 32
+            desc, kind = {"kind": "cnn", "in": (3, 32, 32), "c1": 32, "c2": 64, "k": 5, "fc": 64, "classes": 10}, B.MODEL_CNN
+        d, kw = inputs.param_count(desc), {"model": B.make_model(kind, batch, dims)}
     ld = inputs.pad_ld(d)
     g = np.random.default_rng(31)
     x = dev(inputs.init_params(desc, n, ld, g) if desc else g.standard_normal((n, ld)).astype(np.float32))
@@ -111,7 +187,7 @@ def test_time_with_values_that_are_not_finite(B, model):
             B.dbw_select(h, dev(g.standard_exponential(n).astype(np.float32)), dev(np.full(n, 5, np.int32)))
             def call(): B.dbw_round(h, x, out, 0.0)
         else:
-            bx = dev(g.standard_normal((n, batch, 256)).astype(np.float32))
+            bx = dev(g.standard_normal((n, batch, 256 if model == "perceptron" else 3 * 32 * 32)).astype(np.float32))
             by, loss = dev(g.integers(0, 10, (n, batch)).astype(np.int32)), torch.zeros(n, device="cuda")
             def call(): B.dbw_grad(h, x, bx, by, out, loss)
         finite, values = _time(call), x.clone()
