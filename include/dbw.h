@@ -25,6 +25,11 @@
  * Inside a row the model parameters are stored layer by layer, weight [out][in]
  * (convolutions [Cout][Cin][kh][kw]) followed by the bias [out].
  *
+ * Precision.  Parameters, gradients and sums are fp32 throughout; sums come as close to the exact ones as those of fp32
+ * multiply-adds (a convolution's sum that zeros leave a single term of: within 2^-23 of it).  Values of magnitude below
+ * 2^-110 (8e-34) enter the dense average, the convolutions and the gradients of the fully connected layers to within 2^-133 each.  The zero border of a convolution is part of its sums (0 times an
+ * infinite or NaN weight is NaN).
+ *
  * Graph.  The communication graph G = (N, E) of Section 2.1 is given in CSR form
  * without self loops: the neighbours of worker i are colidx[rowptr[i] .. rowptr[i+1]),
  * strictly ascending; the graph must be symmetric and connected.  deg_i is the row

@@ -364,7 +364,7 @@ __device__ __forceinline__ void split_tile(const Dense<KCA> &A, const Dense<KCB>
         }
         __builtin_amdgcn_sched_barrier(0);     // nothing that consumes them moves up here
 #pragma unroll
-        for (int s = 0; s < BK / 16; ++s) split_bf16::mma32(TA::frag(As, wm, s, lane), TB::frag(Bs, wn, s, lane), acc, small);
+        for (int s = 0; s < BK / 16; ++s) split_bf16::mma32<true>(TA::frag(As, wm, s, lane), TB::frag(Bs, wn, s, lane), acc, small);
     }
     split_bf16::add_small(acc, small);
     const int n = n0 + wn + (lane & 31);

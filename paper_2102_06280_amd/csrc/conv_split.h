@@ -100,7 +100,7 @@ __device__ __forceinline__ void prepare(float *tile /* LDS [16 channels][32 rows
         float v[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) v[j] = tile[((8 * (lane / 32) + j) * 32 + lane % 32) * KK + (FLIP ? KK - 1 - tap : tap)];
-        const planes p = split_bf16::split8(v);
+        const planes p = split_bf16::split8_nearest(v);
         u32x4 *at = d + ((int64_t)(g * KK + tap) * mbt + mb) * 192 + lane;
         at[0] = p.h;
         at[64] = p.m;
@@ -223,7 +223,7 @@ __global__ __launch_bounds__(THREADS, 2) void forward_kernel(FwdArgs a)
                             v[j] = ok ? f : 0.f;
                             cd[j] = ok ? code : 4;
                         }
-                        const planes p = split_bf16::split8(v);
+                        const planes p = split_bf16::split8_nearest(v);
                         u32x4 *d = img + hh * half + s * POS + (2 * wy + pad) * WP + 2 * wx + pad;
 #pragma unroll
                         for (int k = 0; k < 4; ++k) {
@@ -247,7 +247,7 @@ __global__ __launch_bounds__(THREADS, 2) void forward_kernel(FwdArgs a)
                             const float f = a.in[w * a.in_stride + (ok ? ((int64_t)(b0 + s) * a.s.Cin + ch) * HW + px : 0)];
                             v[j] = ok ? f : 0.f;
                         }
-                        const planes p = split_bf16::split8(v);
+                        const planes p = split_bf16::split8_nearest(v);
                         u32x4 *d = img + hh * half + s * POS + (y + pad) * WP + x + pad;
                         d[0] = p.h;
                         d[plane] = p.m;
@@ -412,7 +412,7 @@ __global__ __launch_bounds__(THREADS, 2) void first_kernel(FwdArgs a, FirstPlan 
             const float f = wg[ok ? (co * pairs + pair) * KS + j : 0];
             v[j] = ok ? f : 0.f;
         }
-        const planes p = split_bf16::split8(v);
+        const planes p = split_bf16::split8_nearest(v);
         wl[e] = p.h;
         wl[e + wplane] = p.m;
         wl[e + 2 * wplane] = p.l;
@@ -433,7 +433,7 @@ __global__ __launch_bounds__(THREADS, 2) void first_kernel(FwdArgs a, FirstPlan 
                 const float f = src[min(max(x, 0), W - 1)];
                 v[j] = (unsigned)x < (unsigned)W ? f : 0.f;
             }
-            const planes p = split_bf16::split8(v);
+            const planes p = split_bf16::split8_nearest(v);
             u32x4 *d = img + (sc * HP + y + pad) * IPG + g;
             d[0] = p.h;
             d[iplane] = p.m;
@@ -699,7 +699,7 @@ __global__ __launch_bounds__(64 * WGRAD_MAX_WAVES) void wgrad_kernel(WgradArgs a
                             const float f = src[min(max(x, 0), W - 1)];
                             v[j] = (unsigned)x < (unsigned)W ? f : 0.f;
                         }
-                        const planes p = split_bf16::split8(v);
+                        const planes p = split_bf16::split8_nearest(v);
                         u32x4 *d = img + (c * HP + y + pad) * per + m;
                         d[0] = p.h;
                         d[iplane] = p.m;
@@ -720,7 +720,7 @@ __global__ __launch_bounds__(64 * WGRAD_MAX_WAVES) void wgrad_kernel(WgradArgs a
                         const int code = cdw[o + (ok ? xw : 0)];
                         cd[j] = ok ? code : 4;
                     }
-                    const planes p = split_bf16::split8(g);      // both halves of a word: the window's value
+                    const planes p = split_bf16::split8_nearest(g);      // both halves of a word: the window's value
                     u32x4 *d = dz + (co * DP + 2 * yh * RE) / 8 + m;
 #pragma unroll
                     for (int r = 0; r < 2; ++r) {

@@ -1,12 +1,12 @@
 // X' = P X for more than 32 workers, or rows off 16-byte boundaries, fused with the local SGD step (see mix_dense.hip).
 //
-// Every fp32 value is split into three bf16 values for the multiplies (split_bf16.h): no bit of an operand is
-// dropped and the sums are fp32.  P (N x N, zero-padded to NPAD = 32 * MB) is tiny and lives in registers: a
-// wavefront keeps the three planes of its 32 rows for the whole kernel (192 of the 256 registers it can have, for
-// N = 256).  The workgroup walks over column tiles of X.  A tile goes from global memory straight into LDS as it
-// is (raw); each wavefront then splits the 1024 elements it fetched itself, eight rows of a column per lane and
-// step, into the planes' fragment order [8 rows][column][8 values], where a lane's 16 bytes are its fragment of one
-// matrix instruction: every LDS access is a run of consecutive 16-byte (raw: 4-byte) pieces.  The planes are double
+// Every fp32 value is split into three bf16 values for the multiplies and the sums are fp32 (split_bf16.h has the errors).
+// P (N x N, zero-padded to NPAD = 32 * MB) is tiny and lives in registers: a wavefront keeps the three planes of its 32
+// rows for the whole kernel (192 of the 256 registers it can have, for N = 256).  The workgroup walks over column tiles
+// of X.  A tile goes from global memory straight into LDS as it is (raw); each wavefront then splits the 1024 elements it
+// fetched itself, eight rows of a column per lane and step, into the planes' fragment order [8 rows][column][8 values],
+// where a lane's 16 bytes are its fragment of one matrix instruction: every LDS access is a run of consecutive 16-byte
+// (raw: 4-byte) pieces.  The planes are double
 // buffered, so that one of the two wavefronts of a SIMD splits and stores while the other multiplies, with one
 // barrier per tile.  Gradients go through LDS too, by the same kind of load, because no registers are left to keep them in
 // while the wave multiplies (requested into registers instead, they pushed P out to scratch memory: 0.95 ms).
@@ -180,7 +180,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void kernel(
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int s = 0; s < STEP; ++s) P[s4 + s] = split_bf16::split8(v[s]);
+        for (int s = 0; s < STEP; ++s) P[s4 + s] = split_bf16::split8_nearest(v[s]);
         __builtin_amdgcn_sched_barrier(0);
     }
     wait_memory<0>();
@@ -208,7 +208,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void kernel(
             b.h = b0[2 * s * C::TC];
             b.m = b0[2 * s * C::TC + C::GROUPS];
             b.l = b0[2 * s * C::TC + 2 * C::GROUPS];
-            split_bf16::mma32(P[s], b, acc, small);
+            split_bf16::mma32<false>(P[s], b, acc, small);
             __builtin_amdgcn_sched_barrier(0);
         }
         split_bf16::add_small(acc, small);

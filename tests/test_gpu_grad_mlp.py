@@ -470,3 +470,24 @@ def test_dense_products_on_unpadded_rows(B, orc, dims, batch, n):
     others = np.array([i for i in range(n) if i != 1])
     assert np.array_equal(grads_bad.cpu().numpy()[others], got[others]) and np.array_equal(loss_bad.cpu().numpy()[others], gl[others])
     assert not np.isfinite(grads_bad.cpu().numpy()[1]).all()
+
+
+def test_weight_gradient_of_one_sample_is_rounded_once(B):
+    """A batch of one on odd widths: every weight gradient is the product of the unit's bias gradient and the input value, rounded once
+    (2^-24 of it, and the 2^-32 that the three bf16 values of either factor leave out)."""
+    dims, n = [617, 301, 75, 26], 3
+    desc = {"kind": "mlp", "dims": dims, "loss": "xent"}
+    d = inputs.param_count(desc)
+    rowptr, colidx = inputs.graph_complete(n)
+    g = np.random.default_rng(3)
+    params, x = inputs.init_params(desc, n, d, g), g.standard_normal((n, 1, 617)).astype(np.float32)
+    h = B.dbw_create(rowptr, colidx, n, d, ld=d, model=B.make_model(B.MODEL_MLP, 1, dims))
+    try:
+        grads, loss = torch.zeros((n, d), device="cuda"), torch.zeros(n, device="cuda")
+        B.dbw_grad(h, dev(params), dev(x), dev(g.integers(0, 26, (n, 1)).astype(np.int32)), grads, loss)
+        got = grads.cpu().numpy().astype(np.float64)
+    finally:
+        B.dbw_destroy(h)
+    w, b = got[:, :617 * 301].reshape(n, 301, 617), got[:, 617 * 301:617 * 301 + 301]
+    want = b[:, :, None] * x
+    assert (want != 0).any() and np.all(np.abs(w - want) <= (2.0 ** -24 + 2.0 ** -30) * np.abs(want))

@@ -1,4 +1,4 @@
-"""Infinities and NaN in the kernels that split fp32 values into three bf16 values: element by element
+"""Infinities, NaN and the largest floats in the kernels that split fp32 values into three bf16 values: element by element
 what plain sums give (the oracle), and in about the time that other values take."""
 import numpy as np
 import pytest
@@ -55,7 +55,7 @@ def gradients(B, desc, dims, params, x, y):
 # One filter row and two with a partial last step, widths on and off 16 and 8, 3 x 3 and 5 x 5, one and several blocks of
 # output channels, one and several samples per workgroup, shared blocks of the weight gradient and not.
 CNN = [(1, 28, 28, 6, 16, 5, 20, 10), (3, 12, 20, 9, 40, 5, 12, 5), (2, 16, 16, 17, 33, 3, 12, 4), (1, 8, 8, 4, 70, 3, 8, 3)]
-CNN_WHERE = ["pixels", "conv1 +inf", "conv2 +inf", "conv2 -inf", "conv2 nan"]
+CNN_WHERE = ["pixels", "largest", "conv1 +inf", "conv2 +inf", "conv2 -inf", "conv2 nan"]
 
 
 @pytest.mark.parametrize("where", CNN_WHERE)
@@ -63,7 +63,8 @@ CNN_WHERE = ["pixels", "conv1 +inf", "conv2 +inf", "conv2 -inf", "conv2 nan"]
 def test_cnn_element_by_element(B, orc, shape, where):
     """Worker 1 of two, batch 3.  pixels: an infinite pixel inside one sample and one in the corner of another, under negative
     filters, so that the pooled maps and the loss stay finite and only those weight gradients of conv1 are lost that the
-    pixels enter (0 * inf), not those of filter positions that would need an output outside the image.  conv1 / conv2: one infinite or NaN weight at a filter's centre, which no output reaches
+    pixels enter (0 * inf), not those of filter positions that would need an output outside the image.  largest: the
+    largest float as a pixel.  conv1 / conv2: one infinite or NaN weight at a filter's centre, which no output reaches
     over the border with; conv1's under positive pixels, so that the channel is infinite throughout, and below filters
     of both signs, so that all of conv2 is inf - inf.  Tolerance as for finite gradients (3e-5 per layer)."""
     C0, H, W, C1, C2, K, F, NC = shape
@@ -81,6 +82,9 @@ def test_cnn_element_by_element(B, orc, shape, where):
         w1[:, c] = -np.abs(w1[:, c]) - 0.01
         x[1, 0, c, H // 2, W // 2] = np.inf
         x[1, 2, c, 0, W - 1] = np.inf
+    elif where == "largest":
+        params[1, :C1 * C0 * KK] *= 1e-6
+        x[1, 0, c, H // 2, W // 2] = np.finfo(np.float32).max
     elif where == "conv1 +inf":
         x[1, :, c] = np.abs(x[1, :, c]) + 0.1
         w1[C1 - 1, c, centre] = np.inf
