@@ -18,11 +18,12 @@
 //                  chunk run next to each other on the same XCD so the chunk stays in that
 //                  XCD's L2 while its readers run.  Workgroup ids are dealt round-robin to
 //                  the 8 XCDs, hence the id -> (chunk, worker) map.
+// Short rows off 16-byte boundaries take mix_csr_columns, a thread per column and worker.
 //
 // Gradients and results are touched exactly once, so they use non-temporal accesses and
 // do not push parameter rows out of the caches.  The summation order is fixed (self, then
 // selected neighbours in ascending index): results are bit-reproducible and identical
-// between the two kernels.
+// between the kernels.
 #include <algorithm>
 
 #include "dbw_internal.h"
@@ -48,48 +49,50 @@ __device__ __forceinline__ float4 fma4(float w, float4 a, float4 acc)
 }
 
 // Four consecutive floats of a row.  WIDE: the rows start on 16-byte boundaries and are padded to a multiple of four
-// floats.  Otherwise the same 16 bytes are fetched on a 4-byte boundary, which the memory instructions allow (the type says
-// so to the compiler), and the last, partial group of a row is taken apart, because what follows it need not be
-// this row's memory.  A wave's accesses stay one run; the lines at its ends are touched twice, which is why the
-// accesses are then not marked as streaming (the caches join the halves).
+// floats.  Otherwise the same 16 bytes are accessed on a 4-byte boundary, which the memory instructions allow (the type says
+// so to the compiler), and the last, partial group of a row, behind which need not be this row's memory, is moved back to
+// end with it: its first columns are computed twice, to the same values.  A wave's accesses stay one run; the lines at its
+// ends are touched twice, which is why the accesses are then not marked as streaming (the caches join the halves).
 typedef float vf4_any __attribute__((ext_vector_type(4), aligned(4)));
 
+// First column of group c of a row of d columns (at least four of them unless WIDE).
 template <bool WIDE>
-__device__ __forceinline__ float4 load_row(const float *p, int64_t left /* floats up to column d */)
+__device__ __forceinline__ int64_t group_column(int64_t c, int64_t d) { return WIDE ? 4 * c : min(4 * c, d - 4); }
+
+template <bool WIDE>
+__device__ __forceinline__ float4 load_row(const float *p)
 {
     if (WIDE) {
         const vf4 v = *(const vf4 *)p;
         return make_float4(v.x, v.y, v.z, v.w);
     }
-    if (left >= 4) {
-        const vf4_any v = *(const vf4_any *)p;
-        return make_float4(v.x, v.y, v.z, v.w);
-    }
-    return make_float4(p[0], left > 1 ? p[1] : 0.f, left > 2 ? p[2] : 0.f, 0.f);
+    const vf4_any v = *(const vf4_any *)p;
+    return make_float4(v.x, v.y, v.z, v.w);
 }
 
 template <bool WIDE>
-__device__ __forceinline__ float4 load_stream(const float *p, int64_t left)
+__device__ __forceinline__ float4 load_stream(const float *p)
 {
-    if (!WIDE) return load_row<WIDE>(p, left);
+    if (!WIDE) return load_row<WIDE>(p);
     const vf4 v = __builtin_nontemporal_load((const vf4 *)p);
     return make_float4(v.x, v.y, v.z, v.w);
 }
 
-// Stores up to column d: padding stays untouched.
+// Stores up to column d (`left` columns from p on): padding stays untouched.
 template <bool WIDE>
 __device__ __forceinline__ void store_stream(float *p, float4 v, int64_t left)
 {
-    if (left >= 4) {
-        vf4 t;
-        t.x = v.x; t.y = v.y; t.z = v.z; t.w = v.w;
-        if (WIDE) __builtin_nontemporal_store(t, (vf4 *)p);
-        else *(vf4_any *)p = t;
-        return;
+    vf4 t;
+    t.x = v.x; t.y = v.y; t.z = v.z; t.w = v.w;
+    if (!WIDE) {
+        *(vf4_any *)p = t;
+    } else if (left >= 4) {
+        __builtin_nontemporal_store(t, (vf4 *)p);
+    } else {
+        p[0] = v.x;
+        if (left > 1) p[1] = v.y;
+        if (left > 2) p[2] = v.z;
     }
-    p[0] = v.x;
-    if (left > 1) p[1] = v.y;
-    if (left > 2) p[2] = v.z;
 }
 
 // Persistent workgroup, tiles of N rows x TC4 float4 columns (N * TC4 <= LDS_TILE).
@@ -136,8 +139,9 @@ __global__ __launch_bounds__(LDS_THREADS) void mix_lds_tiles(
             xs[u] = make_float4(0.f, 0.f, 0.f, 0.f);
             gs[u] = xs[u];
             if (col[u] < TC4 && c < n_vec) {
-                xs[u] = load_stream<WIDE>(&x[rowoff[u] + 4 * c], d - 4 * c);
-                if (HAS_G) gs[u] = load_stream<WIDE>(&g[rowoff[u] + 4 * c], d - 4 * c);
+                const int64_t at = rowoff[u] + group_column<WIDE>(c, d);
+                xs[u] = load_stream<WIDE>(&x[at]);
+                if (HAS_G) gs[u] = load_stream<WIDE>(&g[at]);
                 if (ORDER == DBW_ORDER_ATC && HAS_G) xs[u] = fma4(-eta[u], gs[u], xs[u]);
             }
         }
@@ -168,7 +172,7 @@ __global__ __launch_bounds__(LDS_THREADS) void mix_lds_tiles(
                 for (int k = 0; k < cnt[u]; ++k)
                     acc = fma4(s_w[beg[u] + k], tl[s_idx[beg[u] + k] * TC4 + col[u]], acc);
                 if (ORDER == DBW_ORDER_CTA && HAS_G) acc = fma4(-eta[u], gc[u], acc);
-                store_stream<WIDE>(&out[rowoff[u] + 4 * c], acc, d - 4 * c);
+                store_stream<WIDE>(&out[rowoff[u] + group_column<WIDE>(c, d)], acc, d - 4 * c);
             }
         }
         if (nx < n_tiles) {
@@ -198,18 +202,25 @@ __global__ __launch_bounds__(MIX_THREADS) void mix_csr_vec4(
 
     const int beg = rowptr[i], cnt = p[i];
     const float ws = self_w[i], eta_i = lr.at(i);
-    const int64_t c0 = chunk * (int64_t)(MIX_THREADS * UNROLL) + threadIdx.x;
     const float *xi = x + (int64_t)i * ld;
+    // groups beyond the row: WIDE: left out; otherwise the last one once more, without a condition in the way of the loads
+    int64_t at[UNROLL];
+    bool ok[UNROLL];
+#pragma unroll
+    for (int u = 0; u < UNROLL; ++u) {
+        const int64_t c = chunk * (int64_t)(MIX_THREADS * UNROLL) + threadIdx.x + (int64_t)u * MIX_THREADS;
+        at[u] = group_column<WIDE>(c, d);
+        ok[u] = c < n_vec;
+    }
 
     float4 acc[UNROLL], gv[UNROLL];
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u) {
-        const int64_t c = c0 + (int64_t)u * MIX_THREADS;
         acc[u] = make_float4(0.f, 0.f, 0.f, 0.f);
         gv[u] = acc[u];
-        if (c < n_vec) {
-            float4 v = load_row<WIDE>(xi + 4 * c, d - 4 * c);
-            if (HAS_G) gv[u] = load_stream<WIDE>(&g[(int64_t)i * ld + 4 * c], d - 4 * c);
+        if (!WIDE || ok[u]) {
+            float4 v = load_row<WIDE>(xi + at[u]);
+            if (HAS_G) gv[u] = load_stream<WIDE>(&g[(int64_t)i * ld + at[u]]);
             if (ORDER == DBW_ORDER_ATC && HAS_G) v = fma4(-eta_i, gv[u], v);
             acc[u] = make_float4(ws * v.x, ws * v.y, ws * v.z, ws * v.w);
         }
@@ -220,23 +231,45 @@ __global__ __launch_bounds__(MIX_THREADS) void mix_csr_vec4(
         const float *xj = x + (int64_t)j * ld;
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u) {
-            const int64_t c = c0 + (int64_t)u * MIX_THREADS;
-            if (c < n_vec) {
-                float4 v = load_row<WIDE>(xj + 4 * c, d - 4 * c);
-                if (ORDER == DBW_ORDER_ATC && HAS_G) v = fma4(-eta_j, load_row<WIDE>(&g[(int64_t)j * ld + 4 * c], d - 4 * c), v);
+            if (!WIDE || ok[u]) {
+                float4 v = load_row<WIDE>(xj + at[u]);
+                if (ORDER == DBW_ORDER_ATC && HAS_G) v = fma4(-eta_j, load_row<WIDE>(&g[(int64_t)j * ld + at[u]]), v);
                 acc[u] = fma4(w, v, acc[u]);
             }
         }
     }
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u) {
-        const int64_t c = c0 + (int64_t)u * MIX_THREADS;
-        if (c < n_vec) {
+        if (ok[u]) {
             float4 r = acc[u];
             if (ORDER == DBW_ORDER_CTA && HAS_G) r = fma4(-eta_i, gv[u], r);
-            store_stream<WIDE>(&out[(int64_t)i * ld + 4 * c], r, d - 4 * c);
+            store_stream<WIDE>(&out[(int64_t)i * ld + at[u]], r, d - at[u]);
         }
     }
+}
+
+// One thread per column and worker, for rows off 16-byte boundaries that are short (see launch).
+template <int ORDER, bool HAS_G, class LR>
+__global__ __launch_bounds__(MIX_THREADS) void mix_csr_columns(
+    int n_chunks, int64_t ld, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ p,
+    const int32_t *__restrict__ sel_idx, const float *__restrict__ sel_w, const float *__restrict__ self_w,
+    const float *__restrict__ x, const float *__restrict__ g, float *__restrict__ out, LR lr, int64_t d)
+{
+    const int i = blockIdx.x / n_chunks;
+    const int64_t c = (int64_t)(blockIdx.x % n_chunks) * MIX_THREADS + threadIdx.x;
+    if (c >= d) return;
+    const int beg = rowptr[i], cnt = p[i];
+    float v = x[(int64_t)i * ld + c];
+    if (ORDER == DBW_ORDER_ATC && HAS_G) v = fmaf(-lr.at(i), g[(int64_t)i * ld + c], v);
+    float acc = self_w[i] * v;
+    for (int k = 0; k < cnt; ++k) {
+        const int j = sel_idx[beg + k];
+        float vj = x[(int64_t)j * ld + c];
+        if (ORDER == DBW_ORDER_ATC && HAS_G) vj = fmaf(-lr.at(j), g[(int64_t)j * ld + c], vj);
+        acc = fmaf(sel_w[beg + k], vj, acc);
+    }
+    if (ORDER == DBW_ORDER_CTA && HAS_G) acc = fmaf(-lr.at(i), g[(int64_t)i * ld + c], acc);
+    out[(int64_t)i * ld + c] = acc;
 }
 
 int device_cus()
@@ -270,10 +303,36 @@ int launch_lds(dbw_ctx *c, const float *x, const float *g, float *out, LR lr, in
     return DBW_OK;
 }
 
-template <int ORDER, bool HAS_G, bool WIDE, class LR>
-int launch_aligned(dbw_ctx *c, const float *x, const float *g, float *out, LR lr, hipStream_t s)
+template <int ORDER, bool HAS_G, int UNROLL, bool WIDE, class LR>
+int launch_vec4(dbw_ctx *c, const float *x, const float *g, float *out, LR lr, int64_t n_vec, hipStream_t s)
 {
-    constexpr int UNROLL = 2;
+    const int64_t per = (int64_t)MIX_THREADS * UNROLL;
+    const int64_t n_chunks = (n_vec + per - 1) / per;
+    const int64_t per_xcd = (n_chunks + MIX_XCDS - 1) / MIX_XCDS;
+    const int64_t blocks = per_xcd * MIX_XCDS * c->N;
+    if (n_chunks > INT32_MAX || blocks > INT32_MAX) return DBW_ERR_UNSUPPORTED;
+    dbw_timer tm(c, "mix_csr_vec4", s);
+    hipLaunchKernelGGL((mix_csr_vec4<ORDER, HAS_G, UNROLL, WIDE, LR>), dim3((unsigned)blocks), dim3(MIX_THREADS), 0, s,
+                       c->N, n_vec, c->ld, (int)n_chunks, c->rowptr, c->p, c->sel_idx, c->sel_w, c->self_w, x, g, out, lr, c->d);
+    DBW_HIP(hipGetLastError());
+    return DBW_OK;
+}
+
+template <int ORDER, bool HAS_G, class LR>
+int launch_columns(dbw_ctx *c, const float *x, const float *g, float *out, LR lr, hipStream_t s)
+{
+    const int64_t n_chunks = (c->d + MIX_THREADS - 1) / MIX_THREADS, blocks = n_chunks * c->N;
+    if (blocks > INT32_MAX) return DBW_ERR_UNSUPPORTED;
+    dbw_timer tm(c, "mix_csr_columns", s);
+    hipLaunchKernelGGL((mix_csr_columns<ORDER, HAS_G, LR>), dim3((unsigned)blocks), dim3(MIX_THREADS), 0, s, (int)n_chunks, c->ld,
+                       c->rowptr, c->p, c->sel_idx, c->sel_w, c->self_w, x, g, out, lr, c->d);
+    DBW_HIP(hipGetLastError());
+    return DBW_OK;
+}
+
+template <int ORDER, bool HAS_G, bool WIDE, class LR>
+int launch_groups(dbw_ctx *c, const float *x, const float *g, float *out, LR lr, hipStream_t s)
+{
     // groups of four columns; the last may straddle column d
     const int64_t n_vec = (c->d + 3) / 4;
     // Tile width: a power of two of groups of four columns, 8..256, that holds all N rows in 64 KB.  The widest one
@@ -293,7 +352,10 @@ int launch_aligned(dbw_ctx *c, const float *x, const float *g, float *out, LR lr
             tc4 = cand;
         }
     }
-    const bool use_lds = tc4 >= 8 && c->nnz <= LDS_MAX_EDGES && (n_vec + tc4 - 1) / tc4 >= device_cus() / 2;
+    bool use_lds = tc4 >= 8 && c->nnz <= LDS_MAX_EDGES && (n_vec + tc4 - 1) / tc4 >= device_cus() / 2;
+    // A tile of few rows is small, and few neighbours' rows stay in the caches anyway (rows of 2 000 003 columns off 16-byte
+    // boundaries, sparse kernels: two workers 30 us with tiles, 9.8 without; eight in a complete graph 46, 36; twelve 61, 75).
+    if (!WIDE && c->N <= 8) use_lds = false;
     if (use_lds) {
         switch (tc4) {
         case 256: return launch_lds<ORDER, HAS_G, 256, WIDE, LR>(c, x, g, out, lr, n_vec, s);
@@ -304,28 +366,22 @@ int launch_aligned(dbw_ctx *c, const float *x, const float *g, float *out, LR lr
         default: return launch_lds<ORDER, HAS_G, 8, WIDE, LR>(c, x, g, out, lr, n_vec, s);
         }
     }
-    const int64_t per = (int64_t)MIX_THREADS * UNROLL;
-    const int64_t n_chunks = (n_vec + per - 1) / per;
-    const int64_t per_xcd = (n_chunks + MIX_XCDS - 1) / MIX_XCDS;
-    const int64_t blocks = per_xcd * MIX_XCDS * c->N;
-    if (n_chunks > INT32_MAX || blocks > INT32_MAX) return DBW_ERR_UNSUPPORTED;
-    dbw_timer tm(c, "mix_csr_vec4", s);
-    hipLaunchKernelGGL((mix_csr_vec4<ORDER, HAS_G, UNROLL, WIDE, LR>), dim3((unsigned)blocks), dim3(MIX_THREADS), 0, s,
-                       c->N, n_vec, c->ld, (int)n_chunks, c->rowptr, c->p, c->sel_idx, c->sel_w, c->self_w, x, g, out, lr, c->d);
-    DBW_HIP(hipGetLastError());
-    return DBW_OK;
+    return launch_vec4<ORDER, HAS_G, WIDE ? 2 : 1, WIDE, LR>(c, x, g, out, lr, n_vec, s);
 }
 
 template <int ORDER, bool HAS_G, class LR>
 int launch(dbw_ctx *c, const float *x, const float *g, float *out, LR lr, hipStream_t s)
 {
     // Rows without padding or on odd addresses (N = 48 x 1 000 003 columns, row stride 1 000 003: 129 us against 106 on
-    // padded rows; N = 128 x 2.8 M: 1.08 ms against 0.82).  They are never sent to a thread per column, which
-    // gathers its neighbours from the caches: 359 us and 3.97 ms at these sizes.
+    // padded rows; N = 128 x 2.8 M: 1.08 ms against 0.82).
     const bool wide = (c->ld % 4 == 0) && ((uintptr_t)x % 16 == 0) && ((uintptr_t)out % 16 == 0) &&
                       (!HAS_G || (uintptr_t)g % 16 == 0);
-    return wide ? launch_aligned<ORDER, HAS_G, true, LR>(c, x, g, out, lr, s)
-                : launch_aligned<ORDER, HAS_G, false, LR>(c, x, g, out, lr, s);
+    if (wide) return launch_groups<ORDER, HAS_G, true, LR>(c, x, g, out, lr, s);
+    // Short ones have too few groups of four for the chip, and a thread per column walks through a long neighbour list faster (400
+    // workers with 8 neighbours: 501 columns 6.2 us against 9.7, 5 001 16 against 11; 48 in a complete graph 10.6 and 11.4,
+    // 11.6 and 11.7; fewer workers: the launch alone).
+    if (c->d < 2048) return launch_columns<ORDER, HAS_G, LR>(c, x, g, out, lr, s);
+    return launch_groups<ORDER, HAS_G, false, LR>(c, x, g, out, lr, s);
 }
 
 }  // namespace

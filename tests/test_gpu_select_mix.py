@@ -259,10 +259,11 @@ def test_dtur_select_equals_the_two_calls(B, orc, name, graph):
 
 
 # Rows on 4-byte boundaries (no padding, or a first element off a 16-byte boundary): the partial group of four at a
-# row's end in every phase, the last row's end = the end of the allocation, wide and narrow tiles, and the kernel without
-# LDS tiles (a row list too long for it).
+# row's end in every phase, the last row's end = the end of the allocation, wide and narrow tiles, the kernel without LDS
+# tiles (few workers, a row list too long for them) and the thread per column (below 2048 columns).
 ODD_ROWS = [("ring8", 7851, 7851, 0), ("ring8", 40001, 40003, 1), ("reg4x32", 70002, 70002, 0), ("reg8x128", 9003, 9005, 3),
-            ("complete100", 1025, 1025, 0), ("ring8", 3, 3, 2)]
+            ("complete100", 1025, 1025, 0), ("ring8", 3, 3, 2), ("reg4x32", 40001, 40001, 0), ("reg4x32", 4099, 4099, 1),
+            ("complete100", 2049, 2049, 1), ("complete100", 2047, 2047, 0), ("ring8", 2050, 2051, 1), ("reg8x128", 2051, 2051, 0)]
 
 
 @pytest.mark.parametrize("order", [0, 1], ids=["cta", "atc"])
@@ -299,3 +300,33 @@ def test_rows_off_16_byte_boundaries(B, orc, gname, d, ld, shift, order):
     want = orc.round_(rowptr, colidx, mask, p, x, gr, np.float32(0.05), order)
     assert_params_close(outs[0][:, :d], want, what=f"{gname} d {d}")
     assert np.array_equal(outs[0][:, :d], outs[1][:, :d])
+
+
+@pytest.mark.parametrize("mix", ["MIX_CSR"])
+def test_few_workers_on_odd_rows_stream(B, mix):
+    """Two workers with rows off 16-byte boundaries: a round reads two arrays and writes one, and takes at most 2.5 times as
+    long as an addition of the same arrays (a kernel whose tiles two rows leave empty took 3.7 and 18 times as long)."""
+    n, d = 2, 2_000_003
+    rowptr, colidx = inputs.graph_complete(n)
+    x, g, out = torch.randn(n, d, device="cuda"), torch.randn(n, d, device="cuda"), torch.zeros(n, d, device="cuda")
+
+    def best(fn):
+        ms = []
+        for _ in range(6):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            for _ in range(20):
+                fn()
+            b.record()
+            torch.cuda.synchronize()
+            ms.append(a.elapsed_time(b) / 20)
+        return min(ms)
+
+    h = B.dbw_create(rowptr, colidx, n, d, ld=d, mix_path=getattr(B, mix))
+    try:
+        B.dbw_select(h, dev(np.array([1.0, 2.0], np.float32)), dev(np.zeros(n, np.int32)))
+        t = best(lambda: B.dbw_round(h, x, out, 0.1, ext_grads=g))
+    finally:
+        B.dbw_destroy(h)
+    plain = best(lambda: torch.add(x, g, alpha=0.1, out=out))
+    assert t <= 2.5 * plain, (t, plain)
