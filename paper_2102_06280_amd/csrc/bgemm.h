@@ -24,14 +24,14 @@
 // fragment of v_mfma_f32_32x32x16_bf16 is one 128-bit read.  A thread therefore fetches eight consecutive k of a row
 // at a time, of a row-contiguous operand with eight loads whose lanes run along the rows.  20 workers, batch 101,
 // 617-301-75-26 on rows without padding: three weight gradients 42 us (fp32 matrix instructions and 4-byte loads 46), two
-// data gradients 26 (26); 11 workers, batch 1 024, 161-185-185-24: 52 (61), 38 (44).  The small partial products have an
-// accumulator of their own, which makes the sums three times as exact.
+// data gradients 26 (26); 11 workers, batch 1 024, 161-185-185-24: 52 (61), 38 (44).  Small and large partial products
+// are summed apart.
 //
-// kernel (forward products of dense layers, convolution operands): 2 x 2 fragments of v_mfma_f32_16x16x4_f32 per
-// wavefront (true fp32).  The sign of a forward product decides whole samples' gradients where it is next to zero, so its
-// rounding is that of the chain and head kernels that compute the same layer; the split form gained nothing, since
-// the fetches bound both.  The three forward products of the first example: 46 us (with 4-byte loads 113), of the second
-// 59 (123).
+// kernel (forward products of dense layers, most data gradients that have a launch to themselves, convolution operands):
+// 2 x 2 fragments of v_mfma_f32_16x16x4_f32 per wavefront (true fp32).  The sign of a forward product decides whole samples'
+// gradients where it is next to zero, so its rounding is that of the chain and head kernels that compute the same layer;
+// the split form gained nothing, since the fetches bound both.  The three forward products of the first example: 46 us
+// (with 4-byte loads 113), of the second 59 (123).
 //   A fragment: lane l holds A[m = l % 16][slot l / 16], B fragment: B[slot l / 16][n = l % 16]
 //   D: 4 floats, d[v] = D[m = 4 * (l / 16) + v][n = l % 16]
 // The four k-slots of instruction j (0..3) of a 16-wide k group are k = 4 * slot + j for
@@ -55,9 +55,10 @@ constexpr int lds_floats(bool kc, int rows) { return kc ? rows * LDS_KC : BK * l
 
 // Dense operand.  KC: element (r, k) at p[w * stride + r * ld + k]; otherwise at
 // p[w * stride + k * ld + r].  Offsets inside one worker's block fit 32 bits.
-template <bool KC_>
+// ALIGNED (see aligned): the tile is fetched 16 bytes at a time without a guard.
+template <bool KC_, bool ALIGNED_ = false>
 struct Dense {
-    static constexpr bool KC = KC_, WIDE = KC_;
+    static constexpr bool KC = KC_, ALIGNED = ALIGNED_, WIDE = KC_ && !ALIGNED_;
     const float *p;
     int64_t ld, stride;
     struct RowCtx { int off; bool ok; };
@@ -108,15 +109,34 @@ __device__ __forceinline__ void load8(const float *src, int left, float *v)
     }
 }
 
-// Operands with a member WIDE that is true (dense ones, contiguous along k) are fetched eight k at a time.
+// Whether every row of an operand starts on a 16-byte boundary and its contiguous extent divides by four.
+template <bool KC>
+inline bool aligned(const Dense<KC> &op, int rows, int K)
+{
+    return (uintptr_t)op.p % 16 == 0 && op.ld % 4 == 0 && op.stride % 4 == 0 && (KC ? K : rows) % 4 == 0;
+}
+
+// How a loader's operand is fetched: dense ones 16 bytes at a time (ALIGNED), dense ones that are contiguous along k eight
+// elements at a time (WIDE), all others element by element.
+template <class L>
+struct fetch_kind {
+    template <class T> static constexpr int test(decltype(T::WIDE) *) { return T::ALIGNED ? 2 : T::WIDE ? 1 : 0; }
+    template <class T> static constexpr int test(...) { return 0; }
+    static constexpr int value = test<L>(nullptr);
+};
 template <class L>
 struct wide {
-    template <class T> static constexpr bool test(decltype(T::WIDE) *) { return T::WIDE; }
-    template <class T> static constexpr bool test(...) { return false; }
-    static constexpr bool value = test<L>(nullptr);
+    static constexpr bool value = fetch_kind<L>::value == 1;
+};
+template <class L>
+struct vectors {
+    static constexpr bool value = fetch_kind<L>::value == 2;
 };
 
 // Global -> registers for a ROWS x 64 operand tile (ROWS / 4 elements per thread).
+//   ALIGNED: elements 4 j .. 4 j + 3 are, with f = tid + 256 j, (row = f / 16, k = 4 (f % 16) ..) of a KC operand, otherwise
+//   (row = 4 (f % (ROWS / 4)) .., k = f / (ROWS / 4)); in the place of a group outside the operand the first one is read and
+//   replaced by zero when the tile is written to LDS (replaced at once, it would have to arrive before the multiplies)
 //   WIDE: elements 8 u .. 8 u + 7 are (row = tid / 8 + 32 u, k = 8 (tid % 8) ..): eight lanes read 256 contiguous bytes
 //   KC: element j of the thread is (row = wave + 4 j, k = lane)
 //   RC: ROWS >= 64; element j is (row = lane + 64 (j % (ROWS / 64)), k = wave + 4 (j / (ROWS / 64)))
@@ -140,10 +160,23 @@ __device__ __forceinline__ void make_rows(const L &op, int r0, int R, int lane, 
 
 template <class L, int ROWS>
 __device__ __forceinline__ void fetch_tile(const L &op, int w, int r0, int R, int k0, int K, int wave, int lane,
-                                           const RowCache<L, ROWS> &rows, float (&v)[ROWS / 4])
+                                           const RowCache<L, ROWS> &rows, float (&v)[ROWS / 4], uint32_t &inside)
 {
     static_assert(L::KC || ROWS >= 64, "a row-contiguous operand needs at least 64 tile rows");
-    if constexpr (wide<L>::value) {
+    if constexpr (vectors<L>::value) {
+        const float *base = op.p + w * op.stride;
+        inside = 0;
+#pragma unroll
+        for (int j = 0; j < ROWS / 16; ++j) {
+            const int f = 64 * wave + lane + 256 * j;
+            const int r = r0 + (L::KC ? f / 16 : 4 * (f % (ROWS / 4))), k = k0 + (L::KC ? 4 * (f % 16) : f / (ROWS / 4));
+            const bool ok = r < R && k < K;
+            const f32x4 q = *(const f32x4 *)(base + (ok ? (L::KC ? r * (int)op.ld + k : k * (int)op.ld + r) : 0));
+            inside |= (ok ? 1u : 0u) << j;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[4 * j + e] = q[e];
+        }
+    } else if constexpr (wide<L>::value) {
         const float *base = op.p + w * op.stride;
         const int tid = 64 * wave + lane;
 #pragma unroll
@@ -170,8 +203,18 @@ __device__ __forceinline__ void fetch_tile(const L &op, int w, int r0, int R, in
 }
 
 template <class L, int ROWS>
-__device__ __forceinline__ void commit_tile(float *lds, int wave, int lane, const float (&v)[ROWS / 4])
+__device__ __forceinline__ void commit_tile(float *lds, int wave, int lane, const float (&v)[ROWS / 4], uint32_t inside)
 {
+    if constexpr (vectors<L>::value) {
+#pragma unroll
+        for (int j = 0; j < ROWS / 16; ++j) {
+            const int f = 64 * wave + lane + 256 * j;
+            const bool ok = inside >> j & 1u;
+            float *d = &lds[L::KC ? f / 16 * LDS_KC + 4 * (f % 16) : f / (ROWS / 4) * lds_rc(ROWS) + 4 * (f % (ROWS / 4))];
+            *(f32x4 *)d = f32x4{ok ? v[4 * j] : 0.f, ok ? v[4 * j + 1] : 0.f, ok ? v[4 * j + 2] : 0.f, ok ? v[4 * j + 3] : 0.f};
+        }
+        return;
+    }
     if constexpr (wide<L>::value) {
         const int tid = 64 * wave + lane;
 #pragma unroll
@@ -232,18 +275,19 @@ __global__ __launch_bounds__(THREADS) void kernel(LA A, LB B, EP E, int M, int N
     make_rows<LA, BM>(A, m0, M, lane, arows);
     make_rows<LB, BN>(B, n0, N, lane, brows);
     float ra[BM / 4], rb[BN / 4];
+    uint32_t ina = 0, inb = 0;
     auto fetch = [&](int k0) {
-        fetch_tile<LA, BM>(A, w, m0, M, k0, kend, wave, lane, arows, ra);
-        fetch_tile<LB, BN>(B, w, n0, N, k0, kend, wave, lane, brows, rb);
+        fetch_tile<LA, BM>(A, w, m0, M, k0, kend, wave, lane, arows, ra, ina);
+        fetch_tile<LB, BN>(B, w, n0, N, k0, kend, wave, lane, brows, rb, inb);
     };
     fetch(kbeg);
     for (int k0 = kbeg; k0 < kend; k0 += BK) {
         __syncthreads();                       // previous tile fully consumed
-        commit_tile<LA, BM>(As, wave, lane, ra);
-        commit_tile<LB, BN>(Bs, wave, lane, rb);
+        commit_tile<LA, BM>(As, wave, lane, ra, ina);
+        commit_tile<LB, BN>(Bs, wave, lane, rb, inb);
         __syncthreads();
         if (k0 + BK < kend) fetch(k0 + BK);    // next tile's loads fly during the MFMAs
-        if constexpr (wide<LA>::value || wide<LB>::value) __builtin_amdgcn_sched_barrier(0);   // nothing that consumes them moves up here
+        if constexpr (fetch_kind<LA>::value || fetch_kind<LB>::value) __builtin_amdgcn_sched_barrier(0);   // nothing that consumes them moves up here
 #pragma unroll
         for (int kg = 0; kg < BK / 16; ++kg) {
             f32x4 fa[2], fb[2];

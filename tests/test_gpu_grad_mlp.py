@@ -46,6 +46,12 @@ SHAPES = [
     ([64, 40, 20], 33, 3, "xent"),
     ([2000, 12], 20, 2, "xent"),
     ([1100, 7], 40, 2, "mse"),
+    # data gradients in a launch of their own: fp32 instruction over few, 64 and 68 units, partial tiles in both directions;
+    # split over 324 units with more than 256 workgroups
+    ([64, 96, 64, 10], 61, 4, "xent"),
+    ([64, 100, 68, 10], 62, 4, "xent"),
+    ([64, 132, 64, 8, 10], 260, 3, "xent"),
+    ([16, 132, 324, 10], 260, 18, "xent"),
 ]
 
 
