@@ -4,7 +4,8 @@
 //
 //   CTA: out = P X - lr G            ATC: out = P (X - lr G)
 //
-// More than 32 workers, and rows off 16-byte boundaries, take the kernel of mix_split.h; the one below does the rest.
+// More than 32 workers take the kernel of mix_split.h, and so do rows off 16-byte boundaries from 17 workers on; up to 16 of
+// those are mix_dense_columns' (at the end).  The kernel below does the rest.
 //
 // P (N x N, zero-padded to NPAD = 32 * MB) is tiny and lives in registers: each of the 8
 // wavefronts of a workgroup keeps the A-operand fragments of one 32-row block of P for the
@@ -270,6 +271,89 @@ __global__ __launch_bounds__(DENSE_THREADS) void mix_dense_kernel(
     }
 }
 
+// Up to NB workers on rows off 16-byte boundaries.  A thread keeps the sums of all workers for V columns in registers and
+// takes in one worker's values after the other, with the column of P that goes with them: wave-uniform, through the scalar
+// cache.  Every value is read once, nothing is staged, and rows of padding cost multiplies only.  V = 4: 16-byte accesses on
+// 4-byte boundaries; the last group of a row is moved back to end with it (columns computed twice, to the same values).
+typedef float vf4_any __attribute__((ext_vector_type(4), aligned(4)));
+
+constexpr int COLUMN_THREADS = 256;
+template <int NB, int V, int ORDER, bool HAS_G, class LR>
+__global__ __launch_bounds__(COLUMN_THREADS) void mix_dense_columns(int N, int64_t d, int64_t ld, const float *__restrict__ Wsw,
+                                                                    const float *__restrict__ x, const float *__restrict__ g,
+                                                                    float *__restrict__ out, LR lr)
+{
+    int64_t c = V * ((int64_t)blockIdx.x * COLUMN_THREADS + threadIdx.x);
+    if (c >= d) return;
+    c = min(c, d - V);
+    auto load = [&](const float *row, float (&v)[V]) {
+        if constexpr (V == 4) {
+            const vf4_any q = *(const vf4_any *)(row + c);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = q[e];
+        } else {
+            v[0] = row[c];
+        }
+    };
+    constexpr bool EPI = ORDER == DBW_ORDER_CTA && HAS_G;
+    float acc[NB][V], late[EPI ? NB : 1][V];                         // (gradients of the epilogue: under way during the sums)
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        if (EPI) load(g + (int64_t)min(i, N - 1) * ld, late[EPI ? i : 0]);
+#pragma unroll
+        for (int e = 0; e < V; ++e) acc[i][e] = 0.f;
+    }
+#pragma unroll 2
+    for (int j = 0; j < N; ++j) {
+        float v[V], gv[V];
+        load(x + (int64_t)j * ld, v);
+        if (ORDER == DBW_ORDER_ATC && HAS_G) {
+            load(g + (int64_t)j * ld, gv);
+            const float eta = lr.at(j);
+#pragma unroll
+            for (int e = 0; e < V; ++e) v[e] = fmaf(-eta, gv[e], v[e]);
+        }
+        const float *p = Wsw + (j >> 1) * 64 + 32 * (j & 1);       // column j of P, rows 0 .. 31
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+#pragma unroll
+            for (int e = 0; e < V; ++e) acc[i][e] = fmaf(p[i], v[e], acc[i][e]);
+    }
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        if (i < N) {
+            if (EPI) {
+                const float eta = lr.at(i);
+#pragma unroll
+                for (int e = 0; e < V; ++e) acc[i][e] = fmaf(-eta, late[EPI ? i : 0][e], acc[i][e]);
+            }
+            float *o = out + (int64_t)i * ld + c;
+            if constexpr (V == 4) *(vf4_any *)o = vf4_any{acc[i][0], acc[i][1], acc[i][2], acc[i][3]};
+            else o[0] = acc[i][0];
+        }
+    }
+}
+
+template <int NB, int V, int ORDER, bool HAS_G, class LR>
+int launch_columns(dbw_ctx *c, const float *W, const float *x, const float *g, float *out, LR lr, hipStream_t s)
+{
+    const int64_t per = (int64_t)V * COLUMN_THREADS, blocks = (c->d + per - 1) / per;
+    if (blocks > INT32_MAX) return DBW_ERR_UNSUPPORTED;
+    dbw_timer tm(c, "mix_dense_kernel", s);
+    hipLaunchKernelGGL((mix_dense_columns<NB, V, ORDER, HAS_G, LR>), dim3((unsigned)blocks), dim3(COLUMN_THREADS), 0, s, c->N, c->d, c->ld, W,
+                       x, g, out, lr);
+    DBW_HIP(hipGetLastError());
+    return DBW_OK;
+}
+
+template <int V, int ORDER, bool HAS_G, class LR>
+int launch_columns_n(dbw_ctx *c, const float *W, const float *x, const float *g, float *out, LR lr, hipStream_t s)
+{
+    if (c->N <= 4) return launch_columns<4, V, ORDER, HAS_G, LR>(c, W, x, g, out, lr, s);
+    if (c->N <= 8) return launch_columns<8, V, ORDER, HAS_G, LR>(c, W, x, g, out, lr, s);
+    return launch_columns<16, V, ORDER, HAS_G, LR>(c, W, x, g, out, lr, s);
+}
+
 template <int ORDER, bool HAS_G, class LR>
 int launch_fp32(dbw_ctx *c, const float *W, const float *x, const float *g, float *out, LR lr, hipStream_t s)
 {
@@ -323,6 +407,14 @@ int launch(dbw_ctx *c, const float *W, const float *x, const float *g, float *ou
     if (c->ld > DBW_DENSE_MAX_LD) return DBW_ERR_UNSUPPORTED;
     const bool wide = c->ld % 4 == 0 && (uintptr_t)x % 16 == 0 && (!HAS_G || (uintptr_t)g % 16 == 0);
     if (!wide) {
+        // Up to 16 workers the 32 rows of the matrix instruction are mostly padding, of which the copies and splits below cost as
+        // much as of the rest (d = 2 000 003 with gradients: N = 2 143 us, here 9.6; N = 8 143, 31.5; N = 16 144, 82; with N = 32 the
+        // two come out even, and rows of 50 000 columns 10.3, 15).  Four columns per thread once that fills the chip (N = 16 x
+        // 357 003 17.7 us with one, 15.5 with four; x 700 001 27.7, 22.9; x 5 001 7.2, 7.9).
+        if (c->N <= 16) {
+            if (c->d >= (int64_t)1 << 19) return launch_columns_n<4, ORDER, HAS_G, LR>(c, W, x, g, out, lr, s);
+            return launch_columns_n<1, ORDER, HAS_G, LR>(c, W, x, g, out, lr, s);
+        }
         switch (c->Npad) {
         case 32: return launch_mb<1, ORDER, HAS_G, false, LR>(c, W, x, g, out, lr, s);
         case 64: return launch_mb<2, ORDER, HAS_G, false, LR>(c, W, x, g, out, lr, s);

@@ -302,7 +302,7 @@ def test_rows_off_16_byte_boundaries(B, orc, gname, d, ld, shift, order):
     assert np.array_equal(outs[0][:, :d], outs[1][:, :d])
 
 
-@pytest.mark.parametrize("mix", ["MIX_CSR"])
+@pytest.mark.parametrize("mix", ["MIX_CSR", "MIX_DENSE"])
 def test_few_workers_on_odd_rows_stream(B, mix):
     """Two workers with rows off 16-byte boundaries: a round reads two arrays and writes one, and takes at most 2.5 times as
     long as an addition of the same arrays (a kernel whose tiles two rows leave empty took 3.7 and 18 times as long)."""
