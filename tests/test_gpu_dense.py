@@ -79,7 +79,10 @@ def test_auto_path_choice(B):
 # tiles (256, 128, 64 and 32 columns) and of a float4, fewer and more tiles than compute units, rows with and without
 # padding (the 4-byte loads).
 EDGES = [(32, 255, 4), (33, 129, 1), (64, 128, 4), (65, 61, 4), (128, 64 * 257 + 3, 1), (129, 33, 1), (256, 32 * 256 + 31, 4),
-         (256, 95, 1), (20, 517, 1), (200, 1, 4)]
+         (256, 95, 1), (20, 517, 1), (200, 1, 4),
+         # a thread per column or four of them: every size of its register block, a last group of one to three columns
+         (2, 1, 1), (4, 1027, 1), (5, 257, 1), (16, 769, 1), (3, (1 << 19) - 1, 1), (8, (1 << 19) + 1, 1), (16, (1 << 19) + 3, 1),
+         (9, (1 << 19) + 2, 1)]
 
 
 @pytest.mark.parametrize("n,d,pad", EDGES, ids=[f"n{n}-d{d}-pad{p}" for n, d, p in EDGES])
