@@ -50,13 +50,13 @@ struct WCfg {
     static constexpr size_t lds_bytes = sizeof(float) * (IMG + COUT * LDD);
 };
 
-// EXPAND: dz is given as the pooled gradients [worker][B][COUT][H/2][W/2] with dz_code of the same shape
-// and is expanded while the delta tile is copied into LDS (see expand_pooled).
-template <int CIN, int MT, int NT, int WM, int WN, int WK, int H, int W, int KS, int PC, bool EXPAND = false>
+// The deltas are given as the pooled gradients [worker][B][COUT][H/2][W/2] with dz_code of the same shape
+// and are expanded while the tile is copied into LDS (see expand_pooled).
+template <int CIN, int MT, int NT, int WM, int WN, int WK, int H, int W, int KS, int PC>
 __global__ __launch_bounds__(64 * WM * WN * WK) void conv_wgrad_kernel(
     const float *__restrict__ in, int64_t in_stride, const float *__restrict__ dz, int64_t dz_stride,
-    float *__restrict__ part, int64_t part_stride, int B, int SB, const uint8_t *__restrict__ dz_code = nullptr,
-    int64_t dz_code_stride = 0)
+    float *__restrict__ part, int64_t part_stride, int B, int SB, const uint8_t *__restrict__ dz_code,
+    int64_t dz_code_stride)
 {
     using C = WCfg<CIN, MT, NT, WM, WN, WK, H, W, KS, PC>;
     __shared__ __attribute__((aligned(16))) float img[C::IMG];
@@ -85,8 +85,8 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void conv_wgrad_kernel(
 
     for (int b = b0; b < b1; ++b) {
         const float *inb = in + w * in_stride + (int64_t)b * CIN * C::PIX;
-        const float *dzb = dz + w * dz_stride + (int64_t)b * C::COUT * (EXPAND ? C::PIX / 4 : C::PIX);
-        const uint8_t *dcb = EXPAND ? dz_code + w * dz_code_stride + (int64_t)b * C::COUT * (C::PIX / 4) : nullptr;
+        const float *dzb = dz + w * dz_stride + (int64_t)b * C::COUT * (C::PIX / 4);
+        const uint8_t *dcb = dz_code + w * dz_code_stride + (int64_t)b * C::COUT * (C::PIX / 4);
         for (int chunk = 0; chunk < C::PIX / PC; ++chunk) {
             __syncthreads();                   // previous tile fully consumed
             if (chunk == 0) {
@@ -98,15 +98,9 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void conv_wgrad_kernel(
                 }
             }
             for (int e = tid; e < C::COUT * (PC / 4); e += C::THREADS) {
-                const int co = e / (PC / 4), p4 = e % (PC / 4);
-                float4 v;
-                if (EXPAND) {
-                    const int p = chunk * PC + 4 * p4;
-                    v = expand_pooled(dzb + co * (C::PIX / 4), dcb + co * (C::PIX / 4), p / W, (p % W) / 4, W);
-                } else {
-                    v = *(const float4 *)&dzb[co * C::PIX + chunk * PC + 4 * p4];
-                }
-                *(float4 *)&dzs[co * C::LDD + 4 * p4] = v;
+                const int co = e / (PC / 4), p4 = e % (PC / 4), p = chunk * PC + 4 * p4;
+                *(float4 *)&dzs[co * C::LDD + 4 * p4] =
+                    expand_pooled(dzb + co * (C::PIX / 4), dcb + co * (C::PIX / 4), p / W, (p % W) / 4, W);
             }
             __syncthreads();
             const int chunk_row = chunk * (PC / W);                  // first image row of the chunk

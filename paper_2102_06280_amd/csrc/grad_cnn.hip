@@ -597,7 +597,7 @@ int launch_grad_cnn(dbw_ctx *c, const float *params, const float *bx, const int3
         const int nb = (B + WGRAD_SB - 1) / WGRAD_SB;
         splits1 = nb * 8;
         dbw_timer tm(c, "conv1_wgrad", s);
-        hipLaunchKernelGGL((convlds::conv_wgrad_kernel<3, 2, 5, 1, 1, 8, 32, 32, 5, 512, true>), dim3(nb, N), dim3(512), 0,
+        hipLaunchKernelGGL((convlds::conv_wgrad_kernel<3, 2, 5, 1, 1, 8, 32, 32, 5, 512>), dim3(nb, N), dim3(512), 0,
                            s, bx, xstride, A + L.dp1, ws, A + L.part1, ws, B, WGRAD_SB, code1, cs);
         DBW_HIP(hipGetLastError());
     } else if (L.split1) {
