@@ -25,7 +25,10 @@ if ROOT not in sys.path:
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E
 MFMA_FP32_PEAK_TFLOPS = 157.3  # MI355X dense fp32 matrix
 MFMA_SPLIT_PEAK_TFLOPS = 2516.6 / 6   # fp32 values as three bf16 values: six dense bf16 matrix instructions for each product
-SPLIT_KERNELS = ("mix_dense", "conv1_forward", "conv2_")   # (the timing names of the kernels that do so)
+# Timing names of the kernels that do so.  ("conv2_" and "conv1_forward" also name the fp32 launches of networks whose filters are
+# not 3 x 3 or 5 x 5; no configuration has one.)
+SPLIT_KERNELS = ("mix_dense_split", "mlp_wgrad_gemm", "mlp_dgrad_split", "conv1_forward", "conv2_")
+
 
 def measured_traffic(kernel: str, cid: int):
     """HBM bytes per launch from hardware counters, as tabulated in profiles/hbm_traffic.md, or None
@@ -239,7 +242,7 @@ def main():
     mix_path = B.dbw_mix_path(wl.h)
     dominant = max(kern, key=lambda k: kern[k][0])
     dom_ms = kern[dominant][0] / kern[dominant][1]
-    if dominant.startswith(("mix_csr", "mix_lds", "mix_tile")):
+    if dominant.startswith(("mix_csr", "mix_lds", "mix_tile", "mix_dense_columns")):
         work = 3.0 * cfg.n * cfg.d * 4          # read X, read G, write X' once each
         roofline = {"bound": "hbm", "achieved": work / (dom_ms * 1e-3) / 1e9, "peak": HBM_PEAK_GBS,
                     "unit": "GB/s", "traffic": None}
@@ -255,7 +258,7 @@ def main():
         work = kernel_flops(cfg, dominant)
         roofline = {"bound": "mfma", "achieved": work / (dom_ms * 1e-3) / 1e12, "peak": MFMA_FP32_PEAK_TFLOPS,
                     "unit": "TFLOP/s", "traffic": None}
-    split = dominant.startswith(SPLIT_KERNELS) and not (dominant.startswith("mix_dense") and cfg.n <= 32)
+    split = dominant.startswith(SPLIT_KERNELS)
     if split:
         roofline["peak"] = MFMA_SPLIT_PEAK_TFLOPS
     roofline["traffic"] = measured_traffic(dominant, cfg.cid)

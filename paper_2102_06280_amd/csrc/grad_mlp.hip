@@ -653,12 +653,14 @@ int dbw_fc_forward_backward(dbw_ctx *c, const dbw_fc_args &a, hipStream_t s)
                                (const float *)nullptr, (int64_t)0, (int64_t)0, a.din, a.din_ld, a.din_stride);
             DBW_HIP(hipGetLastError());
         } else if (dgrad_gemm) {
-            dbw_timer tm(c, "mlp_dgrad_gemm", s);
             // Next to another kernel's weight gradient the launch is short, and the fp32 instruction with unguarded 16-byte loads is
             // faster unless both the reduction and the grid are long (four wavefronts for every compute unit and more): 10 x 256
             // samples, 500 -> 400 units 33.2 us, split 29.5; 10 x 1 024 68, 60; but 4 x 256 22.9, 25.0, 10 x 16 20.3, 23.6, and
             // 10 x 1 024, 128 -> 384 23.8, 27.5, 32 x 64 samples, 32 -> 64 11.1, 13.0.
-            if (bgemm::aligned(dg.A, dg.M, dg.K) && bgemm::aligned(dg.B, dg.N, dg.K) && (dg.K < 5 * bgemm::BK || dg.tiles() * N <= 256))
+            const bool fp32 =
+                bgemm::aligned(dg.A, dg.M, dg.K) && bgemm::aligned(dg.B, dg.N, dg.K) && (dg.K < 5 * bgemm::BK || dg.tiles() * N <= 256);
+            dbw_timer tm(c, fp32 ? "mlp_dgrad_gemm" : "mlp_dgrad_split", s);
+            if (fp32)
                 DBW_HIP(bgemm::launch<64>(Dense<true, true>{dg.A.p, dg.A.ld, dg.A.stride}, Dense<false, true>{dg.B.p, dg.B.ld, dg.B.stride}, dg.E,
                                           dg.M, dg.N, dg.K, N, s));
             else

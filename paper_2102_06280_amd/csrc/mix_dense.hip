@@ -302,7 +302,7 @@ int launch_columns(dbw_ctx *c, const float *W, const float *x, const float *g, f
 {
     const int64_t per = (int64_t)V * COLUMN_THREADS, blocks = (c->d + per - 1) / per;
     if (blocks > INT32_MAX) return DBW_ERR_UNSUPPORTED;
-    dbw_timer tm(c, "mix_dense_kernel", s);
+    dbw_timer tm(c, "mix_dense_columns", s);
     hipLaunchKernelGGL((mix_dense_columns<NB, V, ORDER, HAS_G, LR>), dim3((unsigned)blocks), dim3(COLUMN_THREADS), 0, s, c->N, c->d, c->ld, W,
                        x, g, out, lr);
     DBW_HIP(hipGetLastError());
@@ -344,7 +344,7 @@ int launch_split(dbw_ctx *c, const float *W, const float *x, const float *g, flo
     using C = mixsplit::Cfg<MB, WAVES>;
     const int64_t n_tiles = (c->d + C::TC - 1) / C::TC;
     if (n_tiles > INT32_MAX) return DBW_ERR_UNSUPPORTED;
-    dbw_timer tm(c, "mix_dense_kernel", s);
+    dbw_timer tm(c, "mix_dense_split", s);
     // persistent: as many workgroups as the compute units' LDS holds
     hipLaunchKernelGGL((mixsplit::kernel<MB, WAVES, ORDER, HAS_G, WIDE, LR>), dim3((unsigned)std::min<int64_t>(n_tiles, 256 * 8 / WAVES)),
                        dim3(64 * WAVES), 0, s, c->N, c->d, c->ld, W, x, g, out, lr, (int)n_tiles);

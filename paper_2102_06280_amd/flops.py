@@ -24,7 +24,7 @@ def _mlp(cfg, dims):
                       "mlp_wgrad_gemm": n * (sum(fwd) + sum(dgrad)) / len(fwd),      # a layer's weight and data gradient
                       "mlp_thin_forward": n * sum(fwd) / len(fwd)})
     if dgrad:
-        table["mlp_dgrad_gemm"] = n * sum(dgrad) / len(dgrad)
+        table["mlp_dgrad"] = n * sum(dgrad) / len(dgrad)      # mlp_dgrad_gemm (fp32 instruction) or mlp_dgrad_split
     # the same products when the whole chain of layers runs in one launch and the weight gradients in another
     table["mlp_chain_kernel"] = n * (sum(fwd) + sum(dgrad)) + table["fc_head_kernel"]
     table["mlp_wgrad_kernel"] = n * sum(fwd)
@@ -46,7 +46,7 @@ def _cnn(cfg, desc):
         table.update({"fc32_forward": n * fc[0], "fc32_wgrad": n * fc[0], "fc32_dgrad": n * fc[0]})
     else:
         table.update({"mlp_forward_gemm": n * fc[0], "mlp_wgrad_gemm": 2 * n * fc[0],
-                      "mlp_dgrad_gemm": n * fc[0]})
+                      "mlp_dgrad": n * fc[0]})
     return table
 
 

@@ -75,6 +75,24 @@ def test_auto_path_choice(B):
     assert e.value.code == B.ERR_UNSUPPORTED
 
 
+def test_kernel_and_timing_name_of_every_size(B):
+    """Rows on 16-byte boundaries: the fp32 instruction up to 32 workers, the split form above; off them: a thread per
+    column up to 16, the split form above.  The names that the timing reports tell them apart."""
+    for n, ld, want in [(16, 260, "mix_dense_kernel"), (32, 260, "mix_dense_kernel"), (33, 260, "mix_dense_split"),
+                        (16, 257, "mix_dense_columns"), (17, 257, "mix_dense_split"), (33, 257, "mix_dense_split")]:
+        h = B.dbw_create(*inputs.graph_complete(n), n, 257, ld=ld, mix_path=B.MIX_DENSE)
+        try:
+            x = torch.ones((n, ld), dtype=torch.float32, device="cuda")
+            out = torch.zeros_like(x)
+            B.dbw_select(h, dev(np.arange(n, dtype=np.float32)), dev(np.zeros(n, np.int32)))
+            B.dbw_set_timing(h, True)
+            B.dbw_round(h, x, out, 0.0)
+            assert set(B.dbw_get_timing(h)) == {want}
+            assert torch.allclose(out[:, :257], x[:, :257], rtol=0, atol=1e-5)
+        finally:
+            B.dbw_destroy(h)
+
+
 # Worker counts at the edges of the four sizes of the kernel (32, 64, 128, 256 rows), columns at the edges of their
 # tiles (256, 128, 64 and 32 columns) and of a float4, fewer and more tiles than compute units, rows with and without
 # padding (the 4-byte loads).

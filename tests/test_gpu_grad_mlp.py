@@ -152,6 +152,13 @@ def test_grouped_weight_gradients_match_oracle(B, orc, dims, batch, n, loss_kind
     check_gradients(B, orc, dims, batch, n, loss_kind, grad_path=B.GRAD_LAYERS, expect={"mlp_wgrad_gemm"})
 
 
+def test_instruction_of_lone_data_gradients(B, orc):
+    """Next to the fp32 batch kernels' weight gradients: the fp32 instruction for short reductions, the split form for long
+    ones over many workgroups, and for rows off 16-byte boundaries."""
+    check_gradients(B, orc, [64, 132, 64, 8, 10], 260, 3, "xent", expect={"mlp_dgrad_gemm"})
+    check_gradients(B, orc, [16, 132, 324, 10], 260, 18, "xent", expect={"mlp_dgrad_split"})
+
+
 # Batches of at most 64 samples with widths that divide by 4: forward products and weight gradients straight from
 # global memory into matrix-instruction fragments.  One, two, three and four blocks of 16 samples; batches that
 # end inside a group of four samples; input widths with a partial chunk of 16 (100, 20) and below one chunk (12);
