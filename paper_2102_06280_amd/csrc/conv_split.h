@@ -14,9 +14,13 @@
 // codes need three moves inside a quad of lanes.
 //
 // What bounds it, at 64 workers x 32 samples, 32 -> 64 channels, 16 x 16 pixels (53.7 GFLOP, six times that in bf16):
-// forward 252 us = 1.28 PFLOP/s of bf16, about what this card sustains on this instruction with operands from LDS (a
+// forward 250 us = 1.29 PFLOP/s of bf16, about what this card sustains on this instruction with operands from LDS (a
 // register-resident loop reaches 1.87); the data gradient, with 32 output rows per wave, reads 9 KB of LDS per 12
-// matrix instructions and comes to 264.  The fp32 kernels they replace took 433 and 447 us (122 TFLOP/s).
+// matrix instructions and comes to 254.  The fp32 kernels they replace took 433 and 447 us (122 TFLOP/s).
+//
+// Where a sum is not finite, a workgroup (a wave of first_kernel) multiplies a second time: the small partial products, what is not
+// finite of them dropped, then the large ones.  With one infinite weight of conv2 in every one of those 64 workers a round takes
+// 2.04 ms and with nothing but NaN 2.2 (1.65 with finite values).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -384,6 +388,9 @@ inline bool first_plan(const Shape &s, int workers, FirstPlan &p)
         p.lds = 48 * ((size_t)first_image(s) + (size_t)first_steps(s) * 64);
     }
     const int64_t groups = (int64_t)((s.B + p.spg - 1) / p.spg) * workers;
+    // Several turns, for which the filters are split once, where the chip is full all the same.  One / two / four turns, us:
+    // 8 192 groups (128 workers x 64 samples, 3 x 3) 252, 251, 244; 4 000 (100 x 40, 5 x 5) 205, 197, 197; 2 048 108, 105, 102;
+    // 1 024 58, 56, 72.  Several samples to a group end less evenly (100 x 100 samples of 16 x 16, 2 500 groups: 106, 115, 146).
     p.iters = groups >= 4096 ? 4 : (groups >= 2048 ? 2 : 1);
     return p.lds <= 160 * 1024;
 }
@@ -604,6 +611,10 @@ inline bool wgrad_plan(const Shape &s, int workers, WgradPlan &p)
     p.mb = (s.Cout + 31) / 32;
     p.nb = (s.Cin * s.KS + 31) / 32;
     p.units = p.mb * p.nb;
+    // Eight wavefronts for few blocks: more of them hide the copies and splits, which a workgroup does between barriers, but
+    // their sums meet in LDS.  No number is the best everywhere (four / eight / twelve waves, us): 3 x 3, 32 -> 32 channels on
+    // 8 x 8 224, 188, 208, 16 -> 16 on 16 x 16 171, 158, 215; 5 x 5, 3 -> 32 on 32 x 32 with four blocks 89, 89, 73;
+    // one channel 5 x 5 on 28 x 28 48, 73, 88 (16 workers) and 279, 285, 296 (100).
     p.kw = p.units >= 5 ? 1 : 8 / p.units;
     p.groups = (p.units + WGRAD_MAX_WAVES - 1) / WGRAD_MAX_WAVES;
     p.waves = (p.units + p.groups - 1) / p.groups * p.kw;
@@ -625,7 +636,9 @@ inline bool wgrad_plan(const Shape &s, int workers, WgradPlan &p)
     p.lds = img + wgrad_delta_lds(s, p.mb, p.rows);
     const size_t sums = p.kw > 1 ? sizeof(float) * 64 * 16 * s.KS * (p.waves / p.kw) : 0;
     if (p.lds < sums) p.lds = sums;
-    // enough workgroups for the chip, and no more partial results than that needs
+    // enough workgroups for the chip, and no more partial results than that needs.  A workgroup of up to eight samples: with
+    // four 5 x 5, 32 -> 64 on 16 x 16 takes 267 us and 46 for the sums (255 and 43), 3 x 3 1 -> 8 channels 45 (40); with sixteen
+    // the last turn of workgroups is the emptier (16 -> 32 on 14 x 14 288 against 258, 32 -> 16 on 16 x 16 511 against 342)
     p.sb = (int)((int64_t)s.B * workers * p.groups / (256 * per_cu));
     p.sb = p.sb < 1 ? 1 : (p.sb > 8 ? 8 : p.sb);
     p.splits = (s.B + p.sb - 1) / p.sb;

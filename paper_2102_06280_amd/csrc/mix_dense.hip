@@ -357,7 +357,9 @@ int launch_mb(dbw_ctx *c, const float *W, const float *x, const float *g, float 
 {
     // Up to 64 workers two workgroups of four wavefronts per compute unit, with tiles of half the width, give shorter
     // vectors more even rounds of tiles; longer vectors want the longer pieces of a row (N = 60, four / eight waves:
-    // 134 154 columns 23.0 / 25.7 us, 600 000 93 / 96, 1.2 M 180 / 176, 4 M 600 / 555).
+    // 134 154 columns 23.0 / 25.7 us, 600 000 93 / 96, 1.2 M 180 / 176, 4 M 600 / 555).  The line, 24 tiles for each of 256
+    // workgroups, is 786 432 columns there and where N = 60 crosses; N = 40, with more padding, would rather have four waves to
+    // 1.5 M (114 / 119), and N = 24 off 16-byte boundaries, with tiles twice as wide, takes the same either way (1.5 M 82 / 78).
     if constexpr (MB <= 2)
         if (c->d <= 24 * 256 * (int64_t)mixsplit::Cfg<MB, 8>::TC) return launch_split<MB, 4, ORDER, HAS_G, WIDE, LR>(c, W, x, g, out, lr, s);
     return launch_split<MB, 8, ORDER, HAS_G, WIDE, LR>(c, W, x, g, out, lr, s);

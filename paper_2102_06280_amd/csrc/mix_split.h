@@ -1,4 +1,4 @@
-// X' = P X for more than 32 workers, or rows off 16-byte boundaries, fused with the local SGD step (see mix_dense.hip).
+// X' = P X for more than 32 workers, or more than 16 on rows off 16-byte boundaries, fused with the local SGD step (see mix_dense.hip).
 //
 // Every fp32 value is split into three bf16 values for the multiplies and the sums are fp32 (split_bf16.h has the errors).
 // P (N x N, zero-padded to NPAD = 32 * MB) is tiny and lives in registers: a wavefront keeps the three planes of its 32
