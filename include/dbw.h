@@ -27,8 +27,8 @@
  *
  * Precision.  Parameters, gradients and sums are fp32 throughout; sums come as close to the exact ones as those of fp32
  * multiply-adds (a convolution's sum that zeros leave a single term of: within 2^-23 of it).  Values of magnitude below
- * 2^-110 (8e-34) enter the dense average, the convolutions and the gradients of the fully connected layers to within 2^-133 each.  The zero border of a convolution is part of its sums (0 times an
- * infinite or NaN weight is NaN).
+ * 2^-110 (8e-34) enter the dense average, the convolutions and the gradients of the fully connected layers to within
+ * 2^-133 each.  The zero border of a convolution is part of its sums (0 times an infinite or NaN weight is NaN).
  *
  * Graph.  The communication graph G = (N, E) of Section 2.1 is given in CSR form
  * without self loops: the neighbours of worker i are colidx[rowptr[i] .. rowptr[i+1]),
