@@ -153,6 +153,8 @@ int fill_ctx(dbw_ctx *c, int32_t N, int64_t d, int64_t nnz64, const int32_t *row
     for (int i = 0; i < N; ++i) c->max_deg = std::max(c->max_deg, rowptr[i + 1] - rowptr[i]);
     if (!spanning_links(N, rowptr, colidx, c->h_links)) return DBW_ERR_GRAPH;
     const bool dense_fits = N <= DBW_DENSE_MAX_N && c->ld <= DBW_DENSE_MAX_LD;
+    c->may_average = c->order == DBW_ORDER_CTA && c->mix == DBW_MIX_AUTO && c->nnz <= DBW_AVERAGE_DEGREE * (int64_t)N &&
+                     c->d <= DBW_AVERAGE_MAX_D;
     if (c->mix == DBW_MIX_AUTO)
         c->mix = (dense_fits && (int64_t)c->nnz * 4 > (int64_t)N * N) ? DBW_MIX_DENSE : DBW_MIX_CSR;
     if (c->mix == DBW_MIX_DENSE && !dense_fits) return DBW_ERR_UNSUPPORTED;
@@ -372,7 +374,7 @@ int dbw_grad(dbw_ctx *c, const float *params, const float *batch_x, const int32_
 {
     if (!c || !params || !batch_x || !batch_y || !grads) return DBW_ERR_NULL;
     if (c->model.kind == DBW_MODEL_MLP)
-        return dbw_launch_grad_mlp(c, params, batch_x, batch_y, grads, loss_out, (hipStream_t)stream);
+        return dbw_launch_grad_mlp(c, params, batch_x, batch_y, grads, loss_out, average::Args{}, nullptr, nullptr, (hipStream_t)stream);
     if (c->model.kind == DBW_MODEL_CNN)
         return dbw_launch_grad_cnn(c, params, batch_x, batch_y, grads, loss_out, (hipStream_t)stream);
     return DBW_ERR_STATE;
@@ -389,8 +391,15 @@ static int round_impl(dbw_ctx *c, const float *params_in, float *params_out, con
     hipStream_t s = (hipStream_t)stream;
     const float *g = ext_grads;
     if (c->model.kind != DBW_MODEL_NONE) {
-        const int rc = dbw_grad(c, params_in, batch_x, batch_y, c->grads, loss_out, stream);
-        if (rc != DBW_OK) return rc;
+        bool averaged = false;
+        int rc;
+        if (c->model.kind == DBW_MODEL_MLP && c->may_average && batch_x && batch_y) {
+            const average::Args avg{params_in, c->ld, c->rowptr, c->p, c->sel_idx, c->sel_w, c->self_w, lr_vec, lr};
+            rc = dbw_launch_grad_mlp(c, params_in, batch_x, batch_y, c->grads, loss_out, avg, params_out, &averaged, s);
+        } else {
+            rc = dbw_grad(c, params_in, batch_x, batch_y, c->grads, loss_out, stream);
+        }
+        if (rc != DBW_OK || averaged) return rc;
         g = c->grads;
     } else if (g && overlaps(g, bytes, params_out, bytes)) {
         return DBW_ERR_ALIAS;

@@ -1,0 +1,134 @@
+// The consensus average on a gradient's way to memory (Section 2.1, average first):
+//   out_i = P_ii x_i + sum over selected j of P_ij x_j - lr_i g_i
+// A worker's new parameters need its own gradient only, so the kernel that has computed one can finish the element, instead of writing
+// it for a pass over all parameters that reads it back.  Same terms in the same order as mix_csr.hip: the results are those of
+// a gradient pass and an averaging pass, bit for bit.
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+namespace average {
+
+// x null: gradients are stored as they are
+struct Args {
+    const float *x;                  // the parameters the gradients were taken at [workers][ld]
+    int64_t ld;
+    const int32_t *rowptr, *p, *sel_idx;
+    const float *sel_w, *self_w;
+    const float *lr_vec;             // a rate per worker, or null
+    float lr;
+};
+
+// The selected neighbours of one worker, to be fetched well before use: the first NEAR of them, the same in every lane (in scalar
+// registers).  Not one per lane: a lane that takes no part in a branch may lose what it holds to the other side of the branch.
+constexpr int NEAR = 8;
+struct Row {
+    int beg, cnt, idx[NEAR];
+    float wt[NEAR], self, eta;
+};
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ float uniform(float v) { return __builtin_bit_cast(float, uniform(__builtin_bit_cast(int, v))); }
+__device__ __forceinline__ Row row(const Args &a, int w)
+{
+    Row r{};
+    if (a.x) {
+        r.beg = uniform(a.rowptr[w]);
+        r.cnt = uniform(a.p[w]);
+#pragma unroll
+        for (int k = 0; k < NEAR; ++k) {
+            const int at = k < r.cnt ? r.beg + k : 0;
+            r.idx[k] = uniform(a.sel_idx[at]);
+            r.wt[k] = uniform(a.sel_w[at]);
+        }
+        r.self = uniform(a.self_w[w]);
+        r.eta = uniform(a.lr_vec ? a.lr_vec[w] : a.lr);
+    }
+    return r;
+}
+
+// V: float or a vector of floats with the alignment of the accesses
+template <class V>
+struct lanes {
+    static constexpr int n = sizeof(V) / sizeof(float);
+};
+template <class V>
+__device__ __forceinline__ V fma(float w, V x, V acc)
+{
+    if constexpr (lanes<V>::n == 1) {
+        return fmaf(w, x, acc);
+    } else {
+#pragma unroll
+        for (int e = 0; e < lanes<V>::n; ++e) acc[e] = fmaf(w, x[e], acc[e]);
+        return acc;
+    }
+}
+
+// acc[n] = P_ii x_i + sum over j of P_ij x_j at `base` (uniform) + off[n] (bytes) of the rows of worker i = w and its neighbours, which
+// waits for no gradient.  w is the same for a wavefront; a lane without an element gives any offset of the row.  The elements
+// of several neighbours are fetched at a time (behind the last of them: its own once more).
+template <class V, int N>
+__device__ __forceinline__ void gather(const Args &a, const Row &r, int w, int64_t base, const uint32_t (&off)[N], V (&acc)[N])
+{
+    constexpr int U = N * lanes<V>::n >= 16 ? 2 : 4;
+    auto load = [&](int j, V (&v)[N]) {
+        const char *row = (const char *)(a.x + (int64_t)j * a.ld + base);
+#pragma unroll
+        for (int n = 0; n < N; ++n) v[n] = *(const V *)(row + off[n]);
+    };
+    auto add = [&](float wt, const V (&v)[N]) {
+#pragma unroll
+        for (int n = 0; n < N; ++n) acc[n] = fma<V>(wt, v[n], acc[n]);
+    };
+    load(w, acc);
+#pragma unroll
+    for (int k = 0; k < NEAR; k += U) {
+        if (k > 0 && k >= r.cnt) break;
+        V v[U][N];
+#pragma unroll
+        for (int u = 0; u < U; ++u) load(k + u < r.cnt ? r.idx[k + u] : w, v[u]);
+        if (k == 0) {
+#pragma unroll
+            for (int n = 0; n < N; ++n) acc[n] = r.self * acc[n];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (k + u < r.cnt) add(r.wt[k + u], v[u]);
+    }
+    for (int k = NEAR; k < r.cnt; k += U) {
+        V v[U][N];
+        float wt[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int at = r.beg + min(k + u, r.cnt - 1);
+            wt[u] = uniform(a.sel_w[at]);
+            load(uniform(a.sel_idx[at]), v[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (k + u < r.cnt) add(wt[u], v[u]);
+    }
+}
+
+// g[n], gradients of worker w there -> the new parameters.
+template <class V, int N>
+__device__ __forceinline__ void apply(const Args &a, const Row &r, int w, int64_t base, const uint32_t (&off)[N], V (&g)[N])
+{
+    V acc[N];
+    gather<V, N>(a, r, w, base, off, acc);
+#pragma unroll
+    for (int n = 0; n < N; ++n) g[n] = fma<V>(-r.eta, g[n], acc[n]);
+}
+
+// One gradient of a lane, to `out` (the worker's row).
+__device__ __forceinline__ void store(const Args &a, const Row &r, int w, float *out, int64_t at, float g)
+{
+    float v[1] = {g};
+    if (a.x) {
+        const uint32_t off[1] = {(uint32_t)(4 * at)};
+        apply<float, 1>(a, r, w, 0, off, v);
+    }
+    out[at] = v[0];
+}
+
+}  // namespace average

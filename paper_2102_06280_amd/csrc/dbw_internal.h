@@ -7,6 +7,7 @@
 #include <string>
 #include <vector>
 
+#include "average.h"
 #include "dbw.h"
 #include "dbw_measure.h"
 
@@ -29,6 +30,14 @@ constexpr int DBW_TILES_MAX_N = 256;   // the tile-major mixing kernel holds one
 constexpr int DBW_TAIL_LINKS = 4096;
 constexpr int DBW_TAIL_ROUNDS = 16;
 
+// The kernels that store a fully connected model's gradients form the average themselves (average.h) up to this many neighbours per
+// worker, on average, and rows whose byte offsets fit 32 bits.  A neighbour's row is then read once per reader, from the L2 or
+// the last-level cache, instead of staying in LDS.  Rounds, us, with a pass of its own / on the way: 32 workers, 784-200-10, batch 64,
+// with 4, 8 and 31 neighbours 54.2 / 46.7, 54.7 / 52.0 and 54.9 / 76.5; 48 workers, 300-92-10, batch 32, 8 neighbours 28.6 /
+// 30.1; 64 workers, 784-512-512-10, batch 256, 6 neighbours 799 / 783; 24 workers, 784-10, batch 32, 23 neighbours 23.5 / 42.3.
+constexpr int DBW_AVERAGE_DEGREE = 6;
+constexpr int64_t DBW_AVERAGE_MAX_D = (int64_t)1 << 29;
+
 struct dbw_timing_slot {
     const char *name;
     hipEvent_t start, stop;
@@ -44,6 +53,7 @@ struct dbw_ctx {
     int32_t Npad = 0;                 // N rounded up to a power of two >= 32 (dense path)
     dbw_model model{};
     int64_t in_dim = 0;               // floats per sample
+    bool may_average = false;         // the kernels that store a round's gradients may form the average on the way
     bool selected = false;
 
     std::vector<int32_t> h_rowptr, h_colidx, h_links;
@@ -153,14 +163,20 @@ struct dbw_fc_args {
     const int32_t *y;
     float *loss;
     int grad_path;          // DBW_GRAD_*
+    // A round's average, if the kernels that store the gradients may form it on the way (average.h); then out is where the
+    // new parameters go, and averaged tells the caller whether that has happened (otherwise `grads` has the gradients).
+    average::Args avg;
+    float *out;
+    bool averaged;
 };
 int64_t dbw_fc_scratch_per_worker(int L, const int32_t *dims, int B);
 bool dbw_fc_chain_shape_ok(int L, const int32_t *dims, int B, int workers);   // DBW_GRAD_CHAIN can take this model
 int dbw_fc_prepare();   // one-time kernel attributes of the fully connected path
-int dbw_fc_forward_backward(dbw_ctx *c, const dbw_fc_args &a, hipStream_t s);
+int dbw_fc_forward_backward(dbw_ctx *c, dbw_fc_args &a, hipStream_t s);
 size_t dbw_mlp_scratch_floats(const dbw_ctx *c);
+// out, if not null: averages on the way to there where that is faster, and says so in *averaged (see dbw_fc_args).
 int dbw_launch_grad_mlp(dbw_ctx *c, const float *params, const float *bx, const int32_t *by, float *grads,
-                        float *loss, hipStream_t s);
+                        float *loss, const average::Args &avg, float *out, bool *averaged, hipStream_t s);
 int dbw_cnn_prepare();  // one-time kernel attributes of the convolutions
 size_t dbw_cnn_scratch_floats(const dbw_ctx *c);
 int dbw_launch_grad_cnn(dbw_ctx *c, const float *params, const float *bx, const int32_t *by, float *grads,

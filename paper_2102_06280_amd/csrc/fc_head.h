@@ -24,6 +24,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "average.h"
 #include "dbw.h"
 
 namespace fchead {
@@ -81,6 +82,7 @@ struct Args {
     float *part;                     // [workers][part_stride] scratch for the per-chunk partial sums
     int64_t part_stride;
     int32_t *err;                    // deferred status word
+    average::Args avg;               // what goes to grads: gradients, or new parameters
 };
 
 // Row pitch of the LDS images of a and W: H rounded up to 4 (the k-step of the matrix instruction;
@@ -187,7 +189,8 @@ __device__ __forceinline__ Early fetch_early(const Args &g, int w, int s0, int n
 // floats behind the image zero), Wl the image stage_w makes.  S is a multiple of 16 up to MAX_S.  With da_to_lds the
 // (masked) input gradient replaces the input in al instead of going to g.da.  All THREADS threads call this after a
 // barrier that makes al and Wl visible.
-template <int LOSS>
+// MIX: g.avg is there and the sums over the batch are final (one chunk).
+template <int LOSS, bool MIX = false>
 __device__ __forceinline__ void body(const Args &g, float *zl, float *zp, float *Wl, float *al, int S, int w, int chunk,
                                      int chunks, bool da_to_lds, const Early &early)
 {
@@ -196,6 +199,8 @@ __device__ __forceinline__ void body(const Args &g, float *zl, float *zp, float 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);       // on the scalar unit: loops and branches on it are uniform
     const int l16 = lane & 15, lq = lane >> 4;
     const int s0 = chunk * S, ns = min(S, g.B - s0);
+    average::Row nb{};
+    if constexpr (MIX) nb = average::row(g.avg, w);
 
     // ---- logits z = a W^T: wavefront = (16-sample block, slice of k); partial sums meet in LDS.
     // A lane reads four consecutive k of its row with one 128-bit LDS read; lane group q of both operands then
@@ -322,12 +327,22 @@ __device__ __forceinline__ void body(const Args &g, float *zl, float *zp, float 
                         acc[p][u & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(zv[u], av[p][u], acc[p][u & 1], 0, 0, 0);
             }
 #pragma unroll
-            for (int p = 0; p < 2; ++p)
+            for (int p = 0; p < 2; ++p) {
+                float dw[4];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) dw[v] = acc[p][0][v] + acc[p][1][v];
+                if (MIX && (p == 0 || two)) {
+                    uint32_t off[4];
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) off[v] = 4u * (uint32_t)(min(4 * lq + v, C - 1) * H + min(col[p], H - 1));
+                    average::apply<float, 4>(g.avg, nb, w, g.w_off, off, dw);
+                }
                 if (col[p] < H && (p == 0 || two)) {
 #pragma unroll
                     for (int v = 0; v < 4; ++v)
-                        if (4 * lq + v < C) out_w[(4 * lq + v) * H + col[p]] = acc[p][0][v] + acc[p][1][v];
+                        if (4 * lq + v < C) out_w[(4 * lq + v) * H + col[p]] = dw[v];
                 }
+            }
         }
         // ---- da[sample][col] = sum over classes of dz[sample][class] W[class][col], masked; its column sums.
         // Lane group q carries the classes 4 q + j in instruction j: one 128-bit read of dz per 16 samples.
@@ -368,14 +383,18 @@ __device__ __forceinline__ void body(const Args &g, float *zl, float *zp, float 
             for (int p = 0; p < 2; ++p) {
                 colsum[p] += __shfl_xor(colsum[p], 16, 64);
                 colsum[p] += __shfl_xor(colsum[p], 32, 64);
-                if (out_bprev && lq == 0 && col[p] < H && (p == 0 || two)) out_bprev[col[p]] = colsum[p];
+                if (out_bprev && lq == 0 && col[p] < H && (p == 0 || two)) {
+                    if (MIX) average::store(g.avg, nb, w, g.grads + w * g.p_stride, g.bprev_off + col[p], colsum[p]);
+                    else out_bprev[col[p]] = colsum[p];
+                }
             }
         }
     }
     if (tid < C) {
         float sum = 0.f;
         for (int s = 0; s < ns; ++s) sum += zl[s * MAX_C + tid];
-        out_b[tid] = sum;
+        if (MIX) average::store(g.avg, nb, w, g.grads + w * g.p_stride, g.b_off + tid, sum);
+        else out_b[tid] = sum;
     }
     // ---- the chunk's loss: its samples in a fixed order (tree in LDS)
     if (g.loss) {
@@ -411,7 +430,7 @@ __device__ __forceinline__ float4 split_sum(const float *src, int64_t plane, int
 
 // VEC: the input rows start on 16-byte boundaries and H divides by 4 (128-bit staging loads).
 // SPLIT: the input arrives as split-k partial sums (Args::splits).
-template <int LOSS, bool VEC, bool SPLIT = false>
+template <int LOSS, bool VEC, bool SPLIT = false, bool MIX = false>
 __global__ __launch_bounds__(THREADS) void kernel(Args g)
 {
     extern __shared__ __attribute__((aligned(16))) float sm[];
@@ -487,7 +506,7 @@ __global__ __launch_bounds__(THREADS) void kernel(Args g)
     if (tid < 16) al[S * HP + tid] = 0.f;
     __syncthreads();
 
-    body<LOSS>(g, zl, zp, Wl, al, S, w, chunk, chunks, false, early);
+    body<LOSS, MIX>(g, zl, zp, Wl, al, S, w, chunk, chunks, false, early);
 }
 
 // Sum of the per-chunk partials in chunk order -> dW, db, the bias gradient below, the loss.
@@ -498,6 +517,7 @@ __device__ __forceinline__ void reduce_body(const Args &g, int chunks, int bx, i
     const int n_w = C * H, n_b = C, n_p = g.bprev_off >= 0 ? H : 0;
     const int64_t E = partial_floats(H, C, g.bprev_off >= 0);
     const int e = bx * 256 + threadIdx.x;
+    average::Row nb = average::row(g.avg, w);
     if (e >= E || (e == E - 1 && !g.loss)) return;
     const float *__restrict__ all = g.part + w * g.part_stride;
     float *__restrict__ gw = g.grads + w * g.p_stride;
@@ -509,9 +529,8 @@ __device__ __forceinline__ void reduce_body(const Args &g, int chunks, int bx, i
 #pragma unroll
         for (int u = 0; u < 16; ++u) sum += v[u];
     }
-    if (e < n_w) gw[g.w_off + e] = sum;
-    else if (e < n_w + n_b) gw[g.b_off + (e - n_w)] = sum;
-    else if (e < n_w + n_b + n_p) gw[g.bprev_off + (e - n_w - n_b)] = sum;
+    const int64_t at = e < n_w ? g.w_off + e : (e < n_w + n_b ? g.b_off + (e - n_w) : g.bprev_off + (e - n_w - n_b));
+    if (e < n_w + n_b + n_p) average::store(g.avg, nb, w, gw, at, sum);
     else g.loss[w] = sum / (float)g.B;
 }
 

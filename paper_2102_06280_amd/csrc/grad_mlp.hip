@@ -260,7 +260,8 @@ int launch_grouped_wgrad(dbw_ctx *c, const dbw_fc_args &a, const WgradPlan &wp, 
     }
     q.w_off[wp.layers + 1] = wp.w_end;
     q.dz = a.act; q.dz_stride = wstride;
-    q.grads = a.grads; q.g_stride = c->ld;
+    q.grads = a.averaged ? a.out : a.grads; q.g_stride = c->ld;
+    if (a.averaged) q.avg = a.avg;
     q.part = a.act + 2 * wp.per; q.part_stride = wstride;
     const int64_t len = wp.w_end - wp.w_off[1];
     int splits = (int)std::min<int64_t>(8, std::max<int64_t>(1, 512 / ((int64_t)tiles * N)));
@@ -320,7 +321,7 @@ bool dbw_fc_chain_shape_ok(int L, const int32_t *dims, int B, int workers)
 }
 
 // Forward and backward pass of a stack of fully connected layers for all workers.
-int dbw_fc_forward_backward(dbw_ctx *c, const dbw_fc_args &a, hipStream_t s)
+int dbw_fc_forward_backward(dbw_ctx *c, dbw_fc_args &a, hipStream_t s)
 {
     const int L = a.L, B = a.B, N = c->N;
     const int32_t *dims = a.dims;
@@ -463,6 +464,8 @@ int dbw_fc_forward_backward(dbw_ctx *c, const dbw_fc_args &a, hipStream_t s)
     for (int l = 0; l <= Lw && grouped; ++l) grouped = dims[l] % 4 == 0;
     for (int l = 1; l <= Lw && grouped; ++l)
         grouped = !batch32_layer(B, dims[l - 1], dims[l], c->ld, w_off[l], params, grads);
+    // The average on the way, where the head and one grouped launch store all gradients
+    a.averaged = a.out && head.use && ((chain.use && chain.chunks > 1) || grouped || L == 1) && (L == 1 || (fc32::aligned16(a.out) && fc32::aligned16(params)));
     // A short batch is one chunk of the head per worker, so that its sums over the batch are final.  When the grouped
     // launch follows, which adds per-chunk sums on the side, smaller chunks cost nothing and put the head on more CUs
     // (784-200-10, 64 samples, 32 workers: 16.1 -> 10.9 us with four chunks of 16).
@@ -497,6 +500,10 @@ int dbw_fc_forward_backward(dbw_ctx *c, const dbw_fc_args &a, hipStream_t s)
         h.y = a.y; h.loss = a.loss;
         h.part = act + 2 * per + (split_floats + 3) / 4 * 4; h.part_stride = wstride;
         h.err = c->err;
+        if (a.averaged) {
+            h.avg = a.avg;
+            h.grads = a.out;
+        }
         if (chain.use) {
             mlpchain::Args g{};
             g.B = B; g.L = L; g.K0 = dims[0]; g.H = dims[1]; g.C = dims[L];
@@ -552,7 +559,13 @@ int dbw_fc_forward_backward(dbw_ctx *c, const dbw_fc_args &a, hipStream_t s)
             return DBW_OK;
         };
         int rc;
-        if (head_splits > 0) rc = mse ? go(fchead::kernel<DBW_LOSS_MSE, true, true>) : go(fchead::kernel<DBW_LOSS_XENT, true, true>);
+        if (a.averaged && head.chunks == 1 && head_splits > 0)
+            rc = mse ? go(fchead::kernel<DBW_LOSS_MSE, true, true, true>) : go(fchead::kernel<DBW_LOSS_XENT, true, true, true>);
+        else if (a.averaged && head.chunks == 1 && vec)
+            rc = mse ? go(fchead::kernel<DBW_LOSS_MSE, true, false, true>) : go(fchead::kernel<DBW_LOSS_XENT, true, false, true>);
+        else if (a.averaged && head.chunks == 1)
+            rc = mse ? go(fchead::kernel<DBW_LOSS_MSE, false, false, true>) : go(fchead::kernel<DBW_LOSS_XENT, false, false, true>);
+        else if (head_splits > 0) rc = mse ? go(fchead::kernel<DBW_LOSS_MSE, true, true>) : go(fchead::kernel<DBW_LOSS_XENT, true, true>);
         else if (mse) rc = vec ? go(fchead::kernel<DBW_LOSS_MSE, true>) : go(fchead::kernel<DBW_LOSS_MSE, false>);
         else rc = vec ? go(fchead::kernel<DBW_LOSS_XENT, true>) : go(fchead::kernel<DBW_LOSS_XENT, false>);
         if (rc != DBW_OK) return rc;
@@ -685,6 +698,12 @@ int dbw_fc_prepare()
                              (const void *)fchead::kernel<DBW_LOSS_XENT, false>,
                              (const void *)fchead::kernel<DBW_LOSS_MSE, true, true>,
                              (const void *)fchead::kernel<DBW_LOSS_XENT, true, true>,
+                             (const void *)fchead::kernel<DBW_LOSS_MSE, true, false, true>,
+                             (const void *)fchead::kernel<DBW_LOSS_MSE, false, false, true>,
+                             (const void *)fchead::kernel<DBW_LOSS_XENT, true, false, true>,
+                             (const void *)fchead::kernel<DBW_LOSS_XENT, false, false, true>,
+                             (const void *)fchead::kernel<DBW_LOSS_MSE, true, true, true>,
+                             (const void *)fchead::kernel<DBW_LOSS_XENT, true, true, true>,
                              (const void *)mlpchain::kernel<1, 1>, (const void *)mlpchain::kernel<1, 2>,
                              (const void *)mlpchain::kernel<1, 4>, (const void *)mlpchain::kernel<2, 1>,
                              (const void *)mlpchain::kernel<2, 2>, (const void *)mlpchain::kernel<2, 4>,
@@ -703,7 +722,7 @@ size_t dbw_mlp_scratch_floats(const dbw_ctx *c)
 }
 
 int dbw_launch_grad_mlp(dbw_ctx *c, const float *params, const float *bx, const int32_t *by, float *grads,
-                        float *loss, hipStream_t s)
+                        float *loss, const average::Args &avg, float *out, bool *averaged, hipStream_t s)
 {
     const dbw_model &m = c->model;
     dbw_fc_args a{};
@@ -722,5 +741,9 @@ int dbw_launch_grad_mlp(dbw_ctx *c, const float *params, const float *bx, const 
     a.y = by;
     a.loss = loss;
     a.grad_path = m.grad_path;
-    return dbw_fc_forward_backward(c, a, s);
+    a.avg = avg;
+    a.out = out;
+    const int rc = dbw_fc_forward_backward(c, a, s);
+    if (averaged) *averaged = a.averaged;
+    return rc;
 }

@@ -195,7 +195,9 @@ __global__ __launch_bounds__(mlpwgrad::THREADS) void wgrad_kernel(mlpwgrad::Args
     if (id >= tile_wgs) return;
     const int wt = id * WAVES + wave;
     if (wt >= wave_tiles) return;                               // no barrier below
-    const int bx = wt % tiles, w = wt / tiles;
+    // (with the average on the way: the workers of a tile next to each other, see mlp_wgrad.h)
+    const bool mix = g.avg.x != nullptr;
+    const int bx = mix ? wt / g.workers : wt % tiles, w = mix ? wt % g.workers : wt / tiles;
     int l = 1;
     while (l < g.layers && bx >= pick(g.tile_begin, l + 1)) ++l;
     const int N = pick(g.n_cols, l), H = pick(g.n_rows, l), ntn = (N + TN - 1) / TN;
@@ -209,6 +211,8 @@ __global__ __launch_bounds__(mlpwgrad::THREADS) void wgrad_kernel(mlpwgrad::Args
 
     // group u = samples 4 u .. 4 u + 3, lane group lq takes sample 4 u + lq; a sample beyond the batch: a valid
     // row, zeroed (every load unconditional: loads under a condition each cost a register move per element)
+    average::Row nb{};
+    if (mix) nb = average::row(g.avg, w);
     vec2 x[GROUPS];
     f32x4 y[GROUPS];
 #pragma unroll
@@ -244,22 +248,37 @@ __global__ __launch_bounds__(mlpwgrad::THREADS) void wgrad_kernel(mlpwgrad::Args
     // register r of (i, j), lane (l16, lq): tile row 2 (4 lq + r) + i, tile column 4 l16 + j
     float *__restrict__ out = g.grads + w * g.g_stride + pick(g.w_off, l);
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < 2; ++i) {
+        f32x4 v[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = f32x4{acc[i][0][r], acc[i][1][r], acc[i][2][r], acc[i][3][r]};
+        if (mix) {
+            uint32_t off[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) off[r] = 4u * (uint32_t)(min(m0 + 2 * (4 * lq + r) + i, H - 1) * N + (cols_ok ? n0 + 4 * l16 : 0));
+            average::apply<f32x4, 4>(g.avg, nb, w, pick(g.w_off, l), off, v);
+        }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int row = 2 * (4 * lq + r) + i;
-            const f32x4 v = {acc[i][0][r], acc[i][1][r], acc[i][2][r], acc[i][3][r]};
-            if (cols_ok && m0 + row < H) *(f32x4 *)(out + (int64_t)(m0 + row) * N + n0 + 4 * l16) = v;
+            if (cols_ok && m0 + row < H) *(f32x4 *)(out + (int64_t)(m0 + row) * N + n0 + 4 * l16) = v[r];
         }
+    }
     if (bias) {
-        vec2 v;
+        vec2 v[1];
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             dsum[i] += __shfl_xor(dsum[i], 16, 64);
             dsum[i] += __shfl_xor(dsum[i], 32, 64);
-            v.v[i] = dsum[i];
+            v[0].v[i] = dsum[i];
         }
-        if (lq == 0 && rows_ok) *(vec2 *)(out + (int64_t)H * N + m0 + 2 * l16) = v;
+        if (lq == 0 && rows_ok) {
+            if (mix) {
+                const uint32_t off[1] = {4u * (uint32_t)(H * N + m0 + 2 * l16)};
+                average::apply<vec2, 1>(g.avg, nb, w, pick(g.w_off, l), off, v);
+            }
+            *(vec2 *)(out + (int64_t)H * N + m0 + 2 * l16) = v[0];
+        }
     }
 }
 

@@ -13,7 +13,7 @@
 // feed four different tiles: tile row i of row block e is output m0 + 4 i + e.  One load of dz
 // and one of a per four samples give a wavefront the 16 products of its 64 x 64 output tile; no LDS
 // on the way in.  The four wavefronts of a workgroup share the tile and take every fourth group of
-// four samples; their accumulators meet in LDS and are added in wavefront order.  Long batches
+// four samples; their accumulators meet in LDS and are added in wavefront order, a quarter of the tile by each.  Long batches
 // are also split over workgroups (blockIdx.z); the partial tiles then go to scratch in the very
 // layout of the parameter row (W_1 b_1 W_2 b_2 ...), and reduce_kernel adds them in split order.
 #pragma once
@@ -35,7 +35,17 @@ constexpr int PF = 8;                 // groups of four samples a wavefront keep
 template <int N>
 struct alignas(4 * N) Vec {
     float v[N];
+    __device__ __forceinline__ float &operator[](int i) { return v[i]; }
+    __device__ __forceinline__ float operator[](int i) const { return v[i]; }
 };
+template <int N>
+__device__ __forceinline__ Vec<N> operator*(float s, const Vec<N> &a)
+{
+    Vec<N> r;
+#pragma unroll
+    for (int i = 0; i < N; ++i) r.v[i] = s * a.v[i];
+    return r;
+}
 
 struct Args {
     int B, layers, workers;                  // batch; l = 1 .. layers
@@ -52,6 +62,7 @@ struct Args {
     float *part;                             // [worker][split][w_off[layers + 1] - w_off[1]] when splits > 1
     int64_t part_stride;
     int splits, kper;                        // samples per split, a multiple of 4
+    average::Args avg;                       // what goes to grads: gradients, or new parameters
 };
 
 // grid = (head_blocks x workers) + (tiles of all layers x workers x splits), each rounded up to a multiple of XCDS.
@@ -67,7 +78,7 @@ __global__ __launch_bounds__(THREADS, 2) void kernel(Args g, fchead::Args h, int
 {
     constexpr int TN = 16 * CBK, TP = TN + 4;
     typedef Vec<CBK> vec;
-    __shared__ __attribute__((aligned(16))) float red[WAVES - 1][64 * TP];
+    __shared__ __attribute__((aligned(16))) float red[WAVES][64 * TP];
     __shared__ __attribute__((aligned(16))) float bred[WAVES][64];
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lq = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);       // on the scalar unit: the loops below branch on it
@@ -81,7 +92,10 @@ __global__ __launch_bounds__(THREADS, 2) void kernel(Args g, fchead::Args h, int
     }
     const int b = blockIdx.x - head_grid, per = (gridDim.x - head_grid) / XCDS, id = (b % XCDS) * per + b / XCDS;
     if (id >= tile_wgs) return;
-    const int bx = id % tiles, w = (id / tiles) % g.workers, split = id / (tiles * g.workers);
+    // With the average on the way the workers of a tile run next to each other, on one XCD, whose L2 then holds the
+    // rows that they read of one another.
+    const bool mix = g.avg.x != nullptr && g.splits == 1;
+    const int q = id / g.workers, bx = mix ? q : id % tiles, w = mix ? id - q * g.workers : (id / tiles) % g.workers, split = mix ? 0 : id / (tiles * g.workers);
     int l = 1;
     while (l < g.layers && bx >= pick(g.tile_begin, l + 1)) ++l;
     const int N = pick(g.n_cols, l), H = pick(g.n_rows, l), ntn = (N + TN - 1) / TN;
@@ -96,6 +110,8 @@ __global__ __launch_bounds__(THREADS, 2) void kernel(Args g, fchead::Args h, int
     const float *__restrict__ av = pick(g.a, l) + w * pick(g.a_stride, l) + ncol;
     const int64_t a_ld = pick(g.a_ld, l);
 
+    average::Row nb{};
+    if (mix) nb = average::row(g.avg, w);
     f32x4 acc[4][CBK];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
@@ -173,10 +189,10 @@ __global__ __launch_bounds__(THREADS, 2) void kernel(Args g, fchead::Args h, int
         multiply(x, y);
     }
 
-    // ---- the four wavefronts' tiles: 1, 2, 3 through LDS, added to wavefront 0's in that order.
+    // ---- the four wavefronts' tiles meet in LDS; each adds up (in wavefront order) and stores the rows 4 (4 lq + r) + wave.
     // Register r of row block i, lane (l16, lq): output row 4 (4 lq + r) + i, columns CBK l16 .. CBK l16 + CBK - 1.
-    if (wave > 0) {
-        float *mine_t = red[wave - 1];
+    {
+        float *mine_t = red[wave];
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -200,28 +216,38 @@ __global__ __launch_bounds__(THREADS, 2) void kernel(Args g, fchead::Args h, int
     float *__restrict__ out = g.splits == 1 ? g.grads + w * g.g_stride + pick(g.w_off, l)
                                             : g.part + w * g.part_stride +
                                                   (int64_t)split * (pick(g.w_off, g.layers + 1) - pick(g.w_off, 1)) + (pick(g.w_off, l) - pick(g.w_off, 1));
-    if (wave == 0) {
+    vec v[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+    for (int r = 0; r < 4; ++r) {
+        const int row = 4 * (4 * lq + r) + wave;
+        v[r] = *(const vec *)&red[0][row * TP + CBK * l16];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int row = 4 * (4 * lq + r) + i;
-                vec v;
+        for (int q = 1; q < WAVES; ++q) {
+            const vec o = *(const vec *)&red[q][row * TP + CBK * l16];
 #pragma unroll
-                for (int j = 0; j < CBK; ++j) v.v[j] = acc[i][j][r];
+            for (int j = 0; j < CBK; ++j) v[r].v[j] += o.v[j];
+        }
+    }
+    if (mix) {
+        uint32_t off[4];
 #pragma unroll
-                for (int q = 0; q < WAVES - 1; ++q) {
-                    const vec o = *(const vec *)&red[q][row * TP + CBK * l16];
+        for (int r = 0; r < 4; ++r) off[r] = 4u * (uint32_t)(min(m0 + 4 * (4 * lq + r) + wave, H - 1) * N + ncol);
+        average::apply<vec, 4>(g.avg, nb, w, pick(g.w_off, l), off, v);
+    }
 #pragma unroll
-                    for (int j = 0; j < CBK; ++j) v.v[j] += o.v[j];
-                }
-                if (cols_ok && m0 + row < H) *(vec *)(out + (int64_t)(m0 + row) * N + n0 + CBK * l16) = v;
-            }
-    } else if (wave == 1 && bias && lane < 16 && m0 + 4 * lane < H) {
-        f32x4 v = *(const f32x4 *)&bred[0][4 * lane];
+    for (int r = 0; r < 4; ++r) {
+        const int row = 4 * (4 * lq + r) + wave;
+        if (cols_ok && m0 + row < H) *(vec *)(out + (int64_t)(m0 + row) * N + n0 + CBK * l16) = v[r];
+    }
+    if (wave == 1 && bias && lane < 16 && m0 + 4 * lane < H) {
+        f32x4 b[1] = {*(const f32x4 *)&bred[0][4 * lane]};
 #pragma unroll
-        for (int q = 1; q < WAVES; ++q) v += *(const f32x4 *)&bred[q][4 * lane];
-        *(f32x4 *)(out + (int64_t)H * N + m0 + 4 * lane) = v;
+        for (int q = 1; q < WAVES; ++q) b[0] += *(const f32x4 *)&bred[q][4 * lane];
+        if (mix) {
+            const uint32_t off[1] = {4u * (uint32_t)(H * N + m0 + 4 * lane)};
+            average::apply<f32x4, 1>(g.avg, nb, w, pick(g.w_off, l), off, b);
+        }
+        *(f32x4 *)(out + (int64_t)H * N + m0 + 4 * lane) = b[0];
     }
 }
 
@@ -231,6 +257,7 @@ __device__ __forceinline__ void reduce_body(const Args &g, int bx, int w)
 {
     const int64_t len = pick(g.w_off, g.layers + 1) - pick(g.w_off, 1);
     const int64_t e = 4 * ((int64_t)bx * 256 + threadIdx.x);
+    average::Row nb = average::row(g.avg, w);
     if (e >= len) return;
     const float *__restrict__ p = g.part + w * g.part_stride + e;
     // all loads in flight; a slot beyond the splits re-reads the last one and adds zero (loads under a condition
@@ -245,7 +272,8 @@ __device__ __forceinline__ void reduce_body(const Args &g, int bx, int w)
         for (int q = 0; q < NQ; ++q) t += q < g.splits ? v[q] : f32x4{0.f, 0.f, 0.f, 0.f};
         return t;
     };
-    const f32x4 sum = g.splits <= 2 ? add(std::integral_constant<int, 2>{})
+    f32x4 sum[1];
+    sum[0] = g.splits <= 2 ? add(std::integral_constant<int, 2>{})
                                     : (g.splits <= 4 ? add(std::integral_constant<int, 4>{}) : add(std::integral_constant<int, 8>{}));
     // a group of four lies inside one W_l or one b_l: every boundary is a multiple of 4
     const int64_t pos = pick(g.w_off, 1) + e;
@@ -254,7 +282,12 @@ __device__ __forceinline__ void reduce_body(const Args &g, int bx, int w)
     for (int l = 1; l <= MAX_L; ++l)
         if (l <= g.layers && !pick(g.want_db, l) && pos >= pick(g.w_off, l) + (int64_t)pick(g.n_rows, l) * pick(g.n_cols, l) && pos < pick(g.w_off, l + 1))
             keep = false;
-    if (keep) *(f32x4 *)(g.grads + w * g.g_stride + pos) = sum;
+    if (!keep) return;
+    if (g.avg.x) {
+        const uint32_t off[1] = {(uint32_t)(4 * pos)};
+        average::apply<f32x4, 1>(g.avg, nb, w, 0, off, sum);
+    }
+    *(f32x4 *)(g.grads + w * g.g_stride + pos) = sum[0];
 }
 
 // grid = (ceil(length / 4 / 256), workers)

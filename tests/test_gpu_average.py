@@ -1,0 +1,73 @@
+"""Rounds whose gradient kernels form the average on the way (average first, few neighbours): the same bits as a gradient pass and
+the sparse averaging kernels, which add the same terms in the same order."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2102_06280_amd import inputs
+from gpu_util import dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2102_06280_amd import binding
+    return binding
+
+
+def hub_graph(n, extra):
+    """A ring whose worker 0 is linked to the first `extra` others as well: a list longer than the kernels keep at hand."""
+    nb = [set() for _ in range(n)]
+    for i in range(n):
+        for j in {(i + 1) % n} | ({0} if 0 < i <= extra else set()):
+            if i != j:
+                nb[i].add(j)
+                nb[j].add(i)
+    return (np.cumsum([0] + [len(s) for s in nb]).astype(np.int32), np.array([j for s in nb for j in sorted(s)], np.int32))
+
+
+# dims, batch, loss, workers, pad: one layer in one and in several chunks (aligned and odd rows), batches of at most 16, 32 and 64
+# samples with widths that are no multiple of the tiles, long batches with and without split sums, equal widths (the chain)
+CASES = [([784, 10], 32, "xent", 8, 64), ([101, 7], 64, "mse", 9, 1), ([257, 16], 300, "xent", 5, 1), ([256, 10], 1024, "xent", 6, 64),
+         ([64, 36, 10], 16, "xent", 12, 64), ([300, 92, 10], 32, "mse", 20, 64), ([784, 200, 10], 64, "xent", 24, 64),
+         ([100, 36, 52, 3], 50, "xent", 7, 64), ([200, 320, 100, 10], 256, "xent", 12, 64), ([68, 36, 10], 260, "mse", 4, 64),
+         ([256, 256, 256, 10], 1024, "mse", 10, 64), ([784, 200, 10], 64, "xent", 24, 1)]
+
+
+@pytest.mark.parametrize("rates", ["one", "each"])
+@pytest.mark.parametrize("dims,batch,loss,n,pad", CASES, ids=["-".join(map(str, c[0])) + f"-b{c[1]}-n{c[3]}-pad{c[4]}" for c in CASES])
+def test_average_on_the_way_is_the_average(B, dims, batch, loss, n, pad, rates):
+    desc = {"kind": "mlp", "dims": dims, "loss": loss}
+    d = inputs.param_count(desc)
+    ld = inputs.pad_ld(d, pad)
+    rowptr, colidx = hub_graph(n, n - 2)
+    g = np.random.default_rng(77 + n)
+    params = inputs.init_params(desc, n, ld, g)
+    params[:, :d] += (g.standard_normal((n, d)) * 0.05).astype(np.float32)
+    x, y = dev(g.standard_normal((n, batch, dims[0])).astype(np.float32)), dev(g.integers(0, dims[-1], (n, batch)).astype(np.int32))
+    t = dev(g.standard_exponential(n).astype(np.float32))
+    b = dev(np.minimum(g.integers(0, 2, n), np.diff(rowptr)).astype(np.int32))
+    eta = dev(g.uniform(0.01, 0.2, n).astype(np.float32))
+    model = B.make_model(B.MODEL_MLP, batch, dims, B.LOSS_MSE if loss == "mse" else B.LOSS_XENT)
+    got = {}
+    for name, mix in (("way", B.MIX_AUTO), ("pass", B.MIX_CSR)):
+        h = B.dbw_create(rowptr, colidx, n, d, ld=ld, model=model, mix_path=mix)
+        try:
+            out = torch.full((n, ld), 3.0, device="cuda")
+            lo = torch.zeros(n, device="cuda")
+            B.dbw_select(h, t, b)
+            B.dbw_set_timing(h, True)
+            if rates == "each":
+                B.dbw_round_eta(h, dev(params), out, eta, batch_x=x, batch_y=y, loss_out=lo)
+            else:
+                B.dbw_round(h, dev(params), out, 0.05, batch_x=x, batch_y=y, loss_out=lo)
+            kernels = set(B.dbw_get_timing(h))
+            got[name] = (out.cpu().numpy(), lo.cpu().numpy(), any(k.startswith("mix_") for k in kernels))
+        finally:
+            B.dbw_destroy(h)
+    assert got["pass"][2]
+    assert got["way"][2] == (pad == 1 and len(dims) > 2)      # rows off 16-byte boundaries: the kernels that average are not taken
+    assert np.array_equal(got["way"][0][:, :d], got["pass"][0][:, :d])
+    assert np.all(got["way"][0][:, d:] == 3.0)
+    assert np.array_equal(got["way"][1], got["pass"][1])
