@@ -359,22 +359,26 @@ __global__ __launch_bounds__(THREADS, 2) void forward_kernel(FwdArgs a)
 
 // ---- forward pass, ReLU and pooling of a layer with few input channels (the network's first).
 //
-// With one or three channels the reduction of forward_kernel would be mostly padding.  Here it runs over pairs (c, kh),
-// two of them per step, with the KS taps of a row in a lane's eight values (the rest zero weights).  A lane's eight values of
-// the image are then eight consecutive pixels of a row, starting at any pixel: as in wgrad_kernel a lane reads aligned
-// ones, sixteen here, and the eight fragments for the output pixels 8 m .. 8 m + 7 are shifts of them in registers.  A wave
-// takes 32 positions (y, m) = 256 output pixels at a time, even and odd y in neighbouring lanes for the pooling; the
-// filters stay in LDS, split, over all samples of the workgroup.
+// With one or three channels the reduction of forward_kernel would be mostly padding.  Here it runs over taps (c, kh, kw) in their order in
+// memory, eight to a lane and sixteen to a step: the lower half of a wavefront takes the first half of the filter rows (c, kh), the upper
+// half the other, so that the pattern of rows and taps in a lane's eight values is the same for all lanes, repeats after
+// eight rows, and is known to the compiler.  A lane's values for the output pixels 8 m .. 8 m + 7 come from the sixteen pixels from 8 m on of two
+// to four rows, read as aligned 16-byte groups: two taps side by side are one register or a shift of two, the last tap of a row and the
+// first of the next one permutation.  A wave takes 32 positions (y, m) = 256 output pixels at a time, even and odd y in
+// neighbouring lanes for the pooling; the filters stay in LDS, split, over all samples of the workgroup.
 //
-// The matrix instructions bound it (5 of 8 values of a 5 x 5 filter's reduction are used).  16 workers x 50 samples, 1 -> 16
-// channels on 28 x 28 pixels, 5 x 5: 30 us (implicit fp32 GEMM 68, pooling pass 12); 32 x 32 samples, 3 -> 16 on 32 x 32,
-// 3 x 3: 41 (108 + 17); 64 x 32 samples, 3 -> 32 on 32 x 32, 5 x 5: 107 (an LDS-resident fp32 kernel 113).
+// The matrix instructions bound it (75 of 80 values of a 3-channel 5 x 5 filter's reduction are used, 27 of 32 with 3 x 3).  Then the
+// copies of the images and the epilogue.  us, before with the taps of one row in a lane's eight values (5 or 3 of 8 used) / now:
+// 64 workers x 32 samples, 3 -> 32 channels on 32 x 32 pixels, 5 x 5: 101 / 87; 32 x 32, 3 -> 16 on 32 x 32, 3 x 3: 38 / 29; 16 x 50, 1 -> 16
+// on 28 x 28, 5 x 5: 29 / 26.  A lane finishing one channel only in the epilogue (half the operations, its row of the other
+// channel handed over by selects) was slower: 98, 35, 32.
 struct FirstPlan {
     int spg, iters;             // samples in LDS at a time, and how often
     size_t lds;
 };
 __host__ __device__ inline int first_groups(const Shape &s) { return (s.W + 7) / 8; }            // m
-__host__ __device__ inline int first_steps(const Shape &s) { return (s.Cin * s.KS + 1) / 2; }
+__host__ __device__ inline int first_rows(const Shape &s) { return (s.Cin * s.KS + 1) / 2; }     // filter rows of a half
+__host__ __device__ inline int first_steps(const Shape &s) { return (first_rows(s) * s.KS + 7) / 8; }
 // 16-byte groups of one plane of one sample's image: rows of 8 m + 8 values
 __host__ __device__ inline int first_image(const Shape &s) { return s.Cin * (s.H + s.KS - 1) * (first_groups(s) + 1); }
 inline bool first_plan(const Shape &s, int workers, FirstPlan &p)
@@ -403,20 +407,21 @@ __global__ __launch_bounds__(THREADS, 2) void first_kernel(FwdArgs a, FirstPlan 
     extern __shared__ __attribute__((aligned(16))) u32x4 sm[];
     const int H = a.s.H, W = a.s.W, Cin = a.s.Cin, Cout = a.s.Cout, pad = KS / 2, HP = H + KS - 1, M = first_groups(a.s), IPG = M + 1;
     const int spg = plan.spg, image = first_image(a.s), iplane = spg * image, steps = first_steps(a.s), wplane = steps * 64;
-    const int pairs = Cin * KS, PP = H * W / 4, m0 = 32 * blockIdx.z;
+    const int pairs = Cin * KS, rows = first_rows(a.s), PP = H * W / 4, m0 = 32 * blockIdx.z;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int w = blockIdx.y;
     u32x4 *img = sm, *wl = sm + 3 * iplane;
     const float *inw = a.in + w * a.in_stride, *wg = a.wgt + w * a.wgt_stride;
 
-    for (int e = tid; e < wplane; e += THREADS) {        // filters: lane (row, half) of step e / 64 holds pair 2 step + half
-        const int ln = e % 64, pair = e / 64 * 2 + ln / 32, co = m0 + ln % 32;
+    for (int e = tid; e < wplane; e += THREADS) {        // filters: lane (channel, half) of step e / 64 holds taps 8 step .. of its half
+        const int ln = e % 64, t0 = e / 64 * 8, half = ln / 32, co = m0 + ln % 32;
         float v[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            const bool ok = j < KS && pair < pairs && co < Cout;
-            const float f = wg[ok ? (co * pairs + pair) * KS + j : 0];
+            const int t = t0 + j;
+            const bool ok = t < rows * KS && half * rows + t / KS < pairs && co < Cout;
+            const float f = wg[ok ? (co * pairs + half * rows) * KS + t : 0];
             v[j] = ok ? f : 0.f;
         }
         const planes p = split_bf16::split8_nearest(v);
@@ -466,54 +471,73 @@ __global__ __launch_bounds__(THREADS, 2) void first_kernel(FwdArgs a, FirstPlan 
             auto products = [&](auto small, auto large, auto mask) {
                 constexpr bool SMALL = decltype(small)::value, LARGE = decltype(large)::value, MASK = decltype(mask)::value;
 #pragma unroll 1
-                for (int st = 0; st < steps; ++st) {
-                    const int p0 = 2 * st, p1 = min(2 * st + 1, pairs - 1);               // (beyond the last pair: zero weights)
-                    const u32x4 *src = base + ((lane < 32 ? (p0 / KS) * HP + p0 % KS : (p1 / KS) * HP + p1 % KS)) * IPG;
-                    const bool exists = lane < 32 || 2 * st + 1 < pairs;
-                    const u32x4 *ws = wl + st * 64 + lane;
-                    const u32x4 fh = ws[0], fm = ws[wplane], fl = ws[2 * wplane];
-                    uint32_t d[8];
-                    auto read = [&](int plane) {
-                        const u32x4 lo = src[plane * iplane], hi = src[plane * iplane + 1];
+                for (int s0 = 0; s0 < steps; s0 += KS) {            // eight rows of either half
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            d[i] = lo[i];
-                            d[4 + i] = hi[i];
+                    for (int g = 0; g < KS; ++g) {
+                        if (s0 + g >= steps) break;
+                        const int r0 = 8 * g / KS, NR = (8 * g + 7) / KS - r0 + 1;        // rows of the step; constants once unrolled
+                        const u32x4 *src[4];
+#pragma unroll
+                        for (int r = 0; r < NR; ++r) {
+                            const int row = s0 / KS * 8 + r0 + r, p0 = min(row, pairs - 1), p1 = min(row + rows, pairs - 1);     // (beyond: zero weights)
+                            src[r] = base + (lane < 32 ? (p0 / KS) * HP + p0 % KS : (p1 / KS) * HP + p1 % KS) * IPG;
                         }
-                    };
-                    auto shifted = [&](int x) {          // values x .. x + 7 of the sixteen
-                        u32x4 f;
+                        const u32x4 *ws = wl + (s0 + g) * 64 + lane;
+                        const u32x4 fh = ws[0], fm = ws[wplane], fl = ws[2 * wplane];
+                        uint32_t d[4][8];
+                        auto read = [&](int plane) {
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            f[i] = x % 2 == 0 ? d[x / 2 + i] : __builtin_amdgcn_alignbit(d[x / 2 + i + 1], d[x / 2 + i], 16);
-                            if (MASK) f[i] = 2 * i < KS && exists ? (2 * i + 1 < KS ? f[i] : f[i] & 0xffffu) : 0u;
+                            for (int r = 0; r < NR; ++r) {
+                                const u32x4 lo = src[r][plane * iplane], hi = src[r][plane * iplane + 1];
+#pragma unroll
+                                for (int i = 0; i < 4; ++i) {
+                                    d[r][i] = lo[i];
+                                    d[r][4 + i] = hi[i];
+                                }
+                            }
+                        };
+                        auto shifted = [&](int x) {      // the eight taps' values for output pixel 8 m + x
+                            u32x4 f;
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) {
+                                const int t = 8 * g + 2 * i, ra = t / KS - r0, rb = (t + 1) / KS - r0, pa = x + t % KS, pb = x + (t + 1) % KS;
+                                if (ra == rb)
+                                    f[i] = pa % 2 == 0 ? d[ra][pa / 2] : __builtin_amdgcn_alignbit(d[ra][pa / 2 + 1], d[ra][pa / 2], 16);
+                                else
+                                    f[i] = __builtin_amdgcn_perm(d[rb][pb / 2], d[ra][pa / 2], (pb % 2 ? 0x07060000u : 0x05040000u) | (pa % 2 ? 0x0302u : 0x0100u));
+                                if (MASK) {
+                                    const int tap = s0 * 8 + t, left = min(rows, lane < 32 ? rows : pairs - rows) * KS - tap;     // taps of the half from this one on
+                                    f[i] = left >= 2 ? f[i] : (left == 1 ? f[i] & 0xffffu : 0u);
+                                }
+                            }
+                            return split_bf16::frag(f);
+                        };
+                        auto mma = [&](const u32x4 &f, split_bf16::bf16x8 b, int x) {
+                            acc[x] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(split_bf16::frag(f), b, acc[x], 0, 0, 0);
+                        };
+                        if (SMALL) {
+                            read(2);
+#pragma unroll
+                            for (int x = 0; x < 8; ++x) mma(fh, shifted(x), x);
+                            read(1);
+#pragma unroll
+                            for (int x = 0; x < 8; ++x) {
+                                const auto b = shifted(x);
+                                mma(fm, b, x);
+                                mma(fh, b, x);
+                            }
                         }
-                        return split_bf16::frag(f);
-                    };
-                    auto mma = [&](const u32x4 &f, split_bf16::bf16x8 b, int x) {
-                        acc[x] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(split_bf16::frag(f), b, acc[x], 0, 0, 0);
-                    };
-                    if (SMALL) {
-                        read(2);
-#pragma unroll
-                        for (int x = 0; x < 8; ++x) mma(fh, shifted(x), x);
-                        read(1);
+                        read(0);
 #pragma unroll
                         for (int x = 0; x < 8; ++x) {
                             const auto b = shifted(x);
-                            mma(fm, b, x);
-                            mma(fh, b, x);
+                            if (SMALL) {
+                                mma(fl, b, x);
+                                mma(fm, b, x);
+                            }
+                            if (LARGE) mma(fh, b, x);
                         }
-                    }
-                    read(0);
-#pragma unroll
-                    for (int x = 0; x < 8; ++x) {
-                        const auto b = shifted(x);
-                        if (SMALL) {
-                            mma(fl, b, x);
-                            mma(fm, b, x);
-                        }
-                        if (LARGE) mma(fh, b, x);
+                        __builtin_amdgcn_sched_barrier(0);       // (with the reads of several steps ahead the registers run out)
                     }
                 }
             };
