@@ -6,9 +6,8 @@
 // Parameter row layout: conv1 W [C1][C0][K][K], b [C1]; conv2 W [C2][C1][K][K], b [C2];
 // fc1 W [F][flat], b [F]; fc2 W [classes][F], b [classes].
 //
-// Convolutions with 3 x 3 and 5 x 5 filters take the LDS-resident kernels of conv_split.h (conv1's weight gradient with 3 ->
-// 32 channels that of conv_lds.h); the rest are implicit GEMMs on the batched fp32 MFMA
-// kernel: the patch matrix is never materialised, the operand loaders compute the input address of each element.
+// Convolutions with 3 x 3 and 5 x 5 filters take the LDS-resident kernels of conv_split.h and conv_first_wgrad.h; the rest are implicit GEMMs on the
+// batched fp32 MFMA kernel: the patch matrix is never materialised, the operand loaders compute the input address of each element.
 //   forward   z[co][pix]      = sum_k  W[co][k] * patch[k][pix]        k = (ci, kh, kw)
 //   wgrad     dW[co][k]       = sum_pix dz[co][pix] * patch[k][pix]
 //   dgrad     din[ci][pix_in] = sum_k' W[co][ci][kh][kw] * dz[co][pix_in shifted]   k' = (co, kh, kw)
@@ -18,7 +17,7 @@
 #include <algorithm>
 
 #include "bgemm.h"
-#include "conv_lds.h"
+#include "conv_first_wgrad.h"
 #include "conv_split.h"
 #include "dbw_internal.h"
 
@@ -338,8 +337,6 @@ __global__ __launch_bounds__(256) void channel_sum_kernel(const float *__restric
     if (tid == 0) db[w * dbstride + ch] = red[0];
 }
 
-constexpr int WGRAD_SB = 4;     // samples per workgroup in the LDS-resident weight gradient of conv1 (scratch is sized for it)
-
 struct cnn_layout {
     int C0, H, W, C1, C2, KS, F, NC, B;
     int H2, W2, H4, W4, flat;
@@ -349,11 +346,12 @@ struct cnn_layout {
     // scratch offsets inside a worker's block (floats)
     int64_t z1, p1, z2, p2, dp2, dz2, dp1, dz1, fc_act, part1, part2, filt_fwd, filt_bwd, code1, code2, total;
     int splits1, splits2;
-    bool lds1;                      // conv1 by conv_lds.h (if the batch is aligned)
     bool first;                     // conv1's forward pass by convsplit::first_kernel
+    bool first_wgrad;               // conv1's weight gradient by conv_first_wgrad.h (otherwise, with split1, by wgrad_kernel)
     bool split1, split2;            // weight gradient of conv1 / all three products of conv2 by conv_split.h
     convsplit::WgradPlan wg1, wg2;
     convsplit::FirstPlan fp;
+    convsplit::FirstWgradPlan fw;
 };
 
 // The kernels of conv_split.h take every 3 x 3 and 5 x 5 filter whose images fit LDS, however few the channels: with 2 -> 4
@@ -385,7 +383,6 @@ cnn_layout make_layout(const dbw_model &m, int workers)
     L.b2 = L.w2 + L.C2 * L.C1 * KK;
     L.fc = L.b2 + L.C2;
     const int64_t B = L.B;
-    L.lds1 = L.KS == 5 && L.C0 == 3 && L.H == 32 && L.W == 32 && L.C1 == 32;
     L.split1 = conv_split_fits({L.C0, L.C1, L.H, L.W, L.KS, L.B}, workers, true, L.wg1);
     L.split2 = conv_split_fits({L.C1, L.C2, L.H2, L.W2, L.KS, L.B}, workers, false, L.wg2);
     L.first = (L.KS == 3 || L.KS == 5) && convsplit::first_plan({L.C0, L.C1, L.H, L.W, L.KS, L.B}, workers, L.fp);
@@ -402,11 +399,10 @@ cnn_layout make_layout(const dbw_model &m, int workers)
     L.fc_act = take(dbw_fc_scratch_per_worker(2, L.fc_dims, L.B));
     // split the long pixel reductions of the weight gradients so that the grid fills the chip
     auto pick = [&](int64_t K) { int s = 1; while (s < 32 && K / (s * 2) >= 1024) s *= 2; return s; };
-    L.splits1 = L.split1 ? L.wg1.splits : pick(B * L.H * L.W);
+    L.first_wgrad = L.split1 && convsplit::first_wgrad_plan({L.C0, L.C1, L.H, L.W, L.KS, L.B}, workers, L.fw);
+    L.splits1 = L.first_wgrad ? L.fw.splits : (L.split1 ? L.wg1.splits : pick(B * L.H * L.W));
     L.splits2 = L.split2 ? L.wg2.splits : pick(B * L.H2 * L.W2);
-    // the LDS-resident kernel for conv1 of the 3 -> 32 channel network writes one partial result per 4 samples and wave
-    const int64_t s1 = std::max<int64_t>(L.splits1, L.lds1 ? (B + WGRAD_SB - 1) / WGRAD_SB * 8 : 0);
-    L.part1 = take(s1 * L.C1 * L.C0 * KK);
+    L.part1 = take(L.splits1 * L.C1 * L.C0 * KK);
     L.part2 = take(L.splits2 * L.C2 * L.C1 * KK);
     L.filt_fwd = take(L.split2 ? convsplit::filter_floats(L.C1, L.C2, L.KS) : 0);
     L.filt_bwd = take(L.split2 ? convsplit::filter_floats(L.C2, L.C1, L.KS) : 0);
@@ -448,6 +444,33 @@ int launch_split_wgrad(const convsplit::WgradArgs &a, int workers, hipStream_t s
     else hipLaunchKernelGGL(convsplit::wgrad_kernel<5>, grid, block, a.p.lds, s, a);
     DBW_HIP(hipGetLastError());
     return DBW_OK;
+}
+
+template <int KS, int MB, int NB>
+int launch_first_wgrad_blocks(const convsplit::FirstWgradArgs &a, int workers, hipStream_t s)
+{
+    const dim3 grid(a.p.splits, workers, (a.s.Cout + 16 * MB - 1) / (16 * MB));
+    hipLaunchKernelGGL((convsplit::first_wgrad_kernel<KS, MB, NB>), grid, dim3(convsplit::THREADS), a.p.lds, s, a);
+    DBW_HIP(hipGetLastError());
+    return DBW_OK;
+}
+
+// Taps of 3 x 3 filters: 9, 18, 27, 36, 45, 54, 63, 72 in one to five blocks of sixteen; of 5 x 5: 25, 50, 75 in two, four and five.
+int launch_first_wgrad(const convsplit::FirstWgradArgs &a, int workers, hipStream_t s)
+{
+    auto rows = [&](auto one, auto two) { return a.p.mb == 1 ? one(a, workers, s) : two(a, workers, s); };
+    if (a.s.KS == 3) switch (a.p.nb) {
+        case 1: return rows(launch_first_wgrad_blocks<3, 1, 1>, launch_first_wgrad_blocks<3, 2, 1>);
+        case 2: return rows(launch_first_wgrad_blocks<3, 1, 2>, launch_first_wgrad_blocks<3, 2, 2>);
+        case 3: return rows(launch_first_wgrad_blocks<3, 1, 3>, launch_first_wgrad_blocks<3, 2, 3>);
+        case 4: return rows(launch_first_wgrad_blocks<3, 1, 4>, launch_first_wgrad_blocks<3, 2, 4>);
+        default: return rows(launch_first_wgrad_blocks<3, 1, 5>, launch_first_wgrad_blocks<3, 2, 5>);
+    }
+    switch (a.p.nb) {
+    case 2: return rows(launch_first_wgrad_blocks<5, 1, 2>, launch_first_wgrad_blocks<5, 2, 2>);
+    case 4: return rows(launch_first_wgrad_blocks<5, 1, 4>, launch_first_wgrad_blocks<5, 2, 4>);
+    default: return rows(launch_first_wgrad_blocks<5, 1, 5>, launch_first_wgrad_blocks<5, 2, 5>);
+    }
 }
 
 template <int KS_>
@@ -592,14 +615,10 @@ int launch_grad_cnn(dbw_ctx *c, const float *params, const float *bx, const int3
                               ChannelPixelOut{A + L.dp1, ws, L.C1, L.H2 * L.W2, nullptr, 0}, L.C1, pix2, L.C2 * KK, N,
                               s));
     }
-    int splits1 = L.splits1;
-    if (KS_ == 5 && L.lds1 && L.split1 && (uintptr_t)bx % 16 == 0) {   // conv1 weight gradient (conv_lds.h; it reads code1)
-        const int nb = (B + WGRAD_SB - 1) / WGRAD_SB;
-        splits1 = nb * 8;
+    if (L.first_wgrad) {
         dbw_timer tm(c, "conv1_wgrad", s);
-        hipLaunchKernelGGL((convlds::conv_wgrad_kernel<3, 2, 5, 1, 1, 8, 32, 32, 5, 512>), dim3(nb, N), dim3(512), 0,
-                           s, bx, xstride, A + L.dp1, ws, A + L.part1, ws, B, WGRAD_SB, code1, cs);
-        DBW_HIP(hipGetLastError());
+        const int rc = launch_first_wgrad({{L.C0, L.C1, L.H, L.W, L.KS, B}, L.fw, bx, xstride, A + L.dp1, ws, code1, cs, A + L.part1, ws}, N, s);
+        if (rc != DBW_OK) return rc;
     } else if (L.split1) {
         dbw_timer tm(c, "conv1_wgrad", s);
         const int rc = launch_split_wgrad({{L.C0, L.C1, L.H, L.W, L.KS, B}, L.wg1, bx, xstride, A + L.dp1, ws, code1, cs, A + L.part1, ws}, N, s);
@@ -622,7 +641,7 @@ int launch_grad_cnn(dbw_ctx *c, const float *params, const float *bx, const int3
                            grads + L.b1, ld);
         DBW_HIP(hipGetLastError());
     }
-    const FinishLayer f1{A + L.part1, splits1, L.C1 * L.C0 * KK, grads + L.w1, grads + L.b1, L.split1 ? code1 : nullptr, A + L.dp1,
+    const FinishLayer f1{A + L.part1, L.splits1, L.C1 * L.C0 * KK, grads + L.w1, grads + L.b1, L.split1 ? code1 : nullptr, A + L.dp1,
                          L.C1, L.H2 * L.W2};
     const FinishLayer f2{A + L.part2, L.splits2, L.C2 * L.C1 * KK, grads + L.w2, grads + L.b2, L.split2 ? code2 : nullptr, A + L.dp2,
                          L.C2, L.H4 * L.W4};

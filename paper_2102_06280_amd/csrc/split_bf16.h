@@ -86,36 +86,34 @@ __device__ __forceinline__ planes split8(const float (&x)[8])
     return p;
 }
 
-// Eight values with the nearest high value: 12.  An infinity or a NaN is one in the high plane and NaN in the others.  The half
-// step below the largest float rounds to an infinite bf16, which shows as an infinite remainder (that of an infinity is NaN,
-// which the maximum passes over): then once more, with high values that stay finite.
-__device__ __forceinline__ planes split8_nearest(const float (&x)[8])
+// N values (an even number) with the nearest high value, as pairs: 12 instructions for two.  An infinity or a NaN is one in the high
+// plane and NaN in the others.  The half step below the largest float rounds to an infinite bf16, which shows as an infinite remainder
+// (that of an infinity is NaN, which the maximum passes over): then once more, with high values that stay finite.
+template <int N>
+__device__ __forceinline__ void split_nearest(const float (&x)[N], uint32_t (&h)[N / 2], uint32_t (&m)[N / 2], uint32_t (&l)[N / 2])
 {
-    planes p;
     float rest = 0.f;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        uint32_t m, l;
-        const uint32_t h = nearest(x[2 * q], x[2 * q + 1]);
-        const float a = x[2 * q] - value(h << 16), b = x[2 * q + 1] - value(h & 0xffff0000u);
+    for (int q = 0; q < N / 2; ++q) {
+        h[q] = nearest(x[2 * q], x[2 * q + 1]);
+        const float a = x[2 * q] - value(h[q] << 16), b = x[2 * q + 1] - value(h[q] & 0xffff0000u);
         rest = fmaxf(rest, fmaxf(fabsf(a), fabsf(b)));
-        split_rest(a, b, m, l);
-        p.h[q] = h;
-        p.m[q] = m;
-        p.l[q] = l;
+        split_rest(a, b, m[q], l[q]);
     }
     if (__builtin_expect(rest == __builtin_inff(), 0)) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
+        for (int q = 0; q < N / 2; ++q) {
             const float ha = high_value(x[2 * q]), hb = high_value(x[2 * q + 1]);
-            uint32_t m, l;
-            split_rest(x[2 * q] - ha, x[2 * q + 1] - hb, m, l);
-            p.h[q] = upper(ha, hb);
-            p.m[q] = m;
-            p.l[q] = l;
+            split_rest(x[2 * q] - ha, x[2 * q + 1] - hb, m[q], l[q]);
+            h[q] = upper(ha, hb);
         }
     }
-    return p;
+}
+__device__ __forceinline__ planes split8_nearest(const float (&x)[8])
+{
+    uint32_t h[4], m[4], l[4];
+    split_nearest(x, h, m, l);
+    return {u32x4{h[0], h[1], h[2], h[3]}, u32x4{m[0], m[1], m[2], m[3]}, u32x4{l[0], l[1], l[2], l[3]}};
 }
 
 __device__ __forceinline__ bf16x8 frag(const u32x4 &v) { return __builtin_bit_cast(bf16x8, v); }
