@@ -15,7 +15,9 @@
 // the multiplies left out); for N = 256 x 1 M 0.82 ms, where the memory side alone takes 0.65 (128-byte pieces of rows that
 // lie far apart) and the multiplies and splits alone 0.56.  The fp32 matrix instruction that this kernel used before needs
 // 0.83 ms at its peak rate for the latter shape and took 1.13; N = 128 without gradients, 2.8 M columns: 0.88 -> 0.61 ms;
-// N = 60 x 4 M: 0.60 -> 0.56.  Tried without gain: one 64-column tile with a single set of
+// N = 60 x 4 M: 0.60 -> 0.56.  Results, and from 65 workers on loads, pass the caches by: N = 128 x 2.8 M without gradients 690 -> 678 us
+// (a plain copy of as many bytes: 600), N = 256 x 1 M with them 840 -> 829, N = 100 x 40 000 26.1 -> 24.9; up to 64 workers such
+// loads cost (N = 60 x 200 000 33 -> 35).  Tried without gain: two tiles of X on their way instead of one (685), one 64-column tile with a single set of
 // planes (0.88), wave priorities for either phase, LDS fragments requested a step ahead.
 //
 // D of v_mfma_f32_32x32x16_bf16, lane l: 16 floats, d[v] = D[m = 8 * (v / 4) + 4 * (l / 32) + v % 4][n = l % 32]
@@ -58,12 +60,14 @@ struct Cfg {
 // 64 x 16 (WIDE) or 64 x 4 bytes from global memory (uniform base + lane offset) to LDS at `dst` (uniform) + 16 or 4 * lane.  As inline
 // assembly and not as the builtin: behind the builtin the compiler waits for the loads to land before the next LDS read,
 // whichever LDS array that is from.  The kernel waits itself (vmcnt) before it reads what they bring.  (m0, the LDS
-// address of such a load, has no other user in this kernel.)
-template <bool WIDE>
+// address of such a load, has no other user in this kernel.)  STREAM: not kept in the caches.
+template <bool WIDE, bool STREAM>
 __device__ __forceinline__ void load_to_lds(const char *base, uint32_t lane_off, const float *dst)
 {
     const uint32_t m0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) const float *)dst);
-    if (WIDE)
+    if (WIDE && STREAM)
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(lane_off), "s"(base), "s"(m0) : "memory");
+    else if (WIDE)
         asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(lane_off), "s"(base), "s"(m0) : "memory");
     else
         asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" ::"v"(lane_off), "s"(base), "s"(m0) : "memory");
@@ -121,7 +125,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void kernel(
             const int r = r0 + i / PIECES * PER;                                          // uniform
             const int64_t last = (dcols - 1) / V * V, cb = min(t * C::TC + c0 + 64 * V * (i % PIECES), last);
             const uint32_t c_off = 4u * (uint32_t)min((int64_t)lane_col, last - cb);
-            load_to_lds<WIDE>(uniform_base(src + (int64_t)min(r, N - 1) * ld + cb), (lane_row < N - r ? row_off : 0u) + c_off,
+            load_to_lds<WIDE, MB >= 4>(uniform_base(src + (int64_t)min(r, N - 1) * ld + cb), (lane_row < N - r ? row_off : 0u) + c_off,
                               dst + 1024 * w + 64 * V * i);
         }
     };
@@ -231,7 +235,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void kernel(
         if (full) {
 #pragma unroll
             for (int v = 0; v < 16; ++v)
-                *(float *)(const_cast<char *>(uniform_base(out + (int64_t)(32 * rb + 8 * (v / 4) + (v & 3)) * ld + col0)) + lane_off) = acc[v];
+                __builtin_nontemporal_store(acc[v], (float *)(const_cast<char *>(uniform_base(out + (int64_t)(32 * rb + 8 * (v / 4) + (v & 3)) * ld + col0)) + lane_off));
         } else {
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
