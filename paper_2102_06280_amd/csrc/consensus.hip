@@ -62,8 +62,11 @@ __global__ void phi_fragment_kernel(int N, int Npad, const float *__restrict__ p
 // (next).  Sums as in phi_step_kernel.  Round q's lists are the tail arrays' q-th, the last round's the context's
 // selection state if last_state.  A launch per round and selection (13 us a round) becomes two launches for up to
 // DBW_TAIL_ROUNDS rounds: 8 rounds of 128 workers with 8
-// neighbours 117 -> 33 us, 64 workers in a complete graph 137 -> 77.  grid = Npad / TAIL_COLS.
-constexpr int TAIL_COLS = 8, TAIL_THREADS = 512, TAIL_STAGE = 8;
+// neighbours 117 -> 33 us, 64 workers in a complete graph 137 -> 77.  What is left is a chain of dependent LDS reads, list entry and then
+// product, in every round: four entries at a time, and a thread for every element of 256 rows x 4 columns (eight columns on
+// 512 threads, entry by entry / so): the first example, with 20 000 columns averaged, 36.2 / 26.1; 256 workers, 8 neighbours, 12
+// rounds, 10 000 columns 76.7 / 45.3; 60 workers in a complete graph, 6 rounds 56.7 / 37.9.  grid = Npad / TAIL_COLS.
+constexpr int TAIL_COLS = 4, TAIL_THREADS = 1024, TAIL_STAGE = 8;
 __global__ __launch_bounds__(TAIL_THREADS) void phi_tail_kernel(
     int N, int Npad, int nnz, int rounds, int last_state, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ tail_p,
     const int32_t *__restrict__ tail_idx, const float *__restrict__ tail_w, const float *__restrict__ tail_self,
@@ -102,7 +105,16 @@ __global__ __launch_bounds__(TAIL_THREADS) void phi_tail_kernel(
                 const int2 r = row[q * N + i];
                 const int2 *l = &list[q * nnz + rp[i]];
                 float acc = __int_as_float(r.y) * phi[cur][i * TAIL_COLS + col];
-                for (int k = 0; k < r.x; ++k) acc = fmaf(__int_as_float(l[k].y), phi[cur][l[k].x * TAIL_COLS + col], acc);
+                for (int k = 0; k < r.x; k += 4) {       // four neighbours under way (behind the last: that one again, not added)
+                    int2 e[4];
+                    float v[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) e[u] = l[min(k + u, r.x - 1)];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) v[u] = phi[cur][e[u].x * TAIL_COLS + col];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) acc = k + u < r.x ? fmaf(__int_as_float(e[u].y), v[u], acc) : acc;
+                }
                 phi[cur ^ 1][i * TAIL_COLS + col] = acc;
             }
             cur ^= 1;
