@@ -13,7 +13,7 @@
 //   A fragment: lane l holds A[m = l % 16][k = l / 16], B fragment: B[k = l / 16][n = l % 16],
 //   D: d[v] = D[m = 4 * (l / 16) + v][n = l % 16].
 //
-// grid = (chunks, workers).  With one chunk per worker (batches up to 64) the sums over the batch
+// grid = (chunks x parts, workers).  With one chunk per worker (batches up to 64) the sums over the batch
 // (dW, db, the bias gradient below, the loss) are final.  Otherwise they are written as per-chunk
 // partials and added in chunk order by reduce_kernel, a second launch: a "last workgroup to arrive
 // adds them" scheme inside one launch was measured and rejected, because the memory fence every
@@ -189,10 +189,13 @@ __device__ __forceinline__ Early fetch_early(const Args &g, int w, int s0, int n
 // floats behind the image zero), Wl the image stage_w makes.  S is a multiple of 16 up to MAX_S.  With da_to_lds the
 // (masked) input gradient replaces the input in al instead of going to g.da.  All THREADS threads call this after a
 // barrier that makes al and Wl visible.
-// MIX: g.avg is there and the sums over the batch are final (one chunk).
+// MIX: g.avg is there and the sums over the batch are final (one chunk).  Of `parts` workgroups that all have the chunk's logits, number
+// `part_no` takes every parts-th run of RUN columns of the products behind them (784-10 on 8 workers x 32 samples, where the products
+// and the average were 11 of the kernel's 16 us: four parts, round 21.4 -> 19.1; on 24 workers without the average 23.3 -> 21.7).
+constexpr int RUN = 2 * WAVES * 16;
 template <int LOSS, bool MIX = false>
 __device__ __forceinline__ void body(const Args &g, float *zl, float *zp, float *Wl, float *al, int S, int w, int chunk,
-                                     int chunks, bool da_to_lds, const Early &early)
+                                     int chunks, bool da_to_lds, const Early &early, int part_no = 0, int parts = 1)
 {
     const int H = g.H, C = g.C, HP = row_pitch(H);
     const int tid = threadIdx.x, lane = tid & 63;
@@ -298,10 +301,13 @@ __device__ __forceinline__ void body(const Args &g, float *zl, float *zp, float 
                                     : (chunks == 1 ? g.grads + w * g.p_stride + g.bprev_off : part + (size_t)C * H + C);
     float *__restrict__ da = (g.da && !da_to_lds) ? g.da + w * g.da_stride + (int64_t)s0 * g.da_ld : nullptr;
     const int NB = (H + 15) / 16;                       // 16-column blocks of the input dimension
+    // The only layer of a model: W's image is not needed any more and takes the gradient, which is then averaged row by row
+    // (block by block every wavefront would wait for its neighbours' rows again and again)
+    const bool collect = MIX && !da && !da_to_lds && !out_bprev;
 
     // Two 16-column blocks per pass (nb and nb + WAVES): their chains of dependent instructions and LDS reads overlap.
     // A pass whose second block does not exist computes it on the first one's columns and stores nothing for it.
-    for (int nb0 = wave; nb0 < NB; nb0 += 2 * WAVES) {
+    for (int nb0 = 2 * WAVES * part_no + wave; nb0 < NB; nb0 += 2 * WAVES * parts) {
         const bool two = nb0 + WAVES < NB;
         int col[2];
         col[0] = 16 * nb0 + l16;
@@ -331,6 +337,14 @@ __device__ __forceinline__ void body(const Args &g, float *zl, float *zp, float 
                 float dw[4];
 #pragma unroll
                 for (int v = 0; v < 4; ++v) dw[v] = acc[p][0][v] + acc[p][1][v];
+                if (MIX && collect) {
+                    if (col[p] < H && (p == 0 || two)) {
+#pragma unroll
+                        for (int v = 0; v < 4; ++v)
+                            if (4 * lq + v < C) Wl[(4 * lq + v) * HP + col[p]] = dw[v];
+                    }
+                    continue;
+                }
                 if (MIX && (p == 0 || two)) {
                     uint32_t off[4];
 #pragma unroll
@@ -390,21 +404,55 @@ __device__ __forceinline__ void body(const Args &g, float *zl, float *zp, float 
             }
         }
     }
-    if (tid < C) {
+    if (tid < C && part_no == 0) {
         float sum = 0.f;
         for (int s = 0; s < ns; ++s) sum += zl[s * MAX_C + tid];
-        if (MIX) average::store(g.avg, nb, w, g.grads + w * g.p_stride, g.b_off + tid, sum);
+        if (MIX && collect) zp[MAX_S + tid] = sum;             // (behind red)
+        else if (MIX) average::store(g.avg, nb, w, g.grads + w * g.p_stride, g.b_off + tid, sum);
         else out_b[tid] = sum;
     }
-    // ---- the chunk's loss: its samples in a fixed order (tree in LDS)
-    if (g.loss) {
-        for (int o = MAX_S / 2; o > 0; o >>= 1) {
-            if (tid < o) red[tid] += red[tid + o];
-            __syncthreads();
+    if (MIX && collect) {
+        // the runs of columns of this workgroup, four at a time on whatever boundary they lie, what is left of a run and b one by one
+        typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+        float *row = g.grads + w * g.p_stride;
+        __syncthreads();
+        for (int c0 = RUN * part_no; c0 < H; c0 += RUN * parts) {
+            const int width = min(RUN, H - c0), quads = width / 4, groups = C * quads;
+            for (int g0 = tid; g0 < groups; g0 += 2 * THREADS) {
+                f32x4_any v[2];
+                uint32_t off[2];
+                int at[2];                              // in the image
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const int e = min(g0 + u * THREADS, groups - 1), c = e / quads, k = c0 + 4 * (e - c * quads);
+                    off[u] = 4u * (uint32_t)(c * H + k);
+                    at[u] = c * HP + k;
+                }
+                average::gather<f32x4_any, 2>(g.avg, nb, w, g.w_off, off, v);
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    if (g0 + u * THREADS >= groups) continue;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[u][e] = fmaf(-nb.eta, Wl[at[u] + e], v[u][e]);
+                    *(f32x4_any *)((char *)(row + g.w_off) + off[u]) = v[u];
+                }
+            }
+            for (int e = tid; e < C * (width % 4); e += THREADS) {
+                const int c = e / (width % 4), k = c0 + 4 * quads + e - c * (width % 4);
+                average::store(g.avg, nb, w, row, g.w_off + c * H + k, Wl[c * HP + k]);
+            }
         }
-        if (tid == 0) {
-            if (chunks == 1) g.loss[w] = red[0] / (float)g.B;
-            else part[partial_floats(H, C, g.bprev_off >= 0) - 1] = red[0];
+        if (tid < C && part_no == 0) average::store(g.avg, nb, w, row, g.b_off + tid, zp[MAX_S + tid]);
+    }
+    // ---- the chunk's loss: its samples in a fixed order (a tree inside one wavefront)
+    static_assert(MAX_S == 64, "one sample per lane");
+    if (g.loss && wave == WAVES - 1 && part_no == 0) {
+        float sum = red[lane];
+#pragma unroll
+        for (int o = MAX_S / 2; o > 0; o >>= 1) sum += __shfl_down(sum, o, 64);
+        if (lane == 0) {
+            if (chunks == 1) g.loss[w] = sum / (float)g.B;
+            else part[partial_floats(H, C, g.bprev_off >= 0) - 1] = sum;
         }
     }
 }
@@ -431,7 +479,7 @@ __device__ __forceinline__ float4 split_sum(const float *src, int64_t plane, int
 // VEC: the input rows start on 16-byte boundaries and H divides by 4 (128-bit staging loads).
 // SPLIT: the input arrives as split-k partial sums (Args::splits).
 template <int LOSS, bool VEC, bool SPLIT = false, bool MIX = false>
-__global__ __launch_bounds__(THREADS) void kernel(Args g)
+__global__ __launch_bounds__(THREADS) void kernel(Args g, int parts)
 {
     extern __shared__ __attribute__((aligned(16))) float sm[];
     const int H = g.H, C = g.C, S = g.S, HP = row_pitch(H);
@@ -440,7 +488,7 @@ __global__ __launch_bounds__(THREADS) void kernel(Args g)
     float *Wl = zp + WAVES * 16 * 16;                // [C + 1][HP]: row C and the columns >= H are zero
     float *al = Wl + (C + 1) * HP + 16;              // [S][HP], rows >= ns and columns >= H zero
     const int tid = threadIdx.x;
-    const int chunk = blockIdx.x, chunks = gridDim.x, w = blockIdx.y;
+    const int chunk = blockIdx.x / parts, chunks = gridDim.x / parts, w = blockIdx.y;
     const int s0 = chunk * S, ns = min(S, g.B - s0);
     const float *__restrict__ a = g.a + w * g.a_stride + (int64_t)s0 * g.a_ld;
 
@@ -506,7 +554,7 @@ __global__ __launch_bounds__(THREADS) void kernel(Args g)
     if (tid < 16) al[S * HP + tid] = 0.f;
     __syncthreads();
 
-    body<LOSS, MIX>(g, zl, zp, Wl, al, S, w, chunk, chunks, false, early);
+    body<LOSS, MIX>(g, zl, zp, Wl, al, S, w, chunk, chunks, false, early, blockIdx.x % parts, parts);
 }
 
 // Sum of the per-chunk partials in chunk order -> dW, db, the bias gradient below, the loss.

@@ -548,13 +548,17 @@ int dbw_fc_forward_backward(dbw_ctx *c, dbw_fc_args &a, hipStream_t s)
             if (rc2 != DBW_OK) return rc2;
             return DBW_OK;
         } else {
-        const dim3 grid(head.chunks, N);
+        // Few workgroups: several of them to a chunk, which all stage it and form its logits and share the columns of what follows.  Not where
+        // the chunk is a sum of split products, most of the work then.
+        int parts = 1;
+        if (head_splits == 0) parts = std::max(1, std::min((h.H + fchead::RUN - 1) / fchead::RUN, 256 / (head.chunks * N)));
+        const dim3 grid(head.chunks * parts, N);
         const size_t lds = fchead::lds_bytes(h.H, h.C, h.S);
         const bool vec = h.H % 4 == 0 && h.a_ld % 4 == 0 && h.a_stride % 4 == 0 && (uintptr_t)h.a % 16 == 0;
         const bool mse = a.loss_kind == DBW_LOSS_MSE;
         auto go = [&](auto kern) -> int {
             dbw_timer tm(c, "fc_head_kernel", s);
-            hipLaunchKernelGGL(kern, grid, dim3(fchead::THREADS), lds, s, h);
+            hipLaunchKernelGGL(kern, grid, dim3(fchead::THREADS), lds, s, h, parts);
             DBW_HIP(hipGetLastError());
             return DBW_OK;
         };
