@@ -21,62 +21,79 @@ namespace {
 using bgemm::Dense;
 using bgemm::Epilogue;
 
-// Softmax, mean loss over the batch and its gradient with respect to the logits; one thread per
-// sample, grid = (chunks, workers) with 256 samples per workgroup.  Cross-entropy:
+// Softmax, mean loss over the batch and its gradient with respect to the logits; sixteen lanes per sample, which share its
+// classes; grid = (chunks, workers) with 256 samples per workgroup.  Cross-entropy:
 // dz = (p - onehot(y)) / B.  MSE on the softmax outputs (Appendix B, 2NN): f = sum_c (p_c - o_c)^2,
 // dz_k = 2 p_k ((p_k - o_k) - sum_c p_c (p_c - o_c)) / B.
 // The loss of a worker is the sum of its workgroups' partial sums: each writes its own to
 // loss_part[worker][chunk] and takes a ticket; the last one to arrive adds them in chunk order (so
 // the result does not depend on the order of arrival) and puts the ticket counter back to zero.
+// A thread per sample walked over the classes alone, in one wavefront or two per worker: 20 workers x 101 samples, 26 classes, 13.3 us
+// of a round that took 120.5 and takes 113.6 so; 256-40 on 20 x 1 024 samples 70 -> 56, 784-33 on 6 x 32 40 -> 30.
+constexpr int LOSS_THREADS = 1024, LOSS_LANES = 16;
+template <class F>
+__device__ __forceinline__ float loss_lanes(float v, F op)      // over the lanes of a sample
+{
+#pragma unroll
+    for (int o = 1; o < LOSS_LANES; o <<= 1) v = op(v, __shfl_xor(v, o, LOSS_LANES));
+    return v;
+}
 template <int LOSS>
-__global__ __launch_bounds__(256) void softmax_loss_kernel(
+__global__ __launch_bounds__(LOSS_THREADS) void softmax_loss_kernel(
     int B, int C, const float *__restrict__ logits, int64_t stride_logits, const int32_t *__restrict__ y,
     float *__restrict__ dz, int64_t stride_dz, float *__restrict__ loss, float *__restrict__ loss_part,
     uint32_t *__restrict__ ticket, int32_t *__restrict__ err)
 {
-    __shared__ float red[256];
-    const int chunk = blockIdx.x, chunks = gridDim.x, w = blockIdx.y, tid = threadIdx.x;
+    constexpr int AT_ONCE = LOSS_THREADS / LOSS_LANES;
+    __shared__ float red[LOSS_THREADS / 64];
+    const int chunk = blockIdx.x, chunks = gridDim.x, w = blockIdx.y, tid = threadIdx.x, l = tid % LOSS_LANES;
     const float *z = logits + w * stride_logits;
     float *d = dz + w * stride_dz;
     const float inv_b = 1.0f / (float)B;
-    float part = 0.f;
-    for (int s = chunk * 256 + tid; s < B; s += chunks * 256) {
-        const float *zs = z + (int64_t)s * C;
-        float m = zs[0];
-        for (int c = 1; c < C; ++c) m = fmaxf(m, zs[c]);
-        float sum = 0.f;
-        for (int c = 0; c < C; ++c) sum += expf(zs[c] - m);
-        int label = y[(int64_t)w * B + s];
-        if (label < 0 || label >= C) {                  // clamped for memory safety, reported by dbw_check
-            *err = DBW_ERR_INVALID;
-            label = label < 0 ? 0 : C - 1;
-        }
-        const float inv = 1.0f / sum;
-        if (LOSS == DBW_LOSS_XENT) {
-            for (int c = 0; c < C; ++c)
-                d[(int64_t)s * C + c] = (expf(zs[c] - m) * inv - (c == label ? 1.f : 0.f)) * inv_b;
-            part += logf(sum) + m - zs[label];
-        } else {
-            float f = 0.f, inner = 0.f;
-            for (int c = 0; c < C; ++c) {
-                const float p = expf(zs[c] - m) * inv, e = p - (c == label ? 1.f : 0.f);
-                f += e * e;
-                inner += p * e;
+    auto add = [](float a, float b) { return a + b; };
+    float part = 0.f;                                   // of this lane's samples; the same in the lanes of a sample
+    for (int s0 = chunk * 256; s0 < B; s0 += chunks * 256)
+        for (int s = s0 + tid / LOSS_LANES; s < min(B, s0 + 256); s += AT_ONCE) {
+            const float *zs = z + (int64_t)s * C;
+            float m = -INFINITY;
+            for (int c = l; c < C; c += LOSS_LANES) m = fmaxf(m, zs[c]);
+            m = loss_lanes(m, [](float a, float b) { return fmaxf(a, b); });
+            float sum = 0.f;
+            for (int c = l; c < C; c += LOSS_LANES) sum += expf(zs[c] - m);
+            sum = loss_lanes(sum, add);
+            int label = y[(int64_t)w * B + s];
+            if (label < 0 || label >= C) {              // clamped for memory safety, reported by dbw_check
+                *err = DBW_ERR_INVALID;
+                label = label < 0 ? 0 : C - 1;
             }
-            for (int c = 0; c < C; ++c) {
-                const float p = expf(zs[c] - m) * inv, e = p - (c == label ? 1.f : 0.f);
-                d[(int64_t)s * C + c] = 2.f * p * (e - inner) * inv_b;
+            const float inv = 1.0f / sum;
+            if (LOSS == DBW_LOSS_XENT) {
+                for (int c = l; c < C; c += LOSS_LANES)
+                    d[(int64_t)s * C + c] = (expf(zs[c] - m) * inv - (c == label ? 1.f : 0.f)) * inv_b;
+                part += logf(sum) + m - zs[label];
+            } else {
+                float f = 0.f, inner = 0.f;
+                for (int c = l; c < C; c += LOSS_LANES) {
+                    const float p = expf(zs[c] - m) * inv, e = p - (c == label ? 1.f : 0.f);
+                    f += e * e;
+                    inner += p * e;
+                }
+                f = loss_lanes(f, add);
+                inner = loss_lanes(inner, add);
+                for (int c = l; c < C; c += LOSS_LANES) {
+                    const float p = expf(zs[c] - m) * inv, e = p - (c == label ? 1.f : 0.f);
+                    d[(int64_t)s * C + c] = 2.f * p * (e - inner) * inv_b;
+                }
+                part += f;
             }
-            part += f;
         }
-    }
     if (!loss) return;                                  // uniform: nobody asked for the loss
-    red[tid] = part;
+    part += __shfl_xor(part, 16, 64);                   // the samples of a wavefront, then the wavefronts, in a fixed order
+    part += __shfl_xor(part, 32, 64);
+    if (tid % 64 == 0) red[tid / 64] = part;
     __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if (tid < o) red[tid] += red[tid + o];
-        __syncthreads();
-    }
+    if (tid == 0)
+        for (int q = 1; q < LOSS_THREADS / 64; ++q) red[0] += red[q];
     if (chunks == 1) {
         if (tid == 0) loss[w] = red[0] * inv_b;
         return;
@@ -585,10 +602,10 @@ int dbw_fc_forward_backward(dbw_ctx *c, dbw_fc_args &a, hipStream_t s)
         const dim3 grid(chunks, N);
         dbw_timer tm(c, "softmax_loss_kernel", s);
         if (a.loss_kind == DBW_LOSS_MSE)
-            hipLaunchKernelGGL(softmax_loss_kernel<DBW_LOSS_MSE>, grid, dim3(256), 0, s, B, dims[L], act + a_off[L], wstride,
+            hipLaunchKernelGGL(softmax_loss_kernel<DBW_LOSS_MSE>, grid, dim3(LOSS_THREADS), 0, s, B, dims[L], act + a_off[L], wstride,
                                a.y, act + dz_off[L], wstride, a.loss, c->loss_part, c->loss_ticket, c->err);
         else
-            hipLaunchKernelGGL(softmax_loss_kernel<DBW_LOSS_XENT>, grid, dim3(256), 0, s, B, dims[L], act + a_off[L], wstride,
+            hipLaunchKernelGGL(softmax_loss_kernel<DBW_LOSS_XENT>, grid, dim3(LOSS_THREADS), 0, s, B, dims[L], act + a_off[L], wstride,
                                a.y, act + dz_off[L], wstride, a.loss, c->loss_part, c->loss_ticket, c->err);
         DBW_HIP(hipGetLastError());
     }
