@@ -11,12 +11,15 @@
 // (prepare_kernel) and stream through LDS, two taps (or four) at a time, by loads that bypass the registers.
 //
 // The 32 columns of a fragment are eight 2 x 2 pooling windows, four lanes each: ReLU, pooling and the window
-// codes need three moves inside a quad of lanes.
+// codes need moves inside a quad of lanes only.
 //
 // What bounds it, at 64 workers x 32 samples, 32 -> 64 channels, 16 x 16 pixels (53.7 GFLOP, six times that in bf16):
-// forward 250 us = 1.29 PFLOP/s of bf16, about what this card sustains on this instruction with operands from LDS (a
-// register-resident loop reaches 1.87); the data gradient, with 32 output rows per wave, reads 9 KB of LDS per 12
-// matrix instructions and comes to 254.  The fp32 kernels they replace took 433 and 447 us (122 TFLOP/s).
+// forward 239 us = 1.35 PFLOP/s of bf16 (a register-resident loop reaches 1.87); the data gradient, with 32 output rows per
+// wave, reads 9 KB of LDS per 12 matrix instructions and comes to 232.  The fp32 kernels they replace took 433 and 447 us
+// (122 TFLOP/s).  Of a workgroup's 64 us 50 are the products, which run at about 80 % of that loop, 4 the first copy of the image
+// and the rest the epilogue, which two workgroups of a compute unit tend to reach together: with the four pixels of a window brought into
+// one lane per channel (quad_transpose) a maximum is taken once instead of in all four lanes, and rows are stored in pairs of
+// pixels (248 and 246 us before; 32 x 32, 16 -> 32 channels on 16 x 16, 3 x 3: 28 -> 26.5 and 38 -> 35).
 //
 // Where a sum is not finite, a workgroup (a wave of first_kernel) multiplies a second time: the small partial products, what is not
 // finite of them dropped, then the large ones.  With one infinite weight of conv2 in every one of those 64 workers a round takes
@@ -142,9 +145,25 @@ struct FwdArgs {
 };
 
 template <int CTRL>
-__device__ __forceinline__ float quad(float v)        // the value of lane CTRL / 0x55 of the quad
+__device__ __forceinline__ float quad(float v)        // v of the quad's lanes in the order that CTRL gives
 {
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
+}
+
+// v[i] of lane j of a quad <-> v[j] of lane i
+__device__ __forceinline__ void quad_transpose(float (&v)[4], int lane)
+{
+    auto exchange = [](float &x, float &y, bool upper, auto ctrl) {       // (the moves with all lanes, outside of the selects)
+        const float px = quad<decltype(ctrl)::value>(x), py = quad<decltype(ctrl)::value>(y);
+        x = upper ? py : x;
+        y = upper ? y : px;
+    };
+    const std::integral_constant<int, 0xB1> xor1;
+    const std::integral_constant<int, 0x4E> xor2;
+    exchange(v[0], v[1], lane & 1, xor1);
+    exchange(v[2], v[3], lane & 1, xor1);
+    exchange(v[0], v[2], lane & 2, xor2);
+    exchange(v[1], v[3], lane & 2, xor2);
 }
 
 // 64 x 16 bytes from global memory to LDS; the caller waits for them (see mix_split.h).
@@ -320,38 +339,33 @@ __global__ __launch_bounds__(THREADS, 2) void forward_kernel(FwdArgs a)
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int c0 = m0 + 32 * mb + 8 * k + 4 * (lane >> 5);
-            float bv[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) bv[i] = a.bias && c0 + i < a.s.Cout ? a.bias[w * a.bias_stride + c0 + i] : 0.f;
+            const int co = c0 + (lane & 3);
+            const float bv = a.bias && co < a.s.Cout ? a.bias[w * a.bias_stride + co] : 0.f;
 #pragma unroll
             for (int nb = 0; nb < 2; ++nb) {
-                const int64_t sample = (int64_t)(b0 + smp[nb]) * a.s.Cout;
+                // a pixel of four channels in every lane of a quad -> the four pixels of channel `co` in each
+                float v[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[i] = acc[mb][nb][4 * k + i];
+                quad_transpose(v, lane);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[i] += bv;
+                const int64_t row = (int64_t)(b0 + smp[nb]) * a.s.Cout + co;
                 if (POOL) {
-                    // every lane of the quad holds the window's result for the four channels; it stores one of them
-                    float m = 0.f;
-                    int arg = 4;
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const float v = acc[mb][nb][4 * k + i] + bv[i];
-                        const float v0 = quad<0x00>(v), v1 = quad<0x55>(v), v2 = quad<0xAA>(v), v3 = quad<0xFF>(v);
-                        const float mx = fmaxf(fmaxf(v0, v1), fmaxf(v2, v3));
-                        int ai = v2 == mx ? 2 : 3;
-                        ai = v1 == mx ? 1 : ai;
-                        ai = v0 == mx ? 0 : ai;
-                        ai = mx > 0.f ? ai : 4;
-                        m = (lane & 3) == i ? fmaxf(mx, 0.f) : m;
-                        arg = (lane & 3) == i ? ai : arg;
-                    }
-                    const int co = c0 + (lane & 3);
+                    const float mx = fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3]));
+                    int arg = v[2] == mx ? 2 : 3;
+                    arg = v[1] == mx ? 1 : arg;
+                    arg = v[0] == mx ? 0 : arg;
+                    arg = mx > 0.f ? arg : 4;
                     if (smp[nb] >= 0 && co < a.s.Cout) {
-                        ob[(sample + co) * PP + win[nb]] = m;
-                        a.code[w * a.code_stride + (sample + co) * PP + win[nb]] = (uint8_t)arg;
+                        ob[row * PP + win[nb]] = fmaxf(mx, 0.f);
+                        a.code[w * a.code_stride + row * PP + win[nb]] = (uint8_t)arg;
                     }
-                } else if (smp[nb] >= 0) {
-                    const int y = 2 * (win[nb] / (W / 2)) + (lane >> 1 & 1), x = 2 * (win[nb] % (W / 2)) + (lane & 1);
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        if (c0 + i < a.s.Cout) ob[(sample + c0 + i) * HW + y * W + x] = acc[mb][nb][4 * k + i] + bv[i];
+                } else if (smp[nb] >= 0 && co < a.s.Cout) {
+                    typedef float f32x2_any __attribute__((ext_vector_type(2), aligned(4)));
+                    float *o = ob + row * HW + 2 * (win[nb] / (W / 2)) * W + 2 * (win[nb] % (W / 2));
+                    *(f32x2_any *)o = f32x2_any{v[0], v[1]};
+                    *(f32x2_any *)(o + W) = f32x2_any{v[2], v[3]};
                 }
             }
         }
