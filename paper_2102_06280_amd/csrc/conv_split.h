@@ -21,6 +21,12 @@
 // one lane per channel (quad_transpose) a maximum is taken once instead of in all four lanes, and rows are stored in pairs of
 // pixels (248 and 246 us before; 32 x 32, 16 -> 32 channels on 16 x 16, 3 x 3: 28 -> 26.5 and 38 -> 35).
 //
+// Up to sixteen output channels (of the forward pass, or the first layer's in the data gradient) would leave half of a 32-row block
+// empty: there a wave multiplies 16 x 16 outputs over 32 values, which are the sixteen channels of two taps.  It reads 15 KB of
+// LDS per 24 instructions of half the time, which then bounds it.  Data gradient, 32-row blocks / this: 16 x 50, 16 <- 32 channels on
+// 14 x 14, 5 x 5: 65 / 50 us; 32 x 32, 16 <- 32 on 16 x 16, 3 x 3: 35 / 31; 32 x 32, 12 <- 24 on 10 x 10, 3 x 3: 19.7 / 18.4;
+// a round of 64 x 64, 32 -> 16 on 16 x 16, 5 x 5 (the forward pass): 1075 / 981.  From seventeen rows on half of a block is used at least.
+//
 // Where a sum is not finite, a workgroup (a wave of first_kernel) multiplies a second time: the small partial products, what is not
 // finite of them dropped, then the large ones.  With one infinite weight of conv2 in every one of those 64 workers a round takes
 // 2.04 ms and with nothing but NaN 2.2 (1.65 with finite values).
@@ -59,15 +65,20 @@ __host__ __device__ inline int samples_per_group(const Shape &s)
     return t >= WINDOWS ? 1 : WINDOWS / t;
 }
 __host__ __device__ inline int positions(const Shape &s) { return (s.H + s.KS - 1) * pitch(s); }
-constexpr int chunk_taps(int MB) { return MB == 1 ? 4 : 2; }
+// MB: 32-row blocks of output channels per workgroup, 0 where sixteen rows are all there are.  A step of the reduction is one tap of
+// sixteen channels, with sixteen rows two of them (the last tap meets zeros); a chunk is the steps whose filters are in LDS at a time.
+__host__ __device__ constexpr int step_taps(int Cout) { return Cout <= 16 ? 2 : 1; }
+inline int forward_blocks(int Cout) { return Cout <= 16 ? 0 : (Cout <= 32 ? 1 : 2); }
+constexpr int chunk_steps(int MB) { return MB == 1 ? 4 : 2; }
 inline size_t forward_lds(const Shape &s, int MB)
 {
-    return 16 * ((size_t)6 * samples_per_group(s) * positions(s) + (size_t)2 * chunk_taps(MB) * MB * 192);
+    return 16 * ((size_t)6 * samples_per_group(s) * positions(s) + (size_t)2 * chunk_steps(MB) * (MB ? MB : 1) * 192);
 }
 
-// Filters in fragment order: [worker][16-channel group][tap][32-row block][plane][lane][8 values].
+// Filters in fragment order: [worker][16-channel group][step][32-row block][plane][lane][8 values].
+__host__ __device__ inline int group_steps(int Cout, int KK) { return (KK + step_taps(Cout) - 1) / step_taps(Cout); }
 __host__ __device__ inline int row_blocks(int Cout) { return Cout <= 32 ? 1 : (Cout + 63) / 64 * 2; }
-inline int64_t filter_floats(int Cin, int Cout, int KS) { return (int64_t)((Cin + 15) / 16) * KS * KS * row_blocks(Cout) * 768; }
+inline int64_t filter_floats(int Cin, int Cout, int KS) { return (int64_t)((Cin + 15) / 16) * group_steps(Cout, KS * KS) * row_blocks(Cout) * 768; }
 
 // src: filters [C2][C1][KK] of a convolution C1 -> C2, in its forward order (rows = C2, reduction over C1), or in that
 // of its data gradient (rows = C1, reduction over C2, taps reversed).  A workgroup brings the filters of 32 rows x 16
@@ -102,13 +113,20 @@ __device__ __forceinline__ void prepare(float *tile /* LDS [16 channels][32 rows
         if (e < 512 * KK) tile[(ch * 32 + row) * KK + i % KK] = f[u];
     }
     __syncthreads();
-    for (int e = tid; e < KK * 64; e += PREPARE_THREADS) {
-        const int lane = e % 64, tap = e / 64;
+    const int rows = FLIP ? C1 : C2, steps = group_steps(rows, KK);
+    const bool two = step_taps(rows) == 2;
+    for (int e = tid; e < steps * 64; e += PREPARE_THREADS) {
+        const int lane = e % 64, step = e / 64;
+        const int tap = two ? 2 * step + lane / 32 : step, ch = two ? lane / 16 % 2 : lane / 32, row = two ? lane % 16 : lane % 32;
+        const int t = min(tap, KK - 1);
         float v[8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = tile[((8 * (lane / 32) + j) * 32 + lane % 32) * KK + (FLIP ? KK - 1 - tap : tap)];
+        for (int j = 0; j < 8; ++j) {
+            const float f = tile[((8 * ch + j) * 32 + row) * KK + (FLIP ? KK - 1 - t : t)];
+            v[j] = tap < KK ? f : 0.f;
+        }
         const planes p = split_bf16::split8_nearest(v);
-        u32x4 *at = d + ((int64_t)(g * KK + tap) * mbt + mb) * 192 + lane;
+        u32x4 *at = d + ((int64_t)(g * steps + step) * mbt + mb) * 192 + lane;
         at[0] = p.h;
         at[64] = p.m;
         at[128] = p.l;
@@ -173,13 +191,16 @@ __device__ __forceinline__ void load_to_lds(const u32x4 *src, const u32x4 *dst)
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(m0) : "memory");
 }
 
-// grid = (ceil(B / samples_per_group) x ceil(windows of a sample / 64 if there is one sample), workers, row blocks / MB);
+// grid = (ceil(B / samples_per_group) x ceil(windows of a sample / 64 if there is one sample), workers, row blocks / MB or 1);
 // dynamic LDS = forward_lds.
 template <int MB, bool POOL, bool EXPAND>
 __global__ __launch_bounds__(THREADS, 2) void forward_kernel(FwdArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) u32x4 sm[];
-    constexpr int TCH = chunk_taps(MB);
+    constexpr bool SIXTEEN = MB == 0;                 // rows: matrix instructions of 16 x 16 outputs over two taps
+    constexpr int TCH = chunk_steps(MB), RB = SIXTEEN ? 1 : MB, COLS = SIXTEEN ? 16 : 32, NB = 64 / COLS;
+    using Acc = std::conditional_t<SIXTEEN, split_bf16::f32x4, f32x16>;
+    constexpr int REGS = sizeof(Acc) / 4;
     const int H = a.s.H, W = a.s.W, KS = a.s.KS, KK = KS * KS, HW = H * W, T = HW / 4, WP = pitch(a.s), POS = positions(a.s);
     const int spg = samples_per_group(a.s), xt = spg > 1 ? 1 : (T + WINDOWS - 1) / WINDOWS;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -188,39 +209,39 @@ __global__ __launch_bounds__(THREADS, 2) void forward_kernel(FwdArgs a)
     const int half = spg * POS, plane = 2 * half;     // 16-byte groups of eight channels / of a plane
     u32x4 *img = sm, *wb = sm + 3 * plane;
 
-    const int groups = (a.s.Cin + 15) / 16, mbt = row_blocks(a.s.Cout), cpg = (KK + TCH - 1) / TCH, chunks = groups * cpg;
-    const u32x4 *fl = a.filters + w * a.filters_stride + blockIdx.z * MB * 192 + lane;
+    const int groups = (a.s.Cin + 15) / 16, mbt = row_blocks(a.s.Cout), gs = group_steps(a.s.Cout, KK), cpg = (gs + TCH - 1) / TCH, chunks = groups * cpg;
+    const u32x4 *fl = a.filters + w * a.filters_stride + blockIdx.z * RB * 192 + lane;
     auto fetch = [&](int c) {                          // chunk c of the filters, a quarter of it by each wave
-        const int t0 = c % cpg * TCH, n = min(TCH, KK - t0) * MB * 3;
-        const int64_t first = (int64_t)(c / cpg * KK + t0) * mbt * 192;
+        const int t0 = c % cpg * TCH, n = min(TCH, gs - t0) * RB * 3;
+        const int64_t first = (int64_t)(c / cpg * gs + t0) * mbt * 192;
 #pragma unroll
-        for (int u = 0; u < TCH * MB * 3 / 4; ++u) {
+        for (int u = 0; u < (TCH * RB * 3 + 3) / 4; ++u) {
             const int i = wave + 4 * u;
-            if (i < n) load_to_lds(fl + first + (int64_t)(i / (MB * 3)) * mbt * 192 + i % (MB * 3) * 64, wb + (c & 1) * TCH * MB * 192 + i * 64);
+            if (i < n) load_to_lds(fl + first + (int64_t)(i / (RB * 3)) * mbt * 192 + i % (RB * 3) * 64, wb + (c & 1) * TCH * RB * 192 + i * 64);
         }
     };
     fetch(0);
     for (int e = tid; e < 3 * plane; e += THREADS) img[e] = u32x4{0u, 0u, 0u, 0u};       // the halo stays zero
 
-    // this lane's pixel in each of the two blocks: four lanes per window
-    int pos[2], smp[2], win[2];
+    // this lane's pixel in each of the blocks of columns: four lanes per window
+    int pos[NB], smp[NB], win[NB];
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
-        const int q = q0 + 8 * (2 * wave + nb) + (lane % 32) / 4;
+    for (int nb = 0; nb < NB; ++nb) {
+        const int q = q0 + COLS / 4 * (NB * wave + nb) + lane % COLS / 4;
         smp[nb] = spg > 1 ? q / T : 0;
         win[nb] = spg > 1 ? q % T : q;
         if (smp[nb] >= nb_s || win[nb] >= T) smp[nb] = -1;                                // beyond the samples: never stored
         const int wy = win[nb] / (W / 2), wx = win[nb] % (W / 2);
-        pos[nb] = (smp[nb] < 0 ? 0 : smp[nb] * POS + (2 * wy + (lane >> 1 & 1)) * WP + 2 * wx + (lane & 1)) + (lane >> 5) * half;
+        pos[nb] = (smp[nb] < 0 ? 0 : smp[nb] * POS + (2 * wy + (lane >> 1 & 1)) * WP + 2 * wx + (lane & 1)) + lane / COLS % 2 * half;
     }
-    f32x16 acc[MB][2];
+    Acc acc[RB][NB];
     auto zero = [&] {
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
+        for (int mb = 0; mb < RB; ++mb)
 #pragma unroll
-            for (int nb = 0; nb < 2; ++nb)
+            for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) acc[mb][nb][v] = 0.f;
+                for (int v = 0; v < REGS; ++v) acc[mb][nb][v] = 0.f;
     };
     zero();
 
@@ -284,24 +305,31 @@ __global__ __launch_bounds__(THREADS, 2) void forward_kernel(FwdArgs a)
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
             if (c + 1 < chunks) fetch(c + 1);
-            const int t0 = c % cpg * TCH, nt = min(TCH, KK - t0);
-            const u32x4 *wc = wb + (c & 1) * TCH * MB * 192 + lane;
+            const int t0 = c % cpg * TCH, nt = min(TCH, gs - t0);
+            const u32x4 *wc = wb + (c & 1) * TCH * RB * 192 + lane;
 #pragma unroll
             for (int t = 0; t < TCH; ++t) {
                 if (t < nt) {
-                    const int off = (t0 + t) / KS * WP + (t0 + t) % KS;
-                    planes fa[MB], fb[2];
+                    auto offset = [&](int tap) { return tap / KS * WP + tap % KS; };
+                    int off = offset(step_taps(SIXTEEN ? 16 : 32) * (t0 + t));
+                    bool none = false;                 // behind the last tap: the first position, which is halo
+                    if (SIXTEEN) {
+                        const int second = 2 * (t0 + t) + 1;
+                        none = lane >= 32 && second == KK;
+                        off = lane >= 32 ? offset(second) : off;
+                    }
+                    planes fa[RB], fb[NB];
 #pragma unroll
-                    for (int mb = 0; mb < MB; ++mb) {
-                        const u32x4 *p = wc + (t * MB + mb) * 192;
+                    for (int mb = 0; mb < RB; ++mb) {
+                        const u32x4 *p = wc + (t * RB + mb) * 192;
                         fa[mb] = planes{p[0], p[64], p[128]};
                     }
 #pragma unroll
-                    for (int nb = 0; nb < 2; ++nb) {
-                        const u32x4 *p = img + pos[nb] + off;
+                    for (int nb = 0; nb < NB; ++nb) {
+                        const u32x4 *p = img + (none ? 0 : pos[nb] + off);
                         fb[nb] = planes{p[0], p[plane], p[2 * plane]};
                     }
-                    split_bf16::mma32_block<decltype(small)::value, decltype(large)::value>(fa, fb, acc);
+                    split_bf16::mma_block<decltype(small)::value, decltype(large)::value>(fa, fb, acc);
                 }
             }
         }
@@ -310,10 +338,10 @@ __global__ __launch_bounds__(THREADS, 2) void forward_kernel(FwdArgs a)
     // ---- some sum of the workgroup is not finite: again, in the order that tells infinities from NaN (see split_bf16.h)
     bool bad = false;
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
+    for (int mb = 0; mb < RB; ++mb)
 #pragma unroll
-        for (int nb = 0; nb < 2; ++nb) bad |= smp[nb] >= 0 && split_bf16::any_not_finite(acc[mb][nb]);
-    int *votes = (int *)(wb + (chunks & 1) * TCH * MB * 192);     // in the half of the filters that nobody reads any more
+        for (int nb = 0; nb < NB; ++nb) bad |= smp[nb] >= 0 && split_bf16::any_not_finite(acc[mb][nb]);
+    int *votes = (int *)(wb + (chunks & 1) * TCH * RB * 192);     // in the half of the filters that nobody reads any more
     const int vote = __any(bad);
     if (lane == 0) votes[wave] = vote;
     __syncthreads();
@@ -323,26 +351,26 @@ __global__ __launch_bounds__(THREADS, 2) void forward_kernel(FwdArgs a)
         zero();
         products(std::true_type{}, std::false_type{});
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
+        for (int mb = 0; mb < RB; ++mb)
 #pragma unroll
-            for (int nb = 0; nb < 2; ++nb) split_bf16::drop_not_finite(acc[mb][nb]);
+            for (int nb = 0; nb < NB; ++nb) split_bf16::drop_not_finite(acc[mb][nb]);
         __syncthreads();                               // the filters have been used
         fetch(0);
         products(std::false_type{}, std::true_type{});
     }
 
-    // ---- epilogue.  Register v of a lane: output channel 32 mb + 8 (v / 4) + 4 (lane / 32) + v % 4, the lane's pixel.
+    // ---- epilogue.  Register v of a lane: output channel 32 mb + 8 (v / 4) + 4 (lane / 32) + v % 4 (SIXTEEN: 4 (lane / 16) + v), the lane's pixel.
     const int m0 = 32 * MB * blockIdx.z, PP = T;
     float *ob = a.out + w * a.out_stride;
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
+    for (int mb = 0; mb < RB; ++mb)
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int c0 = m0 + 32 * mb + 8 * k + 4 * (lane >> 5);
+        for (int k = 0; k < REGS / 4; ++k) {
+            const int c0 = m0 + 32 * mb + 8 * k + 4 * (lane / COLS);
             const int co = c0 + (lane & 3);
             const float bv = a.bias && co < a.s.Cout ? a.bias[w * a.bias_stride + co] : 0.f;
 #pragma unroll
-            for (int nb = 0; nb < 2; ++nb) {
+            for (int nb = 0; nb < NB; ++nb) {
                 // a pixel of four channels in every lane of a quad -> the four pixels of channel `co` in each
                 float v[4];
 #pragma unroll

@@ -426,10 +426,12 @@ int launch_split_forward(const convsplit::FwdArgs &a, int workers, hipStream_t s
 {
     const int spg = convsplit::samples_per_group(a.s), t = a.s.H * a.s.W / 4;
     const int xt = spg > 1 ? 1 : (t + convsplit::WINDOWS - 1) / convsplit::WINDOWS, mbt = convsplit::row_blocks(a.s.Cout);
-    const int MB = mbt == 1 ? 1 : 2;
-    const dim3 grid((a.s.B + spg - 1) / spg * xt, workers, mbt / MB);
+    const int MB = convsplit::forward_blocks(a.s.Cout);
+    const dim3 grid((a.s.B + spg - 1) / spg * xt, workers, MB == 2 ? mbt / 2 : 1);
     const size_t lds = convsplit::forward_lds(a.s, MB);
-    if (MB == 1)
+    if (MB == 0)
+        hipLaunchKernelGGL((convsplit::forward_kernel<0, POOL, EXPAND>), grid, dim3(convsplit::THREADS), lds, s, a);
+    else if (MB == 1)
         hipLaunchKernelGGL((convsplit::forward_kernel<1, POOL, EXPAND>), grid, dim3(convsplit::THREADS), lds, s, a);
     else
         hipLaunchKernelGGL((convsplit::forward_kernel<2, POOL, EXPAND>), grid, dim3(convsplit::THREADS), lds, s, a);
@@ -657,7 +659,8 @@ size_t dbw_cnn_scratch_floats(const dbw_ctx *c) { return (size_t)make_layout(c->
 
 int dbw_cnn_prepare()
 {
-    const void *kernels[] = {(const void *)convsplit::forward_kernel<1, true, false>, (const void *)convsplit::forward_kernel<2, true, false>,
+    const void *kernels[] = {(const void *)convsplit::forward_kernel<0, true, false>, (const void *)convsplit::forward_kernel<0, false, true>,
+                             (const void *)convsplit::forward_kernel<1, true, false>, (const void *)convsplit::forward_kernel<2, true, false>,
                              (const void *)convsplit::forward_kernel<1, false, true>, (const void *)convsplit::forward_kernel<2, false, true>,
                              (const void *)convsplit::first_kernel<3>, (const void *)convsplit::first_kernel<5>,
                              (const void *)convsplit::wgrad_kernel<3>, (const void *)convsplit::wgrad_kernel<5>};

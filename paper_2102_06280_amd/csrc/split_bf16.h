@@ -30,6 +30,7 @@
 
 namespace split_bf16 {
 
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -138,17 +139,26 @@ __device__ __forceinline__ void mma32(const planes &a, const planes &b, f32x16 &
     small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(a.h), frag(b.m), small, 0, 0, 0);
 }
 
+// one matrix instruction: 32 x 32 outputs over 16 terms, or 16 x 16 over 32 (lane l: row or column l % 16, terms 8 (l / 16) .. + 7)
+__device__ __forceinline__ void mma(const u32x4 &a, const u32x4 &b, f32x16 &acc)
+{
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(a), frag(b), acc, 0, 0, 0);
+}
+__device__ __forceinline__ void mma(const u32x4 &a, const u32x4 &b, f32x4 &acc)
+{
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag(a), frag(b), acc, 0, 0, 0);
+}
+
 // Six partial products (or the five small ones, or the large one) for a block of A x B accumulators, one kind after the other,
 // the large one last: consecutive instructions are independent.
-template <bool SMALL, bool LARGE, int A, int B>
-__device__ __forceinline__ void mma32_block(const planes (&a)[A], const planes (&b)[B], f32x16 (&acc)[A][B])
+template <bool SMALL, bool LARGE, int A, int B, class Acc>
+__device__ __forceinline__ void mma_block(const planes (&a)[A], const planes (&b)[B], Acc (&acc)[A][B])
 {
     auto step = [&](u32x4 planes::*pa, u32x4 planes::*pb) {
 #pragma unroll
         for (int i = 0; i < A; ++i)
 #pragma unroll
-            for (int j = 0; j < B; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(a[i].*pa), frag(b[j].*pb), acc[i][j], 0, 0, 0);
+            for (int j = 0; j < B; ++j) mma(a[i].*pa, b[j].*pb, acc[i][j]);
     };
     if (SMALL) {
         step(&planes::l, &planes::h);
@@ -164,11 +174,12 @@ __device__ __forceinline__ void mma32_block(const planes (&a)[A], const planes (
 __device__ __forceinline__ bool not_finite(float v) { return (bits(v) & 0x7f800000u) == 0x7f800000u; }
 
 // whether any value of an accumulator is NaN or infinite (0 * v is NaN then)
-__device__ __forceinline__ bool any_not_finite(const f32x16 &acc)
+template <class Acc>
+__device__ __forceinline__ bool any_not_finite(const Acc &acc)
 {
     float t = 0.f;
 #pragma unroll
-    for (int v = 0; v < 16; ++v) t = fmaf(acc[v], 0.f, t);
+    for (int v = 0; v < (int)(sizeof(Acc) / 4); ++v) t = fmaf(acc[v], 0.f, t);
     return t != t;
 }
 
@@ -187,10 +198,11 @@ __device__ __forceinline__ void add_small(f32x16 &large, const f32x16 &small)
 
 // The same where one accumulator is all there is room for: the small partial products of the whole reduction first, then this, then the
 // large ones on top.
-__device__ __forceinline__ void drop_not_finite(f32x16 &small)
+template <class Acc>
+__device__ __forceinline__ void drop_not_finite(Acc &small)
 {
 #pragma unroll
-    for (int v = 0; v < 16; ++v) small[v] = not_finite(small[v]) ? 0.f : small[v];
+    for (int v = 0; v < (int)(sizeof(Acc) / 4); ++v) small[v] = not_finite(small[v]) ? 0.f : small[v];
 }
 
 }  // namespace split_bf16
