@@ -655,9 +655,9 @@ __global__ __launch_bounds__(THREADS, 2) void first_kernel(FwdArgs a, FirstPlan 
 // and add their sums through LDS in wave order.  Every workgroup writes a partial result:
 // part[worker][split][co][c][kh][kw], summed in split order by a separate pass.
 //
-// 64 workers x 32 samples, 32 -> 64 channels, 16 x 16 pixels: 274 us (an fp32 kernel 427); ten blocks on the four
-// SIMDs of a compute unit are three rounds of 2.5, and LDS holds one workgroup.  16 workers x 50 samples: 1 -> 16
-// channels on 28 x 28 pixels 73 us, 16 -> 32 on 14 x 14 60 us (implicit fp32 GEMM: 176 and 231).
+// 64 workers x 32 samples, 32 -> 64 channels, 16 x 16 pixels: 250 us (an fp32 kernel 427); ten blocks on the four
+// SIMDs of a compute unit are three rounds of 2.5, and LDS holds one workgroup.  16 workers x 50 samples, 16 -> 32 channels on
+// 14 x 14: 53 us (implicit fp32 GEMM: 231).
 struct WgradPlan {
     int mb, nb, units;          // 32-row and 32-column blocks
     int kw, waves, groups;      // waves that share a block, waves of a workgroup, workgroups along the blocks
@@ -679,8 +679,7 @@ inline bool wgrad_plan(const Shape &s, int workers, WgradPlan &p)
     p.units = p.mb * p.nb;
     // Eight wavefronts for few blocks: more of them hide the copies and splits, which a workgroup does between barriers, but
     // their sums meet in LDS.  No number is the best everywhere (four / eight / twelve waves, us): 3 x 3, 32 -> 32 channels on
-    // 8 x 8 224, 188, 208, 16 -> 16 on 16 x 16 171, 158, 215; 5 x 5, 3 -> 32 on 32 x 32 with four blocks 89, 89, 73;
-    // one channel 5 x 5 on 28 x 28 48, 73, 88 (16 workers) and 279, 285, 296 (100).
+    // 8 x 8 224, 188, 208, 16 -> 16 on 16 x 16 171, 158, 215.
     p.kw = p.units >= 5 ? 1 : 8 / p.units;
     p.groups = (p.units + WGRAD_MAX_WAVES - 1) / WGRAD_MAX_WAVES;
     p.waves = (p.units + p.groups - 1) / p.groups * p.kw;
@@ -702,10 +701,12 @@ inline bool wgrad_plan(const Shape &s, int workers, WgradPlan &p)
     p.lds = img + wgrad_delta_lds(s, p.mb, p.rows);
     const size_t sums = p.kw > 1 ? sizeof(float) * 64 * 16 * s.KS * (p.waves / p.kw) : 0;
     if (p.lds < sums) p.lds = sums;
-    // enough workgroups for the chip, and no more partial results than that needs.  A workgroup of up to eight samples: with
+    // enough workgroups for the chip, and no more partial results than that needs: samples are given out by the ceiling, so that one turn
+    // holds all workgroups (by the floor, 16 x 50, 16 -> 32 channels on 14 x 14 59.4 us and 14.7 for the sums, 52.7 and 12.1 now; 50 x 20,
+    // 32 -> 24 on 14 x 14, 3 x 3: the round 343, 322).  A workgroup of up to eight samples: with
     // four 5 x 5, 32 -> 64 on 16 x 16 takes 267 us and 46 for the sums (255 and 43), 3 x 3 1 -> 8 channels 45 (40); with sixteen
     // the last turn of workgroups is the emptier (16 -> 32 on 14 x 14 288 against 258, 32 -> 16 on 16 x 16 511 against 342)
-    p.sb = (int)((int64_t)s.B * workers * p.groups / (256 * per_cu));
+    p.sb = (int)(((int64_t)s.B * workers * p.groups + 256 * per_cu - 1) / (256 * per_cu));
     p.sb = p.sb < 1 ? 1 : (p.sb > 8 ? 8 : p.sb);
     p.splits = (s.B + p.sb - 1) / p.sb;
     return true;
