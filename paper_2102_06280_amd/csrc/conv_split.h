@@ -657,12 +657,13 @@ __global__ __launch_bounds__(THREADS, 2) void first_kernel(FwdArgs a, FirstPlan 
 //
 // 64 workers x 32 samples, 32 -> 64 channels, 16 x 16 pixels: 250 us (an fp32 kernel 427); ten blocks on the four
 // SIMDs of a compute unit are three rounds of 2.5, and LDS holds one workgroup.  16 workers x 50 samples, 16 -> 32 channels on
-// 14 x 14: 53 us (implicit fp32 GEMM: 231).
+// 14 x 14: 46 us (implicit fp32 GEMM: 231).
 struct WgradPlan {
     int mb, nb, units;          // 32-row and 32-column blocks
     int kw, waves, groups;      // waves that share a block, waves of a workgroup, workgroups along the blocks
     int rows, sb;               // image rows per delta tile, samples per workgroup
     int splits;                 // partial results per worker
+    bool paired;                // two workgroups have to fit on a compute unit that would not with 5 x 5 filters' registers
     size_t lds;
 };
 constexpr int WGRAD_MAX_WAVES = 12;
@@ -709,6 +710,11 @@ inline bool wgrad_plan(const Shape &s, int workers, WgradPlan &p)
     p.sb = (int)(((int64_t)s.B * workers * p.groups + 256 * per_cu - 1) / (256 * per_cu));
     p.sb = p.sb < 1 ? 1 : (p.sb > 8 ? 8 : p.sb);
     p.splits = (s.B + p.sb - 1) / p.sb;
+    // The 5 x 5 kernel takes 145 registers, three wavefronts to a SIMD: of two workgroups of five to eight the second finds no place.
+    // Limited to 128 (some 24 bytes per lane go to scratch) both run: 16 x 50, 16 -> 32 on 14 x 14 53.8 -> 45.8 us, the round of 20 x 13,
+    // 32 -> 32 on 10 x 10 184 -> 173.  Where one workgroup is all that a compute unit gets, the limit only costs: 32 -> 64 on
+    // 16 x 16 248 -> 258, 16 x 16, 8 -> 16 on 12 x 12 14.1 -> 14.7.
+    p.paired = per_cu == 2 && p.waves > 4 && (int64_t)p.splits * workers * p.groups > 256;
     return true;
 }
 
@@ -726,8 +732,8 @@ struct WgradArgs {
 };
 
 // grid = (ceil(B / sb), workers, groups), block = 64 waves; dynamic LDS = plan.lds.
-template <int KS>
-__global__ __launch_bounds__(64 * WGRAD_MAX_WAVES) void wgrad_kernel(WgradArgs a)
+template <int KS, int PER_SIMD>
+__global__ __launch_bounds__(64 * WGRAD_MAX_WAVES, PER_SIMD) void wgrad_kernel(WgradArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) u32x4 sm[];
     typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));

@@ -442,8 +442,9 @@ int launch_split_forward(const convsplit::FwdArgs &a, int workers, hipStream_t s
 int launch_split_wgrad(const convsplit::WgradArgs &a, int workers, hipStream_t s)
 {
     const dim3 grid((a.s.B + a.p.sb - 1) / a.p.sb, workers, a.p.groups), block(64 * a.p.waves);
-    if (a.s.KS == 3) hipLaunchKernelGGL(convsplit::wgrad_kernel<3>, grid, block, a.p.lds, s, a);
-    else hipLaunchKernelGGL(convsplit::wgrad_kernel<5>, grid, block, a.p.lds, s, a);
+    if (a.s.KS == 3) hipLaunchKernelGGL((convsplit::wgrad_kernel<3, 4>), grid, block, a.p.lds, s, a);
+    else if (a.p.paired) hipLaunchKernelGGL((convsplit::wgrad_kernel<5, 4>), grid, block, a.p.lds, s, a);
+    else hipLaunchKernelGGL((convsplit::wgrad_kernel<5, 3>), grid, block, a.p.lds, s, a);
     DBW_HIP(hipGetLastError());
     return DBW_OK;
 }
@@ -663,7 +664,8 @@ int dbw_cnn_prepare()
                              (const void *)convsplit::forward_kernel<1, true, false>, (const void *)convsplit::forward_kernel<2, true, false>,
                              (const void *)convsplit::forward_kernel<1, false, true>, (const void *)convsplit::forward_kernel<2, false, true>,
                              (const void *)convsplit::first_kernel<3>, (const void *)convsplit::first_kernel<5>,
-                             (const void *)convsplit::wgrad_kernel<3>, (const void *)convsplit::wgrad_kernel<5>};
+                             (const void *)convsplit::wgrad_kernel<3, 4>, (const void *)convsplit::wgrad_kernel<5, 3>,
+                             (const void *)convsplit::wgrad_kernel<5, 4>};
     for (const void *k : kernels) DBW_HIP(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
     return DBW_OK;
 }

@@ -1,6 +1,6 @@
 """Gradients of networks whose second layer has few channels, against the oracle: up to sixteen output channels, of the forward pass
 (channels 2) or of the data gradient (channels 1), take matrix instructions of two taps a step, of which the last one's second is none; more take
-one tap.  Channels on both sides of the line, more input channels than one group of sixteen, windows that fill no block."""
+one tap.  Channels on both sides of the line, more input channels than one group of sixteen, windows that fill no block; the last two have the weight gradient's workgroups two to a compute unit."""
 import numpy as np
 import pytest
 import torch
@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 # input channels, height, width, channels 1 and 2, filter, dense, classes; batch
 SHAPES = [((1, 8, 8, 16, 16, 3, 6, 5), 17), ((1, 28, 28, 15, 17, 5, 6, 5), 3), ((2, 12, 20, 17, 15, 3, 6, 5), 4), ((1, 16, 16, 1, 2, 5, 6, 5), 5),
-          ((3, 20, 12, 33, 16, 5, 7, 4), 3), ((1, 12, 12, 16, 40, 3, 6, 5), 6)]
+          ((3, 20, 12, 33, 16, 5, 7, 4), 3), ((1, 12, 12, 16, 40, 3, 6, 5), 6), ((1, 8, 8, 7, 4, 5, 6, 5), 150), ((1, 8, 8, 13, 33, 5, 6, 5), 120)]
 
 
 @pytest.mark.parametrize("shape,batch", SHAPES, ids=["-".join(map(str, s[0])) + f"-b{s[1]}" for s in SHAPES])
