@@ -92,14 +92,14 @@ __global__ __launch_bounds__(LOSS_THREADS) void softmax_loss_kernel(
     part += __shfl_xor(part, 32, 64);
     if (tid % 64 == 0) red[tid / 64] = part;
     __syncthreads();
-    if (tid == 0)
-        for (int q = 1; q < LOSS_THREADS / 64; ++q) red[0] += red[q];
+    static_assert(LOSS_THREADS / 64 == LOSS_LANES, "one value for each lane of a group");
+    part = loss_lanes(red[l], add);
     if (chunks == 1) {
-        if (tid == 0) loss[w] = red[0] * inv_b;
+        if (tid == 0) loss[w] = part * inv_b;
         return;
     }
     if (tid == 0) {
-        __hip_atomic_store(&loss_part[w * chunks + chunk], red[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&loss_part[w * chunks + chunk], part, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __threadfence();                                // the partial sum is visible before the ticket is taken
         if (atomicAdd(&ticket[w], 1u) == (uint32_t)(chunks - 1)) {
             __threadfence();
