@@ -25,9 +25,9 @@ if ROOT not in sys.path:
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E
 MFMA_FP32_PEAK_TFLOPS = 157.3  # MI355X dense fp32 matrix
 MFMA_SPLIT_PEAK_TFLOPS = 2516.6 / 6   # fp32 values as three bf16 values: six dense bf16 matrix instructions for each product
-# Timing names of the kernels that do so.  ("conv2_" and "conv1_forward" also name the fp32 launches of networks whose filters are
+# Timing names of the kernels that do so.  ("conv2_" and "conv1_" also name the fp32 launches of networks whose filters are
 # not 3 x 3 or 5 x 5; no configuration has one.)
-SPLIT_KERNELS = ("mix_dense_split", "mlp_wgrad_gemm", "mlp_dgrad_split", "conv1_forward", "conv2_")
+SPLIT_KERNELS = ("mix_dense_split", "mlp_wgrad_gemm", "mlp_dgrad_split", "conv1_", "conv2_")
 
 
 def measured_traffic(kernel: str, cid: int):
