@@ -14,11 +14,18 @@
 // The four wavefronts of a workgroup take turns with the pixels; their sums meet in LDS at the end.  Every workgroup writes a
 // partial result: part[worker][split][co][taps], summed in split order by a separate pass.
 //
+// Six of the nine partial products are kept, like in the other convolutions.  A wavefront's six instructions of one step start from
+// zero and their result is added to the sum, so that the sum is rounded once in 32 pixels and not six times.  The bf16 instructions cut off
+// what does not fit towards minus infinity, which adds up; the deltas of odd rows therefore enter negated and
+// their steps are subtracted.  Error of dW against 64 bits (2-norm; normal pixels and deltas), fp32 instruction / products added
+// to the sum directly / now: 64 workers x 32 samples, 3 -> 32 channels, 32 x 32 pixels, 5 x 5 2.3e-7 / 3.7e-7 / 1.2e-7; 4 x 8 1.9e-7 / 2.1e-7 /
+// 0.9e-7; conv_split.h's kernel for the first: 16 x 50, 1 -> 16, 28 x 28, 5 x 5 2.5e-7 / 2.5e-7 / 1.5e-7.
+//
 // us, before (conv_split.h's kernel; an fp32 one for the third) / now: 16 workers x 50 samples, 1 -> 16 channels, 28 x 28 pixels, 5 x 5:
-// 73 / 14; 32 x 32, 3 -> 16, 32 x 32, 3 x 3: 39 / 21; 64 x 32, 3 -> 32, 32 x 32, 5 x 5: 114 / 98.  The last has matrix
-// instructions for 28 us; three wavefronts to a SIMD (registers) wait two thirds of their time, for the copies, the deltas
-// and each other.  Not faster: the next tile's pixels and deltas requested ahead (113, the deltas alone 106), four wavefronts (206,
-// registers spill), larger tiles (101).
+// 73 / 15; 32 x 32, 3 -> 16, 32 x 32, 3 x 3: 39 / 21; 64 x 32, 3 -> 32, 32 x 32, 5 x 5: 114 / 99 (the products added directly: 14, 21,
+// 98).  The last has matrix instructions for 28 us; three wavefronts to a SIMD (registers) wait two thirds of their time, for the copies, the
+// deltas and each other.  Not faster: the next tile's pixels and deltas requested ahead (113, the deltas alone 106), four
+// wavefronts (206, registers spill), larger tiles (101).
 #pragma once
 
 #include "conv_split.h"
@@ -175,6 +182,14 @@ __global__ __launch_bounds__(THREADS, 3) void first_wgrad_kernel(FirstWgradArgs 
                     }
 #pragma unroll
                     for (int r = 0; r < 2; ++r) {
+                        if (r == 1) {                                        // the signs of the second row's, see above
+#pragma unroll
+                            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                                for (int k = 0; k < 3; ++k)
+#pragma unroll
+                                    for (int j = 0; j < 2; ++j) q[mb][k][j] ^= 0x80008000u;
+                        }
                         u32x4 fa[MB][3];                                     // row r: of each window's four pixels one has its value
 #pragma unroll
                         for (int mb = 0; mb < MB; ++mb)
@@ -203,14 +218,19 @@ __global__ __launch_bounds__(THREADS, 3) void first_wgrad_kernel(FirstWgradArgs 
                                             fb[g][k][3] = whole ? fb[g][k][3] : 0u;
                                         }
                                     }
+                            f32x4 t[MB][NG];
+#pragma unroll
+                            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                                for (int g = 0; g < NG; ++g) t[mb][g] = f32x4{0.f, 0.f, 0.f, 0.f};
                             auto step = [&](int ka, int kb) {
 #pragma unroll
                                 for (int g = 0; g < NG; ++g)
                                     if (n0 + g < NB)
 #pragma unroll
                                         for (int mb = 0; mb < MB; ++mb)
-                                            acc[mb][n0 + g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(split_bf16::frag(fa[mb][ka]), split_bf16::frag(fb[g][kb]),
-                                                                                                     acc[mb][n0 + g], 0, 0, 0);
+                                            t[mb][g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(split_bf16::frag(fa[mb][ka]), split_bf16::frag(fb[g][kb]),
+                                                                                               t[mb][g], 0, 0, 0);
                             };
                             if (SMALL) {
                                 step(0, 2);
@@ -220,6 +240,12 @@ __global__ __launch_bounds__(THREADS, 3) void first_wgrad_kernel(FirstWgradArgs 
                                 step(1, 0);
                             }
                             if (LARGE) step(0, 0);
+#pragma unroll
+                            for (int g = 0; g < NG; ++g)
+                                if (n0 + g < NB)
+#pragma unroll
+                                    for (int mb = 0; mb < MB; ++mb) acc[mb][n0 + g] = r == 0 ? acc[mb][n0 + g] + t[mb][g] : acc[mb][n0 + g] - t[mb][g];
+
                         }
                         __builtin_amdgcn_sched_barrier(0);
                     }

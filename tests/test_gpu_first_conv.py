@@ -40,3 +40,57 @@ def test_first_layer_matches_oracle(B, orc, shape, batch):  # noqa: F811
         match_gradients(res, got, layers_close(desc), d, what=str(shape))
     finally:
         B.dbw_destroy(h)
+
+
+def test_weight_gradient_sums_are_as_exact_as_fp32_ones(B):  # noqa: F811
+    """3 -> 32 channels on 32 x 32 pixels, 5 x 5, 64 workers x 32 samples: three samples to a workgroup.  Filters of one and two taps, saturated
+    logits and hidden units that are always on make everything before and behind conv1's weight gradient exact, so that its error is that of
+    its sums.  fp32 multiply-adds of 512 pixels, one in fifteen of which has a delta, and the addition of 64 such sums, each rounding 2.4e-8
+    of the sum so far in the root mean square: 2.4e-8 (34 / 2 + 64 / 2)^(1/2) = 1.7e-7 of the result."""
+    import torch.nn.functional as F
+    n, batch, shape = 64, 32, (3, 32, 32, 32, 64, 5, 512, 10)
+    desc = cnn_desc(shape)
+    d = inputs.param_count(desc)
+    ld = inputs.pad_ld(d)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(77)
+
+    def integers(lo, hi, size):                         # lo .. hi
+        return torch.randint(lo, hi + 1, size, device="cuda", generator=gen).float()
+
+    def taps(size, count, values):
+        at = torch.rand(size, device="cuda", generator=gen).argsort(dim=-1)[..., :count]
+        return torch.zeros(size, device="cuda").scatter_(-1, at, values)
+
+    parts = [taps((n, 32, 75), 2, integers(0, 1, (n, 32, 2)) * 2 - 1), integers(-2, 2, (n, 32)) / 4, taps((n, 64, 800), 1, torch.ones(n, 64, 1, device="cuda")),
+             torch.zeros(n, 64, device="cuda"), integers(-255, 255, (n, 512, 4096)) * (integers(0, 15, (n, 512, 4096)) == 0) * 2.0 ** -30,
+             torch.ones(n, 512, device="cuda"), integers(-8, 8, (n, 10, 512)) / 8, torch.zeros(n, 10, device="cuda")]
+    parts[7][:, 3] = 4096.0
+    params = torch.zeros(n, ld, device="cuda")
+    params[:, :d] = torch.cat([p.flatten(1) for p in parts], 1)
+    x = integers(-2 ** 21, 2 ** 21 - 1, (n, batch, 3 * 32 * 32)) * 2.0 ** -20
+    y = (4 + torch.randint(0, 6, (n, batch), device="cuda", generator=gen)).int()
+    rowptr, colidx = inputs.graph_ring(n)
+    h = B.dbw_create(rowptr, colidx, n, d, ld=ld, model=B.make_model(B.MODEL_CNN, batch, shape))
+    try:
+        grads = torch.zeros_like(params)
+        B.dbw_grad(h, params, x, y, grads, torch.zeros(n, device="cuda"))
+    finally:
+        B.dbw_destroy(h)
+    error = total = 0.0
+    for i in range(0, n, 8):                            # every eighth worker in 64 bits
+        w1 = parts[0][i].double().requires_grad_(True)
+        cols = F.unfold(x[i].double().view(batch, 3, 32, 32), 5, padding=2).transpose(1, 2).reshape(-1, 75)
+        z = (cols @ w1.t() + parts[1][i].double()).view(batch, 1024, 32).transpose(1, 2).reshape(batch, 32, 32, 32)
+        a = F.max_pool2d(torch.relu(z), 2)
+        cols = F.unfold(a, 5, padding=2).transpose(1, 2).reshape(-1, 800)
+        z = (cols @ parts[2][i].double().t()).view(batch, 256, 64).transpose(1, 2).reshape(batch, 64, 16, 16)
+        a = F.max_pool2d(torch.relu(z), 2).flatten(1)
+        a = torch.relu(a @ parts[4][i].double().t() + 1.0)
+        assert float(a.detach().min()) > 0
+        loss = F.cross_entropy(a @ parts[6][i].double().t() + parts[7][i].double(), y[i].long())
+        want = torch.autograd.grad(loss, w1)[0]
+        got = grads[i, :want.numel()].view_as(want).double()
+        error += float((got - want).square().sum())
+        total += float(want.square().sum())
+    assert (error / total) ** 0.5 < 1.7e-7
