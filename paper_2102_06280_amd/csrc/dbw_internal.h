@@ -35,7 +35,16 @@ constexpr int DBW_TAIL_ROUNDS = 16;
 // the last-level cache, instead of staying in LDS.  Rounds, us, with a pass of its own / on the way: 32 workers, 784-200-10, batch 64,
 // with 4, 8 and 31 neighbours 54.2 / 46.7, 54.7 / 52.0 and 54.9 / 76.5; 48 workers, 300-92-10, batch 32, 8 neighbours 28.6 /
 // 30.1; 64 workers, 784-512-512-10, batch 256, 6 neighbours 799 / 783; 24 workers, 784-10, batch 32, 23 neighbours 23.5 / 42.3.
+// The longest list sets the kernel's end: a tile of that worker fetches its neighbours a few at a time, which the products
+// before hide the less the shorter they are.  So a round takes the pass if some worker has more neighbours than average_list says (L
+// layers, B samples); not so a single layer whose samples are summed over several workgroups, since the launch that adds those sums has a
+// thread per value and the chip for itself.  A ring whose worker 0 has as many neighbours as said: 64 workers, 300-92-10, batch 32, 6, 8, 10 and
+// 16 neighbours 31.7 / 30.1, 31.6 / 31.0, 31.5 / 32.5 and 31.6 / 39.8 (32 workers, 8 and 10: 25.7 / 26.0, 25.7 / 27.4); 32 workers, 784-200-10,
+// batch 64, 10, 12 and 16 54.7 / 51.7, 55.1 / 55.2 and 55.1 / 60.4; 784-10, batch 32, 12 and 16 on 32 and 16 on 64 workers 20.8 / 19.1, 22.1 / 20.6
+// and 22.1 / 22.6; 256-256-256-10 on 32, batch 256, 16 neighbours 96.6 / 89.8, batch 1 024, 24 neighbours 255 / 262.  A star of 64 workers,
+// 784-200-10: 88 / 157.  Stars of 64 and 256 workers, 256-10, batch 1 024: 71 / 59 and 259 / 210.
 constexpr int DBW_AVERAGE_DEGREE = 6;
+constexpr int average_list(int L, int B) { return B > 64 ? 16 : (L == 1 || B > 32 ? 12 : 8); }
 constexpr int64_t DBW_AVERAGE_MAX_D = (int64_t)1 << 29;
 
 struct dbw_timing_slot {

@@ -30,8 +30,8 @@ def hub_graph(n, extra):
 # dims, batch, loss, workers, pad: one layer in one and in several chunks (aligned and odd rows), batches of at most 16, 32 and 64
 # samples with widths that are no multiple of the tiles, long batches with and without split sums, equal widths (the chain)
 CASES = [([784, 10], 32, "xent", 8, 64), ([101, 7], 64, "mse", 9, 1), ([257, 16], 300, "xent", 5, 1), ([256, 10], 1024, "xent", 6, 64),
-         ([64, 36, 10], 16, "xent", 12, 64), ([300, 92, 10], 32, "mse", 20, 64), ([784, 200, 10], 64, "xent", 24, 64),
-         ([100, 36, 52, 3], 50, "xent", 7, 64), ([200, 320, 100, 10], 256, "xent", 12, 64), ([68, 36, 10], 260, "mse", 4, 64),
+         ([64, 36, 10], 16, "xent", 14, 64), ([300, 92, 10], 32, "mse", 20, 64), ([784, 200, 10], 64, "xent", 24, 64),
+         ([100, 36, 52, 3], 50, "xent", 7, 64), ([200, 320, 100, 10], 256, "xent", 14, 64), ([68, 36, 10], 260, "mse", 4, 64),
          ([256, 256, 256, 10], 1024, "mse", 10, 64), ([784, 200, 10], 64, "xent", 24, 1)]
 
 
@@ -41,7 +41,7 @@ def test_average_on_the_way_is_the_average(B, dims, batch, loss, n, pad, rates):
     desc = {"kind": "mlp", "dims": dims, "loss": loss}
     d = inputs.param_count(desc)
     ld = inputs.pad_ld(d, pad)
-    rowptr, colidx = hub_graph(n, n - 2)
+    rowptr, colidx = hub_graph(n, min(n - 2, 7 if batch <= 32 else 11))       # (the longest lists that are averaged on the way)
     g = np.random.default_rng(77 + n)
     params = inputs.init_params(desc, n, ld, g)
     params[:, :d] += (g.standard_normal((n, d)) * 0.05).astype(np.float32)
@@ -71,3 +71,33 @@ def test_average_on_the_way_is_the_average(B, dims, batch, loss, n, pad, rates):
     assert np.array_equal(got["way"][0][:, :d], got["pass"][0][:, :d])
     assert np.all(got["way"][0][:, d:] == 3.0)
     assert np.array_equal(got["way"][1], got["pass"][1])
+
+
+@pytest.mark.parametrize("dims,batch,extra,on_the_way", [([784, 10], 32, 11, True), ([784, 10], 32, 12, False), ([300, 92, 10], 32, 7, True),
+                                                         ([300, 92, 10], 32, 8, False), ([784, 200, 10], 64, 11, True), ([784, 200, 10], 64, 12, False),
+                                                         ([256, 256, 256, 10], 256, 15, True), ([256, 256, 256, 10], 256, 16, False), ([256, 10], 300, 30, True)])
+def test_long_neighbour_lists_take_the_pass(B, dims, batch, extra, on_the_way):
+    """One worker with many neighbours sets the end of the kernels that average on the way, however few the others have on average."""
+    n = 32
+    rowptr, colidx = hub_graph(n, extra)
+    assert np.diff(rowptr).max() == extra + (1 if extra < n - 1 else 0) and colidx.size <= 6 * n
+    desc = {"kind": "mlp", "dims": dims, "loss": "xent"}
+    d = inputs.param_count(desc)
+    ld = inputs.pad_ld(d)
+    g = np.random.default_rng(5)
+    params = inputs.init_params(desc, n, ld, g)
+    x, y = dev(g.standard_normal((n, batch, dims[0])).astype(np.float32)), dev(g.integers(0, dims[-1], (n, batch)).astype(np.int32))
+    t, b = dev(g.standard_exponential(n).astype(np.float32)), dev(np.zeros(n, np.int32))
+    got = {}
+    for mix in (B.MIX_AUTO, B.MIX_CSR):
+        h = B.dbw_create(rowptr, colidx, n, d, ld=ld, model=B.make_model(B.MODEL_MLP, batch, dims), mix_path=mix)
+        try:
+            out = torch.zeros(n, ld, device="cuda")
+            B.dbw_select(h, t, b)
+            B.dbw_set_timing(h, True)
+            B.dbw_round(h, dev(params), out, 0.05, batch_x=x, batch_y=y)
+            got[mix] = (out.cpu().numpy(), any(k.startswith("mix_") for k in B.dbw_get_timing(h)))
+        finally:
+            B.dbw_destroy(h)
+    assert got[B.MIX_CSR][1] and got[B.MIX_AUTO][1] != on_the_way
+    assert np.array_equal(got[B.MIX_AUTO][0], got[B.MIX_CSR][0])
