@@ -393,7 +393,13 @@ static int round_impl(dbw_ctx *c, const float *params_in, float *params_out, con
     if (c->model.kind != DBW_MODEL_NONE) {
         bool averaged = false;
         int rc;
-        if (c->model.kind == DBW_MODEL_MLP && c->may_average && batch_x && batch_y) {
+        // The kernels that average on the way write params_out while others still read the batch or write the losses: a caller
+        // whose buffers overlap there gets all gradients first, as if the two steps were two calls.
+        const size_t samples = (size_t)c->N * (size_t)c->model.batch;
+        const bool apart = batch_x && batch_y && !overlaps(batch_x, samples * (size_t)c->in_dim * sizeof(float), params_out, bytes) &&
+                           !overlaps(batch_y, samples * sizeof(int32_t), params_out, bytes) &&
+                           !(loss_out && overlaps(loss_out, sizeof(float) * (size_t)c->N, params_out, bytes));
+        if (c->model.kind == DBW_MODEL_MLP && c->may_average && apart) {
             const average::Args avg{params_in, c->ld, c->rowptr, c->p, c->sel_idx, c->sel_w, c->self_w, lr_vec, lr};
             rc = dbw_launch_grad_mlp(c, params_in, batch_x, batch_y, c->grads, loss_out, avg, params_out, &averaged, s);
         } else {

@@ -101,3 +101,39 @@ def test_long_neighbour_lists_take_the_pass(B, dims, batch, extra, on_the_way):
             B.dbw_destroy(h)
     assert got[B.MIX_CSR][1] and got[B.MIX_AUTO][1] != on_the_way
     assert np.array_equal(got[B.MIX_AUTO][0], got[B.MIX_CSR][0])
+
+
+@pytest.mark.parametrize("what", ["batch_x", "batch_y", "loss_out"])
+def test_buffers_inside_the_new_parameters_take_the_pass(B, what):
+    """The batch may lie where the new parameters go, and the losses may lie there: all gradients are taken before anything is written."""
+    dims, batch, n = [256, 36, 10], 4, 16
+    rowptr, colidx = hub_graph(n, 3)
+    desc = {"kind": "mlp", "dims": dims, "loss": "xent"}
+    d = inputs.param_count(desc)
+    ld = inputs.pad_ld(d)
+    g = np.random.default_rng(6)
+    params = dev(inputs.init_params(desc, n, ld, g))
+    x, y = dev(g.standard_normal((n, batch, dims[0])).astype(np.float32)), dev(g.integers(0, dims[-1], (n, batch)).astype(np.int32))
+    t, b = dev(g.standard_exponential(n).astype(np.float32)), dev(np.zeros(n, np.int32))
+    h = B.dbw_create(rowptr, colidx, n, d, ld=ld, model=B.make_model(B.MODEL_MLP, batch, dims))
+    try:
+        got = []
+        for inside in (False, True):
+            out, loss, bx, by = torch.zeros(n, ld, device="cuda"), torch.zeros(n, device="cuda"), x, y
+            if inside and what == "batch_x":
+                bx = out.view(-1)[64:64 + x.numel()].view(x.shape)
+                bx.copy_(x)
+            elif inside and what == "batch_y":
+                by = out.view(-1)[3 * ld:3 * ld + y.numel()].view(y.shape).view(torch.int32)
+                by.copy_(y)
+            elif inside:
+                loss = out.view(-1)[5 * ld + 8:5 * ld + 8 + n]
+            B.dbw_select(h, t, b)
+            B.dbw_set_timing(h, True)
+            B.dbw_round(h, params, out, 0.05, batch_x=bx, batch_y=by, loss_out=loss)
+            assert any(k.startswith("mix_") for k in B.dbw_get_timing(h)) == inside
+            B.dbw_set_timing(h, False)
+            got.append(out[:, :d].cpu().numpy())
+        assert np.array_equal(got[0], got[1])
+    finally:
+        B.dbw_destroy(h)
