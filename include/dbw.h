@@ -77,7 +77,9 @@ enum {
 
 /* How the masked consensus average is evaluated. */
 enum {
-    DBW_MIX_AUTO = 0,  /* dense when it is supported and the graph holds more than N*N/4 links */
+    DBW_MIX_AUTO = 0,  /* dense when it is supported and the graph holds more than N*N/4 links.  The kernels that compute
+                        * a fully connected model's gradients may form the average too, with the results of the path
+                        * that dbw_mix_path names */
     DBW_MIX_CSR = 1,   /* gather over the selected neighbours only (HBM bound) */
     DBW_MIX_DENSE = 2  /* materialise P(k) as N x N and multiply on the matrix cores; needs N <= 256
                         * and ld <= 26 843 545 (DBW_ERR_UNSUPPORTED from dbw_create otherwise).

@@ -153,11 +153,12 @@ int fill_ctx(dbw_ctx *c, int32_t N, int64_t d, int64_t nnz64, const int32_t *row
     for (int i = 0; i < N; ++i) c->max_deg = std::max(c->max_deg, rowptr[i + 1] - rowptr[i]);
     if (!spanning_links(N, rowptr, colidx, c->h_links)) return DBW_ERR_GRAPH;
     const bool dense_fits = N <= DBW_DENSE_MAX_N && c->ld <= DBW_DENSE_MAX_LD;
-    c->may_average = c->order == DBW_ORDER_CTA && c->mix == DBW_MIX_AUTO && c->nnz <= DBW_AVERAGE_DEGREE * (int64_t)N &&
-                     c->d <= DBW_AVERAGE_MAX_D;
-    if (c->mix == DBW_MIX_AUTO)
+    const bool automatic = c->mix == DBW_MIX_AUTO;
+    if (automatic)
         c->mix = (dense_fits && (int64_t)c->nnz * 4 > (int64_t)N * N) ? DBW_MIX_DENSE : DBW_MIX_CSR;
     if (c->mix == DBW_MIX_DENSE && !dense_fits) return DBW_ERR_UNSUPPORTED;
+    c->may_average = automatic && c->order == DBW_ORDER_CTA && c->nnz <= DBW_AVERAGE_DEGREE * (int64_t)N && c->d <= DBW_AVERAGE_MAX_D &&
+                     (c->mix == DBW_MIX_CSR || N <= DBW_AVERAGE_DENSE);
     c->Npad = 32;                                   // dense path: padded to a power of two
     while (c->Npad < N) c->Npad *= 2;
 
@@ -400,7 +401,8 @@ static int round_impl(dbw_ctx *c, const float *params_in, float *params_out, con
                            !overlaps(batch_y, samples * sizeof(int32_t), params_out, bytes) &&
                            !(loss_out && overlaps(loss_out, sizeof(float) * (size_t)c->N, params_out, bytes));
         if (c->model.kind == DBW_MODEL_MLP && c->may_average && apart) {
-            const average::Args avg{params_in, c->ld, c->rowptr, c->p, c->sel_idx, c->sel_w, c->self_w, lr_vec, lr};
+            const average::Args avg{params_in, c->ld, c->rowptr, c->p, c->sel_idx, c->sel_w, c->self_w,
+                                    c->mix == DBW_MIX_DENSE ? c->Wdense : nullptr, c->N, lr_vec, lr};
             rc = dbw_launch_grad_mlp(c, params_in, batch_x, batch_y, c->grads, loss_out, avg, params_out, &averaged, s);
         } else {
             rc = dbw_grad(c, params_in, batch_x, batch_y, c->grads, loss_out, stream);

@@ -1,8 +1,9 @@
 // The consensus average on a gradient's way to memory (Section 2.1, average first):
 //   out_i = P_ii x_i + sum over selected j of P_ij x_j - lr_i g_i
 // A worker's new parameters need its own gradient only, so the kernel that has computed one can finish the element, instead of writing
-// it for a pass over all parameters that reads it back.  Same terms in the same order as mix_csr.hip: the results are those of
-// a gradient pass and an averaging pass, bit for bit.
+// it for a pass over all parameters that reads it back.  Same terms in the same order as mix_csr.hip, or, in a context that averages
+// densely, as mix_dense.hip's fp32 kernels (all workers, ascending; those not waited for with weight 0, so that an infinity or a NaN of
+// any worker reaches every row): the results are those of a gradient pass and an averaging pass, bit for bit.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -16,32 +17,48 @@ struct Args {
     int64_t ld;
     const int32_t *rowptr, *p, *sel_idx;
     const float *sel_w, *self_w;
+    const float *dense;              // P(k) as mix_dense_kernel holds it, of a context that averages densely (NEAR + 1 workers at most), else null
+    int workers;
     const float *lr_vec;             // a rate per worker, or null
     float lr;
 };
 
-// The selected neighbours of one worker, to be fetched well before use: the first NEAR of them, the same in every lane (in scalar
-// registers).  Not one per lane: a lane that takes no part in a branch may lose what it holds to the other side of the branch.
+// What one worker adds up, to be fetched well before use: the row that it starts with (its own; densely worker 0's) with its weight, and
+// the others, the first NEAR of them here, the same in every lane (in scalar registers).  Not one per lane: a lane that takes no part
+// in a branch may lose what it holds to the other side of the branch.
 constexpr int NEAR = 8;
 struct Row {
-    int beg, cnt, idx[NEAR];
+    int beg, cnt, first, idx[NEAR];
     float wt[NEAR], self, eta;
 };
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ __forceinline__ float uniform(float v) { return __builtin_bit_cast(float, uniform(__builtin_bit_cast(int, v))); }
+// P_ij of up to 32 workers: A fragments of v_mfma_f32_32x32x2_f32
+__device__ __forceinline__ float dense_weight(const Args &a, int i, int j) { return uniform(a.dense[(j >> 1) * 64 + 32 * (j & 1) + i]); }
 __device__ __forceinline__ Row row(const Args &a, int w)
 {
     Row r{};
     if (a.x) {
-        r.beg = uniform(a.rowptr[w]);
-        r.cnt = uniform(a.p[w]);
+        if (a.dense) {
+            r.cnt = a.workers - 1;
 #pragma unroll
-        for (int k = 0; k < NEAR; ++k) {
-            const int at = k < r.cnt ? r.beg + k : 0;
-            r.idx[k] = uniform(a.sel_idx[at]);
-            r.wt[k] = uniform(a.sel_w[at]);
+            for (int k = 0; k < NEAR; ++k) {
+                r.idx[k] = k < r.cnt ? 1 + k : 0;
+                r.wt[k] = dense_weight(a, w, r.idx[k]);
+            }
+            r.self = dense_weight(a, w, 0);
+        } else {
+            r.beg = uniform(a.rowptr[w]);
+            r.cnt = uniform(a.p[w]);
+            r.first = w;
+#pragma unroll
+            for (int k = 0; k < NEAR; ++k) {
+                const int at = k < r.cnt ? r.beg + k : 0;
+                r.idx[k] = uniform(a.sel_idx[at]);
+                r.wt[k] = uniform(a.sel_w[at]);
+            }
+            r.self = uniform(a.self_w[w]);
         }
-        r.self = uniform(a.self_w[w]);
         r.eta = uniform(a.lr_vec ? a.lr_vec[w] : a.lr);
     }
     return r;
@@ -64,7 +81,7 @@ __device__ __forceinline__ V fma(float w, V x, V acc)
     }
 }
 
-// acc[n] = P_ii x_i + sum over j of P_ij x_j at `base` (uniform) + off[n] (bytes) of the rows of worker i = w and its neighbours, which
+// acc[n] = sum over j of P_ij x_j, the row's first term first, at `base` (uniform) + off[n] (bytes) of the rows of worker i = w and its neighbours, which
 // waits for no gradient.  w is the same for a wavefront; a lane without an element gives any offset of the row.  The elements
 // of several neighbours are fetched at a time (behind the last of them: its own once more).
 template <class V, int N>
@@ -80,13 +97,13 @@ __device__ __forceinline__ void gather(const Args &a, const Row &r, int w, int64
 #pragma unroll
         for (int n = 0; n < N; ++n) acc[n] = fma<V>(wt, v[n], acc[n]);
     };
-    load(w, acc);
+    load(r.first, acc);
 #pragma unroll
     for (int k = 0; k < NEAR; k += U) {
         if (k > 0 && k >= r.cnt) break;
         V v[U][N];
 #pragma unroll
-        for (int u = 0; u < U; ++u) load(k + u < r.cnt ? r.idx[k + u] : w, v[u]);
+        for (int u = 0; u < U; ++u) load(k + u < r.cnt ? r.idx[k + u] : r.first, v[u]);
         if (k == 0) {
 #pragma unroll
             for (int n = 0; n < N; ++n) acc[n] = r.self * acc[n];

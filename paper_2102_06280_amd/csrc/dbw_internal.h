@@ -44,6 +44,10 @@ constexpr int DBW_TAIL_ROUNDS = 16;
 // and 22.1 / 22.6; 256-256-256-10 on 32, batch 256, 16 neighbours 96.6 / 89.8, batch 1 024, 24 neighbours 255 / 262.  A star of 64 workers,
 // 784-200-10: 88 / 157.  Stars of 64 and 256 workers, 256-10, batch 1 024: 71 / 59 and 259 / 210.
 constexpr int DBW_AVERAGE_DEGREE = 6;
+// A context that averages densely adds up all workers' rows, on the way as in the pass: up to DBW_AVERAGE_DENSE workers, whose numbers and
+// weights a kernel has at hand.  784-10, batch 32, on 6, 10, 12 and 16 workers 22.0 / 19.2, 22.1 / 20.5, 22.0 / 21.0 and 21.8 / 23.4;
+// 784-200-10, batch 64, on 7, 10 and 12 40.7 / 36.4, 43.1 / 42.7 and 46.3 / 48.6; 64-36-10, batch 16, on 6 and 10 29.4 / 26.9 and 29.5 / 30.1.
+constexpr int DBW_AVERAGE_DENSE = average::NEAR + 1;
 constexpr int average_list(int L, int B) { return B > 64 ? 16 : (L == 1 || B > 32 ? 12 : 8); }
 constexpr int64_t DBW_AVERAGE_MAX_D = (int64_t)1 << 29;
 

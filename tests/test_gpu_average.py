@@ -1,5 +1,5 @@
 """Rounds whose gradient kernels form the average on the way (average first, few neighbours): the same bits as a gradient pass and
-the sparse averaging kernels, which add the same terms in the same order."""
+the averaging kernels, sparse or dense as dbw_mix_path says, which add the same terms in the same order."""
 import numpy as np
 import pytest
 import torch
@@ -32,7 +32,7 @@ def hub_graph(n, extra):
 CASES = [([784, 10], 32, "xent", 8, 64), ([101, 7], 64, "mse", 9, 1), ([257, 16], 300, "xent", 5, 1), ([256, 10], 1024, "xent", 6, 64),
          ([64, 36, 10], 16, "xent", 14, 64), ([300, 92, 10], 32, "mse", 20, 64), ([784, 200, 10], 64, "xent", 24, 64),
          ([100, 36, 52, 3], 50, "xent", 7, 64), ([200, 320, 100, 10], 256, "xent", 14, 64), ([68, 36, 10], 260, "mse", 4, 64),
-         ([256, 256, 256, 10], 1024, "mse", 10, 64), ([784, 200, 10], 64, "xent", 24, 1)]
+         ([256, 256, 256, 10], 1024, "mse", 16, 64), ([784, 200, 10], 64, "xent", 24, 1)]
 
 
 @pytest.mark.parametrize("rates", ["one", "each"])
@@ -51,9 +51,10 @@ def test_average_on_the_way_is_the_average(B, dims, batch, loss, n, pad, rates):
     eta = dev(g.uniform(0.01, 0.2, n).astype(np.float32))
     model = B.make_model(B.MODEL_MLP, batch, dims, B.LOSS_MSE if loss == "mse" else B.LOSS_XENT)
     got = {}
-    for name, mix in (("way", B.MIX_AUTO), ("pass", B.MIX_CSR)):
-        h = B.dbw_create(rowptr, colidx, n, d, ld=ld, model=model, mix_path=mix)
+    for name in ("way", "pass"):
+        h = B.dbw_create(rowptr, colidx, n, d, ld=ld, model=model, mix_path=B.MIX_AUTO if name == "way" else resolved)
         try:
+            resolved = B.dbw_mix_path(h)
             out = torch.full((n, ld), 3.0, device="cuda")
             lo = torch.zeros(n, device="cuda")
             B.dbw_select(h, t, b)
@@ -137,3 +138,41 @@ def test_buffers_inside_the_new_parameters_take_the_pass(B, what):
         assert np.array_equal(got[0], got[1])
     finally:
         B.dbw_destroy(h)
+
+
+@pytest.mark.parametrize("dims,batch", [([784, 10], 32), ([256, 10], 300), ([100, 36, 10], 24), ([64, 36, 10], 260)])
+@pytest.mark.parametrize("n,degree,path", [(6, 2, "dense"), (9, 4, "dense"), (10, 4, "dense"), (16, 2, "sparse")])
+def test_diverged_worker_reaches_the_rows_that_the_path_says(B, dims, batch, n, degree, path):
+    """A NaN and an infinity in the parameters of a worker that nobody waits for: in every row of a dense average, in its own row alone of
+    a sparse one, wherever the new parameters lie."""
+    g = np.random.default_rng(n)
+    rowptr, colidx = inputs.graph_ring(n) if degree == 2 else inputs.graph_regular(n, degree, g)
+    desc = {"kind": "mlp", "dims": dims, "loss": "xent"}
+    d = inputs.param_count(desc)
+    ld = inputs.pad_ld(d)
+    params = inputs.init_params(desc, n, ld, g)
+    params[3, d - 2], params[3, 5] = np.nan, np.inf
+    params = dev(params)
+    x, y = dev(g.standard_normal((n, batch, dims[0])).astype(np.float32)), dev(g.integers(0, dims[-1], (n, batch)).astype(np.int32))
+    times = g.standard_exponential(n).astype(np.float32)
+    times[3] = 100.0
+    b = np.where([3 in colidx[rowptr[i]:rowptr[i + 1]] for i in range(n)], 1, 0).astype(np.int32)
+    h = B.dbw_create(rowptr, colidx, n, d, ld=ld, model=B.make_model(B.MODEL_MLP, batch, dims))
+    try:
+        assert B.dbw_mix_path(h) == (B.MIX_DENSE if path == "dense" else B.MIX_CSR)
+        got = []
+        for shift in (0, 1):                            # new parameters on a 16-byte boundary and off it
+            out = torch.zeros(n * ld + 1, device="cuda")[shift:shift + n * ld].view(n, ld)
+            B.dbw_select(h, dev(times), dev(b))
+            B.dbw_round(h, params, out, 0.05, batch_x=x, batch_y=y)
+            got.append(out[:, :d].cpu().numpy())
+    finally:
+        B.dbw_destroy(h)
+    others = np.arange(n) != 3
+    for o in got:
+        assert np.all(np.isnan(o[3]))                   # (its gradient is NaN throughout)
+        reached = ~np.isfinite(o[others])
+        assert np.array_equal(reached.sum(1), np.full(n - 1, 2 if path == "dense" else 0))
+        if path == "dense":
+            assert np.all(np.isnan(o[others][:, d - 2])) and np.all(np.isnan(o[others][:, 5]))
+    assert np.array_equal(got[0], got[1], equal_nan=True)
