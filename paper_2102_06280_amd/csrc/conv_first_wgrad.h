@@ -50,19 +50,25 @@ __host__ __device__ inline int first_wgrad_version(const Shape &s, int rows)
 }
 __host__ __device__ inline int first_wgrad_plane(const Shape &s, int rows) { return s.Cin * s.KS * first_wgrad_version(s, rows); }
 
+// Left to conv_split.h's kernel, this one / that (us): tiles of two rows, two thirds of whose pixels are halo (16 workers x 32 samples, 3 -> 32
+// channels, 48 x 48 pixels, 5 x 5 125 / 76; 64 x 64 177 / 133; 7 -> 32, 48 x 48, 3 x 3 113 / 78; tiles of four: 2 -> 32, 64 x 64, 5 x 5 0.8 times as
+// long here), and 3 x 3 filters of six to eight channels with more than sixteen output channels, where that kernel's column blocks are more
+// than half full and this one's tiles leave wavefronts idle (6 -> 64, 32 x 32 59 / 51; 7 -> 64, 16 x 16 20.5 / 17.5; 8 -> 32, 24 x 24
+// even; 6 -> 64 on 24 x 24 0.85 times as long here; up to sixteen output channels 6 -> 8, 32 x 32 0.84, five channels 5 -> 64 0.92).
 inline bool first_wgrad_plan(const Shape &s, int workers, FirstWgradPlan &p)
 {
     if (s.KS != 3 && s.KS != 5) return false;
     p.nb = (s.Cin * s.KS * s.KS + 15) / 16;
     if (p.nb > 5) return false;                          // (registers: a wavefront has all taps)
     p.mb = s.Cout <= 16 ? 1 : 2;
+    if (s.KS == 3 && p.nb > 3 && p.mb == 2) return false;
     const size_t sums = sizeof(float) * 4 * p.mb * p.nb * 256;
     int tiles = 1;
     for (;; ++tiles) {                                   // the fewest tiles of which four workgroups fit a compute unit; a thread per group
         p.rows = ((s.H + tiles - 1) / tiles + 1) / 2 * 2;
+        if (p.rows == 2) return false;
         p.lds = (size_t)48 * first_wgrad_plane(s, p.rows);
         if (p.lds <= 39 * 1024 && s.Cin * (p.rows + s.KS - 1) * first_groups(s) <= THREADS) break;
-        if (p.rows == 2) return false;
     }
     if (p.lds < sums) p.lds = sums;
     const int64_t blocks = (int64_t)workers * ((s.Cout + 16 * p.mb - 1) / (16 * p.mb));

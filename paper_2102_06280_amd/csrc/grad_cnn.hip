@@ -461,7 +461,8 @@ int launch_first_wgrad_blocks(const convsplit::FirstWgradArgs &a, int workers, h
     return DBW_OK;
 }
 
-// Taps of 3 x 3 filters: 9, 18, 27, 36, 45, 54, 63, 72 in one to five blocks of sixteen; of 5 x 5: 25, 50, 75 in two, four and five.
+// Taps of 3 x 3 filters: 9, 18, 27, 36, 45, 54, 63, 72 in one to five blocks of sixteen (the
+// last two with one block of output channels only); of 5 x 5: 25, 50, 75 in two, four and five.
 int launch_first_wgrad(const convsplit::FirstWgradArgs &a, int workers, hipStream_t s)
 {
     auto rows = [&](auto one, auto two) { return a.p.mb == 1 ? one(a, workers, s) : two(a, workers, s); };
@@ -469,8 +470,8 @@ int launch_first_wgrad(const convsplit::FirstWgradArgs &a, int workers, hipStrea
         case 1: return rows(launch_first_wgrad_blocks<3, 1, 1>, launch_first_wgrad_blocks<3, 2, 1>);
         case 2: return rows(launch_first_wgrad_blocks<3, 1, 2>, launch_first_wgrad_blocks<3, 2, 2>);
         case 3: return rows(launch_first_wgrad_blocks<3, 1, 3>, launch_first_wgrad_blocks<3, 2, 3>);
-        case 4: return rows(launch_first_wgrad_blocks<3, 1, 4>, launch_first_wgrad_blocks<3, 2, 4>);
-        default: return rows(launch_first_wgrad_blocks<3, 1, 5>, launch_first_wgrad_blocks<3, 2, 5>);
+        case 4: return launch_first_wgrad_blocks<3, 1, 4>(a, workers, s);
+        default: return launch_first_wgrad_blocks<3, 1, 5>(a, workers, s);
     }
     switch (a.p.nb) {
     case 2: return rows(launch_first_wgrad_blocks<5, 1, 2>, launch_first_wgrad_blocks<5, 2, 2>);

@@ -14,7 +14,8 @@ pytestmark = pytest.mark.gpu
 # input channels, height, width, channels 1 and 2, filter, dense, classes; batch
 SHAPES = [((1, 8, 8, 4, 3, 3, 6, 5), 5), ((1, 12, 28, 16, 4, 5, 6, 5), 3), ((2, 12, 8, 9, 4, 5, 6, 5), 4), ((2, 16, 16, 32, 4, 3, 6, 5), 3),
           ((3, 20, 20, 12, 3, 3, 7, 4), 3), ((3, 32, 32, 32, 3, 5, 6, 5), 2), ((4, 8, 12, 16, 4, 3, 6, 5), 9), ((4, 16, 12, 17, 4, 5, 6, 5), 2),
-          ((5, 8, 20, 33, 3, 3, 6, 5), 4), ((6, 12, 12, 5, 4, 5, 6, 5), 3), ((7, 8, 8, 40, 3, 3, 6, 5), 2)]
+          ((5, 8, 20, 33, 3, 3, 6, 5), 4), ((6, 12, 12, 5, 4, 5, 6, 5), 3), ((7, 8, 8, 40, 3, 3, 6, 5), 2),
+          ((6, 8, 12, 17, 3, 3, 6, 5), 4), ((6, 12, 8, 16, 3, 3, 6, 5), 4), ((8, 16, 16, 9, 3, 3, 6, 5), 3), ((3, 12, 48, 5, 3, 5, 6, 5), 2)]
 
 
 @pytest.mark.parametrize("shape,batch", SHAPES, ids=["-".join(map(str, s[0])) + f"-b{s[1]}" for s in SHAPES])
