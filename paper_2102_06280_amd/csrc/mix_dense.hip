@@ -345,9 +345,13 @@ int launch_split(dbw_ctx *c, const float *W, const float *x, const float *g, flo
     const int64_t n_tiles = (c->d + C::TC - 1) / C::TC;
     if (n_tiles > INT32_MAX) return DBW_ERR_UNSUPPORTED;
     dbw_timer tm(c, "mix_dense_split", s);
+    const bool stream = (HAS_G ? 12 : 8) * c->N * c->ld > mixsplit::CACHE_BYTES;
     // persistent: as many workgroups as the compute units' LDS holds
-    hipLaunchKernelGGL((mixsplit::kernel<MB, WAVES, ORDER, HAS_G, WIDE, LR>), dim3((unsigned)std::min<int64_t>(n_tiles, 256 * 8 / WAVES)),
-                       dim3(64 * WAVES), 0, s, c->N, c->d, c->ld, W, x, g, out, lr, (int)n_tiles);
+    const dim3 grid((unsigned)std::min<int64_t>(n_tiles, 256 * 8 / WAVES)), block(64 * WAVES);
+    if (stream)
+        hipLaunchKernelGGL((mixsplit::kernel<MB, WAVES, ORDER, HAS_G, WIDE, true, LR>), grid, block, 0, s, c->N, c->d, c->ld, W, x, g, out, lr, (int)n_tiles);
+    else
+        hipLaunchKernelGGL((mixsplit::kernel<MB, WAVES, ORDER, HAS_G, WIDE, false, LR>), grid, block, 0, s, c->N, c->d, c->ld, W, x, g, out, lr, (int)n_tiles);
     DBW_HIP(hipGetLastError());
     return DBW_OK;
 }

@@ -15,9 +15,12 @@
 // the multiplies left out); for N = 256 x 1 M 0.82 ms, where the memory side alone takes 0.65 (128-byte pieces of rows that
 // lie far apart) and the multiplies and splits alone 0.56.  The fp32 matrix instruction that this kernel used before needs
 // 0.83 ms at its peak rate for the latter shape and took 1.13; N = 128 without gradients, 2.8 M columns: 0.88 -> 0.61 ms;
-// N = 60 x 4 M: 0.60 -> 0.56.  Results, and from 65 workers on loads, pass the caches by: N = 128 x 2.8 M without gradients 690 -> 678 us
-// (a plain copy of as many bytes: 600), N = 256 x 1 M with them 840 -> 829, N = 100 x 40 000 26.1 -> 24.9; up to 64 workers such
-// loads cost (N = 60 x 200 000 33 -> 35).  Tried without gain: two tiles of X on their way instead of one (685), one 64-column tile with a single set of
+// N = 60 x 4 M: 0.60 -> 0.56.  Where X, the result and the gradients together are larger than the last-level cache, results, and from 65
+// workers on loads, pass the caches by: N = 128 x 2.8 M without gradients 690 -> 678 us (a linear stream of as many bytes: 448), N = 256 x 1 M
+// with them 840 -> 829, N = 40 x 1 M without 80 -> 77.5.  Smaller ones are still there when the next round reads them: rounds
+// one after the other of N = 64 x 100 000 and x 400 000 without gradients 12.4 and 35.6 us, past the caches 14.0 and 42.3; the first with
+// gradients 15.7, 16.9; N = 256 x 50 000 with gradients 47, 49.6.  (Loads past the caches cost up to 64 workers: N = 60 x 200 000 33 -> 35.)
+// Tried without gain: two tiles of X on their way instead of one (685), one 64-column tile with a single set of
 // planes (0.88), wave priorities for either phase, LDS fragments requested a step ahead.
 //
 // D of v_mfma_f32_32x32x16_bf16, lane l: 16 floats, d[v] = D[m = 8 * (v / 4) + 4 * (l / 32) + v % 4][n = l % 32]
@@ -29,6 +32,8 @@
 #include "split_bf16.h"
 
 namespace mixsplit {
+
+constexpr int64_t CACHE_BYTES = (int64_t)256 << 20;    // the last-level cache
 
 // A wave-uniform address, pinned to scalar registers.  Global loads and stores take a scalar
 // base plus a 32-bit lane offset; without the pin the compiler folds the lane offset into one
@@ -90,7 +95,8 @@ __device__ __forceinline__ void wait_lds()
 // be fetched and the float4 that straddles column d lies inside its row; otherwise the same elements come 4 bytes
 // per lane, in four times as many instructions (N = 254 x 730 k columns: 0.80 ms against 0.63; a
 // thread per column and row that gathers its operands, as before, 30.7).
-template <int MB, int WAVES, int ORDER, bool HAS_G, bool WIDE, class LR>
+// STREAM: the matrices do not fit the last-level cache, see above.
+template <int MB, int WAVES, int ORDER, bool HAS_G, bool WIDE, bool STREAM, class LR>
 __global__ __launch_bounds__(64 * WAVES, 2) void kernel(
     int N, int64_t dcols /* = d */, int64_t ld, const float *__restrict__ Wsw, const float *__restrict__ x, const float *__restrict__ g,
     float *__restrict__ out, LR lr, int n_tiles)
@@ -125,7 +131,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void kernel(
             const int r = r0 + i / PIECES * PER;                                          // uniform
             const int64_t last = (dcols - 1) / V * V, cb = min(t * C::TC + c0 + 64 * V * (i % PIECES), last);
             const uint32_t c_off = 4u * (uint32_t)min((int64_t)lane_col, last - cb);
-            load_to_lds<WIDE, MB >= 4>(uniform_base(src + (int64_t)min(r, N - 1) * ld + cb), (lane_row < N - r ? row_off : 0u) + c_off,
+            load_to_lds<WIDE, STREAM && MB >= 4>(uniform_base(src + (int64_t)min(r, N - 1) * ld + cb), (lane_row < N - r ? row_off : 0u) + c_off,
                               dst + 1024 * w + 64 * V * i);
         }
     };
@@ -234,8 +240,11 @@ __global__ __launch_bounds__(64 * WAVES, 2) void kernel(
         const uint32_t lane_off = 4u * (uint32_t)(4 * (lane >> 5) * (int)ld + (lane & 31));
         if (full) {
 #pragma unroll
-            for (int v = 0; v < 16; ++v)
-                __builtin_nontemporal_store(acc[v], (float *)(const_cast<char *>(uniform_base(out + (int64_t)(32 * rb + 8 * (v / 4) + (v & 3)) * ld + col0)) + lane_off));
+            for (int v = 0; v < 16; ++v) {
+                float *o = (float *)(const_cast<char *>(uniform_base(out + (int64_t)(32 * rb + 8 * (v / 4) + (v & 3)) * ld + col0)) + lane_off);
+                if (STREAM) __builtin_nontemporal_store(acc[v], o);
+                else *o = acc[v];
+            }
         } else {
 #pragma unroll
             for (int v = 0; v < 16; ++v) {

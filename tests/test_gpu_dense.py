@@ -196,3 +196,41 @@ def test_smallest_and_largest_values(B):
         B.dbw_destroy(h)
     assert np.isfinite(got).all()
     assert np.all(np.abs(got - P @ x) <= 2.0 ** -133 + 2.0 ** -23 * (P @ np.abs(x.astype(np.float64))))
+
+
+@pytest.mark.parametrize("n,orders,pad", [(40, (0, 1, None), 64), (70, (0, None), 4), (100, (None,), 1), (200, (0, 1), 4)])
+def test_matrices_around_the_last_level_cache(B, n, orders, pad):
+    """Results (from 65 workers on: loads as well) pass the caches by once X, the result and the gradients together are larger than 256 MB: the
+    same bits in the columns that a matrix just below and one just above the line have in common, ragged ends included."""
+    rowptr, colidx = inputs.graph_complete(n)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n)
+    t, b = torch.rand(n, device="cuda", generator=gen), torch.full((n,), n // 3, dtype=torch.int32, device="cuda")
+    for order in orders:                                # None: without gradients
+        line = (256 << 20) // ((8 if order is None else 12) * n)
+        sizes = [line - 999, line + 1003]
+        x, gr = torch.empty(n, sizes[0], device="cuda").normal_(generator=gen), None
+        if order is not None:
+            gr = torch.empty(n, sizes[0], device="cuda").normal_(generator=gen)
+        outs = []
+        for d in sizes:
+            ld = inputs.pad_ld(d, pad)
+            assert ((8 if order is None else 12) * n * ld > 256 << 20) == (d == sizes[1])
+            X, G = torch.zeros(n, ld, device="cuda"), None
+            X[:, :sizes[0]] = x
+            if gr is not None:
+                G = torch.zeros(n, ld, device="cuda")
+                G[:, :sizes[0]] = gr
+            out = torch.full((n, ld), 7.0, device="cuda")
+            h = B.dbw_create(rowptr, colidx, n, d, ld=ld, order=order or 0)
+            try:
+                assert B.dbw_mix_path(h) == B.MIX_DENSE
+                B.dbw_select(h, t, b)
+                B.dbw_round(h, X, out, 0.05, ext_grads=G)
+                torch.cuda.synchronize()
+            finally:
+                B.dbw_destroy(h)
+            assert bool((out[:, d:] == 7.0).all()) and bool((out[:, sizes[0]:d] == 0.0).all())
+            outs.append(out[:, :sizes[0]])
+        assert torch.equal(outs[0], outs[1])
+        del outs, X, G, x, gr, out
