@@ -18,9 +18,8 @@ SHAPES = [((1, 8, 8, 4, 3, 3, 6, 5), 5), ((1, 12, 28, 16, 4, 5, 6, 5), 3), ((2, 
           ((6, 8, 12, 17, 3, 3, 6, 5), 4), ((6, 12, 8, 16, 3, 3, 6, 5), 4), ((8, 16, 16, 9, 3, 3, 6, 5), 3), ((3, 12, 48, 5, 3, 5, 6, 5), 2)]
 
 
-@pytest.mark.parametrize("shape,batch", SHAPES, ids=["-".join(map(str, s[0])) + f"-b{s[1]}" for s in SHAPES])
-def test_first_layer_matches_oracle(B, orc, shape, batch):  # noqa: F811
-    n, g, desc = 3, np.random.default_rng(900 + shape[0]), cnn_desc(shape)
+def check_gradients(B, orc, shape, batch, n):  # noqa: F811
+    g, desc = np.random.default_rng(900 + shape[0]), cnn_desc(shape)
     d = inputs.param_count(desc)
     ld = inputs.pad_ld(d)
     rowptr, colidx = inputs.graph_ring(n)
@@ -41,6 +40,23 @@ def test_first_layer_matches_oracle(B, orc, shape, batch):  # noqa: F811
         match_gradients(res, got, layers_close(desc), d, what=str(shape))
     finally:
         B.dbw_destroy(h)
+
+
+@pytest.mark.parametrize("shape,batch", SHAPES, ids=["-".join(map(str, s[0])) + f"-b{s[1]}" for s in SHAPES])
+def test_first_layer_matches_oracle(B, orc, shape, batch):  # noqa: F811
+    check_gradients(B, orc, shape, batch, 3)
+
+
+# 8 workers: the first layer's weight gradient takes two (the fifth shape: three) samples to a workgroup, with one and two blocks of output
+# channels and both filter sizes, the second's three, three, two, two, seven and three, with 5 x 5 filters also as two workgroups to a compute
+# unit; the last workgroup of a worker has fewer.
+SHARED = [((1, 8, 8, 12, 3, 3, 6, 5), 161), ((3, 8, 8, 9, 3, 5, 6, 5), 161), ((2, 8, 8, 20, 35, 3, 6, 5), 115), ((3, 8, 8, 24, 4, 5, 6, 5), 115),
+          ((1, 8, 8, 33, 100, 5, 6, 5), 97), ((3, 20, 20, 9, 3, 5, 6, 5), 161)]
+
+
+@pytest.mark.parametrize("shape,batch", SHARED, ids=["-".join(map(str, s[0])) + f"-b{s[1]}" for s in SHARED])
+def test_workgroups_of_several_samples_match_oracle(B, orc, shape, batch):  # noqa: F811
+    check_gradients(B, orc, shape, batch, 8)
 
 
 def test_weight_gradient_sums_are_as_exact_as_fp32_ones(B):  # noqa: F811
