@@ -157,8 +157,7 @@ int fill_ctx(dbw_ctx *c, int32_t N, int64_t d, int64_t nnz64, const int32_t *row
     if (automatic)
         c->mix = (dense_fits && (int64_t)c->nnz * 4 > (int64_t)N * N) ? DBW_MIX_DENSE : DBW_MIX_CSR;
     if (c->mix == DBW_MIX_DENSE && !dense_fits) return DBW_ERR_UNSUPPORTED;
-    c->may_average = automatic && c->order == DBW_ORDER_CTA && c->nnz <= DBW_AVERAGE_DEGREE * (int64_t)N && c->d <= DBW_AVERAGE_MAX_D &&
-                     (c->mix == DBW_MIX_CSR || N <= DBW_AVERAGE_DENSE);
+    c->may_average = automatic && c->order == DBW_ORDER_CTA && c->nnz <= DBW_AVERAGE_DEGREE * (int64_t)N && c->d <= DBW_AVERAGE_MAX_D;
     c->Npad = 32;                                   // dense path: padded to a power of two
     while (c->Npad < N) c->Npad *= 2;
 

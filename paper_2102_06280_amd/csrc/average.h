@@ -17,7 +17,7 @@ struct Args {
     int64_t ld;
     const int32_t *rowptr, *p, *sel_idx;
     const float *sel_w, *self_w;
-    const float *dense;              // P(k) as mix_dense_kernel holds it, of a context that averages densely (NEAR + 1 workers at most), else null
+    const float *dense;              // P(k) as mix_dense_kernel holds it, of a context that averages densely, else null
     int workers;
     const float *lr_vec;             // a rate per worker, or null
     float lr;
@@ -83,8 +83,8 @@ __device__ __forceinline__ V fma(float w, V x, V acc)
 
 // acc[n] = sum over j of P_ij x_j, the row's first term first, at `base` (uniform) + off[n] (bytes) of the rows of worker i = w and its neighbours, which
 // waits for no gradient.  w is the same for a wavefront; a lane without an element gives any offset of the row.  The elements
-// of several neighbours are fetched at a time (behind the last of them: its own once more).
-template <class V, int N>
+// of several neighbours are fetched at a time (behind the last of them: the first row's once more).  ALL: a dense row may be longer than NEAR.
+template <class V, int N, bool ALL>
 __device__ __forceinline__ void gather(const Args &a, const Row &r, int w, int64_t base, const uint32_t (&off)[N], V (&acc)[N])
 {
     constexpr int U = N * lanes<V>::n >= 16 ? 2 : 4;
@@ -112,38 +112,42 @@ __device__ __forceinline__ void gather(const Args &a, const Row &r, int w, int64
         for (int u = 0; u < U; ++u)
             if (k + u < r.cnt) add(r.wt[k + u], v[u]);
     }
-    for (int k = NEAR; k < r.cnt; k += U) {
-        V v[U][N];
-        float wt[U];
+    auto far = [&](auto entry) {
+        for (int k = NEAR; k < r.cnt; k += U) {
+            V v[U][N];
+            float wt[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int at = r.beg + min(k + u, r.cnt - 1);
-            wt[u] = uniform(a.sel_w[at]);
-            load(uniform(a.sel_idx[at]), v[u]);
+            for (int u = 0; u < U; ++u) load(entry(min(k + u, r.cnt - 1), wt[u]), v[u]);
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (k + u < r.cnt) add(wt[u], v[u]);
         }
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (k + u < r.cnt) add(wt[u], v[u]);
+    };
+    if (ALL && a.dense) {
+        far([&](int k, float &wt) { wt = dense_weight(a, w, 1 + k); return 1 + k; });
+    } else {
+        far([&](int k, float &wt) { wt = uniform(a.sel_w[r.beg + k]); return uniform(a.sel_idx[r.beg + k]); });
     }
 }
 
 // g[n], gradients of worker w there -> the new parameters.
-template <class V, int N>
+template <class V, int N, bool ALL = false>
 __device__ __forceinline__ void apply(const Args &a, const Row &r, int w, int64_t base, const uint32_t (&off)[N], V (&g)[N])
 {
     V acc[N];
-    gather<V, N>(a, r, w, base, off, acc);
+    gather<V, N, ALL>(a, r, w, base, off, acc);
 #pragma unroll
     for (int n = 0; n < N; ++n) g[n] = fma<V>(-r.eta, g[n], acc[n]);
 }
 
 // One gradient of a lane, to `out` (the worker's row).
+template <bool ALL = false>
 __device__ __forceinline__ void store(const Args &a, const Row &r, int w, float *out, int64_t at, float g)
 {
     float v[1] = {g};
     if (a.x) {
         const uint32_t off[1] = {(uint32_t)(4 * at)};
-        apply<float, 1>(a, r, w, 0, off, v);
+        apply<float, 1, ALL>(a, r, w, 0, off, v);
     }
     out[at] = v[0];
 }

@@ -428,7 +428,7 @@ __device__ __forceinline__ void body(const Args &g, float *zl, float *zp, float 
                     off[u] = 4u * (uint32_t)(c * H + k);
                     at[u] = c * HP + k;
                 }
-                average::gather<f32x4_any, 2>(g.avg, nb, w, g.w_off, off, v);
+                average::gather<f32x4_any, 2, true>(g.avg, nb, w, g.w_off, off, v);
 #pragma unroll
                 for (int u = 0; u < 2; ++u) {
                     if (g0 + u * THREADS >= groups) continue;
@@ -439,10 +439,10 @@ __device__ __forceinline__ void body(const Args &g, float *zl, float *zp, float 
             }
             for (int e = tid; e < C * (width % 4); e += THREADS) {
                 const int c = e / (width % 4), k = c0 + 4 * quads + e - c * (width % 4);
-                average::store(g.avg, nb, w, row, g.w_off + c * H + k, Wl[c * HP + k]);
+                average::store<true>(g.avg, nb, w, row, g.w_off + c * H + k, Wl[c * HP + k]);
             }
         }
-        if (tid < C && part_no == 0) average::store(g.avg, nb, w, row, g.b_off + tid, zp[MAX_S + tid]);
+        if (tid < C && part_no == 0) average::store<true>(g.avg, nb, w, row, g.b_off + tid, zp[MAX_S + tid]);
     }
     // ---- the chunk's loss: its samples in a fixed order (a tree inside one wavefront)
     static_assert(MAX_S == 64, "one sample per lane");
@@ -578,7 +578,7 @@ __device__ __forceinline__ void reduce_body(const Args &g, int chunks, int bx, i
         for (int u = 0; u < 16; ++u) sum += v[u];
     }
     const int64_t at = e < n_w ? g.w_off + e : (e < n_w + n_b ? g.b_off + (e - n_w) : g.bprev_off + (e - n_w - n_b));
-    if (e < n_w + n_b + n_p) average::store(g.avg, nb, w, gw, at, sum);
+    if (e < n_w + n_b + n_p) average::store<true>(g.avg, nb, w, gw, at, sum);
     else g.loss[w] = sum / (float)g.B;
 }
 

@@ -483,7 +483,7 @@ int dbw_fc_forward_backward(dbw_ctx *c, dbw_fc_args &a, hipStream_t s)
         grouped = !batch32_layer(B, dims[l - 1], dims[l], c->ld, w_off[l], params, grads);
     // The average on the way, where the head and one grouped launch store all gradients
     a.averaged = a.out && head.use && ((chain.use && chain.chunks > 1) || grouped || L == 1) && (L == 1 || (fc32::aligned16(a.out) && fc32::aligned16(params))) &&
-                 (c->max_deg <= average_list(L, B) || (L == 1 && head.chunks > 1));
+                 ((L == 1 && head.chunks > 1) || (c->mix == DBW_MIX_DENSE ? N <= average_dense(L, B) : c->max_deg <= average_list(L, B, N)));
     // A short batch is one chunk of the head per worker, so that its sums over the batch are final.  When the grouped
     // launch follows, which adds per-chunk sums on the side, smaller chunks cost nothing and put the head on more CUs
     // (784-200-10, 64 samples, 32 workers: 16.1 -> 10.9 us with four chunks of 16).

@@ -232,7 +232,7 @@ __global__ __launch_bounds__(THREADS, 2) void kernel(Args g, fchead::Args h, int
         uint32_t off[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) off[r] = 4u * (uint32_t)(min(m0 + 4 * (4 * lq + r) + wave, H - 1) * N + ncol);
-        average::apply<vec, 4>(g.avg, nb, w, pick(g.w_off, l), off, v);
+        average::apply<vec, 4, true>(g.avg, nb, w, pick(g.w_off, l), off, v);
     }
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -245,7 +245,7 @@ __global__ __launch_bounds__(THREADS, 2) void kernel(Args g, fchead::Args h, int
         for (int q = 1; q < WAVES; ++q) b[0] += *(const f32x4 *)&bred[q][4 * lane];
         if (mix) {
             const uint32_t off[1] = {4u * (uint32_t)(H * N + m0 + 4 * lane)};
-            average::apply<f32x4, 1>(g.avg, nb, w, pick(g.w_off, l), off, b);
+            average::apply<f32x4, 1, true>(g.avg, nb, w, pick(g.w_off, l), off, b);
         }
         *(f32x4 *)(out + (int64_t)H * N + m0 + 4 * lane) = b[0];
     }
@@ -285,7 +285,7 @@ __device__ __forceinline__ void reduce_body(const Args &g, int bx, int w)
     if (!keep) return;
     if (g.avg.x) {
         const uint32_t off[1] = {(uint32_t)(4 * pos)};
-        average::apply<f32x4, 1>(g.avg, nb, w, 0, off, sum);
+        average::apply<f32x4, 1, true>(g.avg, nb, w, 0, off, sum);
     }
     *(f32x4 *)(g.grads + w * g.g_stride + pos) = sum[0];
 }

@@ -29,10 +29,10 @@ def hub_graph(n, extra):
 
 # dims, batch, loss, workers, pad: one layer in one and in several chunks (aligned and odd rows), batches of at most 16, 32 and 64
 # samples with widths that are no multiple of the tiles, long batches with and without split sums, equal widths (the chain)
-CASES = [([784, 10], 32, "xent", 8, 64), ([101, 7], 64, "mse", 9, 1), ([257, 16], 300, "xent", 5, 1), ([256, 10], 1024, "xent", 6, 64),
+CASES = [([784, 10], 32, "xent", 8, 64), ([101, 7], 64, "mse", 9, 1), ([257, 16], 300, "xent", 5, 1), ([103, 9], 200, "mse", 13, 64), ([60, 10], 128, "xent", 12, 1), ([300, 9], 40, "xent", 12, 1), ([256, 10], 1024, "xent", 6, 64),
          ([64, 36, 10], 16, "xent", 14, 64), ([300, 92, 10], 32, "mse", 20, 64), ([784, 200, 10], 64, "xent", 24, 64),
          ([100, 36, 52, 3], 50, "xent", 7, 64), ([200, 320, 100, 10], 256, "xent", 14, 64), ([68, 36, 10], 260, "mse", 4, 64),
-         ([256, 256, 256, 10], 1024, "mse", 16, 64), ([784, 200, 10], 64, "xent", 24, 1)]
+         ([256, 256, 256, 10], 1024, "mse", 16, 64), ([128, 128, 128, 10], 300, "xent", 12, 64), ([68, 36, 10], 260, "xent", 11, 64), ([784, 200, 10], 64, "xent", 24, 1)]
 
 
 @pytest.mark.parametrize("rates", ["one", "each"])
