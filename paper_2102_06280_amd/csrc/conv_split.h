@@ -713,7 +713,10 @@ inline bool wgrad_plan(const Shape &s, int workers, WgradPlan &p)
     // The 5 x 5 kernel takes 145 registers, three wavefronts to a SIMD: of two workgroups of five to eight the second finds no place.
     // Limited to 128 (some 24 bytes per lane go to scratch) both run: 16 x 50, 16 -> 32 on 14 x 14 53.8 -> 45.8 us, the round of 20 x 13,
     // 32 -> 32 on 10 x 10 184 -> 173.  Where one workgroup is all that a compute unit gets, the limit only costs: 32 -> 64 on
-    // 16 x 16 248 -> 258, 16 x 16, 8 -> 16 on 12 x 12 14.1 -> 14.7.
+    // 16 x 16 248 -> 258, 16 x 16, 8 -> 16 on 12 x 12 14.1 -> 14.7.  (Of nine to twelve wavefronts the second workgroup finds no place either
+    // way, and the limit changes nothing: 16 x 32, 20 -> 96 on 8 x 8 57.3 us with it and 58.5 without, 16 x 64, 32 -> 64 on 6 x 6
+    // 71.5 and 72.7.  Their samples given out as for one workgroup would take 48.6 and 62.7, but the sums of a workgroup would be twice as
+    // long and up to 15 % less exact.)
     p.paired = per_cu == 2 && p.waves > 4 && (int64_t)p.splits * workers * p.groups > 256;
     return true;
 }

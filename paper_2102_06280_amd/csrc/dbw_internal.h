@@ -35,21 +35,23 @@ constexpr int DBW_TAIL_ROUNDS = 16;
 // the last-level cache, instead of staying in LDS.  Rounds, us, with a pass of its own / on the way: 32 workers, 784-200-10, batch 64,
 // with 4, 8 and 31 neighbours 54.2 / 46.7, 54.7 / 52.0 and 54.9 / 76.5; 48 workers, 300-92-10, batch 32, 8 neighbours 28.6 /
 // 30.1; 64 workers, 784-512-512-10, batch 256, 6 neighbours 799 / 783; 24 workers, 784-10, batch 32, 23 neighbours 23.5 / 42.3.
-// The longest list sets the kernel's end: a tile of that worker fetches its neighbours a few at a time, which the products
-// before hide the less the shorter they are.  So a round takes the pass if some worker has more neighbours than average_list says (L
-// layers, B samples, N workers); not so a single layer whose samples are summed over several workgroups, since the launch that adds those sums has a
-// thread per value and the chip for itself.  A ring whose worker 0 has as many neighbours as said: 64 workers, 300-92-10, batch 32, 6, 8, 10 and
-// 16 neighbours 31.7 / 30.1, 31.6 / 31.0, 31.5 / 32.5 and 31.6 / 39.8 (32 workers, 8 and 10: 25.7 / 26.0, 25.7 / 27.4); 32 workers, 784-200-10,
-// batch 64, 10, 12 and 16 54.7 / 51.7, 55.1 / 55.2 and 55.1 / 60.4; 784-10, batch 32, 12 and 16 neighbours on 32 workers 20.5 / 19.1 and
-// 20.6 / 20.3, 8, 10 and 16 on 64 20.5 / 20.4, 20.5 / 21.5 and 20.7 / 22.8; 256-256-256-10 on 32, batch 256, 16 neighbours 96.6 / 89.8, batch 1 024, 24 neighbours 255 / 262.  A star of 64 workers,
-// 784-200-10: 88 / 157.  Stars of 64 and 256 workers, 256-10, batch 1 024: 71 / 59 and 259 / 210.
 constexpr int DBW_AVERAGE_DEGREE = 6;
+// The longest list sets the kernel's end: a tile of that worker fetches its neighbours a few at a time, which the products before
+// hide the less the shorter they are.  So a round takes the pass if some worker has more neighbours than this (L layers, B samples,
+// N workers); not so a single layer whose samples are summed over several workgroups, since the launch that adds those sums has
+// a thread per value and the chip for itself.  A ring whose worker 0 has as many neighbours as said: 64 workers, 300-92-10, batch
+// 32, 6, 8, 10 and 16 neighbours 31.7 / 30.1, 31.6 / 31.0, 31.5 / 32.5 and 31.6 / 39.8 (32 workers, 8 and 10: 25.7 / 26.0, 25.7 /
+// 27.4); 32 workers, 784-200-10, batch 64, 10, 12 and 16 54.7 / 51.7, 55.1 / 55.2 and 55.1 / 60.4; 784-10, batch 32, 12 and 16 on 32
+// workers 20.5 / 19.1 and 20.6 / 20.3, 8, 10 and 16 on 64 20.5 / 20.4, 20.5 / 21.5 and 20.7 / 22.8; 256-256-256-10 on 32, batch
+// 256, 16 neighbours 96.6 / 89.8, batch 1 024, 24 neighbours 255 / 262.  A star of 64 workers, 784-200-10: 88 / 157.  Stars of 64
+// and 256 workers, 256-10, batch 1 024: 71 / 59 and 259 / 210.
 constexpr int average_list(int L, int B, int N) { return B > 64 ? 16 : (B > 32 || (L == 1 && N <= 48) ? 12 : 8); }
-// A context that averages densely adds up all workers' rows, on the way as in the pass: up to as many workers as a kernel has at hand, or, for
-// batches of more than 64 and single layers, twelve, and for a single layer with several workgroups' sums any (up to 23 of so few neighbours on average).
-// 784-10, batch 32, on 6, 10, 12 and 16 workers 22.0 / 19.2, 22.1 / 20.5, 22.0 / 21.0 and 21.8 / 23.4; 784-200-10, batch 64, on 7, 10 and 12
-// 40.7 / 36.4, 43.1 / 42.7 and 46.3 / 48.6; 64-36-10, batch 16, on 6, 10 and 12 29.4 / 26.9, 29.5 / 30.1 and 29.4 / 31.7; 256-256-256-10, batch 256, on 10,
-// 12 and 16 62.3 / 57.2, 63.9 / 59.2 and 66.1 / 66.2; 256-10, batch 1 024, on 12, 16 and 22 25.8 / 22.3, 26.6 / 23.5 and 33.1 / 32.0.
+// A context that averages densely adds up all workers' rows, on the way as in the pass: up to as many workers as a kernel has at
+// hand, or, for batches of more than 64 and for single layers, twelve, and any for a single layer with several workgroups' sums
+// (up to 23, with so few neighbours on average).  784-10, batch 32, on 6, 10, 12 and 16 workers 20.7 / 18.1, 20.7 / 18.9, 22.0 / 21.0 and
+// 21.8 / 23.4; 784-200-10, batch 64, on 7, 10 and 12 40.7 / 36.4, 43.1 / 42.7 and 46.3 / 48.6; 64-36-10, batch 16, on 6, 10 and 12 29.4 /
+// 26.9, 29.5 / 30.1 and 29.4 / 31.7; 256-256-256-10, batch 256, on 10, 12 and 16 62.3 / 57.0, 63.9 / 59.3 and 66.1 / 66.2; 256-10, batch
+// 1 024, on 12, 20 and 22 25.8 / 22.3, 32.7 / 29.2 and 32.9 / 30.2.
 constexpr int average_dense(int L, int B) { return L == 1 || B > 64 ? 12 : average::NEAR + 1; }
 constexpr int64_t DBW_AVERAGE_MAX_D = (int64_t)1 << 29;
 

@@ -191,7 +191,9 @@ __device__ __forceinline__ Early fetch_early(const Args &g, int w, int s0, int n
 // barrier that makes al and Wl visible.
 // MIX: g.avg is there and the sums over the batch are final (one chunk).  Of `parts` workgroups that all have the chunk's logits, number
 // `part_no` takes every parts-th run of RUN columns of the products behind them (784-10 on 8 workers x 32 samples, where the products
-// and the average were 11 of the kernel's 16 us: four parts, round 21.4 -> 19.1; on 24 workers without the average 23.3 -> 21.7).
+// and the average were 11 of the kernel's 16 us: four parts, round 21.4 -> 19.1; on 24 workers without the average 23.3 -> 21.7;
+// with nothing in the caches, where every part fetches W and the batch again, without the average 26.5 -> 23.6 and 26.7 -> 24.3,
+// 3072-10 on 8 41.7 -> 39.0).
 constexpr int RUN = 2 * WAVES * 16;
 template <int LOSS, bool MIX = false>
 __device__ __forceinline__ void body(const Args &g, float *zl, float *zp, float *Wl, float *al, int S, int w, int chunk,

@@ -358,6 +358,8 @@ struct cnn_layout {
 // of them on 16 x 16 pixels, where most of a reduction step is padding, the three products take 15 + 15 + 14 us
 // (16 workers, batch 32) against 20 + 98 + 17 of the implicit GEMM, with 32 -> 64 channels (64 workers) 255 + 274 + 264
 // against 433 + 427 + 448 of LDS-resident fp32 kernels.
+// (Layers of up to sixteen output channels are launched with 12 KB less than is asked for here: images at the very edge stay with the
+// implicit GEMM and its fp32 products.)
 bool conv_split_fits(const convsplit::Shape &s, int workers, bool first, convsplit::WgradPlan &plan)
 {
     const size_t most = 160 * 1024;
@@ -409,8 +411,10 @@ cnn_layout make_layout(const dbw_model &m, int workers)
     L.code1 = take((B * L.C1 * L.H2 * L.W2 + 3) / 4);     // one byte per pooled element
     L.code2 = take((B * L.flat + 3) / 4);
     // The workers' blocks start 32 KB apart or a multiple of that.  What lies between was measured on 3 x 32 x 32 images, 64 workers: a
-    // block of 6 MB + 14, 15 or 18 KB makes the dense layer's weight gradient 133 to 145 us and the head 41, multiples of 16 KB (and
-    // 65 and 528 KB) 112 to 115 and 35 to 39, whole megabytes too; the round 1620 us so far, 1596 now; twelve other networks within 0.3 %.
+    // block of 6 MB + 14, 15 or 18 KB makes the dense layer's weight gradient 133 to 147 us and the head 41 to 43, multiples of 16 KB (and
+    // 65 and 528 KB) 112 to 120 and 35 to 39, whole megabytes too.  Both builds in turn in two processes, without and with the spacing:
+    // the round 1646 / 1614 and 1633 / 1615 us; nineteen other networks, this one with 24 or 31 samples or 32 or 48 workers among them,
+    // within 0.5 %.  Why these distances and not others was not found.
     L.total = (o + 8191) / 8192 * 8192;
     return L;
 }
