@@ -345,7 +345,8 @@ int launch_split(dbw_ctx *c, const float *W, const float *x, const float *g, flo
     const int64_t n_tiles = (c->d + C::TC - 1) / C::TC;
     if (n_tiles > INT32_MAX) return DBW_ERR_UNSUPPORTED;
     dbw_timer tm(c, "mix_dense_split", s);
-    const bool stream = (HAS_G ? 12 : 8) * c->N * c->ld > mixsplit::CACHE_BYTES;
+    const bool lines = c->ld % 32 == 0 && ((uintptr_t)x | (uintptr_t)out | (HAS_G ? (uintptr_t)g : 0)) % 128 == 0;
+    const bool stream = lines && (HAS_G ? 12 : 8) * c->N * c->ld > mixsplit::CACHE_BYTES;
     // persistent: as many workgroups as the compute units' LDS holds
     const dim3 grid((unsigned)std::min<int64_t>(n_tiles, 256 * 8 / WAVES)), block(64 * WAVES);
     if (stream)

@@ -15,11 +15,14 @@
 // the multiplies left out); for N = 256 x 1 M 0.82 ms, where the memory side alone takes 0.65 (128-byte pieces of rows that
 // lie far apart) and the multiplies and splits alone 0.56.  The fp32 matrix instruction that this kernel used before needs
 // 0.83 ms at its peak rate for the latter shape and took 1.13; N = 128 without gradients, 2.8 M columns: 0.88 -> 0.61 ms;
-// N = 60 x 4 M: 0.60 -> 0.56.  Where X, the result and the gradients together are larger than the last-level cache, results, and from 65
-// workers on loads, pass the caches by: N = 128 x 2.8 M without gradients 690 -> 678 us (a linear stream of as many bytes: 448), N = 256 x 1 M
-// with them 840 -> 829, N = 40 x 1 M without 80 -> 77.5.  Smaller ones are still there when the next round reads them: rounds
-// one after the other of N = 64 x 100 000 and x 400 000 without gradients 12.4 and 35.6 us, past the caches 14.0 and 42.3; the first with
-// gradients 15.7, 16.9; N = 256 x 50 000 with gradients 47, 49.6.  (Loads past the caches cost up to 64 workers: N = 60 x 200 000 33 -> 35.)
+// N = 60 x 4 M: 0.60 -> 0.56.  Where X, the result and the gradients together are larger than the last-level cache and every row starts on
+// a 128-byte line, results, and from 65 workers on loads, pass the caches by: N = 128 x 2.8 M without gradients 690 -> 678 us (a
+// linear stream of as many bytes: 448), N = 256 x 1 M with them 840 -> 829, N = 128 x 1 M 318 -> 309.  Smaller matrices are still
+// there when the next round reads them: rounds one after the other of N = 64 x 100 000 and x 400 000 without gradients 12.4 and 35.6 us,
+// past the caches 14.0 and 42.3; the first with gradients 15.7, 16.9; N = 256 x 50 000 with gradients 47, 49.6.  A piece of a row that
+// shares its lines with the next piece goes to memory twice past the caches: N = 128 x 1 M without gradients, rows of 4-byte, 16-byte
+// and 64-byte boundaries 355, 337 and 265 us, past the caches 521, 478 and 263, with gradients 445, 441 and 358, 595, 639 and 410.  (Loads
+// past the caches cost up to 64 workers: N = 60 x 200 000 33 -> 35.)
 // Tried without gain: two tiles of X on their way instead of one (685), one 64-column tile with a single set of
 // planes (0.88), wave priorities for either phase, LDS fragments requested a step ahead.
 //
@@ -95,7 +98,8 @@ __device__ __forceinline__ void wait_lds()
 // be fetched and the float4 that straddles column d lies inside its row; otherwise the same elements come 4 bytes
 // per lane, in four times as many instructions (N = 254 x 730 k columns: 0.80 ms against 0.63; a
 // thread per column and row that gathers its operands, as before, 30.7).
-// STREAM: the matrices do not fit the last-level cache, see above.
+// STREAM: the matrices do not fit the last-level cache, see above.  (One store statement for both forms makes the compiler merge the
+// branches of full and ragged blocks, which costs up to 10 % where a block of rows is ragged.)
 template <int MB, int WAVES, int ORDER, bool HAS_G, bool WIDE, bool STREAM, class LR>
 __global__ __launch_bounds__(64 * WAVES, 2) void kernel(
     int N, int64_t dcols /* = d */, int64_t ld, const float *__restrict__ Wsw, const float *__restrict__ x, const float *__restrict__ g,
@@ -241,9 +245,10 @@ __global__ __launch_bounds__(64 * WAVES, 2) void kernel(
         if (full) {
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                float *o = (float *)(const_cast<char *>(uniform_base(out + (int64_t)(32 * rb + 8 * (v / 4) + (v & 3)) * ld + col0)) + lane_off);
-                if (STREAM) __builtin_nontemporal_store(acc[v], o);
-                else *o = acc[v];
+                if constexpr (STREAM)
+                    __builtin_nontemporal_store(acc[v], (float *)(const_cast<char *>(uniform_base(out + (int64_t)(32 * rb + 8 * (v / 4) + (v & 3)) * ld + col0)) + lane_off));
+                else
+                    *(float *)(const_cast<char *>(uniform_base(out + (int64_t)(32 * rb + 8 * (v / 4) + (v & 3)) * ld + col0)) + lane_off) = acc[v];
             }
         } else {
 #pragma unroll

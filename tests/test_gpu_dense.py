@@ -198,10 +198,12 @@ def test_smallest_and_largest_values(B):
     assert np.all(np.abs(got - P @ x) <= 2.0 ** -133 + 2.0 ** -23 * (P @ np.abs(x.astype(np.float64))))
 
 
-@pytest.mark.parametrize("n,orders,pad", [(40, (0, 1, None), 64), (70, (0, None), 4), (100, (None,), 1), (200, (0, 1), 4)])
+@pytest.mark.parametrize("n,orders,pad", [(40, (0, 1, None), 64), (70, (0, None), 32), (100, (None,), 1), (200, (0, 1), 32),
+                                          (200, (0,), 16)])
 def test_matrices_around_the_last_level_cache(B, n, orders, pad):
-    """Results (from 65 workers on: loads as well) pass the caches by once X, the result and the gradients together are larger than 256 MB: the
-    same bits in the columns that a matrix just below and one just above the line have in common, ragged ends included."""
+    """Results (from 65 workers on: loads as well) pass the caches by once X, the result and the gradients together are larger than 256 MB and
+    every row starts on a 128-byte line: the same bits in the columns that a matrix just below and one just above the line have in
+    common, ragged ends and rows off the lines included."""
     rowptr, colidx = inputs.graph_complete(n)
     gen = torch.Generator(device="cuda")
     gen.manual_seed(n)
