@@ -110,11 +110,35 @@ __device__ __forceinline__ void split_nearest(const float (&x)[N], uint32_t (&h)
         }
     }
 }
+// Eight of them into planes: written out, because as a call of split_nearest the compiler schedules the dense average otherwise, up to 6 %
+// slower (36 workers x 3 M columns, local step first, a rate per worker: 385 -> 408 us).
 __device__ __forceinline__ planes split8_nearest(const float (&x)[8])
 {
-    uint32_t h[4], m[4], l[4];
-    split_nearest(x, h, m, l);
-    return {u32x4{h[0], h[1], h[2], h[3]}, u32x4{m[0], m[1], m[2], m[3]}, u32x4{l[0], l[1], l[2], l[3]}};
+    planes p;
+    float rest = 0.f;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        uint32_t m, l;
+        const uint32_t h = nearest(x[2 * q], x[2 * q + 1]);
+        const float a = x[2 * q] - value(h << 16), b = x[2 * q + 1] - value(h & 0xffff0000u);
+        rest = fmaxf(rest, fmaxf(fabsf(a), fabsf(b)));
+        split_rest(a, b, m, l);
+        p.h[q] = h;
+        p.m[q] = m;
+        p.l[q] = l;
+    }
+    if (__builtin_expect(rest == __builtin_inff(), 0)) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float ha = high_value(x[2 * q]), hb = high_value(x[2 * q + 1]);
+            uint32_t m, l;
+            split_rest(x[2 * q] - ha, x[2 * q + 1] - hb, m, l);
+            p.h[q] = upper(ha, hb);
+            p.m[q] = m;
+            p.l[q] = l;
+        }
+    }
+    return p;
 }
 
 __device__ __forceinline__ bf16x8 frag(const u32x4 &v) { return __builtin_bit_cast(bf16x8, v); }
