@@ -92,10 +92,12 @@ __global__ __launch_bounds__(THREADS, 2) void kernel(Args g, fchead::Args h, int
     }
     const int b = blockIdx.x - head_grid, per = (gridDim.x - head_grid) / XCDS, id = (b % XCDS) * per + b / XCDS;
     if (id >= tile_wgs) return;
-    // With the average on the way the workers of a tile run next to each other, on one XCD, whose L2 then holds the
-    // rows that they read of one another.
+    // The tiles of a worker run next to each other, on one XCD, whose L2 then holds the samples that they share, also with the average on
+    // the way: the neighbours' rows come from the last-level cache.  With the workers of a tile together, for those rows' sake, every tile
+    // fetched its samples again: 47 workers, 764-512-10, batch 1024, the round 937 us, 831 so (871 with a pass for the average); 49,
+    // 256-100-10 154, 133 (135); 33, 784-232-6 367, 316 (333); 40, 256-256-256-10 351, 338 (360); 10 of those 102.6, 102.2 (109.5).
     const bool mix = g.avg.x != nullptr && g.splits == 1;
-    const int q = id / g.workers, bx = mix ? q : id % tiles, w = mix ? id - q * g.workers : (id / tiles) % g.workers, split = mix ? 0 : id / (tiles * g.workers);
+    const int bx = id % tiles, w = (id / tiles) % g.workers, split = id / (tiles * g.workers);
     int l = 1;
     while (l < g.layers && bx >= pick(g.tile_begin, l + 1)) ++l;
     const int N = pick(g.n_cols, l), H = pick(g.n_rows, l), ntn = (N + TN - 1) / TN;
