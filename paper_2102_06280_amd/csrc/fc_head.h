@@ -13,7 +13,7 @@
 //   A fragment: lane l holds A[m = l % 16][k = l / 16], B fragment: B[k = l / 16][n = l % 16],
 //   D: d[v] = D[m = 4 * (l / 16) + v][n = l % 16].
 //
-// grid = (chunks x parts, workers).  With one chunk per worker (batches up to 64) the sums over the batch
+// grid = (chunks, workers, parts).  With one chunk per worker (batches up to 64) the sums over the batch
 // (dW, db, the bias gradient below, the loss) are final.  Otherwise they are written as per-chunk
 // partials and added in chunk order by reduce_kernel, a second launch: a "last workgroup to arrive
 // adds them" scheme inside one launch was measured and rejected, because the memory fence every
@@ -193,7 +193,10 @@ __device__ __forceinline__ Early fetch_early(const Args &g, int w, int s0, int n
 // `part_no` takes every parts-th run of RUN columns of the products behind them (784-10 on 8 workers x 32 samples, where the products
 // and the average were 11 of the kernel's 16 us: four parts, round 21.4 -> 19.1; on 24 workers without the average 23.3 -> 21.7;
 // with nothing in the caches, where every part fetches W and the batch again, without the average 26.5 -> 23.6 and 26.7 -> 24.3,
-// 3072-10 on 8 41.7 -> 39.0).
+// 3072-10 on 8 41.7 -> 39.0).  The grid is padded to a multiple of eight workers then, which puts the parts of a chunk on one XCD: its
+// cache holds W and the chunk for all of them.  With the parts next to each other in the grid, 491-10 on 100 workers x 64 samples took
+// 31.5 us a round against 28.9 without parts and 26.1 so, 785-10 x 32 31.8, 28.5 and 26.1; 24 rounds with a batch each of 785-10 on 8
+// 817, 767 and 712.
 constexpr int RUN = 2 * WAVES * 16;
 template <int LOSS, bool MIX = false>
 __device__ __forceinline__ void body(const Args &g, float *zl, float *zp, float *Wl, float *al, int S, int w, int chunk,
@@ -481,7 +484,7 @@ __device__ __forceinline__ float4 split_sum(const float *src, int64_t plane, int
 // VEC: the input rows start on 16-byte boundaries and H divides by 4 (128-bit staging loads).
 // SPLIT: the input arrives as split-k partial sums (Args::splits).
 template <int LOSS, bool VEC, bool SPLIT = false, bool MIX = false>
-__global__ __launch_bounds__(THREADS) void kernel(Args g, int parts)
+__global__ __launch_bounds__(THREADS) void kernel(Args g, int workers)
 {
     extern __shared__ __attribute__((aligned(16))) float sm[];
     const int H = g.H, C = g.C, S = g.S, HP = row_pitch(H);
@@ -490,7 +493,8 @@ __global__ __launch_bounds__(THREADS) void kernel(Args g, int parts)
     float *Wl = zp + WAVES * 16 * 16;                // [C + 1][HP]: row C and the columns >= H are zero
     float *al = Wl + (C + 1) * HP + 16;              // [S][HP], rows >= ns and columns >= H zero
     const int tid = threadIdx.x;
-    const int chunk = blockIdx.x / parts, chunks = gridDim.x / parts, w = blockIdx.y;
+    const int chunk = blockIdx.x, chunks = gridDim.x, w = blockIdx.y;
+    if (w >= workers) return;                        // (the grid is padded where there are parts)
     const int s0 = chunk * S, ns = min(S, g.B - s0);
     const float *__restrict__ a = g.a + w * g.a_stride + (int64_t)s0 * g.a_ld;
 
@@ -556,7 +560,7 @@ __global__ __launch_bounds__(THREADS) void kernel(Args g, int parts)
     if (tid < 16) al[S * HP + tid] = 0.f;
     __syncthreads();
 
-    body<LOSS, MIX>(g, zl, zp, Wl, al, S, w, chunk, chunks, false, early, blockIdx.x % parts, parts);
+    body<LOSS, MIX>(g, zl, zp, Wl, al, S, w, chunk, chunks, false, early, blockIdx.z, gridDim.z);
 }
 
 // Sum of the per-chunk partials in chunk order -> dW, db, the bias gradient below, the loss.
