@@ -13,7 +13,7 @@
 //   A fragment: lane l holds A[m = l % 16][k = l / 16], B fragment: B[k = l / 16][n = l % 16],
 //   D: d[v] = D[m = 4 * (l / 16) + v][n = l % 16].
 //
-// grid = (chunks, workers, parts).  With one chunk per worker (batches up to 64) the sums over the batch
+// grid = (chunks x workers x parts).  With one chunk per worker (batches up to 64) the sums over the batch
 // (dW, db, the bias gradient below, the loss) are final.  Otherwise they are written as per-chunk
 // partials and added in chunk order by reduce_kernel, a second launch: a "last workgroup to arrive
 // adds them" scheme inside one launch was measured and rejected, because the memory fence every
@@ -193,10 +193,9 @@ __device__ __forceinline__ Early fetch_early(const Args &g, int w, int s0, int n
 // `part_no` takes every parts-th run of RUN columns of the products behind them (784-10 on 8 workers x 32 samples, where the products
 // and the average were 11 of the kernel's 16 us: four parts, round 21.4 -> 19.1; on 24 workers without the average 23.3 -> 21.7;
 // with nothing in the caches, where every part fetches W and the batch again, without the average 26.5 -> 23.6 and 26.7 -> 24.3,
-// 3072-10 on 8 41.7 -> 39.0).  The grid is padded to a multiple of eight workers then, which puts the parts of a chunk on one XCD: its
-// cache holds W and the chunk for all of them.  With the parts next to each other in the grid, 491-10 on 100 workers x 64 samples took
-// 31.5 us a round against 28.9 without parts and 26.1 so, 785-10 x 32 31.8, 28.5 and 26.1; 24 rounds with a batch each of 785-10 on 8
-// 817, 767 and 712.
+// 3072-10 on 8 41.7 -> 39.0).
+// The parts of a chunk lie on one XCD, whose cache then holds W and the chunk for all of them: with the parts next to each other in the
+// grid, 491-10 on 100 workers x 64 samples took 31.5 us a round against 28.9 without parts and 26.1 so, 785-10 x 32 31.8, 28.5 and 26.1.
 constexpr int RUN = 2 * WAVES * 16;
 template <int LOSS, bool MIX = false>
 __device__ __forceinline__ void body(const Args &g, float *zl, float *zp, float *Wl, float *al, int S, int w, int chunk,
@@ -484,7 +483,7 @@ __device__ __forceinline__ float4 split_sum(const float *src, int64_t plane, int
 // VEC: the input rows start on 16-byte boundaries and H divides by 4 (128-bit staging loads).
 // SPLIT: the input arrives as split-k partial sums (Args::splits).
 template <int LOSS, bool VEC, bool SPLIT = false, bool MIX = false>
-__global__ __launch_bounds__(THREADS) void kernel(Args g, int workers)
+__global__ __launch_bounds__(THREADS) void kernel(Args g, int chunks, int items, int parts)
 {
     extern __shared__ __attribute__((aligned(16))) float sm[];
     const int H = g.H, C = g.C, S = g.S, HP = row_pitch(H);
@@ -493,8 +492,17 @@ __global__ __launch_bounds__(THREADS) void kernel(Args g, int workers)
     float *Wl = zp + WAVES * 16 * 16;                // [C + 1][HP]: row C and the columns >= H are zero
     float *al = Wl + (C + 1) * HP + 16;              // [S][HP], rows >= ns and columns >= H zero
     const int tid = threadIdx.x;
-    const int chunk = blockIdx.x, chunks = gridDim.x, w = blockIdx.y;
-    if (w >= workers) return;                        // (the grid is padded where there are parts)
+    // Workgroup i runs on XCD i % 8: eight chunks at a time, all their parts eight workgroups apart.  What is left of more than eight
+    // chunks has its parts side by side: gaps in the grid (as there are for fewer than eight chunks) made others wait for a compute unit
+    // where the grid nearly fills the chip (784-10 on 17 to 21 workers x 64 samples, two chunks each: 23 us a round, 28 with gaps).
+    const int whole = (items > 8 ? items / 8 : 1) * 8 * parts, rest = (int)blockIdx.x - whole;
+    int item = (int)blockIdx.x / (8 * parts) * 8 + (int)blockIdx.x % 8, part_no = (int)blockIdx.x / 8 % parts;
+    if (rest >= 0) {
+        item = items / 8 * 8 + rest / parts;
+        part_no = rest % parts;
+    }
+    if (item >= items) return;
+    const int chunk = item % chunks, w = item / chunks;
     const int s0 = chunk * S, ns = min(S, g.B - s0);
     const float *__restrict__ a = g.a + w * g.a_stride + (int64_t)s0 * g.a_ld;
 
@@ -560,7 +568,7 @@ __global__ __launch_bounds__(THREADS) void kernel(Args g, int workers)
     if (tid < 16) al[S * HP + tid] = 0.f;
     __syncthreads();
 
-    body<LOSS, MIX>(g, zl, zp, Wl, al, S, w, chunk, chunks, false, early, blockIdx.z, gridDim.z);
+    body<LOSS, MIX>(g, zl, zp, Wl, al, S, w, chunk, chunks, false, early, part_no, parts);
 }
 
 // Sum of the per-chunk partials in chunk order -> dW, db, the bias gradient below, the loss.

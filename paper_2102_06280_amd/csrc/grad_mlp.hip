@@ -570,13 +570,14 @@ int dbw_fc_forward_backward(dbw_ctx *c, dbw_fc_args &a, hipStream_t s)
         // the chunk is a sum of split products, most of the work then.
         int parts = 1;
         if (head_splits == 0) parts = std::max(1, std::min((h.H + fchead::RUN - 1) / fchead::RUN, 256 / (head.chunks * N)));
-        const dim3 grid(head.chunks, parts > 1 ? (N + 7) / 8 * 8 : N, parts);
+        const int items = head.chunks * N;
+        const dim3 grid(items < 8 && parts > 1 ? 8 * parts : items * parts);
         const size_t lds = fchead::lds_bytes(h.H, h.C, h.S);
         const bool vec = h.H % 4 == 0 && h.a_ld % 4 == 0 && h.a_stride % 4 == 0 && (uintptr_t)h.a % 16 == 0;
         const bool mse = a.loss_kind == DBW_LOSS_MSE;
         auto go = [&](auto kern) -> int {
             dbw_timer tm(c, "fc_head_kernel", s);
-            hipLaunchKernelGGL(kern, grid, dim3(fchead::THREADS), lds, s, h, N);
+            hipLaunchKernelGGL(kern, grid, dim3(fchead::THREADS), lds, s, h, head.chunks, items, parts);
             DBW_HIP(hipGetLastError());
             return DBW_OK;
         };

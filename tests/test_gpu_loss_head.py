@@ -9,7 +9,7 @@ pytestmark = pytest.mark.gpu
 
 LOSS = [([12, 17], 1, 3, "xent"), ([12, 32], 64, 2, "mse"), ([9, 33], 257, 2, "xent"), ([20, 11, 100], 65, 3, "mse"), ([5, 31], 600, 2, "mse")]
 HEAD = [([784, 10], 32, 2, "xent"), ([301, 7], 5, 2, "mse"), ([1027, 16], 33, 1, "xent"), ([513, 1], 64, 3, "xent"), ([20, 516, 10], 70, 2, "xent"),
-        ([258, 9], 200, 2, "mse"), ([300, 5], 17, 9, "xent")]
+        ([258, 9], 200, 2, "mse"), ([300, 5], 17, 9, "xent"), ([784, 10], 64, 7, "mse")]
 
 
 @pytest.mark.parametrize("dims,batch,n,loss", LOSS + HEAD, ids=lambda v: "-".join(map(str, v)) if isinstance(v, list) else str(v))
