@@ -243,6 +243,30 @@ struct WgradPlan {
     int64_t w_end;              // end of b_layers in the parameter row
     int64_t per, split_floats;
 };
+// The tiles of that launch: 64 x 64 when they alone give every CU two workgroups, else 64 x 32; if that still leaves CUs idle, the
+// batch is split as well (partial tiles to scratch, one more launch to add them).  begin, if not null: the first tile of every layer.
+struct WgradTiles {
+    bool thin;                  // one wavefront per 32 x 64 tile, no split (mlp_thin.h)
+    int tn, tiles;
+};
+WgradTiles wgrad_tiles(int layers, const int32_t *dims, int B, int N, int *begin)
+{
+    auto count = [&](int tm, int tn, int *begin) {
+        int t = 0;
+        for (int l = 1; l <= layers; ++l) {
+            if (begin) begin[l] = t;
+            t += ((dims[l] + tm - 1) / tm) * ((dims[l - 1] + tn - 1) / tn);
+        }
+        if (begin) begin[layers + 1] = t;
+        return t;
+    };
+    WgradTiles r{};
+    r.thin = B <= mlpthin::MAX_B;
+    r.tn = !r.thin && (int64_t)count(64, 64, nullptr) * N >= 512 ? 64 : 32;
+    r.tiles = r.thin ? count(mlpthin::WG_TM, mlpthin::WG_TN, begin) : count(64, r.tn, begin);
+    return r;
+}
+
 int launch_grouped_wgrad(dbw_ctx *c, const dbw_fc_args &a, const WgradPlan &wp, const fchead::Args &h, int head_chunks,
                          hipStream_t s)
 {
@@ -251,20 +275,9 @@ int launch_grouped_wgrad(dbw_ctx *c, const dbw_fc_args &a, const WgradPlan &wp, 
     const int64_t wstride = a.act_stride;
     mlpwgrad::Args q{};
     q.B = B; q.layers = wp.layers; q.workers = N;
-    // 64 x 64 tiles when they alone give every CU two workgroups, else 64 x 32; if that still leaves CUs idle, the
-    // batch is split as well (partial tiles to scratch, one more launch to add them)
-    auto count_tiles = [&](int tm, int tn, int *begin) {
-        int t = 0;
-        for (int l = 1; l <= wp.layers; ++l) {
-            if (begin) begin[l] = t;
-            t += ((dims[l] + tm - 1) / tm) * ((dims[l - 1] + tn - 1) / tn);
-        }
-        if (begin) begin[wp.layers + 1] = t;
-        return t;
-    };
-    const bool thin = B <= mlpthin::MAX_B;        // one wavefront per 32 x 64 tile, no split (mlp_thin.h)
-    const int tn = !thin && (int64_t)count_tiles(64, 64, nullptr) * N >= 512 ? 64 : 32;
-    const int tiles = thin ? count_tiles(mlpthin::WG_TM, mlpthin::WG_TN, q.tile_begin) : count_tiles(64, tn, q.tile_begin);
+    const WgradTiles wt = wgrad_tiles(wp.layers, dims, B, N, q.tile_begin);
+    const bool thin = wt.thin;
+    const int tn = wt.tn, tiles = wt.tiles;
     for (int l = 1; l <= wp.layers; ++l) {
         q.n_rows[l] = dims[l];
         q.n_cols[l] = dims[l - 1];
@@ -482,8 +495,14 @@ int dbw_fc_forward_backward(dbw_ctx *c, dbw_fc_args &a, hipStream_t s)
     for (int l = 1; l <= Lw && grouped; ++l)
         grouped = !batch32_layer(B, dims[l - 1], dims[l], c->ld, w_off[l], params, grads);
     // The average on the way, where the head and one grouped launch store all gradients
-    a.averaged = a.out && head.use && ((chain.use && chain.chunks > 1) || grouped || L == 1) && (L == 1 || (fc32::aligned16(a.out) && fc32::aligned16(params))) &&
-                 ((L == 1 && head.chunks > 1) || (c->mix == DBW_MIX_DENSE ? N <= average_dense(L, B) : c->max_deg <= average_list(L, B, N)));
+    a.averaged = a.out && head.use && ((chain.use && chain.chunks > 1) || grouped || L == 1) && (L == 1 || (fc32::aligned16(a.out) && fc32::aligned16(params)));
+    if (a.averaged && (L > 1 || head.chunks == 1)) {
+        const int64_t tiles = (int64_t)wgrad_tiles(Lw, dims, B, N, nullptr).tiles * N;
+        if (c->mix == DBW_MIX_DENSE)
+            a.averaged = N <= average_dense(L, B, tiles);
+        else
+            a.averaged = c->max_deg <= average_list(L, B, N) && c->nnz <= (int64_t)average_degree(L, B, tiles, 4 * c->d * N) * N;
+    }
     // A short batch is one chunk of the head per worker, so that its sums over the batch are final.  When the grouped
     // launch follows, which adds per-chunk sums on the side, smaller chunks cost nothing and put the head on more CUs
     // (784-200-10, 64 samples, 32 workers: 16.1 -> 10.9 us with four chunks of 16).

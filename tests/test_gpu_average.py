@@ -30,7 +30,7 @@ def hub_graph(n, extra):
 # dims, batch, loss, workers, pad: one layer in one and in several chunks (aligned and odd rows), batches of at most 16, 32 and 64
 # samples with widths that are no multiple of the tiles, long batches with and without split sums, equal widths (the chain)
 CASES = [([784, 10], 32, "xent", 8, 64), ([101, 7], 64, "mse", 9, 1), ([257, 16], 300, "xent", 5, 1), ([103, 9], 200, "mse", 13, 64), ([60, 10], 128, "xent", 12, 1), ([300, 9], 40, "xent", 12, 1), ([256, 10], 1024, "xent", 6, 64),
-         ([64, 36, 10], 16, "xent", 14, 64), ([300, 92, 10], 32, "mse", 20, 64), ([784, 200, 10], 64, "xent", 24, 64),
+         ([64, 36, 10], 16, "xent", 14, 64), ([300, 92, 10], 32, "mse", 17, 64), ([784, 200, 10], 64, "xent", 24, 64),
          ([100, 36, 52, 3], 50, "xent", 7, 64), ([200, 320, 100, 10], 256, "xent", 14, 64), ([68, 36, 10], 260, "mse", 4, 64),
          ([256, 256, 256, 10], 1024, "mse", 16, 64), ([128, 128, 128, 10], 300, "xent", 12, 64), ([68, 36, 10], 260, "xent", 11, 64), ([784, 200, 10], 64, "xent", 24, 1)]
 
@@ -102,6 +102,36 @@ def test_long_neighbour_lists_take_the_pass(B, dims, batch, extra, on_the_way):
             B.dbw_destroy(h)
     assert got[B.MIX_CSR][1] and got[B.MIX_AUTO][1] != on_the_way
     assert np.array_equal(got[B.MIX_AUTO][0], got[B.MIX_CSR][0])
+
+
+@pytest.mark.parametrize("dims,batch,n,degree,on_the_way", [([784, 36, 10], 64, 37, 2, True), ([784, 36, 10], 64, 37, 4, False), ([784, 36, 10], 16, 40, 4, False),
+                                                            ([784, 36, 10], 32, 40, 4, True), ([784, 36, 10], 32, 40, 6, False), ([784, 100, 10], 8, 56, 6, True),
+                                                            ([256, 384, 10], 256, 24, 4, True), ([256, 384, 10], 256, 24, 6, False), ([64, 36, 10], 16, 7, 4, True),
+                                                            ([64, 36, 10], 16, 8, 4, False), ([64, 36, 10], 32, 9, 4, True), ([784, 384, 200, 10], 256, 12, 4, False)])
+def test_many_neighbours_take_the_pass(B, dims, batch, n, degree, on_the_way):
+    """Every worker linked to the nearest `degree` on a circle: how many the kernels average on the way depends on the tiles of the gradients."""
+    nb = [sorted({(i + k) % n for k in range(-(degree // 2), degree // 2 + 1)} - {i}) for i in range(n)]
+    rowptr, colidx = np.cumsum([0] + [len(s) for s in nb]).astype(np.int32), np.array(sum(nb, []), np.int32)
+    d = inputs.param_count({"kind": "mlp", "dims": dims, "loss": "xent"})
+    ld = inputs.pad_ld(d)
+    g = np.random.default_rng(6)
+    params = inputs.init_params({"kind": "mlp", "dims": dims, "loss": "xent"}, n, ld, g)
+    x, y = dev(g.standard_normal((n, batch, dims[0])).astype(np.float32)), dev(g.integers(0, dims[-1], (n, batch)).astype(np.int32))
+    t, b = dev(g.standard_exponential(n).astype(np.float32)), dev(np.ones(n, np.int32))
+    got, resolved = {}, B.MIX_AUTO
+    for name in ("auto", "pass"):
+        h = B.dbw_create(rowptr, colidx, n, d, ld=ld, model=B.make_model(B.MODEL_MLP, batch, dims), mix_path=resolved)
+        try:
+            resolved = B.dbw_mix_path(h)
+            out = torch.zeros(n, ld, device="cuda")
+            B.dbw_select(h, t, b)
+            B.dbw_set_timing(h, True)
+            B.dbw_round(h, dev(params), out, 0.05, batch_x=x, batch_y=y)
+            got[name] = (out.cpu().numpy(), any(k.startswith("mix_") for k in B.dbw_get_timing(h)))
+        finally:
+            B.dbw_destroy(h)
+    assert got["pass"][1] and got["auto"][1] != on_the_way
+    assert np.array_equal(got["auto"][0], got["pass"][0])
 
 
 @pytest.mark.parametrize("what", ["batch_x", "batch_y", "loss_out"])
