@@ -36,6 +36,9 @@ constexpr int DBW_TAIL_ROUNDS = 16;
 // with 4, 8 and 31 neighbours 54.2 / 46.7, 54.7 / 52.0 and 54.9 / 76.5; 48 workers, 300-92-10, batch 32, 8 neighbours 28.6 /
 // 30.1; 24 workers, 784-10, batch 32, 23 neighbours 23.5 / 42.3.
 constexpr int DBW_AVERAGE_DEGREE = 6;
+// Fewer where the parameters of a single layer fill an XCD's L2 of 4 MB, which the neighbours' rows are then fetched past: 784-10, batch 32,
+// on 64, 96 and 128 workers (4 MB) with 6 neighbours 20.8 / 19.0, 21.0 / 22.0 and 21.9 / 23.5, with 4 on 128 21.6 / 21.5, on 192 25.2 / 26.8,
+// with 2 on 192 24.6 / 25.5.
 // Fewer for the gradients of several layers (B samples), which come in so many tiles: fewer than a quarter of the chip's wavefronts,
 // and the launch that is saved is worth more; many rounds of them, and the tiles hide one another's fetches; in between every
 // neighbour shows.  Batches of up to 64, a wavefront per tile: 784-36-10, batch 64, with 4 neighbours on 37 workers (962 tiles) 33.5 / 36.2,
@@ -44,7 +47,7 @@ constexpr int DBW_AVERAGE_DEGREE = 6;
 // 6 on 40 (1 680) 133 / 138, 256-384-10 on 24 (576) 71.3 / 72.4.
 constexpr int average_degree(int L, int B, int64_t tiles, int64_t bytes)
 {
-    if (L == 1) return DBW_AVERAGE_DEGREE;
+    if (L == 1) return bytes < (int64_t)5 << 19 ? DBW_AVERAGE_DEGREE : (bytes < (int64_t)5 << 20 ? 4 : 0);
     if (B > 64) return tiles < 512 ? DBW_AVERAGE_DEGREE : 4;
     if (tiles < 512) return tiles < 256 ? DBW_AVERAGE_DEGREE : 4;
     if (tiles < 2048) return B > 32 ? (tiles < 1024 ? 2 : 4) : (B > 16 ? 4 : 2);
