@@ -13,7 +13,7 @@
 //   A fragment: lane l holds A[m = l % 16][k = l / 16], B fragment: B[k = l / 16][n = l % 16],
 //   D: d[v] = D[m = 4 * (l / 16) + v][n = l % 16].
 //
-// grid = (chunks x workers x parts).  With one chunk per worker (batches up to 64) the sums over the batch
+// grid = (chunks, workers), or chunks x workers x parts.  With one chunk per worker (batches up to 64) the sums over the batch
 // (dW, db, the bias gradient below, the loss) are final.  Otherwise they are written as per-chunk
 // partials and added in chunk order by reduce_kernel, a second launch: a "last workgroup to arrive
 // adds them" scheme inside one launch was measured and rejected, because the memory fence every
@@ -492,17 +492,22 @@ __global__ __launch_bounds__(THREADS) void kernel(Args g, int chunks, int items,
     float *Wl = zp + WAVES * 16 * 16;                // [C + 1][HP]: row C and the columns >= H are zero
     float *al = Wl + (C + 1) * HP + 16;              // [S][HP], rows >= ns and columns >= H zero
     const int tid = threadIdx.x;
-    // Workgroup i runs on XCD i % 8: eight chunks at a time, all their parts eight workgroups apart.  What is left of more than eight
-    // chunks has its parts side by side: gaps in the grid (as there are for fewer than eight chunks) made others wait for a compute unit
-    // where the grid nearly fills the chip (784-10 on 17 to 21 workers x 64 samples, two chunks each: 23 us a round, 28 with gaps).
-    const int whole = (items > 8 ? items / 8 : 1) * 8 * parts, rest = (int)blockIdx.x - whole;
-    int item = (int)blockIdx.x / (8 * parts) * 8 + (int)blockIdx.x % 8, part_no = (int)blockIdx.x / 8 % parts;
-    if (rest >= 0) {
-        item = items / 8 * 8 + rest / parts;
-        part_no = rest % parts;
+    // Of several parts workgroup i runs on XCD i % 8: eight chunks at a time, all their parts eight workgroups apart.  What is left of more
+    // than eight chunks has its parts side by side: gaps in the grid (as there are for fewer than eight chunks) made others wait for a compute
+    // unit where the grid nearly fills the chip (784-10 on 17 to 21 workers x 64 samples, two chunks each: 23 us a round, 28 with gaps).
+    int chunk = blockIdx.x, w = blockIdx.y, part_no = 0;
+    if (parts > 1) {
+        const int whole = (items > 8 ? items / 8 : 1) * 8 * parts, rest = (int)blockIdx.x - whole;
+        int item = (int)blockIdx.x / (8 * parts) * 8 + (int)blockIdx.x % 8;
+        part_no = (int)blockIdx.x / 8 % parts;
+        if (rest >= 0) {
+            item = items / 8 * 8 + rest / parts;
+            part_no = rest % parts;
+        }
+        if (item >= items) return;
+        chunk = item % chunks;
+        w = item / chunks;
     }
-    if (item >= items) return;
-    const int chunk = item % chunks, w = item / chunks;
     const int s0 = chunk * S, ns = min(S, g.B - s0);
     const float *__restrict__ a = g.a + w * g.a_stride + (int64_t)s0 * g.a_ld;
 

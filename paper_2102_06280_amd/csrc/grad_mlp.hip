@@ -590,7 +590,7 @@ int dbw_fc_forward_backward(dbw_ctx *c, dbw_fc_args &a, hipStream_t s)
         int parts = 1;
         if (head_splits == 0) parts = std::max(1, std::min((h.H + fchead::RUN - 1) / fchead::RUN, 256 / (head.chunks * N)));
         const int items = head.chunks * N;
-        const dim3 grid(items < 8 && parts > 1 ? 8 * parts : items * parts);
+        const dim3 grid = parts == 1 ? dim3(head.chunks, N) : dim3(items < 8 ? 8 * parts : items * parts);
         const size_t lds = fchead::lds_bytes(h.H, h.C, h.S);
         const bool vec = h.H % 4 == 0 && h.a_ld % 4 == 0 && h.a_stride % 4 == 0 && (uintptr_t)h.a % 16 == 0;
         const bool mse = a.loss_kind == DBW_LOSS_MSE;
