@@ -43,12 +43,13 @@ constexpr int DBW_AVERAGE_DEGREE = 6;
 // and the launch that is saved is worth more; many rounds of them, and the tiles hide one another's fetches; in between every
 // neighbour shows.  Batches of up to 64, a wavefront per tile: 784-36-10, batch 64, with 4 neighbours on 37 workers (962 tiles) 33.5 / 36.2,
 // batch 16, with 6 on 40 (1 040) 26.8 / 32.3; 784-64-10, batch 8, 6 on 48 (1 248) 32.9 / 35.2; 784-200-10, batch 64, with 4 on 128, where 80 MB
-// of parameters leave the L2 before the neighbours ask for them, 141.6 / 150.4.  Longer ones, four wavefronts per tile: 400-384-10, batch 256,
-// 6 on 40 (1 680) 133 / 138, 256-384-10 on 24 (576) 71.3 / 72.4.
-constexpr int average_degree(int L, int B, int64_t tiles, int64_t bytes)
+// of parameters leave the L2 before the neighbours ask for them, 141.6 / 150.4.  Longer ones, four
+// wavefronts per tile, in tiles of 64 x 64 (so many tiles that it need not be halves): 400-384-10, batch 256, 6 on 40 133 / 138, 256-384-10 on
+// 24 71.3 / 72.4.
+constexpr int average_degree(int L, int B, int64_t tiles, bool wide, int64_t bytes)
 {
     if (L == 1) return bytes < (int64_t)5 << 19 ? DBW_AVERAGE_DEGREE : (bytes < (int64_t)5 << 20 ? 4 : 0);
-    if (B > 64) return tiles < 512 ? DBW_AVERAGE_DEGREE : 4;
+    if (B > 64) return wide ? 4 : DBW_AVERAGE_DEGREE;
     if (tiles < 512) return tiles < 256 ? DBW_AVERAGE_DEGREE : 4;
     if (tiles < 2048) return B > 32 ? (tiles < 1024 ? 2 : 4) : (B > 16 ? 4 : 2);
     return B <= 32 || bytes < (int64_t)64 << 20 ? DBW_AVERAGE_DEGREE : 2;
@@ -64,15 +65,13 @@ constexpr int average_degree(int L, int B, int64_t tiles, int64_t bytes)
 // and 256 workers, 256-10, batch 1 024: 71 / 59 and 259 / 210.
 constexpr int average_list(int L, int B, int N) { return B > 64 ? 16 : (B > 32 || (L == 1 && N <= 48) ? 12 : 8); }
 // A context that averages densely adds up all workers' rows, on the way as in the pass: up to as many workers as a kernel has at
-// hand, fewer for the shortest batches, or, for batches of more than 64 in few tiles and for single layers, twelve, and any for a single
-// layer with several workgroups' sums (up to 23, with so few neighbours on average).  784-10, batch 32, on 6, 10, 12 and 16 workers 20.7 /
-// 18.1, 20.7 / 18.9, 22.0 / 21.0 and 21.8 / 23.4; 784-200-10, batch 64, on 7, 10 and 12 40.7 / 36.4, 43.1 / 42.7 and 46.3 / 48.6; 784-36-10,
-// batch 16, on 8 and 9 26.2 / 27.3 and 25.9 / 28.3; 256-256-256-10, batch 256, on 10 and 12 62.3 / 57.0 and 63.9 / 59.3; 784-384-200-10 on 12,
-// 140.5 / 150.4; 256-10, batch 1 024, on 12, 20 and 22 25.8 / 22.3, 32.7 / 29.2 and 32.9 / 30.2.
-constexpr int average_dense(int L, int B, int64_t tiles)
-{
-    return L == 1 || (B > 64 && tiles < 512) ? 12 : (B > 16 ? average::NEAR + 1 : 7);
-}
+// hand, fewer for the shortest batches, or, for batches of more than 64 in tiles of 64 x 32 and for single layers, twelve, and any for a
+// single layer with several workgroups' sums (up to 23, with so few neighbours on average).  784-10, batch 32, on 6, 10, 12 and 16 workers
+// 20.7 / 18.1, 20.7 / 18.9, 22.0 / 21.0 and 21.8 / 23.4; 784-200-10, batch 64, on 7, 10 and 12 40.7 / 36.4, 43.1 / 42.7 and 46.3 / 48.6;
+// 784-36-10, batch 16, on 8 and 9 26.2 / 27.3 and 25.9 / 28.3; 256-256-256-10, batch 256, on 10 and 12 61.8 / 57.1 and 63.1 / 60.0; in tiles
+// of 64 x 64, 784-384-384-10 on 9, 11 and 12 132.6 / 132.6, 151.8 / 158.1 and 159.9 / 167.7; 256-10, batch 1 024, on 12, 20 and 22 25.8 /
+// 22.3, 32.7 / 29.2 and 32.9 / 30.2.
+constexpr int average_dense(int L, int B, bool wide) { return L == 1 || (B > 64 && !wide) ? 12 : (B > 16 ? average::NEAR + 1 : 7); }
 constexpr int64_t DBW_AVERAGE_MAX_D = (int64_t)1 << 29;
 
 struct dbw_timing_slot {

@@ -497,11 +497,13 @@ int dbw_fc_forward_backward(dbw_ctx *c, dbw_fc_args &a, hipStream_t s)
     // The average on the way, where the head and one grouped launch store all gradients
     a.averaged = a.out && head.use && ((chain.use && chain.chunks > 1) || grouped || L == 1) && (L == 1 || (fc32::aligned16(a.out) && fc32::aligned16(params)));
     if (a.averaged && (L > 1 || head.chunks == 1)) {
-        const int64_t tiles = (int64_t)wgrad_tiles(Lw, dims, B, N, nullptr).tiles * N;
+        const WgradTiles wt = wgrad_tiles(Lw, dims, B, N, nullptr);
+        const bool wide = wt.tn == 64;
         if (c->mix == DBW_MIX_DENSE)
-            a.averaged = N <= average_dense(L, B, tiles);
+            a.averaged = N <= average_dense(L, B, wide);
         else
-            a.averaged = c->max_deg <= average_list(L, B, N) && c->nnz <= (int64_t)average_degree(L, B, tiles, 4 * c->d * N) * N;
+            a.averaged = c->max_deg <= average_list(L, B, N) &&
+                         c->nnz <= average_degree(L, B, (int64_t)wt.tiles * N, wide, 4 * c->d * N) * (int64_t)N;
     }
     // A short batch is one chunk of the head per worker, so that its sums over the batch are final.  When the grouped
     // launch follows, which adds per-chunk sums on the side, smaller chunks cost nothing and put the head on more CUs

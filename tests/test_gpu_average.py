@@ -106,9 +106,10 @@ def test_long_neighbour_lists_take_the_pass(B, dims, batch, extra, on_the_way):
 
 @pytest.mark.parametrize("dims,batch,n,degree,on_the_way", [([784, 36, 10], 64, 37, 2, True), ([784, 36, 10], 64, 37, 4, False), ([784, 36, 10], 16, 40, 4, False),
                                                             ([784, 36, 10], 32, 40, 4, True), ([784, 36, 10], 32, 40, 6, False), ([784, 100, 10], 8, 56, 6, True),
-                                                            ([256, 384, 10], 256, 24, 4, True), ([256, 384, 10], 256, 24, 6, False), ([784, 10], 8, 128, 4, True), ([784, 10], 8, 128, 6, False),
+                                                            ([256, 384, 10], 256, 24, 4, True), ([256, 384, 10], 256, 24, 6, False), ([128, 384, 10], 256, 30, 6, True),
+                                                            ([784, 10], 8, 128, 4, True), ([784, 10], 8, 128, 6, False),
                                                             ([784, 10], 8, 192, 2, False), ([784, 10], 70, 192, 2, True), ([64, 36, 10], 16, 7, 4, True),
-                                                            ([64, 36, 10], 16, 8, 4, False), ([64, 36, 10], 32, 9, 4, True), ([784, 384, 200, 10], 256, 12, 4, False)])
+                                                            ([64, 36, 10], 16, 8, 4, False), ([64, 36, 10], 32, 9, 4, True), ([784, 384, 200, 10], 256, 12, 4, False), ([256, 256, 256, 10], 300, 12, 4, True)])
 def test_many_neighbours_take_the_pass(B, dims, batch, n, degree, on_the_way):
     """Every worker linked to the nearest `degree` on a circle: how many the kernels average on the way depends on the tiles of the gradients."""
     nb = [sorted({(i + k) % n for k in range(-(degree // 2), degree // 2 + 1)} - {i}) for i in range(n)]
