@@ -34,7 +34,17 @@ typedef __attribute__((address_space(1))) const void *global_cptr;
 typedef __attribute__((address_space(3))) void *lds_ptr;
 
 constexpr int DENSE_THREADS = 512;
-using mixsplit::uniform_base;
+// The base of an access: scalar, plus a 32-bit lane offset (see global_access.h).  A generic pointer here, hence flat instructions: with
+// global ones the guarded gradient loads of the epilogue are slower, 20 workers x 4 M columns 238 us against 229 (elsewhere the same).
+__device__ __forceinline__ const char *uniform_base(const void *p)
+{
+    const uint64_t a = (uint64_t)p;
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
+    uint64_t v = ((uint64_t)hi << 32) | lo;
+    asm volatile("" : "+s"(v));
+    return (const char *)v;
+}
 
 constexpr int NPAD = 32;                              // padded number of workers
 constexpr int KB = NPAD / 2;                          // k-steps of the 32x32x2 instruction

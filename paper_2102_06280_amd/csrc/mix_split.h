@@ -23,6 +23,11 @@
 // shares its lines with the next piece goes to memory twice past the caches: N = 128 x 1 M without gradients, rows of 4-byte, 16-byte
 // and 64-byte boundaries 355, 337 and 265 us, past the caches 521, 478 and 263, with gradients 445, 441 and 358, 595, 639 and 410.  (Loads
 // past the caches cost up to 64 workers: N = 60 x 200 000 33 -> 35.)
+// The stores are global ones (global_access.h): as flat ones every wait for LDS waited for them as well, N = 128 x 2.8 M
+// without gradients 677 -> 662, N = 256 x 1 M 829 and 832.  The multiplies cost time although they overlap the memory side: without them the two take 631 and 565.
+// The chip runs at 1.7 GHz then (2.4 in a copy), and schedules that keep the matrix cores busier are slower: the two wavefronts
+// of a SIMD half a tile apart, one multiplying while the other stores and splits, 906 and 747 (881 and 768 with each fragment requested
+// right behind the last multiply that reads the one before it).
 // Tried without gain: two tiles of X on their way instead of one (685), one 64-column tile with a single set of
 // planes (0.88), wave priorities for either phase, LDS fragments requested a step ahead.
 //
@@ -32,25 +37,15 @@
 #include <type_traits>
 
 #include "dbw_internal.h"
+#include "global_access.h"
 #include "split_bf16.h"
 
 namespace mixsplit {
 
-constexpr int64_t CACHE_BYTES = (int64_t)256 << 20;    // the last-level cache
+using global_access::bytes;
+using global_access::uniform_base;
 
-// A wave-uniform address, pinned to scalar registers.  Global loads and stores take a scalar
-// base plus a 32-bit lane offset; without the pin the compiler folds the lane offset into one
-// loop-invariant 64-bit vector address per row, and those dozens of register pairs push the
-// P block out to scratch memory.
-__device__ __forceinline__ const char *uniform_base(const void *p)
-{
-    const uint64_t a = (uint64_t)p;
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a);
-    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
-    uint64_t v = ((uint64_t)hi << 32) | lo;
-    asm volatile("" : "+s"(v));
-    return (const char *)v;
-}
+constexpr int64_t CACHE_BYTES = (int64_t)256 << 20;    // the last-level cache
 
 // MB: 32-row blocks of the padded P; WAVES: wavefronts of a workgroup.
 template <int MB, int WAVES>
@@ -70,7 +65,7 @@ struct Cfg {
 // whichever LDS array that is from.  The kernel waits itself (vmcnt) before it reads what they bring.  (m0, the LDS
 // address of such a load, has no other user in this kernel.)  STREAM: not kept in the caches.
 template <bool WIDE, bool STREAM>
-__device__ __forceinline__ void load_to_lds(const char *base, uint32_t lane_off, const float *dst)
+__device__ __forceinline__ void load_to_lds(bytes base, uint32_t lane_off, const float *dst)
 {
     const uint32_t m0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) const float *)dst);
     if (WIDE && STREAM)
@@ -246,16 +241,16 @@ __global__ __launch_bounds__(64 * WAVES, 2) void kernel(
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 if constexpr (STREAM)
-                    __builtin_nontemporal_store(acc[v], (float *)(const_cast<char *>(uniform_base(out + (int64_t)(32 * rb + 8 * (v / 4) + (v & 3)) * ld + col0)) + lane_off));
+                    global_access::store_stream(out + (int64_t)(32 * rb + 8 * (v / 4) + (v & 3)) * ld + col0, lane_off, acc[v]);
                 else
-                    *(float *)(const_cast<char *>(uniform_base(out + (int64_t)(32 * rb + 8 * (v / 4) + (v & 3)) * ld + col0)) + lane_off) = acc[v];
+                    global_access::store(out + (int64_t)(32 * rb + 8 * (v / 4) + (v & 3)) * ld + col0, lane_off, acc[v]);
             }
         } else {
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int row0 = 32 * rb + 8 * (v / 4) + (v & 3);
                 if (row0 + 4 * (lane >> 5) < N && col0 + (lane & 31) < dcols)
-                    *(float *)(const_cast<char *>(uniform_base(out + (int64_t)row0 * ld + col0)) + lane_off) = acc[v];
+                    global_access::store(out + (int64_t)row0 * ld + col0, lane_off, acc[v]);
             }
         }
 
