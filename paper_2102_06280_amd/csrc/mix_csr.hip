@@ -147,7 +147,7 @@ __global__ __launch_bounds__(LDS_THREADS) void mix_lds_tiles(
         }
     };
 
-    int64_t t = blockIdx.x;
+    int64_t t = first_tile(blockIdx.x, gridDim.x);
     if (t >= n_tiles) return;
     fetch(t);
 #pragma unroll
@@ -372,8 +372,8 @@ int launch_groups(dbw_ctx *c, const float *x, const float *g, float *out, LR lr,
 template <int ORDER, bool HAS_G, class LR>
 int launch(dbw_ctx *c, const float *x, const float *g, float *out, LR lr, hipStream_t s)
 {
-    // Rows without padding or on odd addresses (N = 48 x 1 000 003 columns, row stride 1 000 003: 129 us against 106 on
-    // padded rows; N = 128 x 2.8 M: 1.08 ms against 0.82).
+    // Rows without padding or on odd addresses (N = 48 x 1 000 003 columns, row stride 1 000 003: 121 us against 106 on
+    // padded rows; N = 128 x 2.8 M: 0.87 ms against 0.82).
     const bool wide = (c->ld % 4 == 0) && ((uintptr_t)x % 16 == 0) && ((uintptr_t)out % 16 == 0) &&
                       (!HAS_G || (uintptr_t)g % 16 == 0);
     if (wide) return launch_groups<ORDER, HAS_G, true, LR>(c, x, g, out, lr, s);

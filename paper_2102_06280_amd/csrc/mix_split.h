@@ -21,7 +21,8 @@
 // there when the next round reads them: rounds one after the other of N = 64 x 100 000 and x 400 000 without gradients 12.4 and 35.6 us,
 // past the caches 14.0 and 42.3; the first with gradients 15.7, 16.9; N = 256 x 50 000 with gradients 47, 49.6.  A piece of a row that
 // shares its lines with the next piece goes to memory twice past the caches: N = 128 x 1 M without gradients, rows of 4-byte, 16-byte
-// and 64-byte boundaries 355, 337 and 265 us, past the caches 521, 478 and 263, with gradients 445, 441 and 358, 595, 639 and 410.  (Loads
+// and 64-byte boundaries 355, 337 and 265 us, past the caches 521, 478 and 263, with gradients 445, 441 and 358, 595, 639 and 410 (with
+// neighbouring tiles on XCDs of their own, before first_tile took them together: 445 -> 388).  (Loads
 // past the caches cost up to 64 workers: N = 60 x 200 000 33 -> 35.)
 // The stores are global ones (global_access.h): as flat ones every wait for LDS waited for them as well, N = 128 x 2.8 M
 // without gradients 677 -> 662, N = 256 x 1 M 829 and 832.  The multiplies cost time although they overlap the memory side: without them the two take 631 and 565.
@@ -113,7 +114,8 @@ __global__ __launch_bounds__(64 * WAVES, 2) void kernel(
     const int rb = w % MB, cg = w / MB;                          // block of the result
     const int fr = w / C::CBLOCKS * C::RW, fc = w % C::CBLOCKS * C::CW;   // first row and column of the block it splits
 
-    int64_t tile = blockIdx.x;
+    // (rows on lines, past the caches: as they come, N = 128 x 1 M with gradients 308 us, 311 otherwise)
+    int64_t tile = STREAM ? blockIdx.x : first_tile(blockIdx.x, gridDim.x);
     if (tile >= n_tiles) return;
 
     // ---- a block of ROWS x (1024 / ROWS) elements of tile t at (r0, c0) -> 4 KB of LDS, row after row, by LOADS
