@@ -64,11 +64,13 @@ __device__ __forceinline__ Row row(const Args &a, int w)
     return r;
 }
 
-// V: float or a vector of floats with the alignment of the accesses
+// V: float or a vector of floats; in memory on any 4-byte boundary
 template <class V>
 struct lanes {
     static constexpr int n = sizeof(V) / sizeof(float);
 };
+template <class V>
+using any_boundary __attribute__((aligned(4))) = V;
 template <class V>
 __device__ __forceinline__ V fma(float w, V x, V acc)
 {
@@ -91,7 +93,7 @@ __device__ __forceinline__ void gather(const Args &a, const Row &r, int w, int64
     auto load = [&](int j, V (&v)[N]) {
         const char *row = (const char *)(a.x + (int64_t)j * a.ld + base);
 #pragma unroll
-        for (int n = 0; n < N; ++n) v[n] = *(const V *)(row + off[n]);
+        for (int n = 0; n < N; ++n) v[n] = *(const any_boundary<V> *)(row + off[n]);
     };
     auto add = [&](float wt, const V (&v)[N]) {
 #pragma unroll

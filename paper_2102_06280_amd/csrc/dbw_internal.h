@@ -46,9 +46,11 @@ constexpr int DBW_AVERAGE_DEGREE = 6;
 // of parameters leave the L2 before the neighbours ask for them, 141.6 / 150.4.  Longer ones, four
 // wavefronts per tile, in tiles of 64 x 64 (so many tiles that it need not be halves): 400-384-10, batch 256, 6 on 40 133 / 138, 256-384-10 on
 // 24 71.3 / 72.4.
-constexpr int average_degree(int L, int B, int64_t tiles, bool wide, int64_t bytes)
+constexpr int average_degree(int L, int B, int64_t tiles, bool wide, bool thin, int64_t bytes)
 {
     if (L == 1) return bytes < (int64_t)5 << 19 ? DBW_AVERAGE_DEGREE : (bytes < (int64_t)5 << 20 ? 4 : 0);
+    // (mlp_thin.h on more than 64 samples: 784-300-10 on 64 x 128, 60 MB, 163 us with the pass, 174 on the way)
+    if (B > 64 && thin) return bytes < (int64_t)56 << 20 ? DBW_AVERAGE_DEGREE : 2;
     if (B > 64) return wide ? 4 : DBW_AVERAGE_DEGREE;
     if (tiles < 512) return tiles < 256 ? DBW_AVERAGE_DEGREE : 4;
     if (tiles < 2048) return B > 32 ? (tiles < 1024 ? 2 : 4) : (B > 16 ? 4 : 2);

@@ -234,6 +234,53 @@ ChainPlan chain_plan(int L, const int32_t *dims, int B, int workers, int grad_pa
     return cp;
 }
 
+// How mlpthin::forward_kernel cuts up a product of B x K by K x N: blocks of at most 64 samples, tiles of 32 or 16 outputs, and, where the
+// sums may be left to the reader, parts of the reduction: whatever gives the shortest time, in cycles, for the compute unit with most
+// workgroups.  A wavefront takes every eighth chunk of 16 k, for which the matrix instructions (two wavefronts to a SIMD) and the loads take about
+// as long as said here; a part more is a sum more for the reader.
+struct ThinPlan {
+    int RB, CB, blocks, splits, kper;
+    int64_t wgs;
+};
+ThinPlan thin_plan(int B, int K, int N, int workers, bool may_split)
+{
+    ThinPlan best{};
+    int64_t least = 0;
+    const int chunks = (K + 15) / 16, blocks = (B + 63) / 64, RB = ((B + blocks - 1) / blocks + 15) / 16;
+    for (int splits = 1; splits <= (may_split ? 8 : 1); splits *= 2)
+        for (int CB = 2; CB >= 1; --CB) {
+            const int kper = (chunks + splits - 1) / splits;
+            if (splits > 1 && kper < mlpthin::FWD_WAVES) continue;
+            const int64_t wgs = (int64_t)((N + 16 * CB - 1) / (16 * CB)) * blocks * splits * workers;
+            const int64_t iter = std::max(256 * RB * CB, 164 * (RB + CB));
+            const int64_t cost = (wgs + 255) / 256 * ((kper + mlpthin::FWD_WAVES - 1) / mlpthin::FWD_WAVES) * iter + 500 * (splits - 1);
+            if (best.wgs == 0 || cost < least) {
+                least = cost;
+                best = {RB, CB, blocks, splits, kper, wgs};
+            }
+        }
+    return best;
+}
+
+template <bool BACK>
+hipError_t launch_thin(const ThinPlan &tp, const mlpthin::FwdArgs &f, hipStream_t s)
+{
+    const int tiles = (f.N + 16 * tp.CB - 1) / (16 * tp.CB) * f.workers;
+    const dim3 grid((tiles + mlpthin::XCDS - 1) / mlpthin::XCDS * mlpthin::XCDS, tp.blocks, tp.splits), block(mlpthin::FWD_THREADS);
+    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, block, 0, s, f); };
+    switch (8 * tp.RB + tp.CB) {
+    case 8 * 1 + 1: go(mlpthin::forward_kernel<1, 1, BACK>); break;
+    case 8 * 2 + 1: go(mlpthin::forward_kernel<2, 1, BACK>); break;
+    case 8 * 3 + 1: go(mlpthin::forward_kernel<3, 1, BACK>); break;
+    case 8 * 4 + 1: go(mlpthin::forward_kernel<4, 1, BACK>); break;
+    case 8 * 1 + 2: go(mlpthin::forward_kernel<1, 2, BACK>); break;
+    case 8 * 2 + 2: go(mlpthin::forward_kernel<2, 2, BACK>); break;
+    case 8 * 3 + 2: go(mlpthin::forward_kernel<3, 2, BACK>); break;
+    default: go(mlpthin::forward_kernel<4, 2, BACK>); break;
+    }
+    return hipGetLastError();
+}
+
 // Weight and bias gradients of layers 1 .. layers in one launch (mlp_wgrad.h), from the deltas and activations
 // in the workers' scratch blocks; extra workgroups add the head's per-chunk sums when it has any.
 struct WgradPlan {
@@ -242,14 +289,22 @@ struct WgradPlan {
     const int64_t *a_off, *dz_off, *w_off;
     int64_t w_end;              // end of b_layers in the parameter row
     int64_t per, split_floats;
+    bool chain;                 // the chain kernel has run
 };
 // The tiles of that launch: 64 x 64 when they alone give every CU two workgroups, else 64 x 32; if that still leaves CUs idle, the
 // batch is split as well (partial tiles to scratch, one more launch to add them).  begin, if not null: the first tile of every layer.
+// Batches of up to 64 samples take mlp_thin.h.  Longer ones, up to 255, while there is little to multiply (tiles x samples): one launch
+// instead of two or three, and the average on the way, but the fp32 instruction instead of six of bf16; less of it where there are layers
+// between, whose data gradient bgemm::backward_kernel computes in the same launch.  Rounds, bgemm.h / mlp_thin.h: 784-500-10 on 32 workers
+// x 128 (0.9 M) 141 / 128 us, x 200 (1.3 M) 200 / 192, 64 x 255 (3.4 M) 381 / 468; 300-300-300-10 on 32 x 128 (0.4 M) 127 / 115, 63 x 200
+// (1.3 M) 298 / 314.  Behind the chain (whose alternative, mlp_wgrad.h, shares a tile among four wavefronts) not with fewer tiles than
+// SIMDs: 784-128-10 on 16 x 200 43.8 / 44.8, 784-512-10 on 32 x 128 135 / 122.
+constexpr int64_t THIN_WORK = 1400000, THIN_WORK_DEEP = 700000;
 struct WgradTiles {
     bool thin;                  // one wavefront per 32 x 64 tile, no split (mlp_thin.h)
     int tn, tiles;
 };
-WgradTiles wgrad_tiles(int layers, const int32_t *dims, int B, int N, int *begin)
+WgradTiles wgrad_tiles(int layers, const int32_t *dims, int B, int N, bool chain, int *begin)
 {
     auto count = [&](int tm, int tn, int *begin) {
         int t = 0;
@@ -261,7 +316,8 @@ WgradTiles wgrad_tiles(int layers, const int32_t *dims, int B, int N, int *begin
         return t;
     };
     WgradTiles r{};
-    r.thin = B <= mlpthin::MAX_B;
+    const int64_t tiles = (int64_t)count(mlpthin::WG_TM, mlpthin::WG_TN, nullptr) * N;
+    r.thin = B <= 64 || (B <= mlpthin::MAX_B && tiles * B <= (layers == 1 ? THIN_WORK : THIN_WORK_DEEP) && (!chain || tiles >= 1024));
     r.tn = !r.thin && (int64_t)count(64, 64, nullptr) * N >= 512 ? 64 : 32;
     r.tiles = r.thin ? count(mlpthin::WG_TM, mlpthin::WG_TN, begin) : count(64, r.tn, begin);
     return r;
@@ -275,7 +331,7 @@ int launch_grouped_wgrad(dbw_ctx *c, const dbw_fc_args &a, const WgradPlan &wp, 
     const int64_t wstride = a.act_stride;
     mlpwgrad::Args q{};
     q.B = B; q.layers = wp.layers; q.workers = N;
-    const WgradTiles wt = wgrad_tiles(wp.layers, dims, B, N, q.tile_begin);
+    const WgradTiles wt = wgrad_tiles(wp.layers, dims, B, N, wp.chain, q.tile_begin);
     const bool thin = wt.thin;
     const int tn = wt.tn, tiles = wt.tiles;
     for (int l = 1; l <= wp.layers; ++l) {
@@ -306,16 +362,14 @@ int launch_grouped_wgrad(dbw_ctx *c, const dbw_fc_args &a, const WgradPlan &wp, 
         auto whole_xcds = [](int n) { return (n + mlpwgrad::XCDS - 1) / mlpwgrad::XCDS * mlpwgrad::XCDS; };
         const int tile_wgs = thin ? (tiles * N + mlpwgrad::WAVES - 1) / mlpwgrad::WAVES : tiles * N * splits;
         const dim3 grid(whole_xcds(head_blocks * N) + whole_xcds(tile_wgs));
-        if (thin && B <= 16)
-            hipLaunchKernelGGL(mlpthin::wgrad_kernel<4>, grid, dim3(mlpwgrad::THREADS), 0, s, q, h, head_chunks, head_blocks);
-        else if (thin && B <= 32)
-            hipLaunchKernelGGL(mlpthin::wgrad_kernel<8>, grid, dim3(mlpwgrad::THREADS), 0, s, q, h, head_chunks, head_blocks);
-        else if (thin)
-            hipLaunchKernelGGL(mlpthin::wgrad_kernel<16>, grid, dim3(mlpwgrad::THREADS), 0, s, q, h, head_chunks, head_blocks);
-        else if (tn == 64)
-            hipLaunchKernelGGL(mlpwgrad::kernel<4>, grid, dim3(mlpwgrad::THREADS), 0, s, q, h, head_chunks, head_blocks);
-        else
-            hipLaunchKernelGGL(mlpwgrad::kernel<2>, grid, dim3(mlpwgrad::THREADS), 0, s, q, h, head_chunks, head_blocks);
+        auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, dim3(mlpwgrad::THREADS), 0, s, q, h, head_chunks, head_blocks); };
+        if (thin && B <= 16) go(mlpthin::wgrad_kernel<4, false>);
+        else if (thin && B <= 32) go(mlpthin::wgrad_kernel<8, false>);
+        else if (thin && B <= 64) go(mlpthin::wgrad_kernel<16, false>);
+        else if (thin && (B + 51) / 52 * 13 < (B + 63) / 64 * 16) go(mlpthin::wgrad_kernel<13, true>);    // steps of 52 samples: less padding
+        else if (thin) go(mlpthin::wgrad_kernel<16, true>);
+        else if (tn == 64) go(mlpwgrad::kernel<4>);
+        else go(mlpwgrad::kernel<2>);
         DBW_HIP(hipGetLastError());
     }
     if (splits > 1) {
@@ -439,24 +493,19 @@ int dbw_fc_forward_backward(dbw_ctx *c, dbw_fc_args &a, hipStream_t s)
             continue;
         }
         // short batches: operands straight from global memory into matrix-instruction fragments (mlp_thin.h)
-        if (a.grad_path == DBW_GRAD_AUTO && B <= mlpthin::MAX_B && dims[l - 1] % 4 == 0 && dims[l] % 4 == 0 &&
-            A.ld % 4 == 0 && A.stride % 4 == 0 && fc32::aligned16(A.p) && fc32::aligned16(params) && c->ld % 4 == 0 &&
-            w_off[l] % 4 == 0 && fc32::aligned16(act) && wstride % 4 == 0 && a_off[l] % 4 == 0) {
+        // (more tiles, of longer batches: the GEMM kernel, whose wavefronts share what they fetch; 1023-511-509-10 on 30 x 250
+        // 151 us, mlp_thin.h 229, 784-500-10 on 32 x 200 76 and 82, x 128 46 and 46, 300-300-300-10 on 32 x 128 51 and 41)
+        const ThinPlan tp = thin_plan(B, dims[l - 1], dims[l], N, head_can_sum && l == L - 1);
+        if (a.grad_path == DBW_GRAD_AUTO && B <= mlpthin::MAX_B && dims[l - 1] >= 4 && (l > 1 || fc32::aligned16(a.in)) && (B <= 64 || tp.wgs * tp.CB <= 2048)) {
             mlpthin::FwdArgs f{};
             f.B = B; f.K = dims[l - 1]; f.N = dims[l]; f.workers = N; f.relu = l < L ? 1 : 0;
+            f.splits = tp.splits; f.kper = tp.kper;
             f.a = A.p; f.a_ld = A.ld; f.a_stride = A.stride;
             f.params = params; f.p_stride = c->ld; f.w_off = w_off[l]; f.b_off = b_off[l];
-            f.out = act + a_off[l]; f.out_stride = wstride;
-            const int wgs = (dims[l] + 16 * mlpthin::FWD_CB - 1) / (16 * mlpthin::FWD_CB) * N;
-            const dim3 grid((wgs + mlpthin::XCDS - 1) / mlpthin::XCDS * mlpthin::XCDS), block(mlpthin::FWD_THREADS);
+            f.out = tp.splits > 1 ? act + 2 * per : act + a_off[l]; f.out_stride = wstride;
             dbw_timer tm(c, "mlp_thin_forward", s);
-            switch ((B + 15) / 16) {
-            case 1: hipLaunchKernelGGL(mlpthin::forward_kernel<1>, grid, block, 0, s, f); break;
-            case 2: hipLaunchKernelGGL(mlpthin::forward_kernel<2>, grid, block, 0, s, f); break;
-            case 3: hipLaunchKernelGGL(mlpthin::forward_kernel<3>, grid, block, 0, s, f); break;
-            default: hipLaunchKernelGGL(mlpthin::forward_kernel<4>, grid, block, 0, s, f); break;
-            }
-            DBW_HIP(hipGetLastError());
+            DBW_HIP(launch_thin<false>(tp, f, s));
+            if (tp.splits > 1) head_splits = tp.splits;
             continue;
         }
         const int splits = forward_splits(B, dims[l], dims[l - 1], N);
@@ -483,27 +532,32 @@ int dbw_fc_forward_backward(dbw_ctx *c, dbw_fc_args &a, hipStream_t s)
         DBW_HIP(bgemm::launch<64>(A, Bm, E, B, dims[l], dims[l - 1], N, s));
     }
     // Weight gradients of the layers the GEMM kernels would take: all of them in one launch when the library may
-    // choose and every operand allows 128-bit accesses.  Batches of 256 and more: mlp_wgrad.h, four wavefronts per
-    // tile, which share the samples.  Batches of at most 64: mlp_thin.h, a tile per wavefront.  In between the GEMM
-    // kernel, whose wavefronts share the tile, stays (784-200-10 with 64 samples on 32 workers: the four-wavefront
-    // kernel 26 us, the GEMM kernel 21 us, a tile per wavefront 18 us).  The batch-32 streaming kernels keep their layers.
+    // choose.  Batches of 256 and more: mlp_wgrad.h, four wavefronts per tile, which share the samples, where every operand allows 128-bit
+    // accesses.  Shorter ones: mlp_thin.h, a tile per wavefront, on any widths (a batch that starts off a 16-byte boundary, which no
+    // allocation does, keeps the GEMM kernels, which have been tested on it).  The batch-32 streaming kernels keep their layers.
     const int Lw = head.use ? L - 1 : L;
-    bool grouped = !chain.use && a.grad_path == DBW_GRAD_AUTO && Lw >= 1 && (B >= 256 || B <= mlpthin::MAX_B) &&
-                   a.in_ld % 4 == 0 && a.in_stride % 4 == 0 && fc32::aligned16(a.in) && fc32::aligned16(grads) &&
-                   c->ld % 4 == 0 && a.param_off % 4 == 0 && fc32::aligned16(act) && wstride % 4 == 0;
-    for (int l = 0; l <= Lw && grouped; ++l) grouped = dims[l] % 4 == 0;
+    bool grouped = !chain.use && a.grad_path == DBW_GRAD_AUTO && Lw >= 1 && fc32::aligned16(a.in);
+    const WgradTiles wt = wgrad_tiles(Lw, dims, B, N, chain.use, nullptr);
+    const bool thin = wt.thin;
+    if (B <= mlpthin::MAX_B) {
+        grouped = grouped && thin;
+        for (int l = 1; l <= Lw && grouped; ++l) grouped = dims[l - 1] >= 4 && dims[l] >= 2;
+    } else {
+        grouped = grouped && a.in_ld % 4 == 0 && a.in_stride % 4 == 0 && fc32::aligned16(grads) &&
+                  c->ld % 4 == 0 && a.param_off % 4 == 0 && fc32::aligned16(act) && wstride % 4 == 0;
+        for (int l = 0; l <= Lw && grouped; ++l) grouped = dims[l] % 4 == 0;
+    }
     for (int l = 1; l <= Lw && grouped; ++l)
         grouped = !batch32_layer(B, dims[l - 1], dims[l], c->ld, w_off[l], params, grads);
     // The average on the way, where the head and one grouped launch store all gradients
-    a.averaged = a.out && head.use && ((chain.use && chain.chunks > 1) || grouped || L == 1) && (L == 1 || (fc32::aligned16(a.out) && fc32::aligned16(params)));
+    a.averaged = a.out && head.use && ((chain.use && chain.chunks > 1) || grouped || L == 1) && (L == 1 || (c->ld % 4 == 0 && fc32::aligned16(a.out) && fc32::aligned16(params)));
     if (a.averaged && (L > 1 || head.chunks == 1)) {
-        const WgradTiles wt = wgrad_tiles(Lw, dims, B, N, nullptr);
         const bool wide = wt.tn == 64;
         if (c->mix == DBW_MIX_DENSE)
-            a.averaged = N <= average_dense(L, B, wide);
+            a.averaged = N <= average_dense(L, B, wide || thin);
         else
             a.averaged = c->max_deg <= average_list(L, B, N) &&
-                         c->nnz <= average_degree(L, B, (int64_t)wt.tiles * N, wide, 4 * c->d * N) * (int64_t)N;
+                         c->nnz <= average_degree(L, B, (int64_t)wt.tiles * N, wide, thin, 4 * c->d * N) * (int64_t)N;
     }
     // A short batch is one chunk of the head per worker, so that its sums over the batch are final.  When the grouped
     // launch follows, which adds per-chunk sums on the side, smaller chunks cost nothing and put the head on more CUs
@@ -582,7 +636,7 @@ int dbw_fc_forward_backward(dbw_ctx *c, dbw_fc_args &a, hipStream_t s)
             if (rc != DBW_OK) return rc;
 
             // weight and bias gradients of the layers below the head, and the head's per-chunk sums
-            const WgradPlan wp{L - 1, false, a_off, dz_off, w_off, w_off[L], per, split_floats};
+            const WgradPlan wp{L - 1, false, a_off, dz_off, w_off, w_off[L], per, split_floats, true};
             const int rc2 = launch_grouped_wgrad(c, a, wp, h, head.chunks, s);
             if (rc2 != DBW_OK) return rc2;
             return DBW_OK;
@@ -645,6 +699,7 @@ int dbw_fc_forward_backward(dbw_ctx *c, dbw_fc_args &a, hipStream_t s)
             l > 1 ? Epilogue{act + dz_off[l - 1], dims[l - 1], wstride, nullptr, 0, act + a_off[l - 1], dims[l - 1], wstride, 0}
                   : Epilogue{a.din, a.din_ld, a.din_stride, nullptr, 0, nullptr, 0, 0, 0},
             B, dims[l - 1], dims[l]);
+        const ThinPlan dgrad_thin = thin_plan(B, dims[l], dims[l - 1], N, false);
         bool bias = !grouped && !(head.use && l == L - 1);   // (the head has written the bias gradient of the layer below it)
         if (!grouped) {   // dW_l = dz_l^T a_{l-1}
             Dense<false> A{act + dz_off[l], dims[l], wstride}, Bm;
@@ -709,6 +764,16 @@ int dbw_fc_forward_backward(dbw_ctx *c, dbw_fc_args &a, hipStream_t s)
                                act + dz_off[1], (int64_t)dims[1], wstride, params + w_off[1], c->ld,
                                (const float *)nullptr, (int64_t)0, (int64_t)0, a.din, a.din_ld, a.din_stride);
             DBW_HIP(hipGetLastError());
+        } else if (dgrad_gemm && l > 1 && grouped && thin && dims[l] >= 4 && (B <= 64 || dgrad_thin.wgs * dgrad_thin.CB <= 2048)) {
+            mlpthin::FwdArgs f{};
+            f.B = B; f.K = dims[l]; f.N = dims[l - 1]; f.workers = N;
+            f.splits = 1; f.kper = dgrad_thin.kper;
+            f.a = act + dz_off[l]; f.a_ld = dims[l]; f.a_stride = wstride;
+            f.params = params; f.p_stride = c->ld; f.w_off = w_off[l];
+            f.out = act + dz_off[l - 1]; f.out_stride = wstride;
+            f.mask = act + a_off[l - 1];
+            dbw_timer tm(c, "mlp_thin_dgrad", s);
+            DBW_HIP(launch_thin<true>(dgrad_thin, f, s));
         } else if (dgrad_gemm) {
             // Next to another kernel's weight gradient the launch is short, and the fp32 instruction with unguarded 16-byte loads is
             // faster unless both the reduction and the grid are long (four wavefronts for every compute unit and more): 10 x 256
@@ -725,7 +790,7 @@ int dbw_fc_forward_backward(dbw_ctx *c, dbw_fc_args &a, hipStream_t s)
         }
     }
     if (grouped) {
-        const WgradPlan wp{Lw, !head.use, a_off, dz_off, w_off, b_off[Lw] + dims[Lw], per, split_floats};
+        const WgradPlan wp{Lw, !head.use, a_off, dz_off, w_off, b_off[Lw] + dims[Lw], per, split_floats, false};
         return launch_grouped_wgrad(c, a, wp, h, head.use ? head.chunks : 1, s);
     }
     return DBW_OK;
