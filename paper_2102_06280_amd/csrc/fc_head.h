@@ -1,4 +1,4 @@
-// The classifier head of a model in one launch: last fully connected layer (H -> C, C <= 16),
+// The classifier head of a model in one launch: last fully connected layer (H -> C, C <= 32),
 // softmax, loss, and everything of the backward pass that hangs on it (Section 2.1, stochastic
 // gradient of the local loss; cross-entropy as in Section 5, squared error of the softmax outputs
 // as for the 2NN of Appendix B):
@@ -8,10 +8,13 @@
 //        bias gradient of the layer below), unmasked when a is the model's input
 // As separate launches these thin products cost five to eight kernels of 4-13 us each, mostly
 // latency.  Here one workgroup takes S = 16, 32 or 64 samples of one worker, keeps them and W in LDS
-// and runs the three products on the matrix cores with the class dimension padded to the 16
+// and runs the three products on the matrix cores with the class dimension padded to one or two times (CT) the 16
 // columns of v_mfma_f32_16x16x4_f32 (true fp32):
 //   A fragment: lane l holds A[m = l % 16][k = l / 16], B fragment: B[k = l / 16][n = l % 16],
 //   D: d[v] = D[m = 4 * (l / 16) + v][n = l % 16].
+//
+// More than 16 classes used to take the forward GEMM, softmax_loss_kernel and the backward GEMM of the layer: 617-301-75-26 on
+// 20 workers x 101 samples 82 us a round, here 67; 256-25 on 6 x 1 024 39 and 26, 784-500-30 on 16 x 32 73 and 47.  More than 32 still do.
 //
 // grid = (chunks, workers), or chunks x workers x parts.  With one chunk per worker (batches up to 64) the sums over the batch
 // (dW, db, the bias gradient below, the loss) are final.  Otherwise they are written as per-chunk
@@ -32,7 +35,8 @@ namespace fchead {
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int THREADS = 512, WAVES = THREADS / 64;
-constexpr int MAX_C = 16;            // classes, padded to 16
+constexpr int TILE_C = 16;           // classes of one tile of the matrix instruction
+constexpr int MAX_C = 2 * TILE_C;    // classes, padded to a multiple of 16
 constexpr int MAX_S = 64;            // samples per workgroup: 16, 32 or 64
 constexpr int MAX_CHUNKS = 256;
 constexpr size_t LDS_LIMIT = 159 * 1024;     // dynamic part; the kernel also has a few bytes of static LDS
@@ -95,10 +99,11 @@ __host__ __device__ inline int row_pitch(int H)
 }
 __host__ __device__ inline size_t lds_floats(int H, int C, int S)
 {
-    // dz / logits [64][16], partial logits [8 waves][16][16], W image [C + 1][pitch] (the last row is zero and
+    // dz / logits [64][16 CT], partial logits [8 waves][16][16 CT], W image [C + 1][pitch] (the last row is zero and
     // stands for the padding classes), a image [S][pitch], 16 floats of slack behind each image (fragment
     // reads of the last, partly filled 16-column block run past the row)
-    return (size_t)MAX_S * MAX_C + (size_t)WAVES * 16 * 16 + (size_t)(C + 1 + S) * row_pitch(H) + 32;
+    const int NC = (C + TILE_C - 1) / TILE_C * TILE_C;
+    return (size_t)MAX_S * NC + (size_t)WAVES * 16 * NC + (size_t)(C + 1 + S) * row_pitch(H) + 32;
 }
 __host__ __device__ inline size_t lds_bytes(int H, int C, int S) { return sizeof(float) * lds_floats(H, C, S); }
 __host__ __device__ inline int64_t partial_floats(int H, int C, bool bprev) { return (int64_t)C * H + C + (bprev ? H : 0) + 1; }
@@ -170,18 +175,21 @@ __device__ __forceinline__ void stage_w(const Args &g, int w, float *Wl, int tid
 
 // What the body needs from global memory besides the images: the caller fetches it before its own staging, so that
 // the latency passes there and not between two barriers of the body.
+template <int CT>
 struct Early {
-    float bias;      // b[tid % 16] (0 for the padding classes)
-    int label[2];    // y of samples tid / 16 and 32 + tid / 16 of the chunk (0 beyond it)
+    float bias;          // b[tid % NC] (0 for the padding classes), NC = 16 CT
+    int label[2 * CT];   // y of samples tid / NC + q THREADS / NC of the chunk (0 beyond it)
 };
-__device__ __forceinline__ Early fetch_early(const Args &g, int w, int s0, int ns, int tid)
+template <int CT>
+__device__ __forceinline__ Early<CT> fetch_early(const Args &g, int w, int s0, int ns, int tid)
 {
-    Early e;
-    const int c = tid & 15, s = tid >> 4;
+    constexpr int NC = TILE_C * CT;
+    Early<CT> e;
+    const int c = tid & (NC - 1), s = (tid & (THREADS - 1)) / NC;
     e.bias = c < g.C ? g.params[w * g.p_stride + g.b_off + c] : 0.f;
     const int32_t *__restrict__ y = g.y + (int64_t)w * g.B + s0;
-    e.label[0] = s < ns ? y[s] : 0;
-    e.label[1] = s + 32 < ns ? y[s + 32] : 0;
+#pragma unroll
+    for (int q = 0; q < 2 * CT; ++q) e.label[q] = s + q * (THREADS / NC) < ns ? y[s + q * (THREADS / NC)] : 0;
     return e;
 }
 
@@ -197,10 +205,11 @@ __device__ __forceinline__ Early fetch_early(const Args &g, int w, int s0, int n
 // The parts of a chunk lie on one XCD, whose cache then holds W and the chunk for all of them: with the parts next to each other in the
 // grid, 491-10 on 100 workers x 64 samples took 31.5 us a round against 28.9 without parts and 26.1 so, 785-10 x 32 31.8, 28.5 and 26.1.
 constexpr int RUN = 2 * WAVES * 16;
-template <int LOSS, bool MIX = false>
+template <int LOSS, bool MIX = false, int CT = 1>
 __device__ __forceinline__ void body(const Args &g, float *zl, float *zp, float *Wl, float *al, int S, int w, int chunk,
-                                     int chunks, bool da_to_lds, const Early &early, int part_no = 0, int parts = 1)
+                                     int chunks, bool da_to_lds, const Early<CT> &early, int part_no = 0, int parts = 1)
 {
+    constexpr int NC = TILE_C * CT, LOG = CT == 1 ? 4 : 5;           // classes, padded
     const int H = g.H, C = g.C, HP = row_pitch(H);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);       // on the scalar unit: loops and branches on it are uniform
@@ -216,58 +225,70 @@ __device__ __forceinline__ void body(const Args &g, float *zl, float *zp, float 
     {
         const int MB = S / 16, KS = WAVES / MB;
         const int mb = wave % MB, ks = wave / MB;
-        f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = acc0;
+        f32x4 acc[CT][2];
+#pragma unroll
+        for (int t = 0; t < CT; ++t) acc[t][0] = acc[t][1] = f32x4{0.f, 0.f, 0.f, 0.f};
         if (ks < KS) {
             const int G = HP / 16, per = (G + KS - 1) / KS, g_end = min(G, (ks + 1) * per);
-            const float *ap = al + (16 * mb + l16) * HP + 4 * lq, *wp = Wl + min(l16, C) * HP + 4 * lq;
+            const float *ap = al + (16 * mb + l16) * HP + 4 * lq, *wp[CT];
+#pragma unroll
+            for (int t = 0; t < CT; ++t) wp[t] = Wl + min(16 * t + l16, C) * HP + 4 * lq;
 #pragma unroll 2
             for (int gk = ks * per; gk < g_end; ++gk) {
-                const f32x4 a4 = *(const f32x4 *)(ap + 16 * gk), w4 = *(const f32x4 *)(wp + 16 * gk);
-                acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[0], w4[0], acc0, 0, 0, 0);
-                acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[1], w4[1], acc1, 0, 0, 0);
-                acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[2], w4[2], acc0, 0, 0, 0);
-                acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[3], w4[3], acc1, 0, 0, 0);
+                const f32x4 a4 = *(const f32x4 *)(ap + 16 * gk);
+                f32x4 w4[CT];
+#pragma unroll
+                for (int t = 0; t < CT; ++t) w4[t] = *(const f32x4 *)(wp[t] + 16 * gk);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int t = 0; t < CT; ++t) acc[t][e & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[e], w4[t][e], acc[t][e & 1], 0, 0, 0);
             }
             if (ks == KS - 1) {     // the columns behind the last whole group of 16
-                const float *a1 = al + (16 * mb + l16) * HP + lq, *w1 = Wl + min(l16, C) * HP + lq;
+                const float *a1 = al + (16 * mb + l16) * HP + lq, *w1[CT];
+#pragma unroll
+                for (int t = 0; t < CT; ++t) w1[t] = Wl + min(16 * t + l16, C) * HP + lq;
                 for (int q = 4 * G; q < HP / 4; ++q)
-                    acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[4 * q], w1[4 * q], acc0, 0, 0, 0);
+#pragma unroll
+                    for (int t = 0; t < CT; ++t) acc[t][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[4 * q], w1[t][4 * q], acc[t][0], 0, 0, 0);
             }
         }
 #pragma unroll
-        for (int v = 0; v < 4; ++v) zp[(wave * 16 + 4 * lq + v) * 16 + l16] = acc0[v] + acc1[v];
+        for (int t = 0; t < CT; ++t)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) zp[(wave * 16 + 4 * lq + v) * NC + 16 * t + l16] = acc[t][0][v] + acc[t][1][v];
         __syncthreads();
         // sample s, class c: the slices in order, then the bias
-        for (int e = tid; e < S * 16; e += THREADS) {
-            const int s = e >> 4, c = e & 15;
+        for (int e = tid; e < S * NC; e += THREADS) {
+            const int s = e >> LOG, c = e & (NC - 1);
             float z = 0.f;
-            for (int q = 0; q < KS; ++q) z += zp[((q * MB + (s >> 4)) * 16 + (s & 15)) * 16 + c];
-            zl[e] = c < C ? z + early.bias : 0.f;              // c == tid % 16: the stride of e is a multiple of 16
+            for (int q = 0; q < KS; ++q) z += zp[((q * MB + (s >> 4)) * 16 + (s & 15)) * NC + c];
+            zl[e] = c < C ? z + early.bias : 0.f;              // c == tid % NC: the stride of e is a multiple of NC
         }
     }
     __syncthreads();
 
-    // ---- softmax, loss and dz: 16 lanes per sample, one class each; maxima and sums by butterflies over the 16
+    // ---- softmax, loss and dz: 16 CT lanes per sample, one class each; maxima and sums by butterflies over the
     // lanes, so that every lane holds them.  Rows of samples beyond the batch become zero.  The per-sample losses
     // go to red[0 .. 63] (the partial logits are dead) for the tree at the end.
     float *red = zp;
     {
         const float inv_b = 1.0f / (float)g.B;
 #pragma unroll
-        for (int pass = 0; pass < 2; ++pass) {
-            const int s = (tid >> 4) + 32 * pass, c = tid & 15;
-            float *zs = zl + s * MAX_C;
+        for (int pass = 0; pass < 2 * CT; ++pass) {
+            const int s = (tid >> LOG) + (THREADS >> LOG) * pass, c = tid & (NC - 1);
+            float *zs = zl + s * NC;
             float dzv = 0.f, lossv = 0.f;
-            if (s < ns) {                                       // the same for the 16 lanes of a sample
+            if (s < ns) {                                       // the same for the lanes of a sample
                 const bool real = c < C;
                 const float z = real ? zs[c] : -INFINITY;
                 float m = z;
 #pragma unroll
-                for (int o = 1; o < 16; o <<= 1) m = fmaxf(m, __shfl_xor(m, o, 16));
+                for (int o = 1; o < NC; o <<= 1) m = fmaxf(m, __shfl_xor(m, o, NC));
                 const float ex = real ? expf(z - m) : 0.f;
                 float sum = ex;
 #pragma unroll
-                for (int o = 1; o < 16; o <<= 1) sum += __shfl_xor(sum, o, 16);
+                for (int o = 1; o < NC; o <<= 1) sum += __shfl_xor(sum, o, NC);
                 int label = early.label[pass];
                 if (label < 0 || label >= C) {              // clamped for memory safety, reported by dbw_check
                     *g.err = DBW_ERR_INVALID;
@@ -277,16 +298,16 @@ __device__ __forceinline__ void body(const Args &g, float *zl, float *zp, float 
                 if (LOSS == DBW_LOSS_XENT) {
                     float zl_ = c == label ? z : 0.f;           // z of the label's class, to every lane
 #pragma unroll
-                    for (int o = 1; o < 16; o <<= 1) zl_ += __shfl_xor(zl_, o, 16);
+                    for (int o = 1; o < NC; o <<= 1) zl_ += __shfl_xor(zl_, o, NC);
                     lossv = logf(sum) + m - zl_;
                     dzv = real ? (pr - hot) * inv_b : 0.f;
                 } else {
                     const float er = real ? pr - hot : 0.f;
                     float f = er * er, inner = pr * er;
 #pragma unroll
-                    for (int o = 1; o < 16; o <<= 1) {
-                        f += __shfl_xor(f, o, 16);
-                        inner += __shfl_xor(inner, o, 16);
+                    for (int o = 1; o < NC; o <<= 1) {
+                        f += __shfl_xor(f, o, NC);
+                        inner += __shfl_xor(inner, o, NC);
                     }
                     lossv = f;
                     dzv = 2.f * pr * (er - inner) * inv_b;
@@ -318,7 +339,8 @@ __device__ __forceinline__ void body(const Args &g, float *zl, float *zp, float 
         col[1] = two ? col[0] + 16 * WAVES : col[0];
         // ---- dW[class][col] = sum over samples of dz[sample][class] a[sample][col]: the operands of 16 samples are
         // read before their instructions, two accumulators per block
-        {
+#pragma unroll
+        for (int t = 0; t < CT; ++t) {
             f32x4 acc[2][2];
 #pragma unroll
             for (int p = 0; p < 2; ++p) acc[p][0] = acc[p][1] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -326,7 +348,7 @@ __device__ __forceinline__ void body(const Args &g, float *zl, float *zp, float 
                 float zv[4], av[2][4];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
-                    zv[u] = zl[(k0 + 4 * u + lq) * MAX_C + l16];
+                    zv[u] = zl[(k0 + 4 * u + lq) * NC + 16 * t + l16];
 #pragma unroll
                     for (int p = 0; p < 2; ++p) av[p][u] = al[(k0 + 4 * u + lq) * HP + col[p]];
                 }
@@ -345,34 +367,35 @@ __device__ __forceinline__ void body(const Args &g, float *zl, float *zp, float 
                     if (col[p] < H && (p == 0 || two)) {
 #pragma unroll
                         for (int v = 0; v < 4; ++v)
-                            if (4 * lq + v < C) Wl[(4 * lq + v) * HP + col[p]] = dw[v];
+                            if (16 * t + 4 * lq + v < C) Wl[(16 * t + 4 * lq + v) * HP + col[p]] = dw[v];
                     }
                     continue;
                 }
                 if (MIX && (p == 0 || two)) {
                     uint32_t off[4];
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) off[v] = 4u * (uint32_t)(min(4 * lq + v, C - 1) * H + min(col[p], H - 1));
+                    for (int v = 0; v < 4; ++v) off[v] = 4u * (uint32_t)(min(16 * t + 4 * lq + v, C - 1) * H + min(col[p], H - 1));
                     average::apply<float, 4>(g.avg, nb, w, g.w_off, off, dw);
                 }
                 if (col[p] < H && (p == 0 || two)) {
 #pragma unroll
                     for (int v = 0; v < 4; ++v)
-                        if (4 * lq + v < C) out_w[(4 * lq + v) * H + col[p]] = dw[v];
+                        if (16 * t + 4 * lq + v < C) out_w[(16 * t + 4 * lq + v) * H + col[p]] = dw[v];
                 }
             }
         }
         // ---- da[sample][col] = sum over classes of dz[sample][class] W[class][col], masked; its column sums.
-        // Lane group q carries the classes 4 q + j in instruction j: one 128-bit read of dz per 16 samples.
+        // Lane group q carries the classes 16 t + 4 q + j in instruction (t, j): one 128-bit read of dz per 16 samples.
         if (da || da_to_lds) {
-            float wv[2][4];
+            float wv[2][4 * CT];
 #pragma unroll
             for (int p = 0; p < 2; ++p)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) wv[p][j] = Wl[min(4 * lq + j, C) * HP + col[p]];
+                for (int j = 0; j < 4 * CT; ++j) wv[p][j] = Wl[min(16 * (j / 4) + 4 * lq + j % 4, C) * HP + col[p]];
             float colsum[2] = {0.f, 0.f};
             for (int mb = 0; mb < S / 16; ++mb) {
-                const f32x4 zq = *(const f32x4 *)(zl + (16 * mb + l16) * MAX_C + 4 * lq);
+                const f32x4 zq = *(const f32x4 *)(zl + (16 * mb + l16) * NC + 4 * lq),
+                            zq1 = CT > 1 ? *(const f32x4 *)(zl + (16 * mb + l16) * NC + NC - 16 + 4 * lq) : zq;
                 float keep[2][4];
 #pragma unroll
                 for (int p = 0; p < 2; ++p)
@@ -380,9 +403,10 @@ __device__ __forceinline__ void body(const Args &g, float *zl, float *zp, float 
                     for (int v = 0; v < 4; ++v) keep[p][v] = al[(16 * mb + 4 * lq + v) * HP + col[p]];
                 f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
+                for (int j = 0; j < 4 * CT; ++j)
 #pragma unroll
-                    for (int p = 0; p < 2; ++p) acc[p] = __builtin_amdgcn_mfma_f32_16x16x4f32(zq[j], wv[p][j], acc[p], 0, 0, 0);
+                    for (int p = 0; p < 2; ++p)
+                        acc[p] = __builtin_amdgcn_mfma_f32_16x16x4f32(j < 4 ? zq[j % 4] : zq1[j % 4], wv[p][j], acc[p], 0, 0, 0);
 #pragma unroll
                 for (int p = 0; p < 2; ++p) {
                     if (p == 1 && !two) continue;
@@ -410,7 +434,7 @@ __device__ __forceinline__ void body(const Args &g, float *zl, float *zp, float 
     }
     if (tid < C && part_no == 0) {
         float sum = 0.f;
-        for (int s = 0; s < ns; ++s) sum += zl[s * MAX_C + tid];
+        for (int s = 0; s < ns; ++s) sum += zl[s * NC + tid];
         if (MIX && collect) zp[MAX_S + tid] = sum;             // (behind red)
         else if (MIX) average::store(g.avg, nb, w, g.grads + w * g.p_stride, g.b_off + tid, sum);
         else out_b[tid] = sum;
@@ -482,14 +506,15 @@ __device__ __forceinline__ float4 split_sum(const float *src, int64_t plane, int
 
 // VEC: the input rows start on 16-byte boundaries and H divides by 4 (128-bit staging loads).
 // SPLIT: the input arrives as split-k partial sums (Args::splits).
-template <int LOSS, bool VEC, bool SPLIT = false, bool MIX = false>
+template <int LOSS, bool VEC, bool SPLIT, bool MIX, int CT>
 __global__ __launch_bounds__(THREADS) void kernel(Args g, int chunks, int items, int parts)
 {
     extern __shared__ __attribute__((aligned(16))) float sm[];
     const int H = g.H, C = g.C, S = g.S, HP = row_pitch(H);
-    float *zl = sm;                                  // [64][16]: logits, then dz
-    float *zp = zl + MAX_S * MAX_C;                  // [8][16][16]: partial logits of the wavefronts
-    float *Wl = zp + WAVES * 16 * 16;                // [C + 1][HP]: row C and the columns >= H are zero
+    constexpr int NC = TILE_C * CT;
+    float *zl = sm;                                  // [64][NC]: logits, then dz
+    float *zp = zl + MAX_S * NC;                     // [8][16][NC]: partial logits of the wavefronts
+    float *Wl = zp + WAVES * 16 * NC;                // [C + 1][HP]: row C and the columns >= H are zero
     float *al = Wl + (C + 1) * HP + 16;              // [S][HP], rows >= ns and columns >= H zero
     const int tid = threadIdx.x;
     // Of several parts workgroup i runs on XCD i % 8: eight chunks at a time, all their parts eight workgroups apart.  What is left of more
@@ -511,7 +536,7 @@ __global__ __launch_bounds__(THREADS) void kernel(Args g, int chunks, int items,
     const int s0 = chunk * S, ns = min(S, g.B - s0);
     const float *__restrict__ a = g.a + w * g.a_stride + (int64_t)s0 * g.a_ld;
 
-    const Early early = fetch_early(g, w, s0, ns, tid);
+    const Early<CT> early = fetch_early<CT>(g, w, s0, ns, tid);
     // ---- stage W and this chunk of a; everything the fragments may touch beyond them is zero
     stage_w(g, w, Wl, tid);
     if (SPLIT) {
@@ -573,7 +598,7 @@ __global__ __launch_bounds__(THREADS) void kernel(Args g, int chunks, int items,
     if (tid < 16) al[S * HP + tid] = 0.f;
     __syncthreads();
 
-    body<LOSS, MIX>(g, zl, zp, Wl, al, S, w, chunk, chunks, false, early, part_no, parts);
+    body<LOSS, MIX, CT>(g, zl, zp, Wl, al, S, w, chunk, chunks, false, early, part_no, parts);
 }
 
 // Sum of the per-chunk partials in chunk order -> dW, db, the bias gradient below, the loss.

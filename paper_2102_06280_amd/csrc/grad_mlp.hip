@@ -180,7 +180,11 @@ HeadPlan head_plan(int L, const int32_t *dims, int B, int workers)
     const int H = dims[L - 1], C = dims[L];
     HeadPlan hp{false, 0, 0, 0};
     if (C > fchead::MAX_C || fchead::lds_bytes(H, C, 16) > fchead::LDS_LIMIT) return hp;
-    auto fits = [&](int S) { return fchead::lds_bytes(H, C, S) <= fchead::LDS_LIMIT; };
+    // More than 16 classes in several chunks: two workgroups to a compute unit, or the layer's own kernels are faster (497-18 on 19 workers x
+    // 1 024 samples 66 us, with chunks that fill a unit's LDS 72; 256-25 on 6 x 1 024 39 and 26).
+    const size_t limit = C > fchead::TILE_C && B > 64 ? 80 * 1024 : fchead::LDS_LIMIT;
+    auto fits = [&](int S) { return fchead::lds_bytes(H, C, S) <= limit; };
+    if (!fits(16)) return hp;
     int S;
     const int whole = B <= 16 ? 16 : (B <= 32 ? 32 : 64);
     if (B <= 64 && fits(whole))
@@ -207,7 +211,7 @@ struct ChainPlan {
 ChainPlan chain_plan(int L, const int32_t *dims, int B, int workers, int grad_path)
 {
     ChainPlan cp{false, 0, 0, 0};
-    if (grad_path == DBW_GRAD_LAYERS || L < 2 || L > mlpchain::MAX_L || dims[L] > fchead::MAX_C) return cp;
+    if (grad_path == DBW_GRAD_LAYERS || L < 2 || L > mlpchain::MAX_L || dims[L] > fchead::TILE_C) return cp;
     const int H = dims[1];
     if (H != 128 && H != 256 && H != 512) return cp;
     for (int l = 2; l < L; ++l)
@@ -237,7 +241,8 @@ ChainPlan chain_plan(int L, const int32_t *dims, int B, int workers, int grad_pa
 // How mlpthin::forward_kernel cuts up a product of B x K by K x N: blocks of at most 64 samples, tiles of 32 or 16 outputs, and, where the
 // sums may be left to the reader, parts of the reduction: whatever gives the shortest time, in cycles, for the compute unit with most
 // workgroups.  A wavefront takes every eighth chunk of 16 k, for which the matrix instructions (two wavefronts to a SIMD) and the loads take about
-// as long as said here; a part more is a sum more for the reader.
+// as long as said here; a part more is a sum more for the reader, the head (and none where the head's workgroups would rather share its
+// chunks by runs of columns: 784-420-10 on 20 workers x 19 samples 44 us, in two parts 47).
 struct ThinPlan {
     int RB, CB, blocks, splits, kper;
     int64_t wgs;
@@ -495,7 +500,7 @@ int dbw_fc_forward_backward(dbw_ctx *c, dbw_fc_args &a, hipStream_t s)
         // short batches: operands straight from global memory into matrix-instruction fragments (mlp_thin.h)
         // (more tiles, of longer batches: the GEMM kernel, whose wavefronts share what they fetch; 1023-511-509-10 on 30 x 250
         // 151 us, mlp_thin.h 229, 784-500-10 on 32 x 200 76 and 82, x 128 46 and 46, 300-300-300-10 on 32 x 128 51 and 41)
-        const ThinPlan tp = thin_plan(B, dims[l - 1], dims[l], N, head_can_sum && l == L - 1);
+        const ThinPlan tp = thin_plan(B, dims[l - 1], dims[l], N, head_can_sum && l == L - 1 && dims[l] <= fchead::RUN);
         if (a.grad_path == DBW_GRAD_AUTO && B <= mlpthin::MAX_B && dims[l - 1] >= 4 && (l > 1 || fc32::aligned16(a.in)) && (B <= 64 || tp.wgs * tp.CB <= 2048)) {
             mlpthin::FwdArgs f{};
             f.B = B; f.K = dims[l - 1]; f.N = dims[l]; f.workers = N; f.relu = l < L ? 1 : 0;
@@ -656,16 +661,19 @@ int dbw_fc_forward_backward(dbw_ctx *c, dbw_fc_args &a, hipStream_t s)
             DBW_HIP(hipGetLastError());
             return DBW_OK;
         };
-        int rc;
-        if (a.averaged && head.chunks == 1 && head_splits > 0)
-            rc = mse ? go(fchead::kernel<DBW_LOSS_MSE, true, true, true>) : go(fchead::kernel<DBW_LOSS_XENT, true, true, true>);
-        else if (a.averaged && head.chunks == 1 && vec)
-            rc = mse ? go(fchead::kernel<DBW_LOSS_MSE, true, false, true>) : go(fchead::kernel<DBW_LOSS_XENT, true, false, true>);
-        else if (a.averaged && head.chunks == 1)
-            rc = mse ? go(fchead::kernel<DBW_LOSS_MSE, false, false, true>) : go(fchead::kernel<DBW_LOSS_XENT, false, false, true>);
-        else if (head_splits > 0) rc = mse ? go(fchead::kernel<DBW_LOSS_MSE, true, true>) : go(fchead::kernel<DBW_LOSS_XENT, true, true>);
-        else if (mse) rc = vec ? go(fchead::kernel<DBW_LOSS_MSE, true>) : go(fchead::kernel<DBW_LOSS_MSE, false>);
-        else rc = vec ? go(fchead::kernel<DBW_LOSS_XENT, true>) : go(fchead::kernel<DBW_LOSS_XENT, false>);
+        const bool mix = a.averaged && head.chunks == 1;
+        auto go_split = [&](auto loss, auto ct) -> int {
+            constexpr int LOSS = decltype(loss)::value, CT = decltype(ct)::value;
+            if (mix && head_splits > 0) return go(fchead::kernel<LOSS, true, true, true, CT>);
+            if (mix && vec) return go(fchead::kernel<LOSS, true, false, true, CT>);
+            if (mix) return go(fchead::kernel<LOSS, false, false, true, CT>);
+            if (head_splits > 0) return go(fchead::kernel<LOSS, true, true, false, CT>);
+            return vec ? go(fchead::kernel<LOSS, true, false, false, CT>) : go(fchead::kernel<LOSS, false, false, false, CT>);
+        };
+        auto go_classes = [&](auto loss) -> int {
+            return h.C <= fchead::TILE_C ? go_split(loss, std::integral_constant<int, 1>{}) : go_split(loss, std::integral_constant<int, 2>{});
+        };
+        const int rc = mse ? go_classes(std::integral_constant<int, DBW_LOSS_MSE>{}) : go_classes(std::integral_constant<int, DBW_LOSS_XENT>{});
         if (rc != DBW_OK) return rc;
         }
         if (head.chunks > 1 && !grouped) {          // (the grouped weight-gradient launch adds them otherwise)
@@ -802,17 +810,18 @@ int dbw_fc_prepare()
 {
     static bool done = false;
     if (done) return DBW_OK;
-    const void *kernels[] = {(const void *)fchead::kernel<DBW_LOSS_MSE, true>, (const void *)fchead::kernel<DBW_LOSS_MSE, false>,
-                             (const void *)fchead::kernel<DBW_LOSS_XENT, true>,
-                             (const void *)fchead::kernel<DBW_LOSS_XENT, false>,
-                             (const void *)fchead::kernel<DBW_LOSS_MSE, true, true>,
-                             (const void *)fchead::kernel<DBW_LOSS_XENT, true, true>,
-                             (const void *)fchead::kernel<DBW_LOSS_MSE, true, false, true>,
-                             (const void *)fchead::kernel<DBW_LOSS_MSE, false, false, true>,
-                             (const void *)fchead::kernel<DBW_LOSS_XENT, true, false, true>,
-                             (const void *)fchead::kernel<DBW_LOSS_XENT, false, false, true>,
-                             (const void *)fchead::kernel<DBW_LOSS_MSE, true, true, true>,
-                             (const void *)fchead::kernel<DBW_LOSS_XENT, true, true, true>,
+    const void *kernels[] = {(const void *)fchead::kernel<DBW_LOSS_MSE, true, false, false, 1>, (const void *)fchead::kernel<DBW_LOSS_MSE, false, false, false, 1>,
+                             (const void *)fchead::kernel<DBW_LOSS_MSE, true, true, false, 1>, (const void *)fchead::kernel<DBW_LOSS_MSE, true, false, true, 1>,
+                             (const void *)fchead::kernel<DBW_LOSS_MSE, false, false, true, 1>, (const void *)fchead::kernel<DBW_LOSS_MSE, true, true, true, 1>,
+                             (const void *)fchead::kernel<DBW_LOSS_XENT, true, false, false, 1>, (const void *)fchead::kernel<DBW_LOSS_XENT, false, false, false, 1>,
+                             (const void *)fchead::kernel<DBW_LOSS_XENT, true, true, false, 1>, (const void *)fchead::kernel<DBW_LOSS_XENT, true, false, true, 1>,
+                             (const void *)fchead::kernel<DBW_LOSS_XENT, false, false, true, 1>, (const void *)fchead::kernel<DBW_LOSS_XENT, true, true, true, 1>,
+                             (const void *)fchead::kernel<DBW_LOSS_MSE, true, false, false, 2>, (const void *)fchead::kernel<DBW_LOSS_MSE, false, false, false, 2>,
+                             (const void *)fchead::kernel<DBW_LOSS_MSE, true, true, false, 2>, (const void *)fchead::kernel<DBW_LOSS_MSE, true, false, true, 2>,
+                             (const void *)fchead::kernel<DBW_LOSS_MSE, false, false, true, 2>, (const void *)fchead::kernel<DBW_LOSS_MSE, true, true, true, 2>,
+                             (const void *)fchead::kernel<DBW_LOSS_XENT, true, false, false, 2>, (const void *)fchead::kernel<DBW_LOSS_XENT, false, false, false, 2>,
+                             (const void *)fchead::kernel<DBW_LOSS_XENT, true, true, false, 2>, (const void *)fchead::kernel<DBW_LOSS_XENT, true, false, true, 2>,
+                             (const void *)fchead::kernel<DBW_LOSS_XENT, false, false, true, 2>, (const void *)fchead::kernel<DBW_LOSS_XENT, true, true, true, 2>,
                              (const void *)mlpchain::kernel<1, 1>, (const void *)mlpchain::kernel<1, 2>,
                              (const void *)mlpchain::kernel<1, 4>, (const void *)mlpchain::kernel<2, 1>,
                              (const void *)mlpchain::kernel<2, 2>, (const void *)mlpchain::kernel<2, 4>,

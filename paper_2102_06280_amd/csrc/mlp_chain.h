@@ -61,7 +61,7 @@ __host__ __device__ inline int64_t slot_floats(int K0, int H, int S)
 __host__ __device__ inline size_t lds_bytes(int K0, int H, int C, int S, int L)
 {
     const int slots = L - 1 > 2 ? L - 1 : 2;
-    return sizeof(float) * ((size_t)fchead::MAX_S * fchead::MAX_C + (size_t)WAVES * 256 +
+    return sizeof(float) * ((size_t)fchead::MAX_S * fchead::TILE_C + (size_t)WAVES * 256 +
                             (size_t)(C + 1) * fchead::row_pitch(H) + 16 + (size_t)slots * slot_floats(K0, H, S));
 }
 
@@ -300,7 +300,7 @@ __global__ __launch_bounds__(THREADS) void kernel(Args g)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);       // on the scalar unit
 
     float *zl = sm;
-    float *zp = zl + fchead::MAX_S * fchead::MAX_C;
+    float *zp = zl + fchead::MAX_S * fchead::TILE_C;
     float *Wl = zp + WAVES * 256;
     float *slots = Wl + (C + 1) * HP + 16;
     const int64_t Z = slot_floats(K0, H, S);
@@ -316,7 +316,7 @@ __global__ __launch_bounds__(THREADS) void kernel(Args g)
     const int n0 = wave * 16 * CB;
     BRegs<CBI> b0;
     if (K0 >= 64) load_fwd<CBI>(b0, pw + pick(g.w_off, 1), K0, 0, n0, lane);
-    const fchead::Early early = fchead::fetch_early(g.head, w, s0, ns, tid);
+    const fchead::Early<1> early = fchead::fetch_early<1>(g.head, w, s0, ns, tid);
     fchead::stage_w(g.head, w, Wl, tid);
     {   // the chunk of the batch, rows beyond it zero
         const float *__restrict__ x = g.x + w * g.x_stride + (int64_t)s0 * g.x_ld;
