@@ -8,7 +8,7 @@ from test_gpu_grad_mlp import B, check_gradients  # noqa: F401  (B: the fixture)
 
 pytestmark = pytest.mark.gpu
 
-GRADIENTS = [([784, 17], 32, 2, "xent"), ([301, 32], 5, 2, "mse"), ([20, 516, 31], 70, 3, "xent"), ([33, 29, 30], 17, 3, "mse"), ([64, 48, 25], 300, 3, "xent"),
+GRADIENTS = [([784, 17], 32, 2, "xent"), ([301, 32], 5, 2, "mse"), ([20, 260, 31], 70, 3, "xent"), ([20, 516, 31], 64, 3, "mse"), ([33, 29, 30], 17, 3, "mse"), ([64, 48, 25], 300, 3, "xent"),
              ([1605, 36, 20], 30, 3, "mse"), ([40, 24, 33], 40, 3, "xent")]
 AVERAGE = [([784, 26], 32, "xent", 8, 64), ([101, 17], 64, "mse", 9, 1), ([256, 32], 600, "xent", 6, 64), ([300, 92, 20], 32, "mse", 17, 64)]
 
