@@ -646,18 +646,24 @@ __global__ __launch_bounds__(THREADS, 2) void first_kernel(FwdArgs a, FirstPlan 
 // ---- weight gradient: dW[co][c][kh][kw] = sum over samples and pixels of dz[co][y][x] in[c][y + kh - pad][x + kw - pad],
 // with dz given as pooled gradients and window codes.
 //
-// The reduction runs over the pixels of a row, 16 at a time (rows padded with zeros to a multiple of 16), so a lane's
-// fragments are eight consecutive pixels.  Of the image these would start at any pixel, depending on kw, and LDS
-// reads want aligned ones: the 32 columns of a fragment are therefore pairs (c, kh), a lane reads the twelve pixels from x
-// on once, and the KS fragments of its kw are shifts of those inside the registers (none for an even kw, four
+// The reduction runs over the pixels of a pair of rows, 16 of each at a time (rows padded with zeros to a multiple of 16).  The deltas are
+// pooled, so that of two neighbouring pixels at most one is not zero: v_smfmac_f32_32x32x32_bf16, whose first operand has two values
+// for every four terms and four bits that say which, multiplies both rows' pixels in the time of one's.  Of the image a lane's
+// fragment is sixteen consecutive pixels, which would start at any one, depending on kw, and LDS
+// reads want aligned ones: the 32 columns of a fragment are therefore pairs (c, kh), a lane reads the twenty pixels from x
+// on once, and the KS fragments of its kw are shifts of those inside the registers (none for an even kw, eight
 // v_alignbit for an odd one).  A wave owns 32 output channels x 32 pairs x all kw; image and deltas are split when they
-// are copied into LDS.  Where there are few such blocks, several waves share one, take turns with the 16-pixel steps
+// are copied into LDS.  Where there are few such blocks, several waves share one, take turns with the steps
 // and add their sums through LDS in wave order.  Every workgroup writes a partial result:
 // part[worker][split][co][c][kh][kw], summed in split order by a separate pass.
 //
-// 64 workers x 32 samples, 32 -> 64 channels, 16 x 16 pixels: 250 us (an fp32 kernel 427); ten blocks on the four
-// SIMDs of a compute unit are three rounds of 2.5, and LDS holds one workgroup.  16 workers x 50 samples, 16 -> 32 channels on
-// 14 x 14: 46 us (implicit fp32 GEMM: 231).
+// 64 workers x 32 samples, 32 -> 64 channels, 16 x 16 pixels: 170 us, with a dense instruction of 16 pixels 246, an fp32 kernel 427; 145 of
+// them without the copies into LDS, 80 the copies alone.  Ten blocks on the four SIMDs of a compute unit are three rounds of 2.5, and
+// LDS holds one workgroup.  16 workers x 50 samples, 16 -> 32 channels on 14 x 14: 34 us, 45 (implicit fp32 GEMM: 231).  Error of
+// dW against 64 bits, dense / sparse: 2.34e-7 / 2.31e-7 for the first, 1.52e-7 / 1.46e-7 for the second, 1.62e-7 / 1.43e-7 for 16 -> 64 on 12 x 12.
+//
+// What a sparse instruction leaves out is not multiplied, so where a pixel, and not only where a sum, is not finite the workgroup goes
+// through its products again with every delta written out (two dense steps of 16 pixels; LDS is laid out for these).
 struct WgradPlan {
     int mb, nb, units;          // 32-row and 32-column blocks
     int kw, waves, groups;      // waves that share a block, waves of a workgroup, workgroups along the blocks
@@ -768,33 +774,39 @@ __global__ __launch_bounds__(64 * WGRAD_MAX_WAVES, PER_SIMD) void wgrad_kernel(W
     };
     zero();
 
-    // the partial products of the whole reduction, all of them or those of one kind.  MASK: pixels that meet only the padding of the delta
-    // rows are left out (otherwise they meet zeros there, which is the same for finite values)
-    auto products = [&](auto small, auto large, auto mask) {
-        constexpr bool SMALL = decltype(small)::value, LARGE = decltype(large)::value, MASK = decltype(mask)::value;
+    // The image of a sample, split, into LDS; whether this thread has seen a pixel that is not finite.
+    auto copy_image = [&](int b) {
+        const int per = IP / 8;
+        float t = 0.f;
+        for (int e = tid; e < Cin * H * per; e += threads) {
+            const int m = e % per, y = e / per % H, c = e / per / H;
+            const float *src = inw + (((int64_t)b * Cin + c) * H + y) * W;
+            float v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int x = 8 * m + j - pad;
+                const float f = src[min(max(x, 0), W - 1)];
+                v[j] = (unsigned)x < (unsigned)W ? f : 0.f;
+            }
+#pragma unroll
+            for (int j = 0; j < 8; ++j) t = fmaf(v[j], 0.f, t);
+            const planes p = split_bf16::split8_nearest(v);
+            u32x4 *d = img + (c * HP + y + pad) * per + m;
+            d[0] = p.h;
+            d[iplane] = p.m;
+            d[2 * iplane] = p.l;
+        }
+        return t != t;
+    };
+    // the partial products of one kind of the whole reduction, every delta written out.  Pixels that meet only the padding of the delta
+    // rows are left out
+    auto products = [&](auto small, auto large) {
+        constexpr bool SMALL = decltype(small)::value, LARGE = decltype(large)::value;
         for (int b = b0; b < b1; ++b)
             for (int r0 = 0; r0 < H; r0 += a.p.rows) {
                 const int rows = min(a.p.rows, H - r0);
                 __syncthreads();                           // the previous tile has been used
-                if (r0 == 0) {
-                    const int per = IP / 8;
-                    for (int e = tid; e < Cin * H * per; e += threads) {
-                        const int m = e % per, y = e / per % H, c = e / per / H;
-                        const float *src = inw + (((int64_t)b * Cin + c) * H + y) * W;
-                        float v[8];
-#pragma unroll
-                        for (int j = 0; j < 8; ++j) {
-                            const int x = 8 * m + j - pad;
-                            const float f = src[min(max(x, 0), W - 1)];
-                            v[j] = (unsigned)x < (unsigned)W ? f : 0.f;
-                        }
-                        const planes p = split_bf16::split8_nearest(v);
-                        u32x4 *d = img + (c * HP + y + pad) * per + m;
-                        d[0] = p.h;
-                        d[iplane] = p.m;
-                        d[2 * iplane] = p.l;
-                    }
-                }
+                if (r0 == 0) copy_image(b);
                 const int per = RE / 8;
                 for (int e = tid; e < Cout * (rows / 2) * per; e += threads) {       // four windows: eight pixels of two rows
                     const int m = e % per, yh = e / per % (rows / 2), co = e / per / (rows / 2);
@@ -844,7 +856,7 @@ __global__ __launch_bounds__(64 * WGRAD_MAX_WAVES, PER_SIMD) void wgrad_kernel(W
 #pragma unroll
                             for (int i = 0; i < 4; ++i) {
                                 fb[k][i] = k % 2 == 0 ? d[k / 2 + i] : __builtin_amdgcn_alignbit(d[k / 2 + i + 1], d[k / 2 + i], 16);
-                                if (MASK) fb[k][i] = 8 * x8 + 8 * (lane >> 5) + 2 * i < W ? fb[k][i] : 0u;
+                                fb[k][i] = 8 * x8 + 8 * (lane >> 5) + 2 * i < W ? fb[k][i] : 0u;
                             }
                     };
                     auto step = [&](const u32x4 &x) {
@@ -868,23 +880,102 @@ __global__ __launch_bounds__(64 * WGRAD_MAX_WAVES, PER_SIMD) void wgrad_kernel(W
                 }
             }
     };
-    products(std::true_type{}, std::true_type{}, std::false_type{});
+    // The deltas are pooled: of the two pixels of a window in an image row at most one is not zero.  So the first time through a sparse
+    // instruction multiplies 32 pixels, sixteen of a pair of rows, in the time of sixteen.  LDS holds of four windows, for each plane, the values that lie
+    // in the upper row and those in the lower one (zero where the other row has it), and for all planes which pixel of the window
+    // they stand for: [plane][channel][row pair][four windows][8 values], [channel][row pair][four windows] of 16 bits.
+    const int per = RE / 8, dgroups = a.p.rows / 2 * per + 1, splane = 32 * a.p.mb * dgroups;
+    uint16_t *places = (uint16_t *)(dz + 3 * splane);
+    const int half = lane >> 5;
+    const int arow = (32 * mb + (lane & 31)) * dgroups + half, brow = (((nc / KS) * HP + nc % KS + half) * IP) / 8;
+    bool bad = false;                                  // a pixel is not finite (those that meet no delta are not multiplied)
+    for (int b = b0; b < b1; ++b)
+        for (int r0 = 0; r0 < H; r0 += a.p.rows) {
+            const int rows = min(a.p.rows, H - r0);
+            __syncthreads();                           // the previous tile has been used
+            if (r0 == 0) bad |= copy_image(b);
+            for (int e = tid; e < Cout * (rows / 2) * per; e += threads) {
+                const int m = e % per, yh = e / per % (rows / 2), co = e / per / (rows / 2);
+                const int64_t o = ((int64_t)b * Cout + co) * (H * W / 4) + (r0 / 2 + yh) * (W >> 1);
+                float g[4];
+                int cd[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int xw = 4 * m + j;
+                    const bool ok = xw < W / 2;
+                    g[j] = dpw[o + (ok ? xw : 0)];
+                    const int code = cdw[o + (ok ? xw : 0)];
+                    cd[j] = ok ? code : 4;
+                }
+                uint32_t h[2], mi[2], lo[2], up[2], down[2], place = 0;
+                split_bf16::split_nearest<4>(g, h, mi, lo);
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const int c0 = cd[2 * q], c1 = cd[2 * q + 1];
+                    up[q] = (c0 < 2 ? 0xffffu : 0u) | (c1 < 2 ? 0xffff0000u : 0u);
+                    down[q] = (c0 >> 1 == 1 ? 0xffffu : 0u) | (c1 >> 1 == 1 ? 0xffff0000u : 0u);
+                    place |= (uint32_t)((c0 & 1) | (2 | (c1 & 1)) << 2) << (4 * q);
+                }
+                const int at = co * dgroups + yh * per + m;
+                dz[at] = u32x4{h[0] & up[0], h[1] & up[1], h[0] & down[0], h[1] & down[1]};
+                dz[at + splane] = u32x4{mi[0] & up[0], mi[1] & up[1], mi[0] & down[0], mi[1] & down[1]};
+                dz[at + 2 * splane] = u32x4{lo[0] & up[0], lo[1] & up[1], lo[0] & down[0], lo[1] & down[1]};
+                places[at] = (uint16_t)(place | place << 8);
+            }
+            __syncthreads();
+            if (idle) continue;
+            const int steps = rows / 2 * segs;
+            for (int st = kwave; st < steps; st += a.p.kw) {
+                const int yh = st / segs, sg = st % segs, at = arow + yh * per + 2 * sg;
+                planes fa;
+                fa.h = dz[at];
+                fa.m = dz[at + splane];
+                fa.l = dz[at + 2 * splane];
+                const int place = places[at] | 0x8888;   // (channels beyond the last: two different places as well)
+                const u32x4 *bp = img + brow + (r0 + 2 * yh) * (IP / 8) + 2 * sg;
+                // fragment kw of one plane of the image: elements kw .. kw + 15 of the twenty read
+                split_bf16::u32x8 fb[KS];
+                auto read = [&](int plane) {
+                    const u32x4 q0 = bp[plane * iplane], q1 = bp[plane * iplane + 1];
+                    const u32x2 r = *(const u32x2 *)&bp[plane * iplane + 2];
+                    const uint32_t d[10] = {q0[0], q0[1], q0[2], q0[3], q1[0], q1[1], q1[2], q1[3], r[0], r[1]};
+#pragma unroll
+                    for (int k = 0; k < KS; ++k)
+#pragma unroll
+                        for (int i = 0; i < 8; ++i) fb[k][i] = k % 2 == 0 ? d[k / 2 + i] : __builtin_amdgcn_alignbit(d[k / 2 + i + 1], d[k / 2 + i], 16);
+                };
+                auto step = [&](const u32x4 &x) {
+#pragma unroll
+                    for (int k = 0; k < KS; ++k) split_bf16::mma_sparse(x, fb[k], place, acc[k]);
+                };
+                read(2);
+                step(fa.h);
+                read(1);
+                step(fa.m);
+                step(fa.h);
+                read(0);
+                step(fa.l);
+                step(fa.m);
+                step(fa.h);
+            }
+        }
     // ---- some sum of the workgroup is not finite: again, in the order that tells infinities from NaN (see split_bf16.h).  The
     // look at the sums and the vote take 2 us of 38 (489 samples of 16 x 16, 12 -> 24 channels); looking at the middle filter column
     // alone would take 1, but miss partial products beyond the range of fp32 whose sum is an infinity
-    bool bad = false;
 #pragma unroll
     for (int k = 0; k < KS; ++k) bad |= n < Cin * KS && split_bf16::any_not_finite(acc[k]);
-    uint8_t *votes = (uint8_t *)(dz + DP / 8 - 1);     // behind the first delta row: 16 bytes that nobody else uses, zero so far
+    uint8_t *votes = (uint8_t *)(dz + dgroups - 1);    // behind the first channel's deltas: 16 bytes that nobody else uses, zero so far
     if (__any(bad) && lane == 0) votes[wave] = 1;
     __syncthreads();
     const u32x4 vote = *(const u32x4 *)votes;
     if (vote[0] | vote[1] | vote[2]) {                 // (12 waves at most)
         zero();
-        products(std::true_type{}, std::false_type{}, std::true_type{});
+        __syncthreads();                               // the votes have been read
+        for (int e = tid; e < 3 * dplane; e += threads) dz[e] = u32x4{0u, 0u, 0u, 0u};
+        products(std::true_type{}, std::false_type{});
 #pragma unroll
         for (int k = 0; k < KS; ++k) split_bf16::drop_not_finite(acc[k]);
-        products(std::false_type{}, std::true_type{}, std::true_type{});
+        products(std::false_type{}, std::true_type{});
     }
     // ---- the waves that share a block: their sums through LDS, added to the first one's in wave order
     float *sums = (float *)sm + (wave % upg) * 1024 * KS + lane;

@@ -173,6 +173,18 @@ __device__ __forceinline__ void mma(const u32x4 &a, const u32x4 &b, f32x4 &acc)
     acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag(a), frag(b), acc, 0, 0, 0);
 }
 
+// One sparse matrix instruction: 32 x 32 outputs over 32 terms, of which every four in a row have at most two nonzero values of a, in the
+// time of mma's 16.  Lane l of b holds column l % 32 and the terms 16 (l / 32) .. + 15.  Lane l of a holds row l % 32 and, in pairs, the values
+// of the terms 8 (l / 32) + 0 .. 3, + 4 .. 7, 16 + 8 (l / 32) + 0 .. 3 and + 4 .. 7; four bits of `index` for each pair, from bit 0 on, say
+// which two of its four terms they are, the first one's place in the lower two bits (layout as probed on the card: every place of
+// every pair, against b = the terms' numbers).
+typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x16 __attribute__((ext_vector_type(16)));
+__device__ __forceinline__ void mma_sparse(const u32x4 &a, const u32x8 &b, int index, f32x16 &acc)
+{
+    acc = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(frag(a), __builtin_bit_cast(bf16x16, b), acc, index, 0, 0);
+}
+
 // Six partial products (or the five small ones, or the large one) for a block of A x B accumulators, one kind after the other,
 // the large one last: consecutive instructions are independent.
 template <bool SMALL, bool LARGE, int A, int B, class Acc>
