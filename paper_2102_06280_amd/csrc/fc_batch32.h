@@ -117,72 +117,86 @@ __global__ __launch_bounds__(THREADS) void forward_kernel(
 // row r sits at position p ^ (r % 8) of the row, which spreads both access patterns over all
 // banks.
 // Compared with forward_kernel the inputs are fetched once instead of once per 32 output units.
-// Needs N == 128 NF, K % 256 == 0.  grid = (K / 256, workers).
+// A workgroup takes `subs` such slices one after the other and adds their sums: fewer partial sums to write and for the next
+// kernel to read.  64 workers, 4096 -> 512: two 104 us and the head behind it 27, one 112 and 37 (1024 workgroups, for whom the compute
+// units have 768 places); four 143, with four wavefronts to a compute unit.
+// Needs N == 128 NF, K % (256 subs) == 0.  grid = (K / (256 subs), workers).
 constexpr int KSLICE = 256;
 template <int NF>
 __global__ __launch_bounds__(THREADS) void forward_ksplit_kernel(
-    int K, const float *__restrict__ x, int64_t ldx, int64_t x_stride, const float *__restrict__ W, int64_t w_stride,
+    int K, int subs, const float *__restrict__ x, int64_t ldx, int64_t x_stride, const float *__restrict__ W, int64_t w_stride,
     float *__restrict__ part, int64_t part_stride)
 {
     constexpr int LDX = KSLICE + 4, N = 128 * NF, WINDOWS = KSLICE / 32, STEPS = WINDOWS * NF;
     __shared__ __attribute__((aligned(16))) float xs[32 * LDX];
     __shared__ __attribute__((aligned(16))) float turn[4][32 * 32];
-    const int slice = blockIdx.x, w = blockIdx.y, k0 = slice * KSLICE;
+    const int slice = blockIdx.x, w = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63;
     const int q = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 31, ks = lane >> 5;
-    for (int e = tid; e < 32 * (KSLICE / 4); e += THREADS) {
-        const int m = e / (KSLICE / 4), c4 = e % (KSLICE / 4);
-        *(f32x4 *)&xs[m * LDX + 4 * c4] = *(const f32x4 *)(x + w * x_stride + (int64_t)m * ldx + k0 + 4 * c4);
-    }
     const int lrow = lane >> 3, piece = lane & 7;
-    const float *wl = W + w * w_stride + (int64_t)(q * (N / 4) + lrow) * K + k0 + 4 * piece;
-    auto request = [&](int step, f32x4 (&b)[4]) {
-        const int win = step / NF, f = step % NF;
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            b[i] = __builtin_nontemporal_load((const f32x4 *)(wl + (int64_t)(32 * f + 8 * i) * K + 32 * win));
-    };
     float *mine = turn[q];
     const int put = lrow * 32 + 4 * (piece ^ lrow);                  // + 256 i: row 8 i + lrow
     int get[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) get[j] = r * 32 + 4 * ((4 * ks + j) ^ (r & 7));
-    f32x16 acc[NF];
+    f32x16 sum[NF];
 #pragma unroll
     for (int f = 0; f < NF; ++f)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[f][v] = 0.f;
+        for (int v = 0; v < 16; ++v) sum[f][v] = 0.f;
     constexpr int AHEAD = 2;                                          // steps requested before they are used
-    f32x4 st[AHEAD + 1][4], wb[4], xa[4];
+    for (int sub = 0; sub < subs; ++sub) {
+        const int k0 = (slice * subs + sub) * KSLICE;
+        if (sub > 0) __syncthreads();                                 // the inputs of the slice before have been used
+        for (int e = tid; e < 32 * (KSLICE / 4); e += THREADS) {
+            const int m = e / (KSLICE / 4), c4 = e % (KSLICE / 4);
+            *(f32x4 *)&xs[m * LDX + 4 * c4] = *(const f32x4 *)(x + w * x_stride + (int64_t)m * ldx + k0 + 4 * c4);
+        }
+        const float *wl = W + w * w_stride + (int64_t)(q * (N / 4) + lrow) * K + k0 + 4 * piece;
+        auto request = [&](int step, f32x4 (&b)[4]) {
+            const int win = step / NF, f = step % NF;
 #pragma unroll
-    for (int a = 0; a < AHEAD; ++a)
-        if (a < STEPS) request(a, st[a]);
-    __syncthreads();
+            for (int i = 0; i < 4; ++i)
+                b[i] = __builtin_nontemporal_load((const f32x4 *)(wl + (int64_t)(32 * f + 8 * i) * K + 32 * win));
+        };
+        f32x16 acc[NF];
 #pragma unroll
-    for (int step = 0; step < STEPS; ++step) {
-        const int win = step / NF, f = step % NF;
-        if (step + AHEAD < STEPS) request(step + AHEAD, st[(step + AHEAD) % (AHEAD + 1)]);
+        for (int f = 0; f < NF; ++f)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) *(f32x4 *)&mine[put + 256 * i] = st[step % (AHEAD + 1)][i];
+            for (int v = 0; v < 16; ++v) acc[f][v] = 0.f;
+        f32x4 st[AHEAD + 1][4], wb[4], xa[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) wb[j] = *(const f32x4 *)&mine[get[j]];
-        if (f == 0) {
+        for (int a = 0; a < AHEAD; ++a)
+            if (a < STEPS) request(a, st[a]);
+        __syncthreads();
 #pragma unroll
-            for (int j = 0; j < 4; ++j) xa[j] = *(const f32x4 *)&xs[r * LDX + 32 * win + 16 * ks + 4 * j];
+        for (int step = 0; step < STEPS; ++step) {
+            const int win = step / NF, f = step % NF;
+            if (step + AHEAD < STEPS) request(step + AHEAD, st[(step + AHEAD) % (AHEAD + 1)]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) *(f32x4 *)&mine[put + 256 * i] = st[step % (AHEAD + 1)][i];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) wb[j] = *(const f32x4 *)&mine[get[j]];
+            if (f == 0) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) xa[j] = *(const f32x4 *)&xs[r * LDX + 32 * win + 16 * ks + 4 * j];
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    acc[f] = __builtin_amdgcn_mfma_f32_32x32x2f32(xa[j][e], wb[j][e], acc[f], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                acc[f] = __builtin_amdgcn_mfma_f32_32x32x2f32(xa[j][e], wb[j][e], acc[f], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
+        for (int f = 0; f < NF; ++f) sum[f] += acc[f];
     }
     float *pb = part + w * part_stride + (int64_t)slice * 32 * N + q * (N / 4) + r;
 #pragma unroll
     for (int f = 0; f < NF; ++f)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) pb[(int64_t)d_row(v, lane) * N + 32 * f] = acc[f][v];
+        for (int v = 0; v < 16; ++v) pb[(int64_t)d_row(v, lane) * N + 32 * f] = sum[f][v];
 }
 
 // ---------------------------------------------------------------------------------------------

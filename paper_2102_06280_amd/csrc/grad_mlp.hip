@@ -459,7 +459,9 @@ int dbw_fc_forward_backward(dbw_ctx *c, dbw_fc_args &a, hipStream_t s)
         Bm = {params + w_off[l], dims[l - 1], c->ld};
         if (batch32_layer(B, dims[l - 1], dims[l], c->ld, w_off[l], params, grads) && A.ld % 4 == 0 &&
             A.stride % 4 == 0 && fc32::aligned16(A.p) && wstride % 4 == 0 && a_off[l] % 4 == 0 && fc32::aligned16(act)) {
-            const int slices = dims[l - 1] / fc32::KSLICE, nf = dims[l] / 128;
+            int subs = 1;                                // slices of a workgroup: while two workgroups to a compute unit are left
+            while (subs < 4 && dims[l - 1] % (2 * subs * fc32::KSLICE) == 0 && (int64_t)dims[l - 1] / (2 * subs * fc32::KSLICE) * N >= 512) subs *= 2;
+            const int slices = dims[l - 1] / (subs * fc32::KSLICE), nf = dims[l] / 128;
             if (dims[l] % 128 == 0 && nf <= 4 && slices <= MAX_SPLITS) {      // split along k, inputs read once
                 float *part = act + 2 * per;
                 {
@@ -467,7 +469,7 @@ int dbw_fc_forward_backward(dbw_ctx *c, dbw_fc_args &a, hipStream_t s)
                     const dim3 grid(slices, N), block(fc32::THREADS);
                     const float *Wl = params + w_off[l];
                     auto go = [&](auto kern) {
-                        hipLaunchKernelGGL(kern, grid, block, 0, s, dims[l - 1], A.p, A.ld, A.stride, Wl, c->ld, part,
+                        hipLaunchKernelGGL(kern, grid, block, 0, s, dims[l - 1], subs, A.p, A.ld, A.stride, Wl, c->ld, part,
                                            wstride);
                     };
                     switch (nf) {

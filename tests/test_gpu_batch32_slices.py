@@ -1,0 +1,11 @@
+"""Forward products of wide layers on 32 samples, cut along k: workgroups that take two and four slices one after the other, against the oracle."""
+import pytest
+
+from test_gpu_grad_mlp import B, check_gradients  # noqa: F401  (B: the fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dims,n", [([4096, 128, 10], 64), ([8192, 128, 3], 64)], ids=["two", "four"])
+def test_slices_of_a_workgroup(B, orc, dims, n):  # noqa: F811
+    check_gradients(B, orc, dims, 32, n, "xent", expect={"fc32_forward", "fc32_wgrad", "fc_head_kernel"})
