@@ -185,12 +185,19 @@ HeadPlan head_plan(int L, const int32_t *dims, int B, int workers)
     const size_t limit = C > fchead::TILE_C && B > 64 ? 80 * 1024 : fchead::LDS_LIMIT;
     auto fits = [&](int S) { return fchead::lds_bytes(H, C, S) <= limit; };
     if (!fits(16)) return hp;
+    // Longer batches: W is staged, and a partial sum of dW written and read, once per chunk, so as many samples to a chunk as leave work for the
+    // chip.  Rounds, chunks of 16 / 32: 784-10 on 6 workers x 1 024 (192 chunks of 32) 31.2 / 24.2 us, on 30 x 150 30.7 / 23.5, 256-10 on 6 x
+    // 1 024 19.2 / 17.0, 4 x 1 024 (128) 17.1 / 17.1, 784-10 on 20 x 100 (80) 19.6 / 20.2, behind other
+    // layers 133-111-42-10 on 16 x 256 (128) 65.5 / 67.5, 300-100-10 on 40 x 100 (160) 36.9 / 36.0; of 32 / 64, two workgroups to a compute unit:
+    // 128-10 on 64 x 1 024 39.7 / 31.7, 200-10 on 60 x 300 23.1 / 21.8.
     int S;
     const int whole = B <= 16 ? 16 : (B <= 32 ? 32 : 64);
     if (B <= 64 && fits(whole))
         S = whole;                                   // one chunk per worker: no partial sums at all
-    else                                             // 32 samples per workgroup when that still fills the chip, else 16
-        S = (fits(32) && (int64_t)((B + 31) / 32) * workers >= 256) ? 32 : 16;
+    else if (fchead::lds_bytes(H, C, 64) <= 80 * 1024 && (int64_t)((B + 63) / 64) * workers >= 256)
+        S = 64;
+    else
+        S = fits(32) && (int64_t)((B + 31) / 32) * workers >= (L == 1 ? 128 : 160) ? 32 : 16;
     const int chunks = (B + S - 1) / S;
     if (chunks > fchead::MAX_CHUNKS) return hp;
     hp.use = true;
