@@ -378,8 +378,8 @@ int launch_grouped_wgrad(dbw_ctx *c, const dbw_fc_args &a, const WgradPlan &wp, 
         if (thin && B <= 16) go(mlpthin::wgrad_kernel<4, false>);
         else if (thin && B <= 32) go(mlpthin::wgrad_kernel<8, false>);
         else if (thin && B <= 64) go(mlpthin::wgrad_kernel<16, false>);
-        else if (thin && (B + 51) / 52 * 13 < (B + 63) / 64 * 16) go(mlpthin::wgrad_kernel<13, true>);    // steps of 52 samples: less padding
-        else if (thin) go(mlpthin::wgrad_kernel<16, true>);
+        else if (thin && (B + 35) / 36 * 9 <= (B + 31) / 32 * 8) go(mlpthin::wgrad_kernel<9, true>);      // the less padding
+        else if (thin) go(mlpthin::wgrad_kernel<8, true>);
         else if (tn == 64) go(mlpwgrad::kernel<4>);
         else go(mlpwgrad::kernel<2>);
         DBW_HIP(hipGetLastError());
@@ -516,7 +516,7 @@ int dbw_fc_forward_backward(dbw_ctx *c, dbw_fc_args &a, hipStream_t s)
             f.splits = tp.splits; f.kper = tp.kper;
             f.a = A.p; f.a_ld = A.ld; f.a_stride = A.stride;
             f.params = params; f.p_stride = c->ld; f.w_off = w_off[l]; f.b_off = b_off[l];
-            f.out = tp.splits > 1 ? act + 2 * per : act + a_off[l]; f.out_stride = wstride;
+            f.out = tp.splits > 1 ? act + 2 * per : act + a_off[l]; f.out_ld = dims[l]; f.out_stride = wstride;
             dbw_timer tm(c, "mlp_thin_forward", s);
             DBW_HIP(launch_thin<false>(tp, f, s));
             if (tp.splits > 1) head_splits = tp.splits;
@@ -781,14 +781,16 @@ int dbw_fc_forward_backward(dbw_ctx *c, dbw_fc_args &a, hipStream_t s)
                                act + dz_off[1], (int64_t)dims[1], wstride, params + w_off[1], c->ld,
                                (const float *)nullptr, (int64_t)0, (int64_t)0, a.din, a.din_ld, a.din_stride);
             DBW_HIP(hipGetLastError());
-        } else if (dgrad_gemm && l > 1 && grouped && thin && dims[l] >= 4 && (B <= 64 || dgrad_thin.wgs * dgrad_thin.CB <= 2048)) {
+        } else if (dgrad_gemm && grouped && thin && dims[l] >= 4 && !(l == 1 && bgemm::aligned(dg.A, dg.M, dg.K) && bgemm::aligned(dg.B, dg.N, dg.K)) && (B <= 64 || dgrad_thin.wgs * dgrad_thin.CB <= 2048)) {
+            // (The gradient of a stack's own input, wide and with a short reduction, stays on the GEMM kernel where rows are aligned: 16 workers x
+            // 50 samples, 128 -> 1568 12.4 us, here 14.8.  Elsewhere that would be the split form: rounds of 290 -> 600 on 5 x 32 139, 127.)
             mlpthin::FwdArgs f{};
             f.B = B; f.K = dims[l]; f.N = dims[l - 1]; f.workers = N;
             f.splits = 1; f.kper = dgrad_thin.kper;
             f.a = act + dz_off[l]; f.a_ld = dims[l]; f.a_stride = wstride;
             f.params = params; f.p_stride = c->ld; f.w_off = w_off[l];
-            f.out = act + dz_off[l - 1]; f.out_stride = wstride;
-            f.mask = act + a_off[l - 1];
+            f.out = l > 1 ? act + dz_off[l - 1] : a.din; f.out_ld = l > 1 ? dims[l - 1] : a.din_ld; f.out_stride = l > 1 ? wstride : a.din_stride;
+            f.mask = l > 1 ? act + a_off[l - 1] : nullptr;
             dbw_timer tm(c, "mlp_thin_dgrad", s);
             DBW_HIP(launch_thin<true>(dgrad_thin, f, s));
         } else if (dgrad_gemm) {

@@ -1,7 +1,7 @@
 // Fully connected layers on short batches (up to 255 samples per worker), all workers in one launch
 // (Section 2.1, stochastic gradient of the local loss):
 //   forward_kernel         a_l[s][n] = act(sum_k a_{l-1}[s][k] W_l[n][k] + b_l[n])
-//   forward_kernel (BACK)  dz_{l-1}[s][n] = sum_k dz_l[s][k] W_l[k][n] where a_{l-1}[s][n] > 0
+//   forward_kernel (BACK)  dz_{l-1}[s][n] = sum_k dz_l[s][k] W_l[k][n] where a_{l-1}[s][n] > 0 (the gradient of the input: everywhere)
 //   wgrad_kernel           dW_l[m][n] = sum_s dz_l[s][m] a_{l-1}[s][n],   db_l[m] = sum_s dz_l[s][m]
 // With so few samples the tiled GEMM kernel (bgemm.h) spends its time on LDS round trips and
 // barriers: a 64 x 784 x 200 product per worker reached a fifth of the matrix rate.  Here every
@@ -22,7 +22,7 @@
 // wgrad: both operands are contiguous along their output index; the layout trick of mlp_wgrad.h
 // (a lane's four consecutive outputs go to four different tiles) applies, but with at most 16 groups
 // of four samples a tile is too little work to share: every wavefront owns a 32 x 64 tile, fetches
-// all its samples at once (of more than 64: 52 or 64 at a time), multiplies and stores, with no LDS and no barrier.
+// all its samples at once (of more than 64: 36 or 32 at a time, summed apart), multiplies and stores, with no LDS and no barrier.
 //
 // Widths or rows that are no multiple of four floats, and batches of 65 to 255 samples, took bgemm.h (and several launches for what
 // is one here); rounds, before and now: 617-301-75-10 on 20 workers x 101 samples 96 / 75 us, 783-200-10 on 32 x 50 69 / 47,
@@ -50,9 +50,9 @@ struct FwdArgs {
     int64_t a_ld, a_stride;
     const float *params;                 // worker rows of stride p_stride; W [N][K] at w_off, b [N] at b_off
     int64_t p_stride, w_off, b_off;
-    float *out;                          // a_l [B][N] at out + w * out_stride; splits > 1: sums [split][B][N], without bias and ReLU
-    int64_t out_stride;
-    const float *mask;                   // BACK: a_{l-1} [B][N], stride out_stride: the result is kept where it is positive
+    float *out;                          // a_l [B][out_ld] at out + w * out_stride; splits > 1: sums [split][B][out_ld], without bias and ReLU
+    int64_t out_ld, out_stride;
+    const float *mask;                   // BACK: a_{l-1}, laid out like out: the result is kept where it is positive (null: everywhere)
 };
 
 typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
@@ -137,8 +137,9 @@ __global__ __launch_bounds__(FWD_THREADS) void forward_kernel(FwdArgs g)
     // row the row's last four: no condition stands in the way of the load)
     static_assert(TM * (TN / 4) <= FWD_THREADS, "four results to a thread");
     const int er = tid / (TN / 4), ec = n0 + 4 * (tid % (TN / 4)), left = g.N - ec;
-    const int64_t row_at = (int64_t)min(m0 + er, g.B - 1) * g.N;
-    const float *late_at = BACK ? g.mask + w * g.out_stride + row_at : wp + (g.b_off - g.w_off);
+    const int64_t row_at = (int64_t)min(m0 + er, g.B - 1) * g.out_ld;
+    const bool masked = BACK && g.mask;
+    const float *late_at = masked ? g.mask + w * g.out_stride + row_at : wp + (BACK ? 0 : g.b_off - g.w_off);
     f32x4 late = {0.f, 0.f, 0.f, 0.f};
     if (g.N >= 4) late = *(const f32x4_any *)(late_at + min(ec, g.N - 4));
     for (int n = 0; n < mine; ++n) {
@@ -213,7 +214,7 @@ __global__ __launch_bounds__(FWD_THREADS) void forward_kernel(FwdArgs g)
     }
     if (BACK) {
 #pragma unroll
-        for (int c = 0; c < 4; ++c) v[c] = late[c] > 0.f ? v[c] : 0.f;
+        for (int c = 0; c < 4; ++c) v[c] = !masked || late[c] > 0.f ? v[c] : 0.f;
     } else if (g.splits == 1) {
         v += late;
         if (g.relu) {
@@ -221,7 +222,7 @@ __global__ __launch_bounds__(FWD_THREADS) void forward_kernel(FwdArgs g)
             for (int c = 0; c < 4; ++c) v[c] = fmaxf(v[c], 0.f);
         }
     }
-    float *__restrict__ out = g.out + w * g.out_stride + (int64_t)split * g.B * g.N + row_at + ec;
+    float *__restrict__ out = g.out + w * g.out_stride + (int64_t)split * g.B * g.out_ld + row_at + ec;
     if (left >= 4) {
         *(f32x4_any *)out = v;
     } else {
@@ -237,6 +238,10 @@ __global__ __launch_bounds__(FWD_THREADS) void forward_kernel(FwdArgs g)
 // leave as one 128-bit store).  grid = head_blocks x workers + ceil(tiles x workers / 4) workgroups of four
 // wavefronts, each part rounded up to a multiple of XCDS; the workgroups in front of the tiles add the head's
 // per-chunk sums as in mlp_wgrad.h.
+// LONG: more than 64 samples, 4 GROUPS at a time, whose sums are formed from zero and then added: less rounding than in one long sum (dW of
+// 784-200 on 128 samples against 64 bits 1.5e-7, 1.9e-7; 1000-501 on 250 2.0e-7, 2.7e-7; the split form of bgemm.h, which these
+// had before, 1.7e-7 and 2.2e-7), and with 36 or 32 samples in flight instead of 64 three wavefronts to a SIMD have registers for it
+// (784-512 on 32 workers x 128 samples 66 us, 70 with 52 or 64 and one sum, 76 with 52 or 64 and sums apart).
 constexpr int WG_TM = 32, WG_TN = 64;
 template <int GROUPS, bool LONG>
 __global__ __launch_bounds__(mlpwgrad::THREADS) void wgrad_kernel(mlpwgrad::Args g, fchead::Args h, int chunks, int head_blocks)
@@ -280,11 +285,18 @@ __global__ __launch_bounds__(mlpwgrad::THREADS) void wgrad_kernel(mlpwgrad::Args
     average::Row nb{};
     if (mix) nb = average::row(g.avg, w);
     // row block i, column block j: tile row 2 m + i, tile column 4 n + j for the instruction's indices m, n
-    f32x4 acc[2][4];
+    f32x4 acc[2][4], sum[LONG ? 2 : 1][4];                      // LONG: a step's sum apart
+    auto zero = [&] {
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    };
+    zero();
+#pragma unroll
+    for (int i = 0; LONG && i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) sum[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     vec2 dsum = {0.f, 0.f};
     int s0 = 0;
     do {
@@ -313,7 +325,20 @@ __global__ __launch_bounds__(mlpwgrad::THREADS) void wgrad_kernel(mlpwgrad::Args
                 for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[i], yv[j], acc[i][j], 0, 0, 0);
         }
         s0 += 4 * GROUPS;
+        if constexpr (LONG) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) sum[i][j] += acc[i][j];
+            zero();
+        }
     } while (LONG && s0 < g.B);
+    if constexpr (LONG) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[i][j] = sum[i][j];
+    }
     // register r of (i, j), lane (l16, lq): tile row 2 (4 lq + r) + i, tile column 4 l16 + j
     float *__restrict__ out = g.grads + w * g.g_stride + pick(g.w_off, l);
 #pragma unroll

@@ -1,5 +1,5 @@
 """Gradients of fully connected layers on short batches of any width against the oracle: reductions and outputs on both sides of the
-steps of 16 and of a lane's four, batches on both sides of the blocks of 64 samples and of the steps of 52, outputs narrower than a
+steps of 16 and of a lane's four, batches on both sides of the blocks of 64 samples and of the steps of 36 and 32, outputs narrower than a
 lane's pair, forward products in parts that the head adds."""
 import pytest
 
@@ -12,7 +12,8 @@ SHAPES = [([4, 2, 3], 1, 3, {"mlp_thin_forward", "mlp_wgrad_kernel"}), ([5, 5, 4
           ([15, 31, 5], 16, 3, {"mlp_thin_forward", "mlp_wgrad_kernel"}), ([17, 33, 6], 17, 3, {"mlp_thin_forward", "mlp_wgrad_kernel"}),
           ([130, 65, 63, 7], 65, 3, {"mlp_thin_forward", "mlp_thin_dgrad", "mlp_wgrad_kernel"}),
           ([47, 34, 35, 29, 20], 104, 3, {"mlp_thin_forward", "mlp_thin_dgrad", "mlp_wgrad_kernel"}),
-          ([47, 37, 18, 10], 105, 3, {"mlp_thin_forward", "mlp_thin_dgrad", "mlp_wgrad_kernel"}),
+          ([47, 37, 18, 10], 105, 3, {"mlp_thin_forward", "mlp_thin_dgrad", "mlp_wgrad_kernel"}), ([37, 26, 10], 108, 3, {"mlp_thin_forward", "mlp_wgrad_kernel"}),
+          ([47, 37, 18, 10], 109, 3, {"mlp_thin_forward", "mlp_thin_dgrad", "mlp_wgrad_kernel"}),
           ([21, 6, 5, 10], 255, 4, {"mlp_thin_forward", "mlp_thin_dgrad", "mlp_wgrad_kernel"}),
           ([1605, 36, 10], 30, 3, {"mlp_thin_forward", "mlp_wgrad_kernel"}), ([2063, 40, 10], 80, 3, {"mlp_thin_forward", "mlp_wgrad_kernel"}),
           ([333, 77, 55, 17], 60, 12, {"mlp_thin_forward", "mlp_thin_dgrad", "mlp_wgrad_kernel"}),
