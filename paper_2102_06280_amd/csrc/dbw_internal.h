@@ -153,15 +153,27 @@ bool dbw_fused_dtur_select_fits(const dbw_ctx *c);
 int dbw_launch_dtur_select(dbw_ctx *c, const float *t, int32_t *b_out, float *theta_out, hipStream_t s);
 int dbw_launch_dtur_reset(dbw_ctx *c, hipStream_t s);
 int dbw_launch_dense_weights(dbw_ctx *c, float *P, hipStream_t s);
-// Tile that a workgroup of an average over column tiles starts with (it goes on in steps of the grid).  Workgroups go round the eight
-// XCDs; numbered so, neighbouring tiles, which share cache lines unless every row starts on one, are worked on by one XCD at a
-// time, whose L2 then fetches a shared line once and writes it once.  Rows of odd length without padding, 48 workers x 1 000 003 columns
+// Order in which the workgroups of an average over column tiles take them, a round of tiles being one to each.  Workgroups go round the
+// eight XCDs; numbered by XCD (TOGETHER), neighbouring tiles, which share cache lines unless every row starts on one, are worked on by one XCD at
+// a time, whose L2 then fetches a shared line once and writes it once.  Rows of odd length without padding, 48 workers x 1 000 003 columns
 // with gradients 131 -> 121 us, 128 x 2 800 001 1093 -> 872, densely 128 x 1 000 001 446 -> 381, 256 x 500 001 555 -> 502; rows on lines the
-// same, 64 x 2 160 000 314 -> 308.  Fewer tiles than a whole number of rounds over the XCDs: as they come.
-__device__ __forceinline__ int64_t first_tile(uint32_t block, uint32_t grid)
-{
-    return grid % 8 == 0 ? (block % 8) * (grid / 8) + block / 8 : block;
-}
+// same, 64 x 2 160 000 314 -> 308.  The tiles of a last, partial round go to the XCDs in turn, or half of the chip would have them all (densely 34
+// workers x 47 710 columns 12.2 us, 14.1 so).
+template <bool TOGETHER, class T>
+struct TileWalk {
+    T whole, n_tiles;                 // tiles of whole rounds, and all
+    T grid, block;
+    __device__ __forceinline__ TileWalk(T n) : whole(n / (T)gridDim.x * (T)gridDim.x), n_tiles(n), grid((T)gridDim.x), block((T)blockIdx.x) {}
+    __device__ __forceinline__ T first() const      // (a grid has no more workgroups than there are tiles)
+    {
+        return TOGETHER && grid % 8 == 0 ? (block % 8) * (grid / 8) + block / 8 : block;
+    }
+    __device__ __forceinline__ T next(T t) const      // n_tiles or more: none
+    {
+        if (!TOGETHER) return t + grid;
+        return t + grid < whole ? t + grid : (t < whole ? whole + block : n_tiles);
+    }
+};
 // mix_csr.hip
 // Learning rate of a round as the mixing kernels see it: one value for all workers, or
 // eta_j per worker read from device memory (Section 2.1).

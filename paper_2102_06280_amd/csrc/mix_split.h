@@ -22,7 +22,7 @@
 // past the caches 14.0 and 42.3; the first with gradients 15.7, 16.9; N = 256 x 50 000 with gradients 47, 49.6.  A piece of a row that
 // shares its lines with the next piece goes to memory twice past the caches: N = 128 x 1 M without gradients, rows of 4-byte, 16-byte
 // and 64-byte boundaries 355, 337 and 265 us, past the caches 521, 478 and 263, with gradients 445, 441 and 358, 595, 639 and 410 (with
-// neighbouring tiles on XCDs of their own, before first_tile took them together: 445 -> 388).  (Loads
+// neighbouring tiles on XCDs of their own, before TileWalk took them together: 445 -> 388).  (Loads
 // past the caches cost up to 64 workers: N = 60 x 200 000 33 -> 35.)
 // The stores are global ones (global_access.h): as flat ones every wait for LDS waited for them as well, N = 128 x 2.8 M
 // without gradients 677 -> 662, N = 256 x 1 M 829 and 832.  The multiplies cost time although they overlap the memory side: without them the two take 631 and 565.
@@ -115,7 +115,8 @@ __global__ __launch_bounds__(64 * WAVES, 2) void kernel(
     const int fr = w / C::CBLOCKS * C::RW, fc = w % C::CBLOCKS * C::CW;   // first row and column of the block it splits
 
     // (rows on lines, past the caches: as they come, N = 128 x 1 M with gradients 308 us, 311 otherwise)
-    int64_t tile = STREAM ? blockIdx.x : first_tile(blockIdx.x, gridDim.x);
+    const TileWalk<!STREAM, int> walk(n_tiles);          // (rows of at most DBW_DENSE_MAX_LD columns)
+    int tile = walk.first(), next = walk.next(tile);
     if (tile >= n_tiles) return;
 
     // ---- a block of ROWS x (1024 / ROWS) elements of tile t at (r0, c0) -> 4 KB of LDS, row after row, by LOADS
@@ -197,17 +198,16 @@ __global__ __launch_bounds__(64 * WAVES, 2) void kernel(
     wait_memory<0>();
     split(0);
     wait_lds();
-    if (tile + gridDim.x < n_tiles) {
-        fetch_x(tile + gridDim.x);
-        if (PRO) fetch_g(tile + gridDim.x);
+    if (next < n_tiles) {
+        fetch_x(next);
+        if (PRO) fetch_g(next);
     }
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
 
     int buf = 0;
-    for (; tile < n_tiles; tile += gridDim.x) {
-        const int64_t next = tile + gridDim.x;
-        const int64_t col0 = tile * C::TC + 32 * cg;                              // uniform
+    for (; tile < n_tiles; tile = next, next = walk.next(next)) {
+        const int64_t col0 = (int64_t)tile * C::TC + 32 * cg;                              // uniform
         const bool full = 32 * rb + 32 <= N && col0 + 32 <= dcols;                // uniform: no element needs a guard
         const u32x4 *b0 = &pl[buf][0][(lane >> 5) * C::TC + 32 * cg + (lane & 31)];
         split_bf16::f32x16 acc, small;
@@ -266,9 +266,10 @@ __global__ __launch_bounds__(64 * WAVES, 2) void kernel(
             if (full) wait_memory<EPI ? 16 + LOADS : 16>(); else wait_memory<EPI ? LOADS : 0>();
             split(buf ^ 1);
             wait_lds();                                // raw_x (PRO: raw_g) has been read, the planes are written
-            if (next + gridDim.x < n_tiles) {
-                fetch_x(next + gridDim.x);
-                if (PRO) fetch_g(next + gridDim.x);
+            const int after = walk.next(next);
+            if (after < n_tiles) {
+                fetch_x(after);
+                if (PRO) fetch_g(after);
             }
         }
         // the planes of the next tile are complete, those of this one free (loads and stores stay under way)

@@ -133,15 +133,6 @@ __global__ __launch_bounds__(FWD_THREADS) void forward_kernel(FwdArgs g)
         }
     };
     if (mine > 0) fetch(0);
-    // the four results that this thread stores; their bias, or what masks them, arrives meanwhile (of the last, partial group of a
-    // row the row's last four: no condition stands in the way of the load)
-    static_assert(TM * (TN / 4) <= FWD_THREADS, "four results to a thread");
-    const int er = tid / (TN / 4), ec = n0 + 4 * (tid % (TN / 4)), left = g.N - ec;
-    const int64_t row_at = (int64_t)min(m0 + er, g.B - 1) * g.out_ld;
-    const bool masked = BACK && g.mask;
-    const float *late_at = masked ? g.mask + w * g.out_stride + row_at : wp + (BACK ? 0 : g.b_off - g.w_off);
-    f32x4 late = {0.f, 0.f, 0.f, 0.f};
-    if (g.N >= 4) late = *(const f32x4_any *)(late_at + min(ec, g.N - 4));
     for (int n = 0; n < mine; ++n) {
         f32x4 x[RB], y[CB];
 #pragma unroll
@@ -178,6 +169,16 @@ __global__ __launch_bounds__(FWD_THREADS) void forward_kernel(FwdArgs g)
         }
         multiply(x, y);
     }
+
+    // the four results that this thread stores; their bias, or what masks them, arrives during the sums below (of the last, partial group of a
+    // row the row's last four: no condition stands in the way of the load)
+    static_assert(TM * (TN / 4) <= FWD_THREADS, "four results to a thread");
+    const int er = tid / (TN / 4), ec = n0 + 4 * (tid % (TN / 4)), left = g.N - ec;
+    const int64_t row_at = (int64_t)min(m0 + er, g.B - 1) * g.out_ld;
+    const bool masked = BACK && g.mask;
+    const float *late_at = masked ? g.mask + w * g.out_stride + row_at : wp + (BACK ? 0 : g.b_off - g.w_off);
+    f32x4 late = {0.f, 0.f, 0.f, 0.f};
+    if (g.N >= 4) late = *(const f32x4_any *)(late_at + min(ec, g.N - 4));
 
     // ---- the eight partial tiles: wavefronts 4..7 hand theirs to 0..3 through LDS, which add them and put
     // the sums back; then all threads add the four sums in order, bias, ReLU, 128-bit stores.
