@@ -64,13 +64,18 @@ __device__ __forceinline__ Row row(const Args &a, int w)
     return r;
 }
 
-// V: float or a vector of floats; in memory on any 4-byte boundary
+// V: float or a vector of floats
 template <class V>
 struct lanes {
     static constexpr int n = sizeof(V) / sizeof(float);
 };
+// A V in memory on any 4-byte boundary.  A structure: an attribute that lowers the alignment of a type which depends on a template's
+// argument, or is one, is dropped, and the load promises the boundary of the whole vector.
 template <class V>
-using any_boundary __attribute__((aligned(4))) = V;
+struct __attribute__((packed, aligned(4))) any_boundary {
+    V v;
+};
+static_assert(alignof(any_boundary<float __attribute__((ext_vector_type(4)))>) == 4, "no boundary beyond a float's");
 template <class V>
 __device__ __forceinline__ V fma(float w, V x, V acc)
 {
@@ -93,7 +98,7 @@ __device__ __forceinline__ void gather(const Args &a, const Row &r, int w, int64
     auto load = [&](int j, V (&v)[N]) {
         const char *row = (const char *)(a.x + (int64_t)j * a.ld + base);
 #pragma unroll
-        for (int n = 0; n < N; ++n) v[n] = *(const any_boundary<V> *)(row + off[n]);
+        for (int n = 0; n < N; ++n) v[n] = ((const any_boundary<V> *)(row + off[n]))->v;
     };
     auto add = [&](float wt, const V (&v)[N]) {
 #pragma unroll

@@ -447,7 +447,7 @@ __device__ __forceinline__ void body(const Args &g, float *zl, float *zp, float 
         for (int c0 = RUN * part_no; c0 < H; c0 += RUN * parts) {
             const int width = min(RUN, H - c0), quads = width / 4, groups = C * quads;
             for (int g0 = tid; g0 < groups; g0 += 2 * THREADS) {
-                f32x4_any v[2];
+                f32x4 v[2];
                 uint32_t off[2];
                 int at[2];                              // in the image
 #pragma unroll
@@ -456,7 +456,7 @@ __device__ __forceinline__ void body(const Args &g, float *zl, float *zp, float 
                     off[u] = 4u * (uint32_t)(c * H + k);
                     at[u] = c * HP + k;
                 }
-                average::gather<f32x4_any, 2, true>(g.avg, nb, w, g.w_off, off, v);
+                average::gather<f32x4, 2, true>(g.avg, nb, w, g.w_off, off, v);
 #pragma unroll
                 for (int u = 0; u < 2; ++u) {
                     if (g0 + u * THREADS >= groups) continue;
