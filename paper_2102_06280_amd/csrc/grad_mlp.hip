@@ -169,6 +169,17 @@ bool batch32_layer(int B, int in, int out, int64_t ld_params, int64_t w_off, con
            fc32::aligned16(params) && fc32::aligned16(grads);
 }
 
+// LDS that a workgroup of the head may take.  More than 16 classes in several chunks: two workgroups to a compute unit, or the layer's own
+// kernels are faster (497-18 on 19 workers x 1 024 samples 66 us, with chunks that fill a unit's LDS 72; 256-25 on 6 x 1 024 39 and 26).
+size_t head_lds_limit(int C, int B) { return C > fchead::TILE_C && B > 64 ? 80 * 1024 : fchead::LDS_LIMIT; }
+// The shapes that the head takes for some number of workers, and the chunks that it then has at most: only these need memory for its
+// partial sums, which is as much as a chunk's W for every 16 samples.
+bool head_fits(int H, int C, int B)
+{
+    return C <= fchead::MAX_C && fchead::lds_bytes(H, C, 16) <= head_lds_limit(C, B) && (B + fchead::MAX_S - 1) / fchead::MAX_S <= fchead::MAX_CHUNKS;
+}
+int head_max_chunks(int B) { return std::min((B + 15) / 16, fchead::MAX_CHUNKS); }
+
 // The fused classifier head (fc_head.h) takes the last layer when it is narrow enough.
 struct HeadPlan {
     bool use;
@@ -179,12 +190,8 @@ HeadPlan head_plan(int L, const int32_t *dims, int B, int workers)
 {
     const int H = dims[L - 1], C = dims[L];
     HeadPlan hp{false, 0, 0, 0};
-    if (C > fchead::MAX_C || fchead::lds_bytes(H, C, 16) > fchead::LDS_LIMIT) return hp;
-    // More than 16 classes in several chunks: two workgroups to a compute unit, or the layer's own kernels are faster (497-18 on 19 workers x
-    // 1 024 samples 66 us, with chunks that fill a unit's LDS 72; 256-25 on 6 x 1 024 39 and 26).
-    const size_t limit = C > fchead::TILE_C && B > 64 ? 80 * 1024 : fchead::LDS_LIMIT;
-    auto fits = [&](int S) { return fchead::lds_bytes(H, C, S) <= limit; };
-    if (!fits(16)) return hp;
+    if (!head_fits(H, C, B)) return hp;
+    auto fits = [&](int S) { return fchead::lds_bytes(H, C, S) <= head_lds_limit(C, B); };
     // Longer batches: W is staged, and a partial sum of dW written and read, once per chunk, so as many samples to a chunk as leave work for the
     // chip.  Rounds, chunks of 16 / 32: 784-10 on 6 workers x 1 024 (192 chunks of 32) 31.2 / 24.2 us, on 30 x 150 30.7 / 23.5, 256-10 on 6 x
     // 1 024 19.2 / 17.0, 4 x 1 024 (128) 17.1 / 17.1, 784-10 on 20 x 100 (80) 19.6 / 20.2, behind other
@@ -406,8 +413,8 @@ int64_t dbw_fc_scratch_per_worker(int L, const int32_t *dims, int B)
     int64_t part = 0;
     for (int l = 1; l <= L; ++l) part = std::max<int64_t>(part, (int64_t)MAX_SPLITS * B * dims[l]);
     part = (part + 3) / 4 * 4;
-    if (dims[L] <= fchead::MAX_C)      // partial sums of the fused head, at its smaller chunk size, behind the split partials
-        part += (int64_t)((B + 15) / 16) * fchead::partial_floats(dims[L - 1], dims[L], L > 1);
+    if (head_fits(dims[L - 1], dims[L], B))      // partial sums of the fused head, at its smallest chunk size, behind the split partials
+        part += (int64_t)head_max_chunks(B) * fchead::partial_floats(dims[L - 1], dims[L], L > 1);
     return 2 * act_floats(L, dims, B) + (part + 3) / 4 * 4;
 }
 
