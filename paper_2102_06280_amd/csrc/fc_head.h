@@ -16,9 +16,16 @@
 // More than 16 classes used to take the forward GEMM, softmax_loss_kernel and the backward GEMM of the layer: 617-301-75-26 on
 // 20 workers x 101 samples 82 us a round, here 67; 256-25 on 6 x 1 024 39 and 26, 784-500-30 on 16 x 32 73 and 47.  More than 32 still do.
 //
+// Sums are short, started from zero and added to one another, so that more samples to a chunk or more classes round no more than smaller chunks
+// or the GEMM kernels did.  Error of dW and db against 64 bits in 1e-7, smaller chunks or the GEMM kernels / one sum after the other / here:
+// 784-10 on 150 samples 1.29 1.37 / 1.44 1.67 / 1.19 1.33, 256-25 on 1 024 1.43 1.99 / 1.62 2.02 / 1.00 1.50, the bias gradient below the head of
+// 128-96-20 on 1 024 0.65 / 0.79 / 0.59.  Rounds, one sum after the other / here: 784-10 on 30 workers x 150 23.8 / 23.9 us, on 8 x 32 18.1 / 18.5,
+// 200-10 on 60 x 300 21.4 / 22.1, 128-10 on 64 x 1 024 31.8 / 32.3, 256-25 on 8 x 1 024 26.7 / 26.9.  (Four accumulators in the weight gradient
+// take registers that a third workgroup needs: 64-10 on 40 x 1 024 21.1 / 24.0.)
+//
 // grid = (chunks, workers), or chunks x workers x parts.  With one chunk per worker (batches up to 64) the sums over the batch
 // (dW, db, the bias gradient below, the loss) are final.  Otherwise they are written as per-chunk
-// partials and added in chunk order by reduce_kernel, a second launch: a "last workgroup to arrive
+// partials and added by reduce_kernel, a second launch: a "last workgroup to arrive
 // adds them" scheme inside one launch was measured and rejected, because the memory fence every
 // workgroup needs before it takes its ticket writes back its XCD's whole L2 (46 us for 384
 // workgroups against 6 us of arithmetic).
@@ -225,9 +232,9 @@ __device__ __forceinline__ void body(const Args &g, float *zl, float *zp, float 
     {
         const int MB = S / 16, KS = WAVES / MB;
         const int mb = wave % MB, ks = wave / MB;
-        f32x4 acc[CT][2];
+        f32x4 acc[CT][4];            // four short sums instead of a long one: less rounding, and instructions that don't wait for each other
 #pragma unroll
-        for (int t = 0; t < CT; ++t) acc[t][0] = acc[t][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int t = 0; t < CT; ++t) acc[t][0] = acc[t][1] = acc[t][2] = acc[t][3] = f32x4{0.f, 0.f, 0.f, 0.f};
         if (ks < KS) {
             const int G = HP / 16, per = (G + KS - 1) / KS, g_end = min(G, (ks + 1) * per);
             const float *ap = al + (16 * mb + l16) * HP + 4 * lq, *wp[CT];
@@ -242,7 +249,7 @@ __device__ __forceinline__ void body(const Args &g, float *zl, float *zp, float 
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
 #pragma unroll
-                    for (int t = 0; t < CT; ++t) acc[t][e & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[e], w4[t][e], acc[t][e & 1], 0, 0, 0);
+                    for (int t = 0; t < CT; ++t) acc[t][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[e], w4[t][e], acc[t][e], 0, 0, 0);
             }
             if (ks == KS - 1) {     // the columns behind the last whole group of 16
                 const float *a1 = al + (16 * mb + l16) * HP + lq, *w1[CT];
@@ -256,7 +263,7 @@ __device__ __forceinline__ void body(const Args &g, float *zl, float *zp, float 
 #pragma unroll
         for (int t = 0; t < CT; ++t)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) zp[(wave * 16 + 4 * lq + v) * NC + 16 * t + l16] = acc[t][0][v] + acc[t][1][v];
+            for (int v = 0; v < 4; ++v) zp[(wave * 16 + 4 * lq + v) * NC + 16 * t + l16] = (acc[t][0][v] + acc[t][1][v]) + (acc[t][2][v] + acc[t][3][v]);
         __syncthreads();
         // sample s, class c: the slices in order, then the bias
         for (int e = tid; e < S * NC; e += THREADS) {
@@ -338,13 +345,15 @@ __device__ __forceinline__ void body(const Args &g, float *zl, float *zp, float 
         col[0] = 16 * nb0 + l16;
         col[1] = two ? col[0] + 16 * WAVES : col[0];
         // ---- dW[class][col] = sum over samples of dz[sample][class] a[sample][col]: the operands of 16 samples are
-        // read before their instructions, two accumulators per block
+        // read before their instructions, two accumulators per block; their sums start from zero and are added apart, so that a long chunk
+        // rounds no more than short ones
 #pragma unroll
         for (int t = 0; t < CT; ++t) {
-            f32x4 acc[2][2];
-#pragma unroll
-            for (int p = 0; p < 2; ++p) acc[p][0] = acc[p][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+            f32x4 sum[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
             for (int k0 = 0; k0 < S; k0 += 16) {
+                f32x4 acc[2][2];
+#pragma unroll
+                for (int p = 0; p < 2; ++p) acc[p][0] = acc[p][1] = f32x4{0.f, 0.f, 0.f, 0.f};
                 float zv[4], av[2][4];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
@@ -357,12 +366,14 @@ __device__ __forceinline__ void body(const Args &g, float *zl, float *zp, float 
 #pragma unroll
                     for (int p = 0; p < 2; ++p)
                         acc[p][u & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(zv[u], av[p][u], acc[p][u & 1], 0, 0, 0);
+#pragma unroll
+                for (int p = 0; p < 2; ++p) sum[p] += acc[p][0] + acc[p][1];
             }
 #pragma unroll
             for (int p = 0; p < 2; ++p) {
                 float dw[4];
 #pragma unroll
-                for (int v = 0; v < 4; ++v) dw[v] = acc[p][0][v] + acc[p][1][v];
+                for (int v = 0; v < 4; ++v) dw[v] = sum[p][v];
                 if (MIX && collect) {
                     if (col[p] < H && (p == 0 || two)) {
 #pragma unroll
@@ -403,13 +414,22 @@ __device__ __forceinline__ void body(const Args &g, float *zl, float *zp, float 
                     for (int v = 0; v < 4; ++v) keep[p][v] = al[(16 * mb + 4 * lq + v) * HP + col[p]];
                 f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-                for (int j = 0; j < 4 * CT; ++j)
+                for (int j = 0; j < 4; ++j)
 #pragma unroll
-                    for (int p = 0; p < 2; ++p)
-                        acc[p] = __builtin_amdgcn_mfma_f32_16x16x4f32(j < 4 ? zq[j % 4] : zq1[j % 4], wv[p][j], acc[p], 0, 0, 0);
+                    for (int p = 0; p < 2; ++p) acc[p] = __builtin_amdgcn_mfma_f32_16x16x4f32(zq[j], wv[p][j], acc[p], 0, 0, 0);
+                if (CT > 1) {                                 // the other classes' sum apart: less rounding
+                    f32x4 more[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+#pragma unroll
+                        for (int p = 0; p < 2; ++p) more[p] = __builtin_amdgcn_mfma_f32_16x16x4f32(zq1[j], wv[p][4 * CT - 4 + j], more[p], 0, 0, 0);
+#pragma unroll
+                    for (int p = 0; p < 2; ++p) acc[p] += more[p];
+                }
 #pragma unroll
                 for (int p = 0; p < 2; ++p) {
                     if (p == 1 && !two) continue;
+                    f32x4 ds;
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
                         const int s = 16 * mb + 4 * lq + v;
@@ -417,8 +437,9 @@ __device__ __forceinline__ void body(const Args &g, float *zl, float *zp, float 
                         if (g.mask && !(keep[p][v] > 0.f)) d = 0.f;
                         if (da_to_lds) al[s * HP + col[p]] = d;       // this wavefront alone reads and writes these columns
                         else if (s < ns && col[p] < H) da[(int64_t)s * g.da_ld + col[p]] = d;
-                        colsum[p] += d;                        // rows beyond the batch have dz = 0
+                        ds[v] = d;
                     }
+                    colsum[p] += (ds[0] + ds[1]) + (ds[2] + ds[3]);      // rows beyond the batch have dz = 0
                 }
             }
 #pragma unroll
@@ -433,8 +454,11 @@ __device__ __forceinline__ void body(const Args &g, float *zl, float *zp, float 
         }
     }
     if (tid < C && part_no == 0) {
-        float sum = 0.f;
-        for (int s = 0; s < ns; ++s) sum += zl[s * NC + tid];
+        float every[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};      // every eighth sample (rows beyond the batch are zero)
+        for (int s = 0; s < ns; s += 8)
+#pragma unroll
+            for (int q = 0; q < 8; ++q) every[q] += zl[(s + q) * NC + tid];
+        const float sum = ((every[0] + every[1]) + (every[2] + every[3])) + ((every[4] + every[5]) + (every[6] + every[7]));
         if (MIX && collect) zp[MAX_S + tid] = sum;             // (behind red)
         else if (MIX) average::store(g.avg, nb, w, g.grads + w * g.p_stride, g.b_off + tid, sum);
         else out_b[tid] = sum;
@@ -601,7 +625,7 @@ __global__ __launch_bounds__(THREADS) void kernel(Args g, int chunks, int items,
     body<LOSS, MIX, CT>(g, zl, zp, Wl, al, S, w, chunk, chunks, false, early, part_no, parts);
 }
 
-// Sum of the per-chunk partials in chunk order -> dW, db, the bias gradient below, the loss.
+// Sum of the per-chunk partials in a fixed order -> dW, db, the bias gradient below, the loss.
 // Blocks bx = 0 .. ceil(E / 256) - 1 of 256 threads per worker w, E = partial_floats.
 __device__ __forceinline__ void reduce_body(const Args &g, int chunks, int bx, int w)
 {
@@ -614,12 +638,15 @@ __device__ __forceinline__ void reduce_body(const Args &g, int chunks, int bx, i
     const float *__restrict__ all = g.part + w * g.part_stride;
     float *__restrict__ gw = g.grads + w * g.p_stride;
     float sum = 0.f;
-    for (int q0 = 0; q0 < chunks; q0 += 16) {           // sixteen loads in flight, added in chunk order
+    for (int q0 = 0; q0 < chunks; q0 += 16) {           // sixteen loads in flight, added by pairs
         float v[16];
 #pragma unroll
         for (int u = 0; u < 16; ++u) v[u] = q0 + u < chunks ? all[(int64_t)(q0 + u) * E + e] : 0.f;
 #pragma unroll
-        for (int u = 0; u < 16; ++u) sum += v[u];
+        for (int o = 8; o > 0; o /= 2)
+#pragma unroll
+            for (int u = 0; u < o; ++u) v[u] += v[u + o];
+        sum += v[0];
     }
     const int64_t at = e < n_w ? g.w_off + e : (e < n_w + n_b ? g.b_off + (e - n_w) : g.bprev_off + (e - n_w - n_b));
     if (e < n_w + n_b + n_p) average::store<true>(g.avg, nb, w, gw, at, sum);
