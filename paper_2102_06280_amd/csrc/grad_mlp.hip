@@ -281,6 +281,10 @@ ThinPlan thin_plan(int B, int K, int N, int workers, bool may_split)
     return best;
 }
 
+// More tiles, of longer batches: the GEMM kernel, whose wavefronts share what they fetch; 1023-511-509-10 on 30 x 250 151 us, mlp_thin.h
+// 229, 784-500-10 on 32 x 200 76 and 82, x 128 46 and 46, 300-300-300-10 on 32 x 128 51 and 41.
+bool thin_forward(int B, const ThinPlan &tp) { return B <= 64 || tp.wgs * tp.CB <= 2048; }
+
 template <bool BACK>
 hipError_t launch_thin(const ThinPlan &tp, const mlpthin::FwdArgs &f, hipStream_t s)
 {
@@ -315,9 +319,11 @@ struct WgradPlan {
 // Batches of up to 64 samples take mlp_thin.h.  Longer ones, up to 255, while there is little to multiply (tiles x samples): one launch
 // instead of two or three, and the average on the way, but the fp32 instruction instead of six of bf16; less of it where there are layers
 // between, whose data gradient bgemm::backward_kernel computes in the same launch.  Rounds, bgemm.h / mlp_thin.h: 784-500-10 on 32 workers
-// x 128 (0.9 M) 141 / 128 us, x 200 (1.3 M) 200 / 192, 64 x 255 (3.4 M) 381 / 468; 300-300-300-10 on 32 x 128 (0.4 M) 127 / 115, 63 x 200
-// (1.3 M) 298 / 314.  Behind the chain (whose alternative, mlp_wgrad.h, shares a tile among four wavefronts) not with fewer tiles than
-// SIMDs: 784-128-10 on 16 x 200 43.8 / 44.8, 784-512-10 on 32 x 128 135 / 122.
+// x 128 (0.9 M) 139 / 124 us, 784-200-10 on 32 x 200 (0.6 M) 116 / 97, 64 x 255 (3.4 M) 381 / 468; 300-300-300-10 on 16 x 200 (0.5 M) 112 / 92,
+// 63 x 200 (1.3 M) 298 / 314.  Only where the forward products are mlp_thin.h's as well, whose rounding makes up for that of these sums: dW of
+// 784-300 on 32 x 200, whose forward product is bgemm.h's, 2.89e-7 with bgemm.h, 2.97e-7 here; 784-200 on 32 x 128 1.84, 1.53.  (784-500-10 on 32 x
+// 200 would be 196 / 185 us.)  Behind the chain (whose alternative, mlp_wgrad.h, shares a tile among four wavefronts) not with fewer tiles than
+// SIMDs: 784-128-10 on 16 x 200 43.8 / 44.8, 784-512-10 on 32 x 128 130 / 118.
 constexpr int64_t THIN_WORK = 1400000, THIN_WORK_DEEP = 700000;
 struct WgradTiles {
     bool thin;                  // one wavefront per 32 x 64 tile, no split (mlp_thin.h)
@@ -337,6 +343,7 @@ WgradTiles wgrad_tiles(int layers, const int32_t *dims, int B, int N, bool chain
     WgradTiles r{};
     const int64_t tiles = (int64_t)count(mlpthin::WG_TM, mlpthin::WG_TN, nullptr) * N;
     r.thin = B <= 64 || (B <= mlpthin::MAX_B && tiles * B <= (layers == 1 ? THIN_WORK : THIN_WORK_DEEP) && (!chain || tiles >= 1024));
+    for (int l = 1; l <= layers && r.thin && !chain; ++l) r.thin = thin_forward(B, thin_plan(B, dims[l - 1], dims[l], N, false));
     r.tn = !r.thin && (int64_t)count(64, 64, nullptr) * N >= 512 ? 64 : 32;
     r.tiles = r.thin ? count(mlpthin::WG_TM, mlpthin::WG_TN, begin) : count(64, r.tn, begin);
     return r;
@@ -514,10 +521,11 @@ int dbw_fc_forward_backward(dbw_ctx *c, dbw_fc_args &a, hipStream_t s)
             continue;
         }
         // short batches: operands straight from global memory into matrix-instruction fragments (mlp_thin.h)
-        // (more tiles, of longer batches: the GEMM kernel, whose wavefronts share what they fetch; 1023-511-509-10 on 30 x 250
-        // 151 us, mlp_thin.h 229, 784-500-10 on 32 x 200 76 and 82, x 128 46 and 46, 300-300-300-10 on 32 x 128 51 and 41)
-        const ThinPlan tp = thin_plan(B, dims[l - 1], dims[l], N, head_can_sum && l == L - 1 && dims[l] <= fchead::RUN);
-        if (a.grad_path == DBW_GRAD_AUTO && B <= mlpthin::MAX_B && dims[l - 1] >= 4 && (l > 1 || fc32::aligned16(a.in)) && (B <= 64 || tp.wgs * tp.CB <= 2048)) {
+        const bool may_split = head_can_sum && l == L - 1 && dims[l] <= fchead::RUN;
+        ThinPlan tp = thin_plan(B, dims[l - 1], dims[l], N, may_split);
+        if (may_split && !thin_forward(B, tp))             // in one part (784-200-10 on 32 x 128: the round 72.6 us with the GEMM kernel, 67.1 so)
+            tp = thin_plan(B, dims[l - 1], dims[l], N, false);
+        if (a.grad_path == DBW_GRAD_AUTO && B <= mlpthin::MAX_B && dims[l - 1] >= 4 && (l > 1 || fc32::aligned16(a.in)) && thin_forward(B, tp)) {
             mlpthin::FwdArgs f{};
             f.B = B; f.K = dims[l - 1]; f.N = dims[l]; f.workers = N; f.relu = l < L ? 1 : 0;
             f.splits = tp.splits; f.kper = tp.kper;
@@ -788,7 +796,7 @@ int dbw_fc_forward_backward(dbw_ctx *c, dbw_fc_args &a, hipStream_t s)
                                act + dz_off[1], (int64_t)dims[1], wstride, params + w_off[1], c->ld,
                                (const float *)nullptr, (int64_t)0, (int64_t)0, a.din, a.din_ld, a.din_stride);
             DBW_HIP(hipGetLastError());
-        } else if (dgrad_gemm && grouped && thin && dims[l] >= 4 && !(l == 1 && bgemm::aligned(dg.A, dg.M, dg.K) && bgemm::aligned(dg.B, dg.N, dg.K)) && (B <= 64 || dgrad_thin.wgs * dgrad_thin.CB <= 2048)) {
+        } else if (dgrad_gemm && grouped && thin && dims[l] >= 4 && !(l == 1 && bgemm::aligned(dg.A, dg.M, dg.K) && bgemm::aligned(dg.B, dg.N, dg.K)) && thin_forward(B, dgrad_thin)) {
             // (The gradient of a stack's own input, wide and with a short reduction, stays on the GEMM kernel where rows are aligned: 16 workers x
             // 50 samples, 128 -> 1568 12.4 us, here 14.8.  Elsewhere that would be the split form: rounds of 290 -> 600 on 5 x 32 139, 127.)
             mlpthin::FwdArgs f{};

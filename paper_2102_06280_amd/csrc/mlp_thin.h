@@ -239,13 +239,15 @@ __global__ __launch_bounds__(FWD_THREADS) void forward_kernel(FwdArgs g)
 // leave as one 128-bit store).  grid = head_blocks x workers + ceil(tiles x workers / 4) workgroups of four
 // wavefronts, each part rounded up to a multiple of XCDS; the workgroups in front of the tiles add the head's
 // per-chunk sums as in mlp_wgrad.h.
-// LONG: more than 64 samples, 4 GROUPS at a time, whose sums are formed from zero and then added: less rounding than in one long sum (dW of
-// 784-200 on 128 samples against 64 bits 1.5e-7, 1.9e-7; 1000-501 on 250 2.0e-7, 2.7e-7; the split form of bgemm.h, which these
-// had before, 1.7e-7 and 2.2e-7), and with 36 or 32 samples in flight instead of 64 three wavefronts to a SIMD have registers for it
-// (784-512 on 32 workers x 128 samples 66 us, 70 with 52 or 64 and one sum, 76 with 52 or 64 and sums apart).
+// Sums of at most 32 samples start from zero and are added afterwards: less rounding than in one long sum.  LONG: more than 64 samples, 4 GROUPS at a
+// time, in sums of half of that.  Error of dW and db against 64 bits in 1e-7, bgemm.h / sums of whole steps / here: 64-33 on 200 samples 1.38 1.41 /
+// 1.29 1.48 / 1.17 1.15, 617-301 on 101 1.91 1.24 / 1.83 1.12 / 1.80 1.06, 333-77 on 60 (one sum) 1.77 1.24 / 1.79 1.14 / 1.67 1.12.  (A third level of
+// sums and steps of 12 samples: 784-300 on 200 2.97 -> 2.94.)  With 36 or 32 samples in flight instead of 64 three wavefronts to a SIMD have
+// registers for LONG (784-512 on 32 workers x 128 samples 66 us, 76 with 52 or 64 and sums apart).  The bound on the wavefronts keeps the sums out
+// of accumulation registers, which they would need besides the others: 784-200-10 on 32 x 64 samples 46.8 -> 46.3 us a round.
 constexpr int WG_TM = 32, WG_TN = 64;
 template <int GROUPS, bool LONG>
-__global__ __launch_bounds__(mlpwgrad::THREADS) void wgrad_kernel(mlpwgrad::Args g, fchead::Args h, int chunks, int head_blocks)
+__global__ __launch_bounds__(mlpwgrad::THREADS, GROUPS == 4 ? 4 : 3) void wgrad_kernel(mlpwgrad::Args g, fchead::Args h, int chunks, int head_blocks)
 {
     constexpr int TM = WG_TM, TN = WG_TN, WAVES = mlpwgrad::WAVES;
     typedef float vec2 __attribute__((ext_vector_type(2)));
@@ -286,19 +288,24 @@ __global__ __launch_bounds__(mlpwgrad::THREADS) void wgrad_kernel(mlpwgrad::Args
     average::Row nb{};
     if (mix) nb = average::row(g.avg, w);
     // row block i, column block j: tile row 2 m + i, tile column 4 n + j for the instruction's indices m, n
-    f32x4 acc[2][4], sum[LONG ? 2 : 1][4];                      // LONG: a step's sum apart
-    auto zero = [&] {
+    constexpr int APART = LONG ? (GROUPS + 1) / 2 : 8;          // groups whose sum is formed from zero
+    f32x4 acc[2][4], sum[2][4];
+    vec2 dacc = {0.f, 0.f}, dsum = dacc;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = sum[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto add = [&] {
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int j = 0; j < 4; ++j) {
+                sum[i][j] += acc[i][j];
+                acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+        dsum += dacc;
+        dacc = vec2{0.f, 0.f};
     };
-    zero();
-#pragma unroll
-    for (int i = 0; LONG && i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) sum[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    vec2 dsum = {0.f, 0.f};
     int s0 = 0;
     do {
         vec2 x[GROUPS];
@@ -313,40 +320,32 @@ __global__ __launch_bounds__(mlpwgrad::THREADS) void wgrad_kernel(mlpwgrad::Args
                                            // saves registers by fetching a few groups at a time: 18.1 against 17.6 us)
 #pragma unroll
         for (int u = 0; u < GROUPS; ++u) {
+            const bool first = !LONG && u < APART;
             vec2 xv = x[u];
             f32x4 yv = y[u];
             if (s0 + 4 * u + lq >= g.B) {
                 xv = vec2{0.f, 0.f};
                 yv = f32x4{0.f, 0.f, 0.f, 0.f};
             }
-            dsum += xv;
+            (first ? dsum : dacc) += xv;
 #pragma unroll
             for (int i = 0; i < 2; ++i)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[i], yv[j], acc[i][j], 0, 0, 0);
+                for (int j = 0; j < 4; ++j) {
+                    f32x4 &to = first ? sum[i][j] : acc[i][j];
+                    to = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[i], yv[j], to, 0, 0, 0);
+                }
+            if (LONG ? (u + 1) % APART == 0 || u + 1 == GROUPS : GROUPS > APART && u + 1 == GROUPS) add();
         }
         s0 += 4 * GROUPS;
-        if constexpr (LONG) {
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) sum[i][j] += acc[i][j];
-            zero();
-        }
     } while (LONG && s0 < g.B);
-    if constexpr (LONG) {
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) acc[i][j] = sum[i][j];
-    }
     // register r of (i, j), lane (l16, lq): tile row 2 (4 lq + r) + i, tile column 4 l16 + j
     float *__restrict__ out = g.grads + w * g.g_stride + pick(g.w_off, l);
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         f32x4 v[4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) v[r] = f32x4{acc[i][0][r], acc[i][1][r], acc[i][2][r], acc[i][3][r]};
+        for (int r = 0; r < 4; ++r) v[r] = f32x4{sum[i][0][r], sum[i][1][r], sum[i][2][r], sum[i][3][r]};
         if (mix) {
             uint32_t off[4];
 #pragma unroll
