@@ -574,7 +574,9 @@ int dbw_fc_forward_backward(dbw_ctx *c, dbw_fc_args &a, hipStream_t s)
     } else {
         grouped = grouped && a.in_ld % 4 == 0 && a.in_stride % 4 == 0 && fc32::aligned16(grads) &&
                   c->ld % 4 == 0 && a.param_off % 4 == 0 && fc32::aligned16(act) && wstride % 4 == 0;
-        for (int l = 0; l <= Lw && grouped; ++l) grouped = dims[l] % 4 == 0;
+        // (also the head's classes, of more than 16: there the layers below took the GEMM kernels before the head took the last one, and
+        // mlp_wgrad.h rounds more: dW of 64-48-25 on 300 samples 1.19e-7, 1.39; 32 workers 43.6 us a round, 35.8; 16 x 600 256-100-25 59, 51)
+        for (int l = 0; l <= (dims[L] > fchead::TILE_C ? L : Lw) && grouped; ++l) grouped = dims[l] % 4 == 0;
     }
     for (int l = 1; l <= Lw && grouped; ++l)
         grouped = !batch32_layer(B, dims[l - 1], dims[l], c->ld, w_off[l], params, grads);
