@@ -256,7 +256,9 @@ ChainPlan chain_plan(int L, const int32_t *dims, int B, int workers, int grad_pa
 // sums may be left to the reader, parts of the reduction: whatever gives the shortest time, in cycles, for the compute unit with most
 // workgroups.  A wavefront takes every eighth chunk of 16 k, for which the matrix instructions (two wavefronts to a SIMD) and the loads take about
 // as long as said here; a part more is a sum more for the reader, the head (and none where the head's workgroups would rather share its
-// chunks by runs of columns: 784-420-10 on 20 workers x 19 samples 44 us, in two parts 47).
+// chunks by runs of columns: 784-420-10 on 20 workers x 19 samples 44 us, in two parts 47).  Rounds, with nothing for the loads beside the
+// instructions and 500 for a part / so: 784-700-30 on 64 x 64 (tiles of 16 outputs / 32) 252 / 232 us, 256-168-10 on 32 x 64 (two parts / one) 35.2 /
+// 34.1, 1024-200-10 on 16 x 64 40.2 / 39.0; with 1 500 for a part 784-128-10 on 8 x 32 26.5 instead of 25.9.
 struct ThinPlan {
     int RB, CB, blocks, splits, kper;
     int64_t wgs;
@@ -271,8 +273,8 @@ ThinPlan thin_plan(int B, int K, int N, int workers, bool may_split)
             const int kper = (chunks + splits - 1) / splits;
             if (splits > 1 && kper < mlpthin::FWD_WAVES) continue;
             const int64_t wgs = (int64_t)((N + 16 * CB - 1) / (16 * CB)) * blocks * splits * workers;
-            const int64_t iter = std::max(256 * RB * CB, 164 * (RB + CB));
-            const int64_t cost = (wgs + 255) / 256 * ((kper + mlpthin::FWD_WAVES - 1) / mlpthin::FWD_WAVES) * iter + 500 * (splits - 1);
+            const int64_t iter = 256 * RB * CB + 100 * (RB + CB);
+            const int64_t cost = (wgs + 255) / 256 * ((kper + mlpthin::FWD_WAVES - 1) / mlpthin::FWD_WAVES) * iter + 800 * (splits - 1);
             if (best.wgs == 0 || cost < least) {
                 least = cost;
                 best = {RB, CB, blocks, splits, kper, wgs};

@@ -247,7 +247,7 @@ __global__ __launch_bounds__(FWD_THREADS) void forward_kernel(FwdArgs g)
 // of accumulation registers, which they would need besides the others: 784-200-10 on 32 x 64 samples 46.8 -> 46.3 us a round.
 constexpr int WG_TM = 32, WG_TN = 64;
 template <int GROUPS, bool LONG>
-__global__ __launch_bounds__(mlpwgrad::THREADS, GROUPS == 4 ? 4 : 3) void wgrad_kernel(mlpwgrad::Args g, fchead::Args h, int chunks, int head_blocks)
+__global__ __launch_bounds__(mlpwgrad::THREADS, GROUPS == 4 ? 1 : 3) void wgrad_kernel(mlpwgrad::Args g, fchead::Args h, int chunks, int head_blocks)
 {
     constexpr int TM = WG_TM, TN = WG_TN, WAVES = mlpwgrad::WAVES;
     typedef float vec2 __attribute__((ext_vector_type(2)));
