@@ -207,6 +207,10 @@ HeadPlan head_plan(int L, const int32_t *dims, int B, int workers)
         S = fits(32) && (int64_t)((B + 31) / 32) * workers >= (L == 1 ? 128 : 160) ? 32 : 16;
     const int chunks = (B + S - 1) / S;
     if (chunks > fchead::MAX_CHUNKS) return hp;
+    // More than 16 classes in chunks of a short batch that does not fit whole, one workgroup to a compute unit: the layer's own kernels from half of
+    // the chip on (978-17 on 61 workers x 64 samples 42.4 / 30.5 us, 784-20 on 44 x 48 31.4 / 25.7, 784-26 on 32 x 64 30.5 / 32.3).  Behind other
+    // layers the head saves them more (400-600-20 on 64 x 33 106.5 / 113.1).
+    if (L == 1 && C > fchead::TILE_C && chunks > 1 && B <= 64 && fchead::lds_bytes(H, C, S) > 80 * 1024 && (int64_t)chunks * workers > 128) return hp;
     hp.use = true;
     hp.chunks = chunks;
     hp.S = S;

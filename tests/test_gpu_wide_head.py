@@ -21,3 +21,10 @@ def test_gradients_match_oracle(B, orc, dims, batch, n, loss):  # noqa: F811
 @pytest.mark.parametrize("dims,batch,loss,n,pad", AVERAGE, ids=["-".join(map(str, s[0])) + f"-b{s[1]}" for s in AVERAGE])
 def test_average_on_the_way(B, dims, batch, loss, n, pad):  # noqa: F811
     average_on_the_way(B, dims, batch, loss, n, pad, "each")
+
+
+@pytest.mark.parametrize("dims,batch,n,head", [([978, 17], 64, 32, True), ([978, 17], 64, 33, False), ([784, 20], 48, 42, True), ([784, 20], 48, 43, False),
+                                               ([256, 20], 64, 64, True), ([40, 600, 20], 33, 64, True)])
+def test_chunks_of_a_short_batch(B, orc, dims, batch, n, head):  # noqa: F811
+    """A short batch that does not fit the head's LDS whole, in chunks of one workgroup to a compute unit, on half of the chip and beyond."""
+    check_gradients(B, orc, dims, batch, n, "xent", expect={"fc_head_kernel" if head else "softmax_loss_kernel"})
