@@ -157,7 +157,7 @@ int dbw_launch_dense_weights(dbw_ctx *c, float *P, hipStream_t s);
 // eight XCDs; numbered by XCD (TOGETHER), neighbouring tiles, which share cache lines unless every row starts on one, are worked on by one XCD at
 // a time, whose L2 then fetches a shared line once and writes it once.  Rows of odd length without padding, 48 workers x 1 000 003 columns
 // with gradients 131 -> 121 us, 128 x 2 800 001 1093 -> 872, densely 128 x 1 000 001 446 -> 381, 256 x 500 001 555 -> 502; rows on lines the
-// same, 64 x 2 160 000 314 -> 308.  The tiles of a last, partial round go to the XCDs in turn, or half of the chip would have them all (densely 34
+// same to within what differs from card to card (64 x 2 160 000 314 -> 308; 128 x 2 800 000, local step first, 822 -> 826 on one, 811 -> 796 on another).  The tiles of a last, partial round go to the XCDs in turn, or half of the chip would have them all (densely 34
 // workers x 47 710 columns 12.2 us, 14.1 so).
 template <bool TOGETHER, class T>
 struct TileWalk {

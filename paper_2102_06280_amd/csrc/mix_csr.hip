@@ -98,8 +98,7 @@ __device__ __forceinline__ void store_stream(float *p, float4 v, int64_t left)
 // Persistent workgroup, tiles of N rows x TC4 float4 columns (N * TC4 <= LDS_TILE).
 // Element f of a tile is (row f / TC4, column f % TC4); thread `tid` owns elements
 // tid + u * LDS_THREADS, the same (row, column offset) in every tile.
-// TOGETHER: the order of the tiles (TileWalk).
-template <int ORDER, bool HAS_G, int TC4, bool WIDE, class LR, bool TOGETHER = true>
+template <int ORDER, bool HAS_G, int TC4, bool WIDE, class LR>
 __global__ __launch_bounds__(LDS_THREADS) void mix_lds_tiles(
     int N, int nnz, int64_t n_vec, int64_t ld, int64_t n_tiles, const int32_t *__restrict__ rowptr,
     const int32_t *__restrict__ p, const int32_t *__restrict__ sel_idx, const float *__restrict__ sel_w,
@@ -148,7 +147,7 @@ __global__ __launch_bounds__(LDS_THREADS) void mix_lds_tiles(
         }
     };
 
-    const TileWalk<TOGETHER, int64_t> walk(n_tiles);
+    const TileWalk<true, int64_t> walk(n_tiles);
     int64_t t = walk.first();
     if (t >= n_tiles) return;
     fetch(t);
@@ -286,12 +285,12 @@ int device_cus()
     return cus;
 }
 
-template <int ORDER, bool HAS_G, int TC4, bool WIDE, class LR, bool TOGETHER = true>
+template <int ORDER, bool HAS_G, int TC4, bool WIDE, class LR>
 int launch_lds(dbw_ctx *c, const float *x, const float *g, float *out, LR lr, int64_t n_vec, hipStream_t s)
 {
     const int64_t n_tiles = (n_vec + TC4 - 1) / TC4;
     const size_t lds = sizeof(float4) * 2 * LDS_TILE + (size_t)c->nnz * 8;
-    auto kern = mix_lds_tiles<ORDER, HAS_G, TC4, WIDE, LR, TOGETHER>;
+    auto kern = mix_lds_tiles<ORDER, HAS_G, TC4, WIDE, LR>;
     static bool attr_set = false;                      // per instantiation
     if (!attr_set) {
         DBW_HIP(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
@@ -363,12 +362,7 @@ int launch_groups(dbw_ctx *c, const float *x, const float *g, float *out, LR lr,
         case 256: return launch_lds<ORDER, HAS_G, 256, WIDE, LR>(c, x, g, out, lr, n_vec, s);
         case 128: return launch_lds<ORDER, HAS_G, 128, WIDE, LR>(c, x, g, out, lr, n_vec, s);
         case 64: return launch_lds<ORDER, HAS_G, 64, WIDE, LR>(c, x, g, out, lr, n_vec, s);
-        case 32:
-            // Rows that start on lines and pieces of 512 bytes: apart, N = 128 x 2.8 M, local step first, 822 us, together 829 (pieces of 1 KB:
-            // 64 x 2.16 M 314 and 308).
-            if (WIDE && c->ld % 32 == 0 && ((uintptr_t)x | (uintptr_t)out | (HAS_G ? (uintptr_t)g : 0)) % 128 == 0)
-                return launch_lds<ORDER, HAS_G, 32, WIDE, LR, !WIDE>(c, x, g, out, lr, n_vec, s);
-            return launch_lds<ORDER, HAS_G, 32, WIDE, LR>(c, x, g, out, lr, n_vec, s);
+        case 32: return launch_lds<ORDER, HAS_G, 32, WIDE, LR>(c, x, g, out, lr, n_vec, s);
         case 16: return launch_lds<ORDER, HAS_G, 16, WIDE, LR>(c, x, g, out, lr, n_vec, s);
         default: return launch_lds<ORDER, HAS_G, 8, WIDE, LR>(c, x, g, out, lr, n_vec, s);
         }
