@@ -49,8 +49,10 @@ constexpr int DBW_AVERAGE_DEGREE = 6;
 constexpr int average_degree(int L, int B, int64_t tiles, bool wide, bool thin, int64_t bytes)
 {
     if (L == 1) return bytes < (int64_t)5 << 19 ? DBW_AVERAGE_DEGREE : (bytes < (int64_t)5 << 20 ? 4 : 0);
-    // (mlp_thin.h on more than 64 samples: 784-300-10 on 64 x 128, 60 MB, 163 us with the pass, 174 on the way)
-    if (B > 64 && thin) return bytes < (int64_t)56 << 20 ? DBW_AVERAGE_DEGREE : 2;
+    // (mlp_thin.h on more than 64 samples, which it takes up to some 90 MB of parameters: with a pass / on the way, 4 neighbours, 784-200-10 on 64 x
+    // 128, 41 MB, 118.9 / 121.1, 784-256-10 on 64 x 100, 51 MB, 138.0 / 124.3, 1024-256-10 on 64 x 96, 67 MB, 165.9 / 150.4, 1200-256-10 on 64 x
+    // 100, 79 MB, 174.8 / 172.1; with 6 the third 167.8 / 153.9, 784-200-10 on 32 x 128 72.2 / 69.1)
+    if (B > 64 && thin) return DBW_AVERAGE_DEGREE;
     if (B > 64) return wide ? 4 : DBW_AVERAGE_DEGREE;
     if (tiles < 512) return tiles < 256 ? DBW_AVERAGE_DEGREE : 4;
     if (tiles < 2048) return B > 32 ? (tiles < 1024 ? 2 : 4) : (B > 16 ? 4 : 2);

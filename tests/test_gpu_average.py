@@ -32,7 +32,11 @@ def hub_graph(n, extra):
 CASES = [([784, 10], 32, "xent", 8, 64), ([101, 7], 64, "mse", 9, 1), ([257, 16], 300, "xent", 5, 1), ([103, 9], 200, "mse", 13, 64), ([60, 10], 128, "xent", 12, 1), ([300, 9], 40, "xent", 12, 1), ([256, 10], 1024, "xent", 6, 64),
          ([64, 36, 10], 16, "xent", 14, 64), ([300, 92, 10], 32, "mse", 17, 64), ([784, 200, 10], 64, "xent", 24, 64),
          ([100, 36, 52, 3], 50, "xent", 7, 64), ([200, 320, 100, 10], 256, "xent", 14, 64), ([68, 36, 10], 260, "mse", 4, 64),
-         ([256, 256, 256, 10], 1024, "mse", 16, 64), ([128, 128, 128, 10], 300, "xent", 12, 64), ([68, 36, 10], 260, "xent", 11, 64), ([784, 200, 10], 64, "xent", 24, 1)]
+         ([256, 256, 256, 10], 1024, "mse", 16, 64), ([128, 128, 128, 10], 300, "xent", 12, 64), ([68, 36, 10], 260, "xent", 11, 64), ([784, 200, 10], 64, "xent", 24, 1),
+         # widths that are no multiple of four, whose last pairs of rows and groups of columns are moved back: up to 64 samples, steps of 36 and of 32,
+         # rows without padding that start on 16-byte boundaries and rows that don't
+         ([47, 37, 18, 10], 50, "xent", 20, 64), ([47, 37, 18, 10], 105, "mse", 20, 64), ([47, 37, 18, 10], 109, "xent", 20, 64),
+         ([21, 7, 5, 10], 255, "xent", 20, 64), ([617, 301, 75, 26], 101, "xent", 20, 1), ([47, 37, 18, 9], 105, "xent", 20, 1)]
 
 
 @pytest.mark.parametrize("rates", ["one", "each"])
@@ -68,7 +72,7 @@ def test_average_on_the_way_is_the_average(B, dims, batch, loss, n, pad, rates):
         finally:
             B.dbw_destroy(h)
     assert got["pass"][2]
-    assert got["way"][2] == (pad == 1 and len(dims) > 2)      # rows off 16-byte boundaries: the kernels that average are not taken
+    assert got["way"][2] == (ld % 4 != 0 and len(dims) > 2)   # rows off 16-byte boundaries: the kernels that average are not taken
     assert np.array_equal(got["way"][0][:, :d], got["pass"][0][:, :d])
     assert np.all(got["way"][0][:, d:] == 3.0)
     assert np.array_equal(got["way"][1], got["pass"][1])
@@ -109,7 +113,8 @@ def test_long_neighbour_lists_take_the_pass(B, dims, batch, extra, on_the_way):
                                                             ([256, 384, 10], 256, 24, 4, True), ([256, 384, 10], 256, 24, 6, False), ([128, 384, 10], 256, 30, 6, True),
                                                             ([784, 10], 8, 128, 4, True), ([784, 10], 8, 128, 6, False),
                                                             ([784, 10], 8, 192, 2, False), ([784, 10], 70, 192, 2, True), ([64, 36, 10], 16, 7, 4, True),
-                                                            ([64, 36, 10], 16, 8, 4, False), ([64, 36, 10], 32, 9, 4, True), ([784, 384, 200, 10], 256, 12, 4, False), ([256, 256, 256, 10], 300, 12, 4, True)])
+                                                            ([64, 36, 10], 16, 8, 4, False), ([64, 36, 10], 32, 9, 4, True), ([784, 384, 200, 10], 256, 12, 4, False), ([256, 256, 256, 10], 300, 12, 4, True),
+                                                            ([300, 37, 10], 100, 40, 6, True), ([300, 37, 10], 100, 40, 8, False), ([1024, 255, 10], 96, 64, 6, True)])
 def test_many_neighbours_take_the_pass(B, dims, batch, n, degree, on_the_way):
     """Every worker linked to the nearest `degree` on a circle: how many the kernels average on the way depends on the tiles of the gradients."""
     nb = [sorted({(i + k) % n for k in range(-(degree // 2), degree // 2 + 1)} - {i}) for i in range(n)]
