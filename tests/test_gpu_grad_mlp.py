@@ -55,11 +55,11 @@ SHAPES = [
 ]
 
 
-def check_gradients(B, orc, dims, batch, n, loss_kind, grad_path=0, expect=None):
+def check_gradients(B, orc, dims, batch, n, loss_kind, grad_path=0, expect=None, pad=64):
     g = np.random.default_rng(401)
     desc = {"kind": "mlp", "dims": dims, "loss": loss_kind}
     d = inputs.param_count(desc)
-    ld = inputs.pad_ld(d)
+    ld = inputs.pad_ld(d, pad)
     rowptr, colidx = inputs.graph_ring(max(n, 3)) if n >= 3 else (np.array([0, 1, 2], np.int32), np.array([1, 0], np.int32))
     n = rowptr.size - 1
     params = inputs.init_params(desc, n, ld, g)

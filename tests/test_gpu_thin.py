@@ -24,3 +24,11 @@ SHAPES = [([4, 2, 3], 1, 3, {"mlp_thin_forward", "mlp_wgrad_kernel"}), ([5, 5, 4
 @pytest.mark.parametrize("loss", ["xent", "mse"])
 def test_short_batches_of_any_width(B, orc, dims, batch, n, kernels, loss):  # noqa: F811
     check_gradients(B, orc, dims, batch, n, loss, expect=kernels)
+
+
+@pytest.mark.parametrize("dims,batch,kernels", [([47, 34, 35, 9], 104, {"mlp_thin_forward", "mlp_thin_dgrad", "mlp_wgrad_kernel"}), ([15, 30, 5], 16, {"mlp_thin_forward", "mlp_wgrad_kernel"}),
+                                                ([130, 65, 63, 7], 60, {"mlp_thin_forward", "mlp_thin_dgrad", "mlp_wgrad_kernel"}), ([784, 33], 200, {"mlp_thin_forward", "mlp_wgrad_kernel"})])
+def test_rows_on_any_boundary(B, orc, dims, batch, kernels):  # noqa: F811
+    """Rows without padding, an odd number of parameters: workers and layers start on any 4-byte boundary."""
+    assert (sum((a + 1) * b for a, b in zip(dims, dims[1:]))) % 2 == 1
+    check_gradients(B, orc, dims, batch, 3, "xent", expect=kernels, pad=1)
