@@ -55,7 +55,7 @@ def gradients(B, desc, dims, params, x, y):
 # One filter row and two with a partial last step, widths on and off 16 and 8, 3 x 3 and 5 x 5, one and several blocks of
 # output channels, one and several samples per workgroup, shared blocks of the weight gradient and not.
 CNN = [(1, 28, 28, 6, 16, 5, 20, 10), (3, 12, 20, 9, 40, 5, 12, 5), (2, 16, 16, 17, 33, 3, 12, 4), (1, 8, 8, 4, 70, 3, 8, 3)]
-CNN_WHERE = ["pixels", "largest", "conv1 +inf", "conv2 +inf", "conv2 -inf", "conv2 nan"]
+CNN_WHERE = ["pixels", "pooled", "largest", "conv1 +inf", "conv2 +inf", "conv2 -inf", "conv2 nan"]
 
 
 @pytest.mark.parametrize("where", CNN_WHERE)
@@ -63,7 +63,9 @@ CNN_WHERE = ["pixels", "largest", "conv1 +inf", "conv2 +inf", "conv2 -inf", "con
 def test_cnn_element_by_element(B, orc, shape, where):
     """Worker 1 of two, batch 3.  pixels: an infinite pixel inside one sample and one in the corner of another, under negative
     filters, so that the pooled maps and the loss stay finite and only those weight gradients of conv1 are lost that the
-    pixels enter (0 * inf), not those of filter positions that would need an output outside the image.  largest: the
+    pixels enter (0 * inf), not those of filter positions that would need an output outside the image.  pooled: an infinite pixel under
+    positive filters of one channel, whose pooled values conv2 multiplies by negative weights only, so that every delta that meets them
+    is zero and all other sums are finite: conv2's weight gradient of that channel is lost (0 * inf), of the others none.  largest: the
     largest float as a pixel.  conv1 / conv2: one infinite or NaN weight at a filter's centre, which no output reaches
     over the border with; conv1's under positive pixels, so that the channel is infinite throughout, and below filters
     of both signs, so that all of conv2 is inf - inf.  Tolerance as for finite gradients (3e-5 per layer)."""
@@ -82,6 +84,11 @@ def test_cnn_element_by_element(B, orc, shape, where):
         w1[:, c] = -np.abs(w1[:, c]) - 0.01
         x[1, 0, c, H // 2, W // 2] = np.inf
         x[1, 2, c, 0, W - 1] = np.inf
+    elif where == "pooled":
+        w1[:, c] = -np.abs(w1[:, c]) - 0.01
+        w1[C1 - 1, c] *= -1.0
+        w2[:, C1 - 1] = -np.abs(w2[:, C1 - 1]) - 0.01
+        x[1, 0, c, H // 2, W // 2] = np.inf
     elif where == "largest":
         params[1, :C1 * C0 * KK] *= 1e-6
         x[1, 0, c, H // 2, W // 2] = np.finfo(np.float32).max
@@ -99,6 +106,9 @@ def test_cnn_element_by_element(B, orc, shape, where):
     if where == "pixels":
         lost = np.isnan(want[1, :C1 * C0 * KK].reshape(C1, C0, KK))
         assert lost[:, c].all() and not lost[:, :c].any() and np.isfinite(want[1, C1 * C0 * KK:d]).all()
+    if where == "pooled":
+        lost = np.isnan(want[1, C1 * C0 * KK + C1:][:C2 * C1 * KK].reshape(C2, C1, KK))
+        assert lost[:, C1 - 1].any(1).all() and not lost[:, :C1 - 1].any() and np.isfinite(want[1, C1 * C0 * KK + C1 + C2 * C1 * KK:d]).all()
     np.testing.assert_allclose(loss, wloss, rtol=5e-6, atol=1e-6)
     for i in range(2):
         same_elements(got[i], want[i, :d], slices_of(desc), 3e-5)
@@ -128,11 +138,13 @@ def test_corner_pixel_reaches_its_own_taps_only(B, orc):
 
 
 @pytest.mark.parametrize("sign", [-1, 1])
-@pytest.mark.parametrize("dims,batch", [([65, 63, 70, 20], 66), ([129, 64, 33, 18], 65), ([7, 9, 21], 130)], ids=["65", "129", "7"])
+@pytest.mark.parametrize("dims,batch", [([65, 63, 70, 20], 66), ([129, 64, 33, 18], 65), ([7, 9, 21], 130),
+                                        ([65, 63, 70, 40], 266), ([129, 64, 33, 34], 257), ([7, 9, 37], 300)], ids=["65", "129", "7", "65-long", "129-long", "7-long"])
 def test_mlp_element_by_element(B, orc, dims, batch, sign):
     """An infinite input value of worker 1 under first-layer weights of one sign.  Negative: the layer is -inf, after ReLU zero,
     and of the gradients only that input's column is lost (0 * inf).  Positive: the activations are infinite and the layer above gets
-    inf - inf, so with a third layer its weight gradient is lost as well (0 * inf), with two layers everything is."""
+    inf - inf, so with a third layer its weight gradient is lost as well (0 * inf), with two layers everything is.  Batches of up to 255 take
+    the fp32 kernels and up to 32 classes the fused head, longer batches of odd widths and more classes the split products."""
     desc = {"kind": "mlp", "dims": dims, "loss": "xent"}
     d = inputs.param_count(desc)
     g = np.random.default_rng(21)
