@@ -492,7 +492,7 @@ int dbw_fc_forward_backward(dbw_ctx *c, dbw_fc_args &a, hipStream_t s)
             if (dims[l] % 128 == 0 && nf <= 4 && slices <= MAX_SPLITS) {      // split along k, inputs read once
                 float *part = act + 2 * per;
                 {
-                    dbw_timer tm(c, "fc32_forward", s);
+                    dbw_timer tm(c, subs == 4 ? "fc32_forward_4slices" : subs == 2 ? "fc32_forward_2slices" : "fc32_forward", s);
                     const dim3 grid(slices, N), block(fc32::THREADS);
                     const float *Wl = params + w_off[l];
                     auto go = [&](auto kern) {

@@ -7,7 +7,7 @@ from . import inputs
 
 
 def _head(B, n, h, c, with_input_gradient):
-    """The fused classifier head (last layer h -> c, c <= 16): logits, weight gradient and, below a
+    """The fused classifier head (last layer h -> c, c <= 32): logits, weight gradient and, below a
     hidden layer, the input gradient."""
     return n * 2 * B * h * c * (3 if with_input_gradient else 2)
 
@@ -15,7 +15,7 @@ def _head(B, n, h, c, with_input_gradient):
 def _mlp(cfg, dims):
     B, n = cfg.batch, cfg.n
     L = len(dims) - 1
-    last = L - 1 if dims[-1] <= 16 else L           # layers [0, last) go through the GEMM kernels
+    last = L - 1 if dims[-1] <= 32 else L           # layers [0, last) go through the GEMM kernels
     fwd = [2 * B * dims[l] * dims[l + 1] for l in range(last)]
     dgrad = [2 * B * dims[l] * dims[l + 1] for l in range(1, last)]
     table = {"fc_head_kernel": _head(B, n, dims[-2], dims[-1], L > 1)}

@@ -6,6 +6,7 @@ from test_gpu_grad_mlp import B, check_gradients  # noqa: F401  (B: the fixture)
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("dims,n", [([4096, 128, 10], 64), ([8192, 128, 3], 64)], ids=["two", "four"])
-def test_slices_of_a_workgroup(B, orc, dims, n):  # noqa: F811
-    check_gradients(B, orc, dims, 32, n, "xent", expect={"fc32_forward", "fc32_wgrad", "fc_head_kernel"})
+@pytest.mark.parametrize("dims,n,forward", [([4096, 128, 10], 9, "fc32_forward"), ([4096, 128, 10], 64, "fc32_forward_2slices"), ([8192, 128, 3], 64, "fc32_forward_4slices")],
+                         ids=["one", "two", "four"])
+def test_slices_of_a_workgroup(B, orc, dims, n, forward):  # noqa: F811
+    check_gradients(B, orc, dims, 32, n, "xent", expect={forward, "fc32_wgrad", "fc_head_kernel"})

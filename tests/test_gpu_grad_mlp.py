@@ -39,7 +39,7 @@ SHAPES = [
     ([64, 512, 64, 10], 32, 11, "xent"),
     ([1536, 384, 10], 32, 3, "mse"),
     # the last layer through the fused head in each of its chunk sizes, with ragged chunks, 16 classes,
-    # one class; and around its limits: 20 classes and a 2000-wide last layer take the GEMM kernels
+    # one class; and around its limits: a 2000-wide last layer takes the GEMM kernels, 20 classes two tiles of the head
     ([48, 24, 16], 70, 3, "xent"),
     ([30, 1], 5, 2, "xent"),
     ([203, 77, 9], 97, 40, "mse"),
@@ -162,7 +162,7 @@ def test_instruction_of_lone_data_gradients(B, orc):
 # Batches of at most 64 samples with widths that divide by 4: forward products and weight gradients straight from
 # global memory into matrix-instruction fragments.  One, two, three and four blocks of 16 samples; batches that
 # end inside a group of four samples; input widths with a partial chunk of 16 (100, 20) and below one chunk (12);
-# output widths with partial tiles of 32 columns and of 64 rows; 20 classes (no fused head: the logits go through
+# output widths with partial tiles of 32 columns and of 64 rows; 36 classes (no fused head: the logits go through
 # the same forward kernel without ReLU, and every bias gradient comes from the weight-gradient kernel).
 THIN_SHAPES = [
     ([784, 200, 10], 64, 32, "xent"),
@@ -170,6 +170,7 @@ THIN_SHAPES = [
     ([20, 12, 8], 3, 2, "mse"),
     ([256, 128, 10], 17, 5, "mse"),
     ([64, 40, 20], 33, 3, "xent"),
+    ([64, 40, 36], 33, 3, "xent"),
     ([48, 24, 16], 48, 3, "xent"),
 ]
 
