@@ -14,15 +14,18 @@ namespace global_access {
 
 typedef __attribute__((address_space(1))) char *bytes;
 
-__device__ __forceinline__ bytes uniform_base(const void *p)
+__device__ __forceinline__ uint64_t pinned(const void *p)
 {
     const uint64_t a = (uint64_t)p;
     const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a);
     const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
     uint64_t v = ((uint64_t)hi << 32) | lo;
     asm volatile("" : "+s"(v));
-    return (bytes)v;
+    return v;
 }
+__device__ __forceinline__ bytes uniform_base(const void *p) { return (bytes)pinned(p); }
+// A generic pointer, for kernels that were slower with global accesses or have not been tried with them.
+__device__ __forceinline__ const char *uniform_flat(const void *p) { return (const char *)pinned(p); }
 
 // V: float or a vector type
 template <class V>

@@ -25,6 +25,7 @@
 #include <algorithm>
 
 #include "dbw_internal.h"
+#include "global_access.h"
 #include "mix_split.h"
 
 namespace {
@@ -34,17 +35,9 @@ typedef __attribute__((address_space(1))) const void *global_cptr;
 typedef __attribute__((address_space(3))) void *lds_ptr;
 
 constexpr int DENSE_THREADS = 512;
-// The base of an access: scalar, plus a 32-bit lane offset (see global_access.h).  A generic pointer here, hence flat instructions: with
-// global ones the guarded gradient loads of the epilogue are slower, 20 workers x 4 M columns 238 us against 229 (elsewhere the same).
-__device__ __forceinline__ const char *uniform_base(const void *p)
-{
-    const uint64_t a = (uint64_t)p;
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a);
-    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
-    uint64_t v = ((uint64_t)hi << 32) | lo;
-    asm volatile("" : "+s"(v));
-    return (const char *)v;
-}
+// Flat accesses: with global ones the guarded gradient loads of the epilogue are slower, 20 workers x 4 M columns 238 us against 229 (elsewhere
+// the same).
+using global_access::uniform_flat;
 
 constexpr int NPAD = 32;                              // padded number of workers
 constexpr int KB = NPAD / 2;                          // k-steps of the 32x32x2 instruction
@@ -86,10 +79,10 @@ __global__ __launch_bounds__(DENSE_THREADS) void mix_dense_kernel(
             const float4 *xb = x + (int64_t)k0 * ld4 + tile * (TC / 4);        // uniform base
             float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
             if (FULL || (k < N && col4 < n_vec)) {
-                v = *(const float4 *)(uniform_base(xb) + fetch_lane_off);
+                v = *(const float4 *)(uniform_flat(xb) + fetch_lane_off);
                 if (ORDER == DBW_ORDER_ATC && HAS_G) {
                     const float4 gv =
-                        *(const float4 *)(uniform_base(g + (int64_t)k0 * ld4 + tile * (TC / 4)) + fetch_lane_off);
+                        *(const float4 *)(uniform_flat(g + (int64_t)k0 * ld4 + tile * (TC / 4)) + fetch_lane_off);
                     const float eta = lr.at(k);
                     v.x = fmaf(-eta, gv.x, v.x);
                     v.y = fmaf(-eta, gv.y, v.y);
@@ -119,7 +112,7 @@ __global__ __launch_bounds__(DENSE_THREADS) void mix_dense_kernel(
             const int q = w + 8 * i;                                             // uniform block id
             const int s = q / (KB / 4), kq = q % (KB / 4);
             const float4 *src = x + (int64_t)(8 * kq) * ld4 + tile * (TC / 4) + s * 8;   // uniform base
-            __builtin_amdgcn_global_load_lds((global_cptr)(uniform_base(src) + dma_lane_off),
+            __builtin_amdgcn_global_load_lds((global_cptr)(uniform_flat(src) + dma_lane_off),
                                              (lds_ptr)&lds[buf * TILE + q * 256], 16, 0, 0);
         }
     };
@@ -133,7 +126,7 @@ __global__ __launch_bounds__(DENSE_THREADS) void mix_dense_kernel(
             const int q = w + 8 * i;
             const int s = q / (KB / 4), kq = q % (KB / 4);
             const float4 *src = g + (int64_t)(8 * kq) * ld4 + tile * (TC / 4) + s * 8;   // uniform base
-            gstage[i] = *(const float4 *)(uniform_base(src) + dma_lane_off);
+            gstage[i] = *(const float4 *)(uniform_flat(src) + dma_lane_off);
         }
     };
     auto apply_g = [&](int buf) {
@@ -192,10 +185,10 @@ __global__ __launch_bounds__(DENSE_THREADS) void mix_dense_kernel(
                 const int row0 = 8 * (v / 4) + (v & 3);                           // uniform
                 const float *gb = gs + (int64_t)row0 * ld + col0;
                 if (FULL) {
-                    gv[v] = *(const float *)(uniform_base(gb) + epi_lane_off);
+                    gv[v] = *(const float *)(uniform_flat(gb) + epi_lane_off);
                 } else {
                     const bool ok = row0 + 4 * (lane >> 5) < N && col0 + (lane & 31) < dcols;
-                    gv[v] = ok ? *(const float *)(uniform_base(gb) + epi_lane_off) : 0.f;
+                    gv[v] = ok ? *(const float *)(uniform_flat(gb) + epi_lane_off) : 0.f;
                 }
             }
         }
@@ -239,7 +232,7 @@ __global__ __launch_bounds__(DENSE_THREADS) void mix_dense_kernel(
             }
             float *ob = out + (int64_t)row0 * ld + col0;
             if (FULL || (row0 + 4 * (lane >> 5) < N && col0 + (lane & 31) < dcols))
-                *(float *)(const_cast<char *>(uniform_base(ob)) + epi_lane_off) = r;
+                *(float *)(const_cast<char *>(uniform_flat(ob)) + epi_lane_off) = r;
         }
     }
 }

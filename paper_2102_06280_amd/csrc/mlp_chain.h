@@ -26,12 +26,13 @@
 #pragma once
 
 #include "fc_head.h"
+#include "global_access.h"
 
 namespace mlpchain {
 
 using fchead::f32x4;
 using fchead::pick;
-using fchead::uniform_base;
+using global_access::uniform_flat;
 constexpr int THREADS = fchead::THREADS, WAVES = THREADS / 64;
 constexpr int XCDS = 8;
 constexpr int MAX_L = 8;
@@ -87,7 +88,7 @@ __device__ __forceinline__ void load_fwd_unit(BRegs<CB> &b, const float *__restr
     const uint32_t lane_off = 4u * ((uint32_t)(lane & 15) * (uint32_t)K + 4u * (uint32_t)(lane >> 4));
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb) {
-        const char *base = uniform_base(Wg + (int64_t)(n0 + 16 * cb) * K + k0 + 16 * u);
+        const char *base = uniform_flat(Wg + (int64_t)(n0 + 16 * cb) * K + k0 + 16 * u);
         const f32x4 q = *(const f32x4 *)(base + lane_off);
 #pragma unroll
         for (int e = 0; e < 4; ++e) b.v[u][4 * cb + e] = q[e];
@@ -100,7 +101,7 @@ __device__ __forceinline__ void load_bwd_unit(BRegs<CB> &b, const float *__restr
     const uint32_t lane_off = 4u * (4u * (uint32_t)(lane >> 4) * (uint32_t)ldw + (uint32_t)CB * (uint32_t)(lane & 15));
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        const char *base = uniform_base(Wg + (int64_t)(k0 + 16 * u + j) * ldw + n0);
+        const char *base = uniform_flat(Wg + (int64_t)(k0 + 16 * u + j) * ldw + n0);
         const Vec<CB> q = *(const Vec<CB> *)(base + lane_off);
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) b.v[u][CB * j + cb] = q.v[cb];
@@ -187,7 +188,7 @@ __device__ __forceinline__ void product(f32x4 (&acc)[RB][CB], const float *in, i
             f32x4 bv[CB];
 #pragma unroll
             for (int cb = 0; cb < CB; ++cb)
-                bv[cb] = *(const f32x4 *)(uniform_base(Wg + (int64_t)(n0 + 16 * cb) * ldw + k) + 4u * ((uint32_t)l16 * (uint32_t)ldw + 4u * (uint32_t)lq));
+                bv[cb] = *(const f32x4 *)(uniform_flat(Wg + (int64_t)(n0 + 16 * cb) * ldw + k) + 4u * ((uint32_t)l16 * (uint32_t)ldw + 4u * (uint32_t)lq));
 #pragma unroll
             for (int e = 0; e < 4; ++e)
 #pragma unroll
@@ -199,7 +200,7 @@ __device__ __forceinline__ void product(f32x4 (&acc)[RB][CB], const float *in, i
             Vec<CB> bv[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                bv[j] = *(const Vec<CB> *)(uniform_base(Wg + (int64_t)(k + j) * ldw + n0) + 4u * (4u * (uint32_t)lq * (uint32_t)ldw + (uint32_t)CB * (uint32_t)l16));
+                bv[j] = *(const Vec<CB> *)(uniform_flat(Wg + (int64_t)(k + j) * ldw + n0) + 4u * (4u * (uint32_t)lq * (uint32_t)ldw + (uint32_t)CB * (uint32_t)l16));
 #pragma unroll
             for (int j = 0; j < 4; ++j)
 #pragma unroll
