@@ -28,8 +28,9 @@
 // a round of 64 x 64, 32 -> 16 on 16 x 16, 5 x 5 (the forward pass): 1075 / 981.  From seventeen rows on half of a block is used at least.
 //
 // Where a sum is not finite, a workgroup (a wave of first_kernel) multiplies a second time: the small partial products, what is not
-// finite of them dropped, then the large ones.  With one infinite weight of conv2 in every one of those 64 workers a round takes
-// 2.04 ms and with nothing but NaN 2.2 (1.65 with finite values).
+// finite of them dropped, then the large ones; in the weight gradient both of them dense, after a sparse first time.  With one infinite weight of
+// conv2 in every one of those 64 workers a round takes 2.29 ms, with nothing but NaN 2.07, with an infinite pixel in one sample of
+// each worker 2.17 (1.58 with finite values).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -685,8 +686,9 @@ inline bool wgrad_plan(const Shape &s, int workers, WgradPlan &p)
     p.nb = (s.Cin * s.KS + 31) / 32;
     p.units = p.mb * p.nb;
     // Eight wavefronts for few blocks: more of them hide the copies and splits, which a workgroup does between barriers, but
-    // their sums meet in LDS.  No number is the best everywhere (four / eight / twelve waves, us): 3 x 3, 32 -> 32 channels on
-    // 8 x 8 224, 188, 208, 16 -> 16 on 16 x 16 171, 158, 215.
+    // their sums meet in LDS.  No number is the best everywhere (four / eight / twelve waves, us): 64 workers x 64 samples, 3 x 3, 32 -> 32 channels
+    // on 8 x 8 72, 60, 69, 16 -> 16 on 16 x 16 73, 69, 91; 50 x 20, 3 x 3, 32 -> 24 on 14 x 14 49, 37, 34; 40 x 40, 5 x 5, 16 -> 32 on 14 x 14 62,
+    // 56, 68.
     p.kw = p.units >= 5 ? 1 : 8 / p.units;
     p.groups = (p.units + WGRAD_MAX_WAVES - 1) / WGRAD_MAX_WAVES;
     p.waves = (p.units + p.groups - 1) / p.groups * p.kw;
@@ -709,20 +711,20 @@ inline bool wgrad_plan(const Shape &s, int workers, WgradPlan &p)
     const size_t sums = p.kw > 1 ? sizeof(float) * 64 * 16 * s.KS * (p.waves / p.kw) : 0;
     if (p.lds < sums) p.lds = sums;
     // enough workgroups for the chip, and no more partial results than that needs: samples are given out by the ceiling, so that one turn
-    // holds all workgroups (by the floor, 16 x 50, 16 -> 32 channels on 14 x 14 59.4 us and 14.7 for the sums, 52.7 and 12.1 now; 50 x 20,
-    // 32 -> 24 on 14 x 14, 3 x 3: the round 343, 322).  A workgroup of up to eight samples: with
-    // four 5 x 5, 32 -> 64 on 16 x 16 takes 267 us and 46 for the sums (255 and 43), 3 x 3 1 -> 8 channels 45 (40); with sixteen
-    // the last turn of workgroups is the emptier (16 -> 32 on 14 x 14 288 against 258, 32 -> 16 on 16 x 16 511 against 342)
+    // holds all workgroups (by the floor, 16 x 50, 16 -> 32 channels on 14 x 14 46.0 us and 14.9 for the sums, 36.8 and 12.1 now; 50 x 20,
+    // 32 -> 24 on 14 x 14, 3 x 3: the round 242, 225).  A workgroup of up to eight samples: with four, 64 x 32, 5 x 5, 32 -> 64 on
+    // 16 x 16 takes 193 us and 43 for the sums (181 and 38), 64 x 64, 3 x 3, 32 -> 32 on 8 x 8 78 (60); with sixteen the sums of a workgroup are
+    // twice as long, and only some sizes are faster (64 x 64, 5 x 5, 32 -> 16 on 16 x 16 247 against 256, the others the same)
     p.sb = (int)(((int64_t)s.B * workers * p.groups + 256 * per_cu - 1) / (256 * per_cu));
     p.sb = p.sb < 1 ? 1 : (p.sb > 8 ? 8 : p.sb);
     p.splits = (s.B + p.sb - 1) / p.sb;
-    // The 5 x 5 kernel takes 145 registers, three wavefronts to a SIMD: of two workgroups of five to eight the second finds no place.
-    // Limited to 128 (some 24 bytes per lane go to scratch) both run: 16 x 50, 16 -> 32 on 14 x 14 53.8 -> 45.8 us, the round of 20 x 13,
-    // 32 -> 32 on 10 x 10 184 -> 173.  Where one workgroup is all that a compute unit gets, the limit only costs: 32 -> 64 on
-    // 16 x 16 248 -> 258, 16 x 16, 8 -> 16 on 12 x 12 14.1 -> 14.7.  (Of nine to twelve wavefronts the second workgroup finds no place either
-    // way, and the limit changes nothing: 16 x 32, 20 -> 96 on 8 x 8 57.3 us with it and 58.5 without, 16 x 64, 32 -> 64 on 6 x 6
-    // 71.5 and 72.7.  Their samples given out as for one workgroup would take 48.6 and 62.7, but the sums of a workgroup would be twice as
-    // long and up to 15 % less exact.)
+    // The 5 x 5 kernel takes 161 registers, three wavefronts to a SIMD: of two workgroups of five to eight the second finds no place.
+    // Limited to 128 (44 bytes per lane go to scratch) both run: 16 x 50, 16 -> 32 on 14 x 14 44.0 -> 35.5 us, 20 x 13, 32 -> 32 on 10 x 10
+    // 35.6 -> 26.2, 64 x 64, 8 -> 32 on 10 x 10 71.2 -> 53.2, 32 x 32, 16 -> 64 on 12 x 12 59.8 -> 51.2.  Where one workgroup is all that a compute
+    // unit gets, the limit changes little: 64 x 32, 32 -> 64 on 16 x 16 179 and 177 (the round 1556 either way), 16 x 16, 8 -> 16 on 12 x 12 13.7
+    // and 14.2.  (Of nine to twelve wavefronts the second workgroup finds no place either way: 16 x 32, 20 -> 96 on 8 x 8 48.8 us with it and
+    // without, 16 x 64, 32 -> 64 on 6 x 6 56.9 and 57.5.  Their samples given out as for one workgroup were faster with the dense instruction, 48.6
+    // against 57.3 and 62.7 against 71.5, but the sums of a workgroup twice as long and up to 15 % less exact.)
     p.paired = per_cu == 2 && p.waves > 4 && (int64_t)p.splits * workers * p.groups > 256;
     return true;
 }
