@@ -14,7 +14,7 @@
 //   D: d[v] = D[m = 4 * (l / 16) + v][n = l % 16].
 //
 // More than 16 classes used to take the forward GEMM, softmax_loss_kernel and the backward GEMM of the layer: 617-301-75-26 on
-// 20 workers x 101 samples 82 us a round, here 67; 256-25 on 6 x 1 024 39 and 26, 784-500-30 on 16 x 32 73 and 47.  More than 32 still do.
+// 20 workers x 101 samples 82 us a round, here 67 to 72, as the card has it; 256-25 on 6 x 1 024 39 and 26, 784-500-30 on 16 x 32 73 and 47.  More than 32 still do.
 //
 // Sums are short, started from zero and added to one another, so that more samples to a chunk or more classes round no more than smaller chunks
 // or the GEMM kernels did.  Error of dW and db against 64 bits in 1e-7, smaller chunks or the GEMM kernels / one sum after the other / here:
