@@ -33,6 +33,7 @@
 #include <stdint.h>
 
 #include "fc_head.h"
+#include "mlp_thin_plan.h"
 #include "mlp_wgrad.h"
 
 namespace mlpthin {
@@ -40,8 +41,7 @@ namespace mlpthin {
 using fchead::f32x4;
 using fchead::pick;
 constexpr int XCDS = 8;
-constexpr int FWD_WAVES = 8, FWD_THREADS = 64 * FWD_WAVES;
-constexpr int MAX_B = 255;
+constexpr int FWD_THREADS = 64 * FWD_WAVES;
 
 struct FwdArgs {
     int B, K, N, workers, relu;          // samples, inputs (four or more) and outputs
